@@ -123,10 +123,6 @@ static int calibrate_after_stats(const void* X, tdq_dtype dt, int32_t B, int32_t
   unsigned* hist = reinterpret_cast<unsigned*>(ws + wl.hist);
   const Scalars sc = make_scalars(p);
 
-  void* part = ws + wl.part;
-  if (launch_assign(r, mean, m2, B, T, C, G, group_id, part, img_flag, status, st) != hipSuccess)
-    return TDQ_ERR_HIP;
-
   // One rank select per rank wanted of every set: first the base radius Q_p(|x|) when a
   // percentile is asked for (Eq. DSTG_clip), then Q_zr(|x|) with the projection.
   // binary16 input: one sweep resolves the rank of (nearly) every set exactly, and the
@@ -138,12 +134,17 @@ static int calibrate_after_stats(const void* X, tdq_dtype dt, int32_t B, int32_t
   Bracket* br = reinterpret_cast<Bracket*>(ws + wl.br);
   unsigned* bhist = reinterpret_cast<unsigned*>(ws + wl.bhist);
   const bool two_passes = sc.base_pct > 0.0;
+  void* part = ws + wl.part;
+  if (!single_sweep || exact_only) {     // (the single sweep's own first kernel assigns the sets)
+    if (launch_assign(r, mean, m2, B, T, C, G, group_id, part, img_flag, status, st) != hipSuccess)
+      return TDQ_ERR_HIP;
+  }
   for (int pass = two_passes ? kPassBase : kPassZr; pass >= kPassZr; --pass) {
     const bool keep_base = two_passes && pass == kPassZr;
     if (single_sweep) {
       if (!exact_only) {
-        if (launch_bracket(X, B, T, C, ld_x, G, W, group_id, part, sc, pass, keep_base, grp, br,
-                           bhist, st) != hipSuccess)
+        if (launch_sets(X, B, T, C, ld_x, G, W, r, mean, m2, group_id, sc, pass, keep_base, grp, br,
+                        bhist, img_flag, status, st) != hipSuccess)
           return TDQ_ERR_HIP;
         if (launch_bracket_hist(X, B, T, C, ld_x, G, W, group_id, br, bhist, st) != hipSuccess)
           return TDQ_ERR_HIP;

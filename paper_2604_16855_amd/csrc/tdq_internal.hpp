@@ -100,8 +100,8 @@ hipError_t launch_token_stats(const void* X, tdq_dtype dt, int M, int C, long lo
                               float* r, double* mean, double* m2, hipStream_t st);
 // Token-set assignment.  An image is shared by assign_split(T) workgroups, each of
 // which leaves one partial record per set in `part`; the records are merged into
-// GroupWork either by launch_finalize_groups or, for binary16 input, by the first
-// kernel of the single-sweep rank select (launch_bracket).
+// GroupWork by launch_finalize_groups.  (The single-sweep rank select of binary16 input
+// assigns the sets in its own first kernel, launch_sets.)
 constexpr int kAssignSplitMax = 8;
 int assign_split(int T);
 size_t assign_partial_bytes(int B, int G);
@@ -122,10 +122,10 @@ hipError_t launch_select(unsigned* hist_level, int B, int G, int shift, int bits
                          float* scale, tdq_group_stats* stats, const unsigned* img_flag,
                          unsigned* status, int pass, hipStream_t st);
 // single-sweep rank select for binary16 input
-hipError_t launch_bracket(const void* X, int B, int T, int C, long long ld, int G, int W,
-                          const int* gid, const void* part, const Scalars& sc, int pass,
-                          bool keep_base, GroupWork* grp, Bracket* br, unsigned* bhist,
-                          hipStream_t st);
+hipError_t launch_sets(const void* X, int B, int T, int C, long long ld, int G, int W, const float* r,
+                       const double* mean, const double* m2, int* gid, const Scalars& sc, int pass,
+                       bool keep_base, GroupWork* grp, Bracket* br, unsigned* bhist,
+                       unsigned* img_flag, unsigned* status, hipStream_t st);
 hipError_t launch_bracket_hist(const void* X, int B, int T, int C, long long ld, int G, int W,
                                const int* gid, Bracket* br, unsigned* bhist, hipStream_t st);
 hipError_t launch_bracket_finish(const void* X, int B, int T, int C, long long ld, int G, int W,

@@ -6,12 +6,12 @@
 // histograms needs two sweeps of X for that many bits.  Here a small sample of
 // every set first says where to look:
 //
-//   k_bracket         one workgroup per set reads up to 16 Ki sampled elements and
-//                     finds, in an LDS histogram of their top key bits, the sample
-//                     order statistic whose sample rank corresponds to k.  The key
-//                     interval [lo, lo + W) centred on it (W = as many one-key bins as
-//                     the LDS histogram has per set) holds the true answer unless the
-//                     sample is off by more than W/2 keys.
+//   k_sets            one workgroup per set finds the set's tokens and moments, reads up
+//                     to 8 Ki sampled elements and finds, in an LDS histogram of their top
+//                     key bits, the sample order statistic whose sample rank corresponds
+//                     to k.  The key interval [lo, lo + W) centred on it (W = as many
+//                     one-key bins as the sweep's LDS histogram has per set) holds the true
+//                     answer unless the sample is off by more than W/2 keys.
 //   k_bracket_hist    one sweep of X: per set, the number of keys below lo and an LDS
 //                     histogram, one bin per key, of the keys inside the interval.
 //   k_bracket_finish  one workgroup per set: if below < k <= below + inside, the
@@ -27,68 +27,145 @@
 
 namespace tdq {
 
-constexpr int kSampleThreads = 256;                             // one wavefront per SIMD
-constexpr int kSampleWaves = kSampleThreads / 64;
-constexpr int kSamplePerThread = 64;
 constexpr int kRunLen = 32;                                     // channels per run (64 bytes)
-constexpr int kSampleMax = kSampleThreads * kSamplePerThread;   // 16 Ki keys per set
-constexpr int kSampleRuns = kSampleMax / kRunLen;               // 512 runs
-constexpr int kSampleTokens = kSampleRuns;                      // at most one run per token
 constexpr int kSampleBits = 10;                                 // key bits the sample histogram resolves
 constexpr int kSweepThreads = 1024;
+constexpr int kIdRounds = 16;                                   // range keys a thread of k_sets holds
 
 // ---------------------------------------------------------------------------
-// k_bracket
+// k_sets: one workgroup of NT threads per (image, token set).
+//   1. the image's smallest and largest range key -> the key interval that belongs to this
+//      set: gid = (key - lo) G / width is j exactly for ceil(j width / G) <= key - lo <
+//      ceil((j + 1) width / G), so a token is recognised with two compares and no division;
+//   2. the set's tokens (ids stored, counted, ranked) and their merged moments, summed
+//      about the mean of the set's first token (identical tokens add exact zeros);
+//   3. the sample of the set and the key interval that its order statistic says holds the
+//      k-th smallest |x|.
+// Bound by its chain of dependent steps (three trips to memory, seven barriers), not by
+// traffic: every workgroup reads the image's T range keys itself, which is cheaper than a
+// kernel boundary, and everything per token sits in registers when T <= 16 NT.  Ranks are
+// counted wavefront by wavefront (any numbering of the set's tokens serves the sample), so
+// the wavefronts exchange one count each.  SM = most sampled elements: the rank error of 8 Ki
+// is 0.45 % of the set's mass, about 40 keys at 1024 keys per octave, against a half-width of
+// W / 2 >= 256 keys; with fewer bins per set (more than 32 sets) 16 Ki are drawn.
+// Measured, calibration of one call (two kernels for this before: assignment, then sample):
+// [1, 7744, 64] 46.3 -> 30.9 us, [8, 121, 512] 30.7 -> 26.0, [32, 4096, 1024] 118.7 -> 108.3;
+// with 16 Ki samples 31.7 / 26.9 / 111.0.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kSampleThreads) void k_bracket(
+template <int NT, int SM>
+__global__ __launch_bounds__(NT) void k_sets(
     const u16* __restrict__ X, long long ld, int T, int C, int G, int W, int vec,
-    const int* __restrict__ gid, const SetAcc* __restrict__ part, int S, Scalars sc, int pass,
-    int keep_base, GroupWork* __restrict__ grp, Bracket* __restrict__ br,
-    u32* __restrict__ bhist) {
+    const float* __restrict__ r, const double* __restrict__ mean, const double* __restrict__ m2,
+    int* __restrict__ gid, Scalars sc, int pass, int keep_base, GroupWork* __restrict__ grp,
+    Bracket* __restrict__ br, u32* __restrict__ bhist, u32* __restrict__ img_flag,
+    u32* __restrict__ status) {
+  constexpr int NW = NT / 64;
+  constexpr int kSampleRuns = SM / kRunLen;
+  constexpr int kSampleTokens = kSampleRuns;         // at most one run per token
   __shared__ int sel[kSampleTokens];                 // drawn token of every stratum
   __shared__ long long run_base[kSampleRuns];        // element offset of every run's first channel
   __shared__ int run_len[kSampleRuns];               // channels of the run (<= kRunLen)
   __shared__ u32 shist[1 << kSampleBits];            // sample histogram over the top key bits
-  __shared__ u32 wtot[kSampleWaves];
-  __shared__ u32 s_bin;
-  const int idx = blockIdx.x;
-  const int b = idx / G, j = idx - b * G;
+  __shared__ u32 s_min[NW], s_max[NW], wtot[NW], stot[NW], s_cmax[NW];
+  __shared__ double s_s1[NW], s_s2[NW];
+  __shared__ int s_first;
+  const int j = blockIdx.x, b = blockIdx.y, idx = b * G + j;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // the set ids of the first batch of tokens are on their way while the records are merged
-  constexpr int kRankBatch = 16;
-  const int* gb = gid + (long long)b * T;
-  int gv[kRankBatch];
+  const float* rb = r + (long long)b * T;
+  const double* meanb = mean + (long long)b * T;
+  const double* m2b = m2 + (long long)b * T;
+  int* gb = gid + (long long)b * T;
+  constexpr u32 kDead = 0xFFFFFFFFu;                 // no range key reaches it
+  const bool one_batch = T <= kIdRounds * NT;
+  u32 kv[kIdRounds];
+  auto load_keys = [&](int t0) {
 #pragma unroll
-  for (int u = 0; u < kRankBatch; ++u) {
-    const int t = u * kSampleThreads + tid;
-    gv[u] = t < T ? gb[t] : -1;
-  }
-  // every thread merges the assignment's partial records of this set (same loads, same
-  // order, same result); one of them stores the working record for the later kernels
-  GroupWork w = merge_partials(part, b, j, S, G, C, sc, pass);
-  if (keep_base) w.c_base = grp[idx].c_base;     // left by the base-radius pass (only this
-                                                 // field is read; thread 0 rewrites it unchanged)
-  if (tid == 0) grp[idx] = w;
+    for (int u = 0; u < kIdRounds; ++u) {
+      const int t = t0 + u * NT + tid;
+      kv[u] = t < T ? __float_as_uint(rb[t]) : kDead;
+    }
+  };
 
-  // the sweep adds into this set's histogram and counter: clear them here
-  for (int i = tid; i < W; i += kSampleThreads) bhist[(size_t)idx * W + i] = 0;
-  if (w.tokens == 0) {
+  // ---- 1: key range of the image, key interval of the set
+  load_keys(0);
+  for (int i = tid; i < (1 << kSampleBits); i += NT) shist[i] = 0;
+  u32 kinv = 0, kmax = 0;                            // largest ~key, largest key
+  for (int t0 = 0;;) {
+#pragma unroll
+    for (int u = 0; u < kIdRounds; ++u) {
+      const u32 k = kv[u];
+      kinv = ~k > kinv ? ~k : kinv;                  // ~kDead is 0
+      kmax = k != kDead && k > kmax ? k : kmax;
+    }
+    t0 += kIdRounds * NT;
+    if (t0 >= T) break;
+    load_keys(t0);
+  }
+  kinv = group_max_u32<64>(kinv);
+  kmax = group_max_u32<64>(kmax);
+  if (lane == 63) { s_min[wave] = ~kinv; s_max[wave] = kmax; }
+  __syncthreads();
+  u32 lo = s_min[0], hi = s_max[0];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) {
+    lo = s_min[w] < lo ? s_min[w] : lo;
+    hi = s_max[w] > hi ? s_max[w] : hi;
+  }
+  {
+    const u32 span = (u32)kOctaveFloor << 23;
+    const u32 floor_key = hi > span ? hi - span : 0u;
+    lo = lo > floor_key ? lo : floor_key;
+  }
+  if (tid == 0 && j == 0) {
+    img_flag[b] = hi >= 0x7F800000u ? TDQ_DEV_NONFINITE : 0u;
+    if (b == 0) {                         // counts of sets the sampled interval misses
+      status[1 + pass] = 0u;
+      if (!keep_base) status[1 + (pass ^ 1)] = 0u;
+    }
+  }
+  // ceil(j width / G) = j q + ceil(j rem / G) with width = q G + rem; everything fits 32 bits
+  const u32 width = hi - lo + 1u, wq = width / (u32)G, wr = width - wq * (u32)G;
+  const u32 start = j == 0 ? 0u : lo + (u32)j * wq + ((u32)j * wr + (u32)G - 1u) / (u32)G;
+  const u32 end = j == G - 1 ? hi + 1u : lo + (u32)(j + 1) * wq + ((u32)(j + 1) * wr + (u32)G - 1u) / (u32)G;
+  auto in_set = [&](u32 k) { return k >= start && k < end; };
+
+  // ---- 2: the set's tokens
+  u32 wcount = 0;
+  for (int t0 = 0; t0 < T; t0 += kIdRounds * NT) {
+    if (!one_batch) load_keys(t0);
+#pragma unroll
+    for (int u = 0; u < kIdRounds; ++u) wcount += (u32)__popcll(__ballot(in_set(kv[u])));
+  }
+  if (lane == 0) wtot[wave] = wcount;
+  __syncthreads();
+  u32 tokens_u = 0, running = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    const u32 v = wtot[w];
+    running += w < wave ? v : 0u;
+    tokens_u += v;
+  }
+  if (tokens_u == 0) {
     if (tid == 0) {
+      GroupWork w;
+      w.n = 0; w.k_rem = 0; w.prefix = 0; w.tokens = 0; w.c_base = 0.f; w.sigma = 0.f;
+      grp[idx] = w;
       Bracket e;
       e.lo = 0; e.width = 0; e.below = 0; e.pad = 0;
       br[idx] = e;
     }
     return;
   }
+  // the sweep adds into this set's histogram: clear it here
+  for (int i = tid; i < W; i += NT) bhist[(size_t)idx * W + i] = 0;
 
-  // Sample geometry.  The set's tokens, in index order, are cut into strata of
-  // `stride` tokens (at most kSampleTokens strata) and one token is drawn from each
-  // at a hashed position: a regular stride would alias with any period the token
-  // sequence has (image rows).  Of each drawn token `rpt` runs of kRunLen consecutive
-  // channels are read, the first at a hashed offset, so that all channels are
-  // represented; a row that fits is read whole.
-  const int tokens = (int)w.tokens;
+  // Sample geometry.  The set's tokens are cut into strata of `stride` tokens (at most
+  // kSampleTokens strata) and one token is drawn from each at a hashed position: a regular
+  // stride would alias with any period the token sequence has (image rows).  Of each drawn
+  // token `rpt` runs of kRunLen consecutive channels are read, the first at a hashed offset,
+  // so that all channels are represented; a row that fits is read whole.
+  const int tokens = (int)tokens_u;
   const int stride = (tokens + kSampleTokens - 1) / kSampleTokens;
   const int n_sel = (tokens + stride - 1) / stride;         // <= kSampleTokens
   const int row_runs = (C + kRunLen - 1) / kRunLen;
@@ -96,57 +173,46 @@ __global__ __launch_bounds__(kSampleThreads) void k_bracket(
   rpt = rpt < row_runs ? rpt : row_runs;
   const int cw = rpt == row_runs ? C : rpt * kRunLen;       // channels read per drawn token
   const int n_runs = n_sel * rpt;                           // <= kSampleRuns
-  const long long m = (long long)n_sel * cw;                // sample size, <= kSampleMax
+  const long long m = (long long)n_sel * cw;                // sample size, <= SM
 
-  // Rank of every token inside its set -> the drawn tokens' indices.  Tokens are taken
-  // kRankBatch rounds of kSampleThreads at a time: all set ids of a batch are loaded
-  // together, every wavefront counts its matches of every round (ballot), the counts meet
-  // in LDS once, and every thread turns them into the rank offsets of its own wavefront --
-  // two barriers per batch instead of two per round.
-  __shared__ u32 wcnt[kRankBatch * kSampleWaves];
-  u32 base = 0;
-  for (int t0 = 0; t0 < T; t0 += kRankBatch * kSampleThreads) {
-    if (t0 > 0) {
+  for (int t0 = 0; t0 < T; t0 += kIdRounds * NT) {
+    if (!one_batch) load_keys(t0);
 #pragma unroll
-      for (int u = 0; u < kRankBatch; ++u) {
-        const int t = t0 + u * kSampleThreads + tid;
-        gv[u] = t < T ? gb[t] : -1;
+    for (int u = 0; u < kIdRounds; ++u) {
+      const bool mine = in_set(kv[u]);
+      const unsigned long long mask = __ballot(mine);
+      if (mask == 0) continue;                              // uniform over the wavefront
+      if (mine) {
+        const int t = t0 + u * NT + tid;
+        const u32 rank = running + (u32)__popcll(mask & ((1ull << lane) - 1ull));
+        gb[t] = j;
+        if (rank == 0) s_first = t;
+        if (stride == 1) {
+          sel[rank] = t;
+        } else {
+          const u32 stratum = rank / (u32)stride, first = stratum * (u32)stride;
+          const u32 len = (u32)tokens - first < (u32)stride ? (u32)tokens - first : (u32)stride;
+          const u32 pick =
+              first + (((stratum + 1u) * 2246822519u + (u32)idx * 3266489917u) >> 12) % len;
+          if (rank == pick) sel[stratum] = t;
+        }
       }
+      running += (u32)__popcll(mask);
     }
-    u32 within[kRankBatch];
-#pragma unroll
-    for (int u = 0; u < kRankBatch; ++u) {
-      const unsigned long long mask = __ballot(gv[u] == j);
-      within[u] = (u32)__popcll(mask & ((1ull << lane) - 1ull));
-      if (lane == 0) wcnt[u * kSampleWaves + wave] = (u32)__popcll(mask);
-    }
-    __syncthreads();
-    u32 run = base;
-#pragma unroll
-    for (int u = 0; u < kRankBatch; ++u) {
-      u32 mine = 0;
-#pragma unroll
-      for (int w2 = 0; w2 < kSampleWaves; ++w2) {
-        const u32 v = wcnt[u * kSampleWaves + w2];
-        mine = w2 == wave ? run : mine;
-        run += v;
-      }
-      if (gv[u] == j) {
-        const int t = t0 + u * kSampleThreads + tid;
-        const u32 rank = mine + within[u];
-        const u32 stratum = rank / (u32)stride, first = stratum * (u32)stride;
-        const u32 len = (u32)tokens - first < (u32)stride ? (u32)tokens - first : (u32)stride;
-        const u32 pick =
-            first + (((stratum + 1u) * 2246822519u + (u32)idx * 3266489917u) >> 12) % len;
-        if (rank == pick) sel[stratum] = t;
-      }
-    }
-    base = run;
-    __syncthreads();                     // wcnt is rewritten by the next batch; sel is read below
   }
+  __syncthreads();
+
+  // Moments of the set about the mean of its first token (zero if that is not finite: the
+  // image's results are then undefined anyway and its flag is raised).  The loads are in
+  // flight while the run table is made.
+  const int first_token = s_first;
+  double piv = meanb[first_token];
+  const double cn = (double)C;
+  double a1 = 0.0, a2 = 0.0;
+  u32 cmax = 0;
   // table of runs, so that the load loop below has no division in it
-  for (int q = tid; q < kSampleRuns; q += kSampleThreads) {
-    long long rb = 0;
+  for (int q = tid; q < kSampleRuns; q += NT) {
+    long long rbase = 0;
     int rl = 0;
     if (q < n_runs) {
       const int slot = q / rpt, run = q - slot * rpt;
@@ -155,35 +221,69 @@ __global__ __launch_bounds__(kSampleThreads) void k_bracket(
       // then multiples of 8 channels)
       const u32 off = vec ? (((u32)t * 2654435761u >> 8) % (u32)((C - cw) / 8 + 1)) * 8u
                           : ((u32)t * 2654435761u >> 8) % (u32)(C - cw + 1);
-      rb = ((long long)b * T + t) * ld + off + run * kRunLen;
+      rbase = ((long long)b * T + t) * ld + off + run * kRunLen;
       rl = cw - run * kRunLen;
       rl = rl < kRunLen ? rl : kRunLen;
     } else {
-      rb = ((long long)b * T + sel[0]) * ld;          // a valid address; the key is discarded
+      rbase = ((long long)b * T + sel[0]) * ld;       // a valid address; the key is discarded
     }
-    run_base[q] = rb;
+    run_base[q] = rbase;
     run_len[q] = rl;
   }
+  piv = (piv - piv == 0.0) ? piv : 0.0;
+  for (int t0 = 0; t0 < T; t0 += kIdRounds * NT) {
+    if (!one_batch) load_keys(t0);
+    // half of the rounds at a time, their loads issued together (a token of another set
+    // reads the first token's entry, which is not added)
+#pragma unroll
+    for (int h = 0; h < kIdRounds; h += kIdRounds / 2) {
+      double mv[kIdRounds / 2], qv[kIdRounds / 2];
+#pragma unroll
+      for (int u = 0; u < kIdRounds / 2; ++u) {
+        const bool mine = in_set(kv[h + u]);
+        mv[u] = piv;
+        qv[u] = 0.0;
+        if (__ballot(mine)) {                         // uniform over the wavefront
+          const int t = mine ? t0 + (h + u) * NT + tid : first_token;
+          mv[u] = meanb[t];
+          qv[u] = m2b[t];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < kIdRounds / 2; ++u) {
+        const u32 k = kv[h + u];
+        const bool mine = in_set(k);
+        const double dm = mv[u] - piv;
+        const double d1 = cn * dm;
+        a1 += mine ? d1 : 0.0;
+        a2 += mine ? qv[u] + d1 * dm : 0.0;
+        cmax = mine && k > cmax ? k : cmax;
+      }
+    }
+  }
+  a1 = group_sum_f64<64>(a1);                         // totals in lane 63
+  a2 = group_sum_f64<64>(a2);
+  cmax = group_max_u32<64>(cmax);
+  if (lane == 63) { s_s1[wave] = a1; s_s2[wave] = a2; s_cmax[wave] = cmax; }
   __syncthreads();
 
-  // The sample.  Every live key adds one to an LDS histogram of its top kSampleBits bits.
-  // Loads are issued unconditionally (from a clamped, valid address) so that they overlap.
-  for (int i = tid; i < (1 << kSampleBits); i += kSampleThreads) shist[i] = 0;
+  // ---- 3: the sample.  Every live key adds one to an LDS histogram of its top kSampleBits
+  // bits.  Loads are issued unconditionally (from a clamped, valid address) so that they
+  // overlap.
   if (vec) {
-    // 16-byte pieces of 8 channels: piece p = 256 e + tid is part p % 4 of run p / 4, so a
+    // 16-byte pieces of 8 channels: piece p = NT e + tid is part p % 4 of run p / 4, so a
     // wavefront's load instruction fetches 16 whole runs of 64 bytes; a run's pieces are
     // all live or (runs past the end of the table) all dead.
-    constexpr int kPieces = kSampleMax / 8 / kSampleThreads;      // 8 per thread
+    constexpr int kPieces = SM / 8 / NT;
     uint4 v[kPieces];
     bool live[kPieces];
 #pragma unroll
     for (int e = 0; e < kPieces; ++e) {
-      const int p = e * kSampleThreads + tid;
+      const int p = e * NT + tid;
       const int q = p >> 2, part = p & 3;
       live[e] = part * 8 < run_len[q];
       v[e] = *reinterpret_cast<const uint4*>(X + run_base[q] + (live[e] ? part * 8 : 0));
     }
-    __syncthreads();
 #pragma unroll
     for (int e = 0; e < kPieces; ++e) {
       if (live[e]) {
@@ -196,30 +296,54 @@ __global__ __launch_bounds__(kSampleThreads) void k_bracket(
       }
     }
   } else {
-    // element e of lane l of wavefront w is channel l % 32 of run 8 e + 2 w + l / 32
-    u32 key[kSamplePerThread];
+    // element e of lane l of wavefront w is channel l % 32 of run 2 NW e + 2 w + l / 32
+    constexpr int kPerThread = SM / NT;
+    u32 key[kPerThread];
     const int half = lane >> 5, cl = lane & 31;
 #pragma unroll
-    for (int e = 0; e < kSamplePerThread; ++e) {
-      const int q = e * (2 * kSampleWaves) + 2 * wave + half;
+    for (int e = 0; e < kPerThread; ++e) {
+      const int q = e * (2 * NW) + 2 * wave + half;
       const int rl = run_len[q];
       const int ch = cl < rl ? cl : (rl > 0 ? rl - 1 : 0);
       const u32 x = X[run_base[q] + ch];
       key[e] = cl < rl ? (x & 0x7FFFu) : 0xFFFFu;
     }
-    __syncthreads();
 #pragma unroll
-    for (int e = 0; e < kSamplePerThread; ++e)
+    for (int e = 0; e < kPerThread; ++e)
       if (key[e] != 0xFFFFu) atomicAdd(&shist[key[e] >> (15 - kSampleBits)], 1u);
+  }
+
+  // the set's working record: n, base radius, sigma, rank of this pass (binary64)
+  GroupWork w;
+  w.tokens = tokens_u;
+  w.n = (long long)tokens * (long long)C;
+  w.prefix = 0;
+  const double n = (double)w.n;
+  w.k_rem = (long long)ceil((pass == kPassBase ? sc.base_pct : sc.zr) * n);
+  w.k_rem = w.k_rem < 1 ? 1 : (w.k_rem > w.n ? w.n : w.k_rem);
+  if (tid == 0) {
+    double S1 = s_s1[0], S2 = s_s2[0];
+    u32 km = s_cmax[0];
+    for (int i = 1; i < NW; ++i) {
+      S1 += s_s1[i];
+      S2 += s_s2[i];
+      km = s_cmax[i] > km ? s_cmax[i] : km;
+    }
+    const double mu = S1 / n;
+    double var = S2 / n - mu * mu;
+    var = var > 0.0 ? var : 0.0;
+    w.sigma = (float)(sqrt(var) + sc.eps_std);
+    // (the base-radius pass left its radius in the record)
+    w.c_base = keep_base ? grp[idx].c_base : __uint_as_float(km);
+    grp[idx] = w;
   }
   __syncthreads();
 
   // Sample rank that corresponds to rank k of the set, and the histogram bin that
   // holds that order statistic (the low key bits do not matter to the interval).
-  const double n = (double)w.n, kd = (double)w.k_rem;
-  long long r = (long long)(kd / n * (double)m + 0.5);
-  r = r < 1 ? 1 : (r > m ? m : r);
-  constexpr int kBinsPerThread = (1 << kSampleBits) / kSampleThreads;
+  long long rk = (long long)((double)w.k_rem / n * (double)m + 0.5);
+  rk = rk < 1 ? 1 : (rk > m ? m : rk);
+  constexpr int kBinsPerThread = (1 << kSampleBits) / NT;
   u32 c[kBinsPerThread], mine = 0;
 #pragma unroll
   for (int i = 0; i < kBinsPerThread; ++i) {
@@ -232,25 +356,18 @@ __global__ __launch_bounds__(kSampleThreads) void k_bracket(
     const u32 o = (u32)__shfl_up((int)incl, d, 64);
     if (lane >= d) incl += o;
   }
-  if (lane == 63) wtot[wave] = incl;
+  if (lane == 63) stot[wave] = incl;
   __syncthreads();
-  u32 before = 0;
 #pragma unroll
-  for (int w2 = 0; w2 < kSampleWaves; ++w2) before += w2 < wave ? wtot[w2] : 0u;
-  incl += before;
-  if ((long long)(incl - mine) < r && r <= (long long)incl) {     // exactly one thread
+  for (int w2 = 0; w2 < NW; ++w2) incl += w2 < wave ? stot[w2] : 0u;
+  if ((long long)(incl - mine) < rk && rk <= (long long)incl) {     // exactly one thread
     u32 cum = incl - mine;
     int i = 0;
     for (; i < kBinsPerThread - 1; ++i) {
-      if ((long long)(cum + c[i]) >= r) break;
+      if ((long long)(cum + c[i]) >= rk) break;
       cum += c[i];
     }
-    s_bin = (u32)(tid * kBinsPerThread + i);
-  }
-  __syncthreads();
-  const u32 v = s_bin << (15 - kSampleBits);
-
-  if (tid == 0) {
+    const u32 v = (u32)(tid * kBinsPerThread + i) << (15 - kSampleBits);
     // v <= estimate < v + 2^(15 - kSampleBits): centre the interval on the middle
     const u32 mid = v + (1u << (14 - kSampleBits));
     Bracket e;
@@ -261,16 +378,30 @@ __global__ __launch_bounds__(kSampleThreads) void k_bracket(
   }
 }
 
-hipError_t launch_bracket(const void* X, int B, int T, int C, long long ld, int G, int W,
-                          const int* gid, const void* part, const Scalars& sc, int pass,
-                          bool keep_base, GroupWork* grp, Bracket* br, unsigned* bhist,
-                          hipStream_t st) {
+hipError_t launch_sets(const void* X, int B, int T, int C, long long ld, int G, int W, const float* r,
+                       const double* mean, const double* m2, int* gid, const Scalars& sc, int pass,
+                       bool keep_base, GroupWork* grp, Bracket* br, unsigned* bhist,
+                       unsigned* img_flag, unsigned* status, hipStream_t st) {
   // 16-byte sample loads need rows of whole, aligned 16-byte pieces
   const int vec = ((reinterpret_cast<uintptr_t>(X) & 15) == 0 && ld % 8 == 0 && C % 8 == 0) ? 1 : 0;
-  hipLaunchKernelGGL(k_bracket, dim3(B * G), dim3(kSampleThreads), 0, st,
-                     static_cast<const u16*>(X), ld, T, C, G, W, vec, gid,
-                     static_cast<const SetAcc*>(part), assign_split(T), sc, pass,
-                     keep_base ? 1 : 0, grp, br, bhist);
+#define TDQ_SETS_SM(NT, SM)                                                                        \
+  hipLaunchKernelGGL((k_sets<NT, SM>), dim3(G, B), dim3(NT), 0, st, static_cast<const u16*>(X), ld, \
+                     T, C, G, W, vec, r, mean, m2, gid, sc, pass, keep_base ? 1 : 0, grp, br, bhist, \
+                     img_flag, status)
+#define TDQ_SETS(NT)                                        \
+  do {                                                      \
+    if (W >= 512) TDQ_SETS_SM(NT, 8192); else TDQ_SETS_SM(NT, 16384); \
+  } while (0)
+  // as few threads as hold the image's range keys in registers: [32, 4096, 1024] calibrates
+  // in 111 / 117 / 145 us with 256 / 512 / 1024 threads per set
+  if (T <= kIdRounds * 256)
+    TDQ_SETS(256);
+  else if (T <= kIdRounds * 512)
+    TDQ_SETS(512);
+  else
+    TDQ_SETS(1024);
+#undef TDQ_SETS
+#undef TDQ_SETS_SM
   return hipGetLastError();
 }
 

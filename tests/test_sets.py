@@ -1,0 +1,55 @@
+"""Token sets as the rank select's first kernel forms them: a set is an interval of range keys
+instead of a quotient per token (CPU: the two rules agree), and sizes around the edges of that
+kernel -- one or several batches of tokens per workgroup, 256 / 512 / 1024 threads, sets of one
+token, whole-image sets, rows that do not allow 16-byte loads (GPU, against the oracle)."""
+import numpy as np
+import pytest
+
+from oracle import tdq_oracle as O
+from paper_2604_16855_amd import tdq
+
+
+def _interval_ids(key, lo, hi, G):
+    """gid by key intervals, in the 32-bit arithmetic of the kernel."""
+    width = hi - lo + 1
+    q, rem = divmod(width, G)
+    gid = np.full(key.shape, -1, dtype=np.int64)
+    for j in range(G):
+        start = 0 if j == 0 else lo + j * q + (j * rem + G - 1) // G
+        end = hi + 1 if j == G - 1 else lo + (j + 1) * q + ((j + 1) * rem + G - 1) // G
+        assert 0 <= start <= 1 << 31 and 0 <= end <= 1 << 31
+        gid[(key >= start) & (key < end)] = j
+    return gid
+
+
+@pytest.mark.parametrize("G", [1, 2, 3, 5, 7, 12, 16, 31, 32, 33, 64, 100, 255, 256])
+def test_key_intervals_are_the_quotient_rule(G):
+    rng = np.random.default_rng(G)
+    for span in (0, 1, 2, G - 1, G, G + 1, 1000, 1 << 23, 24 << 23, (1 << 31) - 2):
+        hi = int(rng.integers(span, (1 << 31) - 1))
+        lo = hi - span
+        key = np.concatenate([rng.integers(0, hi + 1, 4000), rng.integers(lo, hi + 1, 4000),
+                              [0, lo, hi, max(lo - 1, 0), min(lo + 1, hi)]])
+        edges = lo + (np.arange(1, G + 1) * (span + 1)) // G
+        key = np.concatenate([key] + [np.clip(edges + d, 0, hi) for d in (-1, 0, 1)]).astype(np.int64)
+        want = np.where(key <= lo, 0, (key - lo) * G // (hi - lo + 1))
+        assert np.array_equal(_interval_ids(key, lo, hi, G), want), (G, lo, hi)
+
+
+def _tokens(T, C, dtype, seed):
+    rng = np.random.Generator(np.random.PCG64(seed))
+    X = rng.laplace(0, 1, (2, T, C)) * rng.lognormal(0, 1.5, (2, T, 1))
+    X[1] = 0.75 if T % 2 else X[1] + 3.0            # one set holding a whole image / far from zero
+    return np.clip(X, -60000, 60000).astype(dtype)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("T,C,G", [(1, 8, 4), (255, 40, 12), (4096, 16, 32), (4097, 24, 32), (8191, 8, 16),
+                                   (8193, 9, 5), (16384, 8, 64), (16385, 16, 1), (40001, 8, 33)])
+def test_set_records_at_batch_edges(T, C, G):
+    import parity_util as U
+    X = _tokens(T, C, np.float16, 31 * T + C)
+    p = tdq.default_params(G)
+    U.assert_calibration_matches(U.gpu_calibrate(X, p), X, p)
+    p.base_pct = 0.99
+    U.assert_calibration_matches(U.gpu_calibrate(X, p, ld_pad=3), X, p)
