@@ -234,19 +234,6 @@ __global__ __launch_bounds__(256) void k_token_stats_wide(const T* __restrict__ 
   }
 }
 
-// Lanes per row of the statistics sweep: enough that a wavefront's load instruction
-// covers whole 128-byte lines (8 lanes), otherwise as few as leave every lane about 4
-// pieces, all loaded at once -- the reduction over the row's lanes costs as many vector
-// instructions as 2 pieces do, and with fewer pieces per lane it, not the memory system,
-// sets the pace (C = 1024: 47.3 / 45.5 / 60.4 us at 8 / 4 / 2 pieces per lane).
-static int stats_lanes_per_row(int C, int V) {
-  const int nvec = (C + V - 1) / V;
-  int L = 1;
-  while (L < nvec && L < 8) L <<= 1;
-  while (L < 64 && L * 4 < nvec) L <<= 1;
-  return L;
-}
-
 template <typename T>
 static hipError_t token_stats_t(const T* X, int M, int C, long long ld, float* r, double* mean,
                                 double* m2, hipStream_t st) {
@@ -257,7 +244,7 @@ static hipError_t token_stats_t(const T* X, int M, int C, long long ld, float* r
                        1.0 / (double)C, r, mean, m2);
     return hipGetLastError();
   }
-  const int L = stats_lanes_per_row(C, V);
+  const int L = sweep_lanes_per_row(C, V);
   const long long threads = (long long)M * L;
   const unsigned grid = (unsigned)((threads + 255) / 256);
 #define TDQ_TS(LL)                                                                       \

@@ -34,7 +34,7 @@ LevelPlan make_level_plan(tdq_dtype dt, int G) {
 }
 
 int bracket_bins(int G) {
-  int w = 2048;
+  int w = kBracketMaxBins;
   while (w >= kBracketMinBins && (long long)G * w > kBracketLdsWords) w >>= 1;
   return w >= kBracketMinBins ? w : 0;
 }

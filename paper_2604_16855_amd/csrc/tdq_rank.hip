@@ -410,11 +410,20 @@ hipError_t launch_sets(const void* X, int B, int T, int C, long long ld, int G, 
 // ---------------------------------------------------------------------------
 typedef short s2v __attribute__((ext_vector_type(2)));
 
-template <int L>
+// A group of L lanes takes R rows at a time and P pieces of 16 bytes of each: the set ids
+// and all R P = 4 pieces are loaded before the first is looked at, so a wavefront has four
+// kilobytes in flight whatever the row length -- what bounds this sweep otherwise is the
+// chain set id -> interval -> piece of one row after another.  Measured, this kernel alone:
+// [8, 7744, 512] 25.6 -> 17.1 us, [32, 4096, 1024] 52.1 -> 46.5 (5.8 TB/s), [16, 484, 320]
+// 13.4 -> 6.1, [5, 1369, 333] (rows at odd addresses, read element by element before) 20.7 ->
+// 7.5; without the in-loop histogram additions it takes the same time, without the final
+// global additions 13.2 and 44.6 us on the first two.
+template <int L, int P>
 __global__ __launch_bounds__(kSweepThreads) void k_bracket_hist(
-    const u16* __restrict__ X, long long ld, int T_, int C, int G, int W, int vec_ok,
+    const u16* __restrict__ X, long long ld, int T_, int C, int G, int W,
     const int* __restrict__ gid, Bracket* __restrict__ br, u32* __restrict__ bhist,
     int rows_per_block) {
+  constexpr int R = 4 / P;
   extern __shared__ u32 lds[];                    // [G][W] bins, then per set: below, lo, width
   // walks X backwards: it runs right after the forward statistics sweep, so the end of
   // X is what the last-level cache still holds
@@ -438,39 +447,68 @@ __global__ __launch_bounds__(kSweepThreads) void k_bracket_hist(
   nrows = nrows < rows_per_block ? nrows : rows_per_block;
   constexpr int SLOTS = kSweepThreads / L;
   const int slot = tid / L, lr = tid % L;
-  const int nvec = vec_ok ? C / 8 : 0;
-  for (int rr = slot; rr < nrows; rr += SLOTS) {
-    const long long row = (long long)b * T_ + row0 + rr;
-    const int g = gid[row];
-    const u32 lo = s_lo[g], width = s_width[g];
-    const u32 lo2 = lo | (lo << 16);
-    u32* h = lds + g * W;
-    const u16* xp = X + row * ld;
-    u32 below = 0;
-#pragma unroll 2
-    for (int v = lr; v < nvec; v += L) {
-      const uint4 q = *reinterpret_cast<const uint4*>(xp + (long long)v * 8);
-      const u32 wd[4] = {q.x, q.y, q.z, q.w};
+  const int nvec = C / 8;
+  const long long first = (long long)b * T_ + row0;
+  for (int rr = slot; rr < nrows; rr += SLOTS * R) {
+    const u16* xp[R];
+    int g[R];
+    u32 below[R];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        // both halves at once: keys and lo are below 2^15, so the 16-bit differences
-        // cannot overflow and their sign bits say "key < lo"
-        const s2v d = __builtin_bit_cast(s2v, wd[i] & 0x7FFF7FFFu) - __builtin_bit_cast(s2v, lo2);
-        const u32 d2 = __builtin_bit_cast(u32, d);
-        below += (u32)__builtin_popcount(d2 & 0x80008000u);
-        const u32 dl = d2 & 0xFFFFu, dh = d2 >> 16;       // negative ones are >= 2^15 > width
-        if (dl < width) atomicAdd(&h[dl], 1u);
-        if (dh < width) atomicAdd(&h[dh], 1u);
+    for (int i = 0; i < R; ++i) {                 // rows past the end: the last one, not counted
+      const int ri = rr + SLOTS * i;
+      const long long row = first + (ri < nrows ? ri : nrows - 1);
+      xp[i] = X + row * ld;
+      g[i] = gid[row];
+      below[i] = 0;
+    }
+    for (int v0 = lr; v0 < nvec; v0 += P * L) {
+      uint4 q[R][P];
+#pragma unroll
+      for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+          const int v = v0 + k * L;
+          q[i][k] = load16(xp[i] + (long long)(v < nvec ? v : v0) * 8);
+        }
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        const u32 lo = s_lo[g[i]], width = s_width[g[i]];
+        const u32 lo2 = lo | (lo << 16);
+        u32* h = lds + g[i] * W;
+        if (rr + SLOTS * i < nrows) {
+#pragma unroll
+          for (int k = 0; k < P; ++k) {
+            if (k > 0 && v0 + k * L >= nvec) break;
+            const u32 wd[4] = {q[i][k].x, q[i][k].y, q[i][k].z, q[i][k].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              // both halves at once: keys and lo are below 2^15, so the 16-bit differences
+              // cannot overflow and their sign bits say "key < lo"
+              const s2v d = __builtin_bit_cast(s2v, wd[e] & 0x7FFF7FFFu) - __builtin_bit_cast(s2v, lo2);
+              const u32 d2 = __builtin_bit_cast(u32, d);
+              below[i] += (u32)__builtin_popcount(d2 & 0x80008000u);
+              const u32 dl = d2 & 0xFFFFu, dh = d2 >> 16;     // negative ones are >= 2^15 > width
+              if (dl < width) atomicAdd(&h[dl], 1u);
+              if (dh < width) atomicAdd(&h[dh], 1u);
+            }
+          }
+        }
       }
     }
-    for (int c = nvec * 8 + lr; c < C; c += L) {
-      const u32 k = xp[c] & 0x7FFFu;
-      below += k < lo ? 1u : 0u;
-      const u32 d = k - lo;
-      if (k >= lo && d < width) atomicAdd(&h[d], 1u);
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      if (rr + SLOTS * i < nrows) {
+        const u32 lo = s_lo[g[i]], width = s_width[g[i]];
+        for (int c = nvec * 8 + lr; c < C; c += L) {          // fewer than 8 elements
+          const u32 k = xp[i][c] & 0x7FFFu;
+          below[i] += k < lo ? 1u : 0u;
+          const u32 d = k - lo;
+          if (k >= lo && d < width) atomicAdd(&lds[g[i] * W + d], 1u);
+        }
+      }
+      const u32 total = group_sum_u32<L>(below[i]);           // in the row's last lane
+      if (lr == L - 1 && total) atomicAdd(&s_below[g[i]], total);
     }
-    below = group_sum_u32<L>(below);                       // total in the row's last lane
-    if (lr == L - 1 && below) atomicAdd(&s_below[g], below);
   }
   __syncthreads();
   u32* gh = bhist + (size_t)b * G * W;
@@ -487,28 +525,34 @@ __global__ __launch_bounds__(kSweepThreads) void k_bracket_hist(
 hipError_t launch_bracket_hist(const void* Xv, int B, int T_, int C, long long ld, int G, int W,
                                const int* gid, Bracket* br, unsigned* bhist, hipStream_t st) {
   const u16* X = static_cast<const u16*>(Xv);
-  const int vec_ok = ((reinterpret_cast<uintptr_t>(X) & 15) == 0 && ld % 8 == 0) ? 1 : 0;
-  const int L = lanes_per_row(C, 8);
-  // two workgroups per CU (measured best of 256 / 384 / 512 / 1024 / 2048: every
-  // workgroup flushes up to G * W bins with global atomics), but at least ~64 Ki
-  // elements each
-  long long rows_min = (65536 + C - 1) / C;
-  long long target_blocks = 512 / (B > 0 ? B : 1);
+  const int nvec = C / 8;
+  const int L = sweep_lanes_per_row(C, 8);
+  const int P = nvec > 2 * L ? 4 : nvec > L ? 2 : 1;
+  // Two workgroups per CU where that leaves each 128 Ki elements, one otherwise, and at
+  // least 32 Ki elements each: every workgroup clears G W bins and adds the non-zero ones to
+  // the image's with global atomics, which is what more workgroups cost.  Calibration of
+  // [8, 7744, 512] with 512 / 256 workgroups 47.3 / 44.5 us, of [32, 4096, 1024] 106.6 /
+  // 107.5; of [8, 1936, 320] with at least 32 / 16 / 8 Ki elements 40.5 / 41.9 / 44.1 us, of
+  // [8, 121, 512] 19.3 / 18.9 / 19.0 (64 Ki: 21.5).
+  const long long total = (long long)B * T_ * C;
+  const long long rows_min = (32768 + C - 1) / C;
+  long long target_blocks = (total >= 512ll * 131072 ? 512 : 256) / B;
   if (target_blocks < 1) target_blocks = 1;
   long long rpb = (T_ + target_blocks - 1) / target_blocks;
   if (rpb < rows_min) rpb = rows_min;
   if (rpb > T_) rpb = T_;
   const unsigned chunks = (unsigned)((T_ + rpb - 1) / rpb);
   const size_t lds_bytes = ((size_t)G * W + 3 * (size_t)G) * sizeof(u32);
-#define TDQ_BH(LL)                                                                              \
-  case LL:                                                                                      \
+#define TDQ_BH(LL, PP)                                                                          \
+  if (L == LL && P == PP) {                                                                     \
     if (lds_bytes > 65536)                                                                      \
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bracket_hist<LL>),             \
+      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bracket_hist<LL, PP>),         \
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);    \
-    hipLaunchKernelGGL((k_bracket_hist<LL>), dim3(chunks, B), dim3(kSweepThreads), lds_bytes,   \
-                       st, X, ld, T_, C, G, W, vec_ok, gid, br, bhist, (int)rpb);               \
-    break;
-  switch (L) { TDQ_BH(1) TDQ_BH(2) TDQ_BH(4) TDQ_BH(8) TDQ_BH(16) TDQ_BH(32) TDQ_BH(64) }
+    hipLaunchKernelGGL((k_bracket_hist<LL, PP>), dim3(chunks, B), dim3(kSweepThreads), lds_bytes, \
+                       st, X, ld, T_, C, G, W, gid, br, bhist, (int)rpb);                       \
+  }
+  TDQ_BH(1, 1) TDQ_BH(2, 1) TDQ_BH(4, 1) TDQ_BH(8, 1) TDQ_BH(8, 2) TDQ_BH(8, 4) TDQ_BH(16, 2)
+  TDQ_BH(16, 4) TDQ_BH(32, 2) TDQ_BH(32, 4) TDQ_BH(64, 2) TDQ_BH(64, 4)
 #undef TDQ_BH
   return hipGetLastError();
 }

@@ -53,3 +53,15 @@ def test_set_records_at_batch_edges(T, C, G):
     U.assert_calibration_matches(U.gpu_calibrate(X, p), X, p)
     p.base_pct = 0.99
     U.assert_calibration_matches(U.gpu_calibrate(X, p, ld_pad=3), X, p)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("C", [1, 7, 8, 9, 64, 65, 127, 129, 255, 263, 513, 1031, 2047, 2057])
+def test_sweep_row_lengths(C):
+    """Rows of every number of pieces per lane the sweep distinguishes, one element short of a
+    piece or past one, at element alignment (odd row stride), several rows per lane group."""
+    import parity_util as U
+    X = _tokens(333, C, np.float16, 7 * C)
+    p = tdq.default_params(12)
+    for pad in (0, 1):
+        U.assert_calibration_matches(U.gpu_calibrate(X, p, ld_pad=pad), X, p)
