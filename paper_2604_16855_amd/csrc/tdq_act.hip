@@ -6,6 +6,8 @@
 // clipx, dequant), Sec. 4.3 (DCRP: Eqs. tau_constraint, zr_constraint, dcrp),
 // Supp. "Quantile Implementation" (rank k = ceil(p n)), Supp. numerical
 // conventions (eps values, ties-to-even rounding), Eq. weight_quant.
+#include <type_traits>
+
 #include "tdq_device.hpp"
 
 namespace tdq {
@@ -565,71 +567,119 @@ hipError_t launch_select(unsigned* hist_level, int B, int G, int, int bits, bool
 // contraction that follows 3 to 5 % faster).
 template <typename T>
 __device__ __forceinline__ uint4 load_last_use(const T* p) {
-  typedef unsigned v4u __attribute__((ext_vector_type(4)));
-  const v4u v = __builtin_nontemporal_load(reinterpret_cast<const v4u*>(p));
+  const v4u_any v = __builtin_nontemporal_load(reinterpret_cast<const v4u_any*>(p));
   return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
-template <typename T, int L>
+// Eight elements -> one word of eight codes.
+template <typename T, bool CLAMP>
+__device__ __forceinline__ u32 quant8(const uint4 (&q)[8 / Elem<T>::V], float c, float d, float rcp) {
+  if constexpr (sizeof(T) == 2) {
+    return quant8_f16<CLAMP>(q[0], c, d, rcp);
+  } else {
+    u32 word = 0;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      float e[4];
+      Elem<float>::unpack(q[j], e);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) word |= (quant_bits<CLAMP>(e[i], c, d, rcp) & 0xFu) << (4 * (4 * j + i));
+    }
+    return word;
+  }
+}
+
+// A group of L lanes takes R rows and P units of 8 elements of each at a time; the set ids
+// and all R P units are loaded before the radii that depend on the ids, so that one trip to
+// memory covers both.  Bound by HBM on large inputs and by that chain on the others; with a
+// row of one unit per lane at a time [131072, 1024] binary16 took 56.2 us and [61952, 512]
+// 18.4, with four units 49.4 (6.8 TB/s) and 13.7.
+template <typename T, int L, int P, int R>
 __global__ __launch_bounds__(256) void k_quantize(const T* __restrict__ X, long long ld, int M, int C,
-                                                  int T_, int G, int vec_ok,
+                                                  int T_, int G, int q_words,
                                                   const int* __restrict__ gid,
                                                   const float* __restrict__ clip,
                                                   const float* __restrict__ scale,
                                                   uint8_t* __restrict__ Q, long long ld_q) {
   constexpr int V = Elem<T>::V;
   constexpr int U = 8 / V;                 // 16-byte loads per 8 elements
+  constexpr int SLOTS = 256 / L;
   // rows are walked from the end of X (measured: no slower than forwards after either
   // form of the rank select)
-  const long long gt = (long long)(gridDim.x - 1 - blockIdx.x) * 256 + threadIdx.x;
-  const long long row = gt / L;
-  const int lr = (int)(gt % L);
-  if (row >= M) return;
-  const int b = (int)(row / T_);
-  const int g = gid ? gid[row] : 0;
-  const float c = clip[(long long)b * G + g];
-  const float d = scale[(long long)b * G + g];
-  const float rcp = 1.0f / d;              // correctly rounded reciprocal
-  const T* xp = X + row * ld;
-  uint8_t* qp = Q + row * ld_q;
-  const int n8 = vec_ok ? C / 8 : 0;       // units of 8 elements -> one 32-bit store
-  if constexpr (sizeof(T) == 2) {
-    const bool need_clamp = !(c <= 7.25f * d);
-    if (__builtin_amdgcn_ballot_w64(need_clamp) == 0) {
-#pragma unroll 4
-      for (int u = lr; u < n8; u += L) {
-        const uint4 q = load_last_use(xp + (long long)u * 8);
-        *reinterpret_cast<u32*>(qp + (long long)u * 4) = quant8_f16<false>(q, c, d, rcp);
-      }
-    } else {
-#pragma unroll 2
-      for (int u = lr; u < n8; u += L) {
-        const uint4 q = load_last_use(xp + (long long)u * 8);
-        *reinterpret_cast<u32*>(qp + (long long)u * 4) = quant8_f16<true>(q, c, d, rcp);
-      }
-    }
-  } else
-#pragma unroll 2
-  for (int u = lr; u < n8; u += L) {
-    u32 word = 0;
+  const u32 row0 = (gridDim.x - 1 - blockIdx.x) * (SLOTS * R) + threadIdx.x / L;
+  const int lr = (int)(threadIdx.x % L);
+  const int n8 = q_words ? C / 8 : 0;      // units of 8 elements -> one 32-bit store
+  if (row0 >= (u32)M) return;
+  const T* xp[R];
+  int g[R];
+  u32 row[R];
 #pragma unroll
-    for (int j = 0; j < U; ++j) {
-      const uint4 q = load_last_use(xp + (long long)u * 8 + j * V);
-      T e[V];
-      Elem<T>::unpack(q, e);
-#pragma unroll
-      for (int i = 0; i < V; ++i)
-        word |= quant_nibble(Elem<T>::val(e[i]), c, d, rcp) << (4 * (j * V + i));
-    }
-    *reinterpret_cast<u32*>(qp + (long long)u * 4) = word;
+  for (int i = 0; i < R; ++i) {            // rows past the end: the last one, not stored
+    row[i] = row0 + SLOTS * i < (u32)M ? row0 + SLOTS * i : (u32)M - 1u;
+    g[i] = gid ? gid[row[i]] : 0;
+    xp[i] = X + (long long)row[i] * ld;
   }
-  // ragged tail / unaligned rows: one byte (two elements) at a time
+  float c[R], d[R], rcp[R];
+  auto radii = [&]() {
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const long long at = (long long)(row[i] / (u32)T_) * G + g[i];
+      c[i] = clip[at];
+      d[i] = scale[at];
+      rcp[i] = 1.0f / d[i];                // correctly rounded reciprocal
+    }
+  };
+  uint4 q[R][P][U];
+  auto load_units = [&](int u0) {
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+      for (int k = 0; k < P; ++k) {
+        const int u = u0 + k * L;
+#pragma unroll
+        for (int h = 0; h < U; ++h) {
+          const T* src = xp[i] + (long long)(u < n8 ? u : u0) * 8 + h * V;
+          // (few elements: nothing to displace, and rows that share lines profit from the cache)
+          q[i][k][h] = R * P == 1 ? load16(src) : load_last_use(src);
+        }
+      }
+  };
+  auto store_units = [&](int u0, auto clamp) {
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+      for (int k = 0; k < P; ++k) {
+        const int u = u0 + k * L;
+        const u32 w = quant8<T, decltype(clamp)::value>(q[i][k], c[i], d[i], rcp[i]);
+        if (u < n8 && row0 + SLOTS * i < (u32)M)
+          *reinterpret_cast<u32*>(Q + (long long)row[i] * ld_q + (long long)u * 4) = w;
+      }
+  };
+  if (lr < n8) load_units(lr);
+  radii();
+  bool need_clamp = false;                 // only radii that are no projection's need the clamp to [-8, 7]
+#pragma unroll
+  for (int i = 0; i < R; ++i) need_clamp |= !(c[i] <= 7.25f * d[i]);
+  const bool any_clamp = __ballot(need_clamp) != 0;
+  for (int u0 = lr; u0 < n8; u0 += P * L) {
+    if (u0 != lr) load_units(u0);
+    if (any_clamp)
+      store_units(u0, std::true_type{});
+    else
+      store_units(u0, std::false_type{});
+  }
+  // ragged tail / unaligned codes: one byte (two elements) at a time
   const int nbytes = (C + 1) / 2;
-  for (int by = n8 * 4 + lr; by < nbytes; by += L) {
-    const int c0 = 2 * by;
-    u32 v = quant_nibble(Elem<T>::val(xp[c0]), c, d, rcp);
-    if (c0 + 1 < C) v |= quant_nibble(Elem<T>::val(xp[c0 + 1]), c, d, rcp) << 4;
-    qp[by] = (uint8_t)v;
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    if (row0 + SLOTS * i >= (u32)M) break;
+    uint8_t* qp = Q + (long long)row[i] * ld_q;
+    for (int by = n8 * 4 + lr; by < nbytes; by += L) {
+      const int c0 = 2 * by;
+      u32 v = quant_nibble(Elem<T>::val(xp[i][c0]), c[i], d[i], rcp[i]);
+      if (c0 + 1 < C) v |= quant_nibble(Elem<T>::val(xp[i][c0 + 1]), c[i], d[i], rcp[i]) << 4;
+      qp[by] = (uint8_t)v;
+    }
   }
 }
 
@@ -637,22 +687,26 @@ template <typename T>
 static hipError_t quantize_t(const T* X, int B, int T_, int C, long long ld, int G, const int* gid,
                              const float* clip, const float* scale, uint8_t* Q, long long ld_q,
                              hipStream_t st) {
-  constexpr int V = Elem<T>::V;
-  const int vec_ok = ((reinterpret_cast<uintptr_t>(X) & 15) == 0 && ld % V == 0 &&
-                      (reinterpret_cast<uintptr_t>(Q) & 3) == 0 && ld_q % 4 == 0)
-                         ? 1 : 0;
-  const int L = lanes_per_row(C, 8);
+  const int q_words = ((reinterpret_cast<uintptr_t>(Q) & 3) == 0 && ld_q % 4 == 0) ? 1 : 0;
+  const int n8 = C / 8;
   const long long M = (long long)B * T_;
-  const long long threads = M * L;
-  const unsigned grid = (unsigned)((threads + 255) / 256);
-#define TDQ_Q(LL)                                                                               \
-  case LL:                                                                                      \
-    hipLaunchKernelGGL((k_quantize<T, LL>), dim3(grid), dim3(256), 0, st, X, ld, (int)M, C, T_, \
-                       G, vec_ok, gid, clip, scale, Q, ld_q);                                   \
-    break;
-  switch (L) {
-    TDQ_Q(1) TDQ_Q(2) TDQ_Q(4) TDQ_Q(8) TDQ_Q(16) TDQ_Q(32) TDQ_Q(64)
-  }
+  // Below 4 Mi elements there are not enough wavefronts to go round if each takes four units
+  // a lane: one unit each ([7744, 64] 2.9 against 4.9 us, [968, 512] 3.0 / 3.6, [6845, 333]
+  // 4.2 / 4.9; [7744, 320] 4.2 / 4.2, [15488, 320] 5.7 / 5.1).
+  const bool few = M * C < (4 << 20);
+  const int L = few ? lanes_per_row(C, 8) : sweep_lanes_per_row(C, 8);
+  const int P = few ? 1 : n8 > 2 * L ? 4 : n8 > L ? 2 : 1;
+  const int R = few ? 1 : 4 / P;
+  const long long rows = (256 / L) * R;
+  const unsigned grid = (unsigned)((M + rows - 1) / rows);
+#define TDQ_Q(LL, PP, RR)                                                                         \
+  if (L == LL && P == PP && R == RR)                                                              \
+    hipLaunchKernelGGL((k_quantize<T, LL, PP, RR>), dim3(grid), dim3(256), 0, st, X, ld, (int)M, C, \
+                       T_, G, q_words, gid, clip, scale, Q, ld_q);
+  TDQ_Q(1, 1, 1) TDQ_Q(2, 1, 1) TDQ_Q(4, 1, 1) TDQ_Q(8, 1, 1) TDQ_Q(16, 1, 1) TDQ_Q(32, 1, 1)
+  TDQ_Q(64, 1, 1)
+  TDQ_Q(1, 1, 4) TDQ_Q(2, 1, 4) TDQ_Q(4, 1, 4) TDQ_Q(8, 1, 4) TDQ_Q(8, 2, 2) TDQ_Q(8, 4, 1)
+  TDQ_Q(16, 2, 2) TDQ_Q(16, 4, 1) TDQ_Q(32, 2, 2) TDQ_Q(32, 4, 1) TDQ_Q(64, 2, 2) TDQ_Q(64, 4, 1)
 #undef TDQ_Q
   return hipGetLastError();
 }

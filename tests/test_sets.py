@@ -65,3 +65,27 @@ def test_sweep_row_lengths(C):
     p = tdq.default_params(12)
     for pad in (0, 1):
         U.assert_calibration_matches(U.gpu_calibrate(X, p, ld_pad=pad), X, p)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+@pytest.mark.parametrize("M,C", [(3, 5), (1021, 8), (70003, 63), (40001, 129), (17001, 264), (9001, 520),
+                                 (4999, 1031), (2100, 2064), (1100, 4099)])
+def test_quantize_row_shapes(M, C, dtype):
+    """Every division of rows and units among lanes, few and many elements, a last workgroup
+    that is not full, rows at element alignment, radii that need the clamp to [-8, 7]."""
+    import torch
+
+    import parity_util as U
+    rng = np.random.Generator(np.random.PCG64(M + C))
+    X = rng.normal(0, 1, (1, M, C)).astype(np.float16 if dtype == "f16" else np.float32)
+    p = tdq.default_params(3)
+    gid = rng.integers(0, 3, (1, M)).astype(np.int32)
+    clip = np.array([[1.5, 3.0, 0.25]], dtype=np.float32)
+    for k, scale in enumerate((clip / np.float32(7.0), clip / np.float32(9.0))):
+        scale = scale.astype(np.float32)
+        d = [torch.from_numpy(a).to(U.dev()) for a in (gid, clip, scale)]
+        Q = tdq.tdq_quantize_act(U.to_device(X, ld_pad=k), p, *d)
+        torch.cuda.synchronize()
+        want = O.quantize_act(X, gid, clip, scale, U.oracle_params(p)).reshape(M, C)
+        assert np.array_equal(U.unpack_device_codes(Q, C), want)
