@@ -109,10 +109,9 @@ __device__ __forceinline__ void store_out_vec<_Float16>(_Float16* p, const float
   __builtin_nontemporal_store(v, reinterpret_cast<h8v*>(p));
 }
 
-// Wavefront tile = (32 MT) x (32 NT) of Y, workgroup = 2 x 2 wavefronts.
-//   MT = NT = 4: 256 x 256 per workgroup, 256 accumulator registers per lane, one
-//                wavefront per SIMD; 3 expand operations per matrix instruction.
-//   MT = NT = 2: 128 x 128, for shapes too small to fill the chip with big tiles.
+// Wavefront tile = (32 MT) x (32 NT) of Y, workgroup = 2 x 2 wavefronts, stages through
+// registers: used with MT = NT = 2 for products of long K whose shape does not suit 256 x 256
+// tiles (the dispatcher says where).
 template <typename OUT, int MT, int NT>
 __global__ __launch_bounds__(GEMM_THREADS, (MT * NT >= 16 ? 1 : MT * NT >= 8 ? 2 : 3)) void k_w4a4_gemm(
     const uint8_t* __restrict__ Qx, long long ld_q, const int* __restrict__ gid,
@@ -793,6 +792,157 @@ __global__ __launch_bounds__(GEMM_THREADS, (MT * NT >= 16 ? 1 : 2)) void k_w4a4_
 }
 
 // ---------------------------------------------------------------------------
+// Kernel for the shapes that do not fill the chip with 256 x 256 tiles, and for any K.
+// A workgroup is 2 x 2 wavefronts of (32 MT) x (32 NT) of Y, MT and NT 1 or 2; these layers
+// are bound by latency (968 x 512 x 512: 11.3 us with the register-staged kernel's two
+// buffers and scales fetched first, 4.8 here; 7744 x 320 x 1280, binary32: 16.0 and 12.5; 61952 x
+// 512 x 64: 13.1 and 8.5), so the point is how many trips to memory follow one another:
+//   * operands arrive by direct-to-LDS loads in stages of 64 bytes (128 codes) per row, a
+//     ring of four slots, three stages in flight: all of a K of 384 at once, no staging
+//     registers (LDS layout of a slot as in k_w4a4_gemm_pipe), and no more LDS than the
+//     stages there are, so that a short K runs more workgroups per CU;
+//   * the token-set ids are fetched with the first stages, the row scales that depend on
+//     them while the matrix instructions run; they meet the accumulators through LDS after
+//     the last stage;
+//   * K tails: 16-byte pieces past the end of the rows are fetched from the row's first
+//     piece instead and the activation fragments are masked to the bytes that count (a zero
+//     in one operand is enough).
+// ---------------------------------------------------------------------------
+template <typename OUT, int MT, int NT>
+__global__ __launch_bounds__(GEMM_THREADS, (MT * NT >= 4 ? 2 : MT * NT >= 2 ? 3 : 6)) void k_w4a4_gemm_ring(
+    const uint8_t* __restrict__ Qx, long long ld_q, const int* __restrict__ gid,
+    const float* __restrict__ scale, int M, int T, int K, int N, int G,
+    const uint8_t* __restrict__ Qw, long long ld_w, const float* __restrict__ w_scale,
+    const float* __restrict__ bias, OUT* __restrict__ Y, long long ld_y, int* __restrict__ acc_dump,
+    int m_tiles, int n_tiles) {
+  constexpr int BM = 64 * MT, BN = 64 * NT, NL = MT + NT, D = 4;
+  constexpr int SLOT = (BM + BN) * BKB;      // A rows then B rows, 64 B each
+  extern __shared__ __attribute__((aligned(1024))) uint8_t ring[];        // min(D, stages) slots
+  __shared__ __attribute__((aligned(16))) float sRow[BM], sCol[BN], sBias[BN];
+
+  // whole rows of tiles per XCD, as in the other kernels
+  const int bid = blockIdx.x;
+  const int xcd = bid % XCDS, idx = bid / XCDS;
+  const int m_tile = (idx / n_tiles) * XCDS + xcd;
+  const int n_tile = idx % n_tiles;
+  if (m_tile >= m_tiles) return;
+  const int m0 = m_tile * BM, n0 = n_tile * BN;
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int kbytes = (K + 1) / 2, row_bytes = 16 * ((K + 31) / 32);
+  const int k_tiles = (kbytes + BKB - 1) / BKB;
+
+  const int my_m = m0 + tid < M ? m0 + tid : M - 1;
+  const int my_n = n0 + tid < N ? n0 + tid : N - 1;
+  int my_g = 0;
+  float my_ws = 0.f, my_bs = 0.f;
+  if (tid < BM && gid) my_g = gid[my_m];
+  if (tid < BN) {
+    my_ws = w_scale[my_n];
+    if (bias) my_bs = bias[my_n];
+  }
+
+  // load e of this wavefront fills 16 rows: block e * 4 + wave of the slot's BM / 16 blocks
+  // of A and BN / 16 of B; lane l writes position l & 3 of row l >> 2
+  const uint8_t* src[NL];
+  const int brow = 16 * wave + (lane >> 2);
+  const int piece = ((lane & 3) ^ ((brow >> 2) & 3)) * 16;      // (64 e rows further: the same)
+#pragma unroll
+  for (int e = 0; e < NL; ++e) {
+    if (e < MT) {
+      const int r = m0 + 64 * e + brow;
+      src[e] = Qx + (long long)(r < M ? r : M - 1) * ld_q;
+    } else {
+      const int r = n0 + 64 * (e - MT) + brow;
+      src[e] = Qw + (long long)(r < N ? r : N - 1) * ld_w;
+    }
+  }
+  const unsigned ring_base = (unsigned)(size_t)(__attribute__((address_space(3))) uint8_t*)ring;
+  const unsigned dma_base = __builtin_amdgcn_readfirstlane(ring_base + wave * 1024);
+  auto load_stage = [&](int kt) {
+    const int kb = kt * BKB + piece;
+    const int off = kb < row_bytes ? kb : 0;                    // past the row's end: any piece of it
+    const unsigned slot = dma_base + (unsigned)(kt & (D - 1)) * SLOT;
+#pragma unroll
+    for (int e = 0; e < NL; ++e) dma16(src[e] + off, slot + e * 4096);
+  };
+#pragma unroll
+  for (int st = 0; st < D - 1; ++st)
+    if (st < k_tiles) load_stage(st);
+  float my_rs = 0.f;
+  if (tid < BM) my_rs = scale[(long long)(my_m / T) * G + my_g];
+
+  v16i acc[MT][NT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
+
+  const int frow = lane & 31, fh = lane >> 5, swz = (frow >> 2) & 3;
+  const int a_row = (wm * 32 * MT + frow) * BKB, b_row = BM * BKB + (wn * 32 * NT + frow) * BKB;
+  auto stage = [&](int kt, bool tail) {
+    const uint8_t* slot = ring + (kt & (D - 1)) * SLOT;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      const int off = ((2 * ks + fh) ^ swz) * 16;
+      uint4 fa[MT], fb[NT];
+#pragma unroll
+      for (int i = 0; i < MT; ++i) fa[i] = *reinterpret_cast<const uint4*>(slot + a_row + i * 32 * BKB + off);
+#pragma unroll
+      for (int j = 0; j < NT; ++j) fb[j] = *reinterpret_cast<const uint4*>(slot + b_row + j * 32 * BKB + off);
+      if (tail) {
+        const int keep = kbytes - (kt * BKB + ks * 32 + fh * 16);       // bytes of this piece that count
+#pragma unroll
+        for (int i = 0; i < MT; ++i) mask_piece(fa[i], keep);
+      }
+#pragma unroll
+      for (int set = 0; set < 2; ++set) {
+        v4i a[MT], b[NT];
+#pragma unroll
+        for (int i = 0; i < MT; ++i) a[i] = set == 0 ? expand(fa[i].x, fa[i].y) : expand(fa[i].z, fa[i].w);
+#pragma unroll
+        for (int j = 0; j < NT; ++j) b[j] = set == 0 ? expand(fb[j].x, fb[j].y) : expand(fb[j].z, fb[j].w);
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+          for (int j = 0; j < NT; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i], b[j], acc[i][j], 0, 0, 0);
+      }
+    }
+  };
+  for (int kt = 0; kt < k_tiles; ++kt) {
+    // stage kt has landed when at most the loads of the stages after it are outstanding
+    const int newer = k_tiles - 1 - kt < D - 2 ? k_tiles - 1 - kt : D - 2;
+    if (newer == 2)
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NL) : "memory");
+    else if (newer == 1)
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NL) : "memory");
+    else
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    // the slot of stage kt - 1: every wavefront drained its reads before this barrier
+    if (kt + D - 1 < k_tiles) load_stage(kt + D - 1);
+    if ((kt + 1) * BKB <= kbytes)
+      stage(kt, false);
+    else
+      stage(kt, true);
+  }
+
+  if (tid < BM) sRow[tid] = acc_dump ? my_rs : my_rs * 0.00390625f;     // takes out the factor 256 (exact)
+  if (tid < BN) {
+    sCol[tid] = my_ws;
+    sBias[tid] = my_bs;
+  }
+  __syncthreads();
+  pipe_epilogue<OUT, MT, NT>(acc, sRow, sCol, sBias, lane, wm, wn, m0, n0, M, N, bias, Y, ld_y, acc_dump);
+}
+
+// ---------------------------------------------------------------------------
 // Wide-stage variant of the pipelined kernel (K a multiple of 256 codes): a stage is
 // 128 bytes = one whole cache line of every operand row, so a line is fetched once
 // (the 64-byte stages above fetch each line twice, two stages apart, and the L1
@@ -1190,6 +1340,23 @@ static void launch_tile(const uint8_t* Qx, long long ld_q, const int* gid, const
 }
 
 template <typename OUT, int MT, int NT>
+static void launch_ring(const uint8_t* Qx, long long ld_q, const int* gid, const float* scale, int M,
+                        int T, int K, int N, int G, const uint8_t* Qw, long long ld_w,
+                        const float* w_scale, const float* bias, void* Y, long long ld_y,
+                        int* acc_dump, hipStream_t st) {
+  constexpr int BM = 64 * MT, BN = 64 * NT;
+  const int m_tiles = (M + BM - 1) / BM, n_tiles = (N + BN - 1) / BN;
+  const long long m_groups = (m_tiles + XCDS - 1) / XCDS;
+  const unsigned grid = (unsigned)(m_groups * XCDS * n_tiles);
+  const int stages = ((K + 1) / 2 + BKB - 1) / BKB;
+  constexpr int D = 4;
+  const size_t lds = (size_t)(stages < D ? stages : D) * (BM + BN) * BKB;
+  hipLaunchKernelGGL((k_w4a4_gemm_ring<OUT, MT, NT>), dim3(grid), dim3(GEMM_THREADS), lds, st, Qx, ld_q,
+                     gid, scale, M, T, K, N, G, Qw, ld_w, w_scale, bias, static_cast<OUT*>(Y), ld_y,
+                     acc_dump, m_tiles, n_tiles);
+}
+
+template <typename OUT, int MT, int NT>
 static void launch_pipe(const uint8_t* Qx, long long ld_q, const int* gid, const float* scale, int M,
                         int T, int K, int N, int G, const uint8_t* Qw, long long ld_w,
                         const float* w_scale, const float* bias, void* Y, long long ld_y,
@@ -1239,6 +1406,21 @@ static void launch_roll(const uint8_t* Qx, long long ld_q, const int* gid, const
                      M / 256, N / 256, 1.0 / (double)T);
 }
 
+// Microseconds the 256 x 256 kernels (one workgroup per CU, whole rows of tiles per XCD) take
+// on an M x K x N product, roughly: rounds of tiles, each its stages plus an output phase
+// (measured: 8192 x 1024 x 4096 in 38 us, 4096^3 51, 16384 x 3072 x 768 34), and the
+// bounds-checked output of edge tiles (33000 x 1024 x 1024: 70).
+static double big_tile_us(int M, int K, int N, int cus) {
+  const long long rows = ((M + 255) / 256 + XCDS - 1) / XCDS, per_xcd = rows * ((N + 255) / 256);
+  const long long rounds = (per_xcd * XCDS + cus - 1) / cus;
+  return (double)rounds * (K * 0.0105 + 5.5) + 2.0 + (M % 256 || N % 256 ? 12.0 : 0.0);
+}
+// The same for the smaller tiles, which spread over the chip whatever the shape: 1.55 POP/s
+// (33000 x 1024 x 1024: 54 us, 8192 x 1024 x 4096: 46), long K 1.7 (12000 x 2048 x 2048: 64).
+static double small_tile_us(int M, int K, int N) {
+  return 2.0 * M * N * K / (K >= 2048 ? 1.7e9 : 1.55e9) + 6.0;
+}
+
 hipError_t launch_w4a4_gemm(const uint8_t* Qx, long long ld_q, const int* gid, const float* scale,
                             int M, int T, int K, int N, int G, const uint8_t* Qw, long long ld_w,
                             const float* w_scale, const float* bias, void* Y, tdq_dtype y_dt,
@@ -1261,28 +1443,43 @@ hipError_t launch_w4a4_gemm(const uint8_t* Qx, long long ld_q, const int* gid, c
       return hipGetLastError();
     }
   }
-  // big tiles once they can fill the 256 CUs at least twice over; the pipelined kernels
-  // need whole stages of K: 256 codes (measured 2 to 3 % faster), else 128
-  const int mode = big_tiles >= 512 ? (K % 256 == 0 ? 3 : K % 128 == 0 ? 2 : 1) : 0;
-#define TDQ_GEMM(OUT, MT, NT)                                                                   \
-  launch_tile<OUT, MT, NT>(Qx, ld_q, gid, scale, M, T, K, N, G, Qw, ld_w, w_scale, bias, Y, ld_y, \
-                           acc_dump, st)
+  // 256 x 256 tiles where they are estimated to be faster (see above); their kernels need
+  // whole stages of K: 256 codes (measured 2 to 3 % faster), else 128
+  const int cus = compute_units() >= XCDS ? compute_units() : 256;
+  const bool big = K % 128 == 0 && big_tile_us(M, K, N, cus) < small_tile_us(M, K, N);
+  // Otherwise tiles of 64 or 128.  Wide and tall enough to fill two workgroups per CU of
+  // 128 x 128 evenly (at least 0.72 of the last round in use): those, they fetch least
+  // (131072 x 1000 x 1024: 178 us against 203 with 64 x 128 tiles; 7744 x 320 x 1280, whose
+  // 610 tiles are 1.2 rounds: 16 against 11).  Else 64 x 128 if that gives two workgroups
+  // per CU and the last column of tiles is more than half full, else 128 x 64 if those fill
+  // three per CU (131072 x 320 x 320: 34 us, 48 with 64 x 128, 51 with 128 x 128), else 64 x 64 (968 x 512 x 512: 4.8 us, 5.6 with 64 x 128, 11 with 128 x 128).
+  auto tiles = [&](int bm, int bn) { return (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  const long long t22 = tiles(128, 128), rounds22 = (t22 + 2 * cus - 1) / (2 * cus);
+  const bool half_empty = N % 128 >= 1 && N % 128 <= 64;
+  const bool full22 = K >= 256 && (!half_empty || N >= 1024) &&
+                      (double)M * N >= 0.72 * 16384.0 * (double)(rounds22 * 2 * cus);
+  const int mode = big ? (K % 256 == 0 ? 7 : 6)
+                   // (long K without big tiles: the register-staged kernel, three workgroups per
+                   // CU; 20000 x 4096 x 500: 54 us against 59, 16384 x 3000 x 768: 47 against 50)
+                   : K >= 2048 && t22 >= 2 * cus ? 5
+                   : full22 ? 4
+                   : !half_empty && tiles(64, 128) >= 480 ? 2
+                   : tiles(128, 64) >= 3 * cus ? 3 : 1;
+#define TDQ_GEMM_ARGS                                                                             \
+  (Qx, ld_q, gid, scale, M, T, K, N, G, Qw, ld_w, w_scale, bias, Y, ld_y, acc_dump, st)
 #define TDQ_GEMM_MODES(OUT)                                                                      \
   switch (mode) {                                                                                \
-    case 3:                                                                                      \
-      launch_wide<OUT>(Qx, ld_q, gid, scale, M, T, K, N, G, Qw, ld_w, w_scale, bias, Y, ld_y,    \
-                       acc_dump, st);                                                            \
-      break;                                                                                     \
-    case 2:                                                                                      \
-      launch_pipe<OUT, 4, 4>(Qx, ld_q, gid, scale, M, T, K, N, G, Qw, ld_w, w_scale, bias, Y,    \
-                             ld_y, acc_dump, st);                                                \
-      break;                                                                                     \
-    case 1: TDQ_GEMM(OUT, 4, 4); break;                                                          \
-    default: TDQ_GEMM(OUT, 2, 2); break;                                                         \
+    case 7: launch_wide<OUT> TDQ_GEMM_ARGS; break;                                               \
+    case 6: launch_pipe<OUT, 4, 4> TDQ_GEMM_ARGS; break;                                         \
+    case 5: launch_tile<OUT, 2, 2> TDQ_GEMM_ARGS; break;                                         \
+    case 4: launch_ring<OUT, 2, 2> TDQ_GEMM_ARGS; break;                                         \
+    case 3: launch_ring<OUT, 2, 1> TDQ_GEMM_ARGS; break;                                         \
+    case 2: launch_ring<OUT, 1, 2> TDQ_GEMM_ARGS; break;                                         \
+    default: launch_ring<OUT, 1, 1> TDQ_GEMM_ARGS; break;                                        \
   }
   if (y_dt == TDQ_F32) { TDQ_GEMM_MODES(float) } else { TDQ_GEMM_MODES(_Float16) }
 #undef TDQ_GEMM_MODES
-#undef TDQ_GEMM
+#undef TDQ_GEMM_ARGS
   return hipGetLastError();
 }
 
