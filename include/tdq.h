@@ -105,10 +105,10 @@ typedef struct tdq_group_stats {
 /* Bits of the device status word (first uint32 of the workspace after a call
  * to tdq_calibrate_groups; read it back after synchronising the stream). */
 #define TDQ_DEV_NONFINITE 1u /* X holds an Inf or NaN: results undefined          */
-/* The second uint32 of the workspace is a diagnostic: after a calibration of
- * binary16 input, the number of (image, token set) pairs whose zr rank was resolved
- * by the per-set radix select because the sampled key interval missed it (or
- * because TDQ_FLAG_EXACT_SELECT was set).  It has no bearing on the results. */
+/* The second uint32 of the workspace is a diagnostic: the number of (image, token set) pairs
+ * whose zr rank was resolved by the per-set radix select because the sampled key interval
+ * missed it, more binary32 keys shared its histogram bin than are collected (or, for binary16
+ * input, because TDQ_FLAG_EXACT_SELECT was set).  It has no bearing on the results. */
 
 int tdq_version(void);
 const char* tdq_status_string(int status);
@@ -130,9 +130,10 @@ size_t tdq_workspace_bytes(int32_t B, int32_t T, int32_t C, tdq_dtype dt, const 
  *     at most 24 octaves below the top (integer arithmetic, exact);
  *  3. per group: c_base = max r_t, sigma = population std + eps_std;
  *     thr = the ceil(zr n)-th smallest |x| of the group, exact: an order statistic
- *     of the magnitude bit patterns found with LDS histograms (binary16 input: one
- *     sweep over a key interval chosen from a sample, verified by counting, with a
- *     radix select for any set the interval missed; binary32 input: radix select);
+ *     of the magnitude bit patterns found with LDS histograms (one sweep, or two for
+ *     binary32 input, over a key interval chosen from a sample, verified by counting, with
+ *     a radix select for any set the interval missed; radix select alone for more than 64
+ *     sets and for binary32 images of several million elements);
  *  4. c = max(min(c_base, q_max tau sigma, 2 q_max thr), eps),
  *     Delta = max(c / q_max, eps)                    (Eqs. dcrp, clipx; Lemma 1).
  *

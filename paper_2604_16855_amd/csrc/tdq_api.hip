@@ -125,35 +125,49 @@ static int calibrate_after_stats(const void* X, tdq_dtype dt, int32_t B, int32_t
 
   // One rank select per rank wanted of every set: first the base radius Q_p(|x|) when a
   // percentile is asked for (Eq. DSTG_clip), then Q_zr(|x|) with the projection.
-  // binary16 input: one sweep resolves the rank of (nearly) every set exactly, and the
-  // kernel that verifies it resolves the others.  binary32 input, or too many sets for
-  // the interval histogram: radix levels.
+  // One sweep (binary16 input) or two (binary32) around a sampled interval resolve the rank of
+  // (nearly) every set exactly, and the kernel that verifies it resolves the others.  Too many
+  // sets for the interval histogram, or binary32 images too large for the lists of collected
+  // keys: radix levels.
   const int W = bracket_bins(G);
-  const bool single_sweep = dt == TDQ_F16 && W > 0 && (long long)T * C < (1ll << 32);
   const bool exact_only = (p->flags & TDQ_FLAG_EXACT_SELECT) != 0;
+  // words per set of the radix levels' histograms, which the sampled route of binary32 input
+  // uses as the lists of collected keys: it expects about 1.04e-4 of a set's elements there
+  // (the interval's 5.3 % over 512 bins) and is taken while that leaves half of a list free
+  // for the largest set an image can have
+  int cap = 0;
+  for (int l = 0; l < lp.n_levels; ++l) cap += 1 << lp.bits[l];
+  cap = cap > kListMax ? kListMax : cap;
+  const bool f16 = dt == TDQ_F16;
+  const bool sampled =
+      W > 0 && (f16 ? (long long)T * C < (1ll << 32)
+                    : !exact_only && (long long)T * C <= (W == 512 ? 5120ll : 2560ll) * cap);
   Bracket* br = reinterpret_cast<Bracket*>(ws + wl.br);
   unsigned* bhist = reinterpret_cast<unsigned*>(ws + wl.bhist);
   const bool two_passes = sc.base_pct > 0.0;
   void* part = ws + wl.part;
-  if (!single_sweep || exact_only) {     // (the single sweep's own first kernel assigns the sets)
+  if (!sampled || exact_only) {          // (the sampled route's own first kernel assigns the sets)
     if (launch_assign(r, mean, m2, B, T, C, G, group_id, part, img_flag, status, st) != hipSuccess)
       return TDQ_ERR_HIP;
   }
   for (int pass = two_passes ? kPassBase : kPassZr; pass >= kPassZr; --pass) {
     const bool keep_base = two_passes && pass == kPassZr;
-    if (single_sweep) {
+    if (sampled) {
       if (!exact_only) {
-        if (launch_sets(X, B, T, C, ld_x, G, W, r, mean, m2, group_id, sc, pass, keep_base, grp, br,
-                        bhist, img_flag, status, st) != hipSuccess)
+        if (launch_sets(X, dt, B, T, C, ld_x, G, W, r, mean, m2, group_id, sc, pass, keep_base, grp,
+                        br, bhist, hist, cap, img_flag, status, st) != hipSuccess)
           return TDQ_ERR_HIP;
-        if (launch_bracket_hist(X, B, T, C, ld_x, G, W, group_id, br, bhist, st) != hipSuccess)
+        if (launch_bracket_hist(X, dt, B, T, C, ld_x, G, W, group_id, br, bhist, st) != hipSuccess)
+          return TDQ_ERR_HIP;
+        if (!f16 && launch_bracket_gather(X, B, T, C, ld_x, G, W, group_id, br, bhist, grp, hist, cap,
+                                          st) != hipSuccess)
           return TDQ_ERR_HIP;
       } else if (launch_finalize_groups(part, B, T, C, G, sc, pass, keep_base, grp, hist, lp, st) !=
                  hipSuccess) {
         return TDQ_ERR_HIP;
       }
-      if (launch_bracket_finish(X, B, T, C, ld_x, G, W, group_id, bhist, exact_only, sc, pass, grp,
-                                br, clip, scale, stats, img_flag, status, st) != hipSuccess)
+      if (launch_bracket_finish(X, dt, B, T, C, ld_x, G, W, group_id, bhist, hist, cap, exact_only, sc,
+                                pass, grp, br, clip, scale, stats, img_flag, status, st) != hipSuccess)
         return TDQ_ERR_HIP;
       continue;
     }

@@ -22,19 +22,20 @@ constexpr int kMaxLevelBits = 11;
 struct GroupWork {
   long long n;          // elements = tokens * C
   long long k_rem;      // rank still to be resolved below the current prefix
-  unsigned prefix;      // magnitude-key bits fixed so far (high bits of thr)
+  unsigned prefix;      // radix levels: magnitude-key bits fixed so far (high bits of thr);
+                        // sampled interval, binary32: keys collected of the set's bin
   unsigned tokens;      // tokens in the set
   float c_base;         // max |x|
   float sigma;          // population std + eps_std
 };
 
-// Key interval [lo, lo + width) that a sample says holds the k-th smallest
+// Key interval [lo, lo + (width << shift)) that a sample says holds the k-th smallest
 // magnitude key of an (image, token set), and what the sweep counted for it.
 struct Bracket {
   unsigned lo;       // first key of the interval
-  unsigned width;    // keys in the interval (one histogram bin each), 0 = nothing to count
+  unsigned width;    // histogram bins of the interval, 0 = nothing to count
   unsigned below;    // elements of the set with key < lo
-  unsigned pad;
+  unsigned shift;    // a bin is 2^shift keys wide (binary16: one key)
 };
 constexpr int kBracketLdsWords = 16384;   // 64 KiB of LDS histogram per workgroup (128 KiB, one
                                           // workgroup per CU, made the sweep 30 % slower)
@@ -46,6 +47,8 @@ constexpr int kBracketMinBins = 256;
 // deviations of the sample's estimate, and every workgroup of the sweep clears and flushes
 // all its bins ([8, 7744, 512] calibrates in 52.4 us with up to 1024 bins, 47.2 with 512).
 constexpr int kBracketMaxBins = 512;
+
+constexpr int kListMax = 1024;            // most words of a set's list of collected keys
 
 // Bins per set of the interval histogram: the LDS budget shared out to G sets, rounded
 // down to a power of two, at most kBracketMaxBins (0 = too many sets: use the multi-level radix
@@ -125,17 +128,23 @@ hipError_t launch_select(unsigned* hist_level, int B, int G, int shift, int bits
                          tdq_dtype dt, const Scalars& sc, GroupWork* grp, float* clip,
                          float* scale, tdq_group_stats* stats, const unsigned* img_flag,
                          unsigned* status, int pass, hipStream_t st);
-// single-sweep rank select for binary16 input
-hipError_t launch_sets(const void* X, int B, int T, int C, long long ld, int G, int W, const float* r,
-                       const double* mean, const double* m2, int* gid, const Scalars& sc, int pass,
-                       bool keep_base, GroupWork* grp, Bracket* br, unsigned* bhist,
-                       unsigned* img_flag, unsigned* status, hipStream_t st);
-hipError_t launch_bracket_hist(const void* X, int B, int T, int C, long long ld, int G, int W,
-                               const int* gid, Bracket* br, unsigned* bhist, hipStream_t st);
-hipError_t launch_bracket_finish(const void* X, int B, int T, int C, long long ld, int G, int W,
-                                 const int* gid, const unsigned* bhist, bool force_miss,
-                                 const Scalars& sc, int pass, GroupWork* grp, const Bracket* br,
-                                 float* clip, float* scale, tdq_group_stats* stats,
+// Rank select guided by a sample: binary16 input in one sweep, binary32 input in two (the
+// second, launch_bracket_gather, collects the keys of one bin per set into `lists`, cap words
+// per set, the first two of them the largest ~key and the largest key).
+hipError_t launch_sets(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G, int W,
+                       const float* r, const double* mean, const double* m2, int* gid,
+                       const Scalars& sc, int pass, bool keep_base, GroupWork* grp, Bracket* br,
+                       unsigned* bhist, unsigned* lists, int cap, unsigned* img_flag,
+                       unsigned* status, hipStream_t st);
+hipError_t launch_bracket_hist(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G,
+                               int W, const int* gid, Bracket* br, unsigned* bhist, hipStream_t st);
+hipError_t launch_bracket_gather(const void* X, int B, int T, int C, long long ld, int G, int W,
+                                 const int* gid, const Bracket* br, const unsigned* bhist,
+                                 GroupWork* grp, unsigned* lists, int cap, hipStream_t st);
+hipError_t launch_bracket_finish(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G,
+                                 int W, const int* gid, const unsigned* bhist, const unsigned* lists,
+                                 int cap, bool force_miss, const Scalars& sc, int pass, GroupWork* grp,
+                                 const Bracket* br, float* clip, float* scale, tdq_group_stats* stats,
                                  const unsigned* img_flag, unsigned* status, hipStream_t st);
 hipError_t launch_quantize(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G,
                            const int* gid, const float* clip, const float* scale, uint8_t* Q,

@@ -1,25 +1,28 @@
-// Rank select of the zr quantile for binary16 activations in ONE sweep of X
-// (constraint C2 of DCRP, Eq. zr_constraint: the k-th smallest |x| of every
+// Rank select of the zr quantile guided by a sample: one sweep of X for binary16 activations,
+// two for binary32 (constraint C2 of DCRP, Eq. zr_constraint: the k-th smallest |x| of every
 // (image, token set), k = ceil(zr n), Supp. "Quantile Implementation").
 //
-// The magnitude key of a binary16 value has 15 bits.  A radix select over LDS
-// histograms needs two sweeps of X for that many bits.  Here a small sample of
-// every set first says where to look:
+// The magnitude key of a binary16 value has 15 bits, that of a binary32 value 31.  A radix
+// select over LDS histograms needs two (four) sweeps of X for that many bits.  Here a small
+// sample of every set first says where to look:
 //
 //   k_sets            one workgroup per set finds the set's tokens and moments, reads up
-//                     to 8 Ki sampled elements and finds, in an LDS histogram of their top
-//                     key bits, the sample order statistic whose sample rank corresponds
-//                     to k.  The key interval [lo, lo + W) centred on it (W = as many
-//                     one-key bins as the sweep's LDS histogram has per set) holds the true
-//                     answer unless the sample is off by more than W/2 keys.
-//   k_bracket_hist    one sweep of X: per set, the number of keys below lo and an LDS
-//                     histogram, one bin per key, of the keys inside the interval.
-//   k_bracket_finish  one workgroup per set: if below < k <= below + inside, the
-//                     answer is the bin where the running count reaches k - below --
-//                     the exact k-th smallest, no matter how the interval was chosen --
-//                     and the set is projected.  Otherwise the set is counted as missed
-//                     and the same workgroup resolves it with a two-level radix select
-//                     over the set's own rows (exact as well, and rare).
+//                     to 8 Ki sampled elements and takes the key interval around the sample
+//                     order statistic that corresponds to k: W one-key bins centred on it
+//                     (binary16), or W bins of 2^shift keys between two sample order
+//                     statistics on either side of it (binary32).  It holds the true answer
+//                     unless the sample is off by more than that.
+//   k_bracket_hist    one sweep of X: per set, the number of keys below the interval and an
+//                     LDS histogram of the keys inside it.
+//   k_bracket_gather  binary32: a second sweep collects the keys of every set that fall into
+//                     the bin where the running count reaches k.
+//   k_bracket_finish  one workgroup per set: if below < k <= below + inside, the answer is the
+//                     bin where the running count reaches k - below -- or, of the keys
+//                     collected from it, the one of the remaining rank: the exact k-th
+//                     smallest, no matter how the interval was chosen -- and the set is
+//                     projected.  Otherwise the set is counted as missed and the same
+//                     workgroup resolves it with a radix select over the set's own rows
+//                     (exact as well, and rare).
 //
 // The result is therefore always the exact order statistic; the sample only decides
 // which of the two routes computes it, i.e. how long it takes.
@@ -52,21 +55,68 @@ constexpr int kIdRounds = 16;                                   // range keys a 
 // [1, 7744, 64] 46.3 -> 30.9 us, [8, 121, 512] 30.7 -> 26.0, [32, 4096, 1024] 118.7 -> 108.3;
 // with 16 Ki samples 31.7 / 26.9 / 111.0.
 // ---------------------------------------------------------------------------
-template <int NT, int SM>
+// One workgroup's search of two 1024-bin LDS histograms (or twice the same) for the bin that
+// holds rank r0 of h0 and r1 of h1 (1-based, at most the histogram's total): bin[i] and the
+// count before it.  Every thread of the workgroup calls it, after a barrier that completes the
+// histograms; the results are valid after the caller's next barrier.  stot [2][NW] is scratch.
+template <int NT>
+__device__ __forceinline__ void find_two_ranks(const u32* h0, const u32* h1, u32 r0, u32 r1,
+                                               u32 (*stot)[NT / 64], u32* bin, u32* before) {
+  constexpr int NW = NT / 64, kBins = 1024 / NT;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  u32 c[2][kBins], mine[2] = {0, 0};
+#pragma unroll
+  for (int i = 0; i < kBins; ++i) {
+    c[0][i] = h0[tid * kBins + i];
+    c[1][i] = h1[tid * kBins + i];
+    mine[0] += c[0][i];
+    mine[1] += c[1][i];
+  }
+  u32 incl[2] = {mine[0], mine[1]};          // inclusive scans over the wavefront
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const u32 o0 = (u32)__shfl_up((int)incl[0], d, 64), o1 = (u32)__shfl_up((int)incl[1], d, 64);
+    if (lane >= d) { incl[0] += o0; incl[1] += o1; }
+  }
+  if (lane == 63) { stot[0][wave] = incl[0]; stot[1][wave] = incl[1]; }
+  __syncthreads();
+#pragma unroll
+  for (int which = 0; which < 2; ++which) {
+#pragma unroll
+    for (int w2 = 0; w2 < NW; ++w2) incl[which] += w2 < wave ? stot[which][w2] : 0u;
+    const u32 r = which == 0 ? r0 : r1;
+    if (incl[which] - mine[which] < r && r <= incl[which]) {      // exactly one thread
+      u32 cum = incl[which] - mine[which];
+      int i = 0;
+      for (; i < kBins - 1; ++i) {
+        if (cum + c[which][i] >= r) break;
+        cum += c[which][i];
+      }
+      bin[which] = (u32)(tid * kBins + i);
+      before[which] = cum;
+    }
+  }
+}
+
+template <typename TX, int NT, int SM>
 __global__ __launch_bounds__(NT) void k_sets(
-    const u16* __restrict__ X, long long ld, int T, int C, int G, int W, int vec,
+    const TX* __restrict__ X, long long ld, int T, int C, int G, int W, int vec,
     const float* __restrict__ r, const double* __restrict__ mean, const double* __restrict__ m2,
     int* __restrict__ gid, Scalars sc, int pass, int keep_base, GroupWork* __restrict__ grp,
-    Bracket* __restrict__ br, u32* __restrict__ bhist, u32* __restrict__ img_flag,
-    u32* __restrict__ status) {
+    Bracket* __restrict__ br, u32* __restrict__ bhist, u32* __restrict__ lists, int cap,
+    u32* __restrict__ img_flag, u32* __restrict__ status) {
   constexpr int NW = NT / 64;
+  constexpr bool F16 = sizeof(TX) == 2;
+  constexpr int V = Elem<TX>::V;
   constexpr int kSampleRuns = SM / kRunLen;
   constexpr int kSampleTokens = kSampleRuns;         // at most one run per token
   __shared__ int sel[kSampleTokens];                 // drawn token of every stratum
   __shared__ long long run_base[kSampleRuns];        // element offset of every run's first channel
   __shared__ int run_len[kSampleRuns];               // channels of the run (<= kRunLen)
-  __shared__ u32 shist[1 << kSampleBits];            // sample histogram over the top key bits
-  __shared__ u32 s_min[NW], s_max[NW], wtot[NW], stot[NW], s_cmax[NW];
+  __shared__ u32 shist[F16 ? 1 : 3][1 << kSampleBits];   // sample histogram over the top key bits;
+                                                     // binary32: then two over the next ones
+  __shared__ u32 s_bin[4], s_before[4];
+  __shared__ u32 s_min[NW], s_max[NW], wtot[NW], stot[2][NW], s_cmax[NW];
   __shared__ double s_s1[NW], s_s2[NW];
   __shared__ int s_first;
   const int j = blockIdx.x, b = blockIdx.y, idx = b * G + j;
@@ -89,7 +139,7 @@ __global__ __launch_bounds__(NT) void k_sets(
 
   // ---- 1: key range of the image, key interval of the set
   load_keys(0);
-  for (int i = tid; i < (1 << kSampleBits); i += NT) shist[i] = 0;
+  for (int i = tid; i < (int)(sizeof(shist) / sizeof(u32)); i += NT) (&shist[0][0])[i] = 0;
   u32 kinv = 0, kmax = 0;                            // largest ~key, largest key
   for (int t0 = 0;;) {
 #pragma unroll
@@ -152,13 +202,14 @@ __global__ __launch_bounds__(NT) void k_sets(
       w.n = 0; w.k_rem = 0; w.prefix = 0; w.tokens = 0; w.c_base = 0.f; w.sigma = 0.f;
       grp[idx] = w;
       Bracket e;
-      e.lo = 0; e.width = 0; e.below = 0; e.pad = 0;
+      e.lo = 0; e.width = 0; e.below = 0; e.shift = 0;
       br[idx] = e;
     }
     return;
   }
   // the sweep adds into this set's histogram: clear it here
   for (int i = tid; i < W; i += NT) bhist[(size_t)idx * W + i] = 0;
+  if (!F16 && tid < 2) lists[(size_t)idx * cap + tid] = 0;
 
   // Sample geometry.  The set's tokens are cut into strata of `stride` tokens (at most
   // kSampleTokens strata) and one token is drawn from each at a hashed position: a regular
@@ -217,9 +268,9 @@ __global__ __launch_bounds__(NT) void k_sets(
     if (q < n_runs) {
       const int slot = q / rpt, run = q - slot * rpt;
       const int t = sel[slot];
-      // (whole 16-byte pieces when the rows allow 16-byte loads: C, cw and the offset are
-      // then multiples of 8 channels)
-      const u32 off = vec ? (((u32)t * 2654435761u >> 8) % (u32)((C - cw) / 8 + 1)) * 8u
+      // (whole 16-byte pieces when the rows consist of them: C, cw and the offset are then
+      // multiples of V channels)
+      const u32 off = vec ? (((u32)t * 2654435761u >> 8) % (u32)((C - cw) / V + 1)) * (u32)V
                           : ((u32)t * 2654435761u >> 8) % (u32)(C - cw + 1);
       rbase = ((long long)b * T + t) * ld + off + run * kRunLen;
       rl = cw - run * kRunLen;
@@ -270,48 +321,45 @@ __global__ __launch_bounds__(NT) void k_sets(
   // ---- 3: the sample.  Every live key adds one to an LDS histogram of its top kSampleBits
   // bits.  Loads are issued unconditionally (from a clamped, valid address) so that they
   // overlap.
+  constexpr int kKeyBits = F16 ? 15 : 31;
+  constexpr int kKeys = SM / NT;                       // sampled keys per thread
+  u32 key[kKeys];
   if (vec) {
-    // 16-byte pieces of 8 channels: piece p = NT e + tid is part p % 4 of run p / 4, so a
-    // wavefront's load instruction fetches 16 whole runs of 64 bytes; a run's pieces are
+    // 16-byte pieces of V channels: piece p = NT e + tid is part p % PPR of run p / PPR, so a
+    // wavefront's load instruction fetches whole runs of 64 (128) bytes; a run's pieces are
     // all live or (runs past the end of the table) all dead.
-    constexpr int kPieces = SM / 8 / NT;
+    constexpr int kPieces = kKeys / V, PPR = kRunLen / V;
     uint4 v[kPieces];
     bool live[kPieces];
 #pragma unroll
     for (int e = 0; e < kPieces; ++e) {
       const int p = e * NT + tid;
-      const int q = p >> 2, part = p & 3;
-      live[e] = part * 8 < run_len[q];
-      v[e] = *reinterpret_cast<const uint4*>(X + run_base[q] + (live[e] ? part * 8 : 0));
+      const int q = p / PPR, part = p % PPR;
+      live[e] = part * V < run_len[q];
+      v[e] = *reinterpret_cast<const uint4*>(X + run_base[q] + (live[e] ? part * V : 0));
     }
 #pragma unroll
     for (int e = 0; e < kPieces; ++e) {
-      if (live[e]) {
-        const u32 wd[4] = {v[e].x, v[e].y, v[e].z, v[e].w};
+      TX x[V];
+      Elem<TX>::unpack(v[e], x);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          atomicAdd(&shist[(wd[i] & 0x7FFFu) >> (15 - kSampleBits)], 1u);
-          atomicAdd(&shist[((wd[i] >> 16) & 0x7FFFu) >> (15 - kSampleBits)], 1u);
-        }
-      }
+      for (int i = 0; i < V; ++i) key[e * V + i] = live[e] ? Elem<TX>::key(x[i]) : kDead;
     }
   } else {
     // element e of lane l of wavefront w is channel l % 32 of run 2 NW e + 2 w + l / 32
-    constexpr int kPerThread = SM / NT;
-    u32 key[kPerThread];
     const int half = lane >> 5, cl = lane & 31;
 #pragma unroll
-    for (int e = 0; e < kPerThread; ++e) {
+    for (int e = 0; e < kKeys; ++e) {
       const int q = e * (2 * NW) + 2 * wave + half;
       const int rl = run_len[q];
       const int ch = cl < rl ? cl : (rl > 0 ? rl - 1 : 0);
-      const u32 x = X[run_base[q] + ch];
-      key[e] = cl < rl ? (x & 0x7FFFu) : 0xFFFFu;
+      const u32 k = Elem<TX>::key(X[run_base[q] + ch]);
+      key[e] = cl < rl ? k : kDead;
     }
-#pragma unroll
-    for (int e = 0; e < kPerThread; ++e)
-      if (key[e] != 0xFFFFu) atomicAdd(&shist[key[e] >> (15 - kSampleBits)], 1u);
   }
+#pragma unroll
+  for (int e = 0; e < kKeys; ++e)
+    if (key[e] != kDead) atomicAdd(&shist[0][key[e] >> (kKeyBits - kSampleBits)], 1u);
 
   // the set's working record: n, base radius, sigma, rank of this pass (binary64)
   GroupWork w;
@@ -339,58 +387,65 @@ __global__ __launch_bounds__(NT) void k_sets(
   }
   __syncthreads();
 
-  // Sample rank that corresponds to rank k of the set, and the histogram bin that
-  // holds that order statistic (the low key bits do not matter to the interval).
+  // Sample rank that corresponds to rank k of the set.
   long long rk = (long long)((double)w.k_rem / n * (double)m + 0.5);
   rk = rk < 1 ? 1 : (rk > m ? m : rk);
-  constexpr int kBinsPerThread = (1 << kSampleBits) / NT;
-  u32 c[kBinsPerThread], mine = 0;
-#pragma unroll
-  for (int i = 0; i < kBinsPerThread; ++i) {
-    c[i] = shist[tid * kBinsPerThread + i];
-    mine += c[i];
-  }
-  u32 incl = mine;                           // inclusive scan over the wavefront
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const u32 o = (u32)__shfl_up((int)incl, d, 64);
-    if (lane >= d) incl += o;
-  }
-  if (lane == 63) stot[wave] = incl;
-  __syncthreads();
-#pragma unroll
-  for (int w2 = 0; w2 < NW; ++w2) incl += w2 < wave ? stot[w2] : 0u;
-  if ((long long)(incl - mine) < rk && rk <= (long long)incl) {     // exactly one thread
-    u32 cum = incl - mine;
-    int i = 0;
-    for (; i < kBinsPerThread - 1; ++i) {
-      if ((long long)(cum + c[i]) >= rk) break;
-      cum += c[i];
-    }
-    const u32 v = (u32)(tid * kBinsPerThread + i) << (15 - kSampleBits);
-    // v <= estimate < v + 2^(15 - kSampleBits): centre the interval on the middle
-    const u32 mid = v + (1u << (14 - kSampleBits));
-    Bracket e;
-    e.below = 0; e.pad = 0;
+  Bracket e;
+  e.below = 0;
+  e.width = (u32)W;
+  e.shift = 0;
+  if constexpr (F16) {
+    // the histogram bin that holds that order statistic (the low key bits do not matter to
+    // the interval): v <= estimate < v + 2^(15 - kSampleBits), the interval of W one-key bins
+    // is centred on the middle
+    find_two_ranks<NT>(shist[0], shist[0], (u32)rk, (u32)rk, stot, s_bin, s_before);
+    __syncthreads();
+    const u32 mid = (s_bin[0] << (15 - kSampleBits)) + (1u << (14 - kSampleBits));
     e.lo = mid > (u32)W / 2 ? mid - (u32)W / 2 : 0u;
-    e.width = (u32)W;
-    br[idx] = e;
+  } else {
+    // The interval between two order statistics of the sample, six standard deviations of
+    // the sample rank to either side, each resolved to 20 of its 31 bits; its W bins are as
+    // wide as that needs, so a bin holds about 1e-4 of the set's elements whatever the
+    // data's offset and spread.
+    const double pq = (double)rk / (double)m;
+    const long long dr = (long long)(6.0 * sqrt((double)rk * (1.0 - pq))) + 2;
+    const u32 r0 = (u32)(rk - dr < 1 ? 1 : rk - dr), r1 = (u32)(rk + dr > m ? m : rk + dr);
+    find_two_ranks<NT>(shist[0], shist[0], r0, r1, stot, s_bin, s_before);
+    __syncthreads();
+    const u32 b0 = s_bin[0], b1 = s_bin[1];
+#pragma unroll
+    for (int i = 0; i < kKeys; ++i) {
+      const u32 top = key[i] >> 21, next = (key[i] >> 11) & 1023u;
+      if (key[i] != kDead && top == b0) atomicAdd(&shist[1][next], 1u);
+      if (key[i] != kDead && top == b1) atomicAdd(&shist[2][next], 1u);
+    }
+    __syncthreads();
+    find_two_ranks<NT>(shist[1], shist[2], r0 - s_before[0], r1 - s_before[1], stot, s_bin + 2,
+                       s_before + 2);
+    __syncthreads();
+    const u32 n0 = s_bin[2], n1 = s_bin[3];
+    e.lo = (b0 << 21) | (n0 << 11);
+    const u32 span = ((b1 << 21) | (n1 << 11)) + 2047u - e.lo;      // last key - first key
+    while ((((unsigned long long)(u32)W << e.shift) - 1ull) < span) ++e.shift;
   }
+  if (tid == 0) br[idx] = e;
 }
 
-hipError_t launch_sets(const void* X, int B, int T, int C, long long ld, int G, int W, const float* r,
-                       const double* mean, const double* m2, int* gid, const Scalars& sc, int pass,
-                       bool keep_base, GroupWork* grp, Bracket* br, unsigned* bhist,
-                       unsigned* img_flag, unsigned* status, hipStream_t st) {
+template <typename TX>
+static void sets_t(const TX* X, int B, int T, int C, long long ld, int G, int W, const float* r,
+                   const double* mean, const double* m2, int* gid, const Scalars& sc, int pass,
+                   bool keep_base, GroupWork* grp, Bracket* br, unsigned* bhist, unsigned* lists,
+                   int cap, unsigned* img_flag, unsigned* status, hipStream_t st) {
+  constexpr int V = Elem<TX>::V;
   // 16-byte sample loads need rows of whole, aligned 16-byte pieces
-  const int vec = ((reinterpret_cast<uintptr_t>(X) & 15) == 0 && ld % 8 == 0 && C % 8 == 0) ? 1 : 0;
+  const int vec = ((reinterpret_cast<uintptr_t>(X) & 15) == 0 && ld % V == 0 && C % V == 0) ? 1 : 0;
 #define TDQ_SETS_SM(NT, SM)                                                                        \
-  hipLaunchKernelGGL((k_sets<NT, SM>), dim3(G, B), dim3(NT), 0, st, static_cast<const u16*>(X), ld, \
-                     T, C, G, W, vec, r, mean, m2, gid, sc, pass, keep_base ? 1 : 0, grp, br, bhist, \
+  hipLaunchKernelGGL((k_sets<TX, NT, SM>), dim3(G, B), dim3(NT), 0, st, X, ld, T, C, G, W, vec, r, \
+                     mean, m2, gid, sc, pass, keep_base ? 1 : 0, grp, br, bhist, lists, cap,       \
                      img_flag, status)
-#define TDQ_SETS(NT)                                        \
-  do {                                                      \
-    if (W >= 512) TDQ_SETS_SM(NT, 8192); else TDQ_SETS_SM(NT, 16384); \
+#define TDQ_SETS(NT)                                                           \
+  do {                                                                         \
+    if (W >= 512 || V == 4) TDQ_SETS_SM(NT, 8192); else TDQ_SETS_SM(NT, 16384); \
   } while (0)
   // as few threads as hold the image's range keys in registers: [32, 4096, 1024] calibrates
   // in 111 / 117 / 145 us with 256 / 512 / 1024 threads per set
@@ -402,6 +457,19 @@ hipError_t launch_sets(const void* X, int B, int T, int C, long long ld, int G, 
     TDQ_SETS(1024);
 #undef TDQ_SETS
 #undef TDQ_SETS_SM
+}
+
+hipError_t launch_sets(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G, int W,
+                       const float* r, const double* mean, const double* m2, int* gid,
+                       const Scalars& sc, int pass, bool keep_base, GroupWork* grp, Bracket* br,
+                       unsigned* bhist, unsigned* lists, int cap, unsigned* img_flag,
+                       unsigned* status, hipStream_t st) {
+  if (dt == TDQ_F16)
+    sets_t<u16>(static_cast<const u16*>(X), B, T, C, ld, G, W, r, mean, m2, gid, sc, pass, keep_base,
+                grp, br, bhist, lists, cap, img_flag, status, st);
+  else
+    sets_t<float>(static_cast<const float*>(X), B, T, C, ld, G, W, r, mean, m2, gid, sc, pass, keep_base,
+                  grp, br, bhist, lists, cap, img_flag, status, st);
   return hipGetLastError();
 }
 
@@ -418,13 +486,14 @@ typedef short s2v __attribute__((ext_vector_type(2)));
 // 13.4 -> 6.1, [5, 1369, 333] (rows at odd addresses, read element by element before) 20.7 ->
 // 7.5; without the in-loop histogram additions it takes the same time, without the final
 // global additions 13.2 and 44.6 us on the first two.
-template <int L, int P>
+template <typename TX, int L, int P>
 __global__ __launch_bounds__(kSweepThreads) void k_bracket_hist(
-    const u16* __restrict__ X, long long ld, int T_, int C, int G, int W,
+    const TX* __restrict__ X, long long ld, int T_, int C, int G, int W,
     const int* __restrict__ gid, Bracket* __restrict__ br, u32* __restrict__ bhist,
     int rows_per_block) {
   constexpr int R = 4 / P;
-  extern __shared__ u32 lds[];                    // [G][W] bins, then per set: below, lo, width
+  constexpr int V = Elem<TX>::V;
+  extern __shared__ u32 lds[];                    // [G][W] bins, then per set: below, lo, width, shift
   // walks X backwards: it runs right after the forward statistics sweep, so the end of
   // X is what the last-level cache still holds
   const int b = (int)(gridDim.y - 1 - blockIdx.y);
@@ -434,11 +503,13 @@ __global__ __launch_bounds__(kSweepThreads) void k_bracket_hist(
   u32* s_below = lds + nwords;
   u32* s_lo = s_below + G;
   u32* s_width = s_lo + G;
+  u32* s_shift = s_width + G;
   for (int i = tid; i < nwords + G; i += kSweepThreads) lds[i] = 0;
   for (int g = tid; g < G; g += kSweepThreads) {
     const Bracket e = br[(long long)b * G + g];
     s_lo[g] = e.lo;
     s_width[g] = e.width;
+    s_shift[g] = e.shift;
   }
   __syncthreads();
 
@@ -447,10 +518,10 @@ __global__ __launch_bounds__(kSweepThreads) void k_bracket_hist(
   nrows = nrows < rows_per_block ? nrows : rows_per_block;
   constexpr int SLOTS = kSweepThreads / L;
   const int slot = tid / L, lr = tid % L;
-  const int nvec = C / 8;
+  const int nvec = C / V;
   const long long first = (long long)b * T_ + row0;
   for (int rr = slot; rr < nrows; rr += SLOTS * R) {
-    const u16* xp[R];
+    const TX* xp[R];
     int g[R];
     u32 below[R];
 #pragma unroll
@@ -468,11 +539,12 @@ __global__ __launch_bounds__(kSweepThreads) void k_bracket_hist(
 #pragma unroll
         for (int k = 0; k < P; ++k) {
           const int v = v0 + k * L;
-          q[i][k] = load16(xp[i] + (long long)(v < nvec ? v : v0) * 8);
+          q[i][k] = load16(xp[i] + (long long)(v < nvec ? v : v0) * V);
         }
 #pragma unroll
       for (int i = 0; i < R; ++i) {
         const u32 lo = s_lo[g[i]], width = s_width[g[i]];
+        const u32 shift = V == 4 ? s_shift[g[i]] : 0u;
         const u32 lo2 = lo | (lo << 16);
         u32* h = lds + g[i] * W;
         if (rr + SLOTS * i < nrows) {
@@ -482,14 +554,23 @@ __global__ __launch_bounds__(kSweepThreads) void k_bracket_hist(
             const u32 wd[4] = {q[i][k].x, q[i][k].y, q[i][k].z, q[i][k].w};
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-              // both halves at once: keys and lo are below 2^15, so the 16-bit differences
-              // cannot overflow and their sign bits say "key < lo"
-              const s2v d = __builtin_bit_cast(s2v, wd[e] & 0x7FFF7FFFu) - __builtin_bit_cast(s2v, lo2);
-              const u32 d2 = __builtin_bit_cast(u32, d);
-              below[i] += (u32)__builtin_popcount(d2 & 0x80008000u);
-              const u32 dl = d2 & 0xFFFFu, dh = d2 >> 16;     // negative ones are >= 2^15 > width
-              if (dl < width) atomicAdd(&h[dl], 1u);
-              if (dh < width) atomicAdd(&h[dh], 1u);
+              if constexpr (V == 8) {
+                // both halves at once: keys and lo are below 2^15, so the 16-bit differences
+                // cannot overflow and their sign bits say "key < lo"
+                const s2v d = __builtin_bit_cast(s2v, wd[e] & 0x7FFF7FFFu) - __builtin_bit_cast(s2v, lo2);
+                const u32 d2 = __builtin_bit_cast(u32, d);
+                below[i] += (u32)__builtin_popcount(d2 & 0x80008000u);
+                const u32 dl = d2 & 0xFFFFu, dh = d2 >> 16;     // negative ones are >= 2^15 > width
+                if (dl < width) atomicAdd(&h[dl], 1u);
+                if (dh < width) atomicAdd(&h[dh], 1u);
+              } else {
+                // keys and lo are below 2^31: the sign of the difference says "key < lo", and
+                // such a difference lies past the last bin (shift <= 22 and 2^31 >> 22 = 512)
+                const u32 d = (wd[e] & 0x7FFFFFFFu) - lo;
+                below[i] += d >> 31;
+                const u32 bin = d >> shift;
+                if (bin < width) atomicAdd(&h[bin], 1u);
+              }
             }
           }
         }
@@ -499,10 +580,11 @@ __global__ __launch_bounds__(kSweepThreads) void k_bracket_hist(
     for (int i = 0; i < R; ++i) {
       if (rr + SLOTS * i < nrows) {
         const u32 lo = s_lo[g[i]], width = s_width[g[i]];
-        for (int c = nvec * 8 + lr; c < C; c += L) {          // fewer than 8 elements
-          const u32 k = xp[i][c] & 0x7FFFu;
+        const u32 shift = V == 4 ? s_shift[g[i]] : 0u;
+        for (int c = nvec * V + lr; c < C; c += L) {          // fewer than V elements
+          const u32 k = Elem<TX>::key(xp[i][c]);
           below[i] += k < lo ? 1u : 0u;
-          const u32 d = k - lo;
+          const u32 d = (k - lo) >> shift;
           if (k >= lo && d < width) atomicAdd(&lds[g[i] * W + d], 1u);
         }
       }
@@ -522,58 +604,255 @@ __global__ __launch_bounds__(kSweepThreads) void k_bracket_hist(
   }
 }
 
-hipError_t launch_bracket_hist(const void* Xv, int B, int T_, int C, long long ld, int G, int W,
-                               const int* gid, Bracket* br, unsigned* bhist, hipStream_t st) {
-  const u16* X = static_cast<const u16*>(Xv);
-  const int nvec = C / 8;
-  const int L = sweep_lanes_per_row(C, 8);
-  const int P = nvec > 2 * L ? 4 : nvec > L ? 2 : 1;
-  // Two workgroups per CU where that leaves each 128 Ki elements, one otherwise, and at
-  // least 32 Ki elements each: every workgroup clears G W bins and adds the non-zero ones to
-  // the image's with global atomics, which is what more workgroups cost.  Calibration of
-  // [8, 7744, 512] with 512 / 256 workgroups 47.3 / 44.5 us, of [32, 4096, 1024] 106.6 /
-  // 107.5; of [8, 1936, 320] with at least 32 / 16 / 8 Ki elements 40.5 / 41.9 / 44.1 us, of
-  // [8, 121, 512] 19.3 / 18.9 / 19.0 (64 Ki: 21.5).
-  const long long total = (long long)B * T_ * C;
+// Rows per workgroup of a sweep.
+// Two workgroups per CU where that leaves each 128 Ki elements, one otherwise, and at least
+// 32 Ki elements each: every workgroup clears G W bins and adds the non-zero ones to the
+// image's with global atomics, which is what more workgroups cost.  Calibration of
+// [8, 7744, 512] with 512 / 256 workgroups 47.3 / 44.5 us, of [32, 4096, 1024] 106.6 /
+// 107.5; of [8, 1936, 320] with at least 32 / 16 / 8 Ki elements 40.5 / 41.9 / 44.1 us, of
+// [8, 121, 512] 19.3 / 18.9 / 19.0 (64 Ki: 21.5).
+static int sweep_rows(int B, int T, int C) {
   const long long rows_min = (32768 + C - 1) / C;
-  long long target_blocks = (total >= 512ll * 131072 ? 512 : 256) / B;
+  long long target_blocks = ((long long)B * T * C >= 512ll * 131072 ? 512 : 256) / B;
   if (target_blocks < 1) target_blocks = 1;
-  long long rpb = (T_ + target_blocks - 1) / target_blocks;
+  long long rpb = (T + target_blocks - 1) / target_blocks;
   if (rpb < rows_min) rpb = rows_min;
-  if (rpb > T_) rpb = T_;
+  return (int)(rpb > T ? T : rpb);
+}
+
+// The (L, P) of a sweep over rows of nvec pieces (see k_bracket_hist).
+#define TDQ_SWEEP_CASES(CASE)                                                             \
+  CASE(1, 1) CASE(2, 1) CASE(4, 1) CASE(8, 1) CASE(8, 2) CASE(8, 4) CASE(16, 2) CASE(16, 4) \
+  CASE(32, 2) CASE(32, 4) CASE(64, 2) CASE(64, 4)
+
+template <typename TX>
+static void bracket_hist_t(const TX* X, int B, int T_, int C, long long ld, int G, int W,
+                           const int* gid, Bracket* br, unsigned* bhist, hipStream_t st) {
+  const int nvec = C / Elem<TX>::V;
+  const int L = sweep_lanes_per_row(C, Elem<TX>::V);
+  const int P = nvec > 2 * L ? 4 : nvec > L ? 2 : 1;
+  const int rpb = sweep_rows(B, T_, C);
   const unsigned chunks = (unsigned)((T_ + rpb - 1) / rpb);
-  const size_t lds_bytes = ((size_t)G * W + 3 * (size_t)G) * sizeof(u32);
+  const size_t lds_bytes = ((size_t)G * W + 4 * (size_t)G) * sizeof(u32);
 #define TDQ_BH(LL, PP)                                                                          \
   if (L == LL && P == PP) {                                                                     \
     if (lds_bytes > 65536)                                                                      \
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bracket_hist<LL, PP>),         \
+      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bracket_hist<TX, LL, PP>),     \
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);    \
-    hipLaunchKernelGGL((k_bracket_hist<LL, PP>), dim3(chunks, B), dim3(kSweepThreads), lds_bytes, \
-                       st, X, ld, T_, C, G, W, gid, br, bhist, (int)rpb);                       \
+    hipLaunchKernelGGL((k_bracket_hist<TX, LL, PP>), dim3(chunks, B), dim3(kSweepThreads),      \
+                       lds_bytes, st, X, ld, T_, C, G, W, gid, br, bhist, rpb);                 \
   }
-  TDQ_BH(1, 1) TDQ_BH(2, 1) TDQ_BH(4, 1) TDQ_BH(8, 1) TDQ_BH(8, 2) TDQ_BH(8, 4) TDQ_BH(16, 2)
-  TDQ_BH(16, 4) TDQ_BH(32, 2) TDQ_BH(32, 4) TDQ_BH(64, 2) TDQ_BH(64, 4)
+  TDQ_SWEEP_CASES(TDQ_BH)
 #undef TDQ_BH
+}
+
+hipError_t launch_bracket_hist(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G,
+                               int W, const int* gid, Bracket* br, unsigned* bhist, hipStream_t st) {
+  if (dt == TDQ_F16)
+    bracket_hist_t<u16>(static_cast<const u16*>(X), B, T, C, ld, G, W, gid, br, bhist, st);
+  else
+    bracket_hist_t<float>(static_cast<const float*>(X), B, T, C, ld, G, W, gid, br, bhist, st);
+  return hipGetLastError();
+}
+
+// The bin of a set's interval histogram (W = 256 or 512 bins) that holds its k-th smallest
+// key, by one wavefront; the same in every lane.  ok = the interval does hold it.
+struct BinPick {
+  bool ok;
+  u32 bin, need;      // rank wanted among the bin's elements (1-based)
+};
+__device__ __forceinline__ BinPick pick_bin(const u32* __restrict__ hb, int W, u32 below, long long k) {
+  const int lane = threadIdx.x & 63;
+  const int per = W / 64;                       // 4 or 8
+  const uint4 c0 = *reinterpret_cast<const uint4*>(hb + lane * per);
+  const uint4 c1 = *reinterpret_cast<const uint4*>(hb + lane * per + (per > 4 ? 4 : 0));
+  const u32 c[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
+  unsigned long long mine = 0;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) mine += i < per ? c[i] : 0u;
+  unsigned long long incl = mine;               // inclusive scan over lanes
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const unsigned long long o = __shfl_up(incl, d, 64);
+    if (lane >= d) incl += o;
+  }
+  const unsigned long long inside = __shfl(incl, 63, 64);
+  const unsigned long long kk = (unsigned long long)k;
+  BinPick r;
+  r.ok = kk > below && kk - below <= inside;
+  const unsigned long long need = kk - below;
+  const unsigned long long hit = __ballot(incl >= need);
+  const int src = r.ok ? __ffsll((long long)hit) - 1 : 0;       // hit != 0 because need <= inside
+  unsigned long long cum = incl - mine;
+  u32 bin = (u32)(lane * per);
+  for (int i = 0; i < per - 1; ++i) {
+    if (cum + c[i] >= need) break;
+    cum += c[i];
+    ++bin;
+  }
+  r.bin = (u32)__shfl((int)bin, src, 64);
+  r.need = (u32)(need - __shfl(cum, src, 64));
+  return r;
+}
+
+// ---------------------------------------------------------------------------
+// k_bracket_gather, binary32 input only: a bin of the interval histogram is 2^shift keys wide
+// there, so a second sweep collects the keys that fall into the bin of every set (about 1e-4
+// of the elements), first per workgroup in LDS.  lists[set]: largest ~key, largest key, then
+// the keys; their number is counted in GroupWork::prefix, and a workgroup that found more than
+// it can keep pushes that number past the list's capacity.  (Equal keys need no list: the
+// smallest and the largest collected key say so.)  Every workgroup finds the bins itself.
+// Calibration of [8, 1024, 768]: 73.4 us with a sweep and a select kernel per eight key bits,
+// 45.3 with the sampled interval (this kernel 11.5, with twice or four times the workgroups
+// 11.0 and 16.8).
+// ---------------------------------------------------------------------------
+constexpr int kGatherWords = 8192;              // LDS words for collected keys, shared by the sets
+
+template <int L, int P>
+__global__ __launch_bounds__(kSweepThreads) void k_bracket_gather(
+    const float* __restrict__ X, long long ld, int T_, int C, int G, int W,
+    const int* __restrict__ gid, const Bracket* __restrict__ br, const u32* __restrict__ bhist,
+    GroupWork* __restrict__ grp, u32* __restrict__ lists, int cap, int rows_per_block) {
+  constexpr int R = 4 / P;
+  __shared__ u32 s_key0[64], s_span[64], s_cnt[64], s_nmin[64], s_max[64], s_at[64];
+  __shared__ u32 s_list[kGatherWords];
+  const int b = blockIdx.y, chunk = blockIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int keep = kGatherWords / G;            // keys kept per set (G <= 64)
+  for (int g = tid >> 6; g < G; g += kSweepThreads / 64) {
+    const long long idx = (long long)b * G + g;
+    const GroupWork w = grp[idx];
+    const Bracket e = br[idx];
+    u32 span = 0, key0 = 0;
+    if (w.tokens != 0 && e.shift != 0) {        // uniform over the wavefront
+      const BinPick p = pick_bin(bhist + (size_t)idx * W, W, e.below, w.k_rem);
+      if (p.ok) {
+        key0 = e.lo + (p.bin << e.shift);
+        span = 1u << e.shift;
+      }
+    }
+    if (lane == 0) {
+      s_key0[g] = key0;
+      s_span[g] = span;
+      s_cnt[g] = 0;
+      s_nmin[g] = 0;
+      s_max[g] = 0;
+    }
+  }
+  __syncthreads();
+  const int row0 = chunk * rows_per_block;
+  int nrows = T_ - row0;
+  nrows = nrows < rows_per_block ? nrows : rows_per_block;
+  constexpr int SLOTS = kSweepThreads / L;
+  const int slot = tid / L, lr = tid % L;
+  const int nvec = C / 4;
+  const long long first = (long long)b * T_ + row0;
+  for (int rr = slot; rr < nrows; rr += SLOTS * R) {
+    const float* xp[R];
+    int g[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {               // rows past the end: the last one, not looked at
+      const int ri = rr + SLOTS * i;
+      const long long row = first + (ri < nrows ? ri : nrows - 1);
+      xp[i] = X + row * ld;
+      g[i] = gid[row];
+    }
+    auto look = [&](int gi, u32 key0, u32 span, u32 k) {
+      if (k - key0 < span) {
+        const u32 at = atomicAdd(&s_cnt[gi], 1u);
+        if (at < (u32)keep) s_list[gi * keep + at] = k;
+        atomicMax(&s_nmin[gi], ~k);
+        atomicMax(&s_max[gi], k);
+      }
+    };
+    for (int v0 = lr; v0 < nvec; v0 += P * L) {
+      uint4 q[R][P];
+#pragma unroll
+      for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+          const int v = v0 + k * L;
+          q[i][k] = load16(xp[i] + (long long)(v < nvec ? v : v0) * 4);
+        }
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        const u32 key0 = s_key0[g[i]], span = rr + SLOTS * i < nrows ? s_span[g[i]] : 0u;
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+          if (k > 0 && v0 + k * L >= nvec) break;
+          look(g[i], key0, span, q[i][k].x & 0x7FFFFFFFu);
+          look(g[i], key0, span, q[i][k].y & 0x7FFFFFFFu);
+          look(g[i], key0, span, q[i][k].z & 0x7FFFFFFFu);
+          look(g[i], key0, span, q[i][k].w & 0x7FFFFFFFu);
+        }
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      if (rr + SLOTS * i < nrows)
+        for (int c = nvec * 4 + lr; c < C; c += L)
+          look(g[i], s_key0[g[i]], s_span[g[i]], Elem<float>::key(xp[i][c]));
+    }
+  }
+  __syncthreads();
+  if (tid < G && s_cnt[tid]) {
+    const long long idx = (long long)b * G + tid;
+    const u32 n = s_cnt[tid];
+    s_at[tid] = atomicAdd(&grp[idx].prefix, n <= (u32)keep ? n : n + (u32)cap);
+    atomicMax(&lists[idx * cap], s_nmin[tid]);
+    atomicMax(&lists[idx * cap + 1], s_max[tid]);
+  }
+  __syncthreads();
+  for (int i = tid; i < G * keep; i += kSweepThreads) {
+    const int g = i / keep, at = i - g * keep;
+    if ((u32)at < s_cnt[g] && s_at[g] < (u32)cap && s_at[g] + (u32)at + 2u < (u32)cap)
+      lists[((long long)b * G + g) * cap + 2 + s_at[g] + at] = s_list[i];
+  }
+}
+
+hipError_t launch_bracket_gather(const void* Xv, int B, int T_, int C, long long ld, int G, int W,
+                                 const int* gid, const Bracket* br, const unsigned* bhist,
+                                 GroupWork* grp, unsigned* lists, int cap, hipStream_t st) {
+  const float* X = static_cast<const float*>(Xv);
+  const int nvec = C / 4;
+  const int L = sweep_lanes_per_row(C, 4);
+  const int P = nvec > 2 * L ? 4 : nvec > L ? 2 : 1;
+  const int rpb = sweep_rows(B, T_, C);
+  const unsigned chunks = (unsigned)((T_ + rpb - 1) / rpb);
+#define TDQ_BG(LL, PP)                                                                             \
+  if (L == LL && P == PP)                                                                          \
+    hipLaunchKernelGGL((k_bracket_gather<LL, PP>), dim3(chunks, B), dim3(kSweepThreads), 0, st, X, \
+                       ld, T_, C, G, W, gid, br, bhist, grp, lists, cap, rpb);
+  TDQ_SWEEP_CASES(TDQ_BG)
+#undef TDQ_BG
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
-// k_bracket_finish: one workgroup per set.  Its first wavefront verifies the interval
-// and, on a hit, finishes the set; on a miss the whole workgroup runs the exact
-// two-level radix select (8 + 7 key bits, LDS histogram) over the set's own rows.
+// k_bracket_finish: one workgroup per set.  Its first wavefront verifies the interval and
+// finds the bin; that is the key itself (binary16, one key per bin), or the workgroup finds
+// it among the keys that the second sweep collected (binary32).  On a miss, or if more keys
+// were collected than fit, it runs an exact radix select (8 key bits a level, LDS histogram)
+// over the set's own rows.  A chain of dependent trips to memory: the record, the interval and
+// the bins are loaded together.
 // ---------------------------------------------------------------------------
 constexpr int kFinishThreads = 256;
 
+template <typename TX>
 __global__ __launch_bounds__(kFinishThreads) void k_bracket_finish(
-    const u16* __restrict__ X, long long ld, int T, int C, int G, int vec_ok,
-    const int* __restrict__ gid, const u32* __restrict__ bhist, int W, int force_miss, Scalars sc,
-    int pass, GroupWork* __restrict__ grp, const Bracket* __restrict__ br,
-    float* __restrict__ clip, float* __restrict__ scale, tdq_group_stats* __restrict__ stats,
-    const u32* __restrict__ img_flag, int B, u32* __restrict__ status) {
+    const TX* __restrict__ X, long long ld, int T, int C, int G,
+    const int* __restrict__ gid, const u32* __restrict__ bhist, int W, const u32* __restrict__ lists,
+    int cap, int force_miss, Scalars sc, int pass, GroupWork* __restrict__ grp,
+    const Bracket* __restrict__ br, float* __restrict__ clip, float* __restrict__ scale,
+    tdq_group_stats* __restrict__ stats, const u32* __restrict__ img_flag, int B,
+    u32* __restrict__ status) {
+  constexpr bool F16 = sizeof(TX) == 2;
+  constexpr int V = Elem<TX>::V;
   __shared__ u32 h[256];
   __shared__ int list[kFinishThreads];
+  __shared__ u32 s_keys[F16 ? 1 : kListMax];
   __shared__ u32 wtot[kFinishThreads / 64];
-  __shared__ u32 s_ok, s_digit;
+  __shared__ u32 s_ok, s_key, s_need, s_digit;
   __shared__ unsigned long long s_rem;
   const int idx = blockIdx.x;
   const int b = idx / G, j = idx - b * G;
@@ -586,66 +865,79 @@ __global__ __launch_bounds__(kFinishThreads) void k_bracket_finish(
     if (lane == 0) status[0] = any ? TDQ_DEV_NONFINITE : 0u;
   }
   const GroupWork w = grp[idx];
-  if (w.tokens == 0) {
-    if (tid == 0 && pass == kPassZr) project_store(idx, w, 0u, true, sc, clip, scale, stats);
-    return;
-  }
+  auto finish = [&](u32 key) {                  // by one thread
+    if (pass == kPassBase)
+      grp[idx].c_base = Elem<TX>::key_to_float(key);     // the set's base radius Q_p(|x|)
+    else
+      project_store(idx, w, key, F16, sc, clip, scale, stats);
+  };
+  enum { kMiss = 0, kDone = 1, kInList = 2 };
   if (wave == 0) {
-    bool ok = false;
-    unsigned long long need = 0, mine = 0, incl = 0;
-    const u32* hb = bhist + (size_t)idx * W;
-    const int per = W / 64;                     // W is a multiple of 64
-    const int first = lane * per;
-    Bracket e;
-    e.lo = 0; e.width = 0; e.below = 0; e.pad = 0;
+    u32 ok = kMiss;
     if (!force_miss) {
-      e = br[idx];
-      const unsigned long long k = (unsigned long long)w.k_rem;
-      for (int i = 0; i < per; ++i) mine += hb[first + i];
-      incl = mine;                              // inclusive scan over lanes
-#pragma unroll
-      for (int d = 1; d < 64; d <<= 1) {
-        const unsigned long long o = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += o;
-      }
-      const unsigned long long inside = __shfl(incl, 63, 64);
-      ok = k > e.below && k - e.below <= inside;
-      need = k - e.below;
-    }
-    if (ok) {                                   // wavefront-uniform
-      const unsigned long long hit = __ballot(incl >= need);
-      const int src = __ffsll((long long)hit) - 1;        // hit != 0 because need <= inside
-      if (lane == src) {
-        unsigned long long cum = incl - mine;
-        int i = 0;
-        for (; i < per - 1; ++i) {
-          const unsigned long long c = hb[first + i];
-          if (cum + c >= need) break;
-          cum += c;
+      const Bracket e = br[idx];
+      const BinPick p = pick_bin(bhist + (size_t)idx * W, W, e.below, w.k_rem);
+      if (w.tokens == 0) {
+        ok = kDone;
+        if (lane == 0 && pass == kPassZr) project_store(idx, w, 0u, F16, sc, clip, scale, stats);
+      } else if (p.ok) {                        // wavefront-uniform
+        u32 key = e.lo + (p.bin << e.shift);
+        ok = kDone;
+        if (!F16 && e.shift != 0) {
+          const u32 lo = ~lists[(size_t)idx * cap], hi = lists[(size_t)idx * cap + 1];
+          key = lo;
+          if (lo != hi) ok = w.prefix + 2u <= (u32)cap ? kInList : kMiss;
         }
-        const u32 key = e.lo + (u32)(first + i);
-        if (pass == kPassBase)
-          grp[idx].c_base = h2f(key);            // the set's base radius Q_p(|x|)
-        else
-          project_store(idx, w, key, true, sc, clip, scale, stats);
+        if (ok == kDone && lane == 0) finish(key);
+        if (lane == 0) s_need = p.need;
       }
+    } else if (w.tokens == 0) {
+      ok = kDone;
+      if (lane == 0 && pass == kPassZr) project_store(idx, w, 0u, F16, sc, clip, scale, stats);
     }
-    if (lane == 0) s_ok = ok ? 1u : 0u;
+    if (lane == 0) s_ok = ok;
   }
   __syncthreads();
-  if (s_ok) return;
+  if (s_ok == kDone) return;
+  if constexpr (!F16) {
+    if (s_ok == kInList) {
+      // the key with fewer than `need` smaller ones and at least `need` not larger
+      const int n = (int)w.prefix;
+      for (int i = tid; i < n; i += kFinishThreads) s_keys[i] = lists[(size_t)idx * cap + 2 + i];
+      __syncthreads();
+      const u32 need = s_need;
+      for (int i = tid; i < n; i += kFinishThreads) {
+        const u32 mine = s_keys[i];
+        u32 less = 0, equal = 0;
+        for (int c = 0; c < n; ++c) {
+          const u32 k = s_keys[c];
+          less += k < mine ? 1u : 0u;
+          equal += k == mine ? 1u : 0u;
+        }
+        if (less < need && need <= less + equal) s_key = mine;     // equal keys write the same
+      }
+      __syncthreads();
+      if (tid == 0) finish(s_key);
+      return;
+    }
+  }
 
   // The interval missed rank k (or the validation switch asked for this route).
   if (tid == 0) atomicAdd(&status[1 + pass], 1u);
   const int* gb = gid + (long long)b * T;
   unsigned long long k = (unsigned long long)w.k_rem;
   u32 prefix = 0;
-  const int nvec = vec_ok ? C / 8 : 0;
-  for (int level = 0; level < 2; ++level) {
-    const int shift = level == 0 ? 7 : 0;
-    const u32 mask = level == 0 ? 255u : 127u;
+  constexpr int kBits = F16 ? 15 : 31, kLevels = F16 ? 2 : 4;
+  const int nvec = C / V;
+  for (int level = 0; level < kLevels; ++level) {
+    const int bits = level == kLevels - 1 ? 7 : 8;
+    const int shift = kBits - 8 * level - bits;
+    const u32 mask = (1u << bits) - 1u;
     h[tid] = 0;                                 // kFinishThreads == 256 bins
     __syncthreads();
+    auto count = [&](u32 key) {
+      if (level == 0 || (key >> (shift + bits)) == prefix) atomicAdd(&h[(key >> shift) & mask], 1u);
+    };
     for (int t0 = 0; t0 < T; t0 += kFinishThreads) {
       // the set's tokens among t0 .. t0 + 255, compacted into `list`
       const int t = t0 + tid;
@@ -662,27 +954,20 @@ __global__ __launch_bounds__(kFinishThreads) void k_bracket_finish(
       if (match) list[before + (u32)__popcll(m & ((1ull << lane) - 1ull))] = t;
       __syncthreads();
       for (u32 i = wave; i < n_list; i += kFinishThreads / 64) {     // one wavefront per row
-        const u16* xp = X + ((long long)b * T + list[i]) * ld;
+        const TX* xp = X + ((long long)b * T + list[i]) * ld;
         for (int v = lane; v < nvec; v += 64) {
-          const uint4 q = *reinterpret_cast<const uint4*>(xp + (long long)v * 8);
-          const u32 wd[4] = {q.x, q.y, q.z, q.w};
+          TX x[V];
+          Elem<TX>::unpack(load16(xp + (long long)v * V), x);
 #pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            const u32 k0 = wd[c] & 0x7FFFu, k1 = (wd[c] >> 16) & 0x7FFFu;
-            if (level == 0 || (k0 >> 7) == prefix) atomicAdd(&h[(k0 >> shift) & mask], 1u);
-            if (level == 0 || (k1 >> 7) == prefix) atomicAdd(&h[(k1 >> shift) & mask], 1u);
-          }
+          for (int c = 0; c < V; ++c) count(Elem<TX>::key(x[c]));
         }
-        for (int c = nvec * 8 + lane; c < C; c += 64) {
-          const u32 k0 = xp[c] & 0x7FFFu;
-          if (level == 0 || (k0 >> 7) == prefix) atomicAdd(&h[(k0 >> shift) & mask], 1u);
-        }
+        for (int c = nvec * V + lane; c < C; c += 64) count(Elem<TX>::key(xp[c]));
       }
       __syncthreads();                          // `list` and `wtot` are reused
     }
     if (tid == 0) {
       unsigned long long cum = 0;
-      const int nb = level == 0 ? 256 : 128;
+      const int nb = 1 << bits;
       int bin = 0;
       for (; bin < nb - 1; ++bin) {
         if (cum + h[bin] >= k) break;
@@ -692,28 +977,26 @@ __global__ __launch_bounds__(kFinishThreads) void k_bracket_finish(
       s_rem = k - cum;
     }
     __syncthreads();
-    prefix = level == 0 ? s_digit : ((prefix << 7) | s_digit);
+    prefix = (prefix << bits) | s_digit;
     k = s_rem;
     __syncthreads();
   }
-  if (tid == 0) {
-    if (pass == kPassBase)
-      grp[idx].c_base = h2f(prefix);
-    else
-      project_store(idx, w, prefix, true, sc, clip, scale, stats);
-  }
+  if (tid == 0) finish(prefix);
 }
 
-hipError_t launch_bracket_finish(const void* Xv, int B, int T, int C, long long ld, int G, int W,
-                                 const int* gid, const unsigned* bhist, bool force_miss,
-                                 const Scalars& sc, int pass, GroupWork* grp, const Bracket* br,
-                                 float* clip, float* scale, tdq_group_stats* stats,
+hipError_t launch_bracket_finish(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G,
+                                 int W, const int* gid, const unsigned* bhist, const unsigned* lists,
+                                 int cap, bool force_miss, const Scalars& sc, int pass, GroupWork* grp,
+                                 const Bracket* br, float* clip, float* scale, tdq_group_stats* stats,
                                  const unsigned* img_flag, unsigned* status, hipStream_t st) {
-  const u16* X = static_cast<const u16*>(Xv);
-  const int vec_ok = ((reinterpret_cast<uintptr_t>(X) & 15) == 0 && ld % 8 == 0) ? 1 : 0;
-  hipLaunchKernelGGL(k_bracket_finish, dim3(B * G), dim3(kFinishThreads), 0, st, X, ld, T, C, G,
-                     vec_ok, gid, bhist, W, force_miss ? 1 : 0, sc, pass, grp, br, clip, scale, stats,
-                     img_flag, B, status);
+  if (dt == TDQ_F16)
+    hipLaunchKernelGGL((k_bracket_finish<u16>), dim3(B * G), dim3(kFinishThreads), 0, st,
+                       static_cast<const u16*>(X), ld, T, C, G, gid, bhist, W, lists, cap,
+                       force_miss ? 1 : 0, sc, pass, grp, br, clip, scale, stats, img_flag, B, status);
+  else
+    hipLaunchKernelGGL((k_bracket_finish<float>), dim3(B * G), dim3(kFinishThreads), 0, st,
+                       static_cast<const float*>(X), ld, T, C, G, gid, bhist, W, lists, cap,
+                       force_miss ? 1 : 0, sc, pass, grp, br, clip, scale, stats, img_flag, B, status);
   return hipGetLastError();
 }
 

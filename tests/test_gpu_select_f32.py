@@ -1,0 +1,59 @@
+"""The two-sweep rank select of binary32 input against the oracle, where it can go wrong: ties
+(all values of a set equal, a fifth of them zero, few distinct values), values close together
+far from zero (the interval is narrow), heavy tails, sets smaller than the sample, several
+batches of tokens, a bin that collects more keys than a list holds, rows at element alignment,
+the percentile base radius, 33 to 64 sets (256 bins), and the largest image of the route next
+to the smallest one past it."""
+import numpy as np
+import pytest
+
+from paper_2604_16855_amd import tdq
+
+import parity_util as U
+
+pytestmark = pytest.mark.gpu
+
+
+def _data(kind, B, T, C, seed):
+    rng = np.random.Generator(np.random.PCG64(seed))
+    X = rng.laplace(0, 1, (B, T, C)) * rng.lognormal(0, 1.0, (B, T, 1))
+    if kind == "equal":
+        X[:] = 0.75
+    elif kind == "relu":
+        X = np.maximum(X, 0.0)
+    elif kind == "levels":                       # 15 distinct magnitudes: every bin is all ties
+        X = np.round(X * 7 / np.abs(X).max(axis=2, keepdims=True)) * np.float32(0.1)
+    elif kind == "two":                          # the rank lies among ties next to other values
+        X = np.where(rng.random((B, T, C)) < 0.3, 0.5, 0.5 + rng.random((B, T, C)) * 1e-4)
+    elif kind == "offset":
+        X = 250.0 + 0.25 * rng.normal(0, 1, (B, T, C))
+    elif kind == "tails":
+        X = 20.0 * rng.standard_t(2.0, (B, T, C))
+    return X.astype(np.float32)
+
+
+@pytest.mark.parametrize("kind", ["laplace", "equal", "relu", "levels", "two", "offset", "tails"])
+@pytest.mark.parametrize("T,C,G", [(70, 40, 3), (1100, 257, 12), (4500, 130, 33), (300, 2052, 64)])
+def test_two_sweep_select(kind, T, C, G):
+    X = _data(kind, 2, T, C, T + C)
+    p = tdq.default_params(G)
+    for pct, pad, zr in ((0.0, 0, 0.2), (0.99, 1, 0.05)):
+        p.base_pct, p.zr = pct, zr
+        g = U.gpu_calibrate(X, p, ld_pad=pad)
+        assert g["status"] == 0
+        U.assert_calibration_matches(g, X, p)
+
+
+def test_interval_holds_the_rank():
+    """On ordinary data no set may need the fallback (it costs time, not accuracy)."""
+    X = _data("laplace", 4, 1024, 768, 5)
+    g = U.gpu_calibrate(X, tdq.default_params(16))
+    U.assert_calibration_matches(g, X, tdq.default_params(16))
+    assert g["exact_sets"] == 0
+
+
+@pytest.mark.parametrize("T", [4480, 4481])
+def test_largest_image_of_the_route(T):
+    X = _data("laplace", 1, T, 1024, T)
+    p = tdq.default_params(4)
+    U.assert_calibration_matches(U.gpu_calibrate(X, p), X, p)
