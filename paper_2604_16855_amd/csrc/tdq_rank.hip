@@ -34,6 +34,7 @@ constexpr int kRunLen = 32;                                     // channels per 
 constexpr int kSampleBits = 10;                                 // key bits the sample histogram resolves
 constexpr int kSweepThreads = 1024;
 constexpr int kIdRounds = 16;                                   // range keys a thread of k_sets holds
+constexpr int kListTokens = 16384;                              // most tokens listed by rank in LDS
 
 // ---------------------------------------------------------------------------
 // k_sets: one workgroup of NT threads per (image, token set).
@@ -44,7 +45,7 @@ constexpr int kIdRounds = 16;                                   // range keys a 
 //      about the mean of the set's first token (identical tokens add exact zeros);
 //   3. the sample of the set and the key interval that its order statistic says holds the
 //      k-th smallest |x|.
-// Bound by its chain of dependent steps (three trips to memory, seven barriers), not by
+// Bound by its chain of dependent steps (two trips to memory, six barriers), not by
 // traffic: every workgroup reads the image's T range keys itself, which is cheaper than a
 // kernel boundary, and everything per token sits in registers when T <= 16 NT.  Ranks are
 // counted wavefront by wavefront (any numbering of the set's tokens serves the sample), so
@@ -53,13 +54,17 @@ constexpr int kIdRounds = 16;                                   // range keys a 
 // W / 2 >= 256 keys; with fewer bins per set (more than 32 sets) 16 Ki are drawn.
 // Measured, calibration of one call (two kernels for this before: assignment, then sample):
 // [1, 7744, 64] 46.3 -> 30.9 us, [8, 121, 512] 30.7 -> 26.0, [32, 4096, 1024] 118.7 -> 108.3;
-// with 16 Ki samples 31.7 / 26.9 / 111.0.
+// with 16 Ki samples 31.7 / 26.9 / 111.0.  Then, this kernel alone: the sample's loads issued
+// before those of the moments, and the tokens listed by rank in LDS, so that only the drawn
+// ones cost divisions (T <= kListTokens; the list of a larger image would not leave LDS for
+// several workgroups): 24.8 -> 20.3 us at [32, 4096, 1024], 14.4 -> 11.9 at [1, 7744, 64].
 // ---------------------------------------------------------------------------
 // One workgroup's search of two 1024-bin LDS histograms (or twice the same) for the bin that
 // holds rank r0 of h0 and r1 of h1 (1-based, at most the histogram's total): bin[i] and the
 // count before it.  Every thread of the workgroup calls it, after a barrier that completes the
 // histograms; the results are valid after the caller's next barrier.  stot [2][NW] is scratch.
-template <int NT>
+// A bin is the sum of COPIES neighbouring words.
+template <int NT, int COPIES>
 __device__ __forceinline__ void find_two_ranks(const u32* h0, const u32* h1, u32 r0, u32 r1,
                                                u32 (*stot)[NT / 64], u32* bin, u32* before) {
   constexpr int NW = NT / 64, kBins = 1024 / NT;
@@ -67,8 +72,13 @@ __device__ __forceinline__ void find_two_ranks(const u32* h0, const u32* h1, u32
   u32 c[2][kBins], mine[2] = {0, 0};
 #pragma unroll
   for (int i = 0; i < kBins; ++i) {
-    c[0][i] = h0[tid * kBins + i];
-    c[1][i] = h1[tid * kBins + i];
+    c[0][i] = 0;
+    c[1][i] = 0;
+#pragma unroll
+    for (int k = 0; k < COPIES; ++k) {
+      c[0][i] += h0[(tid * kBins + i) * COPIES + k];
+      c[1][i] += h1[(tid * kBins + i) * COPIES + k];
+    }
     mine[0] += c[0][i];
     mine[1] += c[1][i];
   }
@@ -100,7 +110,7 @@ __device__ __forceinline__ void find_two_ranks(const u32* h0, const u32* h1, u32
 
 template <typename TX, int NT, int SM>
 __global__ __launch_bounds__(NT) void k_sets(
-    const TX* __restrict__ X, long long ld, int T, int C, int G, int W, int vec,
+    const TX* __restrict__ X, long long ld, int T, int C, int G, int W, int aligned,
     const float* __restrict__ r, const double* __restrict__ mean, const double* __restrict__ m2,
     int* __restrict__ gid, Scalars sc, int pass, int keep_base, GroupWork* __restrict__ grp,
     Bracket* __restrict__ br, u32* __restrict__ bhist, u32* __restrict__ lists, int cap,
@@ -110,11 +120,14 @@ __global__ __launch_bounds__(NT) void k_sets(
   constexpr int V = Elem<TX>::V;
   constexpr int kSampleRuns = SM / kRunLen;
   constexpr int kSampleTokens = kSampleRuns;         // at most one run per token
-  __shared__ int sel[kSampleTokens];                 // drawn token of every stratum
-  __shared__ long long run_base[kSampleRuns];        // element offset of every run's first channel
-  __shared__ int run_len[kSampleRuns];               // channels of the run (<= kRunLen)
-  __shared__ u32 shist[F16 ? 1 : 3][1 << kSampleBits];   // sample histogram over the top key bits;
-                                                     // binary32: then two over the next ones
+  // binary32 values of one magnitude share their top bits: four copies of the first histogram
+  // keep the lanes of a wavefront from all adding to one word
+  constexpr int kCopies = F16 ? 1 : 4;
+  extern __shared__ unsigned short order[];          // the set's tokens by rank (T <= kListTokens)
+  __shared__ int sel[kSampleTokens];                 // more tokens: the one drawn of every stratum
+  __shared__ __attribute__((aligned(16))) u32 shist[kCopies << kSampleBits];   // sample histogram
+                                                     // over the top key bits
+  __shared__ u32 snext[F16 ? 1 : 2][F16 ? 1 : 1 << kSampleBits];   // binary32: two over the next ones
   __shared__ u32 s_bin[4], s_before[4];
   __shared__ u32 s_min[NW], s_max[NW], wtot[NW], stot[2][NW], s_cmax[NW];
   __shared__ double s_s1[NW], s_s2[NW];
@@ -136,10 +149,14 @@ __global__ __launch_bounds__(NT) void k_sets(
       kv[u] = t < T ? __float_as_uint(rb[t]) : kDead;
     }
   };
+  // (the rounds of a batch that hold tokens; the same for every thread)
+  auto in_use = [&](int t0, int u) { return t0 + u * NT < T; };
 
   // ---- 1: key range of the image, key interval of the set
   load_keys(0);
-  for (int i = tid; i < (int)(sizeof(shist) / sizeof(u32)); i += NT) (&shist[0][0])[i] = 0;
+  for (int i = tid; i < (kCopies << kSampleBits); i += NT) shist[i] = 0;
+  if (!F16)
+    for (int i = tid; i < (int)(sizeof(snext) / sizeof(u32)); i += NT) (&snext[0][0])[i] = 0;
   u32 kinv = 0, kmax = 0;                            // largest ~key, largest key
   for (int t0 = 0;;) {
 #pragma unroll
@@ -185,7 +202,10 @@ __global__ __launch_bounds__(NT) void k_sets(
   for (int t0 = 0; t0 < T; t0 += kIdRounds * NT) {
     if (!one_batch) load_keys(t0);
 #pragma unroll
-    for (int u = 0; u < kIdRounds; ++u) wcount += (u32)__popcll(__ballot(in_set(kv[u])));
+    for (int u = 0; u < kIdRounds; ++u) {
+      if (!in_use(t0, u)) break;
+      wcount += (u32)__popcll(__ballot(in_set(kv[u])));
+    }
   }
   if (lane == 0) wtot[wave] = wcount;
   __syncthreads();
@@ -215,21 +235,30 @@ __global__ __launch_bounds__(NT) void k_sets(
   // kSampleTokens strata) and one token is drawn from each at a hashed position: a regular
   // stride would alias with any period the token sequence has (image rows).  Of each drawn
   // token `rpt` runs of kRunLen consecutive channels are read, the first at a hashed offset,
-  // so that all channels are represented; a row that fits is read whole.
+  // so that all channels are represented; a row that fits is read whole, up to the last
+  // V - 1 channels of a row that is not made of whole 16-byte pieces.
   const int tokens = (int)tokens_u;
   const int stride = (tokens + kSampleTokens - 1) / kSampleTokens;
   const int n_sel = (tokens + stride - 1) / stride;         // <= kSampleTokens
-  const int row_runs = (C + kRunLen - 1) / kRunLen;
+  const int Cv = C >= V ? C - C % V : C;                    // channels in whole pieces
+  const int row_runs = (Cv + kRunLen - 1) / kRunLen;
   int rpt = kSampleRuns / n_sel;                            // runs per drawn token, >= 1
   rpt = rpt < row_runs ? rpt : row_runs;
-  const int cw = rpt == row_runs ? C : rpt * kRunLen;       // channels read per drawn token
+  const int cw = rpt == row_runs ? Cv : rpt * kRunLen;      // channels read per drawn token
   const int n_runs = n_sel * rpt;                           // <= kSampleRuns
   const long long m = (long long)n_sel * cw;                // sample size, <= SM
+  const bool listed = T <= kListTokens;
+  auto pick_of = [&](u32 stratum) {                         // rank of the token drawn from a stratum
+    const u32 first = stratum * (u32)stride;
+    const u32 len = (u32)tokens - first < (u32)stride ? (u32)tokens - first : (u32)stride;
+    return first + (((stratum + 1u) * 2246822519u + (u32)idx * 3266489917u) >> 12) % len;
+  };
 
   for (int t0 = 0; t0 < T; t0 += kIdRounds * NT) {
     if (!one_batch) load_keys(t0);
 #pragma unroll
     for (int u = 0; u < kIdRounds; ++u) {
+      if (!in_use(t0, u)) break;
       const bool mine = in_set(kv[u]);
       const unsigned long long mask = __ballot(mine);
       if (mask == 0) continue;                              // uniform over the wavefront
@@ -237,15 +266,12 @@ __global__ __launch_bounds__(NT) void k_sets(
         const int t = t0 + u * NT + tid;
         const u32 rank = running + (u32)__popcll(mask & ((1ull << lane) - 1ull));
         gb[t] = j;
-        if (rank == 0) s_first = t;
-        if (stride == 1) {
-          sel[rank] = t;
+        if (listed) {
+          order[rank] = (unsigned short)t;
         } else {
-          const u32 stratum = rank / (u32)stride, first = stratum * (u32)stride;
-          const u32 len = (u32)tokens - first < (u32)stride ? (u32)tokens - first : (u32)stride;
-          const u32 pick =
-              first + (((stratum + 1u) * 2246822519u + (u32)idx * 3266489917u) >> 12) % len;
-          if (rank == pick) sel[stratum] = t;
+          if (rank == 0) s_first = t;
+          const u32 stratum = rank / (u32)stride;
+          if (rank == pick_of(stratum)) sel[stratum] = t;
         }
       }
       running += (u32)__popcll(mask);
@@ -253,34 +279,44 @@ __global__ __launch_bounds__(NT) void k_sets(
   }
   __syncthreads();
 
+  // The sample's loads first, in flight together with those of the moments.  Pieces of V
+  // channels: piece p = NT e + tid is part p % PPR of run p / PPR, so a wavefront's load
+  // instruction fetches whole runs of 64 (128) bytes; they are issued unconditionally, from a
+  // valid address where there is no piece.
+  constexpr int kKeyBits = F16 ? 15 : 31;
+  constexpr int kKeys = SM / NT;                       // sampled keys per thread
+  constexpr int kPieces = kKeys / V, PPR = kRunLen / V;
+  uint4 v[kPieces];
+  bool live[kPieces];
+  // offsets in steps of whole pieces where the rows consist of aligned ones
+  const u32 step = aligned ? (u32)V : 1u, offsets = (u32)(C - cw) / step + 1u;
+#pragma unroll
+  for (int e = 0; e < kPieces; ++e) {
+    const u32 p = (u32)(e * NT + tid), q = p / PPR, part = p % PPR;
+    const u32 slot = q / (u32)rpt, run = q - slot * (u32)rpt;
+    const int at = (int)(run * kRunLen + part * V);    // channel inside the part of the row read
+    live[e] = q < (u32)n_runs && at < cw;
+    const u32 sl = live[e] ? slot : 0u;
+    const int t = !listed ? sel[sl] : order[stride == 1 ? sl : pick_of(sl)];
+    const u32 off = ((u32)t * 2654435761u >> 8) % offsets * step;
+    const TX* src = X + ((long long)b * T + t) * ld + (live[e] ? (int)off + at : 0);
+    if (C >= V) {
+      v[e] = load16(src);
+    } else {                                           // rows shorter than a piece
+      TX x[V];
+#pragma unroll
+      for (int i = 0; i < V; ++i) x[i] = src[i < C ? i : 0];
+      v[e] = *reinterpret_cast<const uint4*>(x);
+    }
+  }
+
   // Moments of the set about the mean of its first token (zero if that is not finite: the
-  // image's results are then undefined anyway and its flag is raised).  The loads are in
-  // flight while the run table is made.
-  const int first_token = s_first;
+  // image's results are then undefined anyway and its flag is raised).
+  const int first_token = listed ? order[0] : s_first;
   double piv = meanb[first_token];
   const double cn = (double)C;
   double a1 = 0.0, a2 = 0.0;
   u32 cmax = 0;
-  // table of runs, so that the load loop below has no division in it
-  for (int q = tid; q < kSampleRuns; q += NT) {
-    long long rbase = 0;
-    int rl = 0;
-    if (q < n_runs) {
-      const int slot = q / rpt, run = q - slot * rpt;
-      const int t = sel[slot];
-      // (whole 16-byte pieces when the rows consist of them: C, cw and the offset are then
-      // multiples of V channels)
-      const u32 off = vec ? (((u32)t * 2654435761u >> 8) % (u32)((C - cw) / V + 1)) * (u32)V
-                          : ((u32)t * 2654435761u >> 8) % (u32)(C - cw + 1);
-      rbase = ((long long)b * T + t) * ld + off + run * kRunLen;
-      rl = cw - run * kRunLen;
-      rl = rl < kRunLen ? rl : kRunLen;
-    } else {
-      rbase = ((long long)b * T + sel[0]) * ld;       // a valid address; the key is discarded
-    }
-    run_base[q] = rbase;
-    run_len[q] = rl;
-  }
   piv = (piv - piv == 0.0) ? piv : 0.0;
   for (int t0 = 0; t0 < T; t0 += kIdRounds * NT) {
     if (!one_batch) load_keys(t0);
@@ -288,6 +324,7 @@ __global__ __launch_bounds__(NT) void k_sets(
     // reads the first token's entry, which is not added)
 #pragma unroll
     for (int h = 0; h < kIdRounds; h += kIdRounds / 2) {
+      if (!in_use(t0, h)) break;
       double mv[kIdRounds / 2], qv[kIdRounds / 2];
 #pragma unroll
       for (int u = 0; u < kIdRounds / 2; ++u) {
@@ -316,50 +353,22 @@ __global__ __launch_bounds__(NT) void k_sets(
   a2 = group_sum_f64<64>(a2);
   cmax = group_max_u32<64>(cmax);
   if (lane == 63) { s_s1[wave] = a1; s_s2[wave] = a2; s_cmax[wave] = cmax; }
-  __syncthreads();
 
   // ---- 3: the sample.  Every live key adds one to an LDS histogram of its top kSampleBits
-  // bits.  Loads are issued unconditionally (from a clamped, valid address) so that they
-  // overlap.
-  constexpr int kKeyBits = F16 ? 15 : 31;
-  constexpr int kKeys = SM / NT;                       // sampled keys per thread
+  // bits.
   u32 key[kKeys];
-  if (vec) {
-    // 16-byte pieces of V channels: piece p = NT e + tid is part p % PPR of run p / PPR, so a
-    // wavefront's load instruction fetches whole runs of 64 (128) bytes; a run's pieces are
-    // all live or (runs past the end of the table) all dead.
-    constexpr int kPieces = kKeys / V, PPR = kRunLen / V;
-    uint4 v[kPieces];
-    bool live[kPieces];
 #pragma unroll
-    for (int e = 0; e < kPieces; ++e) {
-      const int p = e * NT + tid;
-      const int q = p / PPR, part = p % PPR;
-      live[e] = part * V < run_len[q];
-      v[e] = *reinterpret_cast<const uint4*>(X + run_base[q] + (live[e] ? part * V : 0));
-    }
+  for (int e = 0; e < kPieces; ++e) {
+    TX x[V];
+    Elem<TX>::unpack(v[e], x);
 #pragma unroll
-    for (int e = 0; e < kPieces; ++e) {
-      TX x[V];
-      Elem<TX>::unpack(v[e], x);
-#pragma unroll
-      for (int i = 0; i < V; ++i) key[e * V + i] = live[e] ? Elem<TX>::key(x[i]) : kDead;
-    }
-  } else {
-    // element e of lane l of wavefront w is channel l % 32 of run 2 NW e + 2 w + l / 32
-    const int half = lane >> 5, cl = lane & 31;
-#pragma unroll
-    for (int e = 0; e < kKeys; ++e) {
-      const int q = e * (2 * NW) + 2 * wave + half;
-      const int rl = run_len[q];
-      const int ch = cl < rl ? cl : (rl > 0 ? rl - 1 : 0);
-      const u32 k = Elem<TX>::key(X[run_base[q] + ch]);
-      key[e] = cl < rl ? k : kDead;
-    }
+    for (int i = 0; i < V; ++i) key[e * V + i] = live[e] && i < C ? Elem<TX>::key(x[i]) : kDead;
   }
 #pragma unroll
   for (int e = 0; e < kKeys; ++e)
-    if (key[e] != kDead) atomicAdd(&shist[0][key[e] >> (kKeyBits - kSampleBits)], 1u);
+    if (key[e] != kDead)
+      atomicAdd(&shist[(key[e] >> (kKeyBits - kSampleBits)) * kCopies + (lane & (kCopies - 1))], 1u);
+  __syncthreads();
 
   // the set's working record: n, base radius, sigma, rank of this pass (binary64)
   GroupWork w;
@@ -385,7 +394,6 @@ __global__ __launch_bounds__(NT) void k_sets(
     w.c_base = keep_base ? grp[idx].c_base : __uint_as_float(km);
     grp[idx] = w;
   }
-  __syncthreads();
 
   // Sample rank that corresponds to rank k of the set.
   long long rk = (long long)((double)w.k_rem / n * (double)m + 0.5);
@@ -398,7 +406,7 @@ __global__ __launch_bounds__(NT) void k_sets(
     // the histogram bin that holds that order statistic (the low key bits do not matter to
     // the interval): v <= estimate < v + 2^(15 - kSampleBits), the interval of W one-key bins
     // is centred on the middle
-    find_two_ranks<NT>(shist[0], shist[0], (u32)rk, (u32)rk, stot, s_bin, s_before);
+    find_two_ranks<NT, 1>(shist, shist, (u32)rk, (u32)rk, stot, s_bin, s_before);
     __syncthreads();
     const u32 mid = (s_bin[0] << (15 - kSampleBits)) + (1u << (14 - kSampleBits));
     e.lo = mid > (u32)W / 2 ? mid - (u32)W / 2 : 0u;
@@ -410,17 +418,17 @@ __global__ __launch_bounds__(NT) void k_sets(
     const double pq = (double)rk / (double)m;
     const long long dr = (long long)(6.0 * sqrt((double)rk * (1.0 - pq))) + 2;
     const u32 r0 = (u32)(rk - dr < 1 ? 1 : rk - dr), r1 = (u32)(rk + dr > m ? m : rk + dr);
-    find_two_ranks<NT>(shist[0], shist[0], r0, r1, stot, s_bin, s_before);
+    find_two_ranks<NT, kCopies>(shist, shist, r0, r1, stot, s_bin, s_before);
     __syncthreads();
     const u32 b0 = s_bin[0], b1 = s_bin[1];
 #pragma unroll
     for (int i = 0; i < kKeys; ++i) {
       const u32 top = key[i] >> 21, next = (key[i] >> 11) & 1023u;
-      if (key[i] != kDead && top == b0) atomicAdd(&shist[1][next], 1u);
-      if (key[i] != kDead && top == b1) atomicAdd(&shist[2][next], 1u);
+      if (key[i] != kDead && top == b0) atomicAdd(&snext[0][next], 1u);
+      if (key[i] != kDead && top == b1) atomicAdd(&snext[1][next], 1u);
     }
     __syncthreads();
-    find_two_ranks<NT>(shist[1], shist[2], r0 - s_before[0], r1 - s_before[1], stot, s_bin + 2,
+    find_two_ranks<NT, 1>(snext[0], snext[1], r0 - s_before[0], r1 - s_before[1], stot, s_bin + 2,
                        s_before + 2);
     __syncthreads();
     const u32 n0 = s_bin[2], n1 = s_bin[3];
@@ -437,10 +445,10 @@ static void sets_t(const TX* X, int B, int T, int C, long long ld, int G, int W,
                    bool keep_base, GroupWork* grp, Bracket* br, unsigned* bhist, unsigned* lists,
                    int cap, unsigned* img_flag, unsigned* status, hipStream_t st) {
   constexpr int V = Elem<TX>::V;
-  // 16-byte sample loads need rows of whole, aligned 16-byte pieces
-  const int vec = ((reinterpret_cast<uintptr_t>(X) & 15) == 0 && ld % V == 0 && C % V == 0) ? 1 : 0;
+  const int aligned = ((reinterpret_cast<uintptr_t>(X) & 15) == 0 && ld % V == 0 && C % V == 0) ? 1 : 0;
+  const size_t order_bytes = T <= kListTokens ? (size_t)T * sizeof(unsigned short) : 0;
 #define TDQ_SETS_SM(NT, SM)                                                                        \
-  hipLaunchKernelGGL((k_sets<TX, NT, SM>), dim3(G, B), dim3(NT), 0, st, X, ld, T, C, G, W, vec, r, \
+  hipLaunchKernelGGL((k_sets<TX, NT, SM>), dim3(G, B), dim3(NT), order_bytes, st, X, ld, T, C, G, W, aligned, r, \
                      mean, m2, gid, sc, pass, keep_base ? 1 : 0, grp, br, bhist, lists, cap,       \
                      img_flag, status)
 #define TDQ_SETS(NT)                                                           \
