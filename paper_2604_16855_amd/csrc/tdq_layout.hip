@@ -110,7 +110,7 @@ hipError_t launch_tokenize_chw(const void* X, tdq_dtype dt, int B, int C, int T,
 // (r_t = max_c |x|, mean_t, M2_t = sum_c (x - mean_t)^2; Sec. 4.2), so a convolutional input costs
 // the token-set path one extra write of X, not an extra read and write.  A workgroup
 // owns TT consecutive tokens of one image and walks the channel axis in tiles of 64:
-// every thread keeps the partial statistics of its 4 tokens across the tiles; at the end
+// every thread keeps the partial statistics of its 2 tokens across the tiles; at the end
 // the lanes that share a token (adjacent ones) are reduced with DPP.  The sums are taken
 // about a per-token pivot taken from the first tile, see "Moments" in tdq_device.hpp:
 // binary32 input, the token's first channel; binary16 input, the mean of its first
@@ -119,18 +119,27 @@ hipError_t launch_tokenize_chw(const void* X, tdq_dtype dt, int B, int C, int T,
 // sigma_t sqrt(C / 64) of the token's mean (Cauchy-Schwarz), which bounds what the
 // binary32 partial sums can cost its M2 at (1 + C / 64) * 3 * 2^-24 per partial.
 // ---------------------------------------------------------------------------
+// Tiles of 64 channels x 128 bytes of tokens: what bounds this sweep on ordinary maps is the
+// chain of tiles a workgroup walks, so the tokens are cut finely and a thread reads two
+// neighbouring binary16 tokens with one LDS word.  [8, 320, 44, 44] binary16: this kernel 18.6
+// us with 256 bytes of tokens, 11.7 so, 14.2 / 18.3 with 128 / 256 channels per tile; the
+// whole calibration of [4, 4096, 64, 64] 225 -> 138 us, of [32, 1024, 64, 64] 195 -> 190.
+constexpr int kStatsTileC = 64;                // channels per tile
+
 template <typename T>
 __global__ __launch_bounds__(256) void k_tokenize_stats_chw(
     const T* __restrict__ X, long long ld_c, long long ld_b, int C, int T_, T* __restrict__ Xt,
     long long ld_xt, int vin_ok, int vout_ok, float* __restrict__ r, double* __restrict__ mean,
     double* __restrict__ m2) {
+  constexpr bool F16 = sizeof(T) == 2;
   constexpr int E = 16 / (int)sizeof(T);
-  constexpr int TC = 64;
-  constexpr int TT = 16 * E;
-  constexpr int PITCH = TT + 8 / (int)sizeof(T);
+  constexpr int TC = kStatsTileC;
+  constexpr int TT = 8 * E;                  // 128 bytes of every channel
+  constexpr int PITCH = TT + 4 / (int)sizeof(T);   // one bank further per row
   constexpr int PQ = TC / E;                 // lanes per token
-  constexpr int TPP = 256 / PQ;              // tokens per pass
-  constexpr int NP = TT / TPP;               // passes = tokens per thread (4)
+  constexpr int NP = TT * PQ / 256;          // tokens per thread (2)
+  constexpr int TPW = F16 ? 2 : 1;           // tokens a thread reads together (one 32-bit word)
+  constexpr int LOADS = TC / 32;             // 16-byte loads per thread and tile
   __shared__ __attribute__((aligned(16))) T tile[TC][PITCH];
 
   const int t0 = blockIdx.x * TT, b = blockIdx.y;
@@ -145,12 +154,12 @@ __global__ __launch_bounds__(256) void k_tokenize_stats_chw(
   for (int i = 0; i < NP; ++i) { kmax[i] = 0; a1[i] = 0.0; a2[i] = 0.0; P[i] = 0; }
 
   // the next tile's global loads are in flight while the current one is processed
-  const int lp = tid & 15, ltok = t0 + (tid & 15) * E;
-  uint4 stage[4];
+  const int lp = tid & 7, ltok = t0 + lp * E;
+  uint4 stage[LOADS];
   auto load_tile = [&](int c0) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int c = c0 + (tid >> 4) + 16 * i;
+    for (int i = 0; i < LOADS; ++i) {
+      const int c = c0 + (tid >> 3) + 32 * i;
       if (c < C && vin_ok && ltok + E <= T_) {
         stage[i] = *reinterpret_cast<const uint4*>(xb + (long long)c * ld_c + ltok);
       } else {
@@ -162,75 +171,90 @@ __global__ __launch_bounds__(256) void k_tokenize_stats_chw(
       }
     }
   };
+  // token i of this thread: tokens TPW (tid / PQ + ...) + 0 .. TPW - 1 of every group
+  auto token = [&](int i) { return TPW * (tid / PQ + (256 / PQ) * (i / TPW)) + i % TPW; };
   load_tile(0);
   for (int c0 = 0; c0 < C; c0 += TC) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      uint2* d = reinterpret_cast<uint2*>(&tile[(tid >> 4) + 16 * i][lp * E]);
-      d[0] = make_uint2(stage[i].x, stage[i].y);
-      d[1] = make_uint2(stage[i].z, stage[i].w);
+    for (int i = 0; i < LOADS; ++i) {
+      u32* d = reinterpret_cast<u32*>(&tile[(tid >> 3) + 32 * i][lp * E]);
+      d[0] = stage[i].x;
+      d[1] = stage[i].y;
+      d[2] = stage[i].z;
+      d[3] = stage[i].w;
     }
     __syncthreads();
     if (c0 + TC < C) load_tile(c0 + TC);
     const int c = c0 + q * E;
-    if (c0 == 0) {                               // the tokens' pivots, from the first tile
 #pragma unroll
-      for (int i = 0; i < NP; ++i) {
-        const int tl = tid / PQ + TPP * i;
-        if constexpr (sizeof(T) == 2) {
-          float sum = 0.f;                       // channels past C are zeros in the tile
+    for (int g = 0; g < NP / TPW; ++g) {
+      // E channels of TPW neighbouring tokens
+      u32 w[E];
 #pragma unroll
-          for (int k = 0; k < E; ++k) sum += Elem<T>::val(tile[q * E + k][tl]);
-          sum = xor_reduce_sum<PQ, float>(sum);  // the same bits in all lanes of the token
-          P[i] = sum / (float)(C < TC ? C : TC);
-        } else {
-          P[i] = (double)Elem<T>::val(tile[0][tl]);
-        }
-      }
-    }
+      for (int k = 0; k < E; ++k)
+        w[k] = *reinterpret_cast<const u32*>(&tile[q * E + k][token(g * TPW)]);
 #pragma unroll
-    for (int i = 0; i < NP; ++i) {
-      const int tl = tid / PQ + TPP * i;
-      const int tok = t0 + tl;
-      __attribute__((aligned(16))) T v[E];
+      for (int h = 0; h < TPW; ++h) {
+        const int i = g * TPW + h;
+        const int tok = t0 + token(i);
+        u32 p4[4];                                 // the token's E channels, packed
+        if constexpr (F16) {
 #pragma unroll
-      for (int k = 0; k < E; ++k) v[k] = tile[q * E + k][tl];
-      // channels beyond C are zeros in the tile: they do not change the maximum, and are
-      // kept out of the sums
-      if constexpr (sizeof(T) == 2) {
-        // as in the token-major statistics sweep: the 8 differences and their squares are
-        // first summed in binary32, then accumulated in binary64
-        float p1 = 0.f, p2 = 0.f;
-#pragma unroll
-        for (int k = 0; k < E; ++k) {
-          const float f = Elem<T>::val(v[k]);
-          const u32 key = Elem<T>::key(v[k]);
-          kmax[i] = key > kmax[i] ? key : kmax[i];
-          const float d = c + k < C ? f - P[i] : 0.f;
-          p1 += d;
-          p2 = __builtin_fmaf(d, d, p2);
-        }
-        a1[i] += (double)p1;
-        a2[i] += (double)p2;
-      } else {
-#pragma unroll
-        for (int k = 0; k < E; ++k) {
-          const double f = (double)Elem<T>::val(v[k]);
-          const u32 key = Elem<T>::key(v[k]);
-          kmax[i] = key > kmax[i] ? key : kmax[i];
-          const double d = c + k < C ? f - P[i] : 0.0;
-          a1[i] += d;
-          a2[i] = fma(d, d, a2[i]);
-        }
-      }
-      if (tok < T_) {
-        T* dst = Xt + ((long long)b * T_ + tok) * ld_xt + c;
-        if (vout_ok && c + E <= C) {
-          *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(v);
+          for (int k = 0; k < 4; ++k)
+            p4[k] = __builtin_amdgcn_perm(w[2 * k + 1], w[2 * k], h == 0 ? 0x05040100u : 0x07060302u);
         } else {
 #pragma unroll
-          for (int k = 0; k < E; ++k)
-            if (c + k < C) dst[k] = v[k];
+          for (int k = 0; k < 4; ++k) p4[k] = w[k];
+        }
+        const uint4 pk = make_uint4(p4[0], p4[1], p4[2], p4[3]);
+        T v[E];
+        Elem<T>::unpack(pk, v);
+        if (c0 == 0) {                             // the token's pivot, from the first tile
+          if constexpr (F16) {
+            float sum = 0.f;                       // channels past C are zeros in the tile
+#pragma unroll
+            for (int k = 0; k < E; ++k) sum += Elem<T>::val(v[k]);
+            sum = xor_reduce_sum<PQ, float>(sum);  // the same bits in all lanes of the token
+            P[i] = sum / (float)(C < TC ? C : TC);
+          } else {
+            P[i] = (double)Elem<T>::val(tile[0][token(i)]);
+          }
+        }
+        // channels beyond C are zeros in the tile: they do not change the maximum, and are
+        // kept out of the sums
+        if constexpr (F16) {
+          // as in the token-major statistics sweep: the 8 differences and their squares are
+          // first summed in binary32, then accumulated in binary64
+          float p1 = 0.f, p2 = 0.f;
+#pragma unroll
+          for (int k = 0; k < E; ++k) {
+            const u32 key = Elem<T>::key(v[k]);
+            kmax[i] = key > kmax[i] ? key : kmax[i];
+            const float d = c + k < C ? Elem<T>::val(v[k]) - P[i] : 0.f;
+            p1 += d;
+            p2 = __builtin_fmaf(d, d, p2);
+          }
+          a1[i] += (double)p1;
+          a2[i] += (double)p2;
+        } else {
+#pragma unroll
+          for (int k = 0; k < E; ++k) {
+            const u32 key = Elem<T>::key(v[k]);
+            kmax[i] = key > kmax[i] ? key : kmax[i];
+            const double d = c + k < C ? (double)Elem<T>::val(v[k]) - P[i] : 0.0;
+            a1[i] += d;
+            a2[i] = fma(d, d, a2[i]);
+          }
+        }
+        if (tok < T_) {
+          T* dst = Xt + ((long long)b * T_ + tok) * ld_xt + c;
+          if (vout_ok && c + E <= C) {
+            *reinterpret_cast<uint4*>(dst) = pk;
+          } else {
+#pragma unroll
+            for (int k = 0; k < E; ++k)
+              if (c + k < C) dst[k] = v[k];
+          }
         }
       }
     }
@@ -241,7 +265,7 @@ __global__ __launch_bounds__(256) void k_tokenize_stats_chw(
     const u32 km = group_max_u32<PQ>(kmax[i]);
     const double t1 = group_sum_f64<PQ>(a1[i]);
     const double t2 = group_sum_f64<PQ>(a2[i]);
-    const int tok = t0 + tid / PQ + TPP * i;
+    const int tok = t0 + token(i);
     if (q == PQ - 1 && tok < T_) {               // the group's last lane holds the totals
       const long long row = (long long)b * T_ + tok;
       double mu, qq;
@@ -261,7 +285,7 @@ static hipError_t tokenize_stats_t(const T* X, int B, int C, int T_, long long l
   const int vin_ok =
       ((reinterpret_cast<uintptr_t>(X) & 15) == 0 && ld_c % E == 0 && ld_b % E == 0) ? 1 : 0;
   const int vout_ok = ((reinterpret_cast<uintptr_t>(Xt) & 15) == 0 && ld_xt % E == 0) ? 1 : 0;
-  const dim3 grid((unsigned)((T_ + 16 * E - 1) / (16 * E)), (unsigned)B);
+  const dim3 grid((unsigned)((T_ + 8 * E - 1) / (8 * E)), (unsigned)B);
   hipLaunchKernelGGL((k_tokenize_stats_chw<T>), grid, dim3(256), 0, st, X, ld_c, ld_b, C, T_, Xt,
                      ld_xt, vin_ok, vout_ok, r, mean, m2);
   return hipGetLastError();

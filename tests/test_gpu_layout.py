@@ -171,3 +171,22 @@ def test_token_set_calibration_reads_conv_layout(B, C, H, W, dtype, G):
     exact = np.array_equal(g["scale"], osc) and np.array_equal(g["clip"], oc)
     U.assert_codes_match(U.unpack_device_codes(Q, C), q_ref, Xt_ref, oc[rows, og].reshape(-1),
                          osc[rows, og].reshape(-1), exact)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+@pytest.mark.parametrize("B,C,H,W", [(2, 1, 1, 1), (1, 63, 3, 21), (2, 64, 8, 8), (1, 65, 5, 13), (3, 130, 1, 129),
+                                     (2, 40, 9, 7), (1, 200, 16, 40)])
+def test_fused_statistics_tile_edges(B, C, H, W, dtype):
+    """One tile, one channel or token past a tile, odd token counts (a thread takes two tokens
+    at a time), maps that allow 16-byte loads and maps that do not."""
+    rng = np.random.Generator(np.random.PCG64(B + 3 * C + H * W))
+    X = (rng.laplace(0, 1, (B, C, H, W)) * rng.lognormal(0, 1, (B, 1, H, W)) + 2.0)
+    X = X.astype(np.float16 if dtype == "f16" else np.float32)
+    p = tdq.default_params(5)
+    Xt, gid, clip, scale, stats, ws = tdq.tdq_calibrate_groups_chw(torch.from_numpy(X).to(U.dev()), p, want_stats=True)
+    torch.cuda.synchronize()
+    ref = O.tokenize_chw(X)
+    assert np.array_equal(Xt.cpu().numpy(), ref)
+    g = dict(gid=gid.cpu().numpy(), clip=clip.cpu().numpy(), scale=scale.cpu().numpy(),
+             stats=tdq.stats_to_numpy(stats))
+    U.assert_calibration_matches(g, ref, p)
