@@ -3,14 +3,15 @@
 // followed by tdq_quantize_act compute, in ONE kernel, one workgroup of 1024 threads per
 // image, the steps separated by workgroup barriers instead of kernel boundaries:
 //   A  per-token range, mean and centred second moment  (Sec. 4.2)
-//   B  token -> token set, per-set sums                 (assign_tokens)
+//   B  token -> token set, per-set sums                 (assign_tokens; small images: a
+//      wavefront per set)
 //   C  per set: n, sigma, rank k                        (merge_partials)
 //   D  k-th smallest |x| of every set: radix select on the magnitude bit pattern, 8 bits
 //      per level, LDS histogram [G][256]                (Eq. zr_constraint, exact)
 //   E  projection                                       (Eq. dcrp)
 //   F  quantize + pack                                  (Eqs. clipx, dequant)
 // X is read once per step that needs it (A, every level of D, F) and comes from the
-// cache after the first.  Same arithmetic as the multi-kernel path wherever a result is
+// cache after the first; an image that fits the workgroup's registers is read once.  Same arithmetic as the multi-kernel path wherever a result is
 // rounded: group ids, thresholds and codes are integer work, sigma is binary64.
 #include "tdq_device.hpp"
 
@@ -19,7 +20,18 @@ namespace tdq {
 constexpr int kFusedThreads = 1024;
 constexpr int kFusedMaxG = TDQ_FUSED_MAX_GROUPS;
 
+// REG: the image fits the workgroup's registers (4 pieces of 16 bytes per thread, rows of
+// whole aligned pieces, at most 1024 bytes binary16 / 2048 binary32, at most 1024 tokens): X
+// is then read once, the tokens' statistics stay in LDS, and every set is formed by a
+// wavefront of its own (key intervals as in k_sets) instead of set by set within batches of
+// tokens.  196 x 64 binary32: 20.3 us with every step through memory, 16.3
+// so (X in registers alone 17.8; the top digit counted in four copies of the histogram: 16.7).
+constexpr int kRegPieces = 4;
+constexpr int kRegTokens = 1024;
 template <typename T>
+constexpr int kRegPPL = sizeof(T) == 2 ? 1 : 2;  // pieces of a row per lane
+
+template <typename T, bool REG>
 __global__ __launch_bounds__(kFusedThreads) void k_fused_small(
     const T* __restrict__ X, long long ld, int T_, int C, int G, int L, int vec_ok, int q_vec_ok,
     Scalars sc, int with_base, float* __restrict__ r, double* __restrict__ mean,
@@ -30,9 +42,13 @@ __global__ __launch_bounds__(kFusedThreads) void k_fused_small(
   constexpr bool F16 = sizeof(T) == 2;
   constexpr int NW = kFusedThreads / 64;
   constexpr int kLevels = F16 ? 2 : 4;
-  __shared__ SetAcc wacc[NW * kFusedMaxG];
+  __shared__ SetAcc wacc[REG ? 1 : NW * kFusedMaxG];
+  __shared__ u32 s_key[REG ? kRegTokens : 1];
+  __shared__ double s_mean[REG ? kRegTokens : 1], s_m2[REG ? kRegTokens : 1];
+  __shared__ unsigned char s_gid[REG ? kRegTokens : 1];      // set ids (< kFusedMaxG)
   __shared__ u32 hist[kFusedMaxG * 256];
   __shared__ GroupWork grp[kFusedMaxG];
+  __shared__ SetAcc s_set[REG ? kFusedMaxG : 1];
   __shared__ u32 s_min[NW], s_max[NW], s_lohi[2];
 
   const int b = blockIdx.x;
@@ -45,20 +61,42 @@ __global__ __launch_bounds__(kFusedThreads) void k_fused_small(
   double* m2b = m2 + (long long)b * T_;
   int* gb = gid + (long long)b * T_;
   const int nvec = vec_ok ? C / V : 0;
+  // up to half of the most sets there are two histograms, and both start clear
+  const bool two = 2 * G <= kFusedMaxG;
+  for (int i = tid; i < (two ? G * 512 : 0); i += kFusedThreads) hist[i] = 0;
+
+  // pieces lr, lr + L of rows rsub, rsub + rpp, ...
+  constexpr int PPL = kRegPPL<T>, RPT = REG ? kRegPieces / PPL : 1;
+  uint4 xr[REG ? kRegPieces : 1];
+  if constexpr (REG) {
+#pragma unroll
+    for (int i = 0; i < RPT; ++i)
+#pragma unroll
+      for (int k = 0; k < PPL; ++k) {
+        const int row = rsub + rpp * i, v = lr + L * k;
+        xr[i * PPL + k] = *reinterpret_cast<const uint4*>(
+            Xb + (long long)(row < T_ ? row : T_ - 1) * ld + (long long)(v < nvec ? v : 0) * V);
+      }
+  }
 
   // ---- A: rows are shared out to groups of L lanes; every lane runs every pass (the
   // reductions are lane exchanges), rows past the end are clamped and not stored
-  for (int row0 = 0; row0 < T_; row0 += rpp) {
-    const int row = row0 + rsub;
+  auto row_stats = [&](int row, const uint4* px) {
     const bool valid = row < T_;
     const T* xp = Xb + (long long)(valid ? row : T_ - 1) * ld;
     u32 kmax = 0;
     double a1 = 0.0, a2 = 0.0;
     // binary64 sums about the row's first value (any value of the row is a good enough
     // pivot in binary64; see "Moments" in tdq_device.hpp)
-    const double P = (double)Elem<T>::val(xp[0]);
-    for (int v = lr; v < nvec; v += L) {
-      const uint4 q = *reinterpret_cast<const uint4*>(xp + (long long)v * V);
+    double P;
+    if constexpr (REG) {
+      T e[V];
+      Elem<T>::unpack(px[0], e);
+      P = __shfl((double)Elem<T>::val(e[0]), (int)(threadIdx.x & 63) & ~(L - 1), 64);
+    } else {
+      P = (double)Elem<T>::val(xp[0]);
+    }
+    auto add = [&](const uint4& q) {
       T e[V];
       Elem<T>::unpack(q, e);
 #pragma unroll
@@ -69,14 +107,21 @@ __global__ __launch_bounds__(kFusedThreads) void k_fused_small(
         a1 += d;
         a2 = fma(d, d, a2);
       }
-    }
-    for (int c = nvec * V + lr; c < C; c += L) {
-      const T x = xp[c];
-      const double d = (double)Elem<T>::val(x) - P;
-      const u32 k = Elem<T>::key(x);
-      kmax = k > kmax ? k : kmax;
-      a1 += d;
-      a2 = fma(d, d, a2);
+    };
+    if constexpr (REG) {
+#pragma unroll
+      for (int k = 0; k < PPL; ++k)
+        if (lr + L * k < nvec) add(px[k]);
+    } else {
+      for (int v = lr; v < nvec; v += L) add(*reinterpret_cast<const uint4*>(xp + (long long)v * V));
+      for (int c = nvec * V + lr; c < C; c += L) {
+        const T x = xp[c];
+        const double d = (double)Elem<T>::val(x) - P;
+        const u32 k = Elem<T>::key(x);
+        kmax = k > kmax ? k : kmax;
+        a1 += d;
+        a2 = fma(d, d, a2);
+      }
     }
     for (int m = L >> 1; m > 0; m >>= 1) {       // butterfly: all L lanes end with the same bits
       const u32 ok = (u32)__shfl_xor((int)kmax, m, 64);
@@ -87,22 +132,99 @@ __global__ __launch_bounds__(kFusedThreads) void k_fused_small(
     if (lr == 0 && valid) {
       double mu, q;
       pivot_to_central(P, a1, a2, 1.0 / (double)C, mu, q);
-      rb[row] = Elem<T>::key_to_float(kmax);
-      meanb[row] = mu;
-      m2b[row] = q;
+      const float range = Elem<T>::key_to_float(kmax);
+      if constexpr (REG) {
+        s_key[row] = __float_as_uint(range);
+        s_mean[row] = mu;
+        s_m2[row] = q;
+      } else {
+        rb[row] = range;
+        meanb[row] = mu;
+        m2b[row] = q;
+      }
     }
+  };
+  if constexpr (REG) {
+#pragma unroll
+    for (int i = 0; i < RPT; ++i)
+      if (rpp * i < T_) row_stats(rsub + rpp * i, xr + i * PPL);
+  } else {
+    for (int row0 = 0; row0 < T_; row0 += rpp) row_stats(row0 + rsub, nullptr);
   }
   __syncthreads();                               // the workgroup's global writes are visible to it
 
-  // ---- B
-  assign_tokens(rb, meanb, m2b, T_, C, G, gb, wacc, s_min, s_max, s_lohi, 0, 1);
+  // ---- B, C: one wavefront per set
+  if constexpr (REG) {
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const u32 k1 = tid < T_ ? s_key[tid] : 0u;               // T_ <= kRegTokens = threads
+    const u32 kmax = wave_max_u32(k1), kmin = wave_min_u32(tid < T_ ? k1 : 0xFFFFFFFFu);
+    if (lane == 0) { s_min[wave] = kmin; s_max[wave] = kmax; }
+    __syncthreads();
+    u32 lo = s_min[0], hi = s_max[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) {
+      lo = s_min[w] < lo ? s_min[w] : lo;
+      hi = s_max[w] > hi ? s_max[w] : hi;
+    }
+    const u32 span = (u32)kOctaveFloor << 23, floor_key = hi > span ? hi - span : 0u;
+    lo = lo > floor_key ? lo : floor_key;
+    if (tid == 0) { s_lohi[0] = lo; s_lohi[1] = hi; }
+    const u32 width = hi - lo + 1u, wq = width / (u32)G, wr = width - wq * (u32)G;
+    const double cn = (double)C;
+    for (int j = wave; j < G; j += NW) {
+      const u32 start = j == 0 ? 0u : lo + (u32)j * wq + ((u32)j * wr + (u32)G - 1u) / (u32)G;
+      const u32 end =
+          j == G - 1 ? hi + 1u : lo + (u32)(j + 1) * wq + ((u32)(j + 1) * wr + (u32)G - 1u) / (u32)G;
+      u32 cnt = 0, cmax = 0;
+      double a1 = 0.0, a2 = 0.0, piv = 0.0;
+      for (int t0 = 0; t0 < T_; t0 += 64) {
+        const int t = t0 + lane;
+        const u32 k = t < T_ ? s_key[t] : 0u;
+        const bool mine = t < T_ && k >= start && k < end;
+        const unsigned long long mask = __ballot(mine);
+        if (mask == 0) continue;                             // uniform over the wavefront
+        if (cnt == 0) {                                      // the set's first token
+          piv = s_mean[t0 + __ffsll((long long)mask) - 1];
+          piv = (piv - piv == 0.0) ? piv : 0.0;
+        }
+        cnt += (u32)__popcll(mask);
+        if (mine) {
+          const double dm = s_mean[t] - piv, d1 = cn * dm;
+          a1 += d1;
+          a2 += s_m2[t] + d1 * dm;
+          cmax = k > cmax ? k : cmax;
+          s_gid[t] = (unsigned char)j;
+          gb[t] = j;
+        }
+      }
+      a1 = group_sum_f64<64>(a1);                            // totals in lane 63
+      a2 = group_sum_f64<64>(a2);
+      cmax = group_max_u32<64>(cmax);
+      if (lane == 63) {
+        SetAcc m;
+        m.s1 = a1; m.s2 = a2; m.piv = piv; m.cnt = cnt; m.kmax = cmax;
+        s_set[j] = m;
+      }
+    }
+    __syncthreads();
+  } else {
+    assign_tokens(rb, meanb, m2b, T_, C, G, gb, wacc, s_min, s_max, s_lohi, 0, 1);
+  }
   if (tid == 0 && image_flags) image_flags[b] = s_lohi[1] >= 0x7F800000u ? TDQ_DEV_NONFINITE : 0u;
 
+  int gr[RPT];                                   // REG: the set of every row of this thread
+  if constexpr (REG) {
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) gr[i] = rsub + rpp * i < T_ ? (int)s_gid[rsub + rpp * i] : 0;
+  }
+
+  int seq = 0;                                   // levels done: which of the two histograms is clear
   // one rank select per rank wanted: the percentile base radius first (if asked for)
   for (int pass = with_base ? kPassBase : kPassZr; pass >= kPassZr; --pass) {
     // ---- C
     if (tid < G) {
-      GroupWork w = merge_partials(wacc, 0, tid, NW, G, C, sc, pass);
+      GroupWork w = REG ? merge_partials(s_set, 0, tid, 1, G, C, sc, pass)
+                        : merge_partials(wacc, 0, tid, NW, G, C, sc, pass);
       if (pass == kPassZr && with_base) w.c_base = grp[tid].c_base;
       grp[tid] = w;
     }
@@ -113,34 +235,55 @@ __global__ __launch_bounds__(kFusedThreads) void k_fused_small(
       const int done = 8 * lev;                                  // key bits fixed so far
       const int total_bits = F16 ? 15 : 31;
       const int shift = total_bits - done - bits;                // bits below this level's digit
-      for (int i = tid; i < G * 256; i += kFusedThreads) hist[i] = 0;
+      // (with two histograms the next level's is cleared while this level's is searched)
+      u32* const hcur = hist + (two ? (seq & 1) * G * 256 : 0);
+      u32* const hnext = hist + (two ? ((seq + 1) & 1) * G * 256 : 0);
+      ++seq;
+      if (!two) {
+        for (int i = tid; i < G * 256; i += kFusedThreads) hist[i] = 0;
+      }
       __syncthreads();
-      for (int row = rsub; row < T_; row += rpp) {
-        const T* xp = Xb + (long long)row * ld;
-        const int g = gb[row];
+      auto count_row = [&](int row, int g, const uint4* px) {
         const u32 want = grp[g].prefix;                          // the `done` high bits
-        u32* h = hist + g * 256;
+        u32* h = hcur + g * 256;
         auto count = [&](u32 key) {
           if (done == 0 || (key >> (total_bits - done)) == want)
             atomicAdd(&h[(key >> shift) & ((1u << bits) - 1u)], 1u);
         };
-        for (int v = lr; v < nvec; v += L) {
-          const uint4 q = *reinterpret_cast<const uint4*>(xp + (long long)v * V);
+        auto count_piece = [&](const uint4& q) {
           T e[V];
           Elem<T>::unpack(q, e);
 #pragma unroll
           for (int i = 0; i < V; ++i) count(Elem<T>::key(e[i]));
+        };
+        if constexpr (REG) {
+#pragma unroll
+          for (int k = 0; k < PPL; ++k)
+            if (lr + L * k < nvec) count_piece(px[k]);
+        } else {
+          const T* xp = Xb + (long long)row * ld;
+          for (int v = lr; v < nvec; v += L)
+            count_piece(*reinterpret_cast<const uint4*>(xp + (long long)v * V));
+          for (int c = nvec * V + lr; c < C; c += L) count(Elem<T>::key(xp[c]));
         }
-        for (int c = nvec * V + lr; c < C; c += L) count(Elem<T>::key(xp[c]));
+      };
+      if constexpr (REG) {
+#pragma unroll
+        for (int i = 0; i < RPT; ++i)
+          if (rsub + rpp * i < T_) count_row(rsub + rpp * i, gr[i], xr + i * PPL);
+      } else {
+        for (int row = rsub; row < T_; row += rpp) count_row(row, gb[row], nullptr);
       }
       __syncthreads();
+      if (two)
+        for (int i = tid; i < G * 256; i += kFusedThreads) hnext[i] = 0;
       // a wavefront per set: every lane takes 4 consecutive bins, the running count
       // over the lanes finds the lane, then the bin, where it first reaches the rank
       for (int g = tid >> 6; g < G; g += NW) {
         const GroupWork w = grp[g];
         if (w.tokens == 0) continue;                               // uniform over the wavefront
         const int lane = tid & 63;
-        const uint4 hb = *reinterpret_cast<const uint4*>(&hist[g * 256 + 4 * lane]);
+        const uint4 hb = *reinterpret_cast<const uint4*>(&hcur[g * 256 + 4 * lane]);
         const u32 c4[4] = {hb.x, hb.y, hb.z, hb.w};
         const bool in_range = 4 * lane < (1 << bits);
         long long mine = in_range ? (long long)c4[0] + c4[1] + c4[2] + c4[3] : 0;
@@ -181,6 +324,32 @@ __global__ __launch_bounds__(kFusedThreads) void k_fused_small(
   }
 
   // ---- F
+  if constexpr (REG) {
+    // pieces of V elements -> V / 2 bytes each
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+      const int row = rsub + rpp * i;
+      if (row >= T_) break;
+      const float c = clip[b * G + gr[i]], d = scale[b * G + gr[i]];
+      const float rcp = 1.0f / d;
+      uint8_t* qp = Q + ((long long)b * T_ + row) * ld_q;
+#pragma unroll
+      for (int k = 0; k < PPL; ++k) {
+        const int v = lr + L * k;
+        if (v >= nvec) break;
+        T e[V];
+        Elem<T>::unpack(xr[i * PPL + k], e);
+        u32 word = 0;
+#pragma unroll
+        for (int j = 0; j < V; ++j) word |= quant_nibble(Elem<T>::val(e[j]), c, d, rcp) << (4 * j);
+        if constexpr (F16)
+          *reinterpret_cast<u32*>(qp + (long long)v * 4) = word;
+        else
+          *reinterpret_cast<u16*>(qp + (long long)v * 2) = (u16)word;
+      }
+    }
+    return;
+  }
   const int n8 = (vec_ok && q_vec_ok) ? C / 8 : 0;               // units of 8 elements -> 4 bytes
   const int nbytes = (C + 1) / 2;
   for (int row = rsub; row < T_; row += rpp) {
@@ -221,9 +390,16 @@ static hipError_t fused_t(const T* X, int B, int T_, int C, long long ld, int G,
   const int q_vec_ok = ((reinterpret_cast<uintptr_t>(Q) & 3) == 0 && ld_q % 4 == 0) ? 1 : 0;
   const int L = lanes_per_row(C, 8);
   const int with_base = sc.base_pct > 0.0 ? 1 : 0;
-  hipLaunchKernelGGL((k_fused_small<T>), dim3(B), dim3(kFusedThreads), 0, st, X, ld, T_, C, G, L,
-                     vec_ok, q_vec_ok, sc, with_base, r, mean, m2, gid, clip, scale, stats, image_flags,
-                     Q, ld_q);
+  const bool reg = T_ <= kRegTokens && vec_ok && q_vec_ok && C % V == 0 && C / V <= L * kRegPPL<T> &&
+                   (long long)T_ <= (long long)(kFusedThreads / L) * (kRegPieces / kRegPPL<T>);
+  if (reg)
+    hipLaunchKernelGGL((k_fused_small<T, true>), dim3(B), dim3(kFusedThreads), 0, st, X, ld, T_, C, G, L,
+                       vec_ok, q_vec_ok, sc, with_base, r, mean, m2, gid, clip, scale, stats,
+                       image_flags, Q, ld_q);
+  else
+    hipLaunchKernelGGL((k_fused_small<T, false>), dim3(B), dim3(kFusedThreads), 0, st, X, ld, T_, C, G, L,
+                       vec_ok, q_vec_ok, sc, with_base, r, mean, m2, gid, clip, scale, stats,
+                       image_flags, Q, ld_q);
   return hipGetLastError();
 }
 

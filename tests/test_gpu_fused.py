@@ -109,3 +109,26 @@ def test_fused_refuses_too_many_sets():
     with pytest.raises(tdq.TdqError) as e:
         tdq.tdq_calibrate_quantize_fused(X, tdq.default_params(65))
     assert e.value.status == tdq.ERR_UNSUPPORTED
+
+
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+@pytest.mark.parametrize("B,T,C,G", [(2, 1, 8, 3), (1, 64, 64, 32), (3, 65, 32, 33), (2, 256, 64, 8), (2, 257, 64, 64),
+                                     (1, 1024, 16, 17), (1, 1025, 16, 5), (2, 32, 512, 4), (2, 33, 520, 9)])
+def test_register_resident_edges(B, T, C, G, dtype):
+    """Images at and past the edge of what the single launch keeps in registers (tokens, row
+    length, pieces), one and two LDS histograms, both passes of the rank select."""
+    rng = np.random.Generator(np.random.PCG64(T + C))
+    X = (rng.laplace(0, 1, (B, T, C)) * rng.lognormal(0, 1.2, (B, T, 1)) + 0.5)
+    X = X.astype(np.float16 if dtype == "f16" else np.float32)
+    for pct in (0.0, 0.9):
+        p = tdq.default_params(G)
+        p.base_pct = pct
+        gid, clip, scale, stats, flags, Q, _ = tdq.tdq_calibrate_quantize_fused(
+            torch.from_numpy(X).to(U.dev()), p, want_stats=True)
+        torch.cuda.synchronize()
+        assert int(flags.abs().sum()) == 0
+        g = dict(gid=gid.cpu().numpy(), clip=clip.cpu().numpy(), scale=scale.cpu().numpy(),
+                 stats=tdq.stats_to_numpy(stats))
+        U.assert_calibration_matches(g, X, p)
+        want = O.quantize_act(X, g["gid"], g["clip"], g["scale"], U.oracle_params(p)).reshape(B * T, C)
+        assert np.array_equal(U.unpack_device_codes(Q, C), want)
