@@ -629,18 +629,20 @@ __global__ __launch_bounds__(256) void k_quantize(const T* __restrict__ X, long 
       rcp[i] = 1.0f / d[i];                // correctly rounded reciprocal
     }
   };
-  uint4 q[R][P][U];
+  uint4 q[R][P][U] = {};
   auto load_units = [&](int u0) {
 #pragma unroll
     for (int i = 0; i < R; ++i)
 #pragma unroll
       for (int k = 0; k < P; ++k) {
         const int u = u0 + k * L;
+        if (u < n8) {
 #pragma unroll
-        for (int h = 0; h < U; ++h) {
-          const T* src = xp[i] + (long long)(u < n8 ? u : u0) * 8 + h * V;
-          // (few elements: nothing to displace, and rows that share lines profit from the cache)
-          q[i][k][h] = R * P == 1 ? load16(src) : load_last_use(src);
+          for (int h = 0; h < U; ++h) {
+            const T* src = xp[i] + (long long)u * 8 + h * V;
+            // (few elements: nothing to displace, and rows that share lines profit from the cache)
+            q[i][k][h] = R * P == 1 ? load16(src) : load_last_use(src);
+          }
         }
       }
   };
@@ -690,10 +692,11 @@ static hipError_t quantize_t(const T* X, int B, int T_, int C, long long ld, int
   const int q_words = ((reinterpret_cast<uintptr_t>(Q) & 3) == 0 && ld_q % 4 == 0) ? 1 : 0;
   const int n8 = C / 8;
   const long long M = (long long)B * T_;
-  // Below 4 Mi elements there are not enough wavefronts to go round if each takes four units
-  // a lane: one unit each ([7744, 64] 2.9 against 4.9 us, [968, 512] 3.0 / 3.6, [6845, 333]
-  // 4.2 / 4.9; [7744, 320] 4.2 / 4.2, [15488, 320] 5.7 / 5.1).
-  const bool few = M * C < (4 << 20);
+  // Below 4 Mi binary16 elements there are not enough wavefronts to go round if each takes four
+  // units a lane: one unit each ([7744, 64] 2.9 against 4.9 us, [968, 512] 3.0 / 3.6, [6845, 333]
+  // 4.2 / 4.9; [7744, 320] 4.2 / 4.2, [15488, 320] 5.7 / 5.1).  A binary32 unit is two loads, and
+  // the line lies higher ([8192, 768] 7.7 / 10.0, [54120, 1152] 57.2 / 54.2).
+  const bool few = M * C < (sizeof(T) == 2 ? 4 << 20 : 16 << 20);
   const int L = few ? lanes_per_row(C, 8) : sweep_lanes_per_row(C, 8);
   const int P = few ? 1 : n8 > 2 * L ? 4 : n8 > L ? 2 : 1;
   const int R = few ? 1 : 4 / P;

@@ -34,9 +34,16 @@ LevelPlan make_level_plan(tdq_dtype dt, int G) {
 }
 
 int bracket_bins(int G) {
-  int w = kBracketMaxBins;
+  int w = 2048;
   while (w >= kBracketMinBins && (long long)G * w > kBracketLdsWords) w >>= 1;
   return w >= kBracketMinBins ? w : 0;
+}
+
+int bracket_bins_zr(int G) {
+  const int most = bracket_bins(G);
+  int w = 2048;
+  while (w > 512 && G * w > kBracketLdsWords / 2) w >>= 1;
+  return w < most ? w : most;
 }
 
 WorkspaceLayout make_layout(int B, int T, int G, const LevelPlan& lp) {
@@ -129,19 +136,19 @@ static int calibrate_after_stats(const void* X, tdq_dtype dt, int32_t B, int32_t
   // (nearly) every set exactly, and the kernel that verifies it resolves the others.  Too many
   // sets for the interval histogram, or binary32 images too large for the lists of collected
   // keys: radix levels.
-  const int W = bracket_bins(G);
+  const int Wmax = bracket_bins(G);
   const bool exact_only = (p->flags & TDQ_FLAG_EXACT_SELECT) != 0;
   // words per set of the radix levels' histograms, which the sampled route of binary32 input
-  // uses as the lists of collected keys: it expects about 1.04e-4 of a set's elements there
-  // (the interval's 5.3 % over 512 bins) and is taken while that leaves half of a list free
-  // for the largest set an image can have
+  // uses as the lists of collected keys: it expects up to 2e-4 of a set's elements there (an
+  // interval of about a tenth of its mass over 512 bins) and is taken while that fits the list
+  // with a third to spare for the largest set an image can have
   int cap = 0;
   for (int l = 0; l < lp.n_levels; ++l) cap += 1 << lp.bits[l];
   cap = cap > kListMax ? kListMax : cap;
   const bool f16 = dt == TDQ_F16;
   const bool sampled =
-      W > 0 && (f16 ? (long long)T * C < (1ll << 32)
-                    : !exact_only && (long long)T * C <= (W == 512 ? 5120ll : 2560ll) * cap);
+      Wmax > 0 && (f16 ? (long long)T * C < (1ll << 32)
+                       : !exact_only && (long long)T * C <= (G <= 32 ? 3328ll : 1664ll) * cap);
   Bracket* br = reinterpret_cast<Bracket*>(ws + wl.br);
   unsigned* bhist = reinterpret_cast<unsigned*>(ws + wl.bhist);
   const bool two_passes = sc.base_pct > 0.0;
@@ -152,6 +159,8 @@ static int calibrate_after_stats(const void* X, tdq_dtype dt, int32_t B, int32_t
   }
   for (int pass = two_passes ? kPassBase : kPassZr; pass >= kPassZr; --pass) {
     const bool keep_base = two_passes && pass == kPassZr;
+    // binary32: a bin is as wide as the interval needs, 512 of them (256) are enough
+    const int W = !f16 ? (G <= 32 ? 512 : 256) : pass == kPassZr ? bracket_bins_zr(G) : Wmax;
     if (sampled) {
       if (!exact_only) {
         if (launch_sets(X, dt, B, T, C, ld_x, G, W, r, mean, m2, group_id, sc, pass, keep_base, grp,

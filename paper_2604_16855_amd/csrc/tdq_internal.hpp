@@ -43,17 +43,19 @@ constexpr int kBracketLdsWords = 16384;   // 64 KiB of LDS histogram per workgro
 // bins / 2 keys, 1024 keys per octave) misses too often, and the multi-level radix
 // select over all sets at once is the cheaper route from the start.
 constexpr int kBracketMinBins = 256;
-// Most bins per set: 256 keys (a quarter of an octave) to either side are six standard
-// deviations of the sample's estimate, and every workgroup of the sweep clears and flushes
-// all its bins ([8, 7744, 512] calibrates in 52.4 us with up to 1024 bins, 47.2 with 512).
-constexpr int kBracketMaxBins = 512;
-
 constexpr int kListMax = 1024;            // most words of a set's list of collected keys
 
-// Bins per set of the interval histogram: the LDS budget shared out to G sets, rounded
-// down to a power of two, at most kBracketMaxBins (0 = too many sets: use the multi-level radix
-// select instead).
+// Bins per set of the interval histogram, at most 2048: the LDS budget shared out to G sets,
+// rounded down to a power of two (0 = too many sets: use the multi-level radix select
+// instead).  The zr quantile takes no more than half the budget where that leaves 512 bins --
+// every workgroup of the sweep clears and flushes all its bins ([8, 7744, 512] with 16 sets
+// calibrates in 52.4 us with 1024 of them, 47.2 with 512).  512 bins, a quarter of an octave to
+// either side, are six standard deviations of the sample's estimate in a set of similar
+// tokens; with few sets a set mixes tokens of very different ranges and the sample's error is
+// that of its few hundred tokens, and a percentile base radius lies where keys are sparse:
+// those get more bins and twice the sample (a missed set costs 0.2 ms).
 int bracket_bins(int G);
+int bracket_bins_zr(int G);
 
 // How the magnitude key (15 bits for fp16, 31 for fp32) is split into radix levels.
 struct LevelPlan {

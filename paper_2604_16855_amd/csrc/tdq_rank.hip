@@ -51,7 +51,8 @@ constexpr int kListTokens = 16384;                              // most tokens l
 // counted wavefront by wavefront (any numbering of the set's tokens serves the sample), so
 // the wavefronts exchange one count each.  SM = most sampled elements: the rank error of 8 Ki
 // is 0.45 % of the set's mass, about 40 keys at 1024 keys per octave, against a half-width of
-// W / 2 >= 256 keys; with fewer bins per set (more than 32 sets) 16 Ki are drawn.
+// W / 2 >= 256 keys.  16 Ki are drawn with fewer bins per set (more than 32 sets), for the
+// percentile base radius and with fewer than 8 sets, whose tokens differ more.
 // Measured, calibration of one call (two kernels for this before: assignment, then sample):
 // [1, 7744, 64] 46.3 -> 30.9 us, [8, 121, 512] 30.7 -> 26.0, [32, 4096, 1024] 118.7 -> 108.3;
 // with 16 Ki samples 31.7 / 26.9 / 111.0.  Then, this kernel alone: the sample's loads issued
@@ -411,12 +412,15 @@ __global__ __launch_bounds__(NT) void k_sets(
     const u32 mid = (s_bin[0] << (15 - kSampleBits)) + (1u << (14 - kSampleBits));
     e.lo = mid > (u32)W / 2 ? mid - (u32)W / 2 : 0u;
   } else {
-    // The interval between two order statistics of the sample, six standard deviations of
+    // The interval between two order statistics of the sample, several standard deviations of
     // the sample rank to either side, each resolved to 20 of its 31 bits; its W bins are as
-    // wide as that needs, so a bin holds about 1e-4 of the set's elements whatever the
-    // data's offset and spread.
+    // wide as that needs, so a bin holds about 2e-4 of the set's elements whatever the data's
+    // offset and spread.
+    // (six standard deviations of independent elements and one of whole tokens, as if all
+    // elements of a token lay on one side)
     const double pq = (double)rk / (double)m;
-    const long long dr = (long long)(6.0 * sqrt((double)rk * (1.0 - pq))) + 2;
+    const long long dr =
+        (long long)(sqrt(pq * (1.0 - pq)) * (6.0 * sqrt((double)m) + (double)m / sqrt((double)n_sel))) + 2;
     const u32 r0 = (u32)(rk - dr < 1 ? 1 : rk - dr), r1 = (u32)(rk + dr > m ? m : rk + dr);
     find_two_ranks<NT, kCopies>(shist, shist, r0, r1, stot, s_bin, s_before);
     __syncthreads();
@@ -446,6 +450,7 @@ static void sets_t(const TX* X, int B, int T, int C, long long ld, int G, int W,
                    int cap, unsigned* img_flag, unsigned* status, hipStream_t st) {
   constexpr int V = Elem<TX>::V;
   const int aligned = ((reinterpret_cast<uintptr_t>(X) & 15) == 0 && ld % V == 0 && C % V == 0) ? 1 : 0;
+  const bool few = W >= 512 && G >= 8 && pass == kPassZr;    // 8 Ki sampled elements are enough
   const size_t order_bytes = T <= kListTokens ? (size_t)T * sizeof(unsigned short) : 0;
 #define TDQ_SETS_SM(NT, SM)                                                                        \
   hipLaunchKernelGGL((k_sets<TX, NT, SM>), dim3(G, B), dim3(NT), order_bytes, st, X, ld, T, C, G, W, aligned, r, \
@@ -453,7 +458,7 @@ static void sets_t(const TX* X, int B, int T, int C, long long ld, int G, int W,
                      img_flag, status)
 #define TDQ_SETS(NT)                                                           \
   do {                                                                         \
-    if (W >= 512 || V == 4) TDQ_SETS_SM(NT, 8192); else TDQ_SETS_SM(NT, 16384); \
+    if (few) TDQ_SETS_SM(NT, 8192); else TDQ_SETS_SM(NT, 16384);               \
   } while (0)
   // as few threads as hold the image's range keys in registers: [32, 4096, 1024] calibrates
   // in 111 / 117 / 145 us with 256 / 512 / 1024 threads per set
@@ -663,7 +668,7 @@ hipError_t launch_bracket_hist(const void* X, tdq_dtype dt, int B, int T, int C,
   return hipGetLastError();
 }
 
-// The bin of a set's interval histogram (W = 256 or 512 bins) that holds its k-th smallest
+// The bin of a set's interval histogram (W = 256 to 2048 bins) that holds its k-th smallest
 // key, by one wavefront; the same in every lane.  ok = the interval does hold it.
 struct BinPick {
   bool ok;
@@ -671,13 +676,19 @@ struct BinPick {
 };
 __device__ __forceinline__ BinPick pick_bin(const u32* __restrict__ hb, int W, u32 below, long long k) {
   const int lane = threadIdx.x & 63;
-  const int per = W / 64;                       // 4 or 8
-  const uint4 c0 = *reinterpret_cast<const uint4*>(hb + lane * per);
-  const uint4 c1 = *reinterpret_cast<const uint4*>(hb + lane * per + (per > 4 ? 4 : 0));
-  const u32 c[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
+  const int per = W / 64;                       // 4 to 32
+  const u32* mine_bins = hb + lane * per;
+  uint4 c[2];                                   // up to 8 bins stay in registers
   unsigned long long mine = 0;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) mine += i < per ? c[i] : 0u;
+  for (int i = 0; i < 2; ++i) {
+    c[i] = *reinterpret_cast<const uint4*>(mine_bins + (4 * i < per ? 4 * i : 0));
+    if (4 * i < per) mine += (unsigned long long)c[i].x + c[i].y + c[i].z + c[i].w;
+  }
+  for (int i = 8; i < per; i += 4) {
+    const uint4 q = *reinterpret_cast<const uint4*>(mine_bins + i);
+    mine += (unsigned long long)q.x + q.y + q.z + q.w;
+  }
   unsigned long long incl = mine;               // inclusive scan over lanes
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
@@ -693,10 +704,25 @@ __device__ __forceinline__ BinPick pick_bin(const u32* __restrict__ hb, int W, u
   const int src = r.ok ? __ffsll((long long)hit) - 1 : 0;       // hit != 0 because need <= inside
   unsigned long long cum = incl - mine;
   u32 bin = (u32)(lane * per);
-  for (int i = 0; i < per - 1; ++i) {
-    if (cum + c[i] >= need) break;
-    cum += c[i];
-    ++bin;
+  bool found = false;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const u32 v = (&c[i >> 2].x)[i & 3];
+    found = found || i >= per - 1 || cum + v >= need;
+    if (!found) {
+      cum += v;
+      ++bin;
+    }
+  }
+  if (per > 8 && lane == src) {                 // past the ones in registers
+    for (int i = 8; i < per - 1 && !found; ++i) {
+      const u32 v = mine_bins[i];
+      found = cum + v >= need;
+      if (!found) {
+        cum += v;
+        ++bin;
+      }
+    }
   }
   r.bin = (u32)__shfl((int)bin, src, 64);
   r.need = (u32)(need - __shfl(cum, src, 64));
@@ -705,7 +731,7 @@ __device__ __forceinline__ BinPick pick_bin(const u32* __restrict__ hb, int W, u
 
 // ---------------------------------------------------------------------------
 // k_bracket_gather, binary32 input only: a bin of the interval histogram is 2^shift keys wide
-// there, so a second sweep collects the keys that fall into the bin of every set (about 1e-4
+// there, so a second sweep collects the keys that fall into the bin of every set (about 2e-4
 // of the elements), first per workgroup in LDS.  lists[set]: largest ~key, largest key, then
 // the keys; their number is counted in GroupWork::prefix, and a workgroup that found more than
 // it can keep pushes that number past the list's capacity.  (Equal keys need no list: the

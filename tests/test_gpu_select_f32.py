@@ -52,7 +52,7 @@ def test_interval_holds_the_rank():
     assert g["exact_sets"] == 0
 
 
-@pytest.mark.parametrize("T", [4480, 4481])
+@pytest.mark.parametrize("T", [2912, 2913])
 def test_largest_image_of_the_route(T):
     X = _data("laplace", 1, T, 1024, T)
     p = tdq.default_params(4)
