@@ -160,13 +160,15 @@ static int calibrate_after_stats(const void* X, tdq_dtype dt, int32_t B, int32_t
   for (int pass = two_passes ? kPassBase : kPassZr; pass >= kPassZr; --pass) {
     const bool keep_base = two_passes && pass == kPassZr;
     // binary32: a bin is as wide as the interval needs, 512 of them (256) are enough
-    const int W = !f16 ? (G <= 32 ? 512 : 256) : pass == kPassZr ? bracket_bins_zr(G) : Wmax;
+    // (binary16: few bins where the interval fits them, else all that there is room for)
+    const int W = !f16 ? (G <= 32 ? 512 : 256) : Wmax;
+    const int Wfew = f16 && pass == kPassZr ? bracket_bins_zr(G) : W;
     if (sampled) {
       if (!exact_only) {
-        if (launch_sets(X, dt, B, T, C, ld_x, G, W, r, mean, m2, group_id, sc, pass, keep_base, grp,
+        if (launch_sets(X, dt, B, T, C, ld_x, G, Wfew, W, r, mean, m2, group_id, sc, pass, keep_base, grp,
                         br, bhist, hist, cap, img_flag, status, st) != hipSuccess)
           return TDQ_ERR_HIP;
-        if (launch_bracket_hist(X, dt, B, T, C, ld_x, G, W, group_id, br, bhist, st) != hipSuccess)
+        if (launch_bracket_hist(X, dt, B, T, C, ld_x, G, Wfew, W, group_id, br, bhist, st) != hipSuccess)
           return TDQ_ERR_HIP;
         if (!f16 && launch_bracket_gather(X, B, T, C, ld_x, G, W, group_id, br, bhist, grp, hist, cap,
                                           st) != hipSuccess)
@@ -175,7 +177,7 @@ static int calibrate_after_stats(const void* X, tdq_dtype dt, int32_t B, int32_t
                  hipSuccess) {
         return TDQ_ERR_HIP;
       }
-      if (launch_bracket_finish(X, dt, B, T, C, ld_x, G, W, group_id, bhist, hist, cap, exact_only, sc,
+      if (launch_bracket_finish(X, dt, B, T, C, ld_x, G, Wfew, W, group_id, bhist, hist, cap, exact_only, sc,
                                 pass, grp, br, clip, scale, stats, img_flag, status, st) != hipSuccess)
         return TDQ_ERR_HIP;
       continue;

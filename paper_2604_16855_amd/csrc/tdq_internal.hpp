@@ -47,13 +47,14 @@ constexpr int kListMax = 1024;            // most words of a set's list of colle
 
 // Bins per set of the interval histogram, at most 2048: the LDS budget shared out to G sets,
 // rounded down to a power of two (0 = too many sets: use the multi-level radix select
-// instead).  The zr quantile takes no more than half the budget where that leaves 512 bins --
-// every workgroup of the sweep clears and flushes all its bins ([8, 7744, 512] with 16 sets
-// calibrates in 52.4 us with 1024 of them, 47.2 with 512).  512 bins, a quarter of an octave to
-// either side, are six standard deviations of the sample's estimate in a set of similar
-// tokens; with few sets a set mixes tokens of very different ranges and the sample's error is
-// that of its few hundred tokens, and a percentile base radius lies where keys are sparse:
-// those get more bins and twice the sample (a missed set costs 0.2 ms).
+// instead).  For the zr quantile most sets use bracket_bins_zr(G) of them, no more than half the
+// budget where that leaves 512 -- every workgroup of the sweep clears and flushes all its bins
+// ([8, 7744, 512] with 16 sets calibrates in 52.4 us with 1024 of them, 47.2 with 512), and 512, a
+// quarter of an octave to either side, are six standard deviations of the sample's estimate in a
+// set of similar tokens; a set whose sample says that its keys are sparse there uses all.  With
+// few sets a set mixes tokens of very different ranges and the sample's error is that of its few
+// hundred tokens, and a percentile base radius lies where keys are sparse: those get more bins and
+// twice the sample.
 int bracket_bins(int G);
 int bracket_bins_zr(int G);
 
@@ -70,8 +71,8 @@ LevelPlan make_level_plan(tdq_dtype dt, int G);
 // Byte offsets of the pieces of the calibration workspace (all 256-aligned).
 struct WorkspaceLayout {
   size_t status;     // uint32[64]; word 0 = device status word, words 1 and 2 = sets whose
-                     // rank the last binary16 calibration's sampled key interval missed in
-                     // pass kPassZr and pass kPassBase (resolved by the per-set radix select)
+                     // rank the last calibration's sampled key interval missed in pass kPassZr
+                     // and pass kPassBase (searched for in the set's own rows)
   size_t img_flag;   // uint32[B]     per-image non-finite flag
   size_t r;          // float[M]      per-token range
   size_t mean;       // double[M]     per-token mean
@@ -109,8 +110,8 @@ hipError_t launch_token_stats(const void* X, tdq_dtype dt, int M, int C, long lo
                               float* r, double* mean, double* m2, hipStream_t st);
 // Token-set assignment.  An image is shared by assign_split(T) workgroups, each of
 // which leaves one partial record per set in `part`; the records are merged into
-// GroupWork by launch_finalize_groups.  (The single-sweep rank select of binary16 input
-// assigns the sets in its own first kernel, launch_sets.)
+// GroupWork by launch_finalize_groups.  (The sampled rank select of either type assigns the sets
+// in its own first kernel, launch_sets.)
 constexpr int kAssignSplitMax = 8;
 int assign_split(int T);
 size_t assign_partial_bytes(int B, int G);
@@ -132,20 +133,21 @@ hipError_t launch_select(unsigned* hist_level, int B, int G, int shift, int bits
                          unsigned* status, int pass, hipStream_t st);
 // Rank select guided by a sample: binary16 input in one sweep, binary32 input in two (the
 // second, launch_bracket_gather, collects the keys of one bin per set into `lists`, cap words
-// per set, the first two of them the largest ~key and the largest key).
-hipError_t launch_sets(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G, int W,
-                       const float* r, const double* mean, const double* m2, int* gid,
+// per set, the first two of them the largest ~key and the largest key).  Of the W bins of a set's
+// interval histogram most sets use the first Wfew.
+hipError_t launch_sets(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G,
+                       int Wfew, int W, const float* r, const double* mean, const double* m2, int* gid,
                        const Scalars& sc, int pass, bool keep_base, GroupWork* grp, Bracket* br,
                        unsigned* bhist, unsigned* lists, int cap, unsigned* img_flag,
                        unsigned* status, hipStream_t st);
 hipError_t launch_bracket_hist(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G,
-                               int W, const int* gid, Bracket* br, unsigned* bhist, hipStream_t st);
+                               int Wfew, int W, const int* gid, Bracket* br, unsigned* bhist, hipStream_t st);
 hipError_t launch_bracket_gather(const void* X, int B, int T, int C, long long ld, int G, int W,
                                  const int* gid, const Bracket* br, const unsigned* bhist,
                                  GroupWork* grp, unsigned* lists, int cap, hipStream_t st);
 hipError_t launch_bracket_finish(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G,
-                                 int W, const int* gid, const unsigned* bhist, const unsigned* lists,
-                                 int cap, bool force_miss, const Scalars& sc, int pass, GroupWork* grp,
+                                 int Wfew, int W, const int* gid, const unsigned* bhist,
+                                 const unsigned* lists, int cap, bool force_miss, const Scalars& sc, int pass, GroupWork* grp,
                                  const Bracket* br, float* clip, float* scale, tdq_group_stats* stats,
                                  const unsigned* img_flag, unsigned* status, hipStream_t st);
 hipError_t launch_quantize(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G,

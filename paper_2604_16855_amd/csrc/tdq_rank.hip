@@ -6,12 +6,11 @@
 // select over LDS histograms needs two (four) sweeps of X for that many bits.  Here a small
 // sample of every set first says where to look:
 //
-//   k_sets            one workgroup per set finds the set's tokens and moments, reads up
-//                     to 8 Ki sampled elements and takes the key interval around the sample
-//                     order statistic that corresponds to k: W one-key bins centred on it
-//                     (binary16), or W bins of 2^shift keys between two sample order
-//                     statistics on either side of it (binary32).  It holds the true answer
-//                     unless the sample is off by more than that.
+//   k_sets            one workgroup per set finds the set's tokens and moments, reads 8 or
+//                     16 Ki sampled elements and takes the key interval between two sample order
+//                     statistics on either side of the one that corresponds to k: one-key bins
+//                     (binary16), or bins of about equal mass (binary32).  It holds the true
+//                     answer unless the sample is off by more than that.
 //   k_bracket_hist    one sweep of X: per set, the number of keys below the interval and an
 //                     LDS histogram of the keys inside it.
 //   k_bracket_gather  binary32: a second sweep collects the keys of every set that fall into
@@ -21,11 +20,15 @@
 //                     collected from it, the one of the remaining rank: the exact k-th
 //                     smallest, no matter how the interval was chosen -- and the set is
 //                     projected.  Otherwise the set is counted as missed and the same
-//                     workgroup resolves it with a radix select over the set's own rows
-//                     (exact as well, and rare).
+//                     workgroup finds the key in the set's own rows, on the side of the
+//                     interval where it must be (exact as well, and rare).
 //
 // The result is therefore always the exact order statistic; the sample only decides
 // which of the two routes computes it, i.e. how long it takes.
+//
+// Zeros are never inside an interval (it starts at key 1 at the lowest): where it starts there,
+// "below" counts exactly the zeros, and a rank among them is answered by that count.  A fifth
+// of an activation behind a rectifier is zeros, which would all meet in one word of LDS.
 #include "tdq_device.hpp"
 
 namespace tdq {
@@ -50,9 +53,11 @@ constexpr int kListTokens = 16384;                              // most tokens l
 // kernel boundary, and everything per token sits in registers when T <= 16 NT.  Ranks are
 // counted wavefront by wavefront (any numbering of the set's tokens serves the sample), so
 // the wavefronts exchange one count each.  SM = most sampled elements: the rank error of 8 Ki
-// is 0.45 % of the set's mass, about 40 keys at 1024 keys per octave, against a half-width of
-// W / 2 >= 256 keys.  16 Ki are drawn with fewer bins per set (more than 32 sets), for the
-// percentile base radius and with fewer than 8 sets, whose tokens differ more.
+// is 0.45 % of the set's mass, about 40 keys at 1024 keys per octave where keys are dense, against
+// a half-width of Wfew / 2 >= 256 keys; where they are not, W bins are used.  16 Ki are drawn with
+// fewer bins per set (more than 32 sets), for the percentile base radius and with fewer than 8
+// sets, whose tokens differ more.  A set smaller than the sample is read with as many loads as it
+// has pieces (2048 images of [49, 96], 64 sets: 920 -> 640 us).
 // Measured, calibration of one call (two kernels for this before: assignment, then sample):
 // [1, 7744, 64] 46.3 -> 30.9 us, [8, 121, 512] 30.7 -> 26.0, [32, 4096, 1024] 118.7 -> 108.3;
 // with 16 Ki samples 31.7 / 26.9 / 111.0.  Then, this kernel alone: the sample's loads issued
@@ -60,58 +65,69 @@ constexpr int kListTokens = 16384;                              // most tokens l
 // ones cost divisions (T <= kListTokens; the list of a larger image would not leave LDS for
 // several workgroups): 24.8 -> 20.3 us at [32, 4096, 1024], 14.4 -> 11.9 at [1, 7744, 64].
 // ---------------------------------------------------------------------------
-// One workgroup's search of two 1024-bin LDS histograms (or twice the same) for the bin that
-// holds rank r0 of h0 and r1 of h1 (1-based, at most the histogram's total): bin[i] and the
-// count before it.  Every thread of the workgroup calls it, after a barrier that completes the
-// histograms; the results are valid after the caller's next barrier.  stot [2][NW] is scratch.
-// A bin is the sum of COPIES neighbouring words.
-template <int NT, int COPIES>
-__device__ __forceinline__ void find_two_ranks(const u32* h0, const u32* h1, u32 r0, u32 r1,
-                                               u32 (*stot)[NT / 64], u32* bin, u32* before) {
+// One workgroup's search of K 1024-bin LDS histograms (or K times the same) for the bin that
+// holds rank r[q] (1-based, at most the histogram's total) of h[q]: bin[q] and the count before
+// it.  Every thread of the workgroup calls it, after a barrier that completes the histograms;
+// the results are valid after the caller's next barrier.  stot [K][NW] is scratch.  A bin is the
+// sum of COPIES neighbouring words.  CUM: cum[1024] gets the counts before every bin of h[0].
+template <int NT, int K, int COPIES, bool CUM>
+__device__ __forceinline__ void find_ranks(const u32* const (&h)[K], const u32 (&r)[K],
+                                           u32 (*stot)[NT / 64], u32* bin, u32* before, u32* cum) {
   constexpr int NW = NT / 64, kBins = 1024 / NT;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  u32 c[2][kBins], mine[2] = {0, 0};
+  u32 c[K][kBins], mine[K], incl[K];
 #pragma unroll
-  for (int i = 0; i < kBins; ++i) {
-    c[0][i] = 0;
-    c[1][i] = 0;
+  for (int q = 0; q < K; ++q) {
+    mine[q] = 0;
 #pragma unroll
-    for (int k = 0; k < COPIES; ++k) {
-      c[0][i] += h0[(tid * kBins + i) * COPIES + k];
-      c[1][i] += h1[(tid * kBins + i) * COPIES + k];
+    for (int i = 0; i < kBins; ++i) {
+      c[q][i] = 0;
+#pragma unroll
+      for (int k = 0; k < COPIES; ++k) c[q][i] += h[q][(tid * kBins + i) * COPIES + k];
+      mine[q] += c[q][i];
     }
-    mine[0] += c[0][i];
-    mine[1] += c[1][i];
+    incl[q] = mine[q];                       // inclusive scans over the wavefront
   }
-  u32 incl[2] = {mine[0], mine[1]};          // inclusive scans over the wavefront
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
-    const u32 o0 = (u32)__shfl_up((int)incl[0], d, 64), o1 = (u32)__shfl_up((int)incl[1], d, 64);
-    if (lane >= d) { incl[0] += o0; incl[1] += o1; }
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+      const u32 o = (u32)__shfl_up((int)incl[q], d, 64);
+      if (lane >= d) incl[q] += o;
+    }
   }
-  if (lane == 63) { stot[0][wave] = incl[0]; stot[1][wave] = incl[1]; }
+#pragma unroll
+  for (int q = 0; q < K; ++q)
+    if (lane == 63) stot[q][wave] = incl[q];
   __syncthreads();
 #pragma unroll
-  for (int which = 0; which < 2; ++which) {
+  for (int q = 0; q < K; ++q) {
 #pragma unroll
-    for (int w2 = 0; w2 < NW; ++w2) incl[which] += w2 < wave ? stot[which][w2] : 0u;
-    const u32 r = which == 0 ? r0 : r1;
-    if (incl[which] - mine[which] < r && r <= incl[which]) {      // exactly one thread
-      u32 cum = incl[which] - mine[which];
+    for (int w2 = 0; w2 < NW; ++w2) incl[q] += w2 < wave ? stot[q][w2] : 0u;
+    if (CUM && q == 0) {
+      u32 at = incl[0] - mine[0];
+#pragma unroll
+      for (int i = 0; i < kBins; ++i) {
+        cum[tid * kBins + i] = at;
+        at += c[0][i];
+      }
+    }
+    if (incl[q] - mine[q] < r[q] && r[q] <= incl[q]) {            // exactly one thread
+      u32 at = incl[q] - mine[q];
       int i = 0;
       for (; i < kBins - 1; ++i) {
-        if (cum + c[which][i] >= r) break;
-        cum += c[which][i];
+        if (at + c[q][i] >= r[q]) break;
+        at += c[q][i];
       }
-      bin[which] = (u32)(tid * kBins + i);
-      before[which] = cum;
+      bin[q] = (u32)(tid * kBins + i);
+      before[q] = at;
     }
   }
 }
 
 template <typename TX, int NT, int SM>
 __global__ __launch_bounds__(NT) void k_sets(
-    const TX* __restrict__ X, long long ld, int T, int C, int G, int W, int aligned,
+    const TX* __restrict__ X, long long ld, int T, int C, int G, int Wfew, int W, int aligned,
     const float* __restrict__ r, const double* __restrict__ mean, const double* __restrict__ m2,
     int* __restrict__ gid, Scalars sc, int pass, int keep_base, GroupWork* __restrict__ grp,
     Bracket* __restrict__ br, u32* __restrict__ bhist, u32* __restrict__ lists, int cap,
@@ -129,8 +145,9 @@ __global__ __launch_bounds__(NT) void k_sets(
   __shared__ __attribute__((aligned(16))) u32 shist[kCopies << kSampleBits];   // sample histogram
                                                      // over the top key bits
   __shared__ u32 snext[F16 ? 1 : 2][F16 ? 1 : 1 << kSampleBits];   // binary32: two over the next ones
+  __shared__ __attribute__((aligned(16))) u32 cum[F16 ? 1024 : 4];                // binary16: sampled elements before every bin
   __shared__ u32 s_bin[4], s_before[4];
-  __shared__ u32 s_min[NW], s_max[NW], wtot[NW], stot[2][NW], s_cmax[NW];
+  __shared__ u32 s_min[NW], s_max[NW], wtot[NW], stot[3][NW], s_cmax[NW];
   __shared__ double s_s1[NW], s_s2[NW];
   __shared__ int s_first;
   const int j = blockIdx.x, b = blockIdx.y, idx = b * G + j;
@@ -228,9 +245,10 @@ __global__ __launch_bounds__(NT) void k_sets(
     }
     return;
   }
-  // the sweep adds into this set's histogram: clear it here
-  for (int i = tid; i < W; i += NT) bhist[(size_t)idx * W + i] = 0;
   if (!F16 && tid < 2) lists[(size_t)idx * cap + tid] = 0;
+
+  // the sweep adds into this set's histogram: clear it here (more of it below if more is used)
+  for (int i = tid; i < Wfew; i += NT) bhist[(size_t)idx * W + i] = 0;
 
   // Sample geometry.  The set's tokens are cut into strata of `stride` tokens (at most
   // kSampleTokens strata) and one token is drawn from each at a hashed position: a regular
@@ -289,10 +307,10 @@ __global__ __launch_bounds__(NT) void k_sets(
   constexpr int kPieces = kKeys / V, PPR = kRunLen / V;
   uint4 v[kPieces];
   bool live[kPieces];
+  const int steps = (n_runs * PPR + NT - 1) / NT;      // small sets need fewer than kPieces
   // offsets in steps of whole pieces where the rows consist of aligned ones
   const u32 step = aligned ? (u32)V : 1u, offsets = (u32)(C - cw) / step + 1u;
-#pragma unroll
-  for (int e = 0; e < kPieces; ++e) {
+  auto load_piece = [&](int e) {
     const u32 p = (u32)(e * NT + tid), q = p / PPR, part = p % PPR;
     const u32 slot = q / (u32)rpt, run = q - slot * (u32)rpt;
     const int at = (int)(run * kRunLen + part * V);    // channel inside the part of the row read
@@ -309,7 +327,10 @@ __global__ __launch_bounds__(NT) void k_sets(
       for (int i = 0; i < V; ++i) x[i] = src[i < C ? i : 0];
       v[e] = *reinterpret_cast<const uint4*>(x);
     }
-  }
+  };
+#pragma unroll
+  for (int e = 0; e < kPieces; ++e)
+    if (e < steps) load_piece(e);                      // uniform
 
   // Moments of the set about the mean of its first token (zero if that is not finite: the
   // image's results are then undefined anyway and its flag is raised).
@@ -356,19 +377,27 @@ __global__ __launch_bounds__(NT) void k_sets(
   if (lane == 63) { s_s1[wave] = a1; s_s2[wave] = a2; s_cmax[wave] = cmax; }
 
   // ---- 3: the sample.  Every live key adds one to an LDS histogram of its top kSampleBits
-  // bits.
-  u32 key[kKeys];
-#pragma unroll
-  for (int e = 0; e < kPieces; ++e) {
+  // bits; zeros, often many, are counted first.
+  u32 key[kKeys], zeros = 0;
+  auto add_piece = [&](int e) {
     TX x[V];
     Elem<TX>::unpack(v[e], x);
 #pragma unroll
-    for (int i = 0; i < V; ++i) key[e * V + i] = live[e] && i < C ? Elem<TX>::key(x[i]) : kDead;
-  }
+    for (int i = 0; i < V; ++i) {
+      const u32 k = live[e] && i < C ? Elem<TX>::key(x[i]) : kDead;
+      key[e * V + i] = k;
+      zeros += k == 0u ? 1u : 0u;
+      if (k != kDead && k != 0u)
+        atomicAdd(&shist[(k >> (kKeyBits - kSampleBits)) * kCopies + (lane & (kCopies - 1))], 1u);
+    }
+  };
 #pragma unroll
-  for (int e = 0; e < kKeys; ++e)
-    if (key[e] != kDead)
-      atomicAdd(&shist[(key[e] >> (kKeyBits - kSampleBits)) * kCopies + (lane & (kCopies - 1))], 1u);
+  for (int e = 0; e < kPieces; ++e)
+    if (e < steps) add_piece(e);
+  if (__ballot(zeros != 0)) {
+    zeros = group_sum_u32<64>(zeros);
+    if (lane == 63) atomicAdd(&shist[0], zeros);
+  }
   __syncthreads();
 
   // the set's working record: n, base radius, sigma, rank of this pass (binary64)
@@ -396,47 +425,75 @@ __global__ __launch_bounds__(NT) void k_sets(
     grp[idx] = w;
   }
 
-  // Sample rank that corresponds to rank k of the set.
+  // Sample rank that corresponds to rank k of the set; its standard deviation as that of a
+  // sample of independent elements (none if the sample is the set), and that of a sample of
+  // whole tokens, as if all elements of a token lay on one side.
   long long rk = (long long)((double)w.k_rem / n * (double)m + 0.5);
   rk = rk < 1 ? 1 : (rk > m ? m : rk);
+  const float mf = (float)m, pq = (float)rk / mf, left_out = w.n > m ? 1.f - mf / (float)n : 0.f;
+  const float dev = sqrtf(pq * (1.f - pq) * left_out * mf), dev_tokens = dev * sqrtf(mf / (float)n_sel);
   Bracket e;
   e.below = 0;
-  e.width = (u32)W;
+  e.width = (u32)Wfew;
   e.shift = 0;
   if constexpr (F16) {
-    // the histogram bin that holds that order statistic (the low key bits do not matter to
-    // the interval): v <= estimate < v + 2^(15 - kSampleBits), the interval of W one-key bins
-    // is centred on the middle
-    find_two_ranks<NT, 1>(shist, shist, (u32)rk, (u32)rk, stot, s_bin, s_before);
+    // The histogram bin that holds that order statistic (the low key bits do not matter to the
+    // interval): Wfew one-key bins centred on its middle, if they reach two and a half
+    // standard deviations to either side.  Else the rank lies where keys are sparse (just above the zeros
+    // of a rectified activation, between the values of a coarse grid): the W bins that leave
+    // equally many sampled keys on either side of it.
+    constexpr int kCell = 1 << (15 - kSampleBits);
+    const u32* const hs[1] = {shist};
+    const u32 rs[1] = {(u32)rk};
+    find_ranks<NT, 1, 1, true>(hs, rs, stot, s_bin, s_before, cum);
     __syncthreads();
-    const u32 mid = (s_bin[0] << (15 - kSampleBits)) + (1u << (14 - kSampleBits));
-    e.lo = mid > (u32)W / 2 ? mid - (u32)W / 2 : 0u;
+    if (wave != 0) return;
+    const int bm = (int)s_bin[0], reach = (int)(2.5f * dev) + 1;
+    auto below_bin = [&](int c) { return c <= 0 ? 0 : c >= 1024 ? (int)m : (int)cum[c]; };
+    const int under = below_bin(bm - Wfew / 2 / kCell + 1), upto = below_bin(bm + Wfew / 2 / kCell);
+    int lo = bm * kCell + kCell / 2 - Wfew / 2;
+    if (!((under == 0 || (int)rk - under >= reach) && (upto == (int)m || upto - (int)rk >= reach))) {
+      e.width = (u32)W;
+      for (int i = Wfew + lane; i < W; i += 64) bhist[(size_t)idx * W + i] = 0;
+      const int nb = W / kCell;                        // 8 to 64 candidates, one per lane
+      const int c0 = bm - nb + 1 + lane;
+      u32 score = 0;
+      if (lane < nb && c0 >= 0) {                      // (the last one, c0 = bm, always is)
+        const int left = (int)rk - below_bin(c0), right = below_bin(c0 + nb) - (int)rk;
+        score = ((u32)(left < right ? left : right) << 6) | (u32)lane;
+      }
+      if (lane == nb - 1) score |= (u32)lane;
+      score = (u32)__builtin_amdgcn_readlane((int)group_max_u32<64>(score), 63);
+      lo = (bm - nb + 1 + (int)(score & 63u)) * kCell;
+    }
+    e.lo = lo > 1 ? (u32)lo : 1u;                      // zeros are counted below
   } else {
-    // The interval between two order statistics of the sample, several standard deviations of
-    // the sample rank to either side, each resolved to 20 of its 31 bits; its W bins are as
-    // wide as that needs, so a bin holds about 2e-4 of the set's elements whatever the data's
-    // offset and spread.
-    // (six standard deviations of independent elements and one of whole tokens, as if all
-    // elements of a token lay on one side)
-    const double pq = (double)rk / (double)m;
-    const long long dr =
-        (long long)(sqrt(pq * (1.0 - pq)) * (6.0 * sqrt((double)m) + (double)m / sqrt((double)n_sel))) + 2;
-    const u32 r0 = (u32)(rk - dr < 1 ? 1 : rk - dr), r1 = (u32)(rk + dr > m ? m : rk + dr);
-    find_two_ranks<NT, kCopies>(shist, shist, r0, r1, stot, s_bin, s_before);
+    // The interval between two order statistics of the sample, six standard deviations of its
+    // elements and one of its tokens to either side, each resolved to 20 of its 31 bits; its W
+    // bins are as wide as that needs, so a bin holds about 2e-4 of the set's elements whatever
+    // the data's offset and spread.
+    const long long dr = (long long)(6.f * dev + dev_tokens) + 2;
+    const u32* const hs[2] = {shist, shist};
+    const u32 rs[2] = {(u32)(rk - dr < 1 ? 1 : rk - dr), (u32)(rk + dr > m ? m : rk + dr)};
+    find_ranks<NT, 2, kCopies, false>(hs, rs, stot, s_bin, s_before, nullptr);
     __syncthreads();
     const u32 b0 = s_bin[0], b1 = s_bin[1];
 #pragma unroll
     for (int i = 0; i < kKeys; ++i) {
-      const u32 top = key[i] >> 21, next = (key[i] >> 11) & 1023u;
-      if (key[i] != kDead && top == b0) atomicAdd(&snext[0][next], 1u);
-      if (key[i] != kDead && top == b1) atomicAdd(&snext[1][next], 1u);
+      if (i / V < steps) {
+        const u32 top = key[i] >> 21, next = (key[i] >> 11) & 1023u;
+        if (key[i] != kDead && top == b0) atomicAdd(&snext[0][next], 1u);
+        if (key[i] != kDead && top == b1) atomicAdd(&snext[1][next], 1u);
+      }
     }
     __syncthreads();
-    find_two_ranks<NT, 1>(snext[0], snext[1], r0 - s_before[0], r1 - s_before[1], stot, s_bin + 2,
-                       s_before + 2);
+    const u32* const hn[2] = {snext[0], snext[1]};
+    const u32 rn[2] = {rs[0] - s_before[0], rs[1] - s_before[1]};
+    find_ranks<NT, 2, 1, false>(hn, rn, stot, s_bin + 2, s_before + 2, nullptr);
     __syncthreads();
     const u32 n0 = s_bin[2], n1 = s_bin[3];
     e.lo = (b0 << 21) | (n0 << 11);
+    e.lo = e.lo > 1u ? e.lo : 1u;                      // zeros are counted below
     const u32 span = ((b1 << 21) | (n1 << 11)) + 2047u - e.lo;      // last key - first key
     while ((((unsigned long long)(u32)W << e.shift) - 1ull) < span) ++e.shift;
   }
@@ -444,16 +501,17 @@ __global__ __launch_bounds__(NT) void k_sets(
 }
 
 template <typename TX>
-static void sets_t(const TX* X, int B, int T, int C, long long ld, int G, int W, const float* r,
+static void sets_t(const TX* X, int B, int T, int C, long long ld, int G, int Wfew, int W, const float* r,
                    const double* mean, const double* m2, int* gid, const Scalars& sc, int pass,
                    bool keep_base, GroupWork* grp, Bracket* br, unsigned* bhist, unsigned* lists,
                    int cap, unsigned* img_flag, unsigned* status, hipStream_t st) {
   constexpr int V = Elem<TX>::V;
   const int aligned = ((reinterpret_cast<uintptr_t>(X) & 15) == 0 && ld % V == 0 && C % V == 0) ? 1 : 0;
-  const bool few = W >= 512 && G >= 8 && pass == kPassZr;    // 8 Ki sampled elements are enough
+  // 8 Ki sampled elements are enough, or the image
+  const bool few = (Wfew >= 512 && G >= 8 && pass == kPassZr) || (long long)T * C <= 8192;
   const size_t order_bytes = T <= kListTokens ? (size_t)T * sizeof(unsigned short) : 0;
 #define TDQ_SETS_SM(NT, SM)                                                                        \
-  hipLaunchKernelGGL((k_sets<TX, NT, SM>), dim3(G, B), dim3(NT), order_bytes, st, X, ld, T, C, G, W, aligned, r, \
+  hipLaunchKernelGGL((k_sets<TX, NT, SM>), dim3(G, B), dim3(NT), order_bytes, st, X, ld, T, C, G, Wfew, W, aligned, r, \
                      mean, m2, gid, sc, pass, keep_base ? 1 : 0, grp, br, bhist, lists, cap,       \
                      img_flag, status)
 #define TDQ_SETS(NT)                                                           \
@@ -472,16 +530,16 @@ static void sets_t(const TX* X, int B, int T, int C, long long ld, int G, int W,
 #undef TDQ_SETS_SM
 }
 
-hipError_t launch_sets(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G, int W,
-                       const float* r, const double* mean, const double* m2, int* gid,
+hipError_t launch_sets(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G,
+                       int Wfew, int W, const float* r, const double* mean, const double* m2, int* gid,
                        const Scalars& sc, int pass, bool keep_base, GroupWork* grp, Bracket* br,
                        unsigned* bhist, unsigned* lists, int cap, unsigned* img_flag,
                        unsigned* status, hipStream_t st) {
   if (dt == TDQ_F16)
-    sets_t<u16>(static_cast<const u16*>(X), B, T, C, ld, G, W, r, mean, m2, gid, sc, pass, keep_base,
+    sets_t<u16>(static_cast<const u16*>(X), B, T, C, ld, G, Wfew, W, r, mean, m2, gid, sc, pass, keep_base,
                 grp, br, bhist, lists, cap, img_flag, status, st);
   else
-    sets_t<float>(static_cast<const float*>(X), B, T, C, ld, G, W, r, mean, m2, gid, sc, pass, keep_base,
+    sets_t<float>(static_cast<const float*>(X), B, T, C, ld, G, Wfew, W, r, mean, m2, gid, sc, pass, keep_base,
                   grp, br, bhist, lists, cap, img_flag, status, st);
   return hipGetLastError();
 }
@@ -501,12 +559,13 @@ typedef short s2v __attribute__((ext_vector_type(2)));
 // global additions 13.2 and 44.6 us on the first two.
 template <typename TX, int L, int P>
 __global__ __launch_bounds__(kSweepThreads) void k_bracket_hist(
-    const TX* __restrict__ X, long long ld, int T_, int C, int G, int W,
+    const TX* __restrict__ X, long long ld, int T_, int C, int G, int W, int lw,
     const int* __restrict__ gid, Bracket* __restrict__ br, u32* __restrict__ bhist,
     int rows_per_block) {
   constexpr int R = 4 / P;
   constexpr int V = Elem<TX>::V;
-  extern __shared__ u32 lds[];                    // [G][W] bins, then per set: below, lo, width, shift
+  // [G][W] bins, then per set: below, lo, width, shift
+  extern __shared__ __attribute__((aligned(16))) u32 lds[];
   // walks X backwards: it runs right after the forward statistics sweep, so the end of
   // X is what the last-level cache still holds
   const int b = (int)(gridDim.y - 1 - blockIdx.y);
@@ -517,14 +576,27 @@ __global__ __launch_bounds__(kSweepThreads) void k_bracket_hist(
   u32* s_lo = s_below + G;
   u32* s_width = s_lo + G;
   u32* s_shift = s_width + G;
-  for (int i = tid; i < nwords + G; i += kSweepThreads) lds[i] = 0;
+  // most sets use the first 2^lw bins; the further ones of those that use more are cleared and
+  // added one by one
+  for (int i = tid; i < (G << lw) / 4; i += kSweepThreads) {
+    const int g = i >> (lw - 2), at = i - (g << (lw - 2));
+    *reinterpret_cast<uint4*>(&lds[g * W + 4 * at]) = make_uint4(0, 0, 0, 0);
+  }
   for (int g = tid; g < G; g += kSweepThreads) {
     const Bracket e = br[(long long)b * G + g];
+    s_below[g] = 0;
     s_lo[g] = e.lo;
     s_width[g] = e.width;
     s_shift[g] = e.shift;
   }
   __syncthreads();
+  const int lane = tid & 63;                      // (G <= 64)
+  const bool wide = W > 1 << lw && __ballot(lane < G && (int)s_width[lane < G ? lane : 0] > 1 << lw) != 0;
+  if (wide) {                                     // the same in every wavefront
+    for (int g = 0; g < G; ++g)
+      for (int i = (1 << lw) + tid; i < (int)s_width[g]; i += kSweepThreads) lds[g * W + i] = 0;
+    __syncthreads();
+  }
 
   const int row0 = chunk * rows_per_block;
   int nrows = T_ - row0;
@@ -578,7 +650,8 @@ __global__ __launch_bounds__(kSweepThreads) void k_bracket_hist(
                 if (dh < width) atomicAdd(&h[dh], 1u);
               } else {
                 // keys and lo are below 2^31: the sign of the difference says "key < lo", and
-                // such a difference lies past the last bin (shift <= 22 and 2^31 >> 22 = 512)
+                // such a difference lies past the last bin (the number of bins is a power of two
+                // and bins << shift at most 2^31, so 2^31 >> shift is at least their number)
                 const u32 d = (wd[e] & 0x7FFFFFFFu) - lo;
                 below[i] += d >> 31;
                 const u32 bin = d >> shift;
@@ -607,10 +680,17 @@ __global__ __launch_bounds__(kSweepThreads) void k_bracket_hist(
   }
   __syncthreads();
   u32* gh = bhist + (size_t)b * G * W;
-  for (int i = tid; i < nwords; i += kSweepThreads) {
-    const u32 v = lds[i];
-    if (v) atomicAdd(&gh[i], v);
+  for (int i = tid; i < G << lw; i += kSweepThreads) {
+    const int g = i >> lw, at = g * W + i - (g << lw);
+    const u32 v = lds[at];
+    if (v) atomicAdd(&gh[at], v);
   }
+  if (wide)
+    for (int g = 0; g < G; ++g)
+      for (int i = (1 << lw) + tid; i < (int)s_width[g]; i += kSweepThreads) {
+        const u32 v = lds[g * W + i];
+        if (v) atomicAdd(&gh[g * W + i], v);
+      }
   for (int g = tid; g < G; g += kSweepThreads) {
     const u32 v = s_below[g];
     if (v) atomicAdd(&br[(long long)b * G + g].below, v);
@@ -639,7 +719,7 @@ static int sweep_rows(int B, int T, int C) {
   CASE(32, 2) CASE(32, 4) CASE(64, 2) CASE(64, 4)
 
 template <typename TX>
-static void bracket_hist_t(const TX* X, int B, int T_, int C, long long ld, int G, int W,
+static void bracket_hist_t(const TX* X, int B, int T_, int C, long long ld, int G, int Wfew, int W,
                            const int* gid, Bracket* br, unsigned* bhist, hipStream_t st) {
   const int nvec = C / Elem<TX>::V;
   const int L = sweep_lanes_per_row(C, Elem<TX>::V);
@@ -647,81 +727,92 @@ static void bracket_hist_t(const TX* X, int B, int T_, int C, long long ld, int 
   const int rpb = sweep_rows(B, T_, C);
   const unsigned chunks = (unsigned)((T_ + rpb - 1) / rpb);
   const size_t lds_bytes = ((size_t)G * W + 4 * (size_t)G) * sizeof(u32);
+  int lw = 0;
+  while (1 << lw < Wfew) ++lw;
 #define TDQ_BH(LL, PP)                                                                          \
   if (L == LL && P == PP) {                                                                     \
     if (lds_bytes > 65536)                                                                      \
       (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bracket_hist<TX, LL, PP>),     \
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);    \
     hipLaunchKernelGGL((k_bracket_hist<TX, LL, PP>), dim3(chunks, B), dim3(kSweepThreads),      \
-                       lds_bytes, st, X, ld, T_, C, G, W, gid, br, bhist, rpb);                 \
+                       lds_bytes, st, X, ld, T_, C, G, W, lw, gid, br, bhist, rpb);                 \
   }
   TDQ_SWEEP_CASES(TDQ_BH)
 #undef TDQ_BH
 }
 
 hipError_t launch_bracket_hist(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G,
-                               int W, const int* gid, Bracket* br, unsigned* bhist, hipStream_t st) {
+                               int Wfew, int W, const int* gid, Bracket* br, unsigned* bhist, hipStream_t st) {
   if (dt == TDQ_F16)
-    bracket_hist_t<u16>(static_cast<const u16*>(X), B, T, C, ld, G, W, gid, br, bhist, st);
+    bracket_hist_t<u16>(static_cast<const u16*>(X), B, T, C, ld, G, Wfew, W, gid, br, bhist, st);
   else
-    bracket_hist_t<float>(static_cast<const float*>(X), B, T, C, ld, G, W, gid, br, bhist, st);
+    bracket_hist_t<float>(static_cast<const float*>(X), B, T, C, ld, G, Wfew, W, gid, br, bhist, st);
   return hipGetLastError();
 }
 
-// The bin of a set's interval histogram (W = 256 to 2048 bins) that holds its k-th smallest
+// The bin of a set's interval histogram (W = 256 to 2048 words) that holds its k-th smallest
 // key, by one wavefront; the same in every lane.  ok = the interval does hold it.
 struct BinPick {
   bool ok;
-  u32 bin, need;      // rank wanted among the bin's elements (1-based)
+  u32 bin, need;              // rank wanted among the bin's elements (1-based)
+  unsigned long long inside;  // elements inside the interval
 };
 __device__ __forceinline__ BinPick pick_bin(const u32* __restrict__ hb, int W, u32 below, long long k) {
   const int lane = threadIdx.x & 63;
-  const int per = W / 64;                       // 4 to 32
-  const u32* mine_bins = hb + lane * per;
-  uint4 c[2];                                   // up to 8 bins stay in registers
+  const int quads = W / 256;                    // 1 to 8 groups of four bins per lane
+  const uint4* mine_bins = reinterpret_cast<const uint4*>(hb) + lane * quads;
+  uint4 c[2];                                   // two groups stay in registers
+  u32 sum[8];                                   // (a set has fewer than 2^32 elements)
+#pragma unroll
+  for (int i = 0; i < 2; ++i) c[i] = mine_bins[i < quads ? i : 0];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) sum[i] = i < 2 && i < quads ? c[i].x + c[i].y + c[i].z + c[i].w : 0u;
+  if (quads > 2) {                              // uniform; the loads issued together
+    uint4 t[6];
+#pragma unroll
+    for (int i = 2; i < 8; ++i) t[i - 2] = mine_bins[i < quads ? i : 0];
+#pragma unroll
+    for (int i = 2; i < 8; ++i)
+      sum[i] = i < quads ? t[i - 2].x + t[i - 2].y + t[i - 2].z + t[i - 2].w : 0u;
+  }
   unsigned long long mine = 0;
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    c[i] = *reinterpret_cast<const uint4*>(mine_bins + (4 * i < per ? 4 * i : 0));
-    if (4 * i < per) mine += (unsigned long long)c[i].x + c[i].y + c[i].z + c[i].w;
-  }
-  for (int i = 8; i < per; i += 4) {
-    const uint4 q = *reinterpret_cast<const uint4*>(mine_bins + i);
-    mine += (unsigned long long)q.x + q.y + q.z + q.w;
-  }
+  for (int i = 0; i < 8; ++i) mine += sum[i];
   unsigned long long incl = mine;               // inclusive scan over lanes
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
     const unsigned long long o = __shfl_up(incl, d, 64);
     if (lane >= d) incl += o;
   }
-  const unsigned long long inside = __shfl(incl, 63, 64);
   const unsigned long long kk = (unsigned long long)k;
   BinPick r;
-  r.ok = kk > below && kk - below <= inside;
+  r.inside = __shfl(incl, 63, 64);
+  r.ok = kk > below && kk - below <= r.inside;
   const unsigned long long need = kk - below;
   const unsigned long long hit = __ballot(incl >= need);
   const int src = r.ok ? __ffsll((long long)hit) - 1 : 0;       // hit != 0 because need <= inside
   unsigned long long cum = incl - mine;
-  u32 bin = (u32)(lane * per);
+  int group = 0;                                // the group of four ...
   bool found = false;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const u32 v = (&c[i >> 2].x)[i & 3];
-    found = found || i >= per - 1 || cum + v >= need;
+  for (int i = 0; i < 7; ++i) {
+    found = found || i >= quads - 1 || cum + sum[i] >= need;
     if (!found) {
-      cum += v;
-      ++bin;
+      cum += sum[i];
+      ++group;
     }
   }
-  if (per > 8 && lane == src) {                 // past the ones in registers
-    for (int i = 8; i < per - 1 && !found; ++i) {
-      const u32 v = mine_bins[i];
-      found = cum + v >= need;
-      if (!found) {
-        cum += v;
-        ++bin;
-      }
+  uint4 q = group == 0 ? c[0] : c[1];
+  if (quads > 2) q = mine_bins[group];
+  u32 bin = (u32)(4 * (lane * quads + group));
+  const u32 v[3] = {q.x, q.y, q.z};             // ... and the bin in it
+  found = false;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    found = found || cum + v[i] >= need;
+    if (!found) {
+      cum += v[i];
+      ++bin;
     }
   }
   r.bin = (u32)__shfl((int)bin, src, 64);
@@ -865,29 +956,197 @@ hipError_t launch_bracket_gather(const void* Xv, int B, int T_, int C, long long
 // ---------------------------------------------------------------------------
 // k_bracket_finish: one workgroup per set.  Its first wavefront verifies the interval and
 // finds the bin; that is the key itself (binary16, one key per bin), or the workgroup finds
-// it among the keys that the second sweep collected (binary32).  On a miss, or if more keys
-// were collected than fit, it runs an exact radix select (8 key bits a level, LDS histogram)
-// over the set's own rows.  A chain of dependent trips to memory: the record, the interval and
-// the bins are loaded together.
+// it among the keys that the second sweep collected (binary32).  A chain of dependent trips to
+// memory: the record, the interval and the bins are loaded together.
+//
+// On a miss, or if more keys were collected than fit, the workgroup searches the set's own rows
+// for the key, only on the side of the interval (or in the bin) where it must lie: an LDS
+// histogram of that range over 2048 bins, then of the bin, until a bin is one key.  One
+// workgroup on one CU: bound by the loads it keeps in flight, so the ids of 2048 tokens are read
+// together, a lane takes four pieces of 16 bytes at a time, and with few sets per call, which may
+// be large, a workgroup has 1024 threads.  A binary16 rank that misses its one-key bins lies close
+// to them, so the first pass looks at the 2047 keys next to the interval one by one.  What a miss
+// cost before (eight key bits a pass) was LDS additions that met in one word: nearly all elements
+// lie on one side of the interval.  Calibration with 18 % zeros, 16 sets, binary16: [1, 1936, 1500]
+// 208 us with 6 missed sets, 70 with 4 so; [8, 7744, 512] 584 with 54, 139 with 18.
 // ---------------------------------------------------------------------------
-constexpr int kFinishThreads = 256;
+constexpr int kFinishBits = 11;                 // key bits a pass resolves
+constexpr int kFinishTokens = 2048;             // tokens looked at together
 
-template <typename TX>
-__global__ __launch_bounds__(kFinishThreads) void k_bracket_finish(
-    const TX* __restrict__ X, long long ld, int T, int C, int G,
-    const int* __restrict__ gid, const u32* __restrict__ bhist, int W, const u32* __restrict__ lists,
+// LDS of the search
+template <int NT>
+struct FinishLds {
+  u32 h[1 << kFinishBits];
+  unsigned short list[kFinishTokens];           // the set's tokens among them
+  u32 wtot[NT / 64], digit;
+  unsigned long long wsum[NT / 64], rest;
+};
+
+// Adds the keys of rows list[0 .. n - 1] (offsets from token t0) that lie in [k0, k0 + span) to
+// the histogram of digits (key - k0 >> shift) - off.  Digit 0 takes all that is below as well and
+// is counted in a register, the last digit takes all that is above and is not counted (what the
+// others do not hold): either may be most of the set, and would meet in one word of LDS.
+// Groups of L lanes take R rows and P pieces of each at a time.
+template <typename TX, int NT, int R, int P>
+__device__ __forceinline__ void count_rows(const TX* __restrict__ Xb, long long ld, int C, int L, int t0,
+                                           const unsigned short* list, int n, u32 k0, u32 span, int shift,
+                                           int off, u32* h) {
+  constexpr int V = Elem<TX>::V;
+  const int lr = threadIdx.x & (L - 1), slot = threadIdx.x / L, slots = NT / L;
+  const int nvec = C / V;
+  u32 low = 0;
+  auto count = [&](u32 key) {
+    const u32 d = key - k0;
+    const int digit = d < span ? (int)(d >> shift) - off : 1 << kFinishBits;
+    low += digit <= 0 ? 1u : 0u;
+    if (digit > 0 && digit < (1 << kFinishBits) - 1) atomicAdd(&h[digit], 1u);
+  };
+  for (int rr = slot; rr < n; rr += slots * R) {
+    const TX* xp[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {               // rows past the end: the last one, not counted
+      const int at = rr + slots * i;
+      xp[i] = Xb + (long long)(t0 + (int)list[at < n ? at : n - 1]) * ld;
+    }
+    for (int v0 = lr; v0 < nvec; v0 += P * L) {
+      uint4 q[R][P];
+#pragma unroll
+      for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+          const int v = v0 + k * L;
+          q[i][k] = load16(xp[i] + (long long)(v < nvec ? v : v0) * V);
+        }
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        if (rr + slots * i >= n) break;
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+          if (k > 0 && v0 + k * L >= nvec) break;
+          TX x[V];
+          Elem<TX>::unpack(q[i][k], x);
+#pragma unroll
+          for (int c = 0; c < V; ++c) count(Elem<TX>::key(x[c]));
+        }
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      if (rr + slots * i >= n) break;
+      for (int c = nvec * V + lr; c < C; c += L) count(Elem<TX>::key(xp[i][c]));
+    }
+  }
+  if (low) atomicAdd(&h[0], low);
+}
+
+// The key of rank `need` (1-based) among the set's keys in [k0, k0 + span), by the whole
+// workgroup.  Every pass divides span by 2^kFinishBits, so three passes at most; near < 0 (> 0):
+// one more before them that looks at the last (first) 2047 keys of the range one by one.
+template <typename TX, int NT>
+__device__ __forceinline__ u32 search_rows(const TX* __restrict__ Xb, long long ld, int T, int C, int L,
+                           const int* __restrict__ gb, int j, u32 k0, u32 span, unsigned long long need,
+                           int near, FinishLds<NT>& s) {
+  constexpr int kBins = 1 << kFinishBits, NW = NT / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int nvec = C / Elem<TX>::V;
+  while (span > 1) {
+    int shift = 32 - __clz(span - 1) - kFinishBits, off = 0;
+    shift = shift > 0 && near == 0 ? shift : 0;
+    if (near < 0 && span > (u32)kBins) off = (int)span - kBins;
+    near = 0;
+    __syncthreads();
+    for (int i = tid; i < kBins; i += NT) s.h[i] = 0;
+    if (tid == 0) s.digit = kBins - 1;
+    for (int t0 = 0; t0 < T; t0 += kFinishTokens) {
+      constexpr int kIds = kFinishTokens / NT;
+      bool mine[kIds];
+      u32 count = 0;
+#pragma unroll
+      for (int u = 0; u < kIds; ++u) {
+        const int t = t0 + u * NT + tid;
+        mine[u] = t < T && gb[t] == j;
+      }
+#pragma unroll
+      for (int u = 0; u < kIds; ++u) count += (u32)__popcll(__ballot(mine[u]));
+      if (lane == 0) s.wtot[wave] = count;
+      __syncthreads();
+      u32 at = 0, n = 0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        at += w < wave ? s.wtot[w] : 0u;
+        n += s.wtot[w];
+      }
+#pragma unroll
+      for (int u = 0; u < kIds; ++u) {
+        const unsigned long long m = __ballot(mine[u]);
+        if (mine[u])
+          s.list[at + (u32)__popcll(m & ((1ull << lane) - 1ull))] = (unsigned short)(u * NT + tid);
+        at += (u32)__popcll(m);
+      }
+      __syncthreads();
+      if (nvec <= L)
+        count_rows<TX, NT, 4, 1>(Xb, ld, C, L, t0, s.list, (int)n, k0, span, shift, off, s.h);
+      else if (nvec <= 2 * L)
+        count_rows<TX, NT, 2, 2>(Xb, ld, C, L, t0, s.list, (int)n, k0, span, shift, off, s.h);
+      else
+        count_rows<TX, NT, 1, 4>(Xb, ld, C, L, t0, s.list, (int)n, k0, span, shift, off, s.h);
+      __syncthreads();                          // `list` and `wtot` are reused
+    }
+    // the bin where the running count reaches `need`
+    constexpr int kPer = kBins / NT;
+    unsigned long long mine = 0;
+    u32 c[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      c[i] = s.h[tid * kPer + i];
+      mine += c[i];
+    }
+    unsigned long long incl = mine;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const unsigned long long o = __shfl_up(incl, d, 64);
+      if (lane >= d) incl += o;
+    }
+    if (lane == 63) s.wsum[wave] = incl;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < NW; ++w) incl += w < wave ? s.wsum[w] : 0ull;
+    if (tid == NT - 1 && incl < need) s.rest = need - incl;       // the last digit
+    if (incl - mine < need && need <= incl) {   // at most one thread
+      unsigned long long cum = incl - mine;
+      int i = 0;
+      for (; i < kPer - 1; ++i) {
+        if (cum + c[i] >= need) break;
+        cum += c[i];
+      }
+      s.digit = (u32)(tid * kPer + i);
+      s.rest = need - cum;
+    }
+    __syncthreads();
+    const u32 digit = s.digit, first = digit == 0 ? 0u : (digit + (u32)off) << shift;
+    const u32 next = digit == kBins - 1 ? span : (digit + (u32)off + 1u) << shift;
+    k0 += first;
+    span = (next < span ? next : span) - first;
+    need = s.rest;
+  }
+  return k0;
+}
+
+template <typename TX, int NT>
+__global__ __launch_bounds__(NT, NT == 256 ? 8 : 4) void k_bracket_finish(
+    const TX* __restrict__ X, long long ld, int T, int C, int G, int L,
+    const int* __restrict__ gid, const u32* __restrict__ bhist, int Wfew, int W, const u32* __restrict__ lists,
     int cap, int force_miss, Scalars sc, int pass, GroupWork* __restrict__ grp,
     const Bracket* __restrict__ br, float* __restrict__ clip, float* __restrict__ scale,
     tdq_group_stats* __restrict__ stats, const u32* __restrict__ img_flag, int B,
     u32* __restrict__ status) {
   constexpr bool F16 = sizeof(TX) == 2;
-  constexpr int V = Elem<TX>::V;
-  __shared__ u32 h[256];
-  __shared__ int list[kFinishThreads];
+  constexpr u32 kKeysAll = F16 ? 1u << 15 : 1u << 31;
+  __shared__ FinishLds<NT> lds;
   __shared__ u32 s_keys[F16 ? 1 : kListMax];
-  __shared__ u32 wtot[kFinishThreads / 64];
-  __shared__ u32 s_ok, s_key, s_need, s_digit;
-  __shared__ unsigned long long s_rem;
+  __shared__ u32 s_ok, s_key, s_need, s_k0, s_span;
+  __shared__ int s_near;
+  __shared__ unsigned long long s_rank;
   const int idx = blockIdx.x;
   const int b = idx / G, j = idx - b * G;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -907,15 +1166,27 @@ __global__ __launch_bounds__(kFinishThreads) void k_bracket_finish(
   };
   enum { kMiss = 0, kDone = 1, kInList = 2 };
   if (wave == 0) {
-    u32 ok = kMiss;
+    u32 ok = kMiss, k0 = 0, span = kKeysAll;    // where a missed key lies, and its rank there
+    int near = 0;
+    unsigned long long rank = (unsigned long long)w.k_rem;
     if (!force_miss) {
       const Bracket e = br[idx];
-      const BinPick p = pick_bin(bhist + (size_t)idx * W, W, e.below, w.k_rem);
+      // (the further bins of a set that uses more are looked at only if the first do not do)
+      BinPick p = pick_bin(bhist + (size_t)idx * W, Wfew, e.below, w.k_rem);
+      if (w.tokens != 0 && !p.ok && (int)e.width > Wfew && w.k_rem > e.below) {
+        const unsigned long long first = p.inside;
+        p = pick_bin(bhist + (size_t)idx * W + Wfew, W - Wfew, e.below + (u32)first, w.k_rem);
+        p.inside += first;
+        p.bin += (u32)Wfew;
+      }
       if (w.tokens == 0) {
         ok = kDone;
         if (lane == 0 && pass == kPassZr) project_store(idx, w, 0u, F16, sc, clip, scale, stats);
       } else if (p.ok) {                        // wavefront-uniform
         u32 key = e.lo + (p.bin << e.shift);
+        k0 = key;
+        span = 1u << e.shift;
+        rank = p.need;
         ok = kDone;
         if (!F16 && e.shift != 0) {
           const u32 lo = ~lists[(size_t)idx * cap], hi = lists[(size_t)idx * cap + 1];
@@ -924,12 +1195,31 @@ __global__ __launch_bounds__(kFinishThreads) void k_bracket_finish(
         }
         if (ok == kDone && lane == 0) finish(key);
         if (lane == 0) s_need = p.need;
+      } else if (rank <= e.below) {             // below the interval
+        span = e.lo;
+        near = F16 ? -1 : 0;
+        if (span == 1u) {                       // ... where there are only zeros
+          ok = kDone;
+          if (lane == 0) finish(0u);
+        }
+      } else {                                  // above it
+        k0 = e.lo + (e.width << e.shift);
+        k0 = k0 < kKeysAll ? k0 : kKeysAll - 1u;
+        span = kKeysAll - k0;
+        near = F16 ? 1 : 0;
+        rank -= e.below + p.inside;
       }
     } else if (w.tokens == 0) {
       ok = kDone;
       if (lane == 0 && pass == kPassZr) project_store(idx, w, 0u, F16, sc, clip, scale, stats);
     }
-    if (lane == 0) s_ok = ok;
+    if (lane == 0) {
+      s_ok = ok;
+      s_k0 = k0;
+      s_span = span;
+      s_near = near;
+      s_rank = rank;
+    }
   }
   __syncthreads();
   if (s_ok == kDone) return;
@@ -937,10 +1227,10 @@ __global__ __launch_bounds__(kFinishThreads) void k_bracket_finish(
     if (s_ok == kInList) {
       // the key with fewer than `need` smaller ones and at least `need` not larger
       const int n = (int)w.prefix;
-      for (int i = tid; i < n; i += kFinishThreads) s_keys[i] = lists[(size_t)idx * cap + 2 + i];
+      for (int i = tid; i < n; i += NT) s_keys[i] = lists[(size_t)idx * cap + 2 + i];
       __syncthreads();
       const u32 need = s_need;
-      for (int i = tid; i < n; i += kFinishThreads) {
+      for (int i = tid; i < n; i += NT) {
         const u32 mine = s_keys[i];
         u32 less = 0, equal = 0;
         for (int c = 0; c < n; ++c) {
@@ -955,82 +1245,30 @@ __global__ __launch_bounds__(kFinishThreads) void k_bracket_finish(
       return;
     }
   }
-
   // The interval missed rank k (or the validation switch asked for this route).
   if (tid == 0) atomicAdd(&status[1 + pass], 1u);
-  const int* gb = gid + (long long)b * T;
-  unsigned long long k = (unsigned long long)w.k_rem;
-  u32 prefix = 0;
-  constexpr int kBits = F16 ? 15 : 31, kLevels = F16 ? 2 : 4;
-  const int nvec = C / V;
-  for (int level = 0; level < kLevels; ++level) {
-    const int bits = level == kLevels - 1 ? 7 : 8;
-    const int shift = kBits - 8 * level - bits;
-    const u32 mask = (1u << bits) - 1u;
-    h[tid] = 0;                                 // kFinishThreads == 256 bins
-    __syncthreads();
-    auto count = [&](u32 key) {
-      if (level == 0 || (key >> (shift + bits)) == prefix) atomicAdd(&h[(key >> shift) & mask], 1u);
-    };
-    for (int t0 = 0; t0 < T; t0 += kFinishThreads) {
-      // the set's tokens among t0 .. t0 + 255, compacted into `list`
-      const int t = t0 + tid;
-      const bool match = t < T && gb[t] == j;
-      const unsigned long long m = __ballot(match);
-      if (lane == 0) wtot[wave] = (u32)__popcll(m);
-      __syncthreads();
-      u32 before = 0, n_list = 0;
-#pragma unroll
-      for (int w2 = 0; w2 < kFinishThreads / 64; ++w2) {
-        before += w2 < wave ? wtot[w2] : 0u;
-        n_list += wtot[w2];
-      }
-      if (match) list[before + (u32)__popcll(m & ((1ull << lane) - 1ull))] = t;
-      __syncthreads();
-      for (u32 i = wave; i < n_list; i += kFinishThreads / 64) {     // one wavefront per row
-        const TX* xp = X + ((long long)b * T + list[i]) * ld;
-        for (int v = lane; v < nvec; v += 64) {
-          TX x[V];
-          Elem<TX>::unpack(load16(xp + (long long)v * V), x);
-#pragma unroll
-          for (int c = 0; c < V; ++c) count(Elem<TX>::key(x[c]));
-        }
-        for (int c = nvec * V + lane; c < C; c += 64) count(Elem<TX>::key(xp[c]));
-      }
-      __syncthreads();                          // `list` and `wtot` are reused
-    }
-    if (tid == 0) {
-      unsigned long long cum = 0;
-      const int nb = 1 << bits;
-      int bin = 0;
-      for (; bin < nb - 1; ++bin) {
-        if (cum + h[bin] >= k) break;
-        cum += h[bin];
-      }
-      s_digit = (u32)bin;
-      s_rem = k - cum;
-    }
-    __syncthreads();
-    prefix = (prefix << bits) | s_digit;
-    k = s_rem;
-    __syncthreads();
-  }
-  if (tid == 0) finish(prefix);
+  const u32 key = search_rows<TX, NT>(X + (long long)b * T * ld, ld, T, C, L, gid + (long long)b * T, j, s_k0,
+                                      s_span, s_rank, s_near, lds);
+  if (tid == 0) finish(key);
 }
 
 hipError_t launch_bracket_finish(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G,
-                                 int W, const int* gid, const unsigned* bhist, const unsigned* lists,
-                                 int cap, bool force_miss, const Scalars& sc, int pass, GroupWork* grp,
+                                 int Wfew, int W, const int* gid, const unsigned* bhist,
+                                 const unsigned* lists, int cap, bool force_miss, const Scalars& sc, int pass, GroupWork* grp,
                                  const Bracket* br, float* clip, float* scale, tdq_group_stats* stats,
                                  const unsigned* img_flag, unsigned* status, hipStream_t st) {
-  if (dt == TDQ_F16)
-    hipLaunchKernelGGL((k_bracket_finish<u16>), dim3(B * G), dim3(kFinishThreads), 0, st,
-                       static_cast<const u16*>(X), ld, T, C, G, gid, bhist, W, lists, cap,
-                       force_miss ? 1 : 0, sc, pass, grp, br, clip, scale, stats, img_flag, B, status);
-  else
-    hipLaunchKernelGGL((k_bracket_finish<float>), dim3(B * G), dim3(kFinishThreads), 0, st,
-                       static_cast<const float*>(X), ld, T, C, G, gid, bhist, W, lists, cap,
-                       force_miss ? 1 : 0, sc, pass, grp, br, clip, scale, stats, img_flag, B, status);
+  const int L = sweep_lanes_per_row(C, dt == TDQ_F16 ? 8 : 4);
+#define TDQ_FINISH(TX, NT)                                                                              \
+  hipLaunchKernelGGL((k_bracket_finish<TX, NT>), dim3(B * G), dim3(NT), 0, st, static_cast<const TX*>(X), \
+                     ld, T, C, G, L, gid, bhist, Wfew, W, lists, cap, force_miss ? 1 : 0, sc, pass, grp,  \
+                     br, clip, scale, stats, img_flag, B, status)
+  const bool large = B * G <= 256;              // one workgroup per CU
+  if (dt == TDQ_F16) {
+    if (large) TDQ_FINISH(u16, 1024); else TDQ_FINISH(u16, 256);
+  } else {
+    if (large) TDQ_FINISH(float, 1024); else TDQ_FINISH(float, 256);
+  }
+#undef TDQ_FINISH
   return hipGetLastError();
 }
 

@@ -1,0 +1,69 @@
+"""The sampled rank select where keys are sparse around the rank: just above the zeros of a
+rectified or masked activation, between the values of a coarse grid, at the edge between two
+groups of values.  Every result against the oracle; the count of sets whose interval missed says
+that the interval was placed well where it can be, and that the search of a set's own rows is
+what found the key where it cannot (that search may cost time, never the result)."""
+import numpy as np
+import pytest
+
+from paper_2604_16855_amd import tdq
+
+import parity_util as U
+
+pytestmark = pytest.mark.gpu
+
+KINDS = ("relu10", "relu15", "relu50", "mask15", "grid", "clamp6", "sigmoid", "near")
+EDGES = ("relu20", "mask20", "two")              # a fifth zero: the rank at the gap itself
+
+
+def _data(kind, B, T, C, dtype, seed):
+    rng = np.random.Generator(np.random.PCG64(seed))
+    x = rng.normal(0, 1, (B, T, C))
+    tok = rng.lognormal(0, 0.5, (B, T, 1))
+    if kind.startswith("relu"):                  # that many per cent of zeros
+        cut = np.quantile(x, int(kind[4:]) / 100)
+        x = np.maximum(x - cut, 0.0) * tok
+    elif kind.startswith("mask"):
+        x = np.where(rng.random(x.shape) < int(kind[4:]) / 100, 0.0, x * tok)
+    elif kind == "grid":
+        x = np.round(20 * rng.laplace(0, 1, x.shape)) * 0.0371
+    elif kind == "clamp6":                       # one token set: all tokens share their range
+        x = np.clip(3 * x + 3, 0, 6)
+    elif kind == "sigmoid":
+        x = 1 / (1 + np.exp(-3 * x))
+    elif kind == "near":                         # within 1e-5 of a constant
+        x = 1 + 1e-5 * x
+    elif kind == "two":
+        x = np.where(rng.random(x.shape) < 0.2, 1e-3 * x, 5 + 0.1 * x)
+    return x.astype(dtype)
+
+
+def _check(X, G, pct=0.0):
+    p = tdq.default_params(G)
+    p.base_pct = pct
+    g = U.gpu_calibrate(X, p)
+    U.assert_calibration_matches(g, X, p)
+    return g["exact_sets"]
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("G", [1, 6, 16])
+def test_interval_reaches_the_rank(kind, G):
+    """No set may need the search on such data."""
+    assert _check(_data(kind, 2, 1024, 768, np.float16, 7), G) == 0
+
+
+@pytest.mark.parametrize("pct", [0.0, 0.99])
+@pytest.mark.parametrize("kind", EDGES)
+@pytest.mark.parametrize("B,T,C,G", [(2, 700, 520, 16), (4, 300, 333, 3), (20, 260, 264, 16), (9, 200, 40, 64),
+                                     (1, 5000, 70, 1)])
+def test_rank_at_the_gap(kind, B, T, C, G, pct):
+    """Few and many sets (1024 and 256 threads in the search), one and several rows per lane
+    group, more tokens than one look takes, row tails."""
+    _check(_data(kind, B, T, C, np.float16, B * T + C), G, pct)
+
+
+def test_search_finds_both_sides():
+    """Images on which intervals do miss, below the interval and above it."""
+    missed = sum(_check(_data(k, 20, 260, 264, np.float16, s), 16) for k in EDGES for s in (1, 2))
+    assert missed > 0
