@@ -113,6 +113,24 @@ static Scalars make_scalars(const tdq_params* p) {
   return s;
 }
 
+// Whether a binary32 calibration samples (two sweeps of X) or takes the radix levels (one sweep per
+// eight to five key bits, whatever the data).
+//   * A bin that collects more keys than a list holds, or an interval that misses, costs a search
+//     of the set's rows by one workgroup: 50 us for 0.2 M elements, 200 for 1 M, against 50 to 70 for
+//     all radix levels of such an image.  So images stay below 1 Mi elements, 0.6 Mi with more
+//     than 32 sets, whose lists are short.
+//   * Its first kernel has a workgroup per set, each of which reads the image's T ranges.  Images
+//     of many tokens and few sets ([1, 400000, 1], one set: 239 us by levels, 473 sampled; 16 sets 467
+//     and 470; [1, 100000, 8], 5 sets: 117 and 159; 16 sets 166 and 130; [1, 16385, 33], one set: 69
+//     and 57) and large batches of small sets ([2048, 49, 96], 5 sets: 127 and 177; [512, 49, 768],
+//     16 sets: 145 and 159; [64, 196, 384], 64 sets: 97 and 86) are faster by levels.
+static bool sampled_f32(int B, int T, int C, int G) {
+  const long long elements = (long long)T * C;
+  if (T > 32768 && T > 16384ll * G) return false;
+  if ((long long)B * G > 4096 && elements < 3072ll * G) return false;
+  return elements < (G <= 32 ? 1ll << 20 : 638976ll);
+}
+
 // Everything of tdq_calibrate_groups after the per-token statistics (which are in the
 // workspace): assignment, rank select(s), projection.  X is token-major.
 static int calibrate_after_stats(const void* X, tdq_dtype dt, int32_t B, int32_t T, int32_t C,
@@ -139,16 +157,12 @@ static int calibrate_after_stats(const void* X, tdq_dtype dt, int32_t B, int32_t
   const int Wmax = bracket_bins(G);
   const bool exact_only = (p->flags & TDQ_FLAG_EXACT_SELECT) != 0;
   // words per set of the radix levels' histograms, which the sampled route of binary32 input
-  // uses as the lists of collected keys: it expects up to 2e-4 of a set's elements there (an
-  // interval of about a tenth of its mass over 512 bins) and is taken while that fits the list
-  // with a third to spare for the largest set an image can have
+  // uses for the head, the cells and the collected keys of a set
   int cap = 0;
   for (int l = 0; l < lp.n_levels; ++l) cap += 1 << lp.bits[l];
   cap = cap > kListMax ? kListMax : cap;
   const bool f16 = dt == TDQ_F16;
-  const bool sampled =
-      Wmax > 0 && (f16 ? (long long)T * C < (1ll << 32)
-                       : !exact_only && (long long)T * C <= (G <= 32 ? 3328ll : 1664ll) * cap);
+  const bool sampled = Wmax > 0 && (f16 ? (long long)T * C < (1ll << 32) : !exact_only && sampled_f32(B, T, C, G));
   Bracket* br = reinterpret_cast<Bracket*>(ws + wl.br);
   unsigned* bhist = reinterpret_cast<unsigned*>(ws + wl.bhist);
   const bool two_passes = sc.base_pct > 0.0;
@@ -160,24 +174,25 @@ static int calibrate_after_stats(const void* X, tdq_dtype dt, int32_t B, int32_t
   for (int pass = two_passes ? kPassBase : kPassZr; pass >= kPassZr; --pass) {
     const bool keep_base = two_passes && pass == kPassZr;
     // binary32: a bin is as wide as the interval needs, 512 of them (256) are enough
-    // (binary16: few bins where the interval fits them, else all that there is room for)
-    const int W = !f16 ? (G <= 32 ? 512 : 256) : Wmax;
+    // binary16: few bins where the interval fits them, else all that there is room for
+    const int W = f16 ? Wmax : G <= 32 ? 512 : 256;
     const int Wfew = f16 && pass == kPassZr ? bracket_bins_zr(G) : W;
+    const int cells = f16 ? 0 : G <= 32 ? 64 : 32;
     if (sampled) {
       if (!exact_only) {
-        if (launch_sets(X, dt, B, T, C, ld_x, G, Wfew, W, r, mean, m2, group_id, sc, pass, keep_base, grp,
+        if (launch_sets(X, dt, B, T, C, ld_x, G, Wfew, W, cells, r, mean, m2, group_id, sc, pass, keep_base, grp,
                         br, bhist, hist, cap, img_flag, status, st) != hipSuccess)
           return TDQ_ERR_HIP;
-        if (launch_bracket_hist(X, dt, B, T, C, ld_x, G, Wfew, W, group_id, br, bhist, st) != hipSuccess)
+        if (launch_bracket_hist(X, dt, B, T, C, ld_x, G, Wfew, W, cells, hist, cap, group_id, br, bhist, st) != hipSuccess)
           return TDQ_ERR_HIP;
-        if (!f16 && launch_bracket_gather(X, B, T, C, ld_x, G, W, group_id, br, bhist, grp, hist, cap,
+        if (!f16 && launch_bracket_gather(X, B, T, C, ld_x, G, W, cells, group_id, br, bhist, grp, hist, cap,
                                           st) != hipSuccess)
           return TDQ_ERR_HIP;
       } else if (launch_finalize_groups(part, B, T, C, G, sc, pass, keep_base, grp, hist, lp, st) !=
                  hipSuccess) {
         return TDQ_ERR_HIP;
       }
-      if (launch_bracket_finish(X, dt, B, T, C, ld_x, G, Wfew, W, group_id, bhist, hist, cap, exact_only, sc,
+      if (launch_bracket_finish(X, dt, B, T, C, ld_x, G, Wfew, W, cells, group_id, bhist, hist, cap, exact_only, sc,
                                 pass, grp, br, clip, scale, stats, img_flag, status, st) != hipSuccess)
         return TDQ_ERR_HIP;
       continue;

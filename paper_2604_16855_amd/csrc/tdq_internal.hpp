@@ -29,13 +29,14 @@ struct GroupWork {
   float sigma;          // population std + eps_std
 };
 
-// Key interval [lo, lo + (width << shift)) that a sample says holds the k-th smallest
-// magnitude key of an (image, token set), and what the sweep counted for it.
+// Key interval that a sample says holds the k-th smallest magnitude key of an (image, token
+// set), and what the sweep counted for it: `width` bins of 2^shift keys from lo on (binary16: of one
+// key), or (binary32, bit 8 of shift) `width` keys cut into cells of 2^(shift & 63) keys.
 struct Bracket {
-  unsigned lo;       // first key of the interval
-  unsigned width;    // histogram bins of the interval, 0 = nothing to count
+  unsigned lo;       // first key of the interval, at least 1
+  unsigned width;    // bins or keys of the interval, 0 = nothing to count
   unsigned below;    // elements of the set with key < lo
-  unsigned shift;    // a bin is 2^shift keys wide (binary16: one key)
+  unsigned shift;
 };
 constexpr int kBracketLdsWords = 16384;   // 64 KiB of LDS histogram per workgroup (128 KiB, one
                                           // workgroup per CU, made the sweep 30 % slower)
@@ -133,20 +134,21 @@ hipError_t launch_select(unsigned* hist_level, int B, int G, int shift, int bits
                          unsigned* status, int pass, hipStream_t st);
 // Rank select guided by a sample: binary16 input in one sweep, binary32 input in two (the
 // second, launch_bracket_gather, collects the keys of one bin per set into `lists`, cap words
-// per set, the first two of them the largest ~key and the largest key).  Of the W bins of a set's
-// interval histogram most sets use the first Wfew.
+// per set).  Of the W bins of a set's interval histogram most binary16 sets use the first Wfew;
+// binary32: the interval is cut into `cells` cells and those into W bins.
 hipError_t launch_sets(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G,
-                       int Wfew, int W, const float* r, const double* mean, const double* m2, int* gid,
+                       int Wfew, int W, int cells, const float* r, const double* mean, const double* m2, int* gid,
                        const Scalars& sc, int pass, bool keep_base, GroupWork* grp, Bracket* br,
                        unsigned* bhist, unsigned* lists, int cap, unsigned* img_flag,
                        unsigned* status, hipStream_t st);
 hipError_t launch_bracket_hist(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G,
-                               int Wfew, int W, const int* gid, Bracket* br, unsigned* bhist, hipStream_t st);
+                               int Wfew, int W, int cells, unsigned* lists, int cap, const int* gid,
+                               Bracket* br, unsigned* bhist, hipStream_t st);
 hipError_t launch_bracket_gather(const void* X, int B, int T, int C, long long ld, int G, int W,
-                                 const int* gid, const Bracket* br, const unsigned* bhist,
+                                 int cells, const int* gid, const Bracket* br, const unsigned* bhist,
                                  GroupWork* grp, unsigned* lists, int cap, hipStream_t st);
 hipError_t launch_bracket_finish(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G,
-                                 int Wfew, int W, const int* gid, const unsigned* bhist,
+                                 int Wfew, int W, int cells, const int* gid, const unsigned* bhist,
                                  const unsigned* lists, int cap, bool force_miss, const Scalars& sc, int pass, GroupWork* grp,
                                  const Bracket* br, float* clip, float* scale, tdq_group_stats* stats,
                                  const unsigned* img_flag, unsigned* status, hipStream_t st);

@@ -39,6 +39,20 @@ constexpr int kSweepThreads = 1024;
 constexpr int kIdRounds = 16;                                   // range keys a thread of k_sets holds
 constexpr int kListTokens = 16384;                              // most tokens listed by rank in LDS
 
+// binary32: what a set's `lists` area of cap words holds.  First a head: the largest ~key and the
+// largest key collected; a key that the sample holds often, or kNoKey, how often the set holds it,
+// and its bin.  Then, if the interval has cells (kCells in Bracket::shift), these: at most 64, each
+// its first bin | number of bins << 16.  Then the collected keys.
+constexpr int kListHead = 8;
+enum { kHeadMin = 0, kHeadMax, kHeadTie, kHeadTies, kHeadTieBin };
+constexpr u32 kNoKey = 0xFFFFFFFFu;
+constexpr u32 kCells = 0x100u;
+
+// Bin of a key d past the interval's start: cell d >> shift is cut into equal parts (1 <= shift).
+__device__ __forceinline__ u32 bin_of(u32 d, u32 shift, u32 cell) {
+  return (cell & 0xFFFFu) + __umulhi(d << (32u - shift), cell >> 16);
+}
+
 // ---------------------------------------------------------------------------
 // k_sets: one workgroup of NT threads per (image, token set).
 //   1. the image's smallest and largest range key -> the key interval that belongs to this
@@ -127,7 +141,7 @@ __device__ __forceinline__ void find_ranks(const u32* const (&h)[K], const u32 (
 
 template <typename TX, int NT, int SM>
 __global__ __launch_bounds__(NT) void k_sets(
-    const TX* __restrict__ X, long long ld, int T, int C, int G, int Wfew, int W, int aligned,
+    const TX* __restrict__ X, long long ld, int T, int C, int G, int Wfew, int W, int cells, int aligned,
     const float* __restrict__ r, const double* __restrict__ mean, const double* __restrict__ m2,
     int* __restrict__ gid, Scalars sc, int pass, int keep_base, GroupWork* __restrict__ grp,
     Bracket* __restrict__ br, u32* __restrict__ bhist, u32* __restrict__ lists, int cap,
@@ -145,6 +159,7 @@ __global__ __launch_bounds__(NT) void k_sets(
   __shared__ __attribute__((aligned(16))) u32 shist[kCopies << kSampleBits];   // sample histogram
                                                      // over the top key bits
   __shared__ u32 snext[F16 ? 1 : 2][F16 ? 1 : 1 << kSampleBits];   // binary32: two over the next ones
+  __shared__ u32 s_cell[F16 ? 1 : 66], s_mode, s_tie;   // binary32: sampled keys per cell, one more at each end
   __shared__ __attribute__((aligned(16))) u32 cum[F16 ? 1024 : 4];                // binary16: sampled elements before every bin
   __shared__ u32 s_bin[4], s_before[4];
   __shared__ u32 s_min[NW], s_max[NW], wtot[NW], stot[3][NW], s_cmax[NW];
@@ -173,8 +188,11 @@ __global__ __launch_bounds__(NT) void k_sets(
   // ---- 1: key range of the image, key interval of the set
   load_keys(0);
   for (int i = tid; i < (kCopies << kSampleBits); i += NT) shist[i] = 0;
-  if (!F16)
+  if (!F16) {
     for (int i = tid; i < (int)(sizeof(snext) / sizeof(u32)); i += NT) (&snext[0][0])[i] = 0;
+    if (tid < 66) s_cell[tid] = 0;
+    if (tid == 0) s_mode = 0;
+  }
   u32 kinv = 0, kmax = 0;                            // largest ~key, largest key
   for (int t0 = 0;;) {
 #pragma unroll
@@ -245,7 +263,6 @@ __global__ __launch_bounds__(NT) void k_sets(
     }
     return;
   }
-  if (!F16 && tid < 2) lists[(size_t)idx * cap + tid] = 0;
 
   // the sweep adds into this set's histogram: clear it here (more of it below if more is used)
   for (int i = tid; i < Wfew; i += NT) bhist[(size_t)idx * W + i] = 0;
@@ -469,9 +486,9 @@ __global__ __launch_bounds__(NT) void k_sets(
     e.lo = lo > 1 ? (u32)lo : 1u;                      // zeros are counted below
   } else {
     // The interval between two order statistics of the sample, six standard deviations of its
-    // elements and one of its tokens to either side, each resolved to 20 of its 31 bits; its W
-    // bins are as wide as that needs, so a bin holds about 2e-4 of the set's elements whatever
-    // the data's offset and spread.
+    // elements and one of its tokens to either side, each resolved to 20 of its 31 bits, in W bins
+    // of 2^shift keys: a bin then holds about 2e-4 of the set's elements whatever the data's
+    // offset and spread.
     const long long dr = (long long)(6.f * dev + dev_tokens) + 2;
     const u32* const hs[2] = {shist, shist};
     const u32 rs[2] = {(u32)(rk - dr < 1 ? 1 : rk - dr), (u32)(rk + dr > m ? m : rk + dr)};
@@ -491,32 +508,121 @@ __global__ __launch_bounds__(NT) void k_sets(
     const u32 rn[2] = {rs[0] - s_before[0], rs[1] - s_before[1]};
     find_ranks<NT, 2, 1, false>(hn, rn, stot, s_bin + 2, s_before + 2, nullptr);
     __syncthreads();
-    const u32 n0 = s_bin[2], n1 = s_bin[3];
-    e.lo = (b0 << 21) | (n0 << 11);
+    e.lo = (b0 << 21) | (s_bin[2] << 11);
     e.lo = e.lo > 1u ? e.lo : 1u;                      // zeros are counted below
-    const u32 span = ((b1 << 21) | (n1 << 11)) + 2047u - e.lo;      // last key - first key
-    while ((((unsigned long long)(u32)W << e.shift) - 1ull) < span) ++e.shift;
+    const u32 last = ((b1 << 21) | (s_bin[3] << 11)) + 2047u - e.lo;      // last key - first key
+    while ((((unsigned long long)(u32)W << e.shift) - 1ull) < last) ++e.shift;
+    // But it may also reach from the smallest key to a normal value, where the rank lies just
+    // above the zeros of an activation, or hold a few values within 1e-5 of each other, and a bin
+    // must not hold more keys than the second sweep can collect.  So the sample is counted in 64
+    // (32) cells, as far as the interval must reach, and where one of them has more than that, a
+    // cell is cut into as many bins as the sample's share of it: bins of equal mass, nearly.
+    // (Bins of equal width collected up to 13 000 keys with 15 % zeros: [8, 1024, 768] with 16 sets
+    // calibrated in 290 us, 62 so; without gaps 45, and 53 so, 60 if every interval is cut.)
+    u32* head = lists + (size_t)idx * cap;
+    if (tid < kListHead) head[tid] = tid == kHeadTie || tid == kHeadTieBin ? kNoKey : 0u;
+    const float enough = (float)(cap - kListHead - cells) * mf / (float)n;     // sampled keys
+    if (e.shift == 0 || (float)(rs[1] - rs[0]) <= enough) {        // the same for every thread
+      if (tid == 0) br[idx] = e;
+      return;
+    }
+    const u32 cshift = e.shift + (u32)__clz(cells) - (u32)__clz(W);
+#pragma unroll
+    for (int i = 0; i < kKeys; ++i) {
+      if (i / V < steps) {
+        const u32 d = key[i] - e.lo;
+        if (key[i] != kDead && d <= last) atomicAdd(&s_cell[1 + (d >> cshift)], 1u);
+      }
+    }
+    __syncthreads();
+    u32 mine = lane < cells ? s_cell[1 + lane] : 0u;
+    const u32 most = (u32)__builtin_amdgcn_readlane((int)group_max_u32<64>((mine << 6) | (u32)lane), 63);
+    if ((float)(most >> 6) <= enough) {
+      if (tid == 0) br[idx] = e;
+      return;
+    }
+    e.width = last + 1u;                               // (no further than that)
+    e.shift = cshift;
+    // That cell may hold ties, which could be more than a list holds, with other values in the
+    // same bin: the key that the sample holds most often there (of those that share its hash) is
+    // counted by itself.
+    u32 tie = kNoKey;
+    {
+      constexpr int kHash = 2048;
+      const u32 heavy = most & 63u;
+      for (int i = tid; i < kHash; i += NT) shist[i] = 0;
+      __syncthreads();
+      auto in_heavy = [&](u32 k) { return k != kDead && k - e.lo <= last && (k - e.lo) >> cshift == heavy; };
+      auto hash = [&](u32 k) { return (k * 2654435761u) >> 21; };
+#pragma unroll
+      for (int i = 0; i < kKeys; ++i)
+        if (i / V < steps && in_heavy(key[i])) atomicAdd(&shist[hash(key[i])], 1u);
+      __syncthreads();
+      u32 best = 0;
+      for (int i = tid; i < kHash; i += NT) {
+        const u32 c = (shist[i] << 11) | (u32)i;       // (at most 2^14 sampled keys)
+        best = c > best ? c : best;
+      }
+      best = group_max_u32<64>(best);
+      if (lane == 63) atomicMax(&s_mode, best);
+      __syncthreads();
+      const u32 often = s_mode >> 11;
+#pragma unroll
+      for (int i = 0; i < kKeys; ++i)
+        if (i / V < steps && in_heavy(key[i]) && hash(key[i]) == (s_mode & (kHash - 1))) s_tie = key[i];   // any of them
+      __syncthreads();
+      if (often >= 4u) {
+        tie = s_tie;
+        if (lane == (int)heavy) mine -= often;
+      }
+    }
+    if (wave != 0) return;
+    // bins of a cell: one, and its share of the others by the sampled keys in it, or the average
+    // with its neighbours if that is more (the density is smooth more often than the sample is)
+    const u32 around = ((lane > 0 ? s_cell[lane] : 0u) + mine + (lane + 1 < cells ? s_cell[2 + lane] : 0u) + 2u) / 3u;
+    u32 parts = lane < cells ? (mine > around ? mine : around) : 0u;
+    u32 total = xor_reduce_sum<64, u32>(parts);
+    total = total > 0u ? total : 1u;
+    parts = lane < cells ? 1u + parts * (u32)(W - cells) / total : 0u;
+    u32 incl = parts;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const u32 o = (u32)__shfl_up((int)incl, d, 64);
+      if (lane >= d) incl += o;
+    }
+    const u32 cell = (incl - parts) | (parts << 16);
+    if (lane < cells) head[kListHead + lane] = cell;
+    const u32 at = tie != kNoKey ? tie - e.lo : 0u;
+    const u32 tie_bin = bin_of(at, e.shift, (u32)__shfl((int)cell, (int)(at >> e.shift), 64));
+    if (lane == 0 && tie != kNoKey) {
+      head[kHeadTie] = tie;
+      head[kHeadTieBin] = tie_bin;
+    }
+    e.shift |= kCells;
   }
   if (tid == 0) br[idx] = e;
 }
 
 template <typename TX>
-static void sets_t(const TX* X, int B, int T, int C, long long ld, int G, int Wfew, int W, const float* r,
+static void sets_t(const TX* X, int B, int T, int C, long long ld, int G, int Wfew, int W, int cells,
+                   const float* r,
                    const double* mean, const double* m2, int* gid, const Scalars& sc, int pass,
                    bool keep_base, GroupWork* grp, Bracket* br, unsigned* bhist, unsigned* lists,
                    int cap, unsigned* img_flag, unsigned* status, hipStream_t st) {
   constexpr int V = Elem<TX>::V;
   const int aligned = ((reinterpret_cast<uintptr_t>(X) & 15) == 0 && ld % V == 0 && C % V == 0) ? 1 : 0;
-  // 8 Ki sampled elements are enough, or the image
+  // 8 Ki sampled elements are enough (binary32: a wider interval costs little), or the image
   const bool few = (Wfew >= 512 && G >= 8 && pass == kPassZr) || (long long)T * C <= 8192;
   const size_t order_bytes = T <= kListTokens ? (size_t)T * sizeof(unsigned short) : 0;
 #define TDQ_SETS_SM(NT, SM)                                                                        \
-  hipLaunchKernelGGL((k_sets<TX, NT, SM>), dim3(G, B), dim3(NT), order_bytes, st, X, ld, T, C, G, Wfew, W, aligned, r, \
+  hipLaunchKernelGGL((k_sets<TX, NT, SM>), dim3(G, B), dim3(NT), order_bytes, st, X, ld, T, C, G, Wfew, W, cells, aligned, r, \
                      mean, m2, gid, sc, pass, keep_base ? 1 : 0, grp, br, bhist, lists, cap,       \
                      img_flag, status)
 #define TDQ_SETS(NT)                                                           \
   do {                                                                         \
-    if (few) TDQ_SETS_SM(NT, 8192); else TDQ_SETS_SM(NT, 16384);               \
+    if constexpr (sizeof(TX) == 4) TDQ_SETS_SM(NT, 8192);                      \
+    else if (few) TDQ_SETS_SM(NT, 8192);                                       \
+    else TDQ_SETS_SM(NT, 16384);                                               \
   } while (0)
   // as few threads as hold the image's range keys in registers: [32, 4096, 1024] calibrates
   // in 111 / 117 / 145 us with 256 / 512 / 1024 threads per set
@@ -531,15 +637,15 @@ static void sets_t(const TX* X, int B, int T, int C, long long ld, int G, int Wf
 }
 
 hipError_t launch_sets(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G,
-                       int Wfew, int W, const float* r, const double* mean, const double* m2, int* gid,
+                       int Wfew, int W, int cells, const float* r, const double* mean, const double* m2, int* gid,
                        const Scalars& sc, int pass, bool keep_base, GroupWork* grp, Bracket* br,
                        unsigned* bhist, unsigned* lists, int cap, unsigned* img_flag,
                        unsigned* status, hipStream_t st) {
   if (dt == TDQ_F16)
-    sets_t<u16>(static_cast<const u16*>(X), B, T, C, ld, G, Wfew, W, r, mean, m2, gid, sc, pass, keep_base,
+    sets_t<u16>(static_cast<const u16*>(X), B, T, C, ld, G, Wfew, W, cells, r, mean, m2, gid, sc, pass, keep_base,
                 grp, br, bhist, lists, cap, img_flag, status, st);
   else
-    sets_t<float>(static_cast<const float*>(X), B, T, C, ld, G, Wfew, W, r, mean, m2, gid, sc, pass, keep_base,
+    sets_t<float>(static_cast<const float*>(X), B, T, C, ld, G, Wfew, W, cells, r, mean, m2, gid, sc, pass, keep_base,
                   grp, br, bhist, lists, cap, img_flag, status, st);
   return hipGetLastError();
 }
@@ -559,12 +665,13 @@ typedef short s2v __attribute__((ext_vector_type(2)));
 // global additions 13.2 and 44.6 us on the first two.
 template <typename TX, int L, int P>
 __global__ __launch_bounds__(kSweepThreads) void k_bracket_hist(
-    const TX* __restrict__ X, long long ld, int T_, int C, int G, int W, int lw,
+    const TX* __restrict__ X, long long ld, int T_, int C, int G, int W, int lw, int cells,
     const int* __restrict__ gid, Bracket* __restrict__ br, u32* __restrict__ bhist,
-    int rows_per_block) {
+    u32* __restrict__ lists, int cap, int rows_per_block) {
   constexpr int R = 4 / P;
   constexpr int V = Elem<TX>::V;
-  // [G][W] bins, then per set: below, lo, width, shift
+  // [G][W] bins, binary32: [G][cells] cells, then per set: below, lo, width (with cells: in keys),
+  // binary32: shift, tie, ties
   extern __shared__ __attribute__((aligned(16))) u32 lds[];
   // walks X backwards: it runs right after the forward statistics sweep, so the end of
   // X is what the last-level cache still holds
@@ -572,26 +679,42 @@ __global__ __launch_bounds__(kSweepThreads) void k_bracket_hist(
   const int chunk = (int)(gridDim.x - 1 - blockIdx.x);
   const int tid = threadIdx.x;
   const int nwords = G * W;
-  u32* s_below = lds + nwords;
+  u32* s_cells = lds + nwords;
+  u32* s_below = s_cells + (V == 4 ? G * cells : 0);
   u32* s_lo = s_below + G;
   u32* s_width = s_lo + G;
   u32* s_shift = s_width + G;
+  u32* s_tie = s_shift + G;
+  u32* s_ties = s_tie + G;
   // most sets use the first 2^lw bins; the further ones of those that use more are cleared and
   // added one by one
-  for (int i = tid; i < (G << lw) / 4; i += kSweepThreads) {
-    const int g = i >> (lw - 2), at = i - (g << (lw - 2));
-    *reinterpret_cast<uint4*>(&lds[g * W + 4 * at]) = make_uint4(0, 0, 0, 0);
+  if constexpr (V == 8) {
+    for (int i = tid; i < (G << lw) / 4; i += kSweepThreads) {
+      const int g = i >> (lw - 2), at = i - (g << (lw - 2));
+      *reinterpret_cast<uint4*>(&lds[g * W + 4 * at]) = make_uint4(0, 0, 0, 0);
+    }
+  } else {
+    for (int i = tid; i < nwords / 4; i += kSweepThreads)
+      reinterpret_cast<uint4*>(lds)[i] = make_uint4(0, 0, 0, 0);
+    for (int i = tid; i < G * cells; i += kSweepThreads) {
+      const int g = i / cells;
+      s_cells[i] = lists[((size_t)b * G + g) * cap + kListHead + (i - g * cells)];
+    }
   }
   for (int g = tid; g < G; g += kSweepThreads) {
     const Bracket e = br[(long long)b * G + g];
     s_below[g] = 0;
     s_lo[g] = e.lo;
     s_width[g] = e.width;
-    s_shift[g] = e.shift;
+    if constexpr (V == 4) {
+      s_shift[g] = e.shift;
+      s_tie[g] = lists[((size_t)b * G + g) * cap + kHeadTie];
+      s_ties[g] = 0;
+    }
   }
   __syncthreads();
   const int lane = tid & 63;                      // (G <= 64)
-  const bool wide = W > 1 << lw && __ballot(lane < G && (int)s_width[lane < G ? lane : 0] > 1 << lw) != 0;
+  const bool wide = V == 8 && W > 1 << lw && __ballot(lane < G && (int)s_width[lane < G ? lane : 0] > 1 << lw) != 0;
   if (wide) {                                     // the same in every wavefront
     for (int g = 0; g < G; ++g)
       for (int i = (1 << lw) + tid; i < (int)s_width[g]; i += kSweepThreads) lds[g * W + i] = 0;
@@ -608,7 +731,7 @@ __global__ __launch_bounds__(kSweepThreads) void k_bracket_hist(
   for (int rr = slot; rr < nrows; rr += SLOTS * R) {
     const TX* xp[R];
     int g[R];
-    u32 below[R];
+    u32 below[R], ties[R];
 #pragma unroll
     for (int i = 0; i < R; ++i) {                 // rows past the end: the last one, not counted
       const int ri = rr + SLOTS * i;
@@ -616,7 +739,38 @@ __global__ __launch_bounds__(kSweepThreads) void k_bracket_hist(
       xp[i] = X + row * ld;
       g[i] = gid[row];
       below[i] = 0;
+      ties[i] = 0;
     }
+    // binary32: keys and lo are below 2^31, the sign of the difference says "key < lo", and such a
+    // difference lies past the last bin (the number of bins is a power of two and bins << shift at
+    // most 2^31, so 2^31 >> shift is at least their number) and past the last cell.  The cells of
+    // several keys are read before the first is used, of those outside the interval as well: one
+    // trip to LDS.
+    auto count32 = [&](const auto& k, int i, u32 lo, u32 width, u32 shift) {
+      constexpr int N = sizeof(k) / sizeof(u32);
+      if (!(shift & kCells)) {
+#pragma unroll
+        for (int c = 0; c < N; ++c) {
+          const u32 d = k[c] - lo, bin = d >> shift;
+          below[i] += d >> 31;
+          if (bin < width) atomicAdd(&lds[g[i] * W + bin], 1u);
+        }
+      } else {
+        const u32 sh = shift & 63u, tie = s_tie[g[i]];
+        u32 d[N], cell[N];
+#pragma unroll
+        for (int c = 0; c < N; ++c) {
+          d[c] = k[c] - lo;
+          below[i] += d[c] >> 31;
+          ties[i] += k[c] == tie ? 1u : 0u;
+          d[c] = k[c] != tie ? d[c] : 0xFFFFFFFFu;
+          cell[c] = s_cells[g[i] * cells + (int)(d[c] < width ? d[c] >> sh : 0u)];
+        }
+#pragma unroll
+        for (int c = 0; c < N; ++c)
+          if (d[c] < width) atomicAdd(&lds[g[i] * W + bin_of(d[c], sh, cell[c])], 1u);
+      }
+    };
     for (int v0 = lr; v0 < nvec; v0 += P * L) {
       uint4 q[R][P];
 #pragma unroll
@@ -637,6 +791,10 @@ __global__ __launch_bounds__(kSweepThreads) void k_bracket_hist(
           for (int k = 0; k < P; ++k) {
             if (k > 0 && v0 + k * L >= nvec) break;
             const u32 wd[4] = {q[i][k].x, q[i][k].y, q[i][k].z, q[i][k].w};
+            if constexpr (V == 4) {
+              const u32 key[4] = {wd[0] & 0x7FFFFFFFu, wd[1] & 0x7FFFFFFFu, wd[2] & 0x7FFFFFFFu, wd[3] & 0x7FFFFFFFu};
+              count32(key, i, lo, width, shift);
+            }
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               if constexpr (V == 8) {
@@ -648,14 +806,6 @@ __global__ __launch_bounds__(kSweepThreads) void k_bracket_hist(
                 const u32 dl = d2 & 0xFFFFu, dh = d2 >> 16;     // negative ones are >= 2^15 > width
                 if (dl < width) atomicAdd(&h[dl], 1u);
                 if (dh < width) atomicAdd(&h[dh], 1u);
-              } else {
-                // keys and lo are below 2^31: the sign of the difference says "key < lo", and
-                // such a difference lies past the last bin (the number of bins is a power of two
-                // and bins << shift at most 2^31, so 2^31 >> shift is at least their number)
-                const u32 d = (wd[e] & 0x7FFFFFFFu) - lo;
-                below[i] += d >> 31;
-                const u32 bin = d >> shift;
-                if (bin < width) atomicAdd(&h[bin], 1u);
               }
             }
           }
@@ -666,12 +816,21 @@ __global__ __launch_bounds__(kSweepThreads) void k_bracket_hist(
     for (int i = 0; i < R; ++i) {
       if (rr + SLOTS * i < nrows) {
         const u32 lo = s_lo[g[i]], width = s_width[g[i]];
-        const u32 shift = V == 4 ? s_shift[g[i]] : 0u;
         for (int c = nvec * V + lr; c < C; c += L) {          // fewer than V elements
           const u32 k = Elem<TX>::key(xp[i][c]);
-          below[i] += k < lo ? 1u : 0u;
-          const u32 d = (k - lo) >> shift;
-          if (k >= lo && d < width) atomicAdd(&lds[g[i] * W + d], 1u);
+          if constexpr (V == 8) {
+            below[i] += k < lo ? 1u : 0u;
+            if (k >= lo && k - lo < width) atomicAdd(&lds[g[i] * W + (k - lo)], 1u);
+          } else {
+            const u32 key[1] = {k};
+            count32(key, i, lo, width, s_shift[g[i]]);
+          }
+        }
+      }
+      if constexpr (V == 4) {
+        if (__ballot(ties[i] != 0) != 0) {
+          const u32 n = group_sum_u32<L>(ties[i]);            // (rows past the end: none)
+          if (lr == L - 1 && n && rr + SLOTS * i < nrows) atomicAdd(&s_ties[g[i]], n);
         }
       }
       const u32 total = group_sum_u32<L>(below[i]);           // in the row's last lane
@@ -680,8 +839,8 @@ __global__ __launch_bounds__(kSweepThreads) void k_bracket_hist(
   }
   __syncthreads();
   u32* gh = bhist + (size_t)b * G * W;
-  for (int i = tid; i < G << lw; i += kSweepThreads) {
-    const int g = i >> lw, at = g * W + i - (g << lw);
+  for (int i = tid; i < (V == 8 ? G << lw : nwords); i += kSweepThreads) {
+    const int g = i >> lw, at = V == 8 ? g * W + i - (g << lw) : i;
     const u32 v = lds[at];
     if (v) atomicAdd(&gh[at], v);
   }
@@ -694,6 +853,8 @@ __global__ __launch_bounds__(kSweepThreads) void k_bracket_hist(
   for (int g = tid; g < G; g += kSweepThreads) {
     const u32 v = s_below[g];
     if (v) atomicAdd(&br[(long long)b * G + g].below, v);
+    if constexpr (V == 4)
+      if (s_ties[g]) atomicAdd(&lists[((size_t)b * G + g) * cap + kHeadTies], s_ties[g]);
   }
 }
 
@@ -720,13 +881,14 @@ static int sweep_rows(int B, int T, int C) {
 
 template <typename TX>
 static void bracket_hist_t(const TX* X, int B, int T_, int C, long long ld, int G, int Wfew, int W,
-                           const int* gid, Bracket* br, unsigned* bhist, hipStream_t st) {
+                           int cells, unsigned* lists, int cap, const int* gid, Bracket* br, unsigned* bhist, hipStream_t st) {
   const int nvec = C / Elem<TX>::V;
   const int L = sweep_lanes_per_row(C, Elem<TX>::V);
   const int P = nvec > 2 * L ? 4 : nvec > L ? 2 : 1;
   const int rpb = sweep_rows(B, T_, C);
   const unsigned chunks = (unsigned)((T_ + rpb - 1) / rpb);
-  const size_t lds_bytes = ((size_t)G * W + 4 * (size_t)G) * sizeof(u32);
+  const size_t lds_bytes =
+      (size_t)G * (sizeof(TX) == 2 ? W + 3 : W + cells + 6) * sizeof(u32);
   int lw = 0;
   while (1 << lw < Wfew) ++lw;
 #define TDQ_BH(LL, PP)                                                                          \
@@ -735,34 +897,39 @@ static void bracket_hist_t(const TX* X, int B, int T_, int C, long long ld, int 
       (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bracket_hist<TX, LL, PP>),     \
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);    \
     hipLaunchKernelGGL((k_bracket_hist<TX, LL, PP>), dim3(chunks, B), dim3(kSweepThreads),      \
-                       lds_bytes, st, X, ld, T_, C, G, W, lw, gid, br, bhist, rpb);                 \
+                       lds_bytes, st, X, ld, T_, C, G, W, lw, cells, gid, br, bhist, lists, cap, rpb);                 \
   }
   TDQ_SWEEP_CASES(TDQ_BH)
 #undef TDQ_BH
 }
 
 hipError_t launch_bracket_hist(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G,
-                               int Wfew, int W, const int* gid, Bracket* br, unsigned* bhist, hipStream_t st) {
+                               int Wfew, int W, int cells, unsigned* lists, int cap, const int* gid,
+                               Bracket* br, unsigned* bhist, hipStream_t st) {
   if (dt == TDQ_F16)
-    bracket_hist_t<u16>(static_cast<const u16*>(X), B, T, C, ld, G, Wfew, W, gid, br, bhist, st);
+    bracket_hist_t<u16>(static_cast<const u16*>(X), B, T, C, ld, G, Wfew, W, cells, lists, cap, gid, br, bhist, st);
   else
-    bracket_hist_t<float>(static_cast<const float*>(X), B, T, C, ld, G, Wfew, W, gid, br, bhist, st);
+    bracket_hist_t<float>(static_cast<const float*>(X), B, T, C, ld, G, Wfew, W, cells, lists, cap, gid, br, bhist, st);
   return hipGetLastError();
 }
 
 // The bin of a set's interval histogram (W = 256 to 2048 words) that holds its k-th smallest
-// key, by one wavefront; the same in every lane.  ok = the interval does hold it.
+// key, by one wavefront; the same in every lane.  ok = the interval does hold it.  (binary32:
+// `ties` more elements lie in bin tie_bin than its word says.)  A set has fewer than 2^32 elements.
 struct BinPick {
   bool ok;
   u32 bin, need;              // rank wanted among the bin's elements (1-based)
-  unsigned long long inside;  // elements inside the interval
+  u32 count;                  // elements of the bin's histogram word
+  u32 inside;                 // elements inside the interval
 };
-__device__ __forceinline__ BinPick pick_bin(const u32* __restrict__ hb, int W, u32 below, long long k) {
+template <bool TIES>
+__device__ __forceinline__ BinPick pick_bin(const u32* __restrict__ hb, int W, u32 below, long long k,
+                                            u32 tie_bin = kNoKey, u32 ties = 0) {
   const int lane = threadIdx.x & 63;
   const int quads = W / 256;                    // 1 to 8 groups of four bins per lane
   const uint4* mine_bins = reinterpret_cast<const uint4*>(hb) + lane * quads;
   uint4 c[2];                                   // two groups stay in registers
-  u32 sum[8];                                   // (a set has fewer than 2^32 elements)
+  u32 sum[8];
 #pragma unroll
   for (int i = 0; i < 2; ++i) c[i] = mine_bins[i < quads ? i : 0];
 #pragma unroll
@@ -775,85 +942,128 @@ __device__ __forceinline__ BinPick pick_bin(const u32* __restrict__ hb, int W, u
     for (int i = 2; i < 8; ++i)
       sum[i] = i < quads ? t[i - 2].x + t[i - 2].y + t[i - 2].z + t[i - 2].w : 0u;
   }
-  unsigned long long mine = 0;
+  if (TIES && ties != 0) {                      // uniform
+    const int at = (int)(tie_bin >> 2) - lane * quads;         // of this lane's groups, if any
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sum[i] += i == at && i < quads ? ties : 0u;
+  }
+  u32 mine = 0;
 #pragma unroll
   for (int i = 0; i < 8; ++i) mine += sum[i];
-  unsigned long long incl = mine;               // inclusive scan over lanes
+  u32 incl = mine;                              // inclusive scan over lanes
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
-    const unsigned long long o = __shfl_up(incl, d, 64);
+    const u32 o = (u32)__shfl_up((int)incl, d, 64);
     if (lane >= d) incl += o;
   }
   const unsigned long long kk = (unsigned long long)k;
   BinPick r;
-  r.inside = __shfl(incl, 63, 64);
+  r.inside = (u32)__builtin_amdgcn_readlane((int)incl, 63);
   r.ok = kk > below && kk - below <= r.inside;
-  const unsigned long long need = kk - below;
+  const u32 need = (u32)(kk - below);
   const unsigned long long hit = __ballot(incl >= need);
   const int src = r.ok ? __ffsll((long long)hit) - 1 : 0;       // hit != 0 because need <= inside
-  unsigned long long cum = incl - mine;
+  u32 cum = incl - mine;
   int group = 0;                                // the group of four ...
   bool found = false;
+  if (quads > 1) {
 #pragma unroll
-  for (int i = 0; i < 7; ++i) {
-    found = found || i >= quads - 1 || cum + sum[i] >= need;
-    if (!found) {
-      cum += sum[i];
-      ++group;
+    for (int i = 0; i < 7; ++i) {
+      found = found || i >= quads - 1 || cum + sum[i] >= need;
+      if (!found) {
+        cum += sum[i];
+        ++group;
+      }
     }
   }
   uint4 q = group == 0 ? c[0] : c[1];
   if (quads > 2) q = mine_bins[group];
   u32 bin = (u32)(4 * (lane * quads + group));
-  const u32 v[3] = {q.x, q.y, q.z};             // ... and the bin in it
+  const u32 v[4] = {q.x, q.y, q.z, q.w};        // ... and the bin in it
+  u32 count = v[0];
   found = false;
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
-    found = found || cum + v[i] >= need;
+    const u32 all = v[i] + (TIES && bin == tie_bin ? ties : 0u);
+    found = found || cum + all >= need;
     if (!found) {
-      cum += v[i];
+      cum += all;
       ++bin;
+      count = v[i + 1];
     }
   }
-  r.bin = (u32)__shfl((int)bin, src, 64);
-  r.need = (u32)(need - __shfl(cum, src, 64));
+  r.bin = (u32)__builtin_amdgcn_readlane((int)bin, src);
+  r.need = need - (u32)__builtin_amdgcn_readlane((int)cum, src);
+  r.count = (u32)__builtin_amdgcn_readlane((int)count, src);
   return r;
 }
 
+// First key and number of keys of a bin (binary32), by one wavefront; cell = the set's cell of this
+// lane.
+__device__ __forceinline__ void bin_keys(u32 cell, int cells, const Bracket& e, u32 bin, u32& key0, u32& span) {
+  if (!(e.shift & kCells)) {
+    key0 = e.lo + (bin << e.shift);
+    span = 1u << e.shift;
+    return;
+  }
+  const int lane = threadIdx.x & 63;
+  const u32 shift = e.shift & 63u;
+  const int c = (int)__popcll(__ballot(lane < cells && (cell & 0xFFFFu) <= bin)) - 1;
+  const u32 its = (u32)__shfl((int)cell, c > 0 ? c : 0, 64), part = bin - (its & 0xFFFFu);
+  // part j of m starts at the first fraction f of the cell with f m >= j 2^shift (exact: below 2^53)
+  const double m = (double)(its >> 16);
+  const u32 from = (u32)ceil((double)((unsigned long long)part << shift) / m);
+  const u32 left = e.width - ((u32)c << shift);            // keys of the interval from the cell on
+  u32 to = (u32)ceil((double)((unsigned long long)(part + 1u) << shift) / m);
+  to = to < left ? to : left;
+  key0 = e.lo + ((u32)c << shift) + from;
+  span = to - from;
+}
+
 // ---------------------------------------------------------------------------
-// k_bracket_gather, binary32 input only: a bin of the interval histogram is 2^shift keys wide
-// there, so a second sweep collects the keys that fall into the bin of every set (about 2e-4
-// of the elements), first per workgroup in LDS.  lists[set]: largest ~key, largest key, then
-// the keys; their number is counted in GroupWork::prefix, and a workgroup that found more than
-// it can keep pushes that number past the list's capacity.  (Equal keys need no list: the
-// smallest and the largest collected key say so.)  Every workgroup finds the bins itself.
-// Calibration of [8, 1024, 768]: 73.4 us with a sweep and a select kernel per eight key bits,
-// 45.3 with the sampled interval (this kernel 11.5, with twice or four times the workgroups
+// k_bracket_gather, binary32 input only: a second sweep collects the keys that fall into the bin
+// of every set that holds the rank (about 2e-4 of the elements), first per workgroup in LDS, and
+// once that is full one by one.  Their number, known from the first sweep, is counted in
+// GroupWork::prefix as they are added.  A bin with more keys than a list holds is not collected;
+// if they all are equal, its smallest and largest key say so.  Every workgroup finds the bins
+// itself.  Calibration of [8, 1024, 768]: 73.4 us with a sweep and a select kernel per eight key
+// bits, 45.3 with the sampled interval (this kernel 11.5, with twice or four times the workgroups
 // 11.0 and 16.8).
 // ---------------------------------------------------------------------------
 constexpr int kGatherWords = 8192;              // LDS words for collected keys, shared by the sets
 
 template <int L, int P>
 __global__ __launch_bounds__(kSweepThreads) void k_bracket_gather(
-    const float* __restrict__ X, long long ld, int T_, int C, int G, int W,
+    const float* __restrict__ X, long long ld, int T_, int C, int G, int W, int cells,
     const int* __restrict__ gid, const Bracket* __restrict__ br, const u32* __restrict__ bhist,
     GroupWork* __restrict__ grp, u32* __restrict__ lists, int cap, int rows_per_block) {
   constexpr int R = 4 / P;
-  __shared__ u32 s_key0[64], s_span[64], s_cnt[64], s_nmin[64], s_max[64], s_at[64];
+  __shared__ u32 s_key0[64], s_span[64], s_cnt[64], s_nmin[64], s_max[64], s_at[64], s_tie[64], s_take[64];
   __shared__ u32 s_list[kGatherWords];
   const int b = blockIdx.y, chunk = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63;
   const int keep = kGatherWords / G;            // keys kept per set (G <= 64)
+  const int keys_at = kListHead + cells, keys_cap = cap - keys_at;
   for (int g = tid >> 6; g < G; g += kSweepThreads / 64) {
     const long long idx = (long long)b * G + g;
     const GroupWork w = grp[idx];
     const Bracket e = br[idx];
-    u32 span = 0, key0 = 0;
-    if (w.tokens != 0 && e.shift != 0) {        // uniform over the wavefront
-      const BinPick p = pick_bin(bhist + (size_t)idx * W, W, e.below, w.k_rem);
-      if (p.ok) {
-        key0 = e.lo + (p.bin << e.shift);
-        span = 1u << e.shift;
+    u32* head = lists + (size_t)idx * cap;
+    const u32 tie = head[kHeadTie], ties = head[kHeadTies], tie_bin = head[kHeadTieBin];
+    const u32 cell = head[kListHead + (lane < cells ? lane : 0)];
+    u32 span = 0, key0 = 0, take = 0;
+    if (w.tokens != 0) {                        // uniform over the wavefront
+      const BinPick p = pick_bin<true>(bhist + (size_t)idx * W, W, e.below, w.k_rem, tie_bin, ties);
+      if (p.ok && p.count != 0) {               // (a bin of ties alone needs no sweep)
+        bin_keys(cell, cells, e, p.bin, key0, span);
+        take = p.count <= (u32)keys_cap ? 1u : 0u;
+        if (span == 1u) {                       // one key: that is the answer
+          span = 0;
+          if (chunk == 0 && lane == 0) {
+            head[kHeadMin] = ~key0;
+            head[kHeadMax] = key0;
+          }
+        }
       }
     }
     if (lane == 0) {
@@ -862,6 +1072,8 @@ __global__ __launch_bounds__(kSweepThreads) void k_bracket_gather(
       s_cnt[g] = 0;
       s_nmin[g] = 0;
       s_max[g] = 0;
+      s_tie[g] = tie;
+      s_take[g] = take;
     }
   }
   __syncthreads();
@@ -883,11 +1095,19 @@ __global__ __launch_bounds__(kSweepThreads) void k_bracket_gather(
       g[i] = gid[row];
     }
     auto look = [&](int gi, u32 key0, u32 span, u32 k) {
-      if (k - key0 < span) {
-        const u32 at = atomicAdd(&s_cnt[gi], 1u);
-        if (at < (u32)keep) s_list[gi * keep + at] = k;
-        atomicMax(&s_nmin[gi], ~k);
-        atomicMax(&s_max[gi], k);
+      if (k - key0 < span && k != s_tie[gi]) {
+        if (~k > s_nmin[gi]) atomicMax(&s_nmin[gi], ~k);
+        if (k > s_max[gi]) atomicMax(&s_max[gi], k);
+        if (s_take[gi]) {
+          const u32 at = atomicAdd(&s_cnt[gi], 1u);
+          if (at < (u32)keep) {
+            s_list[gi * keep + at] = k;
+          } else {
+            const long long idx = (long long)b * G + gi;
+            const u32 to = atomicAdd(&grp[idx].prefix, 1u);
+            if (to < (u32)keys_cap) lists[idx * cap + keys_at + to] = k;
+          }
+        }
       }
     };
     for (int v0 = lr; v0 < nvec; v0 += P * L) {
@@ -920,23 +1140,24 @@ __global__ __launch_bounds__(kSweepThreads) void k_bracket_gather(
     }
   }
   __syncthreads();
-  if (tid < G && s_cnt[tid]) {
+  if (tid < G && s_max[tid]) {                  // (keys are at least 1)
     const long long idx = (long long)b * G + tid;
-    const u32 n = s_cnt[tid];
-    s_at[tid] = atomicAdd(&grp[idx].prefix, n <= (u32)keep ? n : n + (u32)cap);
-    atomicMax(&lists[idx * cap], s_nmin[tid]);
-    atomicMax(&lists[idx * cap + 1], s_max[tid]);
+    const u32 n = s_cnt[tid] < (u32)keep ? s_cnt[tid] : (u32)keep;
+    s_cnt[tid] = n;
+    s_at[tid] = n ? atomicAdd(&grp[idx].prefix, n) : 0u;
+    atomicMax(&lists[idx * cap + kHeadMin], s_nmin[tid]);
+    atomicMax(&lists[idx * cap + kHeadMax], s_max[tid]);
   }
   __syncthreads();
   for (int i = tid; i < G * keep; i += kSweepThreads) {
     const int g = i / keep, at = i - g * keep;
-    if ((u32)at < s_cnt[g] && s_at[g] < (u32)cap && s_at[g] + (u32)at + 2u < (u32)cap)
-      lists[((long long)b * G + g) * cap + 2 + s_at[g] + at] = s_list[i];
+    if ((u32)at < s_cnt[g] && s_at[g] + (u32)at < (u32)keys_cap)
+      lists[((long long)b * G + g) * cap + keys_at + s_at[g] + at] = s_list[i];
   }
 }
 
 hipError_t launch_bracket_gather(const void* Xv, int B, int T_, int C, long long ld, int G, int W,
-                                 const int* gid, const Bracket* br, const unsigned* bhist,
+                                 int cells, const int* gid, const Bracket* br, const unsigned* bhist,
                                  GroupWork* grp, unsigned* lists, int cap, hipStream_t st) {
   const float* X = static_cast<const float*>(Xv);
   const int nvec = C / 4;
@@ -947,7 +1168,7 @@ hipError_t launch_bracket_gather(const void* Xv, int B, int T_, int C, long long
 #define TDQ_BG(LL, PP)                                                                             \
   if (L == LL && P == PP)                                                                          \
     hipLaunchKernelGGL((k_bracket_gather<LL, PP>), dim3(chunks, B), dim3(kSweepThreads), 0, st, X, \
-                       ld, T_, C, G, W, gid, br, bhist, grp, lists, cap, rpb);
+                       ld, T_, C, G, W, cells, gid, br, bhist, grp, lists, cap, rpb);
   TDQ_SWEEP_CASES(TDQ_BG)
 #undef TDQ_BG
   return hipGetLastError();
@@ -1135,8 +1356,8 @@ __device__ __forceinline__ u32 search_rows(const TX* __restrict__ Xb, long long 
 template <typename TX, int NT>
 __global__ __launch_bounds__(NT, NT == 256 ? 8 : 4) void k_bracket_finish(
     const TX* __restrict__ X, long long ld, int T, int C, int G, int L,
-    const int* __restrict__ gid, const u32* __restrict__ bhist, int Wfew, int W, const u32* __restrict__ lists,
-    int cap, int force_miss, Scalars sc, int pass, GroupWork* __restrict__ grp,
+    const int* __restrict__ gid, const u32* __restrict__ bhist, int Wfew, int W, int cells,
+    const u32* __restrict__ lists, int cap, int force_miss, Scalars sc, int pass, GroupWork* __restrict__ grp,
     const Bracket* __restrict__ br, float* __restrict__ clip, float* __restrict__ scale,
     tdq_group_stats* __restrict__ stats, const u32* __restrict__ img_flag, int B,
     u32* __restrict__ status) {
@@ -1144,7 +1365,7 @@ __global__ __launch_bounds__(NT, NT == 256 ? 8 : 4) void k_bracket_finish(
   constexpr u32 kKeysAll = F16 ? 1u << 15 : 1u << 31;
   __shared__ FinishLds<NT> lds;
   __shared__ u32 s_keys[F16 ? 1 : kListMax];
-  __shared__ u32 s_ok, s_key, s_need, s_k0, s_span;
+  __shared__ u32 s_ok, s_key, s_need, s_k0, s_span, s_tie, s_ties;
   __shared__ int s_near;
   __shared__ unsigned long long s_rank;
   const int idx = blockIdx.x;
@@ -1171,11 +1392,20 @@ __global__ __launch_bounds__(NT, NT == 256 ? 8 : 4) void k_bracket_finish(
     unsigned long long rank = (unsigned long long)w.k_rem;
     if (!force_miss) {
       const Bracket e = br[idx];
+      const u32* head = lists + (size_t)idx * cap;
+      u32 lo = 0, hi = 0, tie = kNoKey, ties = 0, tie_bin = kNoKey;
+      if constexpr (!F16) {
+        lo = ~head[kHeadMin];
+        hi = head[kHeadMax];
+        tie = head[kHeadTie];
+        ties = head[kHeadTies];
+        tie_bin = head[kHeadTieBin];
+      }
       // (the further bins of a set that uses more are looked at only if the first do not do)
-      BinPick p = pick_bin(bhist + (size_t)idx * W, Wfew, e.below, w.k_rem);
-      if (w.tokens != 0 && !p.ok && (int)e.width > Wfew && w.k_rem > e.below) {
-        const unsigned long long first = p.inside;
-        p = pick_bin(bhist + (size_t)idx * W + Wfew, W - Wfew, e.below + (u32)first, w.k_rem);
+      BinPick p = pick_bin<!F16>(bhist + (size_t)idx * W, Wfew, e.below, w.k_rem, tie_bin, ties);
+      if (F16 && w.tokens != 0 && !p.ok && (int)e.width > Wfew && w.k_rem > e.below) {
+        const u32 first = p.inside;
+        p = pick_bin<false>(bhist + (size_t)idx * W + Wfew, W - Wfew, e.below + first, w.k_rem);
         p.inside += first;
         p.bin += (u32)Wfew;
       }
@@ -1183,18 +1413,27 @@ __global__ __launch_bounds__(NT, NT == 256 ? 8 : 4) void k_bracket_finish(
         ok = kDone;
         if (lane == 0 && pass == kPassZr) project_store(idx, w, 0u, F16, sc, clip, scale, stats);
       } else if (p.ok) {                        // wavefront-uniform
-        u32 key = e.lo + (p.bin << e.shift);
-        k0 = key;
-        span = 1u << e.shift;
-        rank = p.need;
+        u32 key = e.lo + p.bin;
         ok = kDone;
-        if (!F16 && e.shift != 0) {
-          const u32 lo = ~lists[(size_t)idx * cap], hi = lists[(size_t)idx * cap + 1];
-          key = lo;
-          if (lo != hi) ok = w.prefix + 2u <= (u32)cap ? kInList : kMiss;
+        if constexpr (!F16) {
+          const u32 among = p.bin == tie_bin ? ties : 0u;       // ties in that bin
+          key = p.count == 0 ? tie : lo;
+          if (p.count != 0 && (lo != hi || among != 0)) {
+            if (w.prefix == p.count) {          // all of them were collected
+              ok = kInList;
+            } else {
+              ok = kMiss;
+              bin_keys(head[kListHead + (lane < cells ? lane : 0)], cells, e, p.bin, k0, span);
+              rank = p.need;
+            }
+          }
+          if (lane == 0) {
+            s_need = p.need;
+            s_tie = tie;
+            s_ties = among;
+          }
         }
         if (ok == kDone && lane == 0) finish(key);
-        if (lane == 0) s_need = p.need;
       } else if (rank <= e.below) {             // below the interval
         span = e.lo;
         near = F16 ? -1 : 0;
@@ -1203,11 +1442,11 @@ __global__ __launch_bounds__(NT, NT == 256 ? 8 : 4) void k_bracket_finish(
           if (lane == 0) finish(0u);
         }
       } else {                                  // above it
-        k0 = e.lo + (e.width << e.shift);
+        k0 = e.lo + (e.shift & kCells ? e.width : e.width << e.shift);
         k0 = k0 < kKeysAll ? k0 : kKeysAll - 1u;
         span = kKeysAll - k0;
         near = F16 ? 1 : 0;
-        rank -= e.below + p.inside;
+        rank -= (unsigned long long)e.below + p.inside;
       }
     } else if (w.tokens == 0) {
       ok = kDone;
@@ -1225,14 +1464,16 @@ __global__ __launch_bounds__(NT, NT == 256 ? 8 : 4) void k_bracket_finish(
   if (s_ok == kDone) return;
   if constexpr (!F16) {
     if (s_ok == kInList) {
-      // the key with fewer than `need` smaller ones and at least `need` not larger
+      // the key with fewer than `need` smaller ones and at least `need` not larger, among the
+      // collected ones and the ties
       const int n = (int)w.prefix;
-      for (int i = tid; i < n; i += NT) s_keys[i] = lists[(size_t)idx * cap + 2 + i];
+      const u32* keys = lists + (size_t)idx * cap + kListHead + cells;
+      for (int i = tid; i < n; i += NT) s_keys[i] = keys[i];
       __syncthreads();
-      const u32 need = s_need;
-      for (int i = tid; i < n; i += NT) {
-        const u32 mine = s_keys[i];
-        u32 less = 0, equal = 0;
+      const u32 need = s_need, tie = s_tie, ties = s_ties;
+      for (int i = tid; i < n + (ties ? 1 : 0); i += NT) {
+        const u32 mine = i < n ? s_keys[i] : tie;
+        u32 less = tie < mine ? ties : 0u, equal = tie == mine ? ties : 0u;
         for (int c = 0; c < n; ++c) {
           const u32 k = s_keys[c];
           less += k < mine ? 1u : 0u;
@@ -1253,14 +1494,14 @@ __global__ __launch_bounds__(NT, NT == 256 ? 8 : 4) void k_bracket_finish(
 }
 
 hipError_t launch_bracket_finish(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G,
-                                 int Wfew, int W, const int* gid, const unsigned* bhist,
+                                 int Wfew, int W, int cells, const int* gid, const unsigned* bhist,
                                  const unsigned* lists, int cap, bool force_miss, const Scalars& sc, int pass, GroupWork* grp,
                                  const Bracket* br, float* clip, float* scale, tdq_group_stats* stats,
                                  const unsigned* img_flag, unsigned* status, hipStream_t st) {
   const int L = sweep_lanes_per_row(C, dt == TDQ_F16 ? 8 : 4);
 #define TDQ_FINISH(TX, NT)                                                                              \
   hipLaunchKernelGGL((k_bracket_finish<TX, NT>), dim3(B * G), dim3(NT), 0, st, static_cast<const TX*>(X), \
-                     ld, T, C, G, L, gid, bhist, Wfew, W, lists, cap, force_miss ? 1 : 0, sc, pass, grp,  \
+                     ld, T, C, G, L, gid, bhist, Wfew, W, cells, lists, cap, force_miss ? 1 : 0, sc, pass, grp,  \
                      br, clip, scale, stats, img_flag, B, status)
   const bool large = B * G <= 256;              // one workgroup per CU
   if (dt == TDQ_F16) {

@@ -12,7 +12,7 @@ import parity_util as U
 
 pytestmark = pytest.mark.gpu
 
-KINDS = ("relu10", "relu15", "relu50", "mask15", "grid", "clamp6", "sigmoid", "near")
+KINDS = ("relu10", "relu15", "relu50", "mask15", "grid", "halves", "clamp6", "sigmoid", "near")
 EDGES = ("relu20", "mask20", "two")              # a fifth zero: the rank at the gap itself
 
 
@@ -27,12 +27,18 @@ def _data(kind, B, T, C, dtype, seed):
         x = np.where(rng.random(x.shape) < int(kind[4:]) / 100, 0.0, x * tok)
     elif kind == "grid":
         x = np.round(20 * rng.laplace(0, 1, x.shape)) * 0.0371
+    elif kind == "halves":                       # a dozen values, each a power of two or near one
+        x = 0.5 * np.round(3 * x)
     elif kind == "clamp6":                       # one token set: all tokens share their range
         x = np.clip(3 * x + 3, 0, 6)
     elif kind == "sigmoid":
         x = 1 / (1 + np.exp(-3 * x))
     elif kind == "near":                         # within 1e-5 of a constant
         x = 1 + 1e-5 * x
+    elif kind == "tie":                          # 15 % one value, the rank next to it
+        x = np.where(rng.random(x.shape) < 0.15, 0.2, x * tok)
+    elif kind == "floor":                        # magnitudes clamped from below: the rank among ties
+        x = np.sign(x) * np.maximum(np.abs(x), 0.35)
     elif kind == "two":
         x = np.where(rng.random(x.shape) < 0.2, 1e-3 * x, 5 + 0.1 * x)
     return x.astype(dtype)
@@ -51,6 +57,14 @@ def _check(X, G, pct=0.0):
 def test_interval_reaches_the_rank(kind, G):
     """No set may need the search on such data."""
     assert _check(_data(kind, 2, 1024, 768, np.float16, 7), G) == 0
+
+
+@pytest.mark.parametrize("kind", KINDS + EDGES + ("tie", "floor"))
+@pytest.mark.parametrize("T,C,G", [(1024, 768, 16), (1024, 768, 1), (700, 1496, 5), (600, 1040, 32), (400, 512, 64)])
+def test_bins_hold_little(kind, T, C, G):
+    """binary32: a bin never holds more keys than are collected, whatever the gaps and ties, and
+    the interval reaches the rank."""
+    assert _check(_data(kind, 1, T, C, np.float32, 7), G) == 0
 
 
 @pytest.mark.parametrize("pct", [0.0, 0.99])
