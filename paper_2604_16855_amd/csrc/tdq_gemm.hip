@@ -109,17 +109,16 @@ __device__ __forceinline__ void store_out_vec<_Float16>(_Float16* p, const float
   __builtin_nontemporal_store(v, reinterpret_cast<h8v*>(p));
 }
 
-// Wavefront tile = (32 MT) x (32 NT) of Y, workgroup = 2 x 2 wavefronts, stages through
-// registers: used with MT = NT = 2 for products of long K whose shape does not suit 256 x 256
-// tiles (the dispatcher says where).
-template <typename OUT, int MT, int NT>
-__global__ __launch_bounds__(GEMM_THREADS, (MT * NT >= 16 ? 1 : MT * NT >= 8 ? 2 : 3)) void k_w4a4_gemm(
+// Wavefront tile = 64 x 64 of Y, workgroup = 2 x 2 wavefronts, stages through registers: for
+// products of long K whose shape does not suit 256 x 256 tiles (the dispatcher says where).
+template <typename OUT>
+__global__ __launch_bounds__(GEMM_THREADS, 3) void k_w4a4_gemm(
     const uint8_t* __restrict__ Qx, long long ld_q, const int* __restrict__ gid,
     const float* __restrict__ scale, int M, int T, int K, int N, int G,
     const uint8_t* __restrict__ Qw, long long ld_w, const float* __restrict__ w_scale,
     const float* __restrict__ bias, OUT* __restrict__ Y, long long ld_y, int* __restrict__ acc_dump,
     int m_tiles, int n_tiles) {
-  constexpr int BM = 64 * MT, BN = 64 * NT;
+  constexpr int MT = 2, NT = 2, BM = 64 * MT, BN = 64 * NT;
   __shared__ __attribute__((aligned(16))) uint8_t sA[2][BM * LDS_STRIDE];
   __shared__ __attribute__((aligned(16))) uint8_t sB[2][BN * LDS_STRIDE];
   __shared__ float sRow[BM], sCol[BN], sBias[BN];
@@ -1325,16 +1324,16 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void k_w4a4_gemm_roll(
 #undef TDQ_RSTAGE
 }
 
-template <typename OUT, int MT, int NT>
+template <typename OUT>
 static void launch_tile(const uint8_t* Qx, long long ld_q, const int* gid, const float* scale, int M,
                         int T, int K, int N, int G, const uint8_t* Qw, long long ld_w,
                         const float* w_scale, const float* bias, void* Y, long long ld_y,
                         int* acc_dump, hipStream_t st) {
-  constexpr int BM = 64 * MT, BN = 64 * NT;
+  constexpr int BM = 128, BN = 128;
   const int m_tiles = (M + BM - 1) / BM, n_tiles = (N + BN - 1) / BN;
   const long long m_groups = (m_tiles + XCDS - 1) / XCDS;
   const unsigned grid = (unsigned)(m_groups * XCDS * n_tiles);
-  hipLaunchKernelGGL((k_w4a4_gemm<OUT, MT, NT>), dim3(grid), dim3(GEMM_THREADS), 0, st, Qx, ld_q,
+  hipLaunchKernelGGL((k_w4a4_gemm<OUT>), dim3(grid), dim3(GEMM_THREADS), 0, st, Qx, ld_q,
                      gid, scale, M, T, K, N, G, Qw, ld_w, w_scale, bias, static_cast<OUT*>(Y), ld_y,
                      acc_dump, m_tiles, n_tiles);
 }
@@ -1421,6 +1420,44 @@ static double small_tile_us(int M, int K, int N) {
   return 2.0 * M * N * K / (K >= 2048 ? 1.7e9 : 1.55e9) + 6.0;
 }
 
+// The kernel a product takes where it does not qualify for the rolling one.
+enum LinearKernel { kRing64x64 = 1, kRing64x128, kRing128x64, kRing128x128, kStaged128, kPipe256, kWide256 };
+
+static LinearKernel linear_kernel(int M, int K, int N, int cus) {
+  // 256 x 256 tiles where they are estimated to be faster (see above); their kernels need
+  // whole stages of K: 256 codes (measured 2 to 3 % faster), else 128
+  if (K % 128 == 0 && big_tile_us(M, K, N, cus) < small_tile_us(M, K, N)) return K % 256 == 0 ? kWide256 : kPipe256;
+  // Otherwise tiles of 64 or 128.  Long K without big tiles: the register-staged kernel, three
+  // workgroups per CU (20000 x 4096 x 500: 54 us against 59, 16384 x 3000 x 768: 47 against 50).
+  auto tiles = [&](int bm, int bn) { return (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  const long long t22 = tiles(128, 128), rounds22 = (t22 + 2 * cus - 1) / (2 * cus);
+  if (K >= 2048 && t22 >= 2 * cus) return kStaged128;
+  // Wide and tall enough to fill two workgroups per CU of 128 x 128 evenly (at least 0.72 of the
+  // last round in use): those, they fetch least (131072 x 1000 x 1024: 178 us against 203 with
+  // 64 x 128 tiles; 7744 x 320 x 1280, whose 610 tiles are 1.2 rounds: 16 against 11).  Else
+  // 64 x 128 if that gives nearly two workgroups per CU and the last column of tiles is more than
+  // half full, else 128 x 64 if those fill three per CU (131072 x 320 x 320: 34 us, 48 with
+  // 64 x 128, 51 with 128 x 128), else 64 x 64 (968 x 512 x 512: 4.8 us, 5.6 with 64 x 128, 11 with
+  // 128 x 128).
+  const bool half_empty = N % 128 >= 1 && N % 128 <= 64;
+  if (K >= 256 && (!half_empty || N >= 1024) &&
+      (double)M * N >= 0.72 * 16384.0 * (double)(rounds22 * 2 * cus))
+    return kRing128x128;
+  // (a launch has fewer than 2^32 threads: 2^30 rows of 65 to 128 outputs are 2^24 tiles of 64 rows)
+  auto fits = [&](int bm, int bn) {
+    const long long rows = ((M + bm - 1) / bm + XCDS - 1) / XCDS;
+    return rows * XCDS * ((N + bn - 1) / bn) * GEMM_THREADS < 1ll << 32;
+  };
+  if (!half_empty && tiles(64, 128) * 8 >= 15ll * cus && fits(64, 128)) return kRing64x128;
+  if (tiles(128, 64) >= 3 * cus && fits(128, 64)) return kRing128x64;
+  return fits(64, 64) ? kRing64x64 : kRing128x128;
+}
+
+// (not part of the ABI: the tests ask which kernel their shapes take)
+extern "C" int tdq_linear_kernel_of(int32_t M, int32_t K, int32_t N, int32_t cus) {
+  return linear_kernel(M, K, N, cus);
+}
+
 hipError_t launch_w4a4_gemm(const uint8_t* Qx, long long ld_q, const int* gid, const float* scale,
                             int M, int T, int K, int N, int G, const uint8_t* Qw, long long ld_w,
                             const float* w_scale, const float* bias, void* Y, tdq_dtype y_dt,
@@ -1443,39 +1480,18 @@ hipError_t launch_w4a4_gemm(const uint8_t* Qx, long long ld_q, const int* gid, c
       return hipGetLastError();
     }
   }
-  // 256 x 256 tiles where they are estimated to be faster (see above); their kernels need
-  // whole stages of K: 256 codes (measured 2 to 3 % faster), else 128
   const int cus = compute_units() >= XCDS ? compute_units() : 256;
-  const bool big = K % 128 == 0 && big_tile_us(M, K, N, cus) < small_tile_us(M, K, N);
-  // Otherwise tiles of 64 or 128.  Wide and tall enough to fill two workgroups per CU of
-  // 128 x 128 evenly (at least 0.72 of the last round in use): those, they fetch least
-  // (131072 x 1000 x 1024: 178 us against 203 with 64 x 128 tiles; 7744 x 320 x 1280, whose
-  // 610 tiles are 1.2 rounds: 16 against 11).  Else 64 x 128 if that gives two workgroups
-  // per CU and the last column of tiles is more than half full, else 128 x 64 if those fill
-  // three per CU (131072 x 320 x 320: 34 us, 48 with 64 x 128, 51 with 128 x 128), else 64 x 64 (968 x 512 x 512: 4.8 us, 5.6 with 64 x 128, 11 with 128 x 128).
-  auto tiles = [&](int bm, int bn) { return (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-  const long long t22 = tiles(128, 128), rounds22 = (t22 + 2 * cus - 1) / (2 * cus);
-  const bool half_empty = N % 128 >= 1 && N % 128 <= 64;
-  const bool full22 = K >= 256 && (!half_empty || N >= 1024) &&
-                      (double)M * N >= 0.72 * 16384.0 * (double)(rounds22 * 2 * cus);
-  const int mode = big ? (K % 256 == 0 ? 7 : 6)
-                   // (long K without big tiles: the register-staged kernel, three workgroups per
-                   // CU; 20000 x 4096 x 500: 54 us against 59, 16384 x 3000 x 768: 47 against 50)
-                   : K >= 2048 && t22 >= 2 * cus ? 5
-                   : full22 ? 4
-                   : !half_empty && tiles(64, 128) >= 480 ? 2
-                   : tiles(128, 64) >= 3 * cus ? 3 : 1;
 #define TDQ_GEMM_ARGS                                                                             \
   (Qx, ld_q, gid, scale, M, T, K, N, G, Qw, ld_w, w_scale, bias, Y, ld_y, acc_dump, st)
 #define TDQ_GEMM_MODES(OUT)                                                                      \
-  switch (mode) {                                                                                \
-    case 7: launch_wide<OUT> TDQ_GEMM_ARGS; break;                                               \
-    case 6: launch_pipe<OUT, 4, 4> TDQ_GEMM_ARGS; break;                                         \
-    case 5: launch_tile<OUT, 2, 2> TDQ_GEMM_ARGS; break;                                         \
-    case 4: launch_ring<OUT, 2, 2> TDQ_GEMM_ARGS; break;                                         \
-    case 3: launch_ring<OUT, 2, 1> TDQ_GEMM_ARGS; break;                                         \
-    case 2: launch_ring<OUT, 1, 2> TDQ_GEMM_ARGS; break;                                         \
-    default: launch_ring<OUT, 1, 1> TDQ_GEMM_ARGS; break;                                        \
+  switch (linear_kernel(M, K, N, cus)) {                                                         \
+    case kWide256: launch_wide<OUT> TDQ_GEMM_ARGS; break;                                        \
+    case kPipe256: launch_pipe<OUT, 4, 4> TDQ_GEMM_ARGS; break;                                  \
+    case kStaged128: launch_tile<OUT> TDQ_GEMM_ARGS; break;                                      \
+    case kRing128x128: launch_ring<OUT, 2, 2> TDQ_GEMM_ARGS; break;                              \
+    case kRing128x64: launch_ring<OUT, 2, 1> TDQ_GEMM_ARGS; break;                               \
+    case kRing64x128: launch_ring<OUT, 1, 2> TDQ_GEMM_ARGS; break;                               \
+    case kRing64x64: launch_ring<OUT, 1, 1> TDQ_GEMM_ARGS; break;                                \
   }
   if (y_dt == TDQ_F32) { TDQ_GEMM_MODES(float) } else { TDQ_GEMM_MODES(_Float16) }
 #undef TDQ_GEMM_MODES

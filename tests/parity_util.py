@@ -26,6 +26,16 @@ def oracle_params(p: tdq.Params) -> O.Params:
                     base_pct=p.base_pct)
 
 
+LINEAR_KERNELS = ("", "64x64", "64x128", "128x64", "128x128", "staged", "pipe", "wide")
+
+
+def linear_kernel(M: int, K: int, N: int, cus: int = 0) -> str:
+    """The contraction kernel that M x K x N takes on this GPU (or one of `cus` CUs) where it does
+    not qualify for the rolling one."""
+    cus = cus or torch.cuda.get_device_properties(0).multi_processor_count
+    return LINEAR_KERNELS[tdq.lib().tdq_linear_kernel_of(M, K, N, cus)]
+
+
 def gpu_calibrate(X: np.ndarray, p: tdq.Params, ld_pad: int = 0):
     """X[B,T,C] numpy -> dict of numpy results from tdq_calibrate_groups."""
     Xd = to_device(X, ld_pad)
