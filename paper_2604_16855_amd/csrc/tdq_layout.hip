@@ -142,7 +142,8 @@ __global__ __launch_bounds__(256) void k_tokenize_stats_chw(
   constexpr int LOADS = TC / 32;             // 16-byte loads per thread and tile
   __shared__ __attribute__((aligned(16))) T tile[TC][PITCH];
 
-  const int t0 = blockIdx.x * TT, b = blockIdx.y;
+  const int t0 = (int)((blockIdx.z * gridDim.x + blockIdx.x) * TT), b = blockIdx.y;
+  if (t0 >= T_) return;                      // (the whole workgroup)
   const int tid = threadIdx.x;
   const T* xb = X + (long long)b * ld_b;
   const int q = tid % PQ;
@@ -285,7 +286,9 @@ static hipError_t tokenize_stats_t(const T* X, int B, int C, int T_, long long l
   const int vin_ok =
       ((reinterpret_cast<uintptr_t>(X) & 15) == 0 && ld_c % E == 0 && ld_b % E == 0) ? 1 : 0;
   const int vout_ok = ((reinterpret_cast<uintptr_t>(Xt) & 15) == 0 && ld_xt % E == 0) ? 1 : 0;
-  const dim3 grid((unsigned)((T_ + 8 * E - 1) / (8 * E)), (unsigned)B);
+  // (a grid has fewer than 2^32 threads along an axis: 2^29 tokens of binary32 are 2^24 workgroups)
+  const unsigned tiles = (unsigned)((T_ + 8 * E - 1) / (8 * E)), most = 1u << 22;
+  const dim3 grid(tiles < most ? tiles : most, (unsigned)B, (tiles + most - 1) / most);
   hipLaunchKernelGGL((k_tokenize_stats_chw<T>), grid, dim3(256), 0, st, X, ld_c, ld_b, C, T_, Xt,
                      ld_xt, vin_ok, vout_ok, r, mean, m2);
   return hipGetLastError();

@@ -190,3 +190,15 @@ def test_fused_statistics_tile_edges(B, C, H, W, dtype):
     g = dict(gid=gid.cpu().numpy(), clip=clip.cpu().numpy(), scale=scale.cpu().numpy(),
              stats=tdq.stats_to_numpy(stats))
     U.assert_calibration_matches(g, ref, p)
+
+
+def test_calibrate_chw_of_many_tokens():
+    """More tiles of tokens in one image than an axis of a grid takes (2^29 tokens are 2^24 tiles)."""
+    T = (1 << 29) + 70
+    X = torch.randn((1, 1, T), device=U.dev())
+    p = tdq.default_params(1)
+    p.flags = 0                                   # the radius is the largest magnitude
+    Xt, gid, clip, scale, _, ws = tdq.tdq_calibrate_groups_chw(X, p)
+    assert torch.equal(Xt.view(-1), X.view(-1))
+    assert clip.item() == X.abs().max().item() and int(gid.max()) == 0
+    assert tdq.device_status(ws) == 0
