@@ -131,6 +131,18 @@ static bool sampled_f32(int B, int T, int C, int G) {
   return elements < (G <= 32 ? 1ll << 20 : 638976ll);
 }
 
+// Whether a calibration samples; the validation switch searches every set of a binary16 image and
+// takes the radix levels for a binary32 one.
+static bool samples_rank(tdq_dtype dt, int B, int T, int C, int G, bool exact_only) {
+  if (bracket_bins(G) == 0) return false;              // too many sets for the interval histogram
+  return dt == TDQ_F16 ? (long long)T * C < (1ll << 32) : !exact_only && sampled_f32(B, T, C, G);
+}
+
+// (not part of the ABI: the tests ask which route their images take)
+extern "C" int tdq_samples_rank(int32_t dt, int32_t B, int32_t T, int32_t C, int32_t G) {
+  return samples_rank(static_cast<tdq_dtype>(dt), B, T, C, G, false) ? 1 : 0;
+}
+
 // Everything of tdq_calibrate_groups after the per-token statistics (which are in the
 // workspace): assignment, rank select(s), projection.  X is token-major.
 static int calibrate_after_stats(const void* X, tdq_dtype dt, int32_t B, int32_t T, int32_t C,
@@ -162,7 +174,7 @@ static int calibrate_after_stats(const void* X, tdq_dtype dt, int32_t B, int32_t
   for (int l = 0; l < lp.n_levels; ++l) cap += 1 << lp.bits[l];
   cap = cap > kListMax ? kListMax : cap;
   const bool f16 = dt == TDQ_F16;
-  const bool sampled = Wmax > 0 && (f16 ? (long long)T * C < (1ll << 32) : !exact_only && sampled_f32(B, T, C, G));
+  const bool sampled = samples_rank(dt, B, T, C, G, exact_only);
   Bracket* br = reinterpret_cast<Bracket*>(ws + wl.br);
   unsigned* bhist = reinterpret_cast<unsigned*>(ws + wl.bhist);
   const bool two_passes = sc.base_pct > 0.0;

@@ -388,9 +388,9 @@ def test_cfg4_heavy_sweep_calibration(name):
                                                             (torch.float16, True, 2, 320, 4096 + 40),
                                                             (torch.float32, False, 0, 512, 4096 + 200)])
 def test_large_tile_contraction_sampled(out_dtype, with_bias, ld_pad, K, N):
-    """Shapes that take the large-tile kernels (many 256x256 tiles; K a multiple of
-    256 for the wide-stage pipelined one, K = 384 and 128 for the 128-code-stage one,
-    K = 320 and 200 for the generic one with its K tail; 768 = three wide stages)
+    """Wide products of short K, which take the ring kernel's tiles of 64 to 128 (the 256 x 256
+    kernels: test_gpu_big_tiles.py), with whole stages of K and tails (320 and 200), 768 = once
+    and a half round the ring,
     without the accumulator dump, so interior tiles take the epilogue's fast
     path and the ragged last row of tiles the bounds-checked one; N = 4096 + 40 / + 200
     adds a ragged last COLUMN of tiles.  ld_pad gives Y a padded leading dimension, whose

@@ -26,16 +26,22 @@ def _packed(codes, extra):
     return torch.from_numpy(buf).to(U.dev())
 
 
-@pytest.mark.parametrize("M,K,N,extra", [
-    (1, 1, 1, 0), (63, 31, 65, 0), (65, 33, 64, 16), (64, 127, 63, 0), (129, 128, 129, 32),
-    (200, 129, 72, 0), (130, 255, 250, 0), (257, 384, 40, 16), (100, 385, 130, 0), (70, 511, 90, 0),
-    (66, 513, 70, 48), (90, 1025, 66, 0),                       # 64 x 64 tiles
-    (2000, 320, 2010, 0), (4100, 97, 1024, 0),                  # 64 x 128
-    (25000, 161, 321, 0), (49999, 64, 60, 0),                   # 128 x 64
-    (8197, 289, 1021, 16), (16380, 256, 520, 0),                # 128 x 128
-    (8200, 2049, 1000, 0),                                      # long K
-])
-def test_ring_tiles_and_tails(M, K, N, extra):
+CASES = [(kernel, *c) for kernel, cases in {
+    "64x64": [(1, 1, 1, 0), (63, 31, 65, 0), (65, 33, 64, 16), (64, 127, 63, 0), (129, 128, 129, 32),
+              (200, 129, 72, 0), (130, 255, 250, 0), (257, 384, 40, 16), (100, 385, 130, 0), (70, 511, 90, 0),
+              (66, 513, 70, 48), (90, 1025, 66, 0), (49999, 64, 60, 0)],
+    "64x128": [(2000, 320, 2010, 0), (4100, 97, 1024, 0), (25000, 161, 321, 0), (8197, 289, 1021, 16),
+               (8193, 1025, 1024, 0)],
+    "128x64": [(16380, 256, 520, 0), (60000, 161, 190, 0), (50000, 33, 190, 16), (100001, 97, 33, 0),
+               (60001, 511, 190, 0)],
+    "128x128": [(8192, 289, 1021, 16), (8191, 513, 1021, 0), (8192, 385, 1024, 0), (30001, 641, 250, 48)],
+    "staged": [(8200, 2049, 1000, 0)],                          # long K
+}.items() for c in cases]
+
+
+@pytest.mark.parametrize("kernel,M,K,N,extra", CASES)
+def test_ring_tiles_and_tails(kernel, M, K, N, extra):
+    assert U.linear_kernel(M, K, N) == kernel
     qx, qw = I.random_codes((M, K), M + K), I.random_codes((N, K), N + 3 * K)
     rng = np.random.default_rng(M * N)
     G = 5

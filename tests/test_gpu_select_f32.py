@@ -1,9 +1,9 @@
 """The two-sweep rank select of binary32 input against the oracle, where it can go wrong: ties
 (all values of a set equal, a fifth of them zero, few distinct values), values close together
 far from zero (the interval is narrow), heavy tails, sets smaller than the sample, several
-batches of tokens, a bin that collects more keys than a list holds, rows at element alignment,
-the percentile base radius, 33 to 64 sets (256 bins), and the largest image of the route next
-to the smallest one past it."""
+batches of tokens, ties and other values in one bin, rows at element alignment,
+the percentile base radius, 33 to 64 sets (256 bins), and the largest images of the route next
+to the smallest ones past it."""
 import numpy as np
 import pytest
 
@@ -52,8 +52,27 @@ def test_interval_holds_the_rank():
     assert g["exact_sets"] == 0
 
 
+@pytest.mark.parametrize("B,T,C,G,sampled", [
+    (1, 1023, 1024, 16, True), (1, 1024, 1024, 16, False),       # 1 Mi elements
+    (1, 1023, 1024, 4, True), (1, 1024, 1024, 4, False),
+    (1, 623, 1024, 64, True), (1, 624, 1024, 64, False),         # shorter lists
+    (1, 32768, 9, 1, True), (1, 32769, 9, 1, False),             # many tokens, few sets
+    (1, 49152, 5, 3, True), (1, 49153, 5, 3, False),
+    (128, 30, 35, 32, True), (129, 30, 35, 32, False),           # many small sets
+])
+def test_limits_of_the_route(B, T, C, G, sampled):
+    """The largest images of the sampled route and the smallest past it."""
+    assert bool(tdq.lib().tdq_samples_rank(tdq.TDQ_F32, B, T, C, G)) == sampled
+    X = _data("laplace", B, T, C, T + G)
+    p = tdq.default_params(G)
+    g = U.gpu_calibrate(X, p)
+    U.assert_calibration_matches(g, X, p)
+    assert g["exact_sets"] == 0
+
+
 @pytest.mark.parametrize("T", [2912, 2913])
-def test_largest_image_of_the_route(T):
+def test_images_of_three_million_elements(T):
+    """Radix levels."""
     X = _data("laplace", 1, T, 1024, T)
     p = tdq.default_params(4)
     U.assert_calibration_matches(U.gpu_calibrate(X, p), X, p)
