@@ -55,8 +55,9 @@ typedef enum {
 #define TDQ_FLAG_C1 1u /* constraint C1: Delta <= tau * sigma   (Eq. tau_constraint) */
 #define TDQ_FLAG_C2 2u /* constraint C2: Delta/2 <= Q_zr(|x|)   (Eq. zr_constraint)  */
 /* Validation switch, no effect on the result: resolve the zr rank of every token set
- * of a binary16 input by the per-set radix select alone (the route that is
- * otherwise taken only by a set whose sampled key interval missed the rank). */
+ * of a binary16 input by a search of the set's own rows alone (the route that is
+ * otherwise taken only by a set whose sampled key interval missed the rank); a binary32
+ * input takes the radix levels. */
 #define TDQ_FLAG_EXACT_SELECT 256u
 
 #define TDQ_MAX_GROUPS 256
@@ -106,9 +107,10 @@ typedef struct tdq_group_stats {
  * to tdq_calibrate_groups; read it back after synchronising the stream). */
 #define TDQ_DEV_NONFINITE 1u /* X holds an Inf or NaN: results undefined          */
 /* The second uint32 of the workspace is a diagnostic: the number of (image, token set) pairs
- * whose zr rank was resolved by the per-set radix select because the sampled key interval
+ * whose zr rank was resolved by a search of the set's own rows because the sampled key interval
  * missed it, more binary32 keys shared its histogram bin than are collected (or, for binary16
- * input, because TDQ_FLAG_EXACT_SELECT was set).  It has no bearing on the results. */
+ * input, because TDQ_FLAG_EXACT_SELECT was set).  The third is the same of the base radius's rank
+ * (base_pct).  They have no bearing on the results. */
 
 int tdq_version(void);
 const char* tdq_status_string(int status);
@@ -132,8 +134,11 @@ size_t tdq_workspace_bytes(int32_t B, int32_t T, int32_t C, tdq_dtype dt, const 
  *     thr = the ceil(zr n)-th smallest |x| of the group, exact: an order statistic
  *     of the magnitude bit patterns found with LDS histograms (one sweep, or two for
  *     binary32 input, over a key interval chosen from a sample, verified by counting, with
- *     a radix select for any set the interval missed; radix select alone for more than 64
- *     sets and for binary32 images of several million elements);
+ *     a search of the set's own rows for any set the interval missed; radix levels alone for
+ *     more than 64 sets, and for binary32 images of 2^20 elements or more (638976 with more
+ *     than 32 sets) or of many tokens in few sets (T > 32768 and T > 16384 G), and for thousands of
+ *     sets of no more than 4096 elements each or images with more sets than channels
+ *     (B G T >= 2^23, C <= G));
  *  4. c = max(min(c_base, q_max tau sigma, 2 q_max thr), eps),
  *     Delta = max(c / q_max, eps)                    (Eqs. dcrp, clipx; Lemma 1).
  *
@@ -160,7 +165,7 @@ int tdq_calibrate_groups(const void* X, tdq_dtype dt, int32_t B, int32_t T, int3
  * on one GPU share that GPU's array: calls that overlap in time on one GPU (different
  * streams, or threads) race; calls ordered on one stream do not.
  * status [4] device out or NULL: word 0 the device status word (TDQ_DEV_*), words 1 and 2
- * the counts of token sets resolved by the per-set radix select (zr pass, base-radius
+ * the counts of token sets resolved by a search of their own rows (zr pass, base-radius
  * pass), word 3 zero.  Other arguments as tdq_calibrate_groups.
  */
 #define TDQ_STATIC_SCRATCH_BYTES (16u << 20)

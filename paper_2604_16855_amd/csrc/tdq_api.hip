@@ -113,29 +113,43 @@ static Scalars make_scalars(const tdq_params* p) {
   return s;
 }
 
-// Whether a binary32 calibration samples (two sweeps of X) or takes the radix levels (one sweep per
-// eight to five key bits, whatever the data).
+// Whether the image takes the radix levels (a sweep per eight to five key bits, whatever the data)
+// because of its sets.  The sampled route's first and last kernels have a workgroup per set, and in the
+// first each reads the image's T ranges; figures below are us, sampled against levels.
+//   * Thousands of sets of no more than 4096 elements: [256, 64, 768] with 16 sets, binary32 102 and
+//     93, binary16 56 and 49; [256, 1024, 8] 88 and 60, 57 and 39; [512, 49, 768] with 64 sets, binary16,
+//     247 and 147; [2048, 49, 96] 808 and 265.  Of 8192 elements a set the sampled route is faster
+//     everywhere, and up to 4096 sets it is with few sets an image ([1024, 64, 128] with 4, binary32:
+//     107 and 133) or many ([64, 256, 768] with 64: 101 and 115, 58 and 75).
+//   * More tokens to look at than elements, and more workgroups than run at once: [64, 16384, 8] with 32
+//     sets, binary32 202 and 130, binary16 141 and 91; [256, 16384, 8] 728 and 356, 553 and 253; but
+//     [16, 65536, 8] with 16 sets 124 and 148, 97 and 113.
+static bool many_small_sets(int B, int T, int C, int G) {
+  const long long sets = (long long)B * G;
+  if (sets > (G >= 8 && G <= 32 ? 2048 : 4096) && (long long)T * C <= 4096ll * G) return true;
+  return sets > 512 && sets * T >= 1ll << 23 && C <= G;
+}
+
+// Whether a binary32 image may sample (two sweeps of X).
 //   * A bin that collects more keys than a list holds, or an interval that misses, costs a search
 //     of the set's rows by one workgroup: 50 us for 0.2 M elements, 200 for 1 M, against 50 to 70 for
 //     all radix levels of such an image.  So images stay below 1 Mi elements, 0.6 Mi with more
 //     than 32 sets, whose lists are short.
-//   * Its first kernel has a workgroup per set, each of which reads the image's T ranges.  Images
-//     of many tokens and few sets ([1, 400000, 1], one set: 239 us by levels, 473 sampled; 16 sets 467
-//     and 470; [1, 100000, 8], 5 sets: 117 and 159; 16 sets 166 and 130; [1, 16385, 33], one set: 69
-//     and 57) and large batches of small sets ([2048, 49, 96], 5 sets: 127 and 177; [512, 49, 768],
-//     16 sets: 145 and 159; [64, 196, 384], 64 sets: 97 and 86) are faster by levels.
-static bool sampled_f32(int B, int T, int C, int G) {
-  const long long elements = (long long)T * C;
+//   * A set of many tokens is one workgroup's chain of T / 1024 steps, which a small image's levels
+//     undercut: [1, 400000, 1], one set: 239 us by levels, 473 sampled; 16 sets 467 and 470;
+//     [1, 100000, 8], 5 sets: 117 and 159; 16 sets 166 and 130; [1, 16385, 33], one set: 69 and 57.
+static bool sampled_f32(int T, int C, int G) {
   if (T > 32768 && T > 16384ll * G) return false;
-  if ((long long)B * G > 4096 && elements < 3072ll * G) return false;
-  return elements < (G <= 32 ? 1ll << 20 : 638976ll);
+  return (long long)T * C < (G <= 32 ? 1ll << 20 : 638976ll);
 }
 
 // Whether a calibration samples; the validation switch searches every set of a binary16 image and
 // takes the radix levels for a binary32 one.
 static bool samples_rank(tdq_dtype dt, int B, int T, int C, int G, bool exact_only) {
   if (bracket_bins(G) == 0) return false;              // too many sets for the interval histogram
-  return dt == TDQ_F16 ? (long long)T * C < (1ll << 32) : !exact_only && sampled_f32(B, T, C, G);
+  if (dt == TDQ_F16 && (long long)T * C >= 1ll << 32) return false;
+  if (dt == TDQ_F16 && exact_only) return true;
+  return !exact_only && !many_small_sets(B, T, C, G) && (dt == TDQ_F16 || sampled_f32(T, C, G));
 }
 
 // (not part of the ABI: the tests ask which route their images take)

@@ -58,7 +58,7 @@ def test_interval_holds_the_rank():
     (1, 623, 1024, 64, True), (1, 624, 1024, 64, False),         # shorter lists
     (1, 32768, 9, 1, True), (1, 32769, 9, 1, False),             # many tokens, few sets
     (1, 49152, 5, 3, True), (1, 49153, 5, 3, False),
-    (128, 30, 35, 32, True), (129, 30, 35, 32, False),           # many small sets
+    (64, 30, 35, 32, True), (65, 30, 35, 32, False),             # many small sets
 ])
 def test_limits_of_the_route(B, T, C, G, sampled):
     """The largest images of the sampled route and the smallest past it."""
