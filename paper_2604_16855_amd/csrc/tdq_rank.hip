@@ -69,8 +69,8 @@ __device__ __forceinline__ u32 bin_of(u32 d, u32 shift, u32 cell) {
 // the wavefronts exchange one count each.  SM = most sampled elements: the rank error of 8 Ki
 // is 0.45 % of the set's mass, about 40 keys at 1024 keys per octave where keys are dense, against
 // a half-width of Wfew / 2 >= 256 keys; where they are not, W bins are used.  16 Ki are drawn with
-// fewer bins per set (more than 32 sets), for the percentile base radius and with fewer than 8
-// sets, whose tokens differ more.  A set smaller than the sample is read with as many loads as it
+// fewer bins per set (more than 32 sets), for the percentile base radius, with fewer than 8
+// sets, whose tokens differ more, and for large sets that have no W bins to turn to.  A set smaller than the sample is read with as many loads as it
 // has pieces (2048 images of [49, 96], 64 sets: 920 -> 640 us).
 // Measured, calibration of one call (two kernels for this before: assignment, then sample):
 // [1, 7744, 64] 46.3 -> 30.9 us, [8, 121, 512] 30.7 -> 26.0, [32, 4096, 1024] 118.7 -> 108.3;
@@ -611,8 +611,13 @@ static void sets_t(const TX* X, int B, int T, int C, long long ld, int G, int Wf
                    int cap, unsigned* img_flag, unsigned* status, hipStream_t st) {
   constexpr int V = Elem<TX>::V;
   const int aligned = ((reinterpret_cast<uintptr_t>(X) & 15) == 0 && ld % V == 0 && C % V == 0) ? 1 : 0;
-  // 8 Ki sampled elements are enough (binary32: a wider interval costs little), or the image
-  const bool few = (Wfew >= 512 && G >= 8 && pass == kPassZr) || (long long)T * C <= 8192;
+  // 8 Ki sampled elements are enough (binary32: a wider interval costs little), or the image is no
+  // larger.  17 to 32 sets have no wider interval to fall back on: from 64 Ki elements a set on, where a
+  // missed set's search costs most, they draw 16 Ki.  [32, 4096, 1024], 32 sets: 111.8 -> 116.0 us, but
+  // after a GELU 140 -> 115, clamped to [0, 6] (16 % zeros, five missed sets of 0.1 M to 4 M elements, then
+  // none) 1165 -> 110, with 15 % zeros 226 -> 194.
+  const bool few = (Wfew >= 512 && G >= 8 && pass == kPassZr && (W > Wfew || (long long)T * C <= 65536ll * G)) ||
+                   (long long)T * C <= 8192;
   const size_t order_bytes = T <= kListTokens ? (size_t)T * sizeof(unsigned short) : 0;
 #define TDQ_SETS_SM(NT, SM)                                                                        \
   hipLaunchKernelGGL((k_sets<TX, NT, SM>), dim3(G, B), dim3(NT), order_bytes, st, X, ld, T, C, G, Wfew, W, cells, aligned, r, \
