@@ -77,7 +77,8 @@ __device__ __forceinline__ u32 bin_of(u32 d, u32 shift, u32 cell) {
 // with 16 Ki samples 31.7 / 26.9 / 111.0.  Then, this kernel alone: the sample's loads issued
 // before those of the moments, and the tokens listed by rank in LDS, so that only the drawn
 // ones cost divisions (T <= kListTokens; the list of a larger image would not leave LDS for
-// several workgroups): 24.8 -> 20.3 us at [32, 4096, 1024], 14.4 -> 11.9 at [1, 7744, 64].
+// several workgroups): 24.8 -> 20.3 us at [32, 4096, 1024] (25.4 with 16 Ki samples), 14.4 -> 11.9 at
+// [1, 7744, 64].
 // ---------------------------------------------------------------------------
 // One workgroup's search of K 1024-bin LDS histograms (or K times the same) for the bin that
 // holds rank r[q] (1-based, at most the histogram's total) of h[q]: bin[q] and the count before
