@@ -143,10 +143,11 @@ __global__ __launch_bounds__(256) void k_token_stats(const T* __restrict__ X, lo
                                                      int C, double inv_n, int vec_ok,
                                                      float* __restrict__ r,
                                                      double* __restrict__ mean,
-                                                     double* __restrict__ m2) {
+                                                     double* __restrict__ m2, SelectClear cl) {
   constexpr int V = Elem<T>::V;
   typedef typename PivotOf<T>::type PT;
   const long long gt = (long long)blockIdx.x * 256 + threadIdx.x;
+  clear_select(cl, (unsigned long long)gt, (unsigned long long)gridDim.x * 256);
   const long long row = gt / L;
   const int lr = (int)(gt % L);
   const bool valid = row < M;
@@ -190,13 +191,14 @@ __global__ __launch_bounds__(256) void k_token_stats_wide(const T* __restrict__ 
                                                           int C, double inv_n,
                                                           float* __restrict__ r,
                                                           double* __restrict__ mean,
-                                                          double* __restrict__ m2) {
+                                                          double* __restrict__ m2, SelectClear cl) {
   constexpr int V = Elem<T>::V;
   typedef typename PivotOf<T>::type PT;
   __shared__ double sh1[2][4], sh2[2][4];
   __shared__ u32 shk[4];
   const long long row = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  clear_select(cl, (unsigned long long)row * 256 + tid, (unsigned long long)gridDim.x * 256);
   const T* xp = X + row * ld;
   const int nvec = C / V;
   PT P = row_pivot(xp, C, true);
@@ -238,12 +240,12 @@ __global__ __launch_bounds__(256) void k_token_stats_wide(const T* __restrict__ 
 
 template <typename T>
 static hipError_t token_stats_t(const T* X, int M, int C, long long ld, float* r, double* mean,
-                                double* m2, hipStream_t st) {
+                                double* m2, const SelectClear& cl, hipStream_t st) {
   constexpr int V = Elem<T>::V;
   const int vec_ok = ((reinterpret_cast<uintptr_t>(X) & 15) == 0 && ld % V == 0) ? 1 : 0;
   if (vec_ok && C / V >= 256) {
     hipLaunchKernelGGL((k_token_stats_wide<T>), dim3(M), dim3(256), 0, st, X, ld, M, C,
-                       1.0 / (double)C, r, mean, m2);
+                       1.0 / (double)C, r, mean, m2, cl);
     return hipGetLastError();
   }
   const int L = sweep_lanes_per_row(C, V);
@@ -252,7 +254,7 @@ static hipError_t token_stats_t(const T* X, int M, int C, long long ld, float* r
 #define TDQ_TS(LL)                                                                       \
   case LL:                                                                               \
     hipLaunchKernelGGL((k_token_stats<T, LL>), dim3(grid), dim3(256), 0, st, X, ld, M, C, \
-                       1.0 / (double)C, vec_ok, r, mean, m2);                            \
+                       1.0 / (double)C, vec_ok, r, mean, m2, cl);                        \
     break;
   switch (L) {
     TDQ_TS(1) TDQ_TS(2) TDQ_TS(4) TDQ_TS(8) TDQ_TS(16) TDQ_TS(32) TDQ_TS(64)
@@ -262,10 +264,10 @@ static hipError_t token_stats_t(const T* X, int M, int C, long long ld, float* r
 }
 
 hipError_t launch_token_stats(const void* X, tdq_dtype dt, int M, int C, long long ld, float* r,
-                              double* mean, double* m2, hipStream_t st) {
+                              double* mean, double* m2, const SelectClear& cl, hipStream_t st) {
   if (dt == TDQ_F16)
-    return token_stats_t<u16>(static_cast<const u16*>(X), M, C, ld, r, mean, m2, st);
-  return token_stats_t<float>(static_cast<const float*>(X), M, C, ld, r, mean, m2, st);
+    return token_stats_t<u16>(static_cast<const u16*>(X), M, C, ld, r, mean, m2, cl, st);
+  return token_stats_t<float>(static_cast<const float*>(X), M, C, ld, r, mean, m2, cl, st);
 }
 
 // ---------------------------------------------------------------------------

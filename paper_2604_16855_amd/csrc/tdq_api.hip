@@ -152,9 +152,66 @@ static bool samples_rank(tdq_dtype dt, int B, int T, int C, int G, bool exact_on
   return !exact_only && !many_small_sets(B, T, C, G) && (dt == TDQ_F16 || sampled_f32(T, C, G));
 }
 
+// Whether the sampled route takes one kernel for assignment and rank select together, and if so with how many
+// workgroups per image beyond one per set (-1 = no).  Figures are us per layer, one kernel against three (or
+// four).
+//   * A workgroup for every 8 Ki elements, and no more than 512 in all (two per CU): [8, 121, 512] with 16 sets
+//     22.1 / 22.0 / 21.1 with 64 / 16 / 8 Ki, [16, 484, 320] 35.8 / 34.2 / 33.2.
+//   * No more than 64 Ki elements for each (all tokens may be in one set): every workgroup of a set repeats the
+//     search for its tokens and its interval, so a large batch is better off with one sweep over all sets.
+//     [21, 536, 1344], 80 Ki each, 77.3 against 75.0; [28, 187, 1984], 124 Ki, 71.4 against 68.8; but
+//     [14, 5850, 160], 29 Ki, percentile, 97.9 against 122.3.
+//   * binary32 reads a set's rows twice, so one workgroup sees all of a set: [2, 1400, 32] (45 Ki elements) 38.6
+//     against 44.7, [5, 1280, 84] (107 Ki) 60.5 against 47.4, [1, 377, 416] (157 Ki) 84.0 against 48.2.
+//   * Two ranks share the set's words of the workspace if several workgroups meet in them: 512 bins each are
+//     the least.
+static int whole_extra(tdq_dtype dt, int B, int T, int C, int G, bool two_ranks) {
+  const long long e = (long long)T * C;
+  if (T > kWholeTokens) return -1;
+  if (dt == TDQ_F32) return e <= 57344 ? 0 : -1;
+  long long extra = e / 8192;
+  const long long most = 512 / B - G;
+  if (extra > most) extra = most > 0 ? most : 0;
+  if (two_ranks && extra > 0 && bracket_bins(G) < 1024) return -1;
+  if (e > 65536 * (extra + 1)) return -1;
+  return (int)extra;
+}
+
 // (not part of the ABI: the tests ask which route their images take)
 extern "C" int tdq_samples_rank(int32_t dt, int32_t B, int32_t T, int32_t C, int32_t G) {
   return samples_rank(static_cast<tdq_dtype>(dt), B, T, C, G, false) ? 1 : 0;
+}
+
+static int calibration_extra(tdq_dtype dt, int B, int T, int C, const tdq_params* p) {
+  const bool exact_only = (p->flags & TDQ_FLAG_EXACT_SELECT) != 0;
+  if (exact_only || !samples_rank(dt, B, T, C, p->n_groups, false)) return -1;
+  return whole_extra(dt, B, T, C, p->n_groups, p->base_pct > 0.0 && p->base_pct < 1.0);
+}
+
+// What the statistics kernel clears for the rank select.
+static SelectClear select_clear(tdq_dtype dt, int B, int T, int C, const tdq_params* p, void* workspace,
+                                const WorkspaceLayout& wl) {
+  SelectClear c;
+  memset(&c, 0, sizeof(c));
+  const int extra = calibration_extra(dt, B, T, C, p);
+  if (extra < 0) return c;
+  char* ws = static_cast<char*>(workspace);
+  c.status = reinterpret_cast<unsigned*>(ws + wl.status);
+  if (extra == 0) return c;
+  c.ctl = reinterpret_cast<unsigned*>(ws + wl.part);
+  c.n_ctl = (unsigned)(B * p->n_groups * kSetCtl);
+  c.hist = reinterpret_cast<unsigned*>(ws + wl.bhist);
+  c.n_hist = (unsigned)(B * p->n_groups * bracket_bins(p->n_groups));
+  return c;
+}
+
+// (not part of the ABI: the tests ask which images take the one kernel)
+extern "C" int tdq_whole_extra(int32_t dt, int32_t B, int32_t T, int32_t C, int32_t G, double base_pct) {
+  tdq_params p;
+  tdq_default_params(&p);
+  p.n_groups = G;
+  p.base_pct = base_pct;
+  return calibration_extra(static_cast<tdq_dtype>(dt), B, T, C, &p);
 }
 
 // Everything of tdq_calibrate_groups after the per-token statistics (which are in the
@@ -193,6 +250,14 @@ static int calibrate_after_stats(const void* X, tdq_dtype dt, int32_t B, int32_t
   unsigned* bhist = reinterpret_cast<unsigned*>(ws + wl.bhist);
   const bool two_passes = sc.base_pct > 0.0;
   void* part = ws + wl.part;
+  const int extra = calibration_extra(dt, B, T, C, p);
+  if (extra >= 0) {
+    const int W = two_passes && extra > 0 ? Wmax / 2 : Wmax, few = bracket_bins_zr(G);
+    if (launch_sets_whole(X, dt, B, T, C, ld_x, G, two_passes ? 2 : 1, extra, few < W ? few : W, W, r, mean, m2,
+                          group_id, sc, bhist, part, img_flag, status, clip, scale, stats, st) != hipSuccess)
+      return TDQ_ERR_HIP;
+    return TDQ_OK;
+  }
   if (!sampled || exact_only) {          // (the sampled route's own first kernel assigns the sets)
     if (launch_assign(r, mean, m2, B, T, C, G, group_id, part, img_flag, status, st) != hipSuccess)
       return TDQ_ERR_HIP;
@@ -343,7 +408,7 @@ int tdq_calibrate_groups(const void* X, tdq_dtype dt, int32_t B, int32_t T, int3
   char* ws = static_cast<char*>(workspace);
   if (launch_token_stats(X, dt, B * T, C, ld_x, reinterpret_cast<float*>(ws + wl.r),
                          reinterpret_cast<double*>(ws + wl.mean),
-                         reinterpret_cast<double*>(ws + wl.m2), st) != hipSuccess)
+                         reinterpret_cast<double*>(ws + wl.m2), select_clear(dt, B, T, C, p, ws, wl), st) != hipSuccess)
     return TDQ_ERR_HIP;
   return calibrate_after_stats(X, dt, B, T, C, ld_x, p, group_id, clip, scale, stats, workspace, lp,
                                wl, st);
@@ -404,7 +469,8 @@ int tdq_calibrate_groups_chw(const void* X, tdq_dtype dt, int32_t B, int32_t C, 
   if (launch_tokenize_stats_chw(X, dt, B, C, T, ld_c, ld_b, Xt, ld_xt,
                                 reinterpret_cast<float*>(ws + wl.r),
                                 reinterpret_cast<double*>(ws + wl.mean),
-                                reinterpret_cast<double*>(ws + wl.m2), st) != hipSuccess)
+                                reinterpret_cast<double*>(ws + wl.m2), select_clear(dt, B, T, C, p, ws, wl),
+                                st) != hipSuccess)
     return TDQ_ERR_HIP;
   return calibrate_after_stats(Xt, dt, B, T, C, ld_xt, p, group_id, clip, scale, stats, workspace,
                                lp, wl, st);

@@ -78,6 +78,14 @@ inline int sweep_lanes_per_row(int C, int V) {
   return L;
 }
 
+// Thread `i` of `n` of a statistics kernel clears its share.
+__device__ __forceinline__ void clear_select(const SelectClear& c, unsigned long long i, unsigned long long n) {
+  if (!c.status) return;
+  if (i < 3) c.status[i] = 0u;
+  for (unsigned long long k = i; k < c.n_ctl; k += n) c.ctl[k] = 0u;
+  for (unsigned long long k = i; k < c.n_hist / 4; k += n) reinterpret_cast<uint4*>(c.hist)[k] = make_uint4(0, 0, 0, 0);
+}
+
 // Reductions over groups of L adjacent lanes (L a power of two <= 64) with DPP
 // row shifts and row broadcasts, i.e. at vector-ALU speed instead of one LDS round
 // trip per step.  The result is valid in the LAST lane of every group
@@ -148,6 +156,9 @@ __device__ __forceinline__ u32 group_sum_u32(u32 v) {
   if (L > 32) v += dpp_u32<TDQ_DPP_ROW_BCAST31, 0xC>(v);
   return v;
 }
+
+// Inclusive scan over the wavefront: the partial windows of group_sum_u32<64> are exactly that.
+__device__ __forceinline__ u32 wave_scan_u32(u32 v) { return group_sum_u32<64>(v); }
 
 // ---------------------------------------------------------------------------
 // Moments.  The dispersion of a set is the population standard deviation of all its
@@ -425,10 +436,11 @@ __device__ inline void project_store(int idx, const GroupWork& w, u32 key, bool 
     if (!(c > sc.eps_scale)) { c = sc.eps_scale; bind = TDQ_BIND_EPS; }
     d = c / sc.qmax;
     d = d > sc.eps_scale ? d : sc.eps_scale;
-    // original rank (k_rem has been consumed): recompute for the record
-    const double n = (double)w.n;
-    kk = (long long)ceil(sc.zr * n);
-    kk = kk < 1 ? 1 : (kk > w.n ? w.n : kk);
+    if (stats) {        // original rank (k_rem has been consumed): recompute for the record
+      const double n = (double)w.n;
+      kk = (long long)ceil(sc.zr * n);
+      kk = kk < 1 ? 1 : (kk > w.n ? w.n : kk);
+    }
   }
   clip[idx] = c;
   scale[idx] = d;

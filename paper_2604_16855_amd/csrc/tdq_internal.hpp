@@ -106,9 +106,19 @@ struct Scalars {   // fp32 constants of the projection, rounded once on the host
 constexpr int kPassZr = 0;
 constexpr int kPassBase = 1;
 
+// What a statistics kernel clears for the kernels after it: the status words, and words that
+// workgroups of the rank select add into.
+struct SelectClear {
+  unsigned* status;        // nullptr: nothing to clear
+  unsigned* ctl;
+  unsigned n_ctl;
+  unsigned* hist;          // n_hist words, a multiple of 4, 16-byte aligned
+  unsigned n_hist;
+};
+
 // ---- launch wrappers (each returns the hipError_t of its launch) -------------
 hipError_t launch_token_stats(const void* X, tdq_dtype dt, int M, int C, long long ld,
-                              float* r, double* mean, double* m2, hipStream_t st);
+                              float* r, double* mean, double* m2, const SelectClear& cl, hipStream_t st);
 // Token-set assignment.  An image is shared by assign_split(T) workgroups, each of
 // which leaves one partial record per set in `part`; the records are merged into
 // GroupWork by launch_finalize_groups.  (The sampled rank select of either type assigns the sets
@@ -141,6 +151,18 @@ hipError_t launch_sets(const void* X, tdq_dtype dt, int B, int T, int C, long lo
                        const Scalars& sc, int pass, bool keep_base, GroupWork* grp, Bracket* br,
                        unsigned* bhist, unsigned* lists, int cap, unsigned* img_flag,
                        unsigned* status, hipStream_t st);
+// The same for images of up to kWholeTokens tokens, seen through to the radii: the G + extra workgroups of
+// an image are shared out to its sets and read their rows; ranks = 2: the percentile base radius as well.
+// bhist (ranks * W words per set) and ctl (kSetCtl words per set) are cleared by the statistics kernel if
+// extra > 0.
+constexpr int kWholeTokens = 8192;     // (the list of tokens and the rest fit 64 KiB of LDS)
+constexpr int kListTokens = 16384;     // most tokens of an image listed by rank in LDS
+constexpr int kSetCtl = 4;
+hipError_t launch_sets_whole(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G, int ranks,
+                             int extra, int Wfew, int W, const float* r, const double* mean, const double* m2,
+                             int* gid, const Scalars& sc, unsigned* bhist, void* ctl, unsigned* img_flag,
+                             unsigned* status, float* clip, float* scale, tdq_group_stats* stats,
+                             hipStream_t st);
 hipError_t launch_bracket_hist(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G,
                                int Wfew, int W, int cells, unsigned* lists, int cap, const int* gid,
                                Bracket* br, unsigned* bhist, hipStream_t st);
@@ -178,7 +200,7 @@ hipError_t launch_range_disparity(const void* X, tdq_dtype dt, int B, int T, int
                                   float* max_abs, hipStream_t st);
 hipError_t launch_tokenize_stats_chw(const void* X, tdq_dtype dt, int B, int C, int T, long long ld_c,
                                      long long ld_b, void* Xt, long long ld_xt, float* r, double* mean,
-                                     double* m2, hipStream_t st);
+                                     double* m2, const SelectClear& cl, hipStream_t st);
 hipError_t launch_quantize_f6(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G,
                               const int* gid, const float* clip, const float* scale, uint8_t* F,
                               hipStream_t st);

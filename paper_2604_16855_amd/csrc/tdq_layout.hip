@@ -130,7 +130,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_tokenize_stats_chw(
     const T* __restrict__ X, long long ld_c, long long ld_b, int C, int T_, T* __restrict__ Xt,
     long long ld_xt, int vin_ok, int vout_ok, float* __restrict__ r, double* __restrict__ mean,
-    double* __restrict__ m2) {
+    double* __restrict__ m2, SelectClear cl) {
   constexpr bool F16 = sizeof(T) == 2;
   constexpr int E = 16 / (int)sizeof(T);
   constexpr int TC = kStatsTileC;
@@ -143,6 +143,8 @@ __global__ __launch_bounds__(256) void k_tokenize_stats_chw(
   __shared__ __attribute__((aligned(16))) T tile[TC][PITCH];
 
   const int t0 = (int)((blockIdx.z * gridDim.x + blockIdx.x) * TT), b = blockIdx.y;
+  clear_select(cl, ((unsigned long long)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x,
+               (unsigned long long)gridDim.x * gridDim.y * 256);      // (every z the same)
   if (t0 >= T_) return;                      // (the whole workgroup)
   const int tid = threadIdx.x;
   const T* xb = X + (long long)b * ld_b;
@@ -281,7 +283,7 @@ __global__ __launch_bounds__(256) void k_tokenize_stats_chw(
 template <typename T>
 static hipError_t tokenize_stats_t(const T* X, int B, int C, int T_, long long ld_c, long long ld_b,
                                    T* Xt, long long ld_xt, float* r, double* mean, double* m2,
-                                   hipStream_t st) {
+                                   const SelectClear& cl, hipStream_t st) {
   constexpr int E = 16 / (int)sizeof(T);
   const int vin_ok =
       ((reinterpret_cast<uintptr_t>(X) & 15) == 0 && ld_c % E == 0 && ld_b % E == 0) ? 1 : 0;
@@ -290,18 +292,18 @@ static hipError_t tokenize_stats_t(const T* X, int B, int C, int T_, long long l
   const unsigned tiles = (unsigned)((T_ + 8 * E - 1) / (8 * E)), most = 1u << 22;
   const dim3 grid(tiles < most ? tiles : most, (unsigned)B, (tiles + most - 1) / most);
   hipLaunchKernelGGL((k_tokenize_stats_chw<T>), grid, dim3(256), 0, st, X, ld_c, ld_b, C, T_, Xt,
-                     ld_xt, vin_ok, vout_ok, r, mean, m2);
+                     ld_xt, vin_ok, vout_ok, r, mean, m2, cl);
   return hipGetLastError();
 }
 
 hipError_t launch_tokenize_stats_chw(const void* X, tdq_dtype dt, int B, int C, int T, long long ld_c,
                                      long long ld_b, void* Xt, long long ld_xt, float* r, double* mean,
-                                     double* m2, hipStream_t st) {
+                                     double* m2, const SelectClear& cl, hipStream_t st) {
   if (dt == TDQ_F16)
     return tokenize_stats_t<u16>(static_cast<const u16*>(X), B, C, T, ld_c, ld_b,
-                                 static_cast<u16*>(Xt), ld_xt, r, mean, m2, st);
+                                 static_cast<u16*>(Xt), ld_xt, r, mean, m2, cl, st);
   return tokenize_stats_t<float>(static_cast<const float*>(X), B, C, T, ld_c, ld_b,
-                                 static_cast<float*>(Xt), ld_xt, r, mean, m2, st);
+                                 static_cast<float*>(Xt), ld_xt, r, mean, m2, cl, st);
 }
 
 }  // namespace tdq

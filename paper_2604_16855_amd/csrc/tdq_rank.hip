@@ -23,6 +23,10 @@
 //                     workgroup finds the key in the set's own rows, on the side of the
 //                     interval where it must be (exact as well, and rare).
 //
+// Images of ordinary size take one kernel instead of these (k_sets with WHOLE): the workgroups that find a
+// set's tokens and place its interval then read the set's own rows, several sharing a set, and the last of
+// them to finish verifies, picks and projects.  Nothing but the statistics has to be complete before it.
+//
 // The result is therefore always the exact order statistic; the sample only decides
 // which of the two routes computes it, i.e. how long it takes.
 //
@@ -33,11 +37,23 @@
 
 namespace tdq {
 
+typedef short s2v __attribute__((ext_vector_type(2)));
+typedef unsigned long long u64;
+
 constexpr int kRunLen = 32;                                     // channels per run (64 bytes)
 constexpr int kSampleBits = 10;                                 // key bits the sample histogram resolves
 constexpr int kSweepThreads = 1024;
-constexpr int kIdRounds = 16;                                   // range keys a thread of k_sets holds
-constexpr int kListTokens = 16384;                              // most tokens listed by rank in LDS
+constexpr int kIdRounds = 16;                                   // most range keys a thread of k_sets holds
+
+// Arguments of a k_sets that sees a set through to its radius.
+struct WholeArgs {
+  int extra;                  // workgroups per image beyond one per set
+  int L;                      // lanes per row
+  u32* ctl;                   // per set kSetCtl words, cleared before: parts that have arrived, counts below
+  float* clip;
+  float* scale;
+  tdq_group_stats* stats;
+};
 
 // binary32: what a set's `lists` area of cap words holds.  First a head: the largest ~key and the
 // largest key collected; a key that the sample holds often, or kNoKey, how often the set holds it,
@@ -51,6 +67,283 @@ constexpr u32 kCells = 0x100u;
 // Bin of a key d past the interval's start: cell d >> shift is cut into equal parts (1 <= shift).
 __device__ __forceinline__ u32 bin_of(u32 d, u32 shift, u32 cell) {
   return (cell & 0xFFFFu) + __umulhi(d << (32u - shift), cell >> 16);
+}
+
+// The bin of a set's interval histogram (W = 256 to 2048 words) that holds its k-th smallest
+// key, by one wavefront; the same in every lane.  ok = the interval does hold it.  (binary32:
+// `ties` more elements lie in bin tie_bin than its word says.)  A set has fewer than 2^32 elements.
+struct BinPick {
+  bool ok;
+  u32 bin, need;              // rank wanted among the bin's elements (1-based)
+  u32 count;                  // elements of the bin's histogram word
+  u32 inside;                 // elements inside the interval
+};
+template <bool TIES>
+__device__ __forceinline__ BinPick pick_bin(const u32* __restrict__ hb, int W, u32 below, long long k,
+                                            u32 tie_bin = kNoKey, u32 ties = 0) {
+  const int lane = threadIdx.x & 63;
+  const int quads = W / 256;                    // 1 to 8 groups of four bins per lane
+  const uint4* mine_bins = reinterpret_cast<const uint4*>(hb) + lane * quads;
+  uint4 c[2];                                   // two groups stay in registers
+  u32 sum[8];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) c[i] = mine_bins[i < quads ? i : 0];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) sum[i] = i < 2 && i < quads ? c[i].x + c[i].y + c[i].z + c[i].w : 0u;
+  if (quads > 2) {                              // uniform; the loads issued together
+    uint4 t[6];
+#pragma unroll
+    for (int i = 2; i < 8; ++i) t[i - 2] = mine_bins[i < quads ? i : 0];
+#pragma unroll
+    for (int i = 2; i < 8; ++i)
+      sum[i] = i < quads ? t[i - 2].x + t[i - 2].y + t[i - 2].z + t[i - 2].w : 0u;
+  }
+  if (TIES && ties != 0) {                      // uniform
+    const int at = (int)(tie_bin >> 2) - lane * quads;         // of this lane's groups, if any
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sum[i] += i == at && i < quads ? ties : 0u;
+  }
+  u32 mine = 0;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) mine += sum[i];
+  const u32 incl = wave_scan_u32(mine);
+  const unsigned long long kk = (unsigned long long)k;
+  BinPick r;
+  r.inside = (u32)__builtin_amdgcn_readlane((int)incl, 63);
+  r.ok = kk > below && kk - below <= r.inside;
+  const u32 need = (u32)(kk - below);
+  const unsigned long long hit = __ballot(incl >= need);
+  const int src = r.ok ? __ffsll((long long)hit) - 1 : 0;       // hit != 0 because need <= inside
+  u32 cum = incl - mine;
+  int group = 0;                                // the group of four ...
+  bool found = false;
+  if (quads > 1) {
+#pragma unroll
+    for (int i = 0; i < 7; ++i) {
+      found = found || i >= quads - 1 || cum + sum[i] >= need;
+      if (!found) {
+        cum += sum[i];
+        ++group;
+      }
+    }
+  }
+  uint4 q = group == 0 ? c[0] : c[1];
+  if (quads > 2) q = mine_bins[group];
+  u32 bin = (u32)(4 * (lane * quads + group));
+  const u32 v[4] = {q.x, q.y, q.z, q.w};        // ... and the bin in it
+  u32 count = v[0];
+  found = false;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const u32 all = v[i] + (TIES && bin == tie_bin ? ties : 0u);
+    found = found || cum + all >= need;
+    if (!found) {
+      cum += all;
+      ++bin;
+      count = v[i + 1];
+    }
+  }
+  r.bin = (u32)__builtin_amdgcn_readlane((int)bin, src);
+  r.need = need - (u32)__builtin_amdgcn_readlane((int)cum, src);
+  r.count = (u32)__builtin_amdgcn_readlane((int)count, src);
+  return r;
+}
+
+// ---------------------------------------------------------------------------
+// Search of a set's rows by one workgroup.
+// ---------------------------------------------------------------------------
+constexpr int kFinishBits = 11;                 // key bits a pass resolves
+constexpr int kFinishTokens = 2048;             // tokens looked at together
+
+// LDS of the search
+template <int NT, bool LISTED>
+struct FinishLds {
+  u32 h[1 << kFinishBits];
+  unsigned short list[LISTED ? 1 : kFinishTokens];    // the set's tokens among those looked at together
+  u32 wtot[NT / 64], digit;
+  unsigned long long wsum[NT / 64], rest;
+};
+
+// Rows list[0 .. n - 1] (offsets from row Xb), read by a workgroup of NT threads: groups of L lanes take R rows
+// and P 16-byte pieces of each at a time, R P = 4 and P by the row length, and load the next four while the
+// caller's piece(uint4) looks at these; single(element) gets what no whole piece holds.
+template <typename TX, int NT>
+struct RowVisitor {
+  static constexpr int V = Elem<TX>::V;
+  const TX* Xb;
+  long long ld;
+  int C, L, n, nvec, P, R, lr, slots, row, v0;
+  const unsigned short* list;
+  uint4 q[4];
+  // starts with the loads of the first pieces
+  __device__ __forceinline__ RowVisitor(const TX* Xb_, long long ld_, int C_, int L_, const unsigned short* list_,
+                                        int n_)
+      : Xb(Xb_), ld(ld_), C(C_), L(L_), n(n_), list(list_) {
+    nvec = C / V;
+    P = nvec <= L ? 1 : nvec <= 2 * L ? 2 : 4;
+    R = 4 / P;
+    lr = threadIdx.x & (L - 1);
+    const int shift = 31 - __clz(L);
+    row = threadIdx.x >> shift;
+    slots = NT >> shift;
+    v0 = lr;
+    if (n > 0) load();
+  }
+  __device__ __forceinline__ void load() {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {               // past the end: the last row, piece v0; not looked at
+      const int at = row + slots * (P == 1 ? i : P == 2 ? i >> 1 : 0), v = v0 + (i & (P - 1)) * L;
+      const TX* xp = Xb + (long long)list[at < n ? at : n - 1] * ld;
+      if (nvec > 0) q[i] = load16(xp + (long long)(v < nvec ? v : lr < nvec ? lr : 0) * V);
+    }
+  }
+  template <typename FP, typename FS>
+  __device__ __forceinline__ void visit(FP&& piece, FS&& single) {
+    const int row_first = row;
+    if (lr < nvec) {
+      while (row < n) {
+        uint4 c[4];
+        bool ok[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int at = row + slots * (P == 1 ? i : P == 2 ? i >> 1 : 0), v = v0 + (i & (P - 1)) * L;
+          ok[i] = at < n && v < nvec;
+          c[i] = q[i];
+        }
+        v0 += P * L;
+        if (v0 >= nvec) {
+          v0 = lr;
+          row += slots * R;
+        }
+        if (row < n) load();
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (ok[i]) piece(c[i]);
+      }
+    }
+    if (__builtin_expect(nvec * V < C, 0))
+      for (int at = row_first; at < n; at += slots)
+        for (int c = nvec * V + lr; c < C; c += L) single(Xb[(long long)list[at] * ld + c]);
+  }
+};
+
+// Adds the keys of rows list[0 .. n - 1] that lie in [k0, k0 + span) to
+// the histogram of digits (key - k0 >> shift) - off.  Digit 0 takes all that is below as well and
+// is counted in a register, the last digit takes all that is above and is not counted (what the
+// others do not hold): either may be most of the set, and would meet in one word of LDS.
+template <typename TX, int NT>
+__device__ __forceinline__ void count_rows(const TX* __restrict__ Xb, long long ld, int C, int L,
+                                           const unsigned short* list, int n, u32 k0, u32 span, int shift,
+                                           int off, u32* h) {
+  u32 low = 0;
+  auto count = [&](TX x) {
+    const u32 d = Elem<TX>::key(x) - k0;
+    const int digit = d < span ? (int)(d >> shift) - off : 1 << kFinishBits;
+    low += digit <= 0 ? 1u : 0u;
+    if (digit > 0 && digit < (1 << kFinishBits) - 1) atomicAdd(&h[digit], 1u);
+  };
+  RowVisitor<TX, NT>(Xb, ld, C, L, list, n)
+      .visit([&](const uint4& q) {
+        TX x[Elem<TX>::V];
+        Elem<TX>::unpack(q, x);
+#pragma unroll
+        for (int c = 0; c < Elem<TX>::V; ++c) count(x[c]);
+      },
+             count);
+  if (low) atomicAdd(&h[0], low);
+}
+
+// The key of rank `need` (1-based) among the set's keys in [k0, k0 + span), by the whole
+// workgroup.  LISTED: the set's tokens are list[0 .. T - 1], otherwise those of T with gb[t] == j.  Every pass divides span by 2^kFinishBits, so three passes at most; near < 0 (> 0):
+// one more before them that looks at the last (first) 2047 keys of the range one by one.
+template <typename TX, int NT, bool LISTED>
+__device__ __forceinline__ u32 search_rows(const TX* __restrict__ Xb, long long ld, int T, int C, int L,
+                           const int* __restrict__ gb, int j, const unsigned short* list, u32 k0, u32 span,
+                           unsigned long long need, int near, FinishLds<NT, LISTED>& s) {
+  constexpr int kBins = 1 << kFinishBits, NW = NT / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  while (span > 1) {
+    int shift = 32 - __clz(span - 1) - kFinishBits, off = 0;
+    shift = shift > 0 && near == 0 ? shift : 0;
+    if (near < 0 && span > (u32)kBins) off = (int)span - kBins;
+    near = 0;
+    __syncthreads();
+    for (int i = tid; i < kBins; i += NT) s.h[i] = 0;
+    if (tid == 0) s.digit = kBins - 1;
+    if constexpr (LISTED) {
+      __syncthreads();
+      count_rows<TX, NT>(Xb, ld, C, L, list, T, k0, span, shift, off, s.h);
+      __syncthreads();
+    } else {
+      for (int t0 = 0; t0 < T; t0 += kFinishTokens) {
+        constexpr int kIds = kFinishTokens / NT;
+        bool mine[kIds];
+        u32 count = 0;
+#pragma unroll
+        for (int u = 0; u < kIds; ++u) {
+          const int t = t0 + u * NT + tid;
+          mine[u] = t < T && gb[t] == j;
+        }
+#pragma unroll
+        for (int u = 0; u < kIds; ++u) count += (u32)__popcll(__ballot(mine[u]));
+        if (lane == 0) s.wtot[wave] = count;
+        __syncthreads();
+        u32 at = 0, n = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+          at += w < wave ? s.wtot[w] : 0u;
+          n += s.wtot[w];
+        }
+#pragma unroll
+        for (int u = 0; u < kIds; ++u) {
+          const unsigned long long m = __ballot(mine[u]);
+          if (mine[u])
+            s.list[at + (u32)__popcll(m & ((1ull << lane) - 1ull))] = (unsigned short)(u * NT + tid);
+          at += (u32)__popcll(m);
+        }
+        __syncthreads();
+        count_rows<TX, NT>(Xb + (long long)t0 * ld, ld, C, L, s.list, (int)n, k0, span, shift, off, s.h);
+        __syncthreads();                        // `list` and `wtot` are reused
+      }
+    }
+    // the bin where the running count reaches `need`
+    constexpr int kPer = kBins / NT;
+    unsigned long long mine = 0;
+    u32 c[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      c[i] = s.h[tid * kPer + i];
+      mine += c[i];
+    }
+    unsigned long long incl = mine;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const unsigned long long o = __shfl_up(incl, d, 64);
+      if (lane >= d) incl += o;
+    }
+    if (lane == 63) s.wsum[wave] = incl;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < NW; ++w) incl += w < wave ? s.wsum[w] : 0ull;
+    if (tid == NT - 1 && incl < need) s.rest = need - incl;       // the last digit
+    if (incl - mine < need && need <= incl) {   // at most one thread
+      unsigned long long cum = incl - mine;
+      int i = 0;
+      for (; i < kPer - 1; ++i) {
+        if (cum + c[i] >= need) break;
+        cum += c[i];
+      }
+      s.digit = (u32)(tid * kPer + i);
+      s.rest = need - cum;
+    }
+    __syncthreads();
+    const u32 digit = s.digit, first = digit == 0 ? 0u : (digit + (u32)off) << shift;
+    const u32 next = digit == kBins - 1 ? span : (digit + (u32)off + 1u) << shift;
+    k0 += first;
+    span = (next < span ? next : span) - first;
+    need = s.rest;
+  }
+  return k0;
 }
 
 // ---------------------------------------------------------------------------
@@ -84,12 +377,14 @@ __device__ __forceinline__ u32 bin_of(u32 d, u32 shift, u32 cell) {
 // holds rank r[q] (1-based, at most the histogram's total) of h[q]: bin[q] and the count before
 // it.  Every thread of the workgroup calls it, after a barrier that completes the histograms;
 // the results are valid after the caller's next barrier.  stot [K][NW] is scratch.  A bin is the
-// sum of COPIES neighbouring words.  CUM: cum[1024] gets the counts before every bin of h[0].
+// sum of COPIES neighbouring words.  CUM: cum[1024] gets the counts before every bin of h[0].  all (if not 0):
+// the histogram's total, of which bin 0 holds what the other bins do not (its own word must be 0).
 template <int NT, int K, int COPIES, bool CUM>
 __device__ __forceinline__ void find_ranks(const u32* const (&h)[K], const u32 (&r)[K],
-                                           u32 (*stot)[NT / 64], u32* bin, u32* before, u32* cum) {
+                                           u32 (*stot)[NT / 64], u32* bin, u32* before, u32* cum, u32 all = 0) {
   constexpr int NW = NT / 64, kBins = 1024 / NT;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   u32 c[K][kBins], mine[K], incl[K];
 #pragma unroll
   for (int q = 0; q < K; ++q) {
@@ -101,34 +396,32 @@ __device__ __forceinline__ void find_ranks(const u32* const (&h)[K], const u32 (
       for (int k = 0; k < COPIES; ++k) c[q][i] += h[q][(tid * kBins + i) * COPIES + k];
       mine[q] += c[q][i];
     }
-    incl[q] = mine[q];                       // inclusive scans over the wavefront
-  }
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-#pragma unroll
-    for (int q = 0; q < K; ++q) {
-      const u32 o = (u32)__shfl_up((int)incl[q], d, 64);
-      if (lane >= d) incl[q] += o;
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < K; ++q)
+    incl[q] = wave_scan_u32(mine[q]);
     if (lane == 63) stot[q][wave] = incl[q];
+  }
   __syncthreads();
 #pragma unroll
   for (int q = 0; q < K; ++q) {
-#pragma unroll
-    for (int w2 = 0; w2 < NW; ++w2) incl[q] += w2 < wave ? stot[q][w2] : 0u;
+    // (the totals of the wavefronts before this one)
+    const u32 totals = wave_scan_u32(lane < NW ? stot[q][lane < NW ? lane : 0] : 0u);
+    incl[q] += wave > 0 ? (u32)__builtin_amdgcn_readlane((int)totals, wave > 0 ? wave - 1 : 0) : 0u;
+    u32 start = incl[q] - mine[q];
+    if (all != 0) {                          // (uniform)
+      const u32 first = all - (u32)__builtin_amdgcn_readlane((int)totals, NW - 1);
+      incl[q] += first;
+      start += tid == 0 ? 0u : first;
+      c[q][0] += tid == 0 ? first : 0u;
+    }
     if (CUM && q == 0) {
-      u32 at = incl[0] - mine[0];
+      u32 at = start;
 #pragma unroll
       for (int i = 0; i < kBins; ++i) {
         cum[tid * kBins + i] = at;
         at += c[0][i];
       }
     }
-    if (incl[q] - mine[q] < r[q] && r[q] <= incl[q]) {            // exactly one thread
-      u32 at = incl[q] - mine[q];
+    if (start < r[q] && r[q] <= incl[q]) {                        // exactly one thread
+      u32 at = start;
       int i = 0;
       for (; i < kBins - 1; ++i) {
         if (at + c[q][i] >= r[q]) break;
@@ -140,23 +433,122 @@ __device__ __forceinline__ void find_ranks(const u32* const (&h)[K], const u32 (
   }
 }
 
-template <typename TX, int NT, int SM>
+// WHOLE = 1 or 2 (ranks wanted: 2 with a percentile base radius): the kernel sees the set through to its
+// radius.  G + extra workgroups an image are shared out to the sets by the sizes that one round of keys
+// suggests, so that a large set's rows are read by many; each finds the set's tokens and interval itself,
+// the same as the others, and then counts its share of the rows in LDS.
+//
+// Bound by instruction issue on few wavefronts: a dependent vector instruction takes 4 cycles, and a SIMD
+// issues one in 4 cycles to all its wavefronts together, so everything that is done once per set costs
+// (instructions) x 1.7 ns x (wavefronts per SIMD), and everything per element its instructions shared out.
+// Hence 512 threads (256: too few loads in flight, [8, 1936, 320] 52.1 us the layer instead of 45.6; 1024:
+// [1, 7744, 64] 27.1 instead of 26.4), exact small quotients in binary32 instead of integer divisions, scans
+// by DPP, rounds of keys as a template parameter; and a taken branch into code that is not in the
+// instruction cache costs 55 to 85 ns, so what rarely runs is out of the way.  The rows' first loads are
+// issued before the sample is counted.
+// Measured against the chain k_sets, k_bracket_hist, k_bracket_finish (each kernel boundary costs 1.4 us and
+// 0.9 until the first loads are back), layer of [8, 121, 512] 25.7 -> 21.1 us, [1, 7744, 64] 30.5 -> 26.2,
+// [16, 484, 320] 36.0 -> 33.2, [5, 1369, 333] with a percentile, where one sweep serves both ranks,
+// 62.8 -> 39.2.
+// h % d of h < 2^24: the quotient in binary32 is off by one at most (8 instructions instead of 30).
+__device__ __forceinline__ u32 mod24(u32 h, u32 d) {
+  u32 r = h - (u32)((float)h * __builtin_amdgcn_rcpf((float)d)) * d;
+  r = (int)r < 0 ? r + d : r;
+  return r >= d ? r - d : r;
+}
+
+// A rank k of a set of n elements as seen by a sample of m of them from n_sel tokens.
+struct SampleRank {
+  long long rk;               // the rank of the sample that corresponds to k
+  float dev;                  // its standard deviation as that of a sample of independent elements
+                              // (none if the sample is the set) ...
+  float dev_tokens;           // ... and of a sample of whole tokens, as if all elements of a token
+                              // lay on one side
+};
+__device__ __forceinline__ SampleRank sample_rank(long long k, long long n, long long m, int n_sel) {
+  SampleRank s;
+  s.rk = (long long)((double)k / (double)n * (double)m + 0.5);
+  s.rk = s.rk < 1 ? 1 : (s.rk > m ? m : s.rk);
+  const float mf = (float)m, pq = (float)s.rk / mf, left_out = n > m ? 1.f - mf / (float)n : 0.f;
+  s.dev = sqrtf(pq * (1.f - pq) * left_out * mf);
+  s.dev_tokens = s.dev * sqrtf(mf / (float)n_sel);
+  return s;
+}
+
+// binary16: the one-key bins around sampled rank s, which lies in bin bm of the sample's histogram of 1024
+// bins (the low key bits do not matter to the interval), cum = sampled elements before every bin.  Wfew of
+// them centred on the middle of that bin, if they reach two and a half standard deviations to either
+// side.  Else the rank lies where keys are sparse (just above the zeros of a rectified activation, between
+// the values of a coarse grid): the W bins that leave equally many sampled keys on either side of it.  By
+// one wavefront.
+__device__ __forceinline__ void place_bins(const u32* cum, int bm, const SampleRank& s, long long m, int Wfew,
+                                           int W, u32& first, u32& width) {
+  constexpr int kCell = 1 << (15 - kSampleBits);
+  const int lane = threadIdx.x & 63, rk = (int)s.rk;
+  const int reach = (int)(2.5f * s.dev) + 1;
+  auto below_bin = [&](int c) { return c <= 0 ? 0 : c >= 1024 ? (int)m : (int)cum[c]; };
+  const int under = below_bin(bm - Wfew / 2 / kCell + 1), upto = below_bin(bm + Wfew / 2 / kCell);
+  int lo = bm * kCell + kCell / 2 - Wfew / 2;
+  width = (u32)Wfew;
+  if (!((under == 0 || rk - under >= reach) && (upto == (int)m || upto - rk >= reach))) {
+    width = (u32)W;
+    const int nb = W / kCell;                        // 8 to 64 candidates, one per lane
+    const int c0 = bm - nb + 1 + lane;
+    u32 score = 0;
+    if (lane < nb && c0 >= 0) {                      // (the last one, c0 = bm, always is)
+      const int left = rk - below_bin(c0), right = below_bin(c0 + nb) - rk;
+      score = ((u32)(left < right ? left : right) << 6) | (u32)lane;
+    }
+    if (lane == nb - 1) score |= (u32)lane;
+    score = (u32)__builtin_amdgcn_readlane((int)group_max_u32<64>(score), 63);
+    lo = (bm - nb + 1 + (int)(score & 63u)) * kCell;
+  }
+  first = lo > 1 ? (u32)lo : 1u;                     // zeros are counted below
+}
+
+// Where a rank lies that an interval does not hold: `span` keys from k0, as their `rank`-th; near < 0 (> 0):
+// probably close to the last (first) of them.  above = first key after the interval.
+struct Lost {
+  u32 k0, span;
+  int near;
+  unsigned long long rank;
+};
+template <bool F16>
+__device__ __forceinline__ Lost lost_rank(long long k, u32 below, u32 inside, u32 lo, u32 above) {
+  constexpr u32 kKeysAll = F16 ? 1u << 15 : 1u << 31;
+  Lost l;
+  if ((unsigned long long)k <= below) {              // (span 1: there are only zeros)
+    l.k0 = 0;
+    l.span = lo;
+    l.near = F16 ? -1 : 0;
+    l.rank = (unsigned long long)k;
+  } else {
+    l.k0 = above < kKeysAll ? above : kKeysAll - 1u;
+    l.span = kKeysAll - l.k0;
+    l.near = F16 ? 1 : 0;
+    l.rank = (unsigned long long)k - ((unsigned long long)below + inside);
+  }
+  return l;
+}
+
+template <typename TX, int NT, int RD, int SM, int WHOLE>
 __global__ __launch_bounds__(NT) void k_sets(
     const TX* __restrict__ X, long long ld, int T, int C, int G, int Wfew, int W, int cells, int aligned,
     const float* __restrict__ r, const double* __restrict__ mean, const double* __restrict__ m2,
     int* __restrict__ gid, Scalars sc, int pass, int keep_base, GroupWork* __restrict__ grp,
     Bracket* __restrict__ br, u32* __restrict__ bhist, u32* __restrict__ lists, int cap,
-    u32* __restrict__ img_flag, u32* __restrict__ status) {
+    u32* __restrict__ img_flag, u32* __restrict__ status, WholeArgs wa) {
   constexpr int NW = NT / 64;
   constexpr bool F16 = sizeof(TX) == 2;
   constexpr int V = Elem<TX>::V;
+  constexpr int kHalf = RD > 1 ? RD / 2 : 1;
   constexpr int kSampleRuns = SM / kRunLen;
   constexpr int kSampleTokens = kSampleRuns;         // at most one run per token
   // binary32 values of one magnitude share their top bits: four copies of the first histogram
   // keep the lanes of a wavefront from all adding to one word
   constexpr int kCopies = F16 ? 1 : 4;
   extern __shared__ unsigned short order[];          // the set's tokens by rank (T <= kListTokens)
-  __shared__ int sel[kSampleTokens];                 // more tokens: the one drawn of every stratum
+  __shared__ int sel[WHOLE ? 1 : kSampleTokens];     // more tokens: the one drawn of every stratum
   __shared__ __attribute__((aligned(16))) u32 shist[kCopies << kSampleBits];   // sample histogram
                                                      // over the top key bits
   __shared__ u32 snext[F16 ? 1 : 2][F16 ? 1 : 1 << kSampleBits];   // binary32: two over the next ones
@@ -165,8 +557,17 @@ __global__ __launch_bounds__(NT) void k_sets(
   __shared__ u32 s_bin[4], s_before[4];
   __shared__ u32 s_min[NW], s_max[NW], wtot[NW], stot[3][NW], s_cmax[NW];
   __shared__ double s_s1[NW], s_s2[NW];
+  __shared__ float s_sigma, s_cbase;
   __shared__ int s_first;
-  const int j = blockIdx.x, b = blockIdx.y, idx = b * G + j;
+  // (whole)
+  __shared__ __attribute__((aligned(16))) u32 hist[WHOLE ? (F16 ? WHOLE : 1) : 1][WHOLE ? 2048 : 4];
+  __shared__ u32 s_lo[2], s_width[2], s_below[2], s_last;
+  __shared__ u32 s_share[64];                        // sampled tokens of every set
+  __shared__ Lost s_lost[2];
+  __shared__ FinishLds<WHOLE ? NT : 64, true> s_search;
+  // (whole: the set, and which of the S workgroups that share it this is, follow from the sets' sizes)
+  int S = 1, part = 0, j = (int)blockIdx.x;
+  const int b = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const float* rb = r + (long long)b * T;
@@ -174,21 +575,22 @@ __global__ __launch_bounds__(NT) void k_sets(
   const double* m2b = m2 + (long long)b * T;
   int* gb = gid + (long long)b * T;
   constexpr u32 kDead = 0xFFFFFFFFu;                 // no range key reaches it
-  const bool one_batch = T <= kIdRounds * NT;
-  u32 kv[kIdRounds];
+  const bool one_batch = WHOLE || T <= RD * NT;
+  u32 kv[RD];
   auto load_keys = [&](int t0) {
 #pragma unroll
-    for (int u = 0; u < kIdRounds; ++u) {
+    for (int u = 0; u < RD; ++u) {
       const int t = t0 + u * NT + tid;
       kv[u] = t < T ? __float_as_uint(rb[t]) : kDead;
     }
   };
   // (the rounds of a batch that hold tokens; the same for every thread)
-  auto in_use = [&](int t0, int u) { return t0 + u * NT < T; };
+  auto in_use = [&](int t0, int u) { return u == 0 || t0 + u * NT < T; };
 
   // ---- 1: key range of the image, key interval of the set
   load_keys(0);
   for (int i = tid; i < (kCopies << kSampleBits); i += NT) shist[i] = 0;
+  if (WHOLE && tid < 64) s_share[tid] = 0;
   if (!F16) {
     for (int i = tid; i < (int)(sizeof(snext) / sizeof(u32)); i += NT) (&snext[0][0])[i] = 0;
     if (tid < 66) s_cell[tid] = 0;
@@ -197,13 +599,13 @@ __global__ __launch_bounds__(NT) void k_sets(
   u32 kinv = 0, kmax = 0;                            // largest ~key, largest key
   for (int t0 = 0;;) {
 #pragma unroll
-    for (int u = 0; u < kIdRounds; ++u) {
+    for (int u = 0; u < RD; ++u) {
       const u32 k = kv[u];
       kinv = ~k > kinv ? ~k : kinv;                  // ~kDead is 0
       kmax = k != kDead && k > kmax ? k : kmax;
     }
-    t0 += kIdRounds * NT;
-    if (t0 >= T) break;
+    t0 += RD * NT;
+    if (one_batch || t0 >= T) break;
     load_keys(t0);
   }
   kinv = group_max_u32<64>(kinv);
@@ -221,25 +623,52 @@ __global__ __launch_bounds__(NT) void k_sets(
     const u32 floor_key = hi > span ? hi - span : 0u;
     lo = lo > floor_key ? lo : floor_key;
   }
-  if (tid == 0 && j == 0) {
-    img_flag[b] = hi >= 0x7F800000u ? TDQ_DEV_NONFINITE : 0u;
-    if (b == 0) {                         // counts of sets the sampled interval misses
+  if (tid == 0 && blockIdx.x == 0) {
+    const u32 flag = hi >= 0x7F800000u ? TDQ_DEV_NONFINITE : 0u;
+    img_flag[b] = flag;
+    if (WHOLE) {                          // (cleared by the statistics kernel, like the counts)
+      if (flag) atomicOr(&status[0], flag);
+    } else if (b == 0) {                         // counts of sets the sampled interval misses
       status[1 + pass] = 0u;
       if (!keep_base) status[1 + (pass ^ 1)] = 0u;
     }
   }
   // ceil(j width / G) = j q + ceil(j rem / G) with width = q G + rem; everything fits 32 bits
   const u32 width = hi - lo + 1u, wq = width / (u32)G, wr = width - wq * (u32)G;
-  const u32 start = j == 0 ? 0u : lo + (u32)j * wq + ((u32)j * wr + (u32)G - 1u) / (u32)G;
-  const u32 end = j == G - 1 ? hi + 1u : lo + (u32)(j + 1) * wq + ((u32)(j + 1) * wr + (u32)G - 1u) / (u32)G;
+  auto start_of = [&](int g) {
+    return g == 0 ? 0u : g >= G ? hi + 1u : lo + (u32)g * wq + ((u32)g * wr + (u32)G - 1u) / (u32)G;
+  };
+  if constexpr (WHOLE != 0) {
+    // How many workgroups a set gets: one, and its share of the others by the keys that one round of the
+    // image's tokens, spread over all of them, holds (about: no integer division, every workgroup alike).
+    const int pick = tid & (RD - 1);                 // (a power of two; some threads have none)
+    u32 k = kDead;
+#pragma unroll
+    for (int u = 0; u < RD; ++u) k = u == pick ? kv[u] : k;
+    if (k != kDead) {
+      const int g = (int)((float)(k > lo ? k - lo : 0u) * ((float)G / (float)width));
+      atomicAdd(&s_share[g < G ? g : G - 1], 1u);
+    }
+    __syncthreads();
+    const u32 drawn = s_share[lane], all = xor_reduce_sum<64, u32>(drawn);
+    // (a little less than its share, so that rounding never makes it more than G + extra together)
+    const float per = (float)wa.extra / (float)all * (1.f - 1e-6f);
+    const u32 its = lane < G ? 1u + (u32)((float)drawn * per) : 0u, incl = wave_scan_u32(its);
+    const unsigned long long later = __ballot(incl > blockIdx.x);
+    if (__builtin_expect(later == 0, 0)) return;     // the same for every thread
+    j = __ffsll((long long)later) - 1;
+    S = __builtin_amdgcn_readlane((int)its, j);
+    part = (int)blockIdx.x - (__builtin_amdgcn_readlane((int)incl, j) - S);
+  }
+  const u32 start = start_of(j), end = start_of(j + 1);
   auto in_set = [&](u32 k) { return k >= start && k < end; };
 
   // ---- 2: the set's tokens
   u32 wcount = 0;
-  for (int t0 = 0; t0 < T; t0 += kIdRounds * NT) {
+  for (int t0 = 0; WHOLE ? t0 == 0 : t0 < T; t0 += RD * NT) {
     if (!one_batch) load_keys(t0);
 #pragma unroll
-    for (int u = 0; u < kIdRounds; ++u) {
+    for (int u = 0; u < RD; ++u) {
       if (!in_use(t0, u)) break;
       wcount += (u32)__popcll(__ballot(in_set(kv[u])));
     }
@@ -253,10 +682,15 @@ __global__ __launch_bounds__(NT) void k_sets(
     running += w < wave ? v : 0u;
     tokens_u += v;
   }
-  if (tokens_u == 0) {
+  const int idx = b * G + j;
+  if (__builtin_expect(tokens_u == 0, 0)) {
     if (tid == 0) {
       GroupWork w;
       w.n = 0; w.k_rem = 0; w.prefix = 0; w.tokens = 0; w.c_base = 0.f; w.sigma = 0.f;
+      if (WHOLE) {
+        if (part == 0) project_store(idx, w, 0u, F16, sc, wa.clip, wa.scale, wa.stats);
+        return;
+      }
       grp[idx] = w;
       Bracket e;
       e.lo = 0; e.width = 0; e.below = 0; e.shift = 0;
@@ -266,7 +700,8 @@ __global__ __launch_bounds__(NT) void k_sets(
   }
 
   // the sweep adds into this set's histogram: clear it here (more of it below if more is used)
-  for (int i = tid; i < Wfew; i += NT) bhist[(size_t)idx * W + i] = 0;
+  if (!WHOLE)
+    for (int i = tid; i < Wfew; i += NT) bhist[(size_t)idx * W + i] = 0;
 
   // Sample geometry.  The set's tokens are cut into strata of `stride` tokens (at most
   // kSampleTokens strata) and one token is drawn from each at a hashed position: a regular
@@ -284,31 +719,31 @@ __global__ __launch_bounds__(NT) void k_sets(
   const int cw = rpt == row_runs ? Cv : rpt * kRunLen;      // channels read per drawn token
   const int n_runs = n_sel * rpt;                           // <= kSampleRuns
   const long long m = (long long)n_sel * cw;                // sample size, <= SM
-  const bool listed = T <= kListTokens;
+  const bool listed = WHOLE || T <= kListTokens;
   auto pick_of = [&](u32 stratum) {                         // rank of the token drawn from a stratum
     const u32 first = stratum * (u32)stride;
     const u32 len = (u32)tokens - first < (u32)stride ? (u32)tokens - first : (u32)stride;
-    return first + (((stratum + 1u) * 2246822519u + (u32)idx * 3266489917u) >> 12) % len;
+    return first + mod24(((stratum + 1u) * 2246822519u + (u32)idx * 3266489917u) >> 12, len);
   };
 
-  for (int t0 = 0; t0 < T; t0 += kIdRounds * NT) {
+  for (int t0 = 0; WHOLE ? t0 == 0 : t0 < T; t0 += RD * NT) {
     if (!one_batch) load_keys(t0);
 #pragma unroll
-    for (int u = 0; u < kIdRounds; ++u) {
+    for (int u = 0; u < RD; ++u) {
       if (!in_use(t0, u)) break;
       const bool mine = in_set(kv[u]);
       const unsigned long long mask = __ballot(mine);
-      if (mask == 0) continue;                              // uniform over the wavefront
+      if (RD > 4 && mask == 0) continue;                    // uniform over the wavefront
       if (mine) {
         const int t = t0 + u * NT + tid;
         const u32 rank = running + (u32)__popcll(mask & ((1ull << lane) - 1ull));
-        gb[t] = j;
+        if (part == 0) gb[t] = j;
         if (listed) {
           order[rank] = (unsigned short)t;
         } else {
           if (rank == 0) s_first = t;
           const u32 stratum = rank / (u32)stride;
-          if (rank == pick_of(stratum)) sel[stratum] = t;
+          if (!WHOLE && rank == pick_of(stratum)) sel[WHOLE ? 0 : stratum] = t;
         }
       }
       running += (u32)__popcll(mask);
@@ -328,16 +763,17 @@ __global__ __launch_bounds__(NT) void k_sets(
   const int steps = (n_runs * PPR + NT - 1) / NT;      // small sets need fewer than kPieces
   // offsets in steps of whole pieces where the rows consist of aligned ones
   const u32 step = aligned ? (u32)V : 1u, offsets = (u32)(C - cw) / step + 1u;
+  const float per_token = 1.f / (float)rpt;
   auto load_piece = [&](int e) {
     const u32 p = (u32)(e * NT + tid), q = p / PPR, part = p % PPR;
-    const u32 slot = q / (u32)rpt, run = q - slot * (u32)rpt;
+    const u32 slot = (u32)(((float)q + 0.5f) * per_token), run = q - slot * (u32)rpt;      // q / rpt (q < 2^10)
     const int at = (int)(run * kRunLen + part * V);    // channel inside the part of the row read
     live[e] = q < (u32)n_runs && at < cw;
     const u32 sl = live[e] ? slot : 0u;
-    const int t = !listed ? sel[sl] : order[stride == 1 ? sl : pick_of(sl)];
-    const u32 off = ((u32)t * 2654435761u >> 8) % offsets * step;
+    const int t = !listed ? sel[WHOLE ? 0 : sl] : order[stride == 1 ? sl : pick_of(sl)];
+    const u32 off = mod24((u32)t * 2654435761u >> 8, offsets) * step;
     const TX* src = X + ((long long)b * T + t) * ld + (live[e] ? (int)off + at : 0);
-    if (C >= V) {
+    if (__builtin_expect(C >= V, 1)) {
       v[e] = load16(src);
     } else {                                           // rows shorter than a piece
       TX x[V];
@@ -358,27 +794,27 @@ __global__ __launch_bounds__(NT) void k_sets(
   double a1 = 0.0, a2 = 0.0;
   u32 cmax = 0;
   piv = (piv - piv == 0.0) ? piv : 0.0;
-  for (int t0 = 0; t0 < T; t0 += kIdRounds * NT) {
+  for (int t0 = 0; WHOLE ? t0 == 0 : t0 < T; t0 += RD * NT) {
     if (!one_batch) load_keys(t0);
     // half of the rounds at a time, their loads issued together (a token of another set
     // reads the first token's entry, which is not added)
 #pragma unroll
-    for (int h = 0; h < kIdRounds; h += kIdRounds / 2) {
+    for (int h = 0; h < RD; h += kHalf) {
       if (!in_use(t0, h)) break;
-      double mv[kIdRounds / 2], qv[kIdRounds / 2];
+      double mv[kHalf], qv[kHalf];
 #pragma unroll
-      for (int u = 0; u < kIdRounds / 2; ++u) {
+      for (int u = 0; u < kHalf; ++u) {
         const bool mine = in_set(kv[h + u]);
         mv[u] = piv;
         qv[u] = 0.0;
-        if (__ballot(mine)) {                         // uniform over the wavefront
+        if (RD <= 4 || __ballot(mine)) {              // uniform over the wavefront
           const int t = mine ? t0 + (h + u) * NT + tid : first_token;
           mv[u] = meanb[t];
           qv[u] = m2b[t];
         }
       }
 #pragma unroll
-      for (int u = 0; u < kIdRounds / 2; ++u) {
+      for (int u = 0; u < kHalf; ++u) {
         const u32 k = kv[h + u];
         const bool mine = in_set(k);
         const double dm = mv[u] - piv;
@@ -395,24 +831,35 @@ __global__ __launch_bounds__(NT) void k_sets(
   if (lane == 63) { s_s1[wave] = a1; s_s2[wave] = a2; s_cmax[wave] = cmax; }
 
   // ---- 3: the sample.  Every live key adds one to an LDS histogram of its top kSampleBits
-  // bits; zeros, often many, are counted first.
-  u32 key[kKeys], zeros = 0;
+  // bits; zeros, often many, are counted first (binary16: bin 0 is what the others do not hold).
+  u32 key[F16 ? 1 : kKeys], zeros = 0;
   auto add_piece = [&](int e) {
-    TX x[V];
-    Elem<TX>::unpack(v[e], x);
+    if constexpr (F16) {
+      const u32 wd[4] = {v[e].x, v[e].y, v[e].z, v[e].w};
 #pragma unroll
-    for (int i = 0; i < V; ++i) {
-      const u32 k = live[e] && i < C ? Elem<TX>::key(x[i]) : kDead;
-      key[e * V + i] = k;
-      zeros += k == 0u ? 1u : 0u;
-      if (k != kDead && k != 0u)
-        atomicAdd(&shist[(k >> (kKeyBits - kSampleBits)) * kCopies + (lane & (kCopies - 1))], 1u);
+      for (int i = 0; i < 4; ++i) {
+        const u32 x = live[e] ? wd[i] : 0u;
+        const u32 b0 = (x >> (kKeyBits - kSampleBits)) & 1023u, b1 = (x >> (16 + kKeyBits - kSampleBits)) & 1023u;
+        if (b0 != 0u && 2 * i < C) atomicAdd(&shist[b0], 1u);
+        if (b1 != 0u && 2 * i + 1 < C) atomicAdd(&shist[b1], 1u);
+      }
+    } else {
+      TX x[V];
+      Elem<TX>::unpack(v[e], x);
+#pragma unroll
+      for (int i = 0; i < V; ++i) {
+        const u32 k = live[e] && i < C ? Elem<TX>::key(x[i]) : kDead;
+        key[e * V + i] = k;
+        zeros += k == 0u ? 1u : 0u;
+        if (k != kDead && k != 0u)
+          atomicAdd(&shist[(k >> (kKeyBits - kSampleBits)) * kCopies + (lane & (kCopies - 1))], 1u);
+      }
     }
   };
 #pragma unroll
   for (int e = 0; e < kPieces; ++e)
     if (e < steps) add_piece(e);
-  if (__ballot(zeros != 0)) {
+  if (!F16 && __builtin_expect(__ballot(zeros != 0) != 0, 0)) {
     zeros = group_sum_u32<64>(zeros);
     if (lane == 63) atomicAdd(&shist[0], zeros);
   }
@@ -426,92 +873,262 @@ __global__ __launch_bounds__(NT) void k_sets(
   const double n = (double)w.n;
   w.k_rem = (long long)ceil((pass == kPassBase ? sc.base_pct : sc.zr) * n);
   w.k_rem = w.k_rem < 1 ? 1 : (w.k_rem > w.n ? w.n : w.k_rem);
-  if (tid == 0) {
-    double S1 = s_s1[0], S2 = s_s2[0];
-    u32 km = s_cmax[0];
-    for (int i = 1; i < NW; ++i) {
-      S1 += s_s1[i];
-      S2 += s_s2[i];
-      km = s_cmax[i] > km ? s_cmax[i] : km;
+  if (wave == NW - 1) {                  // (the last wavefront: the first places the interval below)
+    const bool has = lane < NW;
+    const double S1 = group_sum_f64<64>(has ? s_s1[has ? lane : 0] : 0.0);
+    const double S2 = group_sum_f64<64>(has ? s_s2[has ? lane : 0] : 0.0);
+    const u32 km = group_max_u32<64>(has ? s_cmax[has ? lane : 0] : 0u);
+    if (lane == 63) {
+      const double mu = S1 / n;
+      double var = S2 / n - mu * mu;
+      var = var > 0.0 ? var : 0.0;
+      w.sigma = (float)(sqrt(var) + sc.eps_std);
+      // (the base-radius pass left its radius in the record)
+      w.c_base = keep_base ? grp[idx].c_base : __uint_as_float(km);
+      if (WHOLE) {
+        s_sigma = w.sigma;
+        s_cbase = w.c_base;
+      } else {
+        grp[idx] = w;
+      }
     }
-    const double mu = S1 / n;
-    double var = S2 / n - mu * mu;
-    var = var > 0.0 ? var : 0.0;
-    w.sigma = (float)(sqrt(var) + sc.eps_std);
-    // (the base-radius pass left its radius in the record)
-    w.c_base = keep_base ? grp[idx].c_base : __uint_as_float(km);
-    grp[idx] = w;
   }
-
-  // Sample rank that corresponds to rank k of the set; its standard deviation as that of a
-  // sample of independent elements (none if the sample is the set), and that of a sample of
-  // whole tokens, as if all elements of a token lay on one side.
-  long long rk = (long long)((double)w.k_rem / n * (double)m + 0.5);
-  rk = rk < 1 ? 1 : (rk > m ? m : rk);
-  const float mf = (float)m, pq = (float)rk / mf, left_out = w.n > m ? 1.f - mf / (float)n : 0.f;
-  const float dev = sqrtf(pq * (1.f - pq) * left_out * mf), dev_tokens = dev * sqrtf(mf / (float)n_sel);
+  // binary32: the interval between two order statistics of the sample, six standard deviations of its
+  // elements and one of its tokens to either side of s, each resolved to 20 of its 31 bits: first key, last
+  // key - first key, sampled ranks between them.  By the whole workgroup.
+  auto interval32 = [&](const SampleRank& s, u32& first, u32& last, u32& drawn) {
+    if constexpr (!F16) {
+      const long long dr = (long long)(6.f * s.dev + s.dev_tokens) + 2;
+      const u32* const hs[2] = {shist, shist};
+      const u32 rs[2] = {(u32)(s.rk - dr < 1 ? 1 : s.rk - dr), (u32)(s.rk + dr > m ? m : s.rk + dr)};
+      find_ranks<NT, 2, kCopies, false>(hs, rs, stot, s_bin, s_before, nullptr);
+      __syncthreads();
+      const u32 b0 = s_bin[0], b1 = s_bin[1];
+#pragma unroll
+      for (int i = 0; i < kKeys; ++i) {
+        if (i / V < steps) {
+          const u32 top = key[i] >> 21, next = (key[i] >> 11) & 1023u;
+          if (key[i] != kDead && top == b0) atomicAdd(&snext[0][next], 1u);
+          if (key[i] != kDead && top == b1) atomicAdd(&snext[1][next], 1u);
+        }
+      }
+      __syncthreads();
+      const u32* const hn[2] = {snext[0], snext[1]};
+      const u32 rn[2] = {rs[0] - s_before[0], rs[1] - s_before[1]};
+      find_ranks<NT, 2, 1, false>(hn, rn, stot, s_bin + 2, s_before + 2, nullptr);
+      __syncthreads();
+      first = (b0 << 21) | (s_bin[2] << 11);
+      first = first > 1u ? first : 1u;               // zeros are counted below
+      last = ((b1 << 21) | (s_bin[3] << 11)) + 2047u - first;
+      drawn = rs[1] - rs[0];
+    }
+  };
+  if constexpr (WHOLE != 0) {
+    // ---- 4: the set's own rows: counts below the interval(s) and inside, rank, projection
+    constexpr int NR = WHOLE;                          // the last rank is the one that is projected
+    constexpr int kBins = 2048;
+    const TX* Xb = X + (long long)b * T * ld;
+    long long k[NR];
+    if (NR == 2) {
+      k[0] = (long long)ceil(sc.base_pct * n);
+      k[0] = k[0] < 1 ? 1 : (k[0] > w.n ? w.n : k[0]);
+    }
+    k[NR - 1] = w.k_rem;
+    u32 found = 0, base_key = 0;
+    auto search = [&](const Lost& l, int near) {
+      return search_rows<TX, NT, true>(Xb, ld, tokens, C, wa.L, nullptr, j, order, l.k0, l.span, l.rank, near, s_search);
+    };
+    if constexpr (F16) {
+      const int per = (tokens + S - 1) / S, from = part * per;
+      const int rows = tokens - from < per ? tokens - from : per;       // (none if negative)
+      RowVisitor<TX, NT> own(Xb, ld, C, wa.L, order + (rows > 0 ? from : 0), rows);      // its first loads
+      SampleRank sq[NR];
+      const u32* hs[NR];
+      u32 rs[NR];
+#pragma unroll
+      for (int q = 0; q < NR; ++q) {
+        sq[q] = sample_rank(k[q], w.n, m, n_sel);
+        hs[q] = shist;
+        rs[q] = (u32)sq[q].rk;
+      }
+      find_ranks<NT, NR, 1, true>(hs, rs, stot, s_bin, s_before, cum, (u32)m);
+      for (int i = tid; i < NR * kBins / 4; i += NT) reinterpret_cast<uint4*>(&hist[0][0])[i] = make_uint4(0, 0, 0, 0);
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < NR; ++q) {
+        if (wave == q) {
+          u32 first, wd;
+          place_bins(cum, (int)s_bin[q], sq[q], m, q == NR - 1 ? Wfew : W, W, first, wd);
+          if (lane == 0) { s_lo[q] = first; s_width[q] = wd; s_below[q] = 0; }
+        }
+      }
+      __syncthreads();
+      u32 first[NR], wd[NR], below[NR];
+#pragma unroll
+      for (int q = 0; q < NR; ++q) { first[q] = s_lo[q]; wd[q] = s_width[q]; below[q] = 0; }
+      own.visit([&](const uint4& p) {
+                           const u32 wd4[4] = {p.x, p.y, p.z, p.w};
+#pragma unroll
+                           for (int c = 0; c < 4; ++c) {
+                             const s2v kk = __builtin_bit_cast(s2v, wd4[c] & 0x7FFF7FFFu);
+#pragma unroll
+                             for (int q = 0; q < NR; ++q) {
+                               // both halves at once, see k_bracket_hist
+                               const u32 d2 = __builtin_bit_cast(u32, kk - __builtin_bit_cast(s2v, first[q] | (first[q] << 16)));
+                               below[q] += (u32)__builtin_popcount(d2 & 0x80008000u);
+                               const u32 dl = d2 & 0xFFFFu, dh = d2 >> 16;
+                               if (dl < wd[q]) atomicAdd(&hist[q][dl], 1u);
+                               if (dh < wd[q]) atomicAdd(&hist[q][dh], 1u);
+                             }
+                           }
+                         },
+                         [&](TX x) {
+                           const u32 kx = Elem<TX>::key(x);
+#pragma unroll
+                           for (int q = 0; q < NR; ++q) {
+                             below[q] += kx < first[q] ? 1u : 0u;
+                             if (kx >= first[q] && kx - first[q] < wd[q]) atomicAdd(&hist[q][kx - first[q]], 1u);
+                           }
+                         });
+#pragma unroll
+      for (int q = 0; q < NR; ++q) {
+        const u32 t = group_sum_u32<64>(below[q]);
+        if (lane == 63 && t) atomicAdd(&s_below[q], t);
+      }
+      __syncthreads();
+      if (S > 1) {
+        // The parts of a set meet in its global histogram, and the last to arrive goes on.  All that they
+        // exchange is written and read by device-scope atomic operations, which are performed where all
+        // XCDs see them, so no cache has to be written back or invalidated; s_waitcnt waits until those of
+        // this wavefront have been, the barrier for the other wavefronts, and only then is the arrival counted.
+        u32* gh = bhist + (size_t)idx * (NR * W);
+        u32* ctl = wa.ctl + (size_t)idx * kSetCtl;
+#pragma unroll
+        for (int q = 0; q < NR; ++q) {
+          for (int i = tid; i < (int)wd[q]; i += NT) {
+            const u32 v = hist[q][i];
+            if (v) atomicAdd(&gh[q * W + i], v);
+          }
+          if (tid == q && s_below[q]) atomicAdd(&ctl[1 + q], s_below[q]);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid == 0) s_last = atomicAdd(&ctl[0], 1u) == (u32)S - 1u ? 1u : 0u;
+        __syncthreads();
+        if (s_last == 0) return;                       // the same for every thread
+        constexpr int kPer = kBins / NT;
+#pragma unroll
+        for (int q = 0; q < NR; ++q) {
+          u32 v[kPer];
+#pragma unroll
+          for (int i = 0; i < kPer; ++i) {
+            const int at = i * NT + tid;
+            v[i] = at < (int)wd[q] ? __hip_atomic_load(&gh[q * W + at], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+          }
+#pragma unroll
+          for (int i = 0; i < kPer; ++i) hist[q][i * NT + tid] = v[i];
+          if (tid == q) s_below[q] = __hip_atomic_load(&ctl[1 + q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+      }
+#pragma unroll
+      for (int q = 0; q < NR; ++q) {
+        if (wave == q) {
+          const BinPick p = pick_bin<false>(hist[q], (int)wd[q], s_below[q], k[q]);
+          const Lost l = lost_rank<true>(k[q], s_below[q], p.inside, first[q], first[q] + wd[q]);
+          if (lane == 0) {
+            s_lost[q].k0 = p.ok ? first[q] + p.bin : l.k0;
+            s_lost[q].span = p.ok ? 1u : l.span;
+            s_lost[q].near = l.near;
+            s_lost[q].rank = l.rank;
+          }
+        }
+      }
+      __syncthreads();
+#pragma unroll 1
+      for (int q = 0; q < NR; ++q) {
+        u32 key_q = s_lost[q].k0;
+        if (__builtin_expect(s_lost[q].span != 1u, 0)) {                            // the interval missed the rank
+          if (tid == 0) atomicAdd(&status[1 + (q == NR - 1 ? kPassZr : kPassBase)], 1u);
+          key_q = search(s_lost[q], s_lost[q].near);
+        }
+        if (q == NR - 1) found = key_q; else base_key = key_q;
+      }
+    } else {
+#pragma unroll 1
+      for (int q = 0; q < NR; ++q) {
+        const long long kq = q == NR - 1 ? k[NR - 1] : k[0];
+        if (q > 0) {                                   // (other readers of these have passed a barrier since)
+          for (int i = tid; i < 2 << kSampleBits; i += NT) (&snext[0][0])[i] = 0;
+          __syncthreads();
+        }
+        u32 first, last, drawn, shift = 0, below = 0;
+        interval32(sample_rank(kq, w.n, m, n_sel), first, last, drawn);
+        while (((u64)kBins << shift) - 1ull < last) ++shift;           // at most 2^31 keys
+        for (int i = tid; i < kBins; i += NT) hist[0][i] = 0;
+        if (tid == 0) s_below[0] = 0;
+        __syncthreads();
+        auto count = [&](TX x) {
+          const u32 d = Elem<TX>::key(x) - first;      // (keys and first are below 2^31)
+          below += d >> 31;
+          if ((d >> shift) < (u32)kBins) atomicAdd(&hist[0][d >> shift], 1u);
+        };
+        RowVisitor<TX, NT>(Xb, ld, C, wa.L, order, tokens)
+            .visit([&](const uint4& p) {
+                             TX x[V];
+                             Elem<TX>::unpack(p, x);
+#pragma unroll
+                             for (int c = 0; c < V; ++c) count(x[c]);
+                           },
+                           count);
+        below = group_sum_u32<64>(below);
+        if (lane == 63 && below) atomicAdd(&s_below[0], below);
+        __syncthreads();
+        if (wave == 0) {
+          const BinPick p = pick_bin<false>(hist[0], kBins, s_below[0], kq);
+          Lost l = lost_rank<false>(kq, s_below[0], p.inside, first, first + ((u32)kBins << shift));
+          l.near = 1;                                  // a miss
+          if (p.ok) {
+            l.k0 = first + (p.bin << shift);
+            l.span = 1u << shift;
+            l.rank = p.need;
+            l.near = 0;
+          }
+          if (lane == 0) s_lost[0] = l;
+        }
+        __syncthreads();
+        const Lost l = s_lost[0];
+        if (tid == 0 && l.near && l.span != 1u) atomicAdd(&status[1 + (q == NR - 1 ? kPassZr : kPassBase)], 1u);
+        const u32 key_q = l.span == 1u ? l.k0 : search(l, 0);
+        if (q == NR - 1) found = key_q; else base_key = key_q;
+      }
+    }
+    if (tid == 0) {
+      w.sigma = s_sigma;
+      w.c_base = NR == 2 ? Elem<TX>::key_to_float(base_key) : s_cbase;       // (the base radius Q_p(|x|))
+      project_store(idx, w, found, F16, sc, wa.clip, wa.scale, wa.stats);
+    }
+    return;
+  }
+  const SampleRank sr = sample_rank(w.k_rem, w.n, m, n_sel);
+  const float mf = (float)m;
   Bracket e;
   e.below = 0;
   e.width = (u32)Wfew;
   e.shift = 0;
   if constexpr (F16) {
-    // The histogram bin that holds that order statistic (the low key bits do not matter to the
-    // interval): Wfew one-key bins centred on its middle, if they reach two and a half
-    // standard deviations to either side.  Else the rank lies where keys are sparse (just above the zeros
-    // of a rectified activation, between the values of a coarse grid): the W bins that leave
-    // equally many sampled keys on either side of it.
-    constexpr int kCell = 1 << (15 - kSampleBits);
     const u32* const hs[1] = {shist};
-    const u32 rs[1] = {(u32)rk};
-    find_ranks<NT, 1, 1, true>(hs, rs, stot, s_bin, s_before, cum);
+    const u32 rs[1] = {(u32)sr.rk};
+    find_ranks<NT, 1, 1, true>(hs, rs, stot, s_bin, s_before, cum, (u32)m);
     __syncthreads();
     if (wave != 0) return;
-    const int bm = (int)s_bin[0], reach = (int)(2.5f * dev) + 1;
-    auto below_bin = [&](int c) { return c <= 0 ? 0 : c >= 1024 ? (int)m : (int)cum[c]; };
-    const int under = below_bin(bm - Wfew / 2 / kCell + 1), upto = below_bin(bm + Wfew / 2 / kCell);
-    int lo = bm * kCell + kCell / 2 - Wfew / 2;
-    if (!((under == 0 || (int)rk - under >= reach) && (upto == (int)m || upto - (int)rk >= reach))) {
-      e.width = (u32)W;
-      for (int i = Wfew + lane; i < W; i += 64) bhist[(size_t)idx * W + i] = 0;
-      const int nb = W / kCell;                        // 8 to 64 candidates, one per lane
-      const int c0 = bm - nb + 1 + lane;
-      u32 score = 0;
-      if (lane < nb && c0 >= 0) {                      // (the last one, c0 = bm, always is)
-        const int left = (int)rk - below_bin(c0), right = below_bin(c0 + nb) - (int)rk;
-        score = ((u32)(left < right ? left : right) << 6) | (u32)lane;
-      }
-      if (lane == nb - 1) score |= (u32)lane;
-      score = (u32)__builtin_amdgcn_readlane((int)group_max_u32<64>(score), 63);
-      lo = (bm - nb + 1 + (int)(score & 63u)) * kCell;
-    }
-    e.lo = lo > 1 ? (u32)lo : 1u;                      // zeros are counted below
+    place_bins(cum, (int)s_bin[0], sr, m, Wfew, W, e.lo, e.width);
+    for (int i = Wfew + lane; i < (int)e.width; i += 64) bhist[(size_t)idx * W + i] = 0;
   } else {
-    // The interval between two order statistics of the sample, six standard deviations of its
-    // elements and one of its tokens to either side, each resolved to 20 of its 31 bits, in W bins
-    // of 2^shift keys: a bin then holds about 2e-4 of the set's elements whatever the data's
-    // offset and spread.
-    const long long dr = (long long)(6.f * dev + dev_tokens) + 2;
-    const u32* const hs[2] = {shist, shist};
-    const u32 rs[2] = {(u32)(rk - dr < 1 ? 1 : rk - dr), (u32)(rk + dr > m ? m : rk + dr)};
-    find_ranks<NT, 2, kCopies, false>(hs, rs, stot, s_bin, s_before, nullptr);
-    __syncthreads();
-    const u32 b0 = s_bin[0], b1 = s_bin[1];
-#pragma unroll
-    for (int i = 0; i < kKeys; ++i) {
-      if (i / V < steps) {
-        const u32 top = key[i] >> 21, next = (key[i] >> 11) & 1023u;
-        if (key[i] != kDead && top == b0) atomicAdd(&snext[0][next], 1u);
-        if (key[i] != kDead && top == b1) atomicAdd(&snext[1][next], 1u);
-      }
-    }
-    __syncthreads();
-    const u32* const hn[2] = {snext[0], snext[1]};
-    const u32 rn[2] = {rs[0] - s_before[0], rs[1] - s_before[1]};
-    find_ranks<NT, 2, 1, false>(hn, rn, stot, s_bin + 2, s_before + 2, nullptr);
-    __syncthreads();
-    e.lo = (b0 << 21) | (s_bin[2] << 11);
-    e.lo = e.lo > 1u ? e.lo : 1u;                      // zeros are counted below
-    const u32 last = ((b1 << 21) | (s_bin[3] << 11)) + 2047u - e.lo;      // last key - first key
+    // in W bins of 2^shift keys: a bin then holds about 2e-4 of the set's elements whatever the data's
+    // offset and spread
+    u32 last, drawn;
+    interval32(sr, e.lo, last, drawn);
     while ((((unsigned long long)(u32)W << e.shift) - 1ull) < last) ++e.shift;
     // But it may also reach from the smallest key to a normal value, where the rank lies just
     // above the zeros of an activation, or hold a few values within 1e-5 of each other, and a bin
@@ -523,7 +1140,7 @@ __global__ __launch_bounds__(NT) void k_sets(
     u32* head = lists + (size_t)idx * cap;
     if (tid < kListHead) head[tid] = tid == kHeadTie || tid == kHeadTieBin ? kNoKey : 0u;
     const float enough = (float)(cap - kListHead - cells) * mf / (float)n;     // sampled keys
-    if (e.shift == 0 || (float)(rs[1] - rs[0]) <= enough) {        // the same for every thread
+    if (e.shift == 0 || (float)drawn <= enough) {        // the same for every thread
       if (tid == 0) br[idx] = e;
       return;
     }
@@ -585,12 +1202,7 @@ __global__ __launch_bounds__(NT) void k_sets(
     u32 total = xor_reduce_sum<64, u32>(parts);
     total = total > 0u ? total : 1u;
     parts = lane < cells ? 1u + parts * (u32)(W - cells) / total : 0u;
-    u32 incl = parts;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const u32 o = (u32)__shfl_up((int)incl, d, 64);
-      if (lane >= d) incl += o;
-    }
+    const u32 incl = wave_scan_u32(parts);
     const u32 cell = (incl - parts) | (parts << 16);
     if (lane < cells) head[kListHead + lane] = cell;
     const u32 at = tie != kNoKey ? tie - e.lo : 0u;
@@ -620,24 +1232,26 @@ static void sets_t(const TX* X, int B, int T, int C, long long ld, int G, int Wf
   const bool few = (Wfew >= 512 && G >= 8 && pass == kPassZr && (W > Wfew || (long long)T * C <= 65536ll * G)) ||
                    (long long)T * C <= 8192;
   const size_t order_bytes = T <= kListTokens ? (size_t)T * sizeof(unsigned short) : 0;
-#define TDQ_SETS_SM(NT, SM)                                                                        \
-  hipLaunchKernelGGL((k_sets<TX, NT, SM>), dim3(G, B), dim3(NT), order_bytes, st, X, ld, T, C, G, Wfew, W, cells, aligned, r, \
+#define TDQ_SETS_SM(NT, RD, SM)                                                                        \
+  hipLaunchKernelGGL((k_sets<TX, NT, RD, SM, 0>), dim3(G, B), dim3(NT), order_bytes, st, X, ld, T, C, G, Wfew, W, cells, aligned, r, \
                      mean, m2, gid, sc, pass, keep_base ? 1 : 0, grp, br, bhist, lists, cap,       \
-                     img_flag, status)
-#define TDQ_SETS(NT)                                                           \
+                     img_flag, status, WholeArgs())
+#define TDQ_SETS(NT, RD)                                                       \
   do {                                                                         \
-    if constexpr (sizeof(TX) == 4) TDQ_SETS_SM(NT, 8192);                      \
-    else if (few) TDQ_SETS_SM(NT, 8192);                                       \
-    else TDQ_SETS_SM(NT, 16384);                                               \
+    if constexpr (sizeof(TX) == 4) TDQ_SETS_SM(NT, RD, 8192);                  \
+    else if (few) TDQ_SETS_SM(NT, RD, 8192);                                   \
+    else TDQ_SETS_SM(NT, RD, 16384);                                           \
   } while (0)
   // as few threads as hold the image's range keys in registers: [32, 4096, 1024] calibrates
   // in 111 / 117 / 145 us with 256 / 512 / 1024 threads per set
-  if (T <= kIdRounds * 256)
-    TDQ_SETS(256);
+  if (T <= 1024)
+    TDQ_SETS(256, 4);
+  else if (T <= kIdRounds * 256)
+    TDQ_SETS(256, 16);
   else if (T <= kIdRounds * 512)
-    TDQ_SETS(512);
+    TDQ_SETS(512, 16);
   else
-    TDQ_SETS(1024);
+    TDQ_SETS(1024, 16);
 #undef TDQ_SETS
 #undef TDQ_SETS_SM
 }
@@ -656,11 +1270,60 @@ hipError_t launch_sets(const void* X, tdq_dtype dt, int B, int T, int C, long lo
   return hipGetLastError();
 }
 
+template <typename TX, int WHOLE>
+static void sets_whole_t(const TX* X, int B, int T, int C, long long ld, int G, int extra, int Wfew, int W,
+                         const float* r, const double* mean, const double* m2, int* gid, const Scalars& sc,
+                         unsigned* bhist, void* ctl, unsigned* img_flag, unsigned* status, float* clip,
+                         float* scale, tdq_group_stats* stats, hipStream_t st) {
+  constexpr int V = Elem<TX>::V;
+  const int aligned = ((reinterpret_cast<uintptr_t>(X) & 15) == 0 && ld % V == 0 && C % V == 0) ? 1 : 0;
+  WholeArgs wa;
+  wa.extra = extra;
+  wa.L = sweep_lanes_per_row(C, V);
+  wa.ctl = static_cast<u32*>(ctl);
+  wa.clip = clip;
+  wa.scale = scale;
+  wa.stats = stats;
+  const size_t order_bytes = ((size_t)T * sizeof(unsigned short) + 15) & ~(size_t)15;
+#define TDQ_WHOLE_RD(RD, SM)                                                                            \
+  hipLaunchKernelGGL((k_sets<TX, 512, RD, SM, WHOLE>), dim3(G + extra, B), dim3(512), order_bytes, st, X, ld, T, \
+                     C, G, Wfew, W, 0, aligned, r, mean, m2, gid, sc, kPassZr, 0, nullptr, nullptr, bhist, nullptr, \
+                     0, img_flag, status, wa)
+#define TDQ_WHOLE(SM)                                                            \
+  do {                                                                           \
+    if (T <= 512) TDQ_WHOLE_RD(1, SM);                                           \
+    else if (T <= 1024) TDQ_WHOLE_RD(2, SM);                                     \
+    else if (T <= 2048) TDQ_WHOLE_RD(4, SM);                                     \
+    else if (T <= 4096) TDQ_WHOLE_RD(8, SM);                                     \
+    else TDQ_WHOLE_RD(16, SM);                                                   \
+  } while (0)
+  static_assert(kWholeTokens == 512 * kIdRounds, "a thread holds its range keys in registers");
+  if constexpr (sizeof(TX) == 4) TDQ_WHOLE(8192);
+  else TDQ_WHOLE(16384);
+#undef TDQ_WHOLE
+#undef TDQ_WHOLE_RD
+}
+
+hipError_t launch_sets_whole(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G, int ranks,
+                             int extra, int Wfew, int W, const float* r, const double* mean, const double* m2,
+                             int* gid, const Scalars& sc, unsigned* bhist, void* ctl, unsigned* img_flag,
+                             unsigned* status, float* clip, float* scale, tdq_group_stats* stats,
+                             hipStream_t st) {
+#define TDQ_SW(TX, NR)                                                                                       \
+  sets_whole_t<TX, NR>(static_cast<const TX*>(X), B, T, C, ld, G, extra, Wfew, W, r, mean, m2, gid, sc, bhist, \
+                       ctl, img_flag, status, clip, scale, stats, st)
+  if (dt == TDQ_F16) {
+    if (ranks == 1) TDQ_SW(u16, 1); else TDQ_SW(u16, 2);
+  } else {
+    if (ranks == 1) TDQ_SW(float, 1); else TDQ_SW(float, 2);
+  }
+#undef TDQ_SW
+  return hipGetLastError();
+}
+
 // ---------------------------------------------------------------------------
 // k_bracket_hist: the one sweep
 // ---------------------------------------------------------------------------
-typedef short s2v __attribute__((ext_vector_type(2)));
-
 // A group of L lanes takes R rows at a time and P pieces of 16 bytes of each: the set ids
 // and all R P = 4 pieces are loaded before the first is looked at, so a wavefront has four
 // kilobytes in flight whatever the row length -- what bounds this sweep otherwise is the
@@ -919,91 +1582,6 @@ hipError_t launch_bracket_hist(const void* X, tdq_dtype dt, int B, int T, int C,
   return hipGetLastError();
 }
 
-// The bin of a set's interval histogram (W = 256 to 2048 words) that holds its k-th smallest
-// key, by one wavefront; the same in every lane.  ok = the interval does hold it.  (binary32:
-// `ties` more elements lie in bin tie_bin than its word says.)  A set has fewer than 2^32 elements.
-struct BinPick {
-  bool ok;
-  u32 bin, need;              // rank wanted among the bin's elements (1-based)
-  u32 count;                  // elements of the bin's histogram word
-  u32 inside;                 // elements inside the interval
-};
-template <bool TIES>
-__device__ __forceinline__ BinPick pick_bin(const u32* __restrict__ hb, int W, u32 below, long long k,
-                                            u32 tie_bin = kNoKey, u32 ties = 0) {
-  const int lane = threadIdx.x & 63;
-  const int quads = W / 256;                    // 1 to 8 groups of four bins per lane
-  const uint4* mine_bins = reinterpret_cast<const uint4*>(hb) + lane * quads;
-  uint4 c[2];                                   // two groups stay in registers
-  u32 sum[8];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) c[i] = mine_bins[i < quads ? i : 0];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) sum[i] = i < 2 && i < quads ? c[i].x + c[i].y + c[i].z + c[i].w : 0u;
-  if (quads > 2) {                              // uniform; the loads issued together
-    uint4 t[6];
-#pragma unroll
-    for (int i = 2; i < 8; ++i) t[i - 2] = mine_bins[i < quads ? i : 0];
-#pragma unroll
-    for (int i = 2; i < 8; ++i)
-      sum[i] = i < quads ? t[i - 2].x + t[i - 2].y + t[i - 2].z + t[i - 2].w : 0u;
-  }
-  if (TIES && ties != 0) {                      // uniform
-    const int at = (int)(tie_bin >> 2) - lane * quads;         // of this lane's groups, if any
-#pragma unroll
-    for (int i = 0; i < 8; ++i) sum[i] += i == at && i < quads ? ties : 0u;
-  }
-  u32 mine = 0;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) mine += sum[i];
-  u32 incl = mine;                              // inclusive scan over lanes
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const u32 o = (u32)__shfl_up((int)incl, d, 64);
-    if (lane >= d) incl += o;
-  }
-  const unsigned long long kk = (unsigned long long)k;
-  BinPick r;
-  r.inside = (u32)__builtin_amdgcn_readlane((int)incl, 63);
-  r.ok = kk > below && kk - below <= r.inside;
-  const u32 need = (u32)(kk - below);
-  const unsigned long long hit = __ballot(incl >= need);
-  const int src = r.ok ? __ffsll((long long)hit) - 1 : 0;       // hit != 0 because need <= inside
-  u32 cum = incl - mine;
-  int group = 0;                                // the group of four ...
-  bool found = false;
-  if (quads > 1) {
-#pragma unroll
-    for (int i = 0; i < 7; ++i) {
-      found = found || i >= quads - 1 || cum + sum[i] >= need;
-      if (!found) {
-        cum += sum[i];
-        ++group;
-      }
-    }
-  }
-  uint4 q = group == 0 ? c[0] : c[1];
-  if (quads > 2) q = mine_bins[group];
-  u32 bin = (u32)(4 * (lane * quads + group));
-  const u32 v[4] = {q.x, q.y, q.z, q.w};        // ... and the bin in it
-  u32 count = v[0];
-  found = false;
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    const u32 all = v[i] + (TIES && bin == tie_bin ? ties : 0u);
-    found = found || cum + all >= need;
-    if (!found) {
-      cum += all;
-      ++bin;
-      count = v[i + 1];
-    }
-  }
-  r.bin = (u32)__builtin_amdgcn_readlane((int)bin, src);
-  r.need = need - (u32)__builtin_amdgcn_readlane((int)cum, src);
-  r.count = (u32)__builtin_amdgcn_readlane((int)count, src);
-  return r;
-}
-
 // First key and number of keys of a bin (binary32), by one wavefront; cell = the set's cell of this
 // lane.
 __device__ __forceinline__ void bin_keys(u32 cell, int cells, const Bracket& e, u32 bin, u32& key0, u32& span) {
@@ -1197,168 +1775,6 @@ hipError_t launch_bracket_gather(const void* Xv, int B, int T_, int C, long long
 // lie on one side of the interval.  Calibration with 18 % zeros, 16 sets, binary16: [1, 1936, 1500]
 // 208 us with 6 missed sets, 70 with 4 so; [8, 7744, 512] 584 with 54, 139 with 18.
 // ---------------------------------------------------------------------------
-constexpr int kFinishBits = 11;                 // key bits a pass resolves
-constexpr int kFinishTokens = 2048;             // tokens looked at together
-
-// LDS of the search
-template <int NT>
-struct FinishLds {
-  u32 h[1 << kFinishBits];
-  unsigned short list[kFinishTokens];           // the set's tokens among them
-  u32 wtot[NT / 64], digit;
-  unsigned long long wsum[NT / 64], rest;
-};
-
-// Adds the keys of rows list[0 .. n - 1] (offsets from token t0) that lie in [k0, k0 + span) to
-// the histogram of digits (key - k0 >> shift) - off.  Digit 0 takes all that is below as well and
-// is counted in a register, the last digit takes all that is above and is not counted (what the
-// others do not hold): either may be most of the set, and would meet in one word of LDS.
-// Groups of L lanes take R rows and P pieces of each at a time.
-template <typename TX, int NT, int R, int P>
-__device__ __forceinline__ void count_rows(const TX* __restrict__ Xb, long long ld, int C, int L, int t0,
-                                           const unsigned short* list, int n, u32 k0, u32 span, int shift,
-                                           int off, u32* h) {
-  constexpr int V = Elem<TX>::V;
-  const int lr = threadIdx.x & (L - 1), slot = threadIdx.x / L, slots = NT / L;
-  const int nvec = C / V;
-  u32 low = 0;
-  auto count = [&](u32 key) {
-    const u32 d = key - k0;
-    const int digit = d < span ? (int)(d >> shift) - off : 1 << kFinishBits;
-    low += digit <= 0 ? 1u : 0u;
-    if (digit > 0 && digit < (1 << kFinishBits) - 1) atomicAdd(&h[digit], 1u);
-  };
-  for (int rr = slot; rr < n; rr += slots * R) {
-    const TX* xp[R];
-#pragma unroll
-    for (int i = 0; i < R; ++i) {               // rows past the end: the last one, not counted
-      const int at = rr + slots * i;
-      xp[i] = Xb + (long long)(t0 + (int)list[at < n ? at : n - 1]) * ld;
-    }
-    for (int v0 = lr; v0 < nvec; v0 += P * L) {
-      uint4 q[R][P];
-#pragma unroll
-      for (int i = 0; i < R; ++i)
-#pragma unroll
-        for (int k = 0; k < P; ++k) {
-          const int v = v0 + k * L;
-          q[i][k] = load16(xp[i] + (long long)(v < nvec ? v : v0) * V);
-        }
-#pragma unroll
-      for (int i = 0; i < R; ++i) {
-        if (rr + slots * i >= n) break;
-#pragma unroll
-        for (int k = 0; k < P; ++k) {
-          if (k > 0 && v0 + k * L >= nvec) break;
-          TX x[V];
-          Elem<TX>::unpack(q[i][k], x);
-#pragma unroll
-          for (int c = 0; c < V; ++c) count(Elem<TX>::key(x[c]));
-        }
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < R; ++i) {
-      if (rr + slots * i >= n) break;
-      for (int c = nvec * V + lr; c < C; c += L) count(Elem<TX>::key(xp[i][c]));
-    }
-  }
-  if (low) atomicAdd(&h[0], low);
-}
-
-// The key of rank `need` (1-based) among the set's keys in [k0, k0 + span), by the whole
-// workgroup.  Every pass divides span by 2^kFinishBits, so three passes at most; near < 0 (> 0):
-// one more before them that looks at the last (first) 2047 keys of the range one by one.
-template <typename TX, int NT>
-__device__ __forceinline__ u32 search_rows(const TX* __restrict__ Xb, long long ld, int T, int C, int L,
-                           const int* __restrict__ gb, int j, u32 k0, u32 span, unsigned long long need,
-                           int near, FinishLds<NT>& s) {
-  constexpr int kBins = 1 << kFinishBits, NW = NT / 64;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int nvec = C / Elem<TX>::V;
-  while (span > 1) {
-    int shift = 32 - __clz(span - 1) - kFinishBits, off = 0;
-    shift = shift > 0 && near == 0 ? shift : 0;
-    if (near < 0 && span > (u32)kBins) off = (int)span - kBins;
-    near = 0;
-    __syncthreads();
-    for (int i = tid; i < kBins; i += NT) s.h[i] = 0;
-    if (tid == 0) s.digit = kBins - 1;
-    for (int t0 = 0; t0 < T; t0 += kFinishTokens) {
-      constexpr int kIds = kFinishTokens / NT;
-      bool mine[kIds];
-      u32 count = 0;
-#pragma unroll
-      for (int u = 0; u < kIds; ++u) {
-        const int t = t0 + u * NT + tid;
-        mine[u] = t < T && gb[t] == j;
-      }
-#pragma unroll
-      for (int u = 0; u < kIds; ++u) count += (u32)__popcll(__ballot(mine[u]));
-      if (lane == 0) s.wtot[wave] = count;
-      __syncthreads();
-      u32 at = 0, n = 0;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) {
-        at += w < wave ? s.wtot[w] : 0u;
-        n += s.wtot[w];
-      }
-#pragma unroll
-      for (int u = 0; u < kIds; ++u) {
-        const unsigned long long m = __ballot(mine[u]);
-        if (mine[u])
-          s.list[at + (u32)__popcll(m & ((1ull << lane) - 1ull))] = (unsigned short)(u * NT + tid);
-        at += (u32)__popcll(m);
-      }
-      __syncthreads();
-      if (nvec <= L)
-        count_rows<TX, NT, 4, 1>(Xb, ld, C, L, t0, s.list, (int)n, k0, span, shift, off, s.h);
-      else if (nvec <= 2 * L)
-        count_rows<TX, NT, 2, 2>(Xb, ld, C, L, t0, s.list, (int)n, k0, span, shift, off, s.h);
-      else
-        count_rows<TX, NT, 1, 4>(Xb, ld, C, L, t0, s.list, (int)n, k0, span, shift, off, s.h);
-      __syncthreads();                          // `list` and `wtot` are reused
-    }
-    // the bin where the running count reaches `need`
-    constexpr int kPer = kBins / NT;
-    unsigned long long mine = 0;
-    u32 c[kPer];
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      c[i] = s.h[tid * kPer + i];
-      mine += c[i];
-    }
-    unsigned long long incl = mine;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const unsigned long long o = __shfl_up(incl, d, 64);
-      if (lane >= d) incl += o;
-    }
-    if (lane == 63) s.wsum[wave] = incl;
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < NW; ++w) incl += w < wave ? s.wsum[w] : 0ull;
-    if (tid == NT - 1 && incl < need) s.rest = need - incl;       // the last digit
-    if (incl - mine < need && need <= incl) {   // at most one thread
-      unsigned long long cum = incl - mine;
-      int i = 0;
-      for (; i < kPer - 1; ++i) {
-        if (cum + c[i] >= need) break;
-        cum += c[i];
-      }
-      s.digit = (u32)(tid * kPer + i);
-      s.rest = need - cum;
-    }
-    __syncthreads();
-    const u32 digit = s.digit, first = digit == 0 ? 0u : (digit + (u32)off) << shift;
-    const u32 next = digit == kBins - 1 ? span : (digit + (u32)off + 1u) << shift;
-    k0 += first;
-    span = (next < span ? next : span) - first;
-    need = s.rest;
-  }
-  return k0;
-}
-
 template <typename TX, int NT>
 __global__ __launch_bounds__(NT, NT == 256 ? 8 : 4) void k_bracket_finish(
     const TX* __restrict__ X, long long ld, int T, int C, int G, int L,
@@ -1369,7 +1785,7 @@ __global__ __launch_bounds__(NT, NT == 256 ? 8 : 4) void k_bracket_finish(
     u32* __restrict__ status) {
   constexpr bool F16 = sizeof(TX) == 2;
   constexpr u32 kKeysAll = F16 ? 1u << 15 : 1u << 31;
-  __shared__ FinishLds<NT> lds;
+  __shared__ FinishLds<NT, false> lds;
   __shared__ u32 s_keys[F16 ? 1 : kListMax];
   __shared__ u32 s_ok, s_key, s_need, s_k0, s_span, s_tie, s_ties;
   __shared__ int s_near;
@@ -1440,19 +1856,17 @@ __global__ __launch_bounds__(NT, NT == 256 ? 8 : 4) void k_bracket_finish(
           }
         }
         if (ok == kDone && lane == 0) finish(key);
-      } else if (rank <= e.below) {             // below the interval
-        span = e.lo;
-        near = F16 ? -1 : 0;
-        if (span == 1u) {                       // ... where there are only zeros
+      } else {
+        const Lost l = lost_rank<F16>(w.k_rem, e.below, p.inside, e.lo,
+                                      e.lo + (e.shift & kCells ? e.width : e.width << e.shift));
+        k0 = l.k0;
+        span = l.span;
+        near = l.near;
+        rank = l.rank;
+        if (k0 == 0 && span == 1u) {            // below the interval, where there are only zeros
           ok = kDone;
           if (lane == 0) finish(0u);
         }
-      } else {                                  // above it
-        k0 = e.lo + (e.shift & kCells ? e.width : e.width << e.shift);
-        k0 = k0 < kKeysAll ? k0 : kKeysAll - 1u;
-        span = kKeysAll - k0;
-        near = F16 ? 1 : 0;
-        rank -= (unsigned long long)e.below + p.inside;
       }
     } else if (w.tokens == 0) {
       ok = kDone;
@@ -1494,8 +1908,8 @@ __global__ __launch_bounds__(NT, NT == 256 ? 8 : 4) void k_bracket_finish(
   }
   // The interval missed rank k (or the validation switch asked for this route).
   if (tid == 0) atomicAdd(&status[1 + pass], 1u);
-  const u32 key = search_rows<TX, NT>(X + (long long)b * T * ld, ld, T, C, L, gid + (long long)b * T, j, s_k0,
-                                      s_span, s_rank, s_near, lds);
+  const u32 key = search_rows<TX, NT, false>(X + (long long)b * T * ld, ld, T, C, L, gid + (long long)b * T, j,
+                                             nullptr, s_k0, s_span, s_rank, s_near, lds);
   if (tid == 0) finish(key);
 }
 

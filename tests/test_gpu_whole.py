@@ -1,0 +1,92 @@
+"""Calibration by one kernel after the statistics: which images take it (CPU), and its results against the
+oracle and the route that searches every set, at the edges of its rounds of keys, rows of odd length, one and
+several workgroups per set, one and two ranks."""
+import numpy as np
+import pytest
+
+from paper_2604_16855_amd import tdq
+
+import parity_util as U
+
+
+def _extra(dt, B, T, C, G, pct=0.0):
+    return tdq.lib().tdq_whole_extra(dt, B, T, C, G, tdq.C.c_double(pct))
+
+
+@pytest.mark.parametrize("dt,B,T,C,G,pct,extra", [
+    (tdq.TDQ_F16, 8, 121, 512, 16, 0.0, 7), (tdq.TDQ_F16, 1, 7744, 64, 16, 0.0, 60),
+    (tdq.TDQ_F16, 1, 8192, 8, 16, 0.0, 8), (tdq.TDQ_F16, 1, 8193, 8, 16, 0.0, -1),
+    (tdq.TDQ_F16, 32, 1024, 512, 15, 0.0, -1), (tdq.TDQ_F16, 32, 128, 1024, 15, 0.0, 1),  # 512 groups
+    (tdq.TDQ_F16, 32, 129, 1024, 15, 0.0, -1), (tdq.TDQ_F16, 64, 64, 1024, 16, 0.0, 0),
+    (tdq.TDQ_F16, 1, 512, 64, 17, 0.99, -1), (tdq.TDQ_F16, 1, 512, 64, 16, 0.99, 4),       # words for two ranks
+    (tdq.TDQ_F16, 1, 127, 64, 17, 0.99, 0), (tdq.TDQ_F16, 1, 100, 64, 65, 0.0, -1),
+    (tdq.TDQ_F32, 2, 896, 64, 8, 0.0, 0), (tdq.TDQ_F32, 2, 897, 64, 8, 0.99, -1),
+])
+def test_rule(dt, B, T, C, G, pct, extra):
+    assert _extra(dt, B, T, C, G, pct) == extra
+
+
+def test_groups_fit():
+    """Never more than 512 workgroups, or one per set if there are more sets."""
+    rng = np.random.default_rng(5)
+    for _ in range(2000):
+        B, T, C = (int(np.exp(rng.uniform(0, np.log(m)))) for m in (600, 9000, 5000))
+        G = int(rng.integers(1, 65))
+        e = _extra(tdq.TDQ_F16, B, T, C, G, float(rng.choice([0.0, 0.99])))
+        assert e == -1 or B * (G + e) <= max(512, B * G)
+
+
+def _data(kind, B, T, C, dtype, seed):
+    rng = np.random.default_rng(seed)
+    x = rng.laplace(0, 1, (B, T, C)) * np.exp(rng.normal(0, 0.8, (B, T, 1)))
+    if kind == "relu":
+        x = np.maximum(x, 0)
+    elif kind == "pad":                              # tokens of zeros, one set of identical values
+        x[:, ::3] = 0
+    elif kind == "one":                              # all tokens in one set
+        x[:, :, 0] = 9.0
+        x = np.clip(x, -9, 9)
+    return x.astype(dtype)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("pct", [0.0, 0.99])
+@pytest.mark.parametrize("kind", ["lap", "relu", "pad", "one"])
+@pytest.mark.parametrize("dtype,B,T,C,G,pad", [
+    (np.float16, 2, 1, 1, 1, 0), (np.float16, 3, 511, 24, 16, 0), (np.float16, 2, 513, 33, 5, 2),
+    (np.float16, 2, 1025, 17, 16, 1), (np.float16, 1, 2049, 56, 12, 0), (np.float16, 1, 4097, 40, 8, 0),
+    (np.float16, 1, 8192, 9, 3, 0), (np.float16, 5, 70, 1031, 64, 0), (np.float16, 2, 300, 520, 16, 3),
+    (np.float32, 2, 1, 3, 2, 0), (np.float32, 2, 512, 66, 16, 0), (np.float32, 1, 1025, 37, 8, 3),
+    (np.float32, 1, 8192, 7, 5, 0), (np.float32, 3, 20, 2049, 64, 0),
+])
+def test_against_oracle(dtype, B, T, C, G, pad, kind, pct):
+    dt = tdq.TDQ_F16 if dtype is np.float16 else tdq.TDQ_F32
+    X = _data(kind, B, T, C, dtype, T + C)
+    p = tdq.default_params(G)
+    p.base_pct = pct
+    if not (pct and G > 16 and _extra(dt, B, T, C, G) > 0):
+        assert _extra(dt, B, T, C, G, pct) >= 0
+    g = U.gpu_calibrate(X, p, ld_pad=pad)
+    assert g["status"] == 0
+    U.assert_calibration_matches(g, X, p)
+    p.flags |= tdq.FLAG_EXACT_SELECT                 # the general route
+    h = U.gpu_calibrate(X, p, ld_pad=pad)
+    assert np.array_equal(g["gid"], h["gid"]) and np.array_equal(g["stats"]["thr"], h["stats"]["thr"])
+    assert np.array_equal(g["stats"]["c_base"], h["stats"]["c_base"])
+    assert np.allclose(g["scale"], h["scale"], rtol=2e-7, atol=0)        # sigma: sums in another order
+
+
+@pytest.mark.gpu
+def test_status_is_this_calls():
+    """The status area is cleared by each call, and one image that is not finite raises it."""
+    import torch
+    X = torch.from_numpy(_data("lap", 4, 300, 64, np.float16, 1)).cuda()
+    p = tdq.default_params(8)
+    ws = tdq.alloc_workspace(4, 300, 64, tdq.TDQ_F16, p, X.device)
+    ws.fill_(255)
+    Y = X.clone()
+    Y[2, 7, 5] = float("inf")
+    for x, want in ((X, 0), (Y, 1), (X, 0)):
+        tdq.tdq_calibrate_groups(x, p, ws)
+        torch.cuda.synchronize()
+        assert tdq.device_status(ws) == want and (want or tdq.exact_select_sets(ws) == 0)
