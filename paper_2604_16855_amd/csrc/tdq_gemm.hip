@@ -1512,29 +1512,42 @@ hipError_t launch_w4a4_gemm(const uint8_t* Qx, long long ld_q, const int* gid, c
 // unit, not by the matrix cores (which idle three quarters of the time).  The factor 256
 // of the nibble expansion is taken out once at the end (a power of two: exact).
 //
-// Workgroup = 2 x 2 wavefronts, wavefront tile 64 x 64, 128 x 128 per workgroup, two
-// workgroups per CU; a stage is SBY packed bytes (SBY / 16 blocks) of K per row,
-// register-staged and double-buffered.  LDS rows are SBY + 8 bytes apart: the 8-byte
-// fragment reads of 32 consecutive rows then fall on 32 different bank pairs.  The steps
-// of a stage sit in LDS block-major so that the 4 consecutive rows a lane owns are one
-// 16-byte read.
+// The weights are the row operand and the activations the column operand: a lane of the result then
+// holds ONE activation row, so a block's step is one register instead of sixteen, and a stage's four steps
+// of a row are one LDS read.  2 x 2 wavefronts of 32 MB activations x 64 weights; operands by direct-to-LDS
+// loads in stages of 64 bytes (4 blocks) per row, three slots, two stages in flight (LDS layout of a slot
+// as in k_w4a4_gemm_pipe); 64 x 128 tiles (MB = 1) leave three workgroups on a CU, so that one's vector
+// work covers another's waits and the last round of tiles is even.  A lane's results are runs of 4 outputs in
+// 32 rows, so they leave through LDS as whole lines.
+// Before, 128 x 128 tiles staged through registers, two workgroups per CU, 46 vector instructions per matrix
+// instruction (42 here, 39 with MB = 2): us, before and now, 8192 x 768 x 768 20.1 and 16.9, 968 x 512 x 512 15.9
+// and 7.5, 7744 x 320 x 1280 27.8 and 15.9, 4096 x 4096 x 64 66.6 and 38.5, 131072 x 1024 x 4096 1359 and 1312.
+// The 42 instructions alone are 10.2 of the 16.9 (4 cycles each on a SIMD).
 // ---------------------------------------------------------------------------
-template <typename OUT, int SBY>
-__global__ __launch_bounds__(GEMM_THREADS, 2) void k_w4a4_gemm_blocks(
+// 64 floats from 64 addresses -> 64 consecutive floats of LDS
+__device__ __forceinline__ void dma4(const float* gptr, unsigned lds_base) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off"
+               :
+               : "v"(gptr), "s"(lds_base)
+               : "memory");
+}
+
+template <typename OUT, int MB>
+__global__ __launch_bounds__(GEMM_THREADS, (MB == 1 ? 3 : 2)) void k_w4a4_gemm_blocks(
     const uint8_t* __restrict__ Qx, long long ld_q, const float* __restrict__ bscale, long long ld_s,
     int M, int K, int N, const uint8_t* __restrict__ Qw, long long ld_w,
     const float* __restrict__ w_scale, const float* __restrict__ bias, OUT* __restrict__ Y,
-    long long ld_y, int m_tiles, int n_tiles) {
-  constexpr int MT = 2, NT = 2, BM = 128, BN = 128;
-  constexpr int SB = SBY / 16;                         // blocks (= 16-byte pieces) per stage
-  constexpr int STRIDE = SBY + 8;
-  constexpr int RPP = GEMM_THREADS / SB;               // rows per staging pass
-  constexpr int PASSES = BM / RPP;
-  constexpr int DPT = SB / 2;                          // steps per thread and stage
-  __shared__ __attribute__((aligned(16))) uint8_t sA[2][BM * STRIDE];
-  __shared__ __attribute__((aligned(16))) uint8_t sB[2][BN * STRIDE];
-  __shared__ __attribute__((aligned(16))) float sD[2][SB][BM];
-  __shared__ float sCol[BN], sBias[BN];
+    long long ld_y, int m_tiles, int n_tiles, int y_vec_ok) {
+  constexpr int NA = 2, BM = 64 * MB, BN = 128, D = 3;
+  constexpr int SB = BKB / 16;                         // blocks (= 16-byte pieces) per stage
+  constexpr int SLOT = (BM + BN) * BKB;                // activation rows then weight rows, 64 B each
+  constexpr int NL = (BM + BN) / 64 + MB;              // direct loads per wavefront and stage
+  constexpr int W = OutVec<OUT>::W;                    // outputs per 16-byte store
+  constexpr int PITCH = 64 * (int)sizeof(OUT) + 16;    // a row of 64 outputs on its way out
+  __shared__ __attribute__((aligned(1024))) uint8_t ring[D * SLOT];
+  __shared__ __attribute__((aligned(256))) float sD[D][BM][SB];
+  __shared__ __attribute__((aligned(16))) float sCol[BN], sBias[BN];
+  static_assert(4 * 32 * PITCH <= D * SLOT, "the results of 32 rows of every wavefront fit the ring");
 
   const int bid = blockIdx.x;
   const int xcd = bid % XCDS, idx = bid / XCDS;
@@ -1544,236 +1557,199 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void k_w4a4_gemm_blocks(
   const int m0 = m_tile * BM, n0 = n_tile * BN;
 
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const int kbytes = (K + 1) / 2;
-  const int KB = (K + 31) / 32;
-  const int k_tiles = (kbytes + SBY - 1) / SBY;
+  const int kbytes = (K + 1) / 2, KB = (K + 31) / 32;
+  const int k_tiles = (KB + SB - 1) / SB;
 
-  for (int j = tid; j < BN; j += GEMM_THREADS) {
-    const int n = n0 + j;
-    sCol[j] = n < N ? w_scale[n] : 0.f;
-    sBias[j] = (bias && n < N) ? bias[n] : 0.f;
+  if (tid < BN) {
+    const int n = n0 + tid < N ? n0 + tid : N - 1;
+    sCol[tid] = w_scale[n];
+    sBias[tid] = bias ? bias[n] : 0.f;
   }
 
-  // staging: thread t owns the 16-byte piece t % SB of rows t / SB + RPP i of both
-  // operands, and DPT consecutive steps of row t / 2
-  const int pr0 = tid / SB, pc = (tid % SB) * 16;
-  const uint8_t* pa[PASSES];
-  const uint8_t* pb[PASSES];
+  // load e of this wavefront fills 16 rows: lane l writes position l & 3 of row l >> 2; the last MB
+  // loads are the steps of 16 rows, lane l that of row l >> 2 and block l & 3
+  const uint8_t* src[MB + NA];
+  const float* dsrc[MB];
+  const int brow = 16 * wave + (lane >> 2);
+  const int piece = ((lane & 3) ^ ((brow >> 2) & 3)) * 16;
 #pragma unroll
-  for (int i = 0; i < PASSES; ++i) {
-    int r = m0 + pr0 + RPP * i;
-    r = r < M ? r : M - 1;
-    pa[i] = Qx + (long long)r * ld_q + pc;
-    r = n0 + pr0 + RPP * i;
-    r = r < N ? r : N - 1;
-    pb[i] = Qw + (long long)r * ld_w + pc;
-  }
-  const int drow = tid >> 1, dcol = (tid & 1) * DPT;
-  const bool d_row_ok = m0 + drow < M;
-  const float* pd = bscale + (long long)(m0 + (d_row_ok ? drow : 0)) * ld_s + dcol;
-
-  uint4 ga[PASSES], gb[PASSES];
-  float gd[DPT];
-  auto load_stage = [&](int kt) {
-    const int kb = kt * SBY + pc;          // first packed byte of this piece
-    if ((kt + 1) * SBY <= kbytes) {        // a whole stage inside the rows (uniform)
-#pragma unroll
-      for (int i = 0; i < PASSES; ++i) {
-        ga[i] = *reinterpret_cast<const uint4*>(pa[i] + (long long)kt * SBY);
-        gb[i] = *reinterpret_cast<const uint4*>(pb[i] + (long long)kt * SBY);
-      }
-    } else if (kb < kbytes) {
-#pragma unroll
-      for (int i = 0; i < PASSES; ++i) {
-        ga[i] = *reinterpret_cast<const uint4*>(pa[i] + (long long)kt * SBY);
-        gb[i] = *reinterpret_cast<const uint4*>(pb[i] + (long long)kt * SBY);
-      }
-      if (kb + 16 > kbytes) {              // piece straddles the end of the row: zero the rest
-        const int keep = kbytes - kb;
-#pragma unroll
-        for (int i = 0; i < PASSES; ++i) {
-          mask_piece(ga[i], keep);
-          mask_piece(gb[i], keep);
-        }
-      }
+  for (int e = 0; e < MB + NA; ++e) {
+    if (e < MB) {
+      const int r = m0 + 64 * e + brow < M ? m0 + 64 * e + brow : M - 1;
+      src[e] = Qx + (long long)r * ld_q;
+      dsrc[e] = bscale + (long long)r * ld_s;
     } else {
-#pragma unroll
-      for (int i = 0; i < PASSES; ++i) {
-        ga[i] = make_uint4(0, 0, 0, 0);
-        gb[i] = make_uint4(0, 0, 0, 0);
-      }
+      const int r = n0 + 64 * (e - MB) + brow;
+      src[e] = Qw + (long long)(r < N ? r : N - 1) * ld_w;
     }
-    // 4-byte loads, not 16-byte ones: every lane pair reads its own row here, and a
-    // 16-byte load whose 64 lanes fall on 64 different 128-byte lines was measured to
-    // slow the whole kernel down tenfold on this chip.
-    const int b0 = kt * SB + dcol;         // first block of this thread's steps
+  }
+  const unsigned ring_base = (unsigned)(size_t)(__attribute__((address_space(3))) uint8_t*)ring;
+  const unsigned sd_base = (unsigned)(size_t)(__attribute__((address_space(3))) float*)&sD[0][0][0];
+  auto load_stage = [&](int kt, int slot) {
+    const int kb = kt * BKB + piece;
+    const int off = kb < 16 * KB ? kb : 0;               // past the row's end: any piece of it
+    const int blk = kt * SB + (lane & 3);
+    const unsigned to = __builtin_amdgcn_readfirstlane(ring_base + slot * SLOT + wave * 1024);
+    const unsigned to_d = __builtin_amdgcn_readfirstlane(sd_base + slot * (BM * SB * 4) + wave * 256);
 #pragma unroll
-    for (int j = 0; j < DPT; ++j) gd[j] = (d_row_ok && b0 + j < KB) ? pd[kt * SB + j] : 0.f;
+    for (int e = 0; e < MB + NA; ++e) dma16(src[e] + off, to + e * 4096);
+#pragma unroll
+    for (int e = 0; e < MB; ++e) dma4(dsrc[e] + (blk < KB ? blk : KB - 1), to_d + e * 1024);
   };
-  auto store_stage = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < PASSES; ++i) {
-      uint2* d = reinterpret_cast<uint2*>(&sA[buf][(pr0 + RPP * i) * STRIDE + pc]);
-      d[0] = make_uint2(ga[i].x, ga[i].y);
-      d[1] = make_uint2(ga[i].z, ga[i].w);
-      d = reinterpret_cast<uint2*>(&sB[buf][(pr0 + RPP * i) * STRIDE + pc]);
-      d[0] = make_uint2(gb[i].x, gb[i].y);
-      d[1] = make_uint2(gb[i].z, gb[i].w);
-    }
-#pragma unroll
-    for (int j = 0; j < DPT; ++j) sD[buf][dcol + j][drow] = gd[j];
-  };
+  load_stage(0, 0);
+  if (k_tiles > 1) load_stage(1, 1);
 
-  float accf[MT][NT][16];
+  float accf[NA][MB][16];
 #pragma unroll
-  for (int i = 0; i < MT; ++i)
+  for (int i = 0; i < NA; ++i)
 #pragma unroll
-    for (int j = 0; j < NT; ++j)
+    for (int j = 0; j < MB; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) accf[i][j][r] = 0.f;
 
-  load_stage(0);
-  store_stage(0);
-  __syncthreads();
-
-  // Lane l feeds row (l & 31) of a 32-row fragment and, of each 16-byte block of K, the
-  // 8 bytes at offset 8 (l >> 5); it owns column l & 31 and rows 8 q + 4 (l >> 5) + 0..3,
-  // q = 0..3, of every 32 x 32 result.
-  const int frow = lane & 31, fhalf = (lane >> 5) * 8;
-  const int a_off = (wm * 32 * MT + frow) * STRIDE + fhalf;
-  const int b_off = (wn * 32 * NT + frow) * STRIDE + fhalf;
-  const int d_off = wm * 32 * MT + (lane >> 5) * 4;
+  // Lane l feeds row (l & 31) of a 32-row fragment and, of each 16-byte block of K, the 8 bytes at offset
+  // 8 (l >> 5); of a 32 x 32 result it owns activation l & 31 and weights 8 q + 4 (l >> 5) + 0..3.
+  const int frow = lane & 31, fh = lane >> 5, swz = (frow >> 2) & 3;
+  const int x_row = (wm * 32 * MB + frow) * BKB + 8 * fh, w_row = (BM + wn * 64 + frow) * BKB + 8 * fh;
   const v16i zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-  for (int kt = 0; kt < k_tiles; ++kt) {
-    const int cur = kt & 1;
-    if (kt + 1 < k_tiles) load_stage(kt + 1);
-    // one block at a time: unrolled further, the loads of all blocks are hoisted and
-    // the accumulators spill
-#pragma unroll 1
+  auto stage = [&](int kt, int slot, auto tail) {
+    const uint8_t* at = ring + slot * SLOT;
+    float4 d[MB];
+#pragma unroll
+    for (int j = 0; j < MB; ++j) d[j] = *reinterpret_cast<const float4*>(&sD[slot][wm * 32 * MB + j * 32 + frow][0]);
+#pragma unroll
     for (int kb = 0; kb < SB; ++kb) {
-      v4i a[MT], b[NT];
-      float dl[MT][16];
+      if (decltype(tail)::value && kt * SB + kb >= KB) break;            // uniform
+      const int off = (kb ^ swz) * 16;
+      v4i a[NA], b[MB];
 #pragma unroll
-      for (int i = 0; i < MT; ++i) {
-        const uint2 f = *reinterpret_cast<const uint2*>(&sA[cur][a_off + i * 32 * STRIDE + kb * 16]);
+      for (int i = 0; i < NA; ++i) {
+        const uint2 f = *reinterpret_cast<const uint2*>(at + w_row + i * 32 * BKB + off);
         a[i] = expand(f.x, f.y);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const float4 d4 = *reinterpret_cast<const float4*>(&sD[cur][kb][d_off + i * 32 + q * 8]);
-          dl[i][4 * q] = d4.x; dl[i][4 * q + 1] = d4.y; dl[i][4 * q + 2] = d4.z; dl[i][4 * q + 3] = d4.w;
-        }
       }
 #pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        const uint2 f = *reinterpret_cast<const uint2*>(&sB[cur][b_off + j * 32 * STRIDE + kb * 16]);
+      for (int j = 0; j < MB; ++j) {
+        uint2 f = *reinterpret_cast<const uint2*>(at + x_row + j * 32 * BKB + off);
+        if (decltype(tail)::value) {                   // bytes past the row's end do not count
+          const int keep = kbytes - ((kt * SB + kb) * 16 + 8 * fh);
+          f.x &= tail_mask(keep, 0);
+          f.y &= tail_mask(keep, 4);
+        }
         b[j] = expand(f.x, f.y);
       }
-      v16i t[MT][NT];
+      v16i t[NA][MB];
 #pragma unroll
-      for (int i = 0; i < MT; ++i)
+      for (int i = 0; i < NA; ++i)
 #pragma unroll
-        for (int j = 0; j < NT; ++j)
+        for (int j = 0; j < MB; ++j)
           t[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i], b[j], zero, 0, 0, 0);
 #pragma unroll
-      for (int i = 0; i < MT; ++i)
+      for (int i = 0; i < NA; ++i)
 #pragma unroll
-        for (int j = 0; j < NT; ++j)
+        for (int j = 0; j < MB; ++j) {
+          const float dl = kb == 0 ? d[j].x : kb == 1 ? d[j].y : kb == 2 ? d[j].z : d[j].w;
 #pragma unroll
           for (int r = 0; r < 16; ++r)
-            accf[i][j][r] = __builtin_fmaf((float)t[i][j][r], dl[i][r], accf[i][j][r]);
-    }
-    if (kt + 1 < k_tiles) store_stage(cur ^ 1);
-    __syncthreads();
-  }
-
-  const int ccol = lane & 31, rquad = (lane >> 5) * 4;
-  if (m0 + BM <= M && n0 + BN <= N && (long long)(BM + 8) * ld_y < (1ll << 31) / (long long)sizeof(OUT)) {
-    // whole tile inside Y: a wavefront-uniform row pointer plus one per-lane offset, two
-    // rows at a time, the NT column blocks of a row back to back (whole lines of Y)
-    const unsigned lane_offu = (unsigned)(rquad * (int)ld_y + ccol);
-    auto body = [&](auto with_bias) {
-      float ws[NT], bs[NT];
-#pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        ws[j] = sCol[wn * 32 * NT + j * 32 + ccol];
-        bs[j] = sBias[wn * 32 * NT + j * 32 + ccol];
-      }
-      OUT* wtile = Y + (long long)(m0 + wm * 32 * MT) * ld_y + (n0 + wn * 32 * NT);
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; r += 2) {
-          OUT* row0 = wtile + (long long)(i * 32 + (r >> 2) * 8 + (r & 3)) * ld_y + lane_offu;
-          OUT* row1 = row0 + ld_y;
-          float y0[NT], y1[NT];
-#pragma unroll
-          for (int j = 0; j < NT; ++j) {
-            y0[j] = (accf[i][j][r] * 0.00390625f) * ws[j];
-            y1[j] = (accf[i][j][r + 1] * 0.00390625f) * ws[j];
-            if (decltype(with_bias)::value) {
-              y0[j] = y0[j] + bs[j];
-              y1[j] = y1[j] + bs[j];
-            }
-          }
-          if constexpr (sizeof(OUT) == 2) {
-            h2v p[NT];
-#pragma unroll
-            for (int j = 0; j < NT; ++j) p[j] = round_pair_to_half(y0[j], y1[j]);
-#pragma unroll
-            for (int j = 0; j < NT; ++j) __builtin_nontemporal_store(p[j][0], row0 + j * 32);
-#pragma unroll
-            for (int j = 0; j < NT; ++j) __builtin_nontemporal_store(p[j][1], row1 + j * 32);
-          } else {
-#pragma unroll
-            for (int j = 0; j < NT; ++j) store_out<OUT>(row0 + j * 32, y0[j]);
-#pragma unroll
-            for (int j = 0; j < NT; ++j) store_out<OUT>(row1 + j * 32, y1[j]);
-          }
+            accf[i][j][r] = __builtin_fmaf((float)t[i][j][r], dl, accf[i][j][r]);
         }
-    };
-    if (bias)
-      body(std::true_type{});
+    }
+  };
+  int slot = 0;
+  for (int kt = 0; kt < k_tiles; ++kt) {
+    // stage kt has landed when at most the loads of the stage after it are outstanding
+    if (kt + 1 < k_tiles)
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NL) : "memory");
     else
-      body(std::false_type{});
-    return;
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    // the slot of stage kt - 1: every wavefront drained its reads before this barrier
+    if (kt + 2 < k_tiles) load_stage(kt + 2, slot == 0 ? 2 : slot - 1);
+    if ((kt + 1) * BKB <= kbytes)
+      stage(kt, slot, std::false_type{});
+    else
+      stage(kt, slot, std::true_type{});
+    slot = slot == D - 1 ? 0 : slot + 1;
   }
+  __syncthreads();
+
+  // Output, 32 rows of 64 outputs per wavefront at a time, through its own part of the ring.
+  uint8_t* mine = ring + wave * 32 * PITCH;
+  const int n_first = n0 + wn * 64;
+  const bool whole = y_vec_ok && n_first + 64 <= N;
+  constexpr int LPR = 64 / W, RPI = 64 / LPR;          // lanes per row, rows per store instruction
 #pragma unroll
-  for (int i = 0; i < MT; ++i)
+  for (int j = 0; j < MB; ++j) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int rl = wm * 32 * MT + i * 32 + (r >> 2) * 8 + rquad + (r & 3);
-      const int m = m0 + rl;
+    for (int i = 0; i < NA; ++i)
 #pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        const int cl = wn * 32 * NT + j * 32 + ccol;
-        const int n = n0 + cl;
-        if (m < M && n < N) {
-          float y = (accf[i][j][r] * 0.00390625f) * sCol[cl];
-          if (bias) y = y + sBias[cl];
-          store_out<OUT>(Y + (long long)m * ld_y + n, y);
+      for (int q = 0; q < 4; ++q) {
+        const int nl = i * 32 + 8 * q + 4 * fh;        // first of 4 outputs, in this wavefront's 64
+        const float4 ws = *reinterpret_cast<const float4*>(&sCol[wn * 64 + nl]);
+        const float4 bs = *reinterpret_cast<const float4*>(&sBias[wn * 64 + nl]);
+        float y[4] = {(accf[i][j][4 * q] * 0.00390625f) * ws.x, (accf[i][j][4 * q + 1] * 0.00390625f) * ws.y,
+                      (accf[i][j][4 * q + 2] * 0.00390625f) * ws.z, (accf[i][j][4 * q + 3] * 0.00390625f) * ws.w};
+        if (bias) {
+          y[0] += bs.x;
+          y[1] += bs.y;
+          y[2] += bs.z;
+          y[3] += bs.w;
+        }
+        uint8_t* to = mine + frow * PITCH + nl * (int)sizeof(OUT);
+        if constexpr (sizeof(OUT) == 2) {
+          const h2v p0 = round_pair_to_half(y[0], y[1]), p1 = round_pair_to_half(y[2], y[3]);
+          *reinterpret_cast<uint2*>(to) = make_uint2(__builtin_bit_cast(u32, p0), __builtin_bit_cast(u32, p1));
+        } else {
+          *reinterpret_cast<float4*>(to) = make_float4(y[0], y[1], y[2], y[3]);
+        }
+      }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (this wavefront's own writes, in order)
+#pragma unroll
+    for (int it = 0; it < 32 / RPI; ++it) {
+      const int row = it * RPI + lane / LPR, part = lane % LPR;
+      const int m = m0 + wm * 32 * MB + j * 32 + row, n = n_first + part * W;
+      const uint8_t* from = mine + row * PITCH + part * 16;
+      if (m < M) {
+        OUT* y = Y + (long long)m * ld_y + n;
+        if (whole) {
+          typedef u32 v4u __attribute__((ext_vector_type(4)));
+          __builtin_nontemporal_store(*reinterpret_cast<const v4u*>(from), reinterpret_cast<v4u*>(y));
+        } else {
+#pragma unroll
+          for (int k = 0; k < W; ++k)
+            if (n + k < N) __builtin_nontemporal_store(reinterpret_cast<const OUT*>(from)[k], y + k);
         }
       }
     }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read before the next 32 rows overwrite it
+  }
 }
 
-constexpr int kBlkStageBytes = 128;      // packed bytes of K per stage of the block-scaled kernel
 hipError_t launch_w4a4_gemm_blocks(const uint8_t* Qx, long long ld_q, const float* bscale,
                                    long long ld_s, int M, int K, int N, const uint8_t* Qw,
                                    long long ld_w, const float* w_scale, const float* bias, void* Y,
                                    tdq_dtype y_dt, long long ld_y, hipStream_t st) {
-  const int m_tiles = (M + 127) / 128, n_tiles = (N + 127) / 128;
-  const long long m_groups = (m_tiles + XCDS - 1) / XCDS;
-  const unsigned grid = (unsigned)(m_groups * XCDS * n_tiles);
-  if (y_dt == TDQ_F32)
-    hipLaunchKernelGGL((k_w4a4_gemm_blocks<float, kBlkStageBytes>), dim3(grid), dim3(GEMM_THREADS), 0, st, Qx, ld_q,
-                       bscale, ld_s, M, K, N, Qw, ld_w, w_scale, bias, static_cast<float*>(Y), ld_y,
-                       m_tiles, n_tiles);
-  else
-    hipLaunchKernelGGL((k_w4a4_gemm_blocks<_Float16, kBlkStageBytes>), dim3(grid), dim3(GEMM_THREADS), 0, st, Qx,
-                       ld_q, bscale, ld_s, M, K, N, Qw, ld_w, w_scale, bias,
-                       static_cast<_Float16*>(Y), ld_y, m_tiles, n_tiles);
+  const int esz = y_dt == TDQ_F32 ? 4 : 2;
+  const int y_vec_ok = (reinterpret_cast<uintptr_t>(Y) & 15) == 0 && ld_y * esz % 16 == 0 ? 1 : 0;
+  const int n_tiles = (N + 127) / 128;
+  // 128 rows a tile where there are many tiles: 39 vector instructions per matrix instruction instead of 42 weigh
+  // more than an even last round and a third workgroup per CU.  64 / 128 rows, us: 32768 x 320 x 1280 (2560
+  // tiles of 128) 52.2 / 53.6, 131072 x 4096 x 1024 (8192) 1285 / 1223.
+  const bool tall = (long long)((M + 127) / 128) * n_tiles >= 4096;
+  const int bm = tall ? 128 : 64;
+  const int m_tiles = (M + bm - 1) / bm;
+  const unsigned grid = (unsigned)((long long)((m_tiles + XCDS - 1) / XCDS) * XCDS * n_tiles);
+#define TDQ_BLK(OUT, MB)                                                                                       \
+  hipLaunchKernelGGL((k_w4a4_gemm_blocks<OUT, MB>), dim3(grid), dim3(GEMM_THREADS), 0, st, Qx, ld_q, bscale, ld_s, \
+                     M, K, N, Qw, ld_w, w_scale, bias, static_cast<OUT*>(Y), ld_y, m_tiles, n_tiles, y_vec_ok)
+  if (y_dt == TDQ_F32) {
+    if (tall) TDQ_BLK(float, 2); else TDQ_BLK(float, 1);
+  } else {
+    if (tall) TDQ_BLK(_Float16, 2); else TDQ_BLK(_Float16, 1);
+  }
+#undef TDQ_BLK
   return hipGetLastError();
 }
 

@@ -376,3 +376,20 @@ def test_blocks_path_full_size_sampled():
     Y6 = tdq.tdq_w4a4_linear_blocks_f6(F, bs6, C, tdq.tdq_pack_codes_f6(Qw_d, C), N, ws_d)
     torch.cuda.synchronize()
     assert torch.equal(Y6, Y)
+
+
+@pytest.mark.parametrize("out_dtype", [torch.float32, torch.float16])
+@pytest.mark.parametrize("M,K,N", [(63, 128, 63), (64, 129, 64), (65, 127, 65), (1, 384, 127), (130, 385, 129),
+                                   (31, 513, 8), (97, 640, 200)])
+def test_blocks_linear_tile_edges(M, K, N, out_dtype):
+    """One to six stages of four blocks, tiles cut in both directions; and the same bits into rows that
+    16-byte stores cannot write."""
+    codes, bscale, qw, w_scale, bias = _random_block_operands(M, K, N, M + K, spread=1.0)
+    Y = _check_blocks_linear(codes, bscale, qw, w_scale, bias, out_dtype=out_dtype)
+    d = U.dev()
+    Q, Qw = U.pack_to_device(codes), U.pack_to_device(qw)
+    bs, ws, bd = (torch.from_numpy(np.ascontiguousarray(v)).to(d) for v in (bscale, w_scale, bias))
+    wide = torch.full((M, N + 3), 7.0, dtype=out_dtype, device=d)
+    tdq.tdq_w4a4_linear_blocks(Q, bs, K, Qw, ws, bias=bd, out=wide[:, 1:N + 1])
+    assert np.array_equal(wide[:, 1:N + 1].cpu().numpy().astype(np.float64), Y)
+    assert bool((wide[:, 0] == 7).all()) and bool((wide[:, N + 1:] == 7).all())
