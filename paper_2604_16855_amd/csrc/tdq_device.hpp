@@ -160,6 +160,66 @@ __device__ __forceinline__ u32 group_sum_u32(u32 v) {
 // Inclusive scan over the wavefront: the partial windows of group_sum_u32<64> are exactly that.
 __device__ __forceinline__ u32 wave_scan_u32(u32 v) { return group_sum_u32<64>(v); }
 
+// One workgroup's search of K LDS histograms of BINS bins (or K times the same) for the bin that
+// holds rank r[q] (1-based, at most the histogram's total) of h[q]: bin[q] and the count before
+// it.  Every thread of the workgroup calls it, after a barrier that completes the histograms;
+// the results are valid after the caller's next barrier.  stot [K][NW] is scratch.  A bin is the
+// sum of COPIES neighbouring words.  CUM: cum[BINS] gets the counts before every bin of h[0].  all (if not 0):
+// the histogram's total, of which bin 0 holds what the other bins do not (its own word must be 0).
+template <int NT, int K, int COPIES, bool CUM, int BINS = 1024>
+__device__ __forceinline__ void find_ranks(const u32* const (&h)[K], const u32 (&r)[K],
+                                           u32 (*stot)[NT / 64], u32* bin, u32* before, u32* cum, u32 all = 0) {
+  constexpr int NW = NT / 64, kBins = BINS / NT;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  u32 c[K][kBins], mine[K], incl[K];
+#pragma unroll
+  for (int q = 0; q < K; ++q) {
+    mine[q] = 0;
+#pragma unroll
+    for (int i = 0; i < kBins; ++i) {
+      c[q][i] = 0;
+#pragma unroll
+      for (int k = 0; k < COPIES; ++k) c[q][i] += h[q][(tid * kBins + i) * COPIES + k];
+      mine[q] += c[q][i];
+    }
+    incl[q] = wave_scan_u32(mine[q]);
+    if (lane == 63) stot[q][wave] = incl[q];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < K; ++q) {
+    // (the totals of the wavefronts before this one)
+    const u32 totals = wave_scan_u32(lane < NW ? stot[q][lane < NW ? lane : 0] : 0u);
+    incl[q] += wave > 0 ? (u32)__builtin_amdgcn_readlane((int)totals, wave > 0 ? wave - 1 : 0) : 0u;
+    u32 start = incl[q] - mine[q];
+    if (all != 0) {                          // (uniform)
+      const u32 first = all - (u32)__builtin_amdgcn_readlane((int)totals, NW - 1);
+      incl[q] += first;
+      start += tid == 0 ? 0u : first;
+      c[q][0] += tid == 0 ? first : 0u;
+    }
+    if (CUM && q == 0) {
+      u32 at = start;
+#pragma unroll
+      for (int i = 0; i < kBins; ++i) {
+        cum[tid * kBins + i] = at;
+        at += c[0][i];
+      }
+    }
+    if (start < r[q] && r[q] <= incl[q]) {                        // exactly one thread
+      u32 at = start;
+      int i = 0;
+      for (; i < kBins - 1; ++i) {
+        if (at + c[q][i] >= r[q]) break;
+        at += c[q][i];
+      }
+      bin[q] = (u32)(tid * kBins + i);
+      before[q] = at;
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Moments.  The dispersion of a set is the population standard deviation of all its
 // elements (Sec. 4.2), and the bar on it is 1e-6 relative whatever the data's offset.
@@ -415,7 +475,7 @@ __device__ inline void clear_level_hists(u32* __restrict__ hist, const LevelPlan
 // DCRP projection of one (image, token set), in binary32 (Eq. dcrp with the eps
 // floors of the supplementary numerical conventions): key is the magnitude bit
 // pattern of the k-th smallest |x| of the set.  Called by one lane per set.
-__device__ inline void project_store(int idx, const GroupWork& w, u32 key, bool is_f16,
+__device__ inline float2 project_store(int idx, const GroupWork& w, u32 key, bool is_f16,
                                      const Scalars& sc, float* __restrict__ clip,
                                      float* __restrict__ scale,
                                      tdq_group_stats* __restrict__ stats) {
@@ -450,6 +510,7 @@ __device__ inline void project_store(int idx, const GroupWork& w, u32 key, bool 
     s.c_tau = c_tau; s.c_zr = c_zr; s.clip = c; s.scale = d; s.bind = bind;
     stats[idx] = s;
   }
+  return make_float2(c, d);
 }
 
 // ---------------------------------------------------------------------------

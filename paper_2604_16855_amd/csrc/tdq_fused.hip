@@ -10,9 +10,12 @@
 //      per level, LDS histogram [G][256]                (Eq. zr_constraint, exact)
 //   E  projection                                       (Eq. dcrp)
 //   F  quantize + pack                                  (Eqs. clipx, dequant)
+// (few images that fit a workgroup's registers: k_fused_sets, one workgroup per image and set.)
 // X is read once per step that needs it (A, every level of D, F) and comes from the
 // cache after the first; an image that fits the workgroup's registers is read once.  Same arithmetic as the multi-kernel path wherever a result is
 // rounded: group ids, thresholds and codes are integer work, sigma is binary64.
+#include <type_traits>
+
 #include "tdq_device.hpp"
 
 namespace tdq {
@@ -380,6 +383,272 @@ __global__ __launch_bounds__(kFusedThreads) void k_fused_small(
   }
 }
 
+// ---------------------------------------------------------------------------
+// k_fused_sets: images that fit a workgroup's registers, one workgroup per (image, token set).  Every
+// workgroup reads the whole image and finds all its tokens' ranges, because the sets follow from the smallest
+// and the largest; moments, rank select, projection and quantization are those of its own set's rows only,
+// so nothing passes between workgroups.  The rank: an LDS histogram of the key's top bits, then of
+// the next ones of the keys in the bin found (2 levels binary16, 3 binary32), found by the whole workgroup.
+// Moments: sums in binary64 about a value of the set (the first of its first token), so that a set of identical
+// values adds exact zeros.
+// Bound by a chain of a dozen barriers and by instruction issue (see k_sets); 512 threads because
+// what every wavefront does alike costs by the wavefronts on a SIMD.  196 x 64 binary32 with 8 sets: 16.1 us by
+// one workgroup per image, 9.5 so; [8, 64, 128] with 64 sets 24.0 and 9.0; [4, 100, 96] with 32 sets and a percentile
+// 33.9 and 12.6.  (1024 threads: 8.8, 10.1 and 10.9, and slower with many sets.)
+// ---------------------------------------------------------------------------
+constexpr int kSetsThreads = 512;
+constexpr int kSetsPieces = 8;                   // 16-byte pieces per thread, as many bytes as kFusedThreads x kRegPieces
+
+template <typename T>
+__global__ __launch_bounds__(kSetsThreads, 4) void k_fused_sets(
+    const T* __restrict__ X, long long ld, int T_, int C, int G, int L, Scalars sc, int with_base,
+    int* __restrict__ gid, float* __restrict__ clip, float* __restrict__ scale,
+    tdq_group_stats* __restrict__ stats, u32* __restrict__ image_flags, uint8_t* __restrict__ Q,
+    long long ld_q) {
+  constexpr int V = Elem<T>::V, NT = kSetsThreads, NW = NT / 64;
+  constexpr bool F16 = sizeof(T) == 2;
+  constexpr int kKeyBits = F16 ? 15 : 31;
+  constexpr int PPL = kRegPPL<T>, RPT = kSetsPieces / PPL;
+  constexpr int kBins = F16 ? 1024 : 2048;       // 10 + 5 or 11 + 10 + 10 key bits
+  constexpr int kLevels = F16 ? 2 : 3;
+  __shared__ __attribute__((aligned(16))) u32 hist[kLevels][kBins];
+  __shared__ u32 s_key[kRegTokens];
+  __shared__ u32 s_min[NW], s_max[NW], s_cnt[NW], s_kmax[NW], s_first[NW], stot[1][NW], s_bin[1], s_before[1];
+  __shared__ double s_s1[NW], s_s2[NW];
+  __shared__ float s_c, s_d;
+  const int j = blockIdx.x, b = blockIdx.y, idx = b * G + j;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lsh = 31 - __clz(L);
+  const int lr = tid & (L - 1), rsub = tid >> lsh, rpp = NT >> lsh;
+  const T* Xb = X + (long long)b * T_ * ld;
+  const int nvec = C / V;
+
+  // pieces lr, lr + L of rows rsub, rsub + rpp, ...
+  uint4 xr[RPT][PPL];
+#pragma unroll
+  for (int i = 0; i < RPT; ++i)
+#pragma unroll
+    for (int k = 0; k < PPL; ++k) {
+      const int row = rsub + rpp * i, v = lr + L * k;
+      xr[i][k] = *reinterpret_cast<const uint4*>(Xb + (long long)(row < T_ ? row : T_ - 1) * ld +
+                                                 (long long)(v < nvec ? v : 0) * V);
+    }
+  auto clear_hist = [&]() {
+    for (int i = tid; i < kLevels * kBins / 4; i += NT)
+      reinterpret_cast<uint4*>(&hist[0][0])[i] = make_uint4(0, 0, 0, 0);
+  };
+  clear_hist();
+
+  // ---- the tokens' ranges (a lane that has no second piece counts its row's first piece twice)
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    if (i > 0 && rpp * i >= T_) break;           // uniform
+    u32 km = 0;
+#pragma unroll
+    for (int k = 0; k < PPL; ++k) {
+      T e[V];
+      Elem<T>::unpack(xr[i][k], e);
+#pragma unroll
+      for (int c = 0; c < V; ++c) {
+        const u32 key = Elem<T>::key(e[c]);
+        km = key > km ? key : km;
+      }
+    }
+    u32 o;
+    if (L > 1) { o = dpp_u32<TDQ_DPP_ROW_SHR(1), 0xF>(km); km = o > km ? o : km; }
+    if (L > 2) { o = dpp_u32<TDQ_DPP_ROW_SHR(2), 0xF>(km); km = o > km ? o : km; }
+    if (L > 4) { o = dpp_u32<TDQ_DPP_ROW_SHR(4), 0xF>(km); km = o > km ? o : km; }
+    if (L > 8) { o = dpp_u32<TDQ_DPP_ROW_SHR(8), 0xF>(km); km = o > km ? o : km; }
+    if (L > 16) { o = dpp_u32<TDQ_DPP_ROW_BCAST15, 0xA>(km); km = o > km ? o : km; }
+    if (L > 32) { o = dpp_u32<TDQ_DPP_ROW_BCAST31, 0xC>(km); km = o > km ? o : km; }
+    const int row = rsub + rpp * i;
+    if (lr == L - 1 && row < T_) s_key[row] = __float_as_uint(Elem<T>::key_to_float(km));
+  }
+  __syncthreads();
+
+  // ---- the image's key range, the set's key interval (as in k_sets) and tokens
+  constexpr int kPer = kRegTokens / NT;          // tokens per thread
+  u32 k1[kPer], kinv = 0, khi = 0;
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int t = u * NT + tid;
+    k1[u] = t < T_ ? s_key[t] : 0xFFFFFFFFu;     // (no range key)
+    kinv = ~k1[u] > kinv ? ~k1[u] : kinv;
+    khi = k1[u] != 0xFFFFFFFFu && k1[u] > khi ? k1[u] : khi;
+  }
+  kinv = group_max_u32<64>(kinv);
+  khi = group_max_u32<64>(khi);
+  if (lane == 63) { s_min[wave] = ~kinv; s_max[wave] = khi; }
+  __syncthreads();
+  u32 lo = s_min[0], hi = s_max[0];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) {
+    lo = s_min[w] < lo ? s_min[w] : lo;
+    hi = s_max[w] > hi ? s_max[w] : hi;
+  }
+  const u32 span = (u32)kOctaveFloor << 23, floor_key = hi > span ? hi - span : 0u;
+  lo = lo > floor_key ? lo : floor_key;
+  if (tid == 0 && j == 0 && image_flags) image_flags[b] = hi >= 0x7F800000u ? TDQ_DEV_NONFINITE : 0u;
+  const u32 width = hi - lo + 1u, wq = width / (u32)G, wr = width - wq * (u32)G;
+  const u32 start = j == 0 ? 0u : lo + (u32)j * wq + ((u32)j * wr + (u32)G - 1u) / (u32)G;
+  const u32 end = j == G - 1 ? hi + 1u : lo + (u32)(j + 1) * wq + ((u32)(j + 1) * wr + (u32)G - 1u) / (u32)G;
+  auto in_set = [&](u32 k) { return k >= start && k < end; };
+  u32 cnt = 0, kmax = 0, first = 0xFFFFFFFFu;    // tokens, largest range, first token of this wavefront
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const bool mine = in_set(k1[u]);
+    const unsigned long long mask = __ballot(mine);
+    cnt += (u32)__popcll(mask);
+    if (mine) {
+      gid[(long long)b * T_ + u * NT + tid] = j;
+      kmax = k1[u] > kmax ? k1[u] : kmax;
+    }
+    if (mask != 0 && first == 0xFFFFFFFFu) first = (u32)(u * NT + wave * 64 + __ffsll((long long)mask) - 1);
+  }
+  kmax = group_max_u32<64>(kmax);
+  if (lane == 63) { s_cnt[wave] = cnt; s_kmax[wave] = kmax; s_first[wave] = first; }
+  __syncthreads();
+  u32 tokens = 0, t_first = 0xFFFFFFFFu, c_key = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    tokens += s_cnt[w];
+    t_first = s_first[w] < t_first ? s_first[w] : t_first;
+    c_key = s_kmax[w] > c_key ? s_kmax[w] : c_key;
+  }
+  GroupWork w;
+  w.tokens = tokens;
+  w.n = (long long)tokens * C;
+  w.k_rem = 0;
+  w.prefix = 0;
+  w.c_base = __uint_as_float(c_key);
+  w.sigma = 0.f;
+  if (tokens == 0) {
+    if (tid == 0) project_store(idx, w, 0u, F16, sc, clip, scale, stats);
+    return;
+  }
+  bool own[RPT];
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    const int row = rsub + rpp * i;
+    own[i] = row < T_ && in_set(s_key[row < T_ ? row : 0]);
+  }
+
+  // ---- moments, and the top key bits of the set's elements
+  double P = (double)Elem<T>::val(Xb[(long long)t_first * ld]);
+  P = P - P == 0.0 ? P : 0.0;
+  const double n = (double)w.n;
+  double a1 = 0.0, a2 = 0.0;
+  auto each = [&](auto&& f) {                    // the set's elements in this thread's registers
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+#pragma unroll
+      for (int k = 0; k < PPL; ++k) {
+        if (own[i] && lr + L * k < nvec) {
+          // (opaque: keys and values kept from one use to the next would not fit the registers)
+          uint4 q = xr[i][k];
+          asm volatile("" : "+v"(q.x), "+v"(q.y), "+v"(q.z), "+v"(q.w));
+          T e[V];
+          Elem<T>::unpack(q, e);
+#pragma unroll
+          for (int c = 0; c < V; ++c) f(e[c]);
+        }
+      }
+    }
+  };
+  constexpr int kTop = F16 ? 10 : 11;
+  each([&](T x) {
+    const double d = (double)Elem<T>::val(x) - P;
+    a1 += d;
+    a2 = fma(d, d, a2);
+    atomicAdd(&hist[0][Elem<T>::key(x) >> (kKeyBits - kTop)], 1u);
+  });
+  a1 = group_sum_f64<64>(a1);
+  a2 = group_sum_f64<64>(a2);
+  if (lane == 63) { s_s1[wave] = a1; s_s2[wave] = a2; }
+  __syncthreads();
+
+  // ---- the ranks wanted: the percentile base radius first (if asked for)
+  u32 key = 0;
+#pragma unroll 1
+  for (int pass = with_base ? kPassBase : kPassZr; pass >= kPassZr; --pass) {
+    long long k = (long long)ceil((pass == kPassBase ? sc.base_pct : sc.zr) * n);
+    k = k < 1 ? 1 : (k > w.n ? w.n : k);
+    u32 rank = (u32)k;
+    auto find = [&](const u32* h, auto bins) {
+      const u32* const hs[1] = {h};
+      const u32 rs[1] = {rank};
+      find_ranks<NT, 1, 1, false, decltype(bins)::value>(hs, rs, stot, s_bin, s_before, nullptr);
+      __syncthreads();
+      rank -= s_before[0];
+      return s_bin[0];
+    };
+    key = find(hist[0], std::integral_constant<int, kBins>{});
+    if constexpr (F16) {
+      each([&](T x) {
+        const u32 kx = Elem<T>::key(x);
+        if (kx >> 5 == key) atomicAdd(&hist[1][kx & 31u], 1u);
+      });
+      __syncthreads();
+      key = key << 5 | find(hist[1], std::integral_constant<int, kBins>{});
+    } else {
+      each([&](T x) {
+        const u32 kx = Elem<T>::key(x);
+        if (kx >> 20 == key) atomicAdd(&hist[1][kx >> 10 & 1023u], 1u);
+      });
+      __syncthreads();
+      key = key << 10 | find(hist[1], std::integral_constant<int, 1024>{});
+      each([&](T x) {
+        const u32 kx = Elem<T>::key(x);
+        if (kx >> 10 == key) atomicAdd(&hist[kLevels - 1][kx & 1023u], 1u);
+      });
+      __syncthreads();
+      key = key << 10 | find(hist[kLevels - 1], std::integral_constant<int, 1024>{});
+    }
+    if (pass == kPassBase) {
+      w.c_base = Elem<T>::key_to_float(key);
+      __syncthreads();
+      for (int i = tid; i < (kLevels - 1) * kBins; i += NT) hist[1][i] = 0;
+      __syncthreads();
+    }
+  }
+  if (tid == 0) {
+    double S1 = s_s1[0], S2 = s_s2[0];
+#pragma unroll
+    for (int q = 1; q < NW; ++q) { S1 += s_s1[q]; S2 += s_s2[q]; }
+    const double mu = S1 / n;
+    double var = S2 / n - mu * mu;
+    var = var > 0.0 ? var : 0.0;
+    w.sigma = (float)(sqrt(var) + sc.eps_std);
+    const float2 cd = project_store(idx, w, key, F16, sc, clip, scale, stats);
+    s_c = cd.x;
+    s_d = cd.y;
+  }
+  __syncthreads();
+
+  // ---- codes of the set's rows: pieces of V elements -> V / 2 bytes each
+  const float c = s_c, d = s_d, rcp = 1.0f / d;
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    if (!own[i]) continue;
+    uint8_t* qp = Q + ((long long)b * T_ + rsub + rpp * i) * ld_q;
+#pragma unroll
+    for (int k = 0; k < PPL; ++k) {
+      const int v = lr + L * k;
+      if (v >= nvec) break;
+      T e[V];
+      Elem<T>::unpack(xr[i][k], e);
+      u32 word = 0;
+#pragma unroll
+      for (int q = 0; q < V; ++q) word |= quant_nibble(Elem<T>::val(e[q]), c, d, rcp) << (4 * q);
+      if constexpr (F16)
+        *reinterpret_cast<u32*>(qp + (long long)v * 4) = word;
+      else
+        *reinterpret_cast<u16*>(qp + (long long)v * 2) = (u16)word;
+    }
+  }
+}
+
 template <typename T>
 static hipError_t fused_t(const T* X, int B, int T_, int C, long long ld, int G, const Scalars& sc,
                           float* r, double* mean, double* m2, int* gid, float* clip, float* scale,
@@ -392,7 +661,14 @@ static hipError_t fused_t(const T* X, int B, int T_, int C, long long ld, int G,
   const int with_base = sc.base_pct > 0.0 ? 1 : 0;
   const bool reg = T_ <= kRegTokens && vec_ok && q_vec_ok && C % V == 0 && C / V <= L * kRegPPL<T> &&
                    (long long)T_ <= (long long)(kFusedThreads / L) * (kRegPieces / kRegPPL<T>);
-  if (reg)
+  static_assert(kSetsThreads * kSetsPieces == kFusedThreads * kRegPieces, "the same images fit");
+  // A workgroup per set reads its image again: better until the chip holds no more of them at once (two to
+  // four per CU), us per image / per set: 512 sets [32, 196, 64] binary32 18.6 / 12.0; 1024 sets 23.0 / 18.2 of it but
+  // [64, 196, 64] binary16 13.5 / 16.6 and [256, 49, 96] 12.3 / 15.2; 2048 sets [128, 196, 64] 13.7 / 28.3.
+  if (reg && (long long)B * G <= 512)
+    hipLaunchKernelGGL((k_fused_sets<T>), dim3(G, B), dim3(kSetsThreads), 0, st, X, ld, T_, C, G, L, sc,
+                       with_base, gid, clip, scale, stats, image_flags, Q, ld_q);
+  else if (reg)
     hipLaunchKernelGGL((k_fused_small<T, true>), dim3(B), dim3(kFusedThreads), 0, st, X, ld, T_, C, G, L,
                        vec_ok, q_vec_ok, sc, with_base, r, mean, m2, gid, clip, scale, stats,
                        image_flags, Q, ld_q);

@@ -373,66 +373,6 @@ __device__ __forceinline__ u32 search_rows(const TX* __restrict__ Xb, long long 
 // several workgroups): 24.8 -> 20.3 us at [32, 4096, 1024] (25.4 with 16 Ki samples), 14.4 -> 11.9 at
 // [1, 7744, 64].
 // ---------------------------------------------------------------------------
-// One workgroup's search of K 1024-bin LDS histograms (or K times the same) for the bin that
-// holds rank r[q] (1-based, at most the histogram's total) of h[q]: bin[q] and the count before
-// it.  Every thread of the workgroup calls it, after a barrier that completes the histograms;
-// the results are valid after the caller's next barrier.  stot [K][NW] is scratch.  A bin is the
-// sum of COPIES neighbouring words.  CUM: cum[1024] gets the counts before every bin of h[0].  all (if not 0):
-// the histogram's total, of which bin 0 holds what the other bins do not (its own word must be 0).
-template <int NT, int K, int COPIES, bool CUM>
-__device__ __forceinline__ void find_ranks(const u32* const (&h)[K], const u32 (&r)[K],
-                                           u32 (*stot)[NT / 64], u32* bin, u32* before, u32* cum, u32 all = 0) {
-  constexpr int NW = NT / 64, kBins = 1024 / NT;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  u32 c[K][kBins], mine[K], incl[K];
-#pragma unroll
-  for (int q = 0; q < K; ++q) {
-    mine[q] = 0;
-#pragma unroll
-    for (int i = 0; i < kBins; ++i) {
-      c[q][i] = 0;
-#pragma unroll
-      for (int k = 0; k < COPIES; ++k) c[q][i] += h[q][(tid * kBins + i) * COPIES + k];
-      mine[q] += c[q][i];
-    }
-    incl[q] = wave_scan_u32(mine[q]);
-    if (lane == 63) stot[q][wave] = incl[q];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < K; ++q) {
-    // (the totals of the wavefronts before this one)
-    const u32 totals = wave_scan_u32(lane < NW ? stot[q][lane < NW ? lane : 0] : 0u);
-    incl[q] += wave > 0 ? (u32)__builtin_amdgcn_readlane((int)totals, wave > 0 ? wave - 1 : 0) : 0u;
-    u32 start = incl[q] - mine[q];
-    if (all != 0) {                          // (uniform)
-      const u32 first = all - (u32)__builtin_amdgcn_readlane((int)totals, NW - 1);
-      incl[q] += first;
-      start += tid == 0 ? 0u : first;
-      c[q][0] += tid == 0 ? first : 0u;
-    }
-    if (CUM && q == 0) {
-      u32 at = start;
-#pragma unroll
-      for (int i = 0; i < kBins; ++i) {
-        cum[tid * kBins + i] = at;
-        at += c[0][i];
-      }
-    }
-    if (start < r[q] && r[q] <= incl[q]) {                        // exactly one thread
-      u32 at = start;
-      int i = 0;
-      for (; i < kBins - 1; ++i) {
-        if (at + c[q][i] >= r[q]) break;
-        at += c[q][i];
-      }
-      bin[q] = (u32)(tid * kBins + i);
-      before[q] = at;
-    }
-  }
-}
-
 // WHOLE = 1 or 2 (ranks wanted: 2 with a percentile base radius): the kernel sees the set through to its
 // radius.  G + extra workgroups an image are shared out to the sets by the sizes that one round of keys
 // suggests, so that a large set's rows are read by many; each finds the set's tokens and interval itself,

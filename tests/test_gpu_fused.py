@@ -132,3 +132,17 @@ def test_register_resident_edges(B, T, C, G, dtype):
         U.assert_calibration_matches(g, X, p)
         want = O.quantize_act(X, g["gid"], g["clip"], g["scale"], U.oracle_params(p)).reshape(B * T, C)
         assert np.array_equal(U.unpack_device_codes(Q, C), want)
+
+
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+@pytest.mark.parametrize("B,T,C,G", [(128, 20, 64, 4), (171, 20, 64, 3), (8, 40, 32, 64), (9, 40, 32, 64), (1, 1024, 8, 2)])
+def test_workgroup_per_set_and_per_image(B, T, C, G, dtype):
+    """512 sets in all take a workgroup each, more of them one per image; with zeros, empty sets and a
+    percentile, against the oracle."""
+    rng = np.random.default_rng(B + G)
+    X = np.maximum(rng.laplace(0, 1, (B, T, C)) * np.exp(rng.normal(0, 1.5, (B, T, 1))), -0.1).astype(dtype)
+    X[0, : T // 2] = 0
+    for pct in (0.0, 0.95):
+        p = tdq.default_params(G)
+        p.base_pct = pct
+        _check(X, p)
