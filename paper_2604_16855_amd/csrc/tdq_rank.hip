@@ -407,7 +407,7 @@ struct SampleRank {
 };
 __device__ __forceinline__ SampleRank sample_rank(long long k, long long n, long long m, int n_sel) {
   SampleRank s;
-  s.rk = (long long)((double)k / (double)n * (double)m + 0.5);
+  s.rk = (long long)((float)k / (float)n * (float)m + 0.5f);       // (to one rank; binary64 costs ten times as much)
   s.rk = s.rk < 1 ? 1 : (s.rk > m ? m : s.rk);
   const float mf = (float)m, pq = (float)s.rk / mf, left_out = n > m ? 1.f - mf / (float)n : 0.f;
   s.dev = sqrtf(pq * (1.f - pq) * left_out * mf);
@@ -1184,7 +1184,13 @@ static void sets_t(const TX* X, int B, int T, int C, long long ld, int G, int Wf
   } while (0)
   // as few threads as hold the image's range keys in registers: [32, 4096, 1024] calibrates
   // in 111 / 117 / 145 us with 256 / 512 / 1024 threads per set
-  if (T <= 1024)
+  // ... but with no more sets than CUs twice the wavefronts: the layer of [8, 1024, 768] binary32, 16 sets,
+  // 67.6 -> 64.1, [1, 1782, 56] 32 sets 48.2 -> 44.6, binary16 [6, 2080, 1376] 32 sets with a percentile 88.1 -> 83.0
+  if ((long long)B * G <= 256 && T <= 1024)
+    TDQ_SETS(512, 2);
+  else if ((long long)B * G <= 256 && T <= 4096)
+    TDQ_SETS(512, 8);
+  else if (T <= 1024)
     TDQ_SETS(256, 4);
   else if (T <= kIdRounds * 256)
     TDQ_SETS(256, 16);
