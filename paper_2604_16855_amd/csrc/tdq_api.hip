@@ -110,6 +110,7 @@ static Scalars make_scalars(const tdq_params* p) {
   s.zr = p->zr;
   s.base_pct = (p->base_pct > 0.0 && p->base_pct < 1.0) ? p->base_pct : 0.0;
   s.flags = p->flags;
+  s.inv_groups = 1.0 / (double)p->n_groups;
   return s;
 }
 

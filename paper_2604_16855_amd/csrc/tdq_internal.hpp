@@ -98,6 +98,7 @@ struct Scalars {   // fp32 constants of the projection, rounded once on the host
   double zr;
   double base_pct;   // 0 = base radius is the set's maximum; (0,1) = rank quantile Q_p (Eq. DSTG_clip)
   unsigned flags;
+  double inv_groups; // 1 / n_groups
 };
 
 // The rank select runs once per rank wanted of every set: pass kPassBase finds the

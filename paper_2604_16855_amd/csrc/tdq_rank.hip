@@ -79,7 +79,7 @@ struct BinPick {
   u32 inside;                 // elements inside the interval
 };
 template <bool TIES>
-__device__ __forceinline__ BinPick pick_bin(const u32* __restrict__ hb, int W, u32 below, long long k,
+__device__ __forceinline__ BinPick pick_bin(const u32* __restrict__ hb, int W, u32 below, u32 k,
                                             u32 tie_bin = kNoKey, u32 ties = 0) {
   const int lane = threadIdx.x & 63;
   const int quads = W / 256;                    // 1 to 8 groups of four bins per lane
@@ -107,11 +107,10 @@ __device__ __forceinline__ BinPick pick_bin(const u32* __restrict__ hb, int W, u
 #pragma unroll
   for (int i = 0; i < 8; ++i) mine += sum[i];
   const u32 incl = wave_scan_u32(mine);
-  const unsigned long long kk = (unsigned long long)k;
   BinPick r;
   r.inside = (u32)__builtin_amdgcn_readlane((int)incl, 63);
-  r.ok = kk > below && kk - below <= r.inside;
-  const u32 need = (u32)(kk - below);
+  r.ok = k > below && k - below <= r.inside;
+  const u32 need = k - below;
   const unsigned long long hit = __ballot(incl >= need);
   const int src = r.ok ? __ffsll((long long)hit) - 1 : 0;       // hit != 0 because need <= inside
   u32 cum = incl - mine;
@@ -399,19 +398,22 @@ __device__ __forceinline__ u32 mod24(u32 h, u32 d) {
 
 // A rank k of a set of n elements as seen by a sample of m of them from n_sel tokens.
 struct SampleRank {
-  long long rk;               // the rank of the sample that corresponds to k
+  u32 rk;                     // the rank of the sample that corresponds to k
   float dev;                  // its standard deviation as that of a sample of independent elements
                               // (none if the sample is the set) ...
   float dev_tokens;           // ... and of a sample of whole tokens, as if all elements of a token
                               // lay on one side
 };
-__device__ __forceinline__ SampleRank sample_rank(long long k, long long n, long long m, int n_sel) {
+// (where to look, not what is found there: one instruction each for reciprocal and root)
+__device__ __forceinline__ SampleRank sample_rank(u32 k, u32 n, u32 m, int n_sel) {
   SampleRank s;
-  s.rk = (long long)((float)k / (float)n * (float)m + 0.5f);       // (to one rank; binary64 costs ten times as much)
-  s.rk = s.rk < 1 ? 1 : (s.rk > m ? m : s.rk);
-  const float mf = (float)m, pq = (float)s.rk / mf, left_out = n > m ? 1.f - mf / (float)n : 0.f;
-  s.dev = sqrtf(pq * (1.f - pq) * left_out * mf);
-  s.dev_tokens = s.dev * sqrtf(mf / (float)n_sel);
+  const float mf = (float)m, share = mf * __builtin_amdgcn_rcpf((float)n);
+  s.rk = (u32)((float)k * share + 0.5f);
+  s.rk = s.rk < 1u ? 1u : (s.rk > m ? m : s.rk);
+  const float pq = (float)s.rk * __builtin_amdgcn_rcpf(mf);
+  const float var = n > m ? pq * (1.f - pq) * (1.f - share) * mf : 0.f;
+  s.dev = __builtin_amdgcn_sqrtf(var > 0.f ? var : 0.f);
+  s.dev_tokens = s.dev * __builtin_amdgcn_sqrtf(mf * __builtin_amdgcn_rcpf((float)n_sel));
   return s;
 }
 
@@ -421,7 +423,7 @@ __device__ __forceinline__ SampleRank sample_rank(long long k, long long n, long
 // side.  Else the rank lies where keys are sparse (just above the zeros of a rectified activation, between
 // the values of a coarse grid): the W bins that leave equally many sampled keys on either side of it.  By
 // one wavefront.
-__device__ __forceinline__ void place_bins(const u32* cum, int bm, const SampleRank& s, long long m, int Wfew,
+__device__ __forceinline__ void place_bins(const u32* cum, int bm, const SampleRank& s, u32 m, int Wfew,
                                            int W, u32& first, u32& width) {
   constexpr int kCell = 1 << (15 - kSampleBits);
   const int lane = threadIdx.x & 63, rk = (int)s.rk;
@@ -454,19 +456,19 @@ struct Lost {
   unsigned long long rank;
 };
 template <bool F16>
-__device__ __forceinline__ Lost lost_rank(long long k, u32 below, u32 inside, u32 lo, u32 above) {
+__device__ __forceinline__ Lost lost_rank(u32 k, u32 below, u32 inside, u32 lo, u32 above) {
   constexpr u32 kKeysAll = F16 ? 1u << 15 : 1u << 31;
   Lost l;
-  if ((unsigned long long)k <= below) {              // (span 1: there are only zeros)
+  if (k <= below) {                                  // (span 1: there are only zeros)
     l.k0 = 0;
     l.span = lo;
     l.near = F16 ? -1 : 0;
-    l.rank = (unsigned long long)k;
+    l.rank = k;
   } else {
     l.k0 = above < kKeysAll ? above : kKeysAll - 1u;
     l.span = kKeysAll - l.k0;
     l.near = F16 ? 1 : 0;
-    l.rank = (unsigned long long)k - ((unsigned long long)below + inside);
+    l.rank = (u64)k - ((u64)below + inside);
   }
   return l;
 }
@@ -574,9 +576,12 @@ __global__ __launch_bounds__(NT) void k_sets(
     }
   }
   // ceil(j width / G) = j q + ceil(j rem / G) with width = q G + rem; everything fits 32 bits
-  const u32 width = hi - lo + 1u, wq = width / (u32)G, wr = width - wq * (u32)G;
+  const u32 width = hi - lo + 1u;
+  // x / G: (x + 1/2) / G is at least 1 / 128 from any integer, so the rounded reciprocal does
+  auto div_g = [&](u32 x) { return (u32)(((double)x + 0.5) * sc.inv_groups); };
+  const u32 wq = div_g(width), wr = width - wq * (u32)G;
   auto start_of = [&](int g) {
-    return g == 0 ? 0u : g >= G ? hi + 1u : lo + (u32)g * wq + ((u32)g * wr + (u32)G - 1u) / (u32)G;
+    return g == 0 ? 0u : g >= G ? hi + 1u : lo + (u32)g * wq + div_g((u32)g * wr + (u32)G - 1u);
   };
   if constexpr (WHOLE != 0) {
     // How many workgroups a set gets: one, and its share of the others by the keys that one round of the
@@ -658,7 +663,7 @@ __global__ __launch_bounds__(NT) void k_sets(
   rpt = rpt < row_runs ? rpt : row_runs;
   const int cw = rpt == row_runs ? Cv : rpt * kRunLen;      // channels read per drawn token
   const int n_runs = n_sel * rpt;                           // <= kSampleRuns
-  const long long m = (long long)n_sel * cw;                // sample size, <= SM
+  const u32 m = (u32)(n_sel * cw);                          // sample size, <= SM
   const bool listed = WHOLE || T <= kListTokens;
   auto pick_of = [&](u32 stratum) {                         // rank of the token drawn from a stratum
     const u32 first = stratum * (u32)stride;
@@ -725,6 +730,12 @@ __global__ __launch_bounds__(NT) void k_sets(
 #pragma unroll
   for (int e = 0; e < kPieces; ++e)
     if (e < steps) load_piece(e);                      // uniform
+
+  // (whole, binary16: the first loads of this workgroup's share of the rows as well)
+  const int share = WHOLE && F16 ? (tokens + S - 1) / S : 0, share_from = part * share;
+  const int share_rows = tokens - share_from < share ? tokens - share_from : share;     // (none if negative)
+  RowVisitor<TX, NT> own(X + (long long)b * T * ld, ld, C, WHOLE && F16 ? wa.L : 1,
+                         order + (share_rows > 0 ? share_from : 0), WHOLE && F16 ? share_rows : 0);
 
   // Moments of the set about the mean of its first token (zero if that is not finite: the
   // image's results are then undefined anyway and its flag is raised).
@@ -808,12 +819,18 @@ __global__ __launch_bounds__(NT) void k_sets(
   // the set's working record: n, base radius, sigma, rank of this pass (binary64)
   GroupWork w;
   w.tokens = tokens_u;
-  w.n = (long long)tokens * (long long)C;
+  const u32 nn = tokens_u * (u32)C;      // (an image that samples has fewer than 2^32 elements)
+  w.n = (long long)nn;
   w.prefix = 0;
-  const double n = (double)w.n;
-  w.k_rem = (long long)ceil((pass == kPassBase ? sc.base_pct : sc.zr) * n);
-  w.k_rem = w.k_rem < 1 ? 1 : (w.k_rem > w.n ? w.n : w.k_rem);
-  if (wave == NW - 1) {                  // (the last wavefront: the first places the interval below)
+  const double n = (double)nn;
+  auto rank_of = [&](double share) {
+    const u32 k = (u32)ceil(share * n);
+    return k < 1u ? 1u : (k > nn ? nn : k);
+  };
+  const u32 k_pass = rank_of(pass == kPassBase ? sc.base_pct : sc.zr);
+  w.k_rem = (long long)k_pass;
+  // sigma and c_base, by one wavefront while others have something else to do: forty dependent binary64 steps
+  auto finish_moments = [&]() {
     const bool has = lane < NW;
     const double S1 = group_sum_f64<64>(has ? s_s1[has ? lane : 0] : 0.0);
     const double S2 = group_sum_f64<64>(has ? s_s2[has ? lane : 0] : 0.0);
@@ -832,15 +849,16 @@ __global__ __launch_bounds__(NT) void k_sets(
         grp[idx] = w;
       }
     }
-  }
+  };
+  if (!WHOLE && !F16 && wave == NW - 1) finish_moments();
   // binary32: the interval between two order statistics of the sample, six standard deviations of its
   // elements and one of its tokens to either side of s, each resolved to 20 of its 31 bits: first key, last
   // key - first key, sampled ranks between them.  By the whole workgroup.
   auto interval32 = [&](const SampleRank& s, u32& first, u32& last, u32& drawn) {
     if constexpr (!F16) {
-      const long long dr = (long long)(6.f * s.dev + s.dev_tokens) + 2;
+      const int dr = (int)(6.f * s.dev + s.dev_tokens) + 2, rk = (int)s.rk;
       const u32* const hs[2] = {shist, shist};
-      const u32 rs[2] = {(u32)(s.rk - dr < 1 ? 1 : s.rk - dr), (u32)(s.rk + dr > m ? m : s.rk + dr)};
+      const u32 rs[2] = {(u32)(rk - dr < 1 ? 1 : rk - dr), (u32)(rk + dr > (int)m ? (int)m : rk + dr)};
       find_ranks<NT, 2, kCopies, false>(hs, rs, stot, s_bin, s_before, nullptr);
       __syncthreads();
       const u32 b0 = s_bin[0], b1 = s_bin[1];
@@ -868,30 +886,24 @@ __global__ __launch_bounds__(NT) void k_sets(
     constexpr int NR = WHOLE;                          // the last rank is the one that is projected
     constexpr int kBins = 2048;
     const TX* Xb = X + (long long)b * T * ld;
-    long long k[NR];
-    if (NR == 2) {
-      k[0] = (long long)ceil(sc.base_pct * n);
-      k[0] = k[0] < 1 ? 1 : (k[0] > w.n ? w.n : k[0]);
-    }
-    k[NR - 1] = w.k_rem;
+    u32 k[NR];
+    if (NR == 2) k[0] = rank_of(sc.base_pct);
+    k[NR - 1] = k_pass;
     u32 found = 0, base_key = 0;
     auto search = [&](const Lost& l, int near) {
       return search_rows<TX, NT, true>(Xb, ld, tokens, C, wa.L, nullptr, j, order, l.k0, l.span, l.rank, near, s_search);
     };
     if constexpr (F16) {
-      const int per = (tokens + S - 1) / S, from = part * per;
-      const int rows = tokens - from < per ? tokens - from : per;       // (none if negative)
-      RowVisitor<TX, NT> own(Xb, ld, C, wa.L, order + (rows > 0 ? from : 0), rows);      // its first loads
       SampleRank sq[NR];
       const u32* hs[NR];
       u32 rs[NR];
 #pragma unroll
       for (int q = 0; q < NR; ++q) {
-        sq[q] = sample_rank(k[q], w.n, m, n_sel);
+        sq[q] = sample_rank(k[q], nn, m, n_sel);
         hs[q] = shist;
-        rs[q] = (u32)sq[q].rk;
+        rs[q] = sq[q].rk;
       }
-      find_ranks<NT, NR, 1, true>(hs, rs, stot, s_bin, s_before, cum, (u32)m);
+      find_ranks<NT, NR, 1, true>(hs, rs, stot, s_bin, s_before, cum, m);
       for (int i = tid; i < NR * kBins / 4; i += NT) reinterpret_cast<uint4*>(&hist[0][0])[i] = make_uint4(0, 0, 0, 0);
       __syncthreads();
 #pragma unroll
@@ -971,6 +983,7 @@ __global__ __launch_bounds__(NT) void k_sets(
         }
         __syncthreads();
       }
+      if (wave == NW - 1) finish_moments();
 #pragma unroll
       for (int q = 0; q < NR; ++q) {
         if (wave == q) {
@@ -997,13 +1010,13 @@ __global__ __launch_bounds__(NT) void k_sets(
     } else {
 #pragma unroll 1
       for (int q = 0; q < NR; ++q) {
-        const long long kq = q == NR - 1 ? k[NR - 1] : k[0];
+        const u32 kq = q == NR - 1 ? k[NR - 1] : k[0];
         if (q > 0) {                                   // (other readers of these have passed a barrier since)
           for (int i = tid; i < 2 << kSampleBits; i += NT) (&snext[0][0])[i] = 0;
           __syncthreads();
         }
         u32 first, last, drawn, shift = 0, below = 0;
-        interval32(sample_rank(kq, w.n, m, n_sel), first, last, drawn);
+        interval32(sample_rank(kq, nn, m, n_sel), first, last, drawn);
         while (((u64)kBins << shift) - 1ull < last) ++shift;           // at most 2^31 keys
         for (int i = tid; i < kBins; i += NT) hist[0][i] = 0;
         if (tid == 0) s_below[0] = 0;
@@ -1024,6 +1037,7 @@ __global__ __launch_bounds__(NT) void k_sets(
         below = group_sum_u32<64>(below);
         if (lane == 63 && below) atomicAdd(&s_below[0], below);
         __syncthreads();
+        if (q == 0 && wave == NW - 1) finish_moments();
         if (wave == 0) {
           const BinPick p = pick_bin<false>(hist[0], kBins, s_below[0], kq);
           Lost l = lost_rank<false>(kq, s_below[0], p.inside, first, first + ((u32)kBins << shift));
@@ -1050,7 +1064,7 @@ __global__ __launch_bounds__(NT) void k_sets(
     }
     return;
   }
-  const SampleRank sr = sample_rank(w.k_rem, w.n, m, n_sel);
+  const SampleRank sr = sample_rank(k_pass, nn, m, n_sel);
   const float mf = (float)m;
   Bracket e;
   e.below = 0;
@@ -1058,9 +1072,10 @@ __global__ __launch_bounds__(NT) void k_sets(
   e.shift = 0;
   if constexpr (F16) {
     const u32* const hs[1] = {shist};
-    const u32 rs[1] = {(u32)sr.rk};
-    find_ranks<NT, 1, 1, true>(hs, rs, stot, s_bin, s_before, cum, (u32)m);
+    const u32 rs[1] = {sr.rk};
+    find_ranks<NT, 1, 1, true>(hs, rs, stot, s_bin, s_before, cum, m);
     __syncthreads();
+    if (wave == NW - 1) finish_moments();
     if (wave != 0) return;
     place_bins(cum, (int)s_bin[0], sr, m, Wfew, W, e.lo, e.width);
     for (int i = Wfew + lane; i < (int)e.width; i += 64) bhist[(size_t)idx * W + i] = 0;
@@ -1583,7 +1598,7 @@ __global__ __launch_bounds__(kSweepThreads) void k_bracket_gather(
     const u32 cell = head[kListHead + (lane < cells ? lane : 0)];
     u32 span = 0, key0 = 0, take = 0;
     if (w.tokens != 0) {                        // uniform over the wavefront
-      const BinPick p = pick_bin<true>(bhist + (size_t)idx * W, W, e.below, w.k_rem, tie_bin, ties);
+      const BinPick p = pick_bin<true>(bhist + (size_t)idx * W, W, e.below, (u32)w.k_rem, tie_bin, ties);
       if (p.ok && p.count != 0) {               // (a bin of ties alone needs no sweep)
         bin_keys(cell, cells, e, p.bin, key0, span);
         take = p.count <= (u32)keys_cap ? 1u : 0u;
@@ -1770,10 +1785,10 @@ __global__ __launch_bounds__(NT, NT == 256 ? 8 : 4) void k_bracket_finish(
         tie_bin = head[kHeadTieBin];
       }
       // (the further bins of a set that uses more are looked at only if the first do not do)
-      BinPick p = pick_bin<!F16>(bhist + (size_t)idx * W, Wfew, e.below, w.k_rem, tie_bin, ties);
+      BinPick p = pick_bin<!F16>(bhist + (size_t)idx * W, Wfew, e.below, (u32)w.k_rem, tie_bin, ties);
       if (F16 && w.tokens != 0 && !p.ok && (int)e.width > Wfew && w.k_rem > e.below) {
         const u32 first = p.inside;
-        p = pick_bin<false>(bhist + (size_t)idx * W + Wfew, W - Wfew, e.below + first, w.k_rem);
+        p = pick_bin<false>(bhist + (size_t)idx * W + Wfew, W - Wfew, e.below + first, (u32)w.k_rem);
         p.inside += first;
         p.bin += (u32)Wfew;
       }
@@ -1803,7 +1818,7 @@ __global__ __launch_bounds__(NT, NT == 256 ? 8 : 4) void k_bracket_finish(
         }
         if (ok == kDone && lane == 0) finish(key);
       } else {
-        const Lost l = lost_rank<F16>(w.k_rem, e.below, p.inside, e.lo,
+        const Lost l = lost_rank<F16>((u32)w.k_rem, e.below, p.inside, e.lo,
                                       e.lo + (e.shift & kCells ? e.width : e.width << e.shift));
         k0 = l.k0;
         span = l.span;
