@@ -109,12 +109,12 @@ hipError_t launch_tokenize_chw(const void* X, tdq_dtype dt, int B, int C, int T,
 // feature map yields the token-major copy Xt AND every token's range and moments
 // (r_t = max_c |x|, mean_t, M2_t = sum_c (x - mean_t)^2; Sec. 4.2), so a convolutional input costs
 // the token-set path one extra write of X, not an extra read and write.  A workgroup
-// owns TT consecutive tokens of one image and walks the channel axis in tiles of 64:
+// owns TT consecutive tokens of one image and walks the channel axis in tiles of 64 or 128:
 // every thread keeps the partial statistics of its 2 tokens across the tiles; at the end
 // the lanes that share a token (adjacent ones) are reduced with DPP.  The sums are taken
 // about a per-token pivot taken from the first tile, see "Moments" in tdq_device.hpp:
 // binary32 input, the token's first channel; binary16 input, the mean of its first
-// min(C, 64) channels.  The map is read once, so a token cannot be summed again about a
+// min(C, 64 or 128) channels.  The map is read once, so a token cannot be summed again about a
 // better pivot as in the token-major sweep; the mean of 64 of its values lies within
 // sigma_t sqrt(C / 64) of the token's mean (Cauchy-Schwarz), which bounds what the
 // binary32 partial sums can cost its M2 at (1 + C / 64) * 3 * 2^-24 per partial.
@@ -124,22 +124,24 @@ hipError_t launch_tokenize_chw(const void* X, tdq_dtype dt, int B, int C, int T,
 // neighbouring binary16 tokens with one LDS word.  [8, 320, 44, 44] binary16: this kernel 18.6
 // us with 256 bytes of tokens, 11.7 so, 14.2 / 18.3 with 128 / 256 channels per tile; the
 // whole calibration of [4, 4096, 64, 64] 225 -> 138 us, of [32, 1024, 64, 64] 195 -> 190.
-constexpr int kStatsTileC = 64;                // channels per tile
-
-template <typename T>
+// TC channels x PP 16-byte pieces of tokens per tile: 64 x 8, or 128 x 4 where that makes fewer workgroups than
+// CUs (half the tiles in a chain, twice the workgroups).  Calibration, us, 64 x 8 and 128 x 4: [8, 320, 44, 44]
+// (248 workgroups of 64 x 8) 29.4 and 27.0, [2, 2000, 20, 20] (14) 51.0 and 34.8, [1, 512, 30, 30] (15) 25.7 and 21.3;
+// but [16, 320, 44, 44] (496) 32.2 and 32.9, [32, 256, 40, 40] (800) 36.4 and 40.3: half a line a load.
+template <typename T, int TC, int PP>
 __global__ __launch_bounds__(256) void k_tokenize_stats_chw(
     const T* __restrict__ X, long long ld_c, long long ld_b, int C, int T_, T* __restrict__ Xt,
     long long ld_xt, int vin_ok, int vout_ok, float* __restrict__ r, double* __restrict__ mean,
     double* __restrict__ m2, SelectClear cl) {
   constexpr bool F16 = sizeof(T) == 2;
   constexpr int E = 16 / (int)sizeof(T);
-  constexpr int TC = kStatsTileC;
-  constexpr int TT = 8 * E;                  // 128 bytes of every channel
+  constexpr int TT = PP * E;                 // 128 or 64 bytes of every channel
   constexpr int PITCH = TT + 4 / (int)sizeof(T);   // one bank further per row
   constexpr int PQ = TC / E;                 // lanes per token
   constexpr int NP = TT * PQ / 256;          // tokens per thread (2)
   constexpr int TPW = F16 ? 2 : 1;           // tokens a thread reads together (one 32-bit word)
-  constexpr int LOADS = TC / 32;             // 16-byte loads per thread and tile
+  constexpr int LOADS = TC * PP / 256;       // 16-byte loads per thread and tile
+  constexpr int ROWS = 256 / PP;             // channels per load
   __shared__ __attribute__((aligned(16))) T tile[TC][PITCH];
 
   const int t0 = (int)((blockIdx.z * gridDim.x + blockIdx.x) * TT), b = blockIdx.y;
@@ -157,12 +159,12 @@ __global__ __launch_bounds__(256) void k_tokenize_stats_chw(
   for (int i = 0; i < NP; ++i) { kmax[i] = 0; a1[i] = 0.0; a2[i] = 0.0; P[i] = 0; }
 
   // the next tile's global loads are in flight while the current one is processed
-  const int lp = tid & 7, ltok = t0 + lp * E;
+  const int lp = tid % PP, ltok = t0 + lp * E;
   uint4 stage[LOADS];
   auto load_tile = [&](int c0) {
 #pragma unroll
     for (int i = 0; i < LOADS; ++i) {
-      const int c = c0 + (tid >> 3) + 32 * i;
+      const int c = c0 + tid / PP + ROWS * i;
       if (c < C && vin_ok && ltok + E <= T_) {
         stage[i] = *reinterpret_cast<const uint4*>(xb + (long long)c * ld_c + ltok);
       } else {
@@ -180,7 +182,7 @@ __global__ __launch_bounds__(256) void k_tokenize_stats_chw(
   for (int c0 = 0; c0 < C; c0 += TC) {
 #pragma unroll
     for (int i = 0; i < LOADS; ++i) {
-      u32* d = reinterpret_cast<u32*>(&tile[(tid >> 3) + 32 * i][lp * E]);
+      u32* d = reinterpret_cast<u32*>(&tile[tid / PP + ROWS * i][lp * E]);
       d[0] = stage[i].x;
       d[1] = stage[i].y;
       d[2] = stage[i].z;
@@ -290,8 +292,13 @@ static hipError_t tokenize_stats_t(const T* X, int B, int C, int T_, long long l
   const int vout_ok = ((reinterpret_cast<uintptr_t>(Xt) & 15) == 0 && ld_xt % E == 0) ? 1 : 0;
   // (a grid has fewer than 2^32 threads along an axis: 2^29 tokens of binary32 are 2^24 workgroups)
   const unsigned tiles = (unsigned)((T_ + 8 * E - 1) / (8 * E)), most = 1u << 22;
+  if (C > 64 && (long long)tiles * B <= 256) {
+    hipLaunchKernelGGL((k_tokenize_stats_chw<T, 128, 4>), dim3((unsigned)((T_ + 4 * E - 1) / (4 * E)), (unsigned)B),
+                       dim3(256), 0, st, X, ld_c, ld_b, C, T_, Xt, ld_xt, vin_ok, vout_ok, r, mean, m2, cl);
+    return hipGetLastError();
+  }
   const dim3 grid(tiles < most ? tiles : most, (unsigned)B, (tiles + most - 1) / most);
-  hipLaunchKernelGGL((k_tokenize_stats_chw<T>), grid, dim3(256), 0, st, X, ld_c, ld_b, C, T_, Xt,
+  hipLaunchKernelGGL((k_tokenize_stats_chw<T, 64, 8>), grid, dim3(256), 0, st, X, ld_c, ld_b, C, T_, Xt,
                      ld_xt, vin_ok, vout_ok, r, mean, m2, cl);
   return hipGetLastError();
 }

@@ -202,3 +202,21 @@ def test_calibrate_chw_of_many_tokens():
     assert torch.equal(Xt.view(-1), X.view(-1))
     assert clip.item() == X.abs().max().item() and int(gid.max()) == 0
     assert tdq.device_status(ws) == 0
+
+
+@pytest.mark.parametrize("B,C,H,W,dtype", [(8, 65, 32, 64, np.float16), (9, 65, 32, 64, np.float16),
+                                           (9, 129, 31, 65, np.float16), (8, 129, 31, 33, np.float32),
+                                           (9, 129, 31, 33, np.float32), (2, 257, 3, 11, np.float16),
+                                           (1, 128, 4, 4, np.float32)])
+def test_feature_map_tiles(B, C, H, W, dtype):
+    """256 workgroups of 64 x 8 tiles and more, where the tile changes; one and several tiles of channels,
+    tokens that end inside a tile."""
+    X = _feature_map(B, C, H, W, dtype, 3)
+    p = tdq.default_params(5)
+    Xt, gid, clip, scale, stats, ws = tdq.tdq_calibrate_groups_chw(torch.from_numpy(X).to(U.dev()), p, want_stats=True)
+    torch.cuda.synchronize()
+    ref = O.tokenize_chw(X)
+    assert np.array_equal(Xt.cpu().numpy().view(np.uint8), ref.view(np.uint8)) and tdq.device_status(ws) == 0
+    g = dict(gid=gid.cpu().numpy(), clip=clip.cpu().numpy(), scale=scale.cpu().numpy(),
+             stats=tdq.stats_to_numpy(stats))
+    U.assert_calibration_matches(g, ref, p)
