@@ -805,7 +805,11 @@ __global__ __launch_bounds__(GEMM_THREADS, (MT * NT >= 16 ? 1 : 2)) void k_w4a4_
 //     the last stage;
 //   * K tails: 16-byte pieces past the end of the rows are fetched from the row's first
 //     piece instead and the activation fragments are masked to the bytes that count (a zero
-//     in one operand is enough).
+//     in one operand is enough); the half of the last stage that no byte reaches is left out, and one that
+//     is whole is not masked.  With several workgroups on a CU the loop takes what its instructions take, and
+//     a masked stage has twice those of another (15488 x 320 x 640: 10.8 -> 9.4 us, 32768 x 320 x 1280 38.7 ->
+//     35.2).  That stage stands behind the loop, so that the loop is whole stages only (8192 x 768 x 768 9.9 -> 9.5,
+//     131072 x 1000 x 1024 176 -> 169).
 // ---------------------------------------------------------------------------
 template <typename OUT, int MT, int NT>
 __global__ __launch_bounds__(GEMM_THREADS, (MT * NT >= 4 ? 2 : MT * NT >= 2 ? 3 : 6)) void k_w4a4_gemm_ring(
@@ -884,20 +888,20 @@ __global__ __launch_bounds__(GEMM_THREADS, (MT * NT >= 4 ? 2 : MT * NT >= 2 ? 3 
 
   const int frow = lane & 31, fh = lane >> 5, swz = (frow >> 2) & 3;
   const int a_row = (wm * 32 * MT + frow) * BKB, b_row = BM * BKB + (wn * 32 * NT + frow) * BKB;
-  auto stage = [&](int kt, bool tail) {
+  // halves KS0 and (if more than one) the next of a stage, 64 codes of K each; masked: `keep` bytes of the last count
+  auto stage = [&](int kt, auto first, auto halves, bool masked, int keep) {
     const uint8_t* slot = ring + (kt & (D - 1)) * SLOT;
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
+    for (int ks = decltype(first)::value; ks < decltype(first)::value + decltype(halves)::value; ++ks) {
       const int off = ((2 * ks + fh) ^ swz) * 16;
       uint4 fa[MT], fb[NT];
 #pragma unroll
       for (int i = 0; i < MT; ++i) fa[i] = *reinterpret_cast<const uint4*>(slot + a_row + i * 32 * BKB + off);
 #pragma unroll
       for (int j = 0; j < NT; ++j) fb[j] = *reinterpret_cast<const uint4*>(slot + b_row + j * 32 * BKB + off);
-      if (tail) {
-        const int keep = kbytes - (kt * BKB + ks * 32 + fh * 16);       // bytes of this piece that count
+      if (masked) {
 #pragma unroll
-        for (int i = 0; i < MT; ++i) mask_piece(fa[i], keep);
+        for (int i = 0; i < MT; ++i) mask_piece(fa[i], keep - fh * 16);
       }
 #pragma unroll
       for (int set = 0; set < 2; ++set) {
@@ -914,6 +918,9 @@ __global__ __launch_bounds__(GEMM_THREADS, (MT * NT >= 4 ? 2 : MT * NT >= 2 ? 3 
       }
     }
   };
+  typedef std::integral_constant<int, 0> C0;
+  typedef std::integral_constant<int, 1> C1;
+  typedef std::integral_constant<int, 2> C2;
   for (int kt = 0; kt < k_tiles; ++kt) {
     // stage kt has landed when at most the loads of the stages after it are outstanding
     const int newer = k_tiles - 1 - kt < D - 2 ? k_tiles - 1 - kt : D - 2;
@@ -926,10 +933,16 @@ __global__ __launch_bounds__(GEMM_THREADS, (MT * NT >= 4 ? 2 : MT * NT >= 2 ? 3 
     __syncthreads();
     // the slot of stage kt - 1: every wavefront drained its reads before this barrier
     if (kt + D - 1 < k_tiles) load_stage(kt + D - 1);
-    if ((kt + 1) * BKB <= kbytes)
-      stage(kt, false);
+    if ((kt + 1) * BKB <= kbytes) stage(kt, C0(), C2(), false, 0);
+  }
+  // the last stage if it is not whole: the halves that hold something, masked if they are not whole either
+  const int rest = kbytes - (k_tiles - 1) * BKB;                // uniform
+  if (rest < BKB) {
+    if (rest >= 32)
+      stage(k_tiles - 1, C0(), C1(), false, 0);
     else
-      stage(kt, true);
+      stage(k_tiles - 1, C0(), C1(), true, rest);
+    if (rest > 32) stage(k_tiles - 1, C1(), C1(), true, rest - 32);
   }
 
   if (tid < BM) sRow[tid] = acc_dump ? my_rs : my_rs * 0.00390625f;     // takes out the factor 256 (exact)
