@@ -223,7 +223,8 @@ def test_f6_path_end_to_end():
     (1, 1, 1, False, torch.float32), (5, 31, 3, True, torch.float32), (64, 33, 64, False, torch.float32),
     (129, 64, 130, True, torch.float32), (300, 320, 200, False, torch.float16),
     (256, 1280, 320, True, torch.float32), (130, 4100, 140, False, torch.float32),
-    (200, 128, 129, True, torch.float16)])
+    (200, 128, 129, True, torch.float16), (70, 384, 66, False, torch.float32), (70, 512, 66, True, torch.float32),
+    (70, 513, 66, False, torch.float16)])      # three, four and five stages: the last three load nothing
 def test_f6_block_scaled_linear_equals_the_int8_one(M, K, N, with_bias, out_dtype):
     """tdq_w4a4_linear_blocks_f6: the same bits as tdq_w4a4_linear_blocks, and within the
     bound of the binary32 evaluation of the oracle's Algorithm 1 linear."""
