@@ -164,11 +164,15 @@ static bool samples_rank(tdq_dtype dt, int B, int T, int C, int G, bool exact_on
 //     [14, 5850, 160], 29 Ki, percentile, 97.9 against 122.3.
 //   * binary32 reads a set's rows twice, so one workgroup sees all of a set: [2, 1400, 32] (45 Ki elements) 38.6
 //     against 44.7, [5, 1280, 84] (107 Ki) 60.5 against 47.4, [1, 377, 416] (157 Ki) 84.0 against 48.2.
+//   * Up to 1536 sets in all: more workgroups of 512 threads than the chip holds at once take turns with a chain
+//     each, where k_sets has 256 threads and the sweep's workgroups serve all sets.  Calibration, [49, 74, 832] with 32
+//     sets (1568) 31.0 against 29.8, [58, 20, 9] with 32 42.8 against 36.6, [64, 322, 56] with 64 55.7 against 45.6; but
+//     [62, 162, 10] with 24 (1488) 37.4 against 40.0.
 //   * Two ranks share the set's words of the workspace if several workgroups meet in them: 512 bins each are
 //     the least.
 static int whole_extra(tdq_dtype dt, int B, int T, int C, int G, bool two_ranks) {
   const long long e = (long long)T * C;
-  if (T > kWholeTokens) return -1;
+  if (T > kWholeTokens || (long long)B * G > 1536) return -1;
   if (dt == TDQ_F32) return e <= 57344 ? 0 : -1;
   long long extra = e / 8192;
   const long long most = 512 / B - G;

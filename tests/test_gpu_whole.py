@@ -19,6 +19,7 @@ def _extra(dt, B, T, C, G, pct=0.0):
     (tdq.TDQ_F16, 32, 1024, 512, 15, 0.0, -1), (tdq.TDQ_F16, 32, 128, 1024, 15, 0.0, 1),  # 512 groups
     (tdq.TDQ_F16, 32, 129, 1024, 15, 0.0, -1), (tdq.TDQ_F16, 64, 64, 1024, 16, 0.0, 0),
     (tdq.TDQ_F16, 1, 512, 64, 17, 0.99, -1), (tdq.TDQ_F16, 1, 512, 64, 16, 0.99, 4),       # words for two ranks
+    (tdq.TDQ_F16, 96, 50, 32, 16, 0.0, 0), (tdq.TDQ_F16, 97, 50, 32, 16, 0.0, -1),          # 1536 sets
     (tdq.TDQ_F16, 1, 127, 64, 17, 0.99, 0), (tdq.TDQ_F16, 1, 100, 64, 65, 0.0, -1),
     (tdq.TDQ_F32, 2, 896, 64, 8, 0.0, 0), (tdq.TDQ_F32, 2, 897, 64, 8, 0.99, -1),
 ])
