@@ -158,27 +158,32 @@ static bool samples_rank(tdq_dtype dt, int B, int T, int C, int G, bool exact_on
 // four).
 //   * A workgroup for every 8 Ki elements, and no more than 512 in all (two per CU): [8, 121, 512] with 16 sets
 //     22.1 / 22.0 / 21.1 with 64 / 16 / 8 Ki, [16, 484, 320] 35.8 / 34.2 / 33.2.
-//   * No more than 64 Ki elements for each (all tokens may be in one set): every workgroup of a set repeats the
-//     search for its tokens and its interval, so a large batch is better off with one sweep over all sets.
-//     [21, 536, 1344], 80 Ki each, 77.3 against 75.0; [28, 187, 1984], 124 Ki, 71.4 against 68.8; but
+//   * No more than 40 Ki elements for each (all tokens may be in one set), 64 Ki with two ranks: every workgroup of
+//     a set repeats the search for its tokens and its interval, so a large batch is better off with one sweep over
+//     all sets.  [21, 536, 1344], 80 Ki each, 77.3 against 75.0; [28, 187, 1984], 124 Ki, 71.4 against 68.8;
+//     calibration of values on a grid, which meet in few words of LDS, [17, 5107, 131], 44 Ki, 60.8 against 46.8; but
 //     [14, 5850, 160], 29 Ki, percentile, 97.9 against 122.3.
 //   * binary32 reads a set's rows twice, so one workgroup sees all of a set: [2, 1400, 32] (45 Ki elements) 38.6
 //     against 44.7, [5, 1280, 84] (107 Ki) 60.5 against 47.4, [1, 377, 416] (157 Ki) 84.0 against 48.2.
 //   * Up to 1536 sets in all: more workgroups of 512 threads than the chip holds at once take turns with a chain
 //     each, where k_sets has 256 threads and the sweep's workgroups serve all sets.  Calibration, [49, 74, 832] with 32
 //     sets (1568) 31.0 against 29.8, [58, 20, 9] with 32 42.8 against 36.6, [64, 322, 56] with 64 55.7 against 45.6; but
-//     [62, 162, 10] with 24 (1488) 37.4 against 40.0.
+//     [62, 162, 10] with 24 (1488) 37.4 against 40.0.  binary32, whose kernel needs more registers: up to 1024, 512
+//     with two ranks ([42, 3, 2424] with 32, 1344 sets, 48.2 against 41.9; percentile [52, 25, 8] with 16, 832 sets,
+//     72.4 against 60.4, [120, 13, 3821] with 5, 600 sets, 137 against 117; but [292, 187, 8] with 2, 584, 43.0
+//     against 79.8).
 //   * Two ranks share the set's words of the workspace if several workgroups meet in them: 512 bins each are
 //     the least.
 static int whole_extra(tdq_dtype dt, int B, int T, int C, int G, bool two_ranks) {
   const long long e = (long long)T * C;
-  if (T > kWholeTokens || (long long)B * G > 1536) return -1;
+  const long long sets = (long long)B * G;
+  if (T > kWholeTokens || sets > (dt == TDQ_F16 ? 1536 : two_ranks ? 512 : 1024)) return -1;
   if (dt == TDQ_F32) return e <= 57344 ? 0 : -1;
   long long extra = e / 8192;
   const long long most = 512 / B - G;
   if (extra > most) extra = most > 0 ? most : 0;
   if (two_ranks && extra > 0 && bracket_bins(G) < 1024) return -1;
-  if (e > 65536 * (extra + 1)) return -1;
+  if (e > (two_ranks ? 65536 : 40960) * (extra + 1)) return -1;
   return (int)extra;
 }
 

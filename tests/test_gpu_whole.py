@@ -16,8 +16,11 @@ def _extra(dt, B, T, C, G, pct=0.0):
 @pytest.mark.parametrize("dt,B,T,C,G,pct,extra", [
     (tdq.TDQ_F16, 8, 121, 512, 16, 0.0, 7), (tdq.TDQ_F16, 1, 7744, 64, 16, 0.0, 60),
     (tdq.TDQ_F16, 1, 8192, 8, 16, 0.0, 8), (tdq.TDQ_F16, 1, 8193, 8, 16, 0.0, -1),
-    (tdq.TDQ_F16, 32, 1024, 512, 15, 0.0, -1), (tdq.TDQ_F16, 32, 128, 1024, 15, 0.0, 1),  # 512 groups
-    (tdq.TDQ_F16, 32, 129, 1024, 15, 0.0, -1), (tdq.TDQ_F16, 64, 64, 1024, 16, 0.0, 0),
+    (tdq.TDQ_F16, 32, 1024, 512, 15, 0.0, -1), (tdq.TDQ_F16, 32, 80, 1024, 15, 0.0, 1),   # 512 groups
+    (tdq.TDQ_F16, 32, 81, 1024, 15, 0.0, -1), (tdq.TDQ_F16, 64, 40, 1024, 16, 0.0, 0),
+    (tdq.TDQ_F16, 32, 128, 1024, 15, 0.99, 1), (tdq.TDQ_F16, 32, 129, 1024, 15, 0.99, -1),
+    (tdq.TDQ_F32, 64, 20, 64, 16, 0.0, 0), (tdq.TDQ_F32, 65, 20, 64, 16, 0.0, -1),
+    (tdq.TDQ_F32, 32, 20, 64, 16, 0.99, 0), (tdq.TDQ_F32, 33, 20, 64, 16, 0.99, -1),
     (tdq.TDQ_F16, 1, 512, 64, 17, 0.99, -1), (tdq.TDQ_F16, 1, 512, 64, 16, 0.99, 4),       # words for two ranks
     (tdq.TDQ_F16, 96, 50, 32, 16, 0.0, 0), (tdq.TDQ_F16, 97, 50, 32, 16, 0.0, -1),          # 1536 sets
     (tdq.TDQ_F16, 1, 127, 64, 17, 0.99, 0), (tdq.TDQ_F16, 1, 100, 64, 65, 0.0, -1),
