@@ -1259,6 +1259,7 @@ static void sets_whole_t(const TX* X, int B, int T, int C, long long ld, int G, 
     else TDQ_WHOLE_RD(16, SM);                                                   \
   } while (0)
   static_assert(kWholeTokens == 512 * kIdRounds, "a thread holds its range keys in registers");
+  // (16 Ki sampled elements: with 8 Ki a set of [2, 1024, 768], 16 sets, values clamped to [0, 6], missed its rank)
   if constexpr (sizeof(TX) == 4) TDQ_WHOLE(8192);
   else TDQ_WHOLE(16384);
 #undef TDQ_WHOLE
