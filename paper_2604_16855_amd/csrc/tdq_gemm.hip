@@ -109,6 +109,35 @@ __device__ __forceinline__ void store_out_vec<_Float16>(_Float16* p, const float
   __builtin_nontemporal_store(v, reinterpret_cast<h8v*>(p));
 }
 
+// The first `rows` of 32 rows and `cols` of 64 columns of results, staged in LDS by the wavefront, to rows that
+// need not start or end on 16-byte boundaries: neighbouring lanes take neighbouring outputs, with few columns of
+// several rows, so that an instruction writes runs of lines, and whole groups of rows without a branch per row.
+// (A run of outputs per lane instead, stored one by one, leaves every line in pieces to several instructions:
+// 124818 x 32 x 803 by k_w4a4_gemm_blocks, binary16, 877 us, 75 so; 32768 x 1024 x 4095 by k_w4a4_gemm_blocks_f6
+// 913 and 285.  A branch per row, as `rows` may end anywhere, 94 and 286, and 8.7 instead of 7.1 at 71 x 78 x 882.)
+template <typename OUT, typename GET>
+__device__ __forceinline__ void store_rows(OUT* __restrict__ y, long long ld_y, int rows, int cols, int lane,
+                                           GET&& get) {
+  if (cols <= 0) return;
+  const int lg = cols > 32 ? 6 : 32 - __clz(cols - 1 | 1);     // 2^lg lanes a row
+  const int step = 64 >> lg, sub = lane >> lg, col = lane & ((1 << lg) - 1);
+  const int limit = rows < 32 ? rows : 32;
+  if (col >= cols) return;
+  OUT* to = y + sub * ld_y + col;
+  int r0 = 0;
+#pragma unroll 1
+  for (; r0 + 8 * step <= limit; r0 += 8 * step, to += 8 * step * ld_y) {
+    OUT v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = get(r0 + k * step + sub, col);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) __builtin_nontemporal_store(v[k], to + k * step * ld_y);
+  }
+#pragma unroll 1
+  for (int row = r0 + sub; row < limit; row += step, to += step * ld_y)
+    __builtin_nontemporal_store(get(row, col), to);
+}
+
 // Wavefront tile = 64 x 64 of Y, workgroup = 2 x 2 wavefronts, stages through registers: for
 // products of long K whose shape does not suit 256 x 256 tiles (the dispatcher says where).
 template <typename OUT>
@@ -1691,7 +1720,7 @@ __global__ __launch_bounds__(GEMM_THREADS, (MB == 1 ? 3 : 2)) void k_w4a4_gemm_b
   // Output, 32 rows of 64 outputs per wavefront at a time, through its own part of the ring.
   uint8_t* mine = ring + wave * 32 * PITCH;
   const int n_first = n0 + wn * 64;
-  const bool whole = y_vec_ok && n_first + 64 <= N;
+  const bool whole = y_vec_ok && (n_first + 64 <= N || N % W == 0);   // the outputs are whole stores
   constexpr int LPR = 64 / W, RPI = 64 / LPR;          // lanes per row, rows per store instruction
 #pragma unroll
   for (int j = 0; j < MB; ++j) {
@@ -1719,22 +1748,22 @@ __global__ __launch_bounds__(GEMM_THREADS, (MB == 1 ? 3 : 2)) void k_w4a4_gemm_b
         }
       }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (this wavefront's own writes, in order)
+    if (whole) {                                         // (uniform)
+      typedef u32 v4u __attribute__((ext_vector_type(4)));
 #pragma unroll
-    for (int it = 0; it < 32 / RPI; ++it) {
-      const int row = it * RPI + lane / LPR, part = lane % LPR;
-      const int m = m0 + wm * 32 * MB + j * 32 + row, n = n_first + part * W;
-      const uint8_t* from = mine + row * PITCH + part * 16;
-      if (m < M) {
-        OUT* y = Y + (long long)m * ld_y + n;
-        if (whole) {
-          typedef u32 v4u __attribute__((ext_vector_type(4)));
-          __builtin_nontemporal_store(*reinterpret_cast<const v4u*>(from), reinterpret_cast<v4u*>(y));
-        } else {
-#pragma unroll
-          for (int k = 0; k < W; ++k)
-            if (n + k < N) __builtin_nontemporal_store(reinterpret_cast<const OUT*>(from)[k], y + k);
-        }
+      for (int it = 0; it < 32 / RPI; ++it) {
+        const int row = it * RPI + lane / LPR, part = lane % LPR;
+        const int m = m0 + wm * 32 * MB + j * 32 + row;
+        const uint8_t* from = mine + row * PITCH + part * 16;
+        if (m < M && n_first + part * W < N)
+          __builtin_nontemporal_store(*reinterpret_cast<const v4u*>(from),
+                                      reinterpret_cast<v4u*>(Y + (long long)m * ld_y + n_first + part * W));
       }
+    } else {
+      const int m = m0 + wm * 32 * MB + j * 32;
+      store_rows<OUT>(Y + (long long)m * ld_y + n_first, ld_y, M - m, N - n_first, lane, [&](int row, int c) {
+        return *reinterpret_cast<const OUT*>(mine + row * PITCH + c * (int)sizeof(OUT));
+      });
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read before the next 32 rows overwrite it
   }
@@ -2310,6 +2339,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void k_w4a4_gemm_blocks_f6(
   constexpr int RPI = 64 / LPR;                  // rows per store instruction
   const int rsub = lane / LPR, col = (lane % LPR) * W;
   const int nbase = n0 + wn * 64 + col;
+  const bool whole = y_vec_ok && (n0 + wn * 64 + 64 <= N || N % W == 0);   // the outputs are whole stores
 #pragma unroll
   for (int i = 0; i < MT; ++i) {                 // 32 rows at a time
 #pragma unroll
@@ -2329,26 +2359,23 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void k_w4a4_gemm_blocks_f6(
         }
         *reinterpret_cast<float4*>(&T[ml * TP + cw]) = y;
       }
+    if (whole) {                                 // (uniform)
 #pragma unroll
-    for (int it = 0; it < 32 / RPI; ++it) {
-      const int row = it * RPI + rsub;
-      const int m = m0 + wm * 64 + i * 32 + row;
-      float y[W];
+      for (int it = 0; it < 32 / RPI; ++it) {
+        const int row = it * RPI + rsub;
+        const int m = m0 + wm * 64 + i * 32 + row;
+        float y[W];
 #pragma unroll
-      for (int q = 0; q < W / 4; ++q) {
-        const float4 v = *reinterpret_cast<const float4*>(&T[row * TP + col + 4 * q]);
-        y[4 * q] = v.x; y[4 * q + 1] = v.y; y[4 * q + 2] = v.z; y[4 * q + 3] = v.w;
-      }
-      if (m < M) {
-        OUT* yp = Y + (long long)m * ld_y + nbase;
-        if (y_vec_ok && nbase + W - 1 < N) {
-          store_out_vec<OUT>(yp, y);
-        } else {
-#pragma unroll
-          for (int e = 0; e < W; ++e)
-            if (nbase + e < N) store_out<OUT>(yp + e, y[e]);
+        for (int q = 0; q < W / 4; ++q) {
+          const float4 v = *reinterpret_cast<const float4*>(&T[row * TP + col + 4 * q]);
+          y[4 * q] = v.x; y[4 * q + 1] = v.y; y[4 * q + 2] = v.z; y[4 * q + 3] = v.w;
         }
+        if (m < M && nbase < N) store_out_vec<OUT>(Y + (long long)m * ld_y + nbase, y);
       }
+    } else {
+      const int m = m0 + wm * 64 + i * 32, n = n0 + wn * 64;
+      store_rows<OUT>(Y + (long long)m * ld_y + n, ld_y, M - m, N - n, lane,
+                      [&](int row, int c) { return (OUT)T[row * TP + c]; });
     }
   }
 }

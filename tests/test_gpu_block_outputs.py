@@ -1,0 +1,88 @@
+"""Outputs of the block-scaled linears whose rows do not start on 16-byte boundaries or do not end on one:
+what they cost next to rows that do, and their bits in the 128-row tiles that large calls take (4096 tiles
+of 128 x 128 and more), ragged in M, K and N."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import tdq_oracle as O
+from paper_2604_16855_amd import inputs as I
+from paper_2604_16855_amd import tdq
+
+import parity_util as U
+from test_gpu_blocks import _blocks_linear_bound
+
+pytestmark = pytest.mark.gpu
+
+
+def _time(call):
+    """Shortest of five averages, ms."""
+    best = float("inf")
+    for _ in range(5):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        call()
+        torch.cuda.synchronize()
+        a.record()
+        for _ in range(5):
+            call()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) / 5)
+    return best
+
+
+@pytest.mark.parametrize("out_dtype", [torch.float16, torch.float32])
+@pytest.mark.parametrize("six_bit,M,K,N", [(False, 30000, 96, 1000), (True, 32768, 256, 2048)])
+def test_rows_anywhere_cost_little_more(six_bit, M, K, N, out_dtype):
+    """One output more or fewer a row must not double the time (1.1 to 1.5 times measured; three to five times when
+    a lane stored a run of outputs one by one)."""
+    d, g = U.dev(), torch.Generator(device="cuda").manual_seed(3)
+
+    def codes(rows):
+        return torch.randint(0, 256, (rows, tdq.packed_row_bytes(K)), dtype=torch.uint8, device=d, generator=g)
+    Q, steps = codes(M), torch.rand((M, K // 32), device=d, generator=g)
+    if six_bit:
+        Q = tdq.tdq_pack_codes_f6(Q, K)
+    ms = {}
+    for n in (N, N - 1, N + 1):
+        Qw, sw, Y = codes(n), torch.rand(n, device=d, generator=g), torch.empty((M, n), dtype=out_dtype, device=d)
+        if six_bit:
+            Qw = tdq.tdq_pack_codes_f6(Qw, K)
+            ms[n] = _time(lambda: tdq.tdq_w4a4_linear_blocks_f6(Q, steps, K, Qw, n, sw, out=Y))
+        else:
+            ms[n] = _time(lambda: tdq.tdq_w4a4_linear_blocks(Q, steps, K, Qw, sw, out=Y))
+    print({n: f"{1e3 * t:.1f} us" for n, t in ms.items()}, flush=True)
+    assert max(ms.values()) <= 2.0 * ms[N]
+
+
+@pytest.mark.parametrize("out_dtype", [torch.float16, torch.float32])
+@pytest.mark.parametrize("M,K,N", [(524200, 161, 65), (524260, 33, 65), (524260, 130, 40), (131000, 97, 511)])
+def test_tall_tiles_ragged(M, K, N, out_dtype):
+    """4096 tiles of 128 x 128: a masked last stage, blocks past the last one, rows past the last in either half of a
+    tile, bias; whole rows and rows at odd addresses, against the 6-bit kernel everywhere and the oracle on sampled
+    rows."""
+    assert -(-M // 128) * -(-N // 128) >= 4096
+    rng = np.random.default_rng([M, K, N])
+    KB = -(-K // 32)
+    codes, qw = I.random_codes((M, K), 5), I.random_codes((N, K), 6)
+    steps = np.exp(rng.normal(-3.0, 1.0, (M, KB))).astype(np.float32)
+    sw = np.exp(rng.normal(-4.0, 0.5, N)).astype(np.float32)
+    bias = rng.normal(0, 0.02, N).astype(np.float32)
+    Q, Qw = U.pack_to_device(codes), U.pack_to_device(qw)
+    bs, ws, bd = (torch.from_numpy(v).to(U.dev()) for v in (steps, sw, bias))
+    Y = tdq.tdq_w4a4_linear_blocks(Q, bs, K, Qw, ws, bd, out_dtype)
+    Y6 = tdq.tdq_w4a4_linear_blocks_f6(tdq.tdq_pack_codes_f6(Q, K), bs, K, tdq.tdq_pack_codes_f6(Qw, K), N, ws, bd,
+                                       out_dtype)
+    wide = torch.full((M, N + 2), 7.0, dtype=out_dtype, device=U.dev())
+    tdq.tdq_w4a4_linear_blocks(Q, bs, K, Qw, ws, bias=bd, out=wide[:, 1:N + 1])
+    torch.cuda.synchronize()
+    assert torch.equal(Y, Y6)
+    assert torch.equal(wide[:, 1:N + 1], Y)
+    assert bool((wide[:, 0] == 7).all()) and bool((wide[:, N + 1:] == 7).all())
+    rows = np.unique(np.concatenate([np.arange(130), np.arange(M - 130, M), rng.integers(0, M, 200)]))
+    Yref = O.blocks_linear(codes[rows], steps[rows], 32, qw, sw, bias)
+    tol = _blocks_linear_bound(codes[rows], steps[rows], qw, sw, bias, KB)
+    if out_dtype == torch.float16:
+        tol = tol * 1.001 + 2.0 ** -11 * 1.001 * np.abs(Yref) + 2.0 ** -24    # + half an ulp of binary16
+    got = Y[torch.from_numpy(rows).to(U.dev())].cpu().numpy().astype(np.float64)
+    assert (np.abs(got - Yref) <= tol).all()
