@@ -86,6 +86,26 @@ __device__ __forceinline__ void clear_select(const SelectClear& c, unsigned long
   for (unsigned long long k = i; k < c.n_hist / 4; k += n) reinterpret_cast<uint4*>(c.hist)[k] = make_uint4(0, 0, 0, 0);
 }
 
+// h % d of h < 2^24: the quotient in binary32 is off by one at most (8 instructions instead of 30).
+__device__ __forceinline__ u32 mod24(u32 h, u32 d) {
+  u32 r = h - (u32)((float)h * __builtin_amdgcn_rcpf((float)d)) * d;
+  r = (int)r < 0 ? r + d : r;
+  return r >= d ? r - d : r;
+}
+
+// Which of the n workgroups of image b workgroup x is, so that those of one set take turns on the chip.
+// Workgroups are dealt out in the order x, then b: one at a time to the 8 XCDs, and on an XCD to the shader
+// engines.  With n even the same x of all images would run on few of either, and one set often holds most
+// tokens of every image.  So image b starts at b, which makes the distance from image to image odd, as it is if
+// n is; with few workgroups an image one further every 8 / n images.  (b < 2^16.)  k_sets<WHOLE>, us before
+// and now: [82, 11, 1156] with 16 sets 28.3 and 23.5, [37, 14, 232] with 32 24.7 and 14.9; with all tokens of an
+// image in one set [36, 375, 46] with 32 and a percentile 217 and 56, [30, 3342, 7] with 32 116 and 42.
+__device__ __forceinline__ u32 turned(u32 x, u32 n, u32 b) {
+  if (n & 1u) return x;
+  const u32 at = x + mod24(n >= 8 ? b : (((b & 7u) * n) >> 3) + (b >> 3), n);
+  return at >= n ? at - n : at;
+}
+
 // Reductions over groups of L adjacent lanes (L a power of two <= 64) with DPP
 // row shifts and row broadcasts, i.e. at vector-ALU speed instead of one LDS round
 // trip per step.  The result is valid in the LAST lane of every group

@@ -389,13 +389,6 @@ __device__ __forceinline__ u32 search_rows(const TX* __restrict__ Xb, long long 
 // 0.9 until the first loads are back), layer of [8, 121, 512] 25.7 -> 21.1 us, [1, 7744, 64] 30.5 -> 26.2,
 // [16, 484, 320] 36.0 -> 33.2, [5, 1369, 333] with a percentile, where one sweep serves both ranks,
 // 62.8 -> 39.2.
-// h % d of h < 2^24: the quotient in binary32 is off by one at most (8 instructions instead of 30).
-__device__ __forceinline__ u32 mod24(u32 h, u32 d) {
-  u32 r = h - (u32)((float)h * __builtin_amdgcn_rcpf((float)d)) * d;
-  r = (int)r < 0 ? r + d : r;
-  return r >= d ? r - d : r;
-}
-
 // A rank k of a set of n elements as seen by a sample of m of them from n_sel tokens.
 struct SampleRank {
   u32 rk;                     // the rank of the sample that corresponds to k
@@ -599,11 +592,12 @@ __global__ __launch_bounds__(NT) void k_sets(
     // (a little less than its share, so that rounding never makes it more than G + extra together)
     const float per = (float)wa.extra / (float)all * (1.f - 1e-6f);
     const u32 its = lane < G ? 1u + (u32)((float)drawn * per) : 0u, incl = wave_scan_u32(its);
-    const unsigned long long later = __ballot(incl > blockIdx.x);
+    const u32 at = turned(blockIdx.x, gridDim.x, blockIdx.y);
+    const unsigned long long later = __ballot(incl > at);
     if (__builtin_expect(later == 0, 0)) return;     // the same for every thread
     j = __ffsll((long long)later) - 1;
     S = __builtin_amdgcn_readlane((int)its, j);
-    part = (int)blockIdx.x - (__builtin_amdgcn_readlane((int)incl, j) - S);
+    part = (int)at - (__builtin_amdgcn_readlane((int)incl, j) - S);
   }
   const u32 start = start_of(j), end = start_of(j + 1);
   auto in_set = [&](u32 k) { return k >= start && k < end; };
