@@ -153,6 +153,7 @@ __device__ __forceinline__ BinPick pick_bin(const u32* __restrict__ hb, int W, u
 // ---------------------------------------------------------------------------
 constexpr int kFinishBits = 11;                 // key bits a pass resolves
 constexpr int kFinishTokens = 2048;             // tokens looked at together
+constexpr int kWindow = 1 << kFinishBits;       // keys of a pass that looks at them one by one
 
 // LDS of the search
 template <int NT, bool LISTED>
@@ -164,34 +165,35 @@ struct FinishLds {
 };
 
 // Rows list[0 .. n - 1] (offsets from row Xb), read by a workgroup of NT threads: groups of L lanes take R rows
-// and P 16-byte pieces of each at a time, R P = 4 and P by the row length, and load the next four while the
-// caller's piece(uint4) looks at these; single(element) gets what no whole piece holds.
-template <typename TX, int NT>
+// and P 16-byte pieces of each at a time, R P = Q and P by the row length, and (AHEAD) load the next Q while
+// the caller's piece(uint4) looks at these; single(element) gets what no whole piece holds.  (The search loads
+// nothing ahead: with 1024 threads the registers cost it more, [3, 11324, 171] with 31 missed sets 200 us, 190 so.)
+template <typename TX, int NT, int Q, bool AHEAD>
 struct RowVisitor {
   static constexpr int V = Elem<TX>::V;
   const TX* Xb;
   long long ld;
   int C, L, n, nvec, P, R, lr, slots, row, v0;
   const unsigned short* list;
-  uint4 q[4];
+  uint4 q[Q];
   // starts with the loads of the first pieces
   __device__ __forceinline__ RowVisitor(const TX* Xb_, long long ld_, int C_, int L_, const unsigned short* list_,
                                         int n_)
       : Xb(Xb_), ld(ld_), C(C_), L(L_), n(n_), list(list_) {
     nvec = C / V;
     P = nvec <= L ? 1 : nvec <= 2 * L ? 2 : 4;
-    R = 4 / P;
+    R = Q / P;
     lr = threadIdx.x & (L - 1);
     const int shift = 31 - __clz(L);
     row = threadIdx.x >> shift;
     slots = NT >> shift;
     v0 = lr;
-    if (n > 0) load();
+    if (AHEAD && n > 0) load();
   }
   __device__ __forceinline__ void load() {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {               // past the end: the last row, piece v0; not looked at
-      const int at = row + slots * (P == 1 ? i : P == 2 ? i >> 1 : 0), v = v0 + (i & (P - 1)) * L;
+    for (int i = 0; i < Q; ++i) {               // past the end: the last row, piece v0; not looked at
+      const int at = row + slots * (P == 1 ? i : P == 2 ? i >> 1 : i >> 2), v = v0 + (i & (P - 1)) * L;
       const TX* xp = Xb + (long long)list[at < n ? at : n - 1] * ld;
       if (nvec > 0) q[i] = load16(xp + (long long)(v < nvec ? v : lr < nvec ? lr : 0) * V);
     }
@@ -201,11 +203,12 @@ struct RowVisitor {
     const int row_first = row;
     if (lr < nvec) {
       while (row < n) {
-        uint4 c[4];
-        bool ok[4];
+        uint4 c[Q];
+        bool ok[Q];
+        if (!AHEAD) load();
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int at = row + slots * (P == 1 ? i : P == 2 ? i >> 1 : 0), v = v0 + (i & (P - 1)) * L;
+        for (int i = 0; i < Q; ++i) {
+          const int at = row + slots * (P == 1 ? i : P == 2 ? i >> 1 : i >> 2), v = v0 + (i & (P - 1)) * L;
           ok[i] = at < n && v < nvec;
           c[i] = q[i];
         }
@@ -214,64 +217,129 @@ struct RowVisitor {
           v0 = lr;
           row += slots * R;
         }
-        if (row < n) load();
+        if (AHEAD && row < n) load();
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < Q; ++i)
           if (ok[i]) piece(c[i]);
       }
     }
     if (__builtin_expect(nvec * V < C, 0))
-      for (int at = row_first; at < n; at += slots)
-        for (int c = nvec * V + lr; c < C; c += L) single(Xb[(long long)list[at] * ld + c]);
+      for (int at = row_first; at < n; at += 4 * slots)
+        for (int c = nvec * V + lr; c < C; c += L) {
+          TX x[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int ri = at + i * slots;
+            x[i] = Xb[(long long)list[ri < n ? ri : n - 1] * ld + c];
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (at + i * slots < n) single(x[i]);
+        }
   }
 };
 
-// Adds the keys of rows list[0 .. n - 1] that lie in [k0, k0 + span) to
-// the histogram of digits (key - k0 >> shift) - off.  Digit 0 takes all that is below as well and
-// is counted in a register, the last digit takes all that is above and is not counted (what the
-// others do not hold): either may be most of the set, and would meet in one word of LDS.
-template <typename TX, int NT>
+// One pass of the search over rows list[0 .. n - 1]: the histogram of digits (key - k0 >> shift) - off.
+// Digit 0 takes all that is below as well and is counted in a register, the last digit takes all that is above
+// and is not counted (what the others do not hold): either may be most of the set, and would meet in one word
+// of LDS.  binary32: of the keys in [k0, k0 + span).  binary16: of all keys of the set, so that those below
+// need no second compare, both halves of a word at once as in k_bracket_hist.
+template <typename TX, int NT, int Q, bool AHEAD>
 __device__ __forceinline__ void count_rows(const TX* __restrict__ Xb, long long ld, int C, int L,
                                            const unsigned short* list, int n, u32 k0, u32 span, int shift,
                                            int off, u32* h) {
+  constexpr int kBins = 1 << kFinishBits;
   u32 low = 0;
-  auto count = [&](TX x) {
-    const u32 d = Elem<TX>::key(x) - k0;
-    const int digit = d < span ? (int)(d >> shift) - off : 1 << kFinishBits;
-    low += digit <= 0 ? 1u : 0u;
-    if (digit > 0 && digit < (1 << kFinishBits) - 1) atomicAdd(&h[digit], 1u);
-  };
-  RowVisitor<TX, NT>(Xb, ld, C, L, list, n)
-      .visit([&](const uint4& q) {
-        TX x[Elem<TX>::V];
-        Elem<TX>::unpack(q, x);
+  RowVisitor<TX, NT, Q, AHEAD> rows(Xb, ld, C, L, list, n);
+  if constexpr (sizeof(TX) == 2) {
+    const u32 first = k0 + (u32)off + (1u << shift);           // the first key of digit 1 (off: shift is 0)
+    const u32 counted = (u32)(kBins - 2) << shift;             // keys of digits 1 to kBins - 2
+    const u32 first2 = first | (first << 16);
+    rows.visit([&](const uint4& q) {
+      const u32 wd[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
-        for (int c = 0; c < Elem<TX>::V; ++c) count(x[c]);
-      },
-             count);
+      for (int c = 0; c < 4; ++c) {
+        const u32 d2 = __builtin_bit_cast(u32, __builtin_bit_cast(s2v, wd[c] & 0x7FFF7FFFu) -
+                                                   __builtin_bit_cast(s2v, first2));
+        low += (u32)__builtin_popcount(d2 & 0x80008000u);
+        const u32 dl = d2 & 0xFFFFu, dh = d2 >> 16;
+        if (dl < counted) atomicAdd(&h[1 + (dl >> shift)], 1u);
+        if (dh < counted) atomicAdd(&h[1 + (dh >> shift)], 1u);
+      }
+    },
+               [&](TX x) {
+                 const u32 k = Elem<TX>::key(x);
+                 low += k < first ? 1u : 0u;
+                 if (k >= first && k - first < counted) atomicAdd(&h[1 + ((k - first) >> shift)], 1u);
+               });
+  } else {
+    auto count = [&](TX x) {
+      const u32 d = Elem<TX>::key(x) - k0;
+      const int digit = d < span ? (int)(d >> shift) - off : kBins;
+      low += digit <= 0 ? 1u : 0u;
+      if (digit > 0 && digit < kBins - 1) atomicAdd(&h[digit], 1u);
+    };
+    rows.visit([&](const uint4& q) {
+      TX x[Elem<TX>::V];
+      Elem<TX>::unpack(q, x);
+#pragma unroll
+      for (int c = 0; c < Elem<TX>::V; ++c) count(x[c]);
+    },
+               count);
+  }
   if (low) atomicAdd(&h[0], low);
 }
 
-// The key of rank `need` (1-based) among the set's keys in [k0, k0 + span), by the whole
-// workgroup.  LISTED: the set's tokens are list[0 .. T - 1], otherwise those of T with gb[t] == j.  Every pass divides span by 2^kFinishBits, so three passes at most; near < 0 (> 0):
-// one more before them that looks at the last (first) 2047 keys of the range one by one.
+// binary16: which window of `span` keys from k0 to look at, where the set has `from` keys below k0 and `to` below
+// k0 + span, and the one of rank k lies between; cum = sampled keys before every 32nd, m in all.  Half of the
+// window is below the sampled key that as large a share of the sampled ones in the range precede, because a set
+// has keys closer to a gap than its sample.  The same in every wavefront.
+__device__ __forceinline__ int place_window(const u32* cum, u32 m, u32 k0, u32 span, u32 from, u32 to, u32 k) {
+  const u32 s_from = cum[k0 >> 5], s_to = k0 + span < 1u << 15 ? cum[(k0 + span) >> 5] : m;
+  const u32 at = s_from + (u32)((float)(s_to - s_from) * ((float)(k - 1u - from) * __builtin_amdgcn_rcpf((float)(to - from))));
+  int cell = -1;                                 // (cum[0] is 0)
+#pragma unroll
+  for (int i = 0; i < 1024 / 64; ++i)
+    cell += (int)__popcll(__ballot(cum[i * 64 + (threadIdx.x & 63)] <= at));
+  const int start = cell * 32 + 16 - kWindow / 2 - (int)k0, most = (int)span - kWindow;
+  return start < 0 ? 0 : start > most ? most : start;
+}
+
+// The key in [k0, k0 + span) of rank `need` (1-based; binary32: among the set's keys in that range, binary16:
+// among all of the set's), by the whole workgroup.  LISTED: the set's tokens are list[0 .. T - 1], otherwise
+// those of T with gb[t] == j.  Every pass divides span by 2^kFinishBits, so two passes at most (binary32: three);
+// window >= 0: one more before them that looks at the 2046 keys of the range from the window-th on one by one;
+// cum != nullptr (see place_window, `from` and `to` as there): up to two such.  A pass reads all rows of the set,
+// by one workgroup whose instructions set the pace (0.95 M elements 100 us), so what counts is how many passes
+// there are.  Calibration by k_sets<WHOLE> where a fifth of the values is far below the others and the rank between,
+// three passes with the window next to the interval, and now: [2, 4844, 586] with 16 sets, 14 missed, 410 and 120
+// us; [10, 4349, 272] with 8, 9 missed, 339 and 104.  (With one window at the sample's place the first took 127.)
 template <typename TX, int NT, bool LISTED>
 __device__ __forceinline__ u32 search_rows(const TX* __restrict__ Xb, long long ld, int T, int C, int L,
                            const int* __restrict__ gb, int j, const unsigned short* list, u32 k0, u32 span,
-                           unsigned long long need, int near, FinishLds<NT, LISTED>& s) {
-  constexpr int kBins = 1 << kFinishBits, NW = NT / 64;
+                           unsigned long long need, int window, FinishLds<NT, LISTED>& s,
+                           const u32* cum = nullptr, u32 m = 0, u32 from = 0, u32 to = 0) {
+  constexpr int kBins = 1 << kFinishBits, NW = NT / 64, kPer = kBins / NT;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int tries = cum ? 2 : 0;
   while (span > 1) {
     int shift = 32 - __clz(span - 1) - kFinishBits, off = 0;
-    shift = shift > 0 && near == 0 ? shift : 0;
-    if (near < 0 && span > (u32)kBins) off = (int)span - kBins;
-    near = 0;
+    shift = shift > 0 ? shift : 0;
+    if (LISTED && sizeof(TX) == 2 && tries > 0 && span > (u32)kBins) {
+      window = place_window(cum, m, k0, span, from, to, (u32)need);
+      --tries;
+    }
+    if (window >= 0 && span > (u32)kBins) {
+      shift = 0;
+      off = window;
+    }
+    window = -1;
     __syncthreads();
     for (int i = tid; i < kBins; i += NT) s.h[i] = 0;
     if (tid == 0) s.digit = kBins - 1;
     if constexpr (LISTED) {
       __syncthreads();
-      count_rows<TX, NT>(Xb, ld, C, L, list, T, k0, span, shift, off, s.h);
+      count_rows<TX, NT, 8, false>(Xb, ld, C, L, list, T, k0, span, shift, off, s.h);
       __syncthreads();
     } else {
       for (int t0 = 0; t0 < T; t0 += kFinishTokens) {
@@ -301,12 +369,11 @@ __device__ __forceinline__ u32 search_rows(const TX* __restrict__ Xb, long long 
           at += (u32)__popcll(m);
         }
         __syncthreads();
-        count_rows<TX, NT>(Xb + (long long)t0 * ld, ld, C, L, s.list, (int)n, k0, span, shift, off, s.h);
+        count_rows<TX, NT, 4, false>(Xb + (long long)t0 * ld, ld, C, L, s.list, (int)n, k0, span, shift, off, s.h);
         __syncthreads();                        // `list` and `wtot` are reused
       }
     }
     // the bin where the running count reaches `need`
-    constexpr int kPer = kBins / NT;
     unsigned long long mine = 0;
     u32 c[kPer];
 #pragma unroll
@@ -340,7 +407,11 @@ __device__ __forceinline__ u32 search_rows(const TX* __restrict__ Xb, long long 
     const u32 next = digit == kBins - 1 ? span : (digit + (u32)off + 1u) << shift;
     k0 += first;
     span = (next < span ? next : span) - first;
-    need = s.rest;
+    if (sizeof(TX) == 4) need = s.rest;
+    if (LISTED && sizeof(TX) == 2) {                // (the counts around it are known only after a window)
+      if (digit == 0) to = s.h[0];
+      if (digit == kBins - 1) from = (u32)(need - s.rest);
+    }
   }
   return k0;
 }
@@ -441,28 +512,32 @@ __device__ __forceinline__ void place_bins(const u32* cum, int bm, const SampleR
   first = lo > 1 ? (u32)lo : 1u;                     // zeros are counted below
 }
 
-// Where a rank lies that an interval does not hold: `span` keys from k0, as their `rank`-th; near < 0 (> 0):
-// probably close to the last (first) of them.  above = first key after the interval.
+// Where a rank k of n lies that an interval does not hold: among `span` keys from k0, as their `rank`-th
+// (binary16: the set's); `from` of the set's keys are smaller than these, from and these together `to`; binary16:
+// probably in the window that starts at key k0 + window, next to the interval.  above = first key after the interval.
 struct Lost {
-  u32 k0, span;
-  int near;
+  u32 k0, span, from, to;
+  int window;
   unsigned long long rank;
 };
 template <bool F16>
-__device__ __forceinline__ Lost lost_rank(u32 k, u32 below, u32 inside, u32 lo, u32 above) {
+__device__ __forceinline__ Lost lost_rank(u32 k, u32 n, u32 below, u32 inside, u32 lo, u32 above) {
   constexpr u32 kKeysAll = F16 ? 1u << 15 : 1u << 31;
   Lost l;
+  l.window = F16 ? 0 : -1;
   if (k <= below) {                                  // (span 1: there are only zeros)
     l.k0 = 0;
     l.span = lo;
-    l.near = F16 ? -1 : 0;
-    l.rank = k;
+    l.from = 0;
+    l.to = below;
+    if (F16 && lo > (u32)kWindow) l.window = (int)lo - kWindow;
   } else {
     l.k0 = above < kKeysAll ? above : kKeysAll - 1u;
     l.span = kKeysAll - l.k0;
-    l.near = F16 ? 1 : 0;
-    l.rank = (u64)k - ((u64)below + inside);
+    l.from = below + inside;
+    l.to = n;
   }
+  l.rank = F16 ? k : (u64)(k - l.from);
   return l;
 }
 
@@ -728,7 +803,7 @@ __global__ __launch_bounds__(NT) void k_sets(
   // (whole, binary16: the first loads of this workgroup's share of the rows as well)
   const int share = WHOLE && F16 ? (tokens + S - 1) / S : 0, share_from = part * share;
   const int share_rows = tokens - share_from < share ? tokens - share_from : share;     // (none if negative)
-  RowVisitor<TX, NT> own(X + (long long)b * T * ld, ld, C, WHOLE && F16 ? wa.L : 1,
+  RowVisitor<TX, NT, 4, true> own(X + (long long)b * T * ld, ld, C, WHOLE && F16 ? wa.L : 1,
                          order + (share_rows > 0 ? share_from : 0), WHOLE && F16 ? share_rows : 0);
 
   // Moments of the set about the mean of its first token (zero if that is not finite: the
@@ -884,8 +959,9 @@ __global__ __launch_bounds__(NT) void k_sets(
     if (NR == 2) k[0] = rank_of(sc.base_pct);
     k[NR - 1] = k_pass;
     u32 found = 0, base_key = 0;
-    auto search = [&](const Lost& l, int near) {
-      return search_rows<TX, NT, true>(Xb, ld, tokens, C, wa.L, nullptr, j, order, l.k0, l.span, l.rank, near, s_search);
+    auto search = [&](const Lost& l) {
+      return search_rows<TX, NT, true>(Xb, ld, tokens, C, wa.L, nullptr, j, order, l.k0, l.span, l.rank, -1,
+                                       s_search, F16 ? cum : nullptr, m, l.from, l.to);
     };
     if constexpr (F16) {
       SampleRank sq[NR];
@@ -982,13 +1058,12 @@ __global__ __launch_bounds__(NT) void k_sets(
       for (int q = 0; q < NR; ++q) {
         if (wave == q) {
           const BinPick p = pick_bin<false>(hist[q], (int)wd[q], s_below[q], k[q]);
-          const Lost l = lost_rank<true>(k[q], s_below[q], p.inside, first[q], first[q] + wd[q]);
-          if (lane == 0) {
-            s_lost[q].k0 = p.ok ? first[q] + p.bin : l.k0;
-            s_lost[q].span = p.ok ? 1u : l.span;
-            s_lost[q].near = l.near;
-            s_lost[q].rank = l.rank;
+          Lost l = lost_rank<true>(k[q], nn, s_below[q], p.inside, first[q], first[q] + wd[q]);
+          if (p.ok) {
+            l.k0 = first[q] + p.bin;
+            l.span = 1u;
           }
+          if (lane == 0) s_lost[q] = l;
         }
       }
       __syncthreads();
@@ -997,7 +1072,7 @@ __global__ __launch_bounds__(NT) void k_sets(
         u32 key_q = s_lost[q].k0;
         if (__builtin_expect(s_lost[q].span != 1u, 0)) {                            // the interval missed the rank
           if (tid == 0) atomicAdd(&status[1 + (q == NR - 1 ? kPassZr : kPassBase)], 1u);
-          key_q = search(s_lost[q], s_lost[q].near);
+          key_q = search(s_lost[q]);
         }
         if (q == NR - 1) found = key_q; else base_key = key_q;
       }
@@ -1020,7 +1095,7 @@ __global__ __launch_bounds__(NT) void k_sets(
           below += d >> 31;
           if ((d >> shift) < (u32)kBins) atomicAdd(&hist[0][d >> shift], 1u);
         };
-        RowVisitor<TX, NT>(Xb, ld, C, wa.L, order, tokens)
+        RowVisitor<TX, NT, 4, true>(Xb, ld, C, wa.L, order, tokens)
             .visit([&](const uint4& p) {
                              TX x[V];
                              Elem<TX>::unpack(p, x);
@@ -1034,20 +1109,23 @@ __global__ __launch_bounds__(NT) void k_sets(
         if (q == 0 && wave == NW - 1) finish_moments();
         if (wave == 0) {
           const BinPick p = pick_bin<false>(hist[0], kBins, s_below[0], kq);
-          Lost l = lost_rank<false>(kq, s_below[0], p.inside, first, first + ((u32)kBins << shift));
-          l.near = 1;                                  // a miss
+          Lost l = lost_rank<false>(kq, nn, s_below[0], p.inside, first, first + ((u32)kBins << shift));
+          bool miss = true;
           if (p.ok) {
             l.k0 = first + (p.bin << shift);
             l.span = 1u << shift;
             l.rank = p.need;
-            l.near = 0;
+            miss = false;
           }
-          if (lane == 0) s_lost[0] = l;
+          if (lane == 0) {
+            s_lost[0] = l;
+            s_last = miss ? 1u : 0u;
+          }
         }
         __syncthreads();
         const Lost l = s_lost[0];
-        if (tid == 0 && l.near && l.span != 1u) atomicAdd(&status[1 + (q == NR - 1 ? kPassZr : kPassBase)], 1u);
-        const u32 key_q = l.span == 1u ? l.k0 : search(l, 0);
+        if (tid == 0 && s_last && l.span != 1u) atomicAdd(&status[1 + (q == NR - 1 ? kPassZr : kPassBase)], 1u);
+        const u32 key_q = l.span == 1u ? l.k0 : search(l);
         if (q == NR - 1) found = key_q; else base_key = key_q;
       }
     }
@@ -1725,8 +1803,8 @@ hipError_t launch_bracket_gather(const void* Xv, int B, int T_, int C, long long
 // histogram of that range over 2048 bins, then of the bin, until a bin is one key.  One
 // workgroup on one CU: bound by the loads it keeps in flight, so the ids of 2048 tokens are read
 // together, a lane takes four pieces of 16 bytes at a time, and with few sets per call, which may
-// be large, a workgroup has 1024 threads.  A binary16 rank that misses its one-key bins lies close
-// to them, so the first pass looks at the 2047 keys next to the interval one by one.  What a miss
+// be large, a workgroup has 1024 threads.  A binary16 rank that misses its one-key bins often lies close
+// to them, so the first pass looks at the 2046 keys next to the interval one by one.  What a miss
 // cost before (eight key bits a pass) was LDS additions that met in one word: nearly all elements
 // lie on one side of the interval.  Calibration with 18 % zeros, 16 sets, binary16: [1, 1936, 1500]
 // 208 us with 6 missed sets, 70 with 4 so; [8, 7744, 512] 584 with 54, 139 with 18.
@@ -1744,7 +1822,7 @@ __global__ __launch_bounds__(NT, NT == 256 ? 8 : 4) void k_bracket_finish(
   __shared__ FinishLds<NT, false> lds;
   __shared__ u32 s_keys[F16 ? 1 : kListMax];
   __shared__ u32 s_ok, s_key, s_need, s_k0, s_span, s_tie, s_ties;
-  __shared__ int s_near;
+  __shared__ int s_window;
   __shared__ unsigned long long s_rank;
   const int idx = blockIdx.x;
   const int b = idx / G, j = idx - b * G;
@@ -1766,7 +1844,7 @@ __global__ __launch_bounds__(NT, NT == 256 ? 8 : 4) void k_bracket_finish(
   enum { kMiss = 0, kDone = 1, kInList = 2 };
   if (wave == 0) {
     u32 ok = kMiss, k0 = 0, span = kKeysAll;    // where a missed key lies, and its rank there
-    int near = 0;
+    int window = -1;
     unsigned long long rank = (unsigned long long)w.k_rem;
     if (!force_miss) {
       const Bracket e = br[idx];
@@ -1813,11 +1891,11 @@ __global__ __launch_bounds__(NT, NT == 256 ? 8 : 4) void k_bracket_finish(
         }
         if (ok == kDone && lane == 0) finish(key);
       } else {
-        const Lost l = lost_rank<F16>((u32)w.k_rem, e.below, p.inside, e.lo,
+        const Lost l = lost_rank<F16>((u32)w.k_rem, (u32)w.n, e.below, p.inside, e.lo,
                                       e.lo + (e.shift & kCells ? e.width : e.width << e.shift));
         k0 = l.k0;
         span = l.span;
-        near = l.near;
+        window = l.window;
         rank = l.rank;
         if (k0 == 0 && span == 1u) {            // below the interval, where there are only zeros
           ok = kDone;
@@ -1832,7 +1910,7 @@ __global__ __launch_bounds__(NT, NT == 256 ? 8 : 4) void k_bracket_finish(
       s_ok = ok;
       s_k0 = k0;
       s_span = span;
-      s_near = near;
+      s_window = window;
       s_rank = rank;
     }
   }
@@ -1865,7 +1943,7 @@ __global__ __launch_bounds__(NT, NT == 256 ? 8 : 4) void k_bracket_finish(
   // The interval missed rank k (or the validation switch asked for this route).
   if (tid == 0) atomicAdd(&status[1 + pass], 1u);
   const u32 key = search_rows<TX, NT, false>(X + (long long)b * T * ld, ld, T, C, L, gid + (long long)b * T, j,
-                                             nullptr, s_k0, s_span, s_rank, s_near, lds);
+                                             nullptr, s_k0, s_span, s_rank, s_window, lds);
   if (tid == 0) finish(key);
 }
 

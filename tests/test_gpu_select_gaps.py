@@ -67,20 +67,63 @@ def test_bins_hold_little(kind, T, C, G):
     assert _check(_data(kind, 1, T, C, np.float32, 7), G) == 0
 
 
+def _whole(B, T, C, G, pct=0.0):
+    """Whether the one kernel after the statistics does it all (else the chain of kernels)."""
+    assert tdq.lib().tdq_samples_rank(tdq.TDQ_F16, B, T, C, G)
+    return tdq.lib().tdq_whole_extra(tdq.TDQ_F16, B, T, C, G, tdq.C.c_double(pct)) >= 0
+
+
 @pytest.mark.parametrize("pct", [0.0, 0.99])
 @pytest.mark.parametrize("kind", EDGES)
 @pytest.mark.parametrize("B,T,C,G", [(2, 700, 520, 16), (4, 300, 333, 3), (20, 260, 264, 16), (9, 200, 40, 64),
                                      (1, 5000, 70, 1)])
 def test_rank_at_the_gap(kind, B, T, C, G, pct):
-    """Few and many sets (1024 and 256 threads in the search), one and several rows per lane
-    group, more tokens than one look takes, row tails."""
+    """One workgroup and several per set, rows of any length."""
+    assert _whole(B, T, C, G, pct) or (pct and G == 64)
     _check(_data(kind, B, T, C, np.float16, B * T + C), G, pct)
 
 
-def test_search_finds_both_sides():
+@pytest.mark.parametrize("pct", [0.0, 0.99])
+@pytest.mark.parametrize("kind", EDGES)
+@pytest.mark.parametrize("B,T,C,G", [(1, 8200, 72, 16), (2, 8300, 41, 3), (17, 8193, 24, 16), (1, 9000, 9, 5)])
+def test_rank_at_the_gap_in_the_chain(kind, B, T, C, G, pct):
+    """The same by the chain of kernels: 1024 and 256 threads in the search, more tokens than one look
+    takes, one and several rows per lane group, row tails."""
+    assert not _whole(B, T, C, G, pct)
+    _check(_data(kind, B, T, C, np.float16, B * T + C), G, pct)
+
+
+@pytest.mark.parametrize("B,T,C,G,whole", [(20, 260, 264, 16, True), (2, 1500, 600, 8, True), (1, 4000, 333, 5, True),
+                                           (4, 8200, 72, 16, False), (1, 9001, 129, 7, False),
+                                           (17, 8193, 24, 16, False)])
+def test_search_finds_both_sides(B, T, C, G, whole):
     """Images on which intervals do miss, below the interval and above it."""
-    missed = sum(_check(_data(k, 20, 260, 264, np.float16, s), 16) for k in EDGES for s in (1, 2))
+    assert _whole(B, T, C, G) == whole
+    missed = sum(_check(_data(k, B, T, C, np.float16, s), G) for k in EDGES for s in (1, 2))
+    print("missed", missed, flush=True)
     assert missed > 0
+
+
+@pytest.mark.parametrize("kind,B,T,C,G", [("two", 2, 4844, 586, 16), ("mask20", 2, 2000, 1000, 16),
+                                          ("two", 10, 4349, 272, 8)])
+def test_missed_sets_cost_less_than_a_search_of_all(kind, B, T, C, G):
+    """A few missed sets must not make a calibration slower than the validation switch does, which searches
+    every set (0.5 to 0.65 times its time measured; 1.4 to 1.6 where a missed set's rows were read three times)."""
+    import torch
+
+    from test_gpu_block_outputs import _time
+    assert _whole(B, T, C, G)
+    X, ms = torch.from_numpy(_data(kind, B, T, C, np.float16, 1)).to(U.dev()), {}
+    for flag in (tdq.FLAG_EXACT_SELECT, 0):
+        p = tdq.default_params(G)
+        p.flags |= flag
+        ws = tdq.alloc_workspace(B, T, C, tdq.TDQ_F16, p, X.device)
+        out = (torch.empty((B, T), dtype=torch.int32, device=X.device),
+               *(torch.empty((B, G), device=X.device) for _ in range(2)))
+        ms[flag] = _time(lambda: tdq.tdq_calibrate_groups(X, p, ws, out=out))
+    missed = tdq.exact_select_sets(ws)
+    print(f"{missed} missed, {1e3 * ms[0]:.1f} us, all {1e3 * ms[tdq.FLAG_EXACT_SELECT]:.1f} us", flush=True)
+    assert missed > 0 and ms[0] <= ms[tdq.FLAG_EXACT_SELECT]
 
 
 def test_large_sets_without_wider_bins():
