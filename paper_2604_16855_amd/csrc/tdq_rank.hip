@@ -33,6 +33,8 @@
 // Zeros are never inside an interval (it starts at key 1 at the lowest): where it starts there,
 // "below" counts exactly the zeros, and a rank among them is answered by that count.  A fifth
 // of an activation behind a rectifier is zeros, which would all meet in one word of LDS.
+#include <type_traits>
+
 #include "tdq_device.hpp"
 
 namespace tdq {
@@ -459,7 +461,11 @@ __device__ __forceinline__ u32 search_rows(const TX* __restrict__ Xb, long long 
 // Measured against the chain k_sets, k_bracket_hist, k_bracket_finish (each kernel boundary costs 1.4 us and
 // 0.9 until the first loads are back), layer of [8, 121, 512] 25.7 -> 21.1 us, [1, 7744, 64] 30.5 -> 26.2,
 // [16, 484, 320] 36.0 -> 33.2, [5, 1369, 333] with a percentile, where one sweep serves both ranks,
-// 62.8 -> 39.2.
+// 62.8 -> 39.2.  Every workgroup of a set adds the same 16 Ki sampled keys to its LDS, so binary16 images of few
+// different values, which meet in few words, were slower than by the chain until the sample's histogram and
+// such an interval's got copies; calibration, us by the chain, without and with copies: one value [19, 167, 2056]
+// with 12 sets 51, 85, 35 and [2, 7625, 920] with 64 87, 113, 47; values within 1e-4 of 1 [29, 128, 1080] with 12 52,
+// 89, 34; Laplace [16, 484, 320] 21.6, 17.7, 17.2.
 // A rank k of a set of n elements as seen by a sample of m of them from n_sel tokens.
 struct SampleRank {
   u32 rk;                     // the rank of the sample that corresponds to k
@@ -554,9 +560,9 @@ __global__ __launch_bounds__(NT) void k_sets(
   constexpr int kHalf = RD > 1 ? RD / 2 : 1;
   constexpr int kSampleRuns = SM / kRunLen;
   constexpr int kSampleTokens = kSampleRuns;         // at most one run per token
-  // binary32 values of one magnitude share their top bits: four copies of the first histogram
-  // keep the lanes of a wavefront from all adding to one word
-  constexpr int kCopies = F16 ? 1 : 4;
+  // binary32 values of one magnitude share their top bits, and binary16 ones may be few and the same: four
+  // copies of the first histogram keep the lanes of a wavefront from all adding to one word
+  constexpr int kCopies = F16 && !WHOLE ? 1 : 4;
   extern __shared__ unsigned short order[];          // the set's tokens by rank (T <= kListTokens)
   __shared__ int sel[WHOLE ? 1 : kSampleTokens];     // more tokens: the one drawn of every stratum
   __shared__ __attribute__((aligned(16))) u32 shist[kCopies << kSampleBits];   // sample histogram
@@ -571,7 +577,7 @@ __global__ __launch_bounds__(NT) void k_sets(
   __shared__ int s_first;
   // (whole)
   __shared__ __attribute__((aligned(16))) u32 hist[WHOLE ? (F16 ? WHOLE : 1) : 1][WHOLE ? 2048 : 4];
-  __shared__ u32 s_lo[2], s_width[2], s_below[2], s_last;
+  __shared__ u32 s_lo[2], s_width[2], s_below[2], s_copies[2], s_last;
   __shared__ u32 s_share[64];                        // sampled tokens of every set
   __shared__ Lost s_lost[2];
   __shared__ FinishLds<WHOLE ? NT : 64, true> s_search;
@@ -599,7 +605,8 @@ __global__ __launch_bounds__(NT) void k_sets(
 
   // ---- 1: key range of the image, key interval of the set
   load_keys(0);
-  for (int i = tid; i < (kCopies << kSampleBits); i += NT) shist[i] = 0;
+  for (int i = tid; i < (kCopies << kSampleBits) / 4; i += NT)
+    reinterpret_cast<uint4*>(shist)[i] = make_uint4(0, 0, 0, 0);
   if (WHOLE && tid < 64) s_share[tid] = 0;
   if (!F16) {
     for (int i = tid; i < (int)(sizeof(snext) / sizeof(u32)); i += NT) (&snext[0][0])[i] = 0;
@@ -860,8 +867,8 @@ __global__ __launch_bounds__(NT) void k_sets(
       for (int i = 0; i < 4; ++i) {
         const u32 x = live[e] ? wd[i] : 0u;
         const u32 b0 = (x >> (kKeyBits - kSampleBits)) & 1023u, b1 = (x >> (16 + kKeyBits - kSampleBits)) & 1023u;
-        if (b0 != 0u && 2 * i < C) atomicAdd(&shist[b0], 1u);
-        if (b1 != 0u && 2 * i + 1 < C) atomicAdd(&shist[b1], 1u);
+        if (b0 != 0u && 2 * i < C) atomicAdd(&shist[b0 * kCopies + (lane & (kCopies - 1))], 1u);
+        if (b1 != 0u && 2 * i + 1 < C) atomicAdd(&shist[b1 * kCopies + (lane & (kCopies - 1))], 1u);
       }
     } else {
       TX x[V];
@@ -973,7 +980,7 @@ __global__ __launch_bounds__(NT) void k_sets(
         hs[q] = shist;
         rs[q] = sq[q].rk;
       }
-      find_ranks<NT, NR, 1, true>(hs, rs, stot, s_bin, s_before, cum, m);
+      find_ranks<NT, NR, kCopies, true>(hs, rs, stot, s_bin, s_before, cum, m);
       for (int i = tid; i < NR * kBins / 4; i += NT) reinterpret_cast<uint4*>(&hist[0][0])[i] = make_uint4(0, 0, 0, 0);
       __syncthreads();
 #pragma unroll
@@ -981,43 +988,88 @@ __global__ __launch_bounds__(NT) void k_sets(
         if (wave == q) {
           u32 first, wd;
           place_bins(cum, (int)s_bin[q], sq[q], m, q == NR - 1 ? Wfew : W, W, first, wd);
-          if (lane == 0) { s_lo[q] = first; s_width[q] = wd; s_below[q] = 0; }
+          // Where an eighth of the sample lies in the rank's cell (ordinary data has a fiftieth there) a few keys hold
+          // most of the set: the interval's bins get as many copies as there is room for, each in the next bank.
+          const int cell = (int)s_bin[q];
+          const bool hot = ((cell < 1023 ? cum[cell + 1] : m) - cum[cell]) * 8 >= m && wd <= 1024u;
+          if (lane == 0) {
+            s_lo[q] = first; s_width[q] = wd; s_below[q] = 0;
+            s_copies[q] = !hot ? 0u : wd <= 512u ? 2u : 1u;
+          }
         }
       }
       __syncthreads();
-      u32 first[NR], wd[NR], below[NR];
+      u32 first[NR], wd[NR], below[NR], copies[NR];    // (log2)
+      bool hot = false;
 #pragma unroll
-      for (int q = 0; q < NR; ++q) { first[q] = s_lo[q]; wd[q] = s_width[q]; below[q] = 0; }
-      own.visit([&](const uint4& p) {
-                           const u32 wd4[4] = {p.x, p.y, p.z, p.w};
+      for (int q = 0; q < NR; ++q) {
+        first[q] = s_lo[q];
+        wd[q] = s_width[q];
+        below[q] = 0;
+        copies[q] = (u32)__builtin_amdgcn_readfirstlane((int)s_copies[q]);
+        hot = hot || copies[q] != 0;
+      }
+      // (two versions, because an address without copies takes an instruction less)
+      auto look = [&](auto several) {
+        u32* bins[NR];
+        u32 by[NR];
 #pragma unroll
-                           for (int c = 0; c < 4; ++c) {
-                             const s2v kk = __builtin_bit_cast(s2v, wd4[c] & 0x7FFF7FFFu);
+        for (int q = 0; q < NR; ++q) {
+          by[q] = decltype(several)::value ? copies[q] : 0u;
+          bins[q] = decltype(several)::value ? hist[q] + (lane & ((1 << copies[q]) - 1)) : hist[q];
+        }
+        own.visit([&](const uint4& p) {
+          const u32 wd4[4] = {p.x, p.y, p.z, p.w};
 #pragma unroll
-                             for (int q = 0; q < NR; ++q) {
-                               // both halves at once, see k_bracket_hist
-                               const u32 d2 = __builtin_bit_cast(u32, kk - __builtin_bit_cast(s2v, first[q] | (first[q] << 16)));
-                               below[q] += (u32)__builtin_popcount(d2 & 0x80008000u);
-                               const u32 dl = d2 & 0xFFFFu, dh = d2 >> 16;
-                               if (dl < wd[q]) atomicAdd(&hist[q][dl], 1u);
-                               if (dh < wd[q]) atomicAdd(&hist[q][dh], 1u);
-                             }
-                           }
-                         },
-                         [&](TX x) {
-                           const u32 kx = Elem<TX>::key(x);
+          for (int c = 0; c < 4; ++c) {
+            const s2v kk = __builtin_bit_cast(s2v, wd4[c] & 0x7FFF7FFFu);
 #pragma unroll
-                           for (int q = 0; q < NR; ++q) {
-                             below[q] += kx < first[q] ? 1u : 0u;
-                             if (kx >= first[q] && kx - first[q] < wd[q]) atomicAdd(&hist[q][kx - first[q]], 1u);
-                           }
-                         });
+            for (int q = 0; q < NR; ++q) {
+              // both halves at once, see k_bracket_hist
+              const u32 d2 = __builtin_bit_cast(u32, kk - __builtin_bit_cast(s2v, first[q] | (first[q] << 16)));
+              below[q] += (u32)__builtin_popcount(d2 & 0x80008000u);
+              const u32 dl = d2 & 0xFFFFu, dh = d2 >> 16;
+              if (dl < wd[q]) atomicAdd(&bins[q][dl << by[q]], 1u);
+              if (dh < wd[q]) atomicAdd(&bins[q][dh << by[q]], 1u);
+            }
+          }
+        },
+                  [&](TX x) {
+                    const u32 kx = Elem<TX>::key(x);
+#pragma unroll
+                    for (int q = 0; q < NR; ++q) {
+                      below[q] += kx < first[q] ? 1u : 0u;
+                      if (kx >= first[q] && kx - first[q] < wd[q]) atomicAdd(&bins[q][kx - first[q] << by[q]], 1u);
+                    }
+                  });
+      };
+      if (__builtin_expect(hot, 0))
+        look(std::true_type());
+      else
+        look(std::false_type());
 #pragma unroll
       for (int q = 0; q < NR; ++q) {
         const u32 t = group_sum_u32<64>(below[q]);
         if (lane == 63 && t) atomicAdd(&s_below[q], t);
       }
       __syncthreads();
+      if (__builtin_expect(hot, 0)) {                  // the copies of a bin together, at its place without copies
+        u32 v[NR][2];
+#pragma unroll
+        for (int q = 0; q < NR; ++q) {
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            const u32* at = &hist[q][((i * NT + tid) << copies[q]) & (kBins - 1)];
+            v[q][i] = at[0] + (copies[q] > 0 ? at[1] : 0u) + (copies[q] > 1 ? at[2] + at[3] : 0u);
+          }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < NR; ++q)
+          if (copies[q])
+            for (int i = 0; i < 2; ++i) hist[q][i * NT + tid] = (u32)(i * NT + tid) < wd[q] ? v[q][i] : 0u;
+        __syncthreads();
+      }
       if (S > 1) {
         // The parts of a set meet in its global histogram, and the last to arrive goes on.  All that they
         // exchange is written and read by device-scope atomic operations, which are performed where all
