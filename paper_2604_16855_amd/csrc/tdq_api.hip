@@ -262,8 +262,7 @@ static int calibrate_after_stats(const void* X, tdq_dtype dt, int32_t B, int32_t
   void* part = ws + wl.part;
   const int extra = calibration_extra(dt, B, T, C, p);
   if (extra >= 0) {
-    const int W = two_passes && extra > 0 ? Wmax / 2 : Wmax, few = bracket_bins_zr(G);
-    if (launch_sets_whole(X, dt, B, T, C, ld_x, G, two_passes ? 2 : 1, extra, few < W ? few : W, W, r, mean, m2,
+    if (launch_sets_whole(X, dt, B, T, C, ld_x, G, two_passes ? 2 : 1, extra, bracket_bins_zr(G), Wmax, r, mean, m2,
                           group_id, sc, bhist, part, img_flag, status, clip, scale, stats, st) != hipSuccess)
       return TDQ_ERR_HIP;
     return TDQ_OK;

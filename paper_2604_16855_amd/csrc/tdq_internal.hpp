@@ -154,7 +154,7 @@ hipError_t launch_sets(const void* X, tdq_dtype dt, int B, int T, int C, long lo
                        unsigned* status, hipStream_t st);
 // The same for images of up to kWholeTokens tokens, seen through to the radii: the G + extra workgroups of
 // an image are shared out to its sets and read their rows; ranks = 2: the percentile base radius as well.
-// bhist (ranks * W words per set) and ctl (kSetCtl words per set) are cleared by the statistics kernel if
+// bhist (W words per set, for both ranks) and ctl (kSetCtl words per set) are cleared by the statistics kernel if
 // extra > 0.
 constexpr int kWholeTokens = 8192;     // (the list of tokens and the rest fit 64 KiB of LDS)
 constexpr int kListTokens = 16384;     // most tokens of an image listed by rank in LDS

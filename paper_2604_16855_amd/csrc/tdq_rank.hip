@@ -487,22 +487,29 @@ __device__ __forceinline__ SampleRank sample_rank(u32 k, u32 n, u32 m, int n_sel
   return s;
 }
 
+// binary16: whether W one-key bins centred on the middle of the bin bm of the sample's histogram that holds sampled
+// rank s reach two and a half standard deviations to either side (cum as in place_bins).
+__device__ __forceinline__ bool bins_reach(const u32* cum, int bm, const SampleRank& s, u32 m, int W) {
+  constexpr int kCell = 1 << (15 - kSampleBits);
+  const int reach = (int)(2.5f * s.dev) + 1, rk = (int)s.rk;
+  auto below_bin = [&](int c) { return c <= 0 ? 0 : c >= 1024 ? (int)m : (int)cum[c]; };
+  const int under = below_bin(bm - W / 2 / kCell + 1), upto = below_bin(bm + W / 2 / kCell);
+  return (under == 0 || rk - under >= reach) && (upto == (int)m || upto - rk >= reach);
+}
+
 // binary16: the one-key bins around sampled rank s, which lies in bin bm of the sample's histogram of 1024
 // bins (the low key bits do not matter to the interval), cum = sampled elements before every bin.  Wfew of
-// them centred on the middle of that bin, if they reach two and a half standard deviations to either
-// side.  Else the rank lies where keys are sparse (just above the zeros of a rectified activation, between
-// the values of a coarse grid): the W bins that leave equally many sampled keys on either side of it.  By
-// one wavefront.
+// them centred on the middle of that bin, if they reach far enough.  Else the rank lies where keys are sparse
+// (just above the zeros of a rectified activation, between the values of a coarse grid): the W bins that leave
+// equally many sampled keys on either side of it.  By one wavefront.
 __device__ __forceinline__ void place_bins(const u32* cum, int bm, const SampleRank& s, u32 m, int Wfew,
                                            int W, u32& first, u32& width) {
   constexpr int kCell = 1 << (15 - kSampleBits);
   const int lane = threadIdx.x & 63, rk = (int)s.rk;
-  const int reach = (int)(2.5f * s.dev) + 1;
   auto below_bin = [&](int c) { return c <= 0 ? 0 : c >= 1024 ? (int)m : (int)cum[c]; };
-  const int under = below_bin(bm - Wfew / 2 / kCell + 1), upto = below_bin(bm + Wfew / 2 / kCell);
   int lo = bm * kCell + kCell / 2 - Wfew / 2;
   width = (u32)Wfew;
-  if (!((under == 0 || rk - under >= reach) && (upto == (int)m || upto - rk >= reach))) {
+  if (!bins_reach(cum, bm, s, m, Wfew)) {
     width = (u32)W;
     const int nb = W / kCell;                        // 8 to 64 candidates, one per lane
     const int c0 = bm - nb + 1 + lane;
@@ -983,18 +990,33 @@ __global__ __launch_bounds__(NT) void k_sets(
       find_ranks<NT, NR, kCopies, true>(hs, rs, stot, s_bin, s_before, cum, m);
       for (int i = tid; i < NR * kBins / 4; i += NT) reinterpret_cast<uint4*>(&hist[0][0])[i] = make_uint4(0, 0, 0, 0);
       __syncthreads();
+      // Bins of a rank at most.  Workgroups that share a set meet in its W words, so two ranks have half each; but
+      // where that does not reach for one of them and 512 do for the other, it has the rest (the zr quantile just
+      // above 18 % zeros: [5, 1019, 604] with 4 sets and a percentile 61 us, 26 so, 48 by the chain).
+      int room[NR];
+      for (int q = 0; q < NR; ++q) room[q] = NR == 2 && S > 1 ? W / 2 : W;
+      if (NR == 2 && S > 1 && W == 2048) {
+        auto reach = [&](int q, int bins) { return bins_reach(cum, (int)s_bin[q], sq[q], m, bins); };
+        const bool half_0 = reach(0, W / 2), half_1 = reach(NR - 1, W / 2);
+        const bool more_0 = !half_0 && half_1 && reach(NR - 1, 512), more_1 = !half_1 && reach(0, 512);
+        room[0] = more_1 ? 512 : more_0 ? 1536 : W / 2;
+        room[NR - 1] = more_1 ? 1536 : more_0 ? 512 : W / 2;
+      }
 #pragma unroll
       for (int q = 0; q < NR; ++q) {
         if (wave == q) {
           u32 first, wd;
-          place_bins(cum, (int)s_bin[q], sq[q], m, q == NR - 1 ? Wfew : W, W, first, wd);
+          const int most = room[q];
           // Where an eighth of the sample lies in the rank's cell (ordinary data has a fiftieth there) a few keys hold
           // most of the set: the interval's bins get as many copies as there is room for, each in the next bank.
           const int cell = (int)s_bin[q];
-          const bool hot = ((cell < 1023 ? cum[cell + 1] : m) - cum[cell]) * 8 >= m && wd <= 1024u;
+          const bool hot = ((cell < 1023 ? cum[cell + 1] : m) - cum[cell]) * 8 >= m;
+          int few = q == NR - 1 && Wfew < most ? Wfew : most;
+          few = hot && few > 512 ? 512 : few;
+          place_bins(cum, cell, sq[q], m, few, most, first, wd);
           if (lane == 0) {
             s_lo[q] = first; s_width[q] = wd; s_below[q] = 0;
-            s_copies[q] = !hot ? 0u : wd <= 512u ? 2u : 1u;
+            s_copies[q] = !hot || wd > 1024u ? 0u : wd <= 512u ? 2u : 1u;
           }
         }
       }
@@ -1075,13 +1097,13 @@ __global__ __launch_bounds__(NT) void k_sets(
         // exchange is written and read by device-scope atomic operations, which are performed where all
         // XCDs see them, so no cache has to be written back or invalidated; s_waitcnt waits until those of
         // this wavefront have been, the barrier for the other wavefronts, and only then is the arrival counted.
-        u32* gh = bhist + (size_t)idx * (NR * W);
+        u32* gh = bhist + (size_t)idx * W;
         u32* ctl = wa.ctl + (size_t)idx * kSetCtl;
 #pragma unroll
         for (int q = 0; q < NR; ++q) {
           for (int i = tid; i < (int)wd[q]; i += NT) {
             const u32 v = hist[q][i];
-            if (v) atomicAdd(&gh[q * W + i], v);
+            if (v) atomicAdd(&gh[q * room[0] + i], v);
           }
           if (tid == q && s_below[q]) atomicAdd(&ctl[1 + q], s_below[q]);
         }
@@ -1097,7 +1119,7 @@ __global__ __launch_bounds__(NT) void k_sets(
 #pragma unroll
           for (int i = 0; i < kPer; ++i) {
             const int at = i * NT + tid;
-            v[i] = at < (int)wd[q] ? __hip_atomic_load(&gh[q * W + at], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+            v[i] = at < (int)wd[q] ? __hip_atomic_load(&gh[q * room[0] + at], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
           }
 #pragma unroll
           for (int i = 0; i < kPer; ++i) hist[q][i * NT + tid] = v[i];

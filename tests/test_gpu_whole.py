@@ -63,7 +63,7 @@ def _data(kind, B, T, C, dtype, seed):
 @pytest.mark.parametrize("dtype,B,T,C,G,pad", [
     (np.float16, 2, 1, 1, 1, 0), (np.float16, 3, 511, 24, 16, 0), (np.float16, 2, 513, 33, 5, 2),
     (np.float16, 2, 1025, 17, 16, 1), (np.float16, 1, 2049, 56, 12, 0), (np.float16, 1, 4097, 40, 8, 0),
-    (np.float16, 1, 8192, 9, 3, 0), (np.float16, 5, 70, 1031, 64, 0), (np.float16, 2, 300, 520, 16, 3),
+    (np.float16, 1, 8192, 9, 3, 0), (np.float16, 5, 70, 1031, 64, 0), (np.float16, 2, 300, 520, 16, 3), (np.float16, 49, 30, 40, 24, 0),
     (np.float32, 2, 1, 3, 2, 0), (np.float32, 2, 512, 66, 16, 0), (np.float32, 1, 1025, 37, 8, 3),
     (np.float32, 1, 8192, 7, 5, 0), (np.float32, 3, 20, 2049, 64, 0),
 ])
@@ -85,7 +85,8 @@ def test_against_oracle(dtype, B, T, C, G, pad, kind, pct):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("B,T,C,G", [(19, 167, 2056, 12), (2, 2231, 2752, 32), (42, 863, 29, 15)])
+@pytest.mark.parametrize("B,T,C,G", [(19, 167, 2056, 12), (2, 2231, 2752, 32), (42, 863, 29, 15),
+                                     (51, 2213, 103, 4)])
 def test_few_values_cost_little_more(B, T, C, G):
     """Keys that all meet in a few words of LDS: at most twice the time of ordinary data (1.1 to 1.5 times
     measured, 2 to 3.5 times where every addition went to one word)."""
