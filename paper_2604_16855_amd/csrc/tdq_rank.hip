@@ -128,7 +128,9 @@ __device__ __forceinline__ BinPick pick_bin(const u32* __restrict__ hb, int W, u
       }
     }
   }
-  uint4 q = group == 0 ? c[0] : c[1];
+  // (member by member: a choice between the two of c would put them into scratch memory)
+  uint4 q = make_uint4(group == 0 ? c[0].x : c[1].x, group == 0 ? c[0].y : c[1].y, group == 0 ? c[0].z : c[1].z,
+                       group == 0 ? c[0].w : c[1].w);
   if (quads > 2) q = mine_bins[group];
   u32 bin = (u32)(4 * (lane * quads + group));
   const u32 v[4] = {q.x, q.y, q.z, q.w};        // ... and the bin in it
@@ -397,9 +399,12 @@ __device__ __forceinline__ u32 search_rows(const TX* __restrict__ Xb, long long 
     if (incl - mine < need && need <= incl) {   // at most one thread
       unsigned long long cum = incl - mine;
       int i = 0;
-      for (; i < kPer - 1; ++i) {
-        if (cum + c[i] >= need) break;
-        cum += c[i];
+      bool found = false;                       // (a break would put c into scratch memory)
+#pragma unroll
+      for (int k = 0; k < kPer - 1; ++k) {
+        found = found || cum + c[k] >= need;
+        cum += found ? 0u : c[k];
+        i += found ? 0 : 1;
       }
       s.digit = (u32)(tid * kPer + i);
       s.rest = need - cum;
@@ -465,7 +470,9 @@ __device__ __forceinline__ u32 search_rows(const TX* __restrict__ Xb, long long 
 // different values, which meet in few words, were slower than by the chain until the sample's histogram and
 // such an interval's got copies; calibration, us by the chain, without and with copies: one value [19, 167, 2056]
 // with 12 sets 51, 85, 35 and [2, 7625, 920] with 64 87, 113, 47; values within 1e-4 of 1 [29, 128, 1080] with 12 52,
-// 89, 34; Laplace [16, 484, 320] 21.6, 17.7, 17.2.
+// 89, 34; Laplace [16, 484, 320] 21.6, 17.7, 17.2.  80 registers (forced: 2 more are spilled) leave three workgroups
+// on a CU, 768 sets at once; with 86 and two, calls of 1024 to 1536 sets took turns three times and many were
+// slower than by the chain: [40, 100, 64] with 32 sets 23.1, 24.7, 20.3, [60, 37, 88] with 24 24.2, 26.0, 21.2.
 // A rank k of a set of n elements as seen by a sample of m of them from n_sel tokens.
 struct SampleRank {
   u32 rk;                     // the rank of the sample that corresponds to k
@@ -555,7 +562,7 @@ __device__ __forceinline__ Lost lost_rank(u32 k, u32 n, u32 below, u32 inside, u
 }
 
 template <typename TX, int NT, int RD, int SM, int WHOLE>
-__global__ __launch_bounds__(NT) void k_sets(
+__global__ __launch_bounds__(NT, (WHOLE == 1 && sizeof(TX) == 2 && RD <= 8 ? 6 : 1)) void k_sets(
     const TX* __restrict__ X, long long ld, int T, int C, int G, int Wfew, int W, int cells, int aligned,
     const float* __restrict__ r, const double* __restrict__ mean, const double* __restrict__ m2,
     int* __restrict__ gid, Scalars sc, int pass, int keep_base, GroupWork* __restrict__ grp,
