@@ -5,7 +5,7 @@
 #include <stdlib.h>
 #include <string.h>
 
-#include "tdq_internal.hpp"
+#include "tdq_device.hpp"
 
 namespace tdq {
 
@@ -154,8 +154,8 @@ static bool samples_rank(tdq_dtype dt, int B, int T, int C, int G, bool exact_on
 }
 
 // Whether the sampled route takes one kernel for assignment and rank select together, and if so with how many
-// workgroups per image beyond one per set (-1 = no).  Figures are us per layer, one kernel against three (or
-// four).
+// workgroups per image beyond one per set (-1 = no).  Figures are us per layer or calibration, one kernel
+// against three (or four).
 //   * A workgroup for every 8 Ki elements, and no more than 512 in all (two per CU): [8, 121, 512] with 16 sets
 //     22.1 / 22.0 / 21.1 with 64 / 16 / 8 Ki, [16, 484, 320] 35.8 / 34.2 / 33.2.
 //   * No more than 40 Ki elements for each (all tokens may be in one set), 64 Ki with two ranks: every workgroup of
@@ -163,12 +163,18 @@ static bool samples_rank(tdq_dtype dt, int B, int T, int C, int G, bool exact_on
 //     all sets.  [21, 536, 1344], 80 Ki each, 77.3 against 75.0; [28, 187, 1984], 124 Ki, 71.4 against 68.8;
 //     calibration of values on a grid, which meet in few words of LDS, [17, 5107, 131], 44 Ki, 60.8 against 46.8; but
 //     [14, 5850, 160], 29 Ki, percentile, 97.9 against 122.3.
+//   * One rank only (two save a whole sweep): fewer than 64 workgroups beyond the first for a set, which all meet in
+//     the same words ([3, 2125, 1669] with one set, 169, 39.0 against 33.6, [2, 5545, 419] with two 36.8 against
+//     30.3; with 32 to 64 of them 41 calls of 8 Ki elements each 1.22 times as fast, 36 of more 1.04); at least a
+//     quarter of the rows that a workgroup's lanes take at a time, where it has more than 8 Ki elements ([2, 457, 6172]
+//     with 16 sets, two rows for eight wavefronts, 43.8 against 39.5); and with one or two sets of more than 4096
+//     tokens, each read by every workgroup, no more than 16 Ki elements ([58, 6152, 44] 52.7 against 47.8).
 //   * binary32 reads a set's rows twice, so one workgroup sees all of a set: [2, 1400, 32] (45 Ki elements) 38.6
-//     against 44.7, [5, 1280, 84] (107 Ki) 60.5 against 47.4, [1, 377, 416] (157 Ki) 84.0 against 48.2.
-//   * Up to 1536 sets in all: more workgroups of 512 threads than the chip holds at once take turns with a chain
-//     each, where k_sets has 256 threads and the sweep's workgroups serve all sets.  Calibration, [49, 74, 832] with 32
-//     sets (1568) 31.0 against 29.8, [58, 20, 9] with 32 42.8 against 36.6, [64, 322, 56] with 64 55.7 against 45.6; but
-//     [62, 162, 10] with 24 (1488) 37.4 against 40.0.  binary32, whose kernel needs more registers: up to 1024, 512
+//     against 44.7, [5, 1280, 84] (107 Ki) 60.5 against 47.4, [1, 377, 416] (157 Ki) 84.0 against 48.2; an image that
+//     is one set by itself 40 Ki ([2, 576, 74], 42 Ki, 45.0 against 34.1).
+//   * Up to 1536 sets in all, which take two turns on the chip: [49, 74, 832] with 32 sets (1568) 31.0 against 29.8,
+//     [58, 20, 9] with 32 42.8 against 36.6, [64, 322, 56] with 64 55.7 against 45.6; of 94 calls of 1024 to 1536 sets
+//     none is slower, half are faster than 1.27 times.  binary32, whose kernel needs more registers: up to 1024, 512
 //     with two ranks ([42, 3, 2424] with 32, 1344 sets, 48.2 against 41.9; percentile [52, 25, 8] with 16, 832 sets,
 //     72.4 against 60.4, [120, 13, 3821] with 5, 600 sets, 137 against 117; but [292, 187, 8] with 2, 584, 43.0
 //     against 79.8).
@@ -178,10 +184,16 @@ static int whole_extra(tdq_dtype dt, int B, int T, int C, int G, bool two_ranks)
   const long long e = (long long)T * C;
   const long long sets = (long long)B * G;
   if (T > kWholeTokens || sets > (dt == TDQ_F16 ? 1536 : two_ranks ? 512 : 1024)) return -1;
-  if (dt == TDQ_F32) return e <= 57344 ? 0 : -1;
+  if (dt == TDQ_F32) return e <= (G == 1 ? 40960 : 57344) ? 0 : -1;
   long long extra = e / 8192;
   const long long most = 512 / B - G;
   if (extra > most) extra = most > 0 ? most : 0;
+  if (!two_ranks) {
+    const int slots = 512 / sweep_lanes_per_row(C, 8);       // rows that a workgroup's lanes take at a time
+    if (extra >= 64 * G) return -1;
+    if (e > 8192 * (extra + 1) && 4ll * T < slots * (extra + 1)) return -1;
+    if (G <= 2 && T > 4096 && e > 16384 * (extra + 1)) return -1;
+  }
   if (two_ranks && extra > 0 && bracket_bins(G) < 1024) return -1;
   if (e > (two_ranks ? 65536 : 40960) * (extra + 1)) return -1;
   return (int)extra;

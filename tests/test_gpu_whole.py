@@ -25,6 +25,13 @@ def _extra(dt, B, T, C, G, pct=0.0):
     (tdq.TDQ_F16, 96, 50, 32, 16, 0.0, 0), (tdq.TDQ_F16, 97, 50, 32, 16, 0.0, -1),          # 1536 sets
     (tdq.TDQ_F16, 1, 127, 64, 17, 0.99, 0), (tdq.TDQ_F16, 1, 100, 64, 65, 0.0, -1),
     (tdq.TDQ_F32, 2, 896, 64, 8, 0.0, 0), (tdq.TDQ_F32, 2, 897, 64, 8, 0.99, -1),
+    (tdq.TDQ_F32, 2, 640, 64, 1, 0.0, 0), (tdq.TDQ_F32, 2, 641, 64, 1, 0.0, -1),
+    (tdq.TDQ_F16, 1, 4095, 128, 1, 0.0, 63), (tdq.TDQ_F16, 1, 4096, 128, 1, 0.0, -1),      # many share a set
+    (tdq.TDQ_F16, 1, 4096, 128, 2, 0.0, 64), (tdq.TDQ_F16, 3, 2125, 1669, 1, 0.99, 169),
+    (tdq.TDQ_F16, 16, 58, 5470, 4, 0.0, 28), (tdq.TDQ_F16, 16, 57, 5470, 4, 0.0, -1),      # few rows for each
+    (tdq.TDQ_F16, 16, 57, 5470, 4, 0.99, 28), (tdq.TDQ_F16, 1, 57, 5470, 4, 0.0, 38),
+    (tdq.TDQ_F16, 58, 6152, 21, 1, 0.0, 7), (tdq.TDQ_F16, 58, 6152, 22, 1, 0.0, -1),       # many tokens in one set
+    (tdq.TDQ_F16, 58, 4096, 44, 1, 0.0, 7), (tdq.TDQ_F16, 58, 6152, 44, 1, 0.99, 7),
 ])
 def test_rule(dt, B, T, C, G, pct, extra):
     assert _extra(dt, B, T, C, G, pct) == extra
