@@ -244,12 +244,12 @@ struct RowVisitor {
 };
 
 // One pass of the search over rows list[0 .. n - 1]: the histogram of digits (key - k0 >> shift) - off.
-// Digit 0 takes all that is below as well and is counted in a register, the last digit takes all that is above
-// and is not counted (what the others do not hold): either may be most of the set, and would meet in one word
-// of LDS.  binary32: of the keys in [k0, k0 + span).  binary16: of all keys of the set, so that those below
+// Digit 0 takes all that is below as well and is counted in a register (the result), the last digit takes all
+// that is above and is not counted (what the others do not hold): either may be most of the set, and would meet in
+// one word of LDS.  binary32: of the keys in [k0, k0 + span).  binary16: of all keys of the set, so that those below
 // need no second compare, both halves of a word at once as in k_bracket_hist.
 template <typename TX, int NT, int Q, bool AHEAD>
-__device__ __forceinline__ void count_rows(const TX* __restrict__ Xb, long long ld, int C, int L,
+__device__ __forceinline__ u32 count_rows(const TX* __restrict__ Xb, long long ld, int C, int L,
                                            const unsigned short* list, int n, u32 k0, u32 span, int shift,
                                            int off, u32* h) {
   constexpr int kBins = 1 << kFinishBits;
@@ -257,7 +257,8 @@ __device__ __forceinline__ void count_rows(const TX* __restrict__ Xb, long long 
   RowVisitor<TX, NT, Q, AHEAD> rows(Xb, ld, C, L, list, n);
   if constexpr (sizeof(TX) == 2) {
     const u32 first = k0 + (u32)off + (1u << shift);           // the first key of digit 1 (off: shift is 0)
-    const u32 counted = (u32)(kBins - 2) << shift;             // keys of digits 1 to kBins - 2
+    // keys of digits 1 to kBins - 2, no further than the range (what lies past it may be many ties)
+    const u32 most = (u32)(kBins - 2) << shift, left = k0 + span - first, counted = left < most ? left : most;
     const u32 first2 = first | (first << 16);
     rows.visit([&](const uint4& q) {
       const u32 wd[4] = {q.x, q.y, q.z, q.w};
@@ -291,7 +292,7 @@ __device__ __forceinline__ void count_rows(const TX* __restrict__ Xb, long long 
     },
                count);
   }
-  if (low) atomicAdd(&h[0], low);
+  return low;
 }
 
 // binary16: which window of `span` keys from k0 to look at, where the set has `from` keys below k0 and `to` below
@@ -341,10 +342,10 @@ __device__ __forceinline__ u32 search_rows(const TX* __restrict__ Xb, long long 
     __syncthreads();
     for (int i = tid; i < kBins; i += NT) s.h[i] = 0;
     if (tid == 0) s.digit = kBins - 1;
+    u32 low = 0;
     if constexpr (LISTED) {
       __syncthreads();
-      count_rows<TX, NT, 8, false>(Xb, ld, C, L, list, T, k0, span, shift, off, s.h);
-      __syncthreads();
+      low = count_rows<TX, NT, 8, false>(Xb, ld, C, L, list, T, k0, span, shift, off, s.h);
     } else {
       for (int t0 = 0; t0 < T; t0 += kFinishTokens) {
         constexpr int kIds = kFinishTokens / NT;
@@ -373,10 +374,16 @@ __device__ __forceinline__ u32 search_rows(const TX* __restrict__ Xb, long long 
           at += (u32)__popcll(m);
         }
         __syncthreads();
-        count_rows<TX, NT, 4, false>(Xb + (long long)t0 * ld, ld, C, L, s.list, (int)n, k0, span, shift, off, s.h);
+        low += count_rows<TX, NT, 4, false>(Xb + (long long)t0 * ld, ld, C, L, s.list, (int)n, k0, span, shift, off,
+                                            s.h);
         __syncthreads();                        // `list` and `wtot` are reused
       }
     }
+    // (one addition a wavefront: they all go to one word; by every thread, after every look at 2048 tokens, [38,
+    // 37536, 8] with 4 sets, one missed, took 178 us and not 125)
+    low = group_sum_u32<64>(low);
+    if (lane == 63 && low) atomicAdd(&s.h[0], low);
+    __syncthreads();
     // the bin where the running count reaches `need`
     unsigned long long mine = 0;
     u32 c[kPer];
