@@ -36,6 +36,11 @@ def test_key_intervals_are_the_quotient_rule(G):
         assert np.array_equal(_interval_ids(key, lo, hi, G), want), (G, lo, hi)
 
 
+def _extra(dt, B, T, C, G):
+    """-1: the chain of kernels, else one kernel with that many workgroups more than sets an image."""
+    return tdq.lib().tdq_whole_extra(dt, B, T, C, G, tdq.C.c_double(0.0))
+
+
 def _tokens(T, C, dtype, seed):
     rng = np.random.Generator(np.random.PCG64(seed))
     X = rng.laplace(0, 1, (2, T, C)) * rng.lognormal(0, 1.5, (2, T, 1))
@@ -55,13 +60,36 @@ def test_set_records_at_batch_edges(T, C, G):
     U.assert_calibration_matches(U.gpu_calibrate(X, p, ld_pad=3), X, p)
 
 
+ROWS = [1, 7, 8, 9, 64, 65, 127, 129, 255, 263, 513, 1031, 2047, 2057]
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("C", [1, 7, 8, 9, 64, 65, 127, 129, 255, 263, 513, 1031, 2047, 2057])
+@pytest.mark.parametrize("C", ROWS)
 def test_sweep_row_lengths(C):
-    """Rows of every number of pieces per lane the sweep distinguishes, one element short of a
-    piece or past one, at element alignment (odd row stride), several rows per lane group."""
+    """Rows of every number of pieces per lane, one element short of a piece or past one, at
+    element alignment (odd row stride), several rows per lane group: 333 tokens and 12 sets,
+    which one kernel calibrates."""
     import parity_util as U
+    assert _extra(tdq.TDQ_F16, 2, 333, C, 12) >= 0
     X = _tokens(333, C, np.float16, 7 * C)
+    p = tdq.default_params(12)
+    for pad in (0, 1):
+        U.assert_calibration_matches(U.gpu_calibrate(X, p, ld_pad=pad), X, p)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dt", ["f16", "f32"])
+@pytest.mark.parametrize("C", ROWS)
+def test_chain_row_lengths(C, dt):
+    """The same row lengths where the chain of kernels calibrates, so that its sweep over X reads
+    them: one token more than one kernel takes, or (from 255 channels on) more sets."""
+    import parity_util as U
+    B, T = (1, 8193) if C < 255 else (129, 20)
+    np_dt, tdq_dt = (np.float16, tdq.TDQ_F16) if dt == "f16" else (np.float32, tdq.TDQ_F32)
+    assert _extra(tdq_dt, B, T, C, 12) == -1
+    rng = np.random.Generator(np.random.PCG64(11 * C))
+    X = rng.laplace(0, 1, (B, T, C)) * rng.lognormal(0, 1.5, (B, T, 1))
+    X = np.clip(X, -60000, 60000).astype(np_dt)
     p = tdq.default_params(12)
     for pad in (0, 1):
         U.assert_calibration_matches(U.gpu_calibrate(X, p, ld_pad=pad), X, p)
