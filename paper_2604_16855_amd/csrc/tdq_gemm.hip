@@ -1561,10 +1561,13 @@ hipError_t launch_w4a4_gemm(const uint8_t* Qx, long long ld_q, const int* gid, c
 // as in k_w4a4_gemm_pipe); 64 x 128 tiles (MB = 1) leave three workgroups on a CU, so that one's vector
 // work covers another's waits and the last round of tiles is even.  A lane's results are runs of 4 outputs in
 // 32 rows, so they leave through LDS as whole lines.
-// Before, 128 x 128 tiles staged through registers, two workgroups per CU, 46 vector instructions per matrix
-// instruction (42 here, 39 with MB = 2): us, before and now, 8192 x 768 x 768 20.1 and 16.9, 968 x 512 x 512 15.9
-// and 7.5, 7744 x 320 x 1280 27.8 and 15.9, 4096 x 4096 x 64 66.6 and 38.5, 131072 x 1024 x 4096 1359 and 1312.
-// The 42 instructions alone are 10.2 of the 16.9 (4 cycles each on a SIMD).
+// 128 x 128 tiles staged through registers, two workgroups per CU, and now, us: 8192 x 768 x 768 20.3 and 16.5, 968 x
+// 512 x 512 15.9 and 7.8, 7744 x 320 x 1280 26.9 and 14.7, 4096 x 4096 x 64 66.3 and 38.0, 131072 x 1024 x 4096 1354 and
+// 1271, 131072 x 4096 x 1024 1346 and 1215.  What it gave is waits (for LDS 47 M cycles and 2 M in the last but one) and
+// even rounds of tiles.  The loop has 49 vector instructions per matrix instruction (44 with MB = 2): 32 of the
+// rescale, 9 or 6 of nibble expansion, 4 copies of accumulators, as the choice between a whole and a masked stage
+// inside the loop keeps two sets of registers for them, addresses.  At 4 cycles each on a SIMD they are 11.8 of the 16.5.
+// The 8-byte reads of the fragments meet in their banks (80 M cycles over 256 CUs); the vector work covers it.
 // ---------------------------------------------------------------------------
 // 64 floats from 64 addresses -> 64 consecutive floats of LDS
 __device__ __forceinline__ void dma4(const float* gptr, unsigned lds_base) {
@@ -1776,7 +1779,7 @@ hipError_t launch_w4a4_gemm_blocks(const uint8_t* Qx, long long ld_q, const floa
   const int esz = y_dt == TDQ_F32 ? 4 : 2;
   const int y_vec_ok = (reinterpret_cast<uintptr_t>(Y) & 15) == 0 && ld_y * esz % 16 == 0 ? 1 : 0;
   const int n_tiles = (N + 127) / 128;
-  // 128 rows a tile where there are many tiles: 39 vector instructions per matrix instruction instead of 42 weigh
+  // 128 rows a tile where there are many tiles: 44 vector instructions per matrix instruction instead of 49 weigh
   // more than an even last round and a third workgroup per CU.  64 / 128 rows, us: 32768 x 320 x 1280 (2560
   // tiles of 128) 52.2 / 53.6, 131072 x 4096 x 1024 (8192) 1285 / 1223.
   const bool tall = (long long)((M + 127) / 128) * n_tiles >= 4096;
