@@ -259,7 +259,8 @@ int tdq_quantize_act_blocks_chw(const void* X, tdq_dtype dt, int32_t B, int32_t 
 /*
  * tdq_calibrate_groups followed by tdq_quantize_act in ONE launch, for shapes where launch
  * latency rather than bandwidth sets the time (up to a few hundred kilobytes per image;
- * it is correct for any size, one workgroup per image).  Same definitions and outputs:
+ * it is correct for any size).  Few images that each fit the registers of a workgroup take a
+ * workgroup per image and token set, all others one per image.  Same definitions and outputs:
  * group_id, clip, scale, stats (or NULL) as from tdq_calibrate_groups, Qx as from
  * tdq_quantize_act with those radii.  The rank of every set is found by a radix select
  * on LDS histograms (exact).  n_groups <= TDQ_FUSED_MAX_GROUPS, else
