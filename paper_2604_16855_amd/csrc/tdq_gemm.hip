@@ -1547,11 +1547,15 @@ hipError_t launch_w4a4_gemm(const uint8_t* Qx, long long ld_q, const int* gid, c
 //   Y[m, n] = s_w[n] * sum_kb Delta[m, kb] * acc_kb[m, n],
 //   acc_kb[m, n] = sum_{i in block kb} Qx[m, i] * Qw[n, i]   (|acc_kb| <= 32 * 64)
 // The int32 accumulation cannot run over the whole of K any more: one matrix
-// instruction (K = 32) is exactly one block, and its 16 results per lane are converted
-// and folded into a binary32 accumulator with the block's step,
+// instruction (K = 32) is exactly one block, and its 16 results per lane are turned into
+// floats and folded into a binary32 accumulator with the block's step,
 //   f <- fma(float(acc_kb), Delta[m, kb], f),   kb ascending,
 // i.e. 32 vector operations per matrix instruction: this kernel is bound by the vector
-// unit, not by the matrix cores (which idle three quarters of the time).  The factor 256
+// unit, not by the matrix cores (which idle three quarters of the time).
+// The floats cost a subtraction each, not a conversion: the matrix instruction starts from
+// the bits of 1.5 * 2^23 instead of zero.  On this chip v_cvt_f32_i32 takes 4.8 cycles of a
+// SIMD with several wavefronts, an addition, a multiply-add or a bitwise operation 2.6 to
+// 3.1 (conversions, shifts, minima and three-operand integer forms run at half the rate).  The factor 256
 // of the nibble expansion is taken out once at the end (a power of two: exact).
 //
 // The weights are the row operand and the activations the column operand: a lane of the result then
@@ -1564,9 +1568,11 @@ hipError_t launch_w4a4_gemm(const uint8_t* Qx, long long ld_q, const int* gid, c
 // 128 x 128 tiles staged through registers, two workgroups per CU, and now, us: 8192 x 768 x 768 20.3 and 16.5, 968 x
 // 512 x 512 15.9 and 7.8, 7744 x 320 x 1280 26.9 and 14.7, 4096 x 4096 x 64 66.3 and 38.0, 131072 x 1024 x 4096 1354 and
 // 1271, 131072 x 4096 x 1024 1346 and 1215.  What it gave is waits (for LDS 47 M cycles and 2 M in the last but one) and
-// even rounds of tiles.  The loop has 49 vector instructions per matrix instruction (44 with MB = 2): 32 of the
-// rescale, 9 or 6 of nibble expansion, 4 copies of accumulators, as the choice between a whole and a masked stage
-// inside the loop keeps two sets of registers for them, addresses.  At 4 cycles each on a SIMD they are 11.8 of the 16.5.
+// even rounds of tiles.  The loop has 42.6 vector instructions per matrix instruction (38.8 with MB = 2): 32 of the
+// rescale, 9 or 6 of nibble expansion, addresses.  Conversions, with the masked stage inside the loop (four copies of
+// accumulators more), and now: 8192 x 768 x 768 17.5 and 15.9, 7744 x 320 x 1280 14.8 and 13.6, 32768 x 320 x 1280 49.1
+// and 41.6, 131072 x 1024 x 4096 1325 and 1255, 131072 x 4096 x 1024 1262 and 1177.  (The subtrahend as a literal: in a
+// vector register it made the kernel 1 to 5 % slower.)
 // The 8-byte reads of the fragments meet in their banks (80 M cycles over 256 CUs); the vector work covers it.
 // ---------------------------------------------------------------------------
 // 64 floats from 64 addresses -> 64 consecutive floats of LDS
@@ -1659,7 +1665,15 @@ __global__ __launch_bounds__(GEMM_THREADS, (MB == 1 ? 3 : 2)) void k_w4a4_gemm_b
   // 8 (l >> 5); of a 32 x 32 result it owns activation l & 31 and weights 8 q + 4 (l >> 5) + 0..3.
   const int frow = lane & 31, fh = lane >> 5, swz = (frow >> 2) & 3;
   const int x_row = (wm * 32 * MB + frow) * BKB + 8 * fh, w_row = (BM + wn * 64 + frow) * BKB + 8 * fh;
-  const v16i zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+  // The block's sum is added to the bits of 1.5 * 2^23: as a binary32 number the result is that plus the sum,
+  // exactly (|256 acc| <= 2^19), and a subtraction, which runs at twice the rate of a conversion, leaves the sum.
+  u32 magic_bits = 0x4B400000u;
+  asm volatile("" : "+v"(magic_bits));
+  const float magic = 12582912.f;                      // stays a literal of the instruction
+  v16i start;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) start[r] = (int)magic_bits;
+  asm volatile("" : "+v"(start));
   auto stage = [&](int kt, int slot, auto tail) {
     const uint8_t* at = ring + slot * SLOT;
     float4 d[MB];
@@ -1690,7 +1704,7 @@ __global__ __launch_bounds__(GEMM_THREADS, (MB == 1 ? 3 : 2)) void k_w4a4_gemm_b
       for (int i = 0; i < NA; ++i)
 #pragma unroll
         for (int j = 0; j < MB; ++j)
-          t[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i], b[j], zero, 0, 0, 0);
+          t[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i], b[j], start, 0, 0, 0);
 #pragma unroll
       for (int i = 0; i < NA; ++i)
 #pragma unroll
@@ -1698,12 +1712,15 @@ __global__ __launch_bounds__(GEMM_THREADS, (MB == 1 ? 3 : 2)) void k_w4a4_gemm_b
           const float dl = kb == 0 ? d[j].x : kb == 1 ? d[j].y : kb == 2 ? d[j].z : d[j].w;
 #pragma unroll
           for (int r = 0; r < 16; ++r)
-            accf[i][j][r] = __builtin_fmaf((float)t[i][j][r], dl, accf[i][j][r]);
+            accf[i][j][r] = __builtin_fmaf(__builtin_bit_cast(float, (int)t[i][j][r]) - magic, dl, accf[i][j][r]);
         }
     }
   };
+  // Stages whose four blocks are whole, then (if there is one) the last, masked one: with the choice inside the
+  // loop the compiler keeps two sets of accumulators and copies them.
+  const int whole_stages = kbytes / BKB;
   int slot = 0;
-  for (int kt = 0; kt < k_tiles; ++kt) {
+  auto enter = [&](int kt) {
     // stage kt has landed when at most the loads of the stage after it are outstanding
     if (kt + 1 < k_tiles)
       asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NL) : "memory");
@@ -1712,11 +1729,15 @@ __global__ __launch_bounds__(GEMM_THREADS, (MB == 1 ? 3 : 2)) void k_w4a4_gemm_b
     __syncthreads();
     // the slot of stage kt - 1: every wavefront drained its reads before this barrier
     if (kt + 2 < k_tiles) load_stage(kt + 2, slot == 0 ? 2 : slot - 1);
-    if ((kt + 1) * BKB <= kbytes)
-      stage(kt, slot, std::false_type{});
-    else
-      stage(kt, slot, std::true_type{});
+  };
+  for (int kt = 0; kt < whole_stages; ++kt) {
+    enter(kt);
+    stage(kt, slot, std::false_type{});
     slot = slot == D - 1 ? 0 : slot + 1;
+  }
+  if (whole_stages < k_tiles) {
+    enter(whole_stages);
+    stage(whole_stages, slot, std::true_type{});
   }
   __syncthreads();
 
@@ -1779,9 +1800,9 @@ hipError_t launch_w4a4_gemm_blocks(const uint8_t* Qx, long long ld_q, const floa
   const int esz = y_dt == TDQ_F32 ? 4 : 2;
   const int y_vec_ok = (reinterpret_cast<uintptr_t>(Y) & 15) == 0 && ld_y * esz % 16 == 0 ? 1 : 0;
   const int n_tiles = (N + 127) / 128;
-  // 128 rows a tile where there are many tiles: 44 vector instructions per matrix instruction instead of 49 weigh
+  // 128 rows a tile where there are many tiles: 39 vector instructions per matrix instruction instead of 43 weigh
   // more than an even last round and a third workgroup per CU.  64 / 128 rows, us: 32768 x 320 x 1280 (2560
-  // tiles of 128) 52.2 / 53.6, 131072 x 4096 x 1024 (8192) 1285 / 1223.
+  // tiles of 128) 43.1 / 47.3, 131072 x 4096 x 1024 (8192) 1137 / 1114.
   const bool tall = (long long)((M + 127) / 128) * n_tiles >= 4096;
   const int bm = tall ? 128 : 64;
   const int m_tiles = (M + bm - 1) / bm;
