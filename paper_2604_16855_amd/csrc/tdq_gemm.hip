@@ -2081,15 +2081,20 @@ hipError_t launch_w4a4_gemm_f6(const uint8_t* A6, const uint8_t* B6, int K, cons
 // so a lane holds ONE activation row m (= lane % 32) and 16 output channels: Delta[m, kb]
 // is one register per lane instead of sixteen.
 //
-// 128 x 128 tile, 2 x 2 wavefronts of 64 x 64; a stage is 128 codes of K = four scale
-// blocks = four "rounds" of 4 matrix instructions + 64 multiply-adds per wavefront.  The
-// kernel is bound by the vector unit, so the two must overlap inside a wavefront: a round
-// consumes the four results of the round before, one at a time, and re-issues the matrix
-// instruction into the result registers just freed, so every result has three quarters
-// of a round (about 200 cycles) to arrive and the vector unit never waits for the matrix
-// pipe.  Operands of a round are read from LDS during the round before.
+// 128 x 128 tile, 4 x 2 wavefronts of 32 x 64, two workgroups per CU; a stage is 128 codes of
+// K = four scale blocks = four "rounds" of 2 matrix instructions + 32 multiply-adds per
+// wavefront.  The kernel is bound by the issue of vector instructions: a matrix instruction
+// leaves room for four or five of them, each further one costs its own 2.7 cycles
+// (register-only, zeros: 13.9 ns alone, 15 with 4 multiply-adds, 28.7 with 16).  A round consumes
+// the results of the round before, one at a time, and re-issues the matrix instruction into the
+// result registers just freed; operands of a round are read from LDS during the round before.
+// Four wavefronts per SIMD (128 registers each) cover what is left of the waits: with 2 x 2
+// wavefronts of 64 x 64, two per SIMD, us then and now: 32768 x 1024 x 4096 260 and 234,
+// 131072 x 4096 x 1024 889 and 846, 131072 x 1024 x 4096 990 and 940, 7744 x 320 x 1280 14.7 and
+// 13.0, 968 x 512 x 512 8.6 and 7.0, 4096 x 4096 x 64 34.6 and 26.5 (the operands of a fragment are
+// then read from LDS four times instead of three; it has the room).
 //   Ring of three slots of 24 KiB + the stage's scales [4][128], all by direct-to-LDS
-//   loads (8 per wavefront and stage, no staging registers).  Everything read from the
+//   loads (4 per wavefront and stage, no staging registers).  Everything read from the
 //   slot of stage s is read by round 2 of stage s; the barrier in that round publishes
 //   stage s + 1, and right behind it the loads of stage s + 3 go into the slot of stage
 //   s: two full stages of flight.  A half-zero operand is read as such: the lanes of the
@@ -2098,26 +2103,26 @@ hipError_t launch_w4a4_gemm_f6(const uint8_t* A6, const uint8_t* B6, int K, cons
 //   compiler would regroup the instructions.
 // ---------------------------------------------------------------------------
 
+constexpr int BF6_THREADS = 512;
 template <typename OUT>
-__global__ __launch_bounds__(GEMM_THREADS, 2) void k_w4a4_gemm_blocks_f6(
+__global__ __launch_bounds__(BF6_THREADS, 4) void k_w4a4_gemm_blocks_f6(
     const uint8_t* __restrict__ A6, const uint8_t* __restrict__ B6, int KB64,
     const float* __restrict__ bscale, long long ld_s, int M, int K, int N,
     const float* __restrict__ w_scale, const float* __restrict__ bias, OUT* __restrict__ Y,
     long long ld_y, int m_tiles, int n_tiles, int y_vec_ok) {
-  // WM x 2 wavefronts of 64 x 64.  (WM = 4, one workgroup of 256 x 128 per CU, brings a
-  // quarter less into the CU per stage, but was 3 % slower on both large shapes: with one
-  // workgroup per CU nothing overlaps a tile's first loads and its output phase.)
-  constexpr int WM = 2;
-  constexpr int MT = 2, NT = 2, BM = WM * 64, BN = 128;
-  constexpr int NW = 2 * WM, THREADS = NW * 64;
+  // WM x 2 wavefronts of 32 x 64
+  constexpr int WM = 4;
+  constexpr int MT = 1, NT = 2, BM = WM * 32, BN = 128;
+  constexpr int NW = 2 * WM, THREADS = BF6_THREADS;
   constexpr int KS = 2;                          // 64-blocks of K per stage
   constexpr int SBK = 2 * KS;                    // scale blocks per stage
   constexpr int CH = KS * F6_FRAG;               // 3072 bytes per row block and stage
-  constexpr int ACH = 2 * WM;                    // row blocks of A; then 4 of B
+  constexpr int ACH = WM;                    // row blocks of A; then 4 of B
   constexpr int SLOT = (ACH + 4) * CH;
-  constexpr int PIECES = SLOT / 1024;            // 1 KiB direct loads per stage: 24 or 36
-  constexpr int NDMA = (PIECES + NW - 1) / NW;   // per wavefront: 6 or 5 (4 of the 40 twice)
-  constexpr int NVM = NDMA + 2;                  // + 2 scale loads
+  constexpr int PIECES = SLOT / 1024;            // 1 KiB direct loads per stage: 24
+  constexpr int NDMA = PIECES / NW;              // per wavefront: 3
+  constexpr int NVM = NDMA + 1;                  // + a scale load
+  static_assert(NW * 64 == THREADS && NDMA * NW == PIECES && BM == NW * 16, "every wavefront has the same loads");
   __shared__ __attribute__((aligned(1024))) uint8_t ring[3 * SLOT];
   __shared__ __attribute__((aligned(256))) float sD[3][BM][SBK];
   __shared__ __attribute__((aligned(16))) float sCol[BN], sBias[BN];
@@ -2125,7 +2130,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void k_w4a4_gemm_blocks_f6(
   typedef unsigned u2v __attribute__((ext_vector_type(2)));
   typedef const __attribute__((address_space(3))) u2v* lds_u2;
 
-  const int bid = blockIdx.x;
+  const unsigned bid = blockIdx.y * gridDim.x + blockIdx.x;      // gridDim.x is a multiple of XCDS
   const int xcd = bid % XCDS, idx = bid / XCDS;
   const int m_tile = (idx / n_tiles) * XCDS + xcd;
   const int n_tile = idx % n_tiles;
@@ -2147,14 +2152,12 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void k_w4a4_gemm_blocks_f6(
   }
   if (tid < 8) sZero[tid] = 0u;
 
-  // piece wave + NW e of a stage (past the last: one of the first again, the same bytes
-  // to the same place): chunk (row block) piece / 3, 1 KiB part piece % 3
+  // piece wave + NW e of a stage: chunk (row block) piece / 3, 1 KiB part piece % 3
   const uint8_t* sbase[NDMA];
   int piece[NDMA];
 #pragma unroll
   for (int e = 0; e < NDMA; ++e) {
-    int pi = wave + NW * e;
-    pi = pi < PIECES ? pi : pi - PIECES;
+    const int pi = wave + NW * e;
     piece[e] = pi;
     const int c = pi / 3, part = pi % 3;
     long long rb;
@@ -2176,20 +2179,19 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void k_w4a4_gemm_blocks_f6(
   const unsigned zero_addr = (unsigned)(size_t)(__attribute__((address_space(3))) uint8_t*)sZero;
   // scales of a stage, [BM][4] in LDS: one load brings 16 rows x 4 blocks, four lanes per
   // row, so it touches 16 lines (a lane per row would touch 64 for the same 256 bytes,
-  // and the L2 request rate is what this kernel runs against); BM / 16 = 2 NW loads,
-  // wavefront w brings row groups w and w + NW.  Rows and blocks past the end are
+  // and the L2 request rate is what this kernel runs against); wavefront w brings row
+  // group w.  Rows and blocks past the end are
   // clamped to real ones (their products are zero or unused); only the last stage can
   // have fewer than four blocks.
   const float* d_row0 = bscale + (long long)m0 * ld_s;
   const int last_real = KB - 1 - (stages - 1) * SBK;       // 0..3 (or more: no clamp)
-  unsigned d_voff[2], d_voff_last[2];
-#pragma unroll
-  for (int hf = 0; hf < 2; ++hf) {
-    int row = (wave + hf * NW) * 16 + (lane >> 2);
+  unsigned d_voff, d_voff_last;
+  {
+    int row = wave * 16 + (lane >> 2);
     row = m0 + row < M ? row : M - 1 - m0;
     const int b = lane & 3;
-    d_voff[hf] = ((unsigned)row * (unsigned)ld_s + (unsigned)b) * 4u;
-    d_voff_last[hf] = ((unsigned)row * (unsigned)ld_s + (unsigned)(b < last_real ? b : last_real)) * 4u;
+    d_voff = ((unsigned)row * (unsigned)ld_s + (unsigned)b) * 4u;
+    d_voff_last = ((unsigned)row * (unsigned)ld_s + (unsigned)(b < last_real ? b : last_real)) * 4u;
   }
   // stage st (clamped to the last: past the end a harmless re-load) -> slot (run-time
   // 0, 1, 2 in turn: with compile-time slots the compiler hoists every LDS address out
@@ -2201,20 +2203,18 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void k_w4a4_gemm_blocks_f6(
       dma16s(sbase[e] + (long long)sc * CH, lane16,
              __builtin_amdgcn_readfirstlane(ring_base + slot * SLOT + piece[e] * 1024));
     const bool last = sc == stages - 1;
-#pragma unroll
-    for (int hf = 0; hf < 2; ++hf)
-      dma4s(d_row0 + sc * SBK, last ? d_voff_last[hf] : d_voff[hf],
-            __builtin_amdgcn_readfirstlane(sd_base + (slot * BM + (wave + hf * NW) * 16) * SBK * 4));
+    dma4s(d_row0 + sc * SBK, last ? d_voff_last : d_voff,
+          __builtin_amdgcn_readfirstlane(sd_base + (slot * BM + wave * 16) * SBK * 4));
   };
 
   // operand reads.  x (activations): lanes of half h read their 24 bytes, the others the
   // zeros: address = base + flag * offset, one instruction, kept where it is written.
   const bool lower = lane < 32;
-  const unsigned x_lane = ring_base + (wm * 2 * CH + lane * 24);
+  const unsigned x_lane = ring_base + (wm * MT * CH + lane * 24);
   const unsigned w_lane = ring_base + ((ACH + wn * 2) * CH + lane * 24);
   const unsigned x_base[2] = {lower ? x_lane : zero_addr, lower ? zero_addr : x_lane};
   const unsigned x_flag[2] = {lower ? 1u : 0u, lower ? 0u : 1u};
-  const unsigned d_lane = sd_base + (wm * 64 + (lane & 31)) * SBK * 4;
+  const unsigned d_lane = sd_base + (wm * 32 * MT + (lane & 31)) * SBK * 4;
   auto read24 = [&](unsigned addr) {
     const lds_u2 p = (lds_u2)(size_t)addr;
     const u2v q0 = p[0], q1 = p[1], q2 = p[2];
@@ -2287,7 +2287,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void k_w4a4_gemm_blocks_f6(
   } while (0)
 #define TDQ_BF6_ROUND(s, CUR, NXT, R, MORE)                                                       \
   do {                                                                                            \
-    /* the next round's activations first: four slots until they are used */                     \
+    /* the next round's activations first: two slots until they are used */                      \
     __builtin_amdgcn_sched_barrier(0);                                                            \
     if ((R) < 3) read_x(xbuf[((R) + 1) & 1], CUR, ((R) + 1) >> 1, ((R) + 1) & 1);                 \
     else read_x(xbuf[0], NXT, 0, 0);                                                              \
@@ -2296,8 +2296,6 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void k_w4a4_gemm_blocks_f6(
       read_dl(dcur, CUR);                         /* the old ones were spent in round 3 */        \
       read_w(wbuf[1], CUR, 1);                    /* for rounds 2 and 3 */                        \
     }                                                                                             \
-    TDQ_BF6_SLOT(R, 0, 1);                                                                        \
-    TDQ_BF6_SLOT(R, 1, 0);                                                                        \
     if ((R) == 2) {                                                                               \
       __builtin_amdgcn_sched_barrier(0);                                                          \
       asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((MORE) ? NVM : 0) : "memory");          \
@@ -2305,19 +2303,15 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void k_w4a4_gemm_blocks_f6(
       if (MORE) dma_stage(CUR, (s) + 3);                                                          \
       read_w(wbuf[0], NXT, 0);                    /* for rounds 0 and 1 of the next stage */      \
     }                                                                                             \
-    TDQ_BF6_SLOT(R, 1, 1);                                                                        \
-    if ((R) == 3) {                                                                               \
-      dlast[0] = dcur[0][3];                                                                      \
-      dlast[1] = dcur[1][3];                                                                      \
-    }                                                                                             \
+    TDQ_BF6_SLOT(R, 0, 1);                                                                        \
+    if ((R) == 3) dlast[0] = dcur[0][3];                                                          \
     __builtin_amdgcn_sched_barrier(0);                                                            \
   } while (0)
 
   int cur = 0, nxt = 1, nn = 2;
   // The last three stages load nothing and have a loop of their own.  (With one loop, whose stages must not
   // branch and so loaded the last stage again, a tile of 8 stages loaded 11 and waited for them before
-  // its output: 32768 x 1024 x 4096 265.6 us, 248.2 so; 8192 x 768 x 768 16.1 and 15.0; 131072 x 4096 x 1024 888 and
-  // 869.)
+  // its output: with 2 x 2 wavefronts 32768 x 1024 x 4096 265.6 us, 248.2 so; 131072 x 4096 x 1024 888 and 869.)
   int s = 0;
 #pragma unroll 1
   for (; s + 3 < stages; ++s) {
@@ -2345,15 +2339,13 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void k_w4a4_gemm_blocks_f6(
 #undef TDQ_BF6_SLOT
   consume(0, 0, dlast[0]);                       // the last round's results
   consume(0, 1, dlast[0]);
-  consume(1, 0, dlast[1]);
-  consume(1, 1, dlast[1]);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // nothing of ours may still be landing
 
-  // Register r of result (i, j) is row m = 32 i + lane % 32 of the wavefront's 64 and
+  // Register r of result (i, j) is row m = 32 i + lane % 32 of the wavefront's 32 MT and
   // channel 32 j + 8 (r / 4) + 4 (lane / 32) + r % 4: a lane holds short runs of 32 rows,
   // which as stores would touch 32 lines with 8 or 16 bytes each.  So the wavefront's
-  // 64 x 64 results (already scaled) go, 32 rows at a time, through its own 8.5 KiB of the
-  // ring, now free, and leave row-major: every store instruction writes whole 128-byte lines.
+  // results (already scaled) go, 32 rows at a time, through its own 8.5 KiB of the ring,
+  // now free, and leave row-major: every store instruction writes whole 128-byte lines.
   __syncthreads();                               // every wavefront's loads have landed
   constexpr int TP = 68;                         // pitch in floats: 16-byte aligned rows, staggered banks
   float* T = reinterpret_cast<float*>(ring) + wave * (32 * TP);
@@ -2387,7 +2379,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void k_w4a4_gemm_blocks_f6(
 #pragma unroll
       for (int it = 0; it < 32 / RPI; ++it) {
         const int row = it * RPI + rsub;
-        const int m = m0 + wm * 64 + i * 32 + row;
+        const int m = m0 + wm * 32 * MT + i * 32 + row;
         float y[W];
 #pragma unroll
         for (int q = 0; q < W / 4; ++q) {
@@ -2397,7 +2389,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void k_w4a4_gemm_blocks_f6(
         if (m < M && nbase < N) store_out_vec<OUT>(Y + (long long)m * ld_y + nbase, y);
       }
     } else {
-      const int m = m0 + wm * 64 + i * 32, n = n0 + wn * 64;
+      const int m = m0 + wm * 32 * MT + i * 32, n = n0 + wn * 64;
       store_rows<OUT>(Y + (long long)m * ld_y + n, ld_y, M - m, N - n, lane,
                       [&](int row, int c) { return (OUT)T[row * TP + c]; });
     }
@@ -2410,17 +2402,19 @@ hipError_t launch_w4a4_gemm_blocks_f6(const uint8_t* A6, const uint8_t* B6, cons
                                       hipStream_t st) {
   const int KB64 = 2 * ((K + 127) / 128);
   const int m_tiles = (M + 127) / 128, n_tiles = (N + 127) / 128;
-  const long long m_groups = (m_tiles + XCDS - 1) / XCDS;
-  const unsigned grid = (unsigned)(m_groups * XCDS * n_tiles);
+  // An axis of a grid holds fewer than 2^32 threads, and 2^30 rows are 2^23 tiles of 512: two axes (workgroups past
+  // the last tile return)
+  const long long tiles = (long long)((m_tiles + XCDS - 1) / XCDS) * XCDS * n_tiles, axis = 1 << 22;
+  const dim3 grid(tiles < axis ? (unsigned)tiles : (unsigned)axis, (unsigned)((tiles + axis - 1) / axis));
   // 16-byte stores where every row of Y starts on a 16-byte boundary
   const int per16 = y_dt == TDQ_F32 ? 4 : 8;
   const int y_vec_ok = (reinterpret_cast<uintptr_t>(Y) % 16 == 0 && ld_y % per16 == 0) ? 1 : 0;
   if (y_dt == TDQ_F32)
-    hipLaunchKernelGGL((k_w4a4_gemm_blocks_f6<float>), dim3(grid), dim3(GEMM_THREADS), 0, st, A6, B6,
+    hipLaunchKernelGGL((k_w4a4_gemm_blocks_f6<float>), grid, dim3(BF6_THREADS), 0, st, A6, B6,
                        KB64, bscale, ld_s, M, K, N, w_scale, bias, static_cast<float*>(Y), ld_y, m_tiles,
                        n_tiles, y_vec_ok);
   else
-    hipLaunchKernelGGL((k_w4a4_gemm_blocks_f6<_Float16>), dim3(grid), dim3(GEMM_THREADS), 0, st, A6, B6,
+    hipLaunchKernelGGL((k_w4a4_gemm_blocks_f6<_Float16>), grid, dim3(BF6_THREADS), 0, st, A6, B6,
                        KB64, bscale, ld_s, M, K, N, w_scale, bias, static_cast<_Float16*>(Y), ld_y,
                        m_tiles, n_tiles, y_vec_ok);
   return hipGetLastError();
