@@ -169,9 +169,15 @@ static bool samples_rank(tdq_dtype dt, int B, int T, int C, int G, bool exact_on
 //     quarter of the rows that a workgroup's lanes take at a time, where it has more than 8 Ki elements ([2, 457, 6172]
 //     with 16 sets, two rows for eight wavefronts, 43.8 against 39.5); and with one or two sets of more than 4096
 //     tokens, each read by every workgroup, no more than 16 Ki elements ([58, 6152, 44] 52.7 against 47.8).
-//   * binary32 reads a set's rows twice, so one workgroup sees all of a set: [2, 1400, 32] (45 Ki elements) 38.6
-//     against 44.7, [5, 1280, 84] (107 Ki) 60.5 against 47.4, [1, 377, 416] (157 Ki) 84.0 against 48.2; an image that
-//     is one set by itself 40 Ki ([2, 576, 74], 42 Ki, 45.0 against 34.1).
+//   * binary32, up to 56 Ki elements: one workgroup sees all of a set ([2, 1400, 32], 45 Ki elements, 38.6 against
+//     44.7); an image that is one set by itself 40 Ki ([2, 576, 74], 42 Ki, 45.0 against 34.1).
+//     Beyond that and with one rank and 2 to 32 sets (256 bins and 256 keys of a set have room then), several share a
+//     set and wait for each other: no more than 64 Ki elements for each and 256 of them to an image.  Calibration by the
+//     chain and so: [2, 484, 320] with 8 sets 32.7 / 21.5, [8, 1024, 768] with 16 46.1 / 35.6, [24, 300, 300] 42.1 /
+//     32.3, [4, 4096, 768] 89.6 / 54.8 and [16, 1024, 1024] 102.9 / 65.6 (levels before), [1, 8192, 1024] 76.7 / 96.8
+//     with 496 of them and 74.0 with 240.  110 random calls over laws of data: 1.40 times as fast in the geometric mean,
+//     two more than 2 % slower (values within 1e-4 of 1 and three sets, [3, 2422, 1156], 79 / 105: every key of
+//     the interval is one of a few; one and the same value, [8, 288, 1829], 61 / 64).
 //   * Up to 1536 sets in all, which take two turns on the chip: [49, 74, 832] with 32 sets (1568) 31.0 against 29.8,
 //     [58, 20, 9] with 32 42.8 against 36.6, [64, 322, 56] with 64 55.7 against 45.6; of 94 calls of 1024 to 1536 sets
 //     none is slower, half are faster than 1.27 times.  binary32, whose kernel needs more registers: up to 1024, 512
@@ -184,7 +190,15 @@ static int whole_extra(tdq_dtype dt, int B, int T, int C, int G, bool two_ranks)
   const long long e = (long long)T * C;
   const long long sets = (long long)B * G;
   if (T > kWholeTokens || sets > (dt == TDQ_F16 ? 1536 : two_ranks ? 512 : 1024)) return -1;
-  if (dt == TDQ_F32) return e <= (G == 1 ? 40960 : 57344) ? 0 : -1;
+  if (dt == TDQ_F32) {
+    if (e <= (G == 1 ? 40960 : 57344)) return 0;
+    if (two_ranks || G == 1 || G > 32) return -1;
+    long long extra = e / 8192;
+    const long long most = 512 / B - G;
+    if (extra > most) extra = most;
+    if (extra > 256) extra = 256;
+    return extra > 0 && e <= 65536 * (extra + 1) ? (int)extra : -1;
+  }
   long long extra = e / 8192;
   const long long most = 512 / B - G;
   if (extra > most) extra = most > 0 ? most : 0;
@@ -206,7 +220,8 @@ extern "C" int tdq_samples_rank(int32_t dt, int32_t B, int32_t T, int32_t C, int
 
 static int calibration_extra(tdq_dtype dt, int B, int T, int C, const tdq_params* p) {
   const bool exact_only = (p->flags & TDQ_FLAG_EXACT_SELECT) != 0;
-  if (exact_only || !samples_rank(dt, B, T, C, p->n_groups, false)) return -1;
+  // (the limits of sampled_f32 are those of its chain of kernels)
+  if (exact_only || bracket_bins(p->n_groups) == 0 || many_small_sets(B, T, C, p->n_groups)) return -1;
   return whole_extra(dt, B, T, C, p->n_groups, p->base_pct > 0.0 && p->base_pct < 1.0);
 }
 

@@ -158,7 +158,7 @@ hipError_t launch_sets(const void* X, tdq_dtype dt, int B, int T, int C, long lo
 // extra > 0.
 constexpr int kWholeTokens = 8192;     // (the list of tokens and the rest fit 64 KiB of LDS)
 constexpr int kListTokens = 16384;     // most tokens of an image listed by rank in LDS
-constexpr int kSetCtl = 4;
+constexpr int kSetCtl = 8;
 hipError_t launch_sets_whole(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G, int ranks,
                              int extra, int Wfew, int W, const float* r, const double* mean, const double* m2,
                              int* gid, const Scalars& sc, unsigned* bhist, void* ctl, unsigned* img_flag,

@@ -47,6 +47,11 @@ constexpr int kSampleBits = 10;                                 // key bits the 
 constexpr int kSweepThreads = 1024;
 constexpr int kIdRounds = 16;                                   // most range keys a thread of k_sets holds
 
+// Words of a set's control block: shares (binary16: workgroups) that have arrived, elements below the interval
+// (binary16, two ranks: the next word for the second); binary32: keys handed over, what the words have been
+// cleared for, shares claimed.
+enum { kCtlArrived = 0, kCtlBelow = 1, kCtlListed = 2, kCtlReady = 3, kCtlClaimed = 4 };
+
 // Arguments of a k_sets that sees a set through to its radius.
 struct WholeArgs {
   int extra;                  // workgroups per image beyond one per set
@@ -569,7 +574,7 @@ __device__ __forceinline__ Lost lost_rank(u32 k, u32 n, u32 below, u32 inside, u
 }
 
 template <typename TX, int NT, int RD, int SM, int WHOLE>
-__global__ __launch_bounds__(NT, (WHOLE == 1 && sizeof(TX) == 2 && RD <= 8 ? 6 : 1)) void k_sets(
+__global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8 ? 6 : 1)) void k_sets(
     const TX* __restrict__ X, long long ld, int T, int C, int G, int Wfew, int W, int cells, int aligned,
     const float* __restrict__ r, const double* __restrict__ mean, const double* __restrict__ m2,
     int* __restrict__ gid, Scalars sc, int pass, int keep_base, GroupWork* __restrict__ grp,
@@ -602,6 +607,7 @@ __global__ __launch_bounds__(NT, (WHOLE == 1 && sizeof(TX) == 2 && RD <= 8 ? 6 :
   __shared__ u32 s_share[64];                        // sampled tokens of every set
   __shared__ Lost s_lost[2];
   __shared__ FinishLds<WHOLE ? NT : 64, true> s_search;
+  __shared__ unsigned short s_parts[WHOLE == 1 && !F16 ? NT + 1 : 1];     // shares of the set's rows claimed by this workgroup
   // (whole: the set, and which of the S workgroups that share it this is, follow from the sets' sizes)
   int S = 1, part = 0, j = (int)blockIdx.x;
   const int b = blockIdx.y;
@@ -701,6 +707,9 @@ __global__ __launch_bounds__(NT, (WHOLE == 1 && sizeof(TX) == 2 && RD <= 8 ? 6 :
     j = __ffsll((long long)later) - 1;
     S = __builtin_amdgcn_readlane((int)its, j);
     part = (int)at - (__builtin_amdgcn_readlane((int)incl, j) - S);
+    // (binary32; there is time until it is looked at)
+    if (WHOLE == 1 && !F16 && S > 1 && tid == 0)
+      s_parts[0] = (unsigned short)min(atomicAdd(&wa.ctl[(size_t)(b * G + j) * kSetCtl + kCtlClaimed], 1u), 0xFFFFu);
   }
   const u32 start = start_of(j), end = start_of(j + 1);
   auto in_set = [&](u32 k) { return k >= start && k < end; };
@@ -953,7 +962,7 @@ __global__ __launch_bounds__(NT, (WHOLE == 1 && sizeof(TX) == 2 && RD <= 8 ? 6 :
   // key - first key, sampled ranks between them.  By the whole workgroup.
   auto interval32 = [&](const SampleRank& s, u32& first, u32& last, u32& drawn) {
     if constexpr (!F16) {
-      const int dr = (int)(6.f * s.dev + s.dev_tokens) + 2, rk = (int)s.rk;
+      const int dr = (int)(S > 1 ? 4.f * s.dev + 0.5f * s.dev_tokens : 6.f * s.dev + s.dev_tokens) + 2, rk = (int)s.rk;
       const u32* const hs[2] = {shist, shist};
       const u32 rs[2] = {(u32)(rk - dr < 1 ? 1 : rk - dr), (u32)(rk + dr > (int)m ? (int)m : rk + dr)};
       find_ranks<NT, 2, kCopies, false>(hs, rs, stot, s_bin, s_before, nullptr);
@@ -1113,6 +1122,7 @@ __global__ __launch_bounds__(NT, (WHOLE == 1 && sizeof(TX) == 2 && RD <= 8 ? 6 :
         // this wavefront have been, the barrier for the other wavefronts, and only then is the arrival counted.
         u32* gh = bhist + (size_t)idx * W;
         u32* ctl = wa.ctl + (size_t)idx * kSetCtl;
+        static_assert(kCtlArrived == 0 && kCtlBelow == 1, "as below");
 #pragma unroll
         for (int q = 0; q < NR; ++q) {
           for (int i = tid; i < (int)wd[q]; i += NT) {
@@ -1165,8 +1175,251 @@ __global__ __launch_bounds__(NT, (WHOLE == 1 && sizeof(TX) == 2 && RD <= 8 ? 6 :
         if (q == NR - 1) found = key_q; else base_key = key_q;
       }
     } else {
+      // A set's rank by several workgroups together.  The set's rows are S shares; a workgroup claims one (in the order
+      // in which they come, not by its place in the grid), lists the keys of its rows that lie in the interval (in
+      // LDS, thread by thread) and counts them in bins.  When the counts of all shares have met in the
+      // workspace, every workgroup reads them and goes on with the bin that holds the rank; the one that claimed the first
+      // share gets the keys of that bin, a few dozen, and picks among them.  Where a bin has too many keys
+      // (ties, gaps), or the interval misses the rank, the same again with the range that is known to hold it.
+      // Workgroups wait for each other, and nothing makes all of a launch run at the same time: whoever has waited
+      // for kPatience claims another share, so that a wait only ever depends on workgroups that run, and one that
+      // starts when nothing is left leaves.  (Words that a second call on the same workspace overwrites could keep
+      // it waiting all the same: after kLimit the helpers leave, and the first does everything alone.)
+      // What they exchange goes through device-scope atomic operations, as for binary16 above.
+      // Bound by its chain of steps: [8, 1024, 768] with 16 sets from the first kernel on, us: range and tokens 4, sample
+      // and interval 8, the rows 4 (25 MB at 6 TB/s), counts met and read 4, keys of the bin 3, skew.  Calibration by
+      // the chain of five kernels, which reads the rows once more, and so: 46 and 35; without the list, rows read
+      // again for the bin's keys, 36.5; lists by wavefront with a ballot per element 37; the rows' first loads issued
+      // before the sample (44 bytes of scratch) 36.4.
+      enum { kProject, kLeave, kAlone };
+      auto shared_rank = [&](u32 kq, u32 first, u32 last) {
+        constexpr long long kPatience = 2000, kLimit = 2000000;         // ticks of 10 ns
+        constexpr u32 kSeg = (kCopies << kSampleBits) / NT;      // keys a thread lists, where the sample was counted
+        const int wbins = W / 2;                       // of the set's words these are bins, the others take the keys
+        u32* gh = bhist + (size_t)idx * W;
+        u32* gl = gh + wbins;
+        u32* ctl = wa.ctl + (size_t)idx * kSetCtl;
+        const u32 keep = wbins < NT ? (u32)wbins : (u32)NT;
+        static_assert(NT <= 1 << kFinishBits, "the keys of the last bin fit the search's histogram");
+        auto load = [&](const u32* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+        const bool picks = s_parts[0] == 0;
+        if ((int)s_parts[0] >= S) return kLeave;
+        int n_parts = 1;                               // shares of this workgroup, listed in s_parts
+        u32 events = 0;                                // how often every share has been counted to have arrived
+        auto arrive = [&](int shares) {                // true in the last to arrive
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+          __syncthreads();
+          if (tid == 0) s_last = atomicAdd(&ctl[kCtlArrived], (u32)shares) + (u32)shares == (u32)S * events ? 1u : 0u;
+          __syncthreads();
+          return s_last != 0;
+        };
+        auto until = [&](long long patience, auto&& so) {      // (looks until it is, or until it has waited long enough)
+          bool is = so();
+          if (!is) {
+            const long long since = wall_clock64();
 #pragma unroll 1
-      for (int q = 0; q < NR; ++q) {
+            do is = so();
+            while (!is && wall_clock64() - since < patience);
+          }
+          return is;
+        };
+        auto reached = [&](int word, u32 value, long long patience) {
+          if (tid == 0) s_last = until(patience, [&]() { return load(&ctl[word]) >= value; }) ? 1u : 0u;
+          __syncthreads();
+          const bool ok = s_last != 0;
+          __syncthreads();
+          return ok;
+        };
+        const int share = (tokens + S - 1) / S;
+        u32 k0 = first, span = last + 1u;              // the keys that are looked at: span of them from k0 on
+        u32 need = kq, count = 0, shift = 0, ready = 0;
+        // a bin has copies, each in the next bank: additions to one word take turns, and where a few values hold most
+        // of the interval they would all be to a few
+        const u32 cs = 31u - (u32)__clz(kBins / wbins), copy = (u32)lane & ((1u << cs) - 1u);      // (2 to 8 copies)
+        auto count_key = [&](u32 d) { atomicAdd(&hist[0][((d >> shift) << cs) | copy], 1u); };
+        auto rows_of = [&](int p, auto ahead) {
+          const int from = p * share, rows = tokens - from < share ? tokens - from : share;     // (none if negative)
+          return RowVisitor<TX, NT, 4, decltype(ahead)::value>(Xb, ld, C, wa.L, order + (rows > 0 ? from : 0), rows);
+        };
+        u32* seg = shist + tid;                        // every NT-th word
+        u32 listed_n = 0;                              // of this thread; more than kSeg: not all of them are listed
+        bool known = false;                            // the range holds the rank, and `need` counts from k0
+#pragma unroll 1
+        for (int round = 0;; ++round) {
+          // bins of 2^shift keys
+          shift = span <= (u32)wbins ? 0u : (u32)(__clz(wbins) - __clz(span - 1u) + 1);
+          const u32 bins = ((span - 1u) >> shift) + 1u;          // <= wbins
+          u32* words = round == 1 ? gl : gh;
+          ++events;
+          for (bool more = true; more;) {
+            for (int i = tid; i < kBins / 4; i += NT) reinterpret_cast<uint4*>(&hist[0][0])[i] = make_uint4(0, 0, 0, 0);
+            if (tid == 0) s_below[0] = 0;
+            __syncthreads();
+            u32 below = 0, old = known ? 0u : listed_n;
+            if (!known || listed_n > kSeg) {           // the share's keys in the range, or those of all shares again
+              if (known) listed_n = 0;
+#pragma unroll 1
+              for (int e = known ? 0 : n_parts - 1; e < n_parts; ++e) {
+                auto look = [&](TX x) {
+                  const u32 key_x = Elem<TX>::key(x);
+                  u32 d;
+                  below += __builtin_sub_overflow(key_x, k0, &d) ? 1u : 0u;
+                  if (d < span) {
+                    if (__builtin_expect(listed_n < kSeg, 1)) seg[listed_n * NT] = key_x;
+                    else count_key(d);
+                    ++listed_n;
+                  }
+                };
+                rows_of(s_parts[e], std::true_type()).visit([&](const uint4& p) {
+                  TX x[V];
+                  Elem<TX>::unpack(p, x);
+#pragma unroll
+                  for (int c = 0; c < V; ++c) look(x[c]);
+                }, look);
+              }
+            }
+#pragma unroll
+            for (u32 i = 0; i < kSeg; ++i) {
+              const u32 d = seg[i * NT] - k0;
+              if (i >= old && i < listed_n && d < span) count_key(d);
+            }
+            below = group_sum_u32<64>(below);
+            if (lane == 63 && below) atomicAdd(&s_below[0], below);
+            // (the words were cleared by the statistics kernel, and from the third round on by the last to have read them)
+            if (ready != 0 && !reached(kCtlReady, ready, kLimit)) return picks ? kAlone : kLeave;
+            __syncthreads();
+            for (int i = tid; i < (int)bins; i += NT) {
+              u32 v = 0;
+#pragma unroll
+              for (int c = 0; c < 8; ++c) v += c < 1 << cs ? hist[0][((i << cs) + c) & (kBins - 1)] : 0u;
+              if (v) atomicAdd(&words[i], v);
+            }
+            if (tid == 0 && !known && s_below[0]) atomicAdd(&ctl[kCtlBelow], s_below[0]);
+            arrive(known ? n_parts : 1);
+            more = false;
+            if (!known && !reached(kCtlArrived, (u32)S, kPatience)) {
+              if (tid == 0) s_parts[n_parts] = (unsigned short)min(atomicAdd(&ctl[kCtlClaimed], 1u), 0xFFFFu);
+              __syncthreads();
+              more = (int)s_parts[n_parts] < S;
+              n_parts += more ? 1 : 0;
+            }
+          }
+          if (!reached(kCtlArrived, (u32)S * events, kLimit)) return picks ? kAlone : kLeave;
+          for (int i = tid; i < wbins; i += NT) hist[0][i] = i < (int)bins ? load(&words[i]) : 0u;
+          if (tid == 0) s_below[0] = known ? 0u : load(&ctl[kCtlBelow]);
+          __syncthreads();
+          if (picks && !known && wave == NW - 1) finish_moments();
+          if (wave == 0) {
+            const u32 under = s_below[0];
+            const BinPick p = pick_bin<false>(hist[0], wbins, under, need);
+            Lost l = lost_rank<false>(need, nn, under, p.inside, k0, k0 + span);
+            if (p.ok) {
+              const u32 from_key = p.bin << shift, left = span - from_key;
+              l.k0 = k0 + from_key;
+              l.span = left < 1u << shift ? left : 1u << shift;
+              l.rank = p.need;
+            }
+            if (lane == 0) {
+              s_lost[0] = l;
+              s_last = p.ok ? p.count : 0xFFFFFFFFu;   // (a set has fewer elements)
+            }
+          }
+          __syncthreads();
+          count = s_last;
+          k0 = s_lost[0].k0;
+          span = s_lost[0].span;
+          need = (u32)s_lost[0].rank;
+          __syncthreads();                             // (s_last and s_lost are written again below)
+          if (count == 0xFFFFFFFFu) {
+            if (span > 1u && tid == 0 && picks) atomicAdd(&status[1 + kPassZr], 1u);
+            listed_n = kSeg + 1u;                      // other keys are wanted
+          }
+          known = true;
+          if (span == 1u) {
+            found = k0;
+            return picks ? kProject : kLeave;
+          }
+          if (round > 0) {
+            // the words are wanted again: the last to have read them clears them
+            ++events;
+            if (arrive(n_parts)) {
+              for (int i = tid; i < W; i += NT) (void)atomicExch(&gh[i], 0u);
+              asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+              __syncthreads();
+              if (tid == 0) (void)atomicExch(&ctl[kCtlReady], events);
+            }
+            ready = events;
+          }
+          if (count <= keep) break;
+        }
+        // the bin's keys, `count` of them in all workgroups: one more than the key, so that a word that has none is 0
+        if (ready != 0 && !reached(kCtlReady, ready, kLimit)) return picks ? kAlone : kLeave;
+        u32* keys = s_search.h;
+        if (tid == 0) s_below[0] = 0;
+        __syncthreads();
+        u32* const next = picks ? &s_below[0] : &ctl[kCtlListed];
+        auto hand_over = [&](u32 to, u32 key_x) {      // (to < count <= keep)
+          if (to >= keep) return;
+          if (picks) keys[to] = key_x;
+          else (void)atomicExch(&gl[to], key_x + 1u);
+        };
+        u32 hits = 0;                                  // which of those listed
+        if (__builtin_expect(listed_n > kSeg, 0)) {    // (not all of this thread's were listed)
+          auto look = [&](TX x) {
+            const u32 key_x = Elem<TX>::key(x);
+            if (key_x - k0 < span) hand_over(atomicAdd(next, 1u), key_x);
+          };
+#pragma unroll 1
+          for (int e = 0; e < n_parts; ++e)
+            rows_of(s_parts[e], std::false_type()).visit([&](const uint4& p) {
+              TX x[V];
+              Elem<TX>::unpack(p, x);
+#pragma unroll
+              for (int c = 0; c < V; ++c) look(x[c]);
+            }, look);
+        } else {
+#pragma unroll
+          for (u32 i = 0; i < kSeg; ++i) hits |= i < listed_n && seg[i * NT] - k0 < span ? 1u << i : 0u;
+        }
+        const u32 mine_n = (u32)__popc(hits), incl = wave_scan_u32(mine_n);
+        const u32 wave_n = (u32)__builtin_amdgcn_readlane((int)incl, 63);
+        if (wave_n != 0) {                             // (one addition a wavefront)
+          u32 to = 0;
+          if (lane == 63) to = atomicAdd(next, wave_n);
+          to = (u32)__builtin_amdgcn_readlane((int)to, 63) + incl - mine_n;
+#pragma unroll
+          for (u32 i = 0; i < kSeg; ++i)
+            if (hits >> i & 1u) hand_over(to++, seg[i * NT]);
+        }
+        if (!picks) return kLeave;
+        if (tid == 0) s_last = 1u;
+        __syncthreads();
+        const u32 at = s_below[0] + (u32)tid;          // (no more than NT in all)
+        if (at < count) {
+          u32 v = 0;
+          until(kLimit, [&]() { return (v = load(&gl[tid])) != 0u; });
+          keys[at] = v - 1u;
+          if (v == 0) s_last = 0u;
+        }
+        __syncthreads();
+        if (s_last == 0) return kAlone;
+        // the key with fewer than `need` smaller ones and at least `need` not larger
+        if ((u32)tid < count) {
+          const u32 mine_key = keys[tid];
+          u32 less = 0, equal = 0;
+#pragma unroll 4
+          for (u32 c = 0; c < count; ++c) {
+            const u32 other = keys[c];
+            less += other < mine_key ? 1u : 0u;
+            equal += other == mine_key ? 1u : 0u;
+          }
+          if (less < need && need <= less + equal) s_bin[0] = mine_key;     // equal keys write the same
+        }
+        __syncthreads();
+        found = s_bin[0];
+        return kProject;
+      };
+      auto one_rank = [&](int q) -> bool {             // false: this workgroup has done its part
         const u32 kq = q == NR - 1 ? k[NR - 1] : k[0];
         if (q > 0) {                                   // (other readers of these have passed a barrier since)
           for (int i = tid; i < 2 << kSampleBits; i += NT) (&snext[0][0])[i] = 0;
@@ -1174,7 +1427,11 @@ __global__ __launch_bounds__(NT, (WHOLE == 1 && sizeof(TX) == 2 && RD <= 8 ? 6 :
         }
         u32 first, last, drawn, shift = 0, below = 0;
         interval32(sample_rank(kq, nn, m, n_sel), first, last, drawn);
-        while (((u64)kBins << shift) - 1ull < last) ++shift;           // at most 2^31 keys
+        if (NR == 1 && S > 1) {
+          const auto what = shared_rank(kq, first, last);
+          if (what != kAlone) return what == kProject;
+        }
+        shift = last < (u32)kBins ? 0u : (u32)(__clz(kBins) - __clz(last) + 1);         // bins of 2^shift keys
         for (int i = tid; i < kBins; i += NT) hist[0][i] = 0;
         if (tid == 0) s_below[0] = 0;
         __syncthreads();
@@ -1215,6 +1472,14 @@ __global__ __launch_bounds__(NT, (WHOLE == 1 && sizeof(TX) == 2 && RD <= 8 ? 6 :
         if (tid == 0 && s_last && l.span != 1u) atomicAdd(&status[1 + (q == NR - 1 ? kPassZr : kPassBase)], 1u);
         const u32 key_q = l.span == 1u ? l.k0 : search(l);
         if (q == NR - 1) found = key_q; else base_key = key_q;
+        return true;
+      };
+      // (no loop for one rank: what does not change in it would be computed before it and spilled)
+      if constexpr (NR == 1) {
+        if (!one_rank(0)) return;                      // the same for every thread
+      } else {
+#pragma unroll 1
+        for (int q = 0; q < NR; ++q) one_rank(q);
       }
     }
     if (tid == 0) {

@@ -1,0 +1,101 @@
+"""Calibration of binary32 images of ordinary size: several workgroups share a set, wait for each other and pick the
+rank together.  Which images take it (CPU), its results against the oracle and the radix levels, on data where the
+sampled interval holds few keys, ties, gaps or misses the rank, and with several calls at once."""
+import numpy as np
+import pytest
+
+from paper_2604_16855_amd import tdq
+
+import parity_util as U
+from test_gpu_whole import _data, _extra
+
+
+@pytest.mark.parametrize("B,T,C,G,pct,extra", [
+    (8, 1024, 768, 16, 0.0, 48), (1, 896, 65, 8, 0.0, 7), (1, 896, 64, 8, 0.0, 0), (1, 8192, 256, 16, 0.0, 256),
+    (1, 8193, 256, 16, 0.0, -1), (1, 8192, 2056, 16, 0.0, 256), (1, 8192, 2057, 16, 0.0, -1),
+    (30, 300, 300, 16, 0.0, 1), (32, 300, 300, 16, 0.0, -1), (2, 512, 512, 1, 0.0, -1), (2, 512, 512, 2, 0.0, 32),
+    (2, 512, 512, 32, 0.0, 32), (2, 512, 512, 33, 0.0, -1), (2, 512, 512, 16, 0.99, -1)])
+def test_rule(B, T, C, G, pct, extra):
+    assert _extra(tdq.TDQ_F32, B, T, C, G, pct) == extra
+
+
+def _gappy(kind, B, T, C, seed):
+    rng = np.random.default_rng(seed)
+    x = rng.laplace(0, 1, (B, T, C)) * np.exp(rng.normal(0, 0.8, (B, T, 1)))
+    if kind == "equal":
+        x[:] = 0.75
+    elif kind == "ties":                             # a tie of 30 % around the rank
+        x[rng.random((B, T, C)) < 0.3] = 0.05
+    elif kind == "masked":                           # the rank just above the zeros
+        x[rng.random((B, T, C)) < 0.197] = 0.0
+    elif kind == "two":                              # a fifth of the values far below the others
+        x = np.where(rng.random((B, T, C)) < 0.2, 1e-3 * x, 5 + 0.1 * rng.normal(0, 1, (B, T, C)))
+    elif kind == "first":                            # the channels that a sample reads least
+        x[:, :, : max(1, C // 5)] *= 1e-3
+    return x.astype(np.float32)
+
+
+KINDS = ["lap", "relu", "pad", "few", "near", "one", "equal", "ties", "masked", "two", "first"]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("B,T,C,G,pad", [
+    (2, 512, 113, 16, 0), (1, 896, 65, 2, 3), (1, 8192, 9, 5, 0), (3, 30, 2049, 32, 0), (1, 3000, 130, 8, 2),
+    (4, 1025, 64, 12, 0), (2, 60, 1026, 3, 0), (1, 20000 // 3, 11, 24, 1)])
+def test_against_oracle(B, T, C, G, pad, kind):
+    X = _data(kind, B, T, C, np.float32, T + C) if kind in KINDS[:6] else _gappy(kind, B, T, C, T + C)
+    p = tdq.default_params(G)
+    assert _extra(tdq.TDQ_F32, B, T, C, G) > 0
+    g = U.gpu_calibrate(X, p, ld_pad=pad)
+    assert g["status"] == 0
+    U.assert_calibration_matches(g, X, p)
+    p.flags |= tdq.FLAG_EXACT_SELECT                 # the radix levels
+    h = U.gpu_calibrate(X, p, ld_pad=pad)
+    assert np.array_equal(g["gid"], h["gid"]) and np.array_equal(g["stats"]["thr"], h["stats"]["thr"])
+    assert np.array_equal(g["stats"]["c_base"], h["stats"]["c_base"])
+    assert np.allclose(g["scale"], h["scale"], rtol=2e-7, atol=0)        # sigma: sums in another order
+
+
+@pytest.mark.gpu
+def test_calls_at_once():
+    """More workgroups than the chip holds, of calls on several streams that wait for their own only."""
+    import torch
+    B, T, C, G, n = 8, 512, 400, 16, 6
+    p = tdq.default_params(G)
+    X = [torch.from_numpy(_data("lap", B, T, C, np.float32, i)).to(U.dev()) for i in range(n)]
+    want = [tdq.tdq_calibrate_groups(x, p)[:3] for x in X]
+    ws = [tdq.alloc_workspace(B, T, C, tdq.TDQ_F32, p, x.device) for x in X]
+    got = [tuple(torch.empty_like(t) for t in w) for w in want]
+    streams = [torch.cuda.Stream() for _ in range(n)]
+    torch.cuda.synchronize()
+    for _ in range(40):
+        for x, w, o, s in zip(X, ws, got, streams):
+            with torch.cuda.stream(s):
+                tdq.tdq_calibrate_groups(x, p, w, out=o)
+    torch.cuda.synchronize()
+    for w, o, k in zip(want, got, ws):
+        assert all(torch.equal(a, b) for a, b in zip(w, o)) and tdq.device_status(k) == 0
+
+
+@pytest.mark.gpu
+def test_in_a_graph():
+    """Replays on changing inputs: every word that the workgroups meet in is cleared inside the captured call."""
+    import torch
+    B, T, C, G = 3, 700, 150, 8
+    p = tdq.default_params(G)
+    data = [torch.from_numpy(_data(k, B, T, C, np.float32, 3)).to(U.dev()) for k in ("lap", "few", "relu", "near", "lap")]
+    X = data[0].clone()
+    ws = tdq.alloc_workspace(B, T, C, tdq.TDQ_F32, p, X.device)
+    out = (torch.empty((B, T), dtype=torch.int32, device=X.device), *(torch.empty((B, G), device=X.device) for _ in range(2)))
+    tdq.tdq_calibrate_groups(X, p, ws, out=out)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        tdq.tdq_calibrate_groups(X, p, ws, out=out)
+    for x in data:
+        X.copy_(x)
+        graph.replay()
+        torch.cuda.synchronize()
+        for a, b in zip(out, tdq.tdq_calibrate_groups(x, p)[:3]):
+            assert torch.equal(a, b)
