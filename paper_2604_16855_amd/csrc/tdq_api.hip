@@ -158,9 +158,12 @@ static bool samples_rank(tdq_dtype dt, int B, int T, int C, int G, bool exact_on
 // against three (or four).
 //   * A workgroup for every 8 Ki elements, and no more than 512 in all (two per CU): [8, 121, 512] with 16 sets
 //     22.1 / 22.0 / 21.1 with 64 / 16 / 8 Ki, [16, 484, 320] 35.8 / 34.2 / 33.2.
-//   * No more than 40 Ki elements for each (all tokens may be in one set), 64 Ki with two ranks: every workgroup of
-//     a set repeats the search for its tokens and its interval, so a large batch is better off with one sweep over
-//     all sets.  [21, 536, 1344], 80 Ki each, 77.3 against 75.0; [28, 187, 1984], 124 Ki, 71.4 against 68.8;
+//   * No more than 64 Ki elements for each (all tokens may be in one set), 40 Ki with one rank and at most one
+//     workgroup to share a set: every workgroup of a set repeats the search for its tokens and its interval, so a large
+//     batch is better off with one sweep over all sets.  From 40 to 80 Ki 90 random calls are 1.085 times as fast in the
+//     geometric mean, [8, 7744, 512] with 16 sets 43.7 by the chain and 42.4, [4, 8000, 1024] 46.2 and 40.7, [8, 1998, 1600]
+//     46.9 and 37.4, [14, 3222, 392] 34.0 and 34.8; above 64 Ki [26, 577, 2144] 45.3 and 47.9, [3, 4724, 2144] 51.8 and
+//     55.6.  [21, 536, 1344], 80 Ki each, 77.3 against 75.0; [28, 187, 1984], 124 Ki, 71.4 against 68.8;
 //     calibration of values on a grid, which meet in few words of LDS, [17, 5107, 131], 44 Ki, 60.8 against 46.8; but
 //     [14, 5850, 160], 29 Ki, percentile, 97.9 against 122.3.
 //   * One rank only (two save a whole sweep): fewer than 64 workgroups beyond the first for a set, which all meet in
@@ -209,7 +212,7 @@ static int whole_extra(tdq_dtype dt, int B, int T, int C, int G, bool two_ranks)
     if (G <= 2 && T > 4096 && e > 16384 * (extra + 1)) return -1;
   }
   if (two_ranks && extra > 0 && bracket_bins(G) < 1024) return -1;
-  if (e > (two_ranks ? 65536 : 40960) * (extra + 1)) return -1;
+  if (e > (two_ranks || extra > 1 ? 65536 : 40960) * (extra + 1)) return -1;
   return (int)extra;
 }
 
