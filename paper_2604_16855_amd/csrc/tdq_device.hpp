@@ -240,6 +240,32 @@ __device__ __forceinline__ void find_ranks(const u32* const (&h)[K], const u32 (
   }
 }
 
+// The key of rank `need` (1-based) among list[0 .. count - 1], count no more than there are threads, to *out: every
+// key is compared with all, 16 at a time (a loop's branch back costs a lone wavefront about as much as 16 instructions).
+// 16-byte aligned, and the 16 words from list[count] on hold keys that are larger than any.
+__device__ __forceinline__ void pick_listed(const u32* list, u32 count, u32 need, u32* out) {
+  if (threadIdx.x < count) {
+    const u32 mine = list[threadIdx.x];
+    u32 less = 0, equal = 0;
+#pragma unroll 1
+    for (u32 c = 0; c < count; c += 16) {
+      uint4 q[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) q[i] = *reinterpret_cast<const uint4*>(list + c + 4 * i);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const u32 k[4] = {q[i].x, q[i].y, q[i].z, q[i].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          less += k[e] < mine ? 1u : 0u;
+          equal += k[e] == mine ? 1u : 0u;
+        }
+      }
+    }
+    if (less < need && need <= less + equal) *out = mine;      // equal keys write the same
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Moments.  The dispersion of a set is the population standard deviation of all its
 // elements (Sec. 4.2), and the bar on it is 1e-6 relative whatever the data's offset.

@@ -167,7 +167,7 @@ constexpr int kWindow = 1 << kFinishBits;       // keys of a pass that looks at 
 // LDS of the search
 template <int NT, bool LISTED>
 struct FinishLds {
-  u32 h[1 << kFinishBits];
+  __attribute__((aligned(16))) u32 h[1 << kFinishBits];
   unsigned short list[LISTED ? 1 : kFinishTokens];    // the set's tokens among those looked at together
   u32 wtot[NT / 64], digit;
   unsigned long long wsum[NT / 64], rest;
@@ -1200,7 +1200,7 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
         u32* gl = gh + wbins;
         u32* ctl = wa.ctl + (size_t)idx * kSetCtl;
         const u32 keep = wbins < NT ? (u32)wbins : (u32)NT;
-        static_assert(NT <= 1 << kFinishBits, "the keys of the last bin fit the search's histogram");
+        static_assert(NT + 16 <= 1 << kFinishBits, "the keys of the last bin fit the search's histogram");
         auto load = [&](const u32* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
         const bool picks = s_parts[0] == 0;
         if ((int)s_parts[0] >= S) return kLeave;
@@ -1401,20 +1401,10 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
           keys[at] = v - 1u;
           if (v == 0) s_last = 0u;
         }
+        if (tid < 16) keys[count + (u32)tid] = 0xFFFFFFFFu;
         __syncthreads();
         if (s_last == 0) return kAlone;
-        // the key with fewer than `need` smaller ones and at least `need` not larger
-        if ((u32)tid < count) {
-          const u32 mine_key = keys[tid];
-          u32 less = 0, equal = 0;
-#pragma unroll 4
-          for (u32 c = 0; c < count; ++c) {
-            const u32 other = keys[c];
-            less += other < mine_key ? 1u : 0u;
-            equal += other == mine_key ? 1u : 0u;
-          }
-          if (less < need && need <= less + equal) s_bin[0] = mine_key;     // equal keys write the same
-        }
+        pick_listed(keys, count, need, &s_bin[0]);
         __syncthreads();
         found = s_bin[0];
         return kProject;
