@@ -158,12 +158,12 @@ static bool samples_rank(tdq_dtype dt, int B, int T, int C, int G, bool exact_on
 // against three (or four).
 //   * A workgroup for every 8 Ki elements, and no more than 512 in all (two per CU): [8, 121, 512] with 16 sets
 //     22.1 / 22.0 / 21.1 with 64 / 16 / 8 Ki, [16, 484, 320] 35.8 / 34.2 / 33.2.
-//   * No more than 64 Ki elements for each (all tokens may be in one set), 40 Ki with one rank and at most one
-//     workgroup to share a set: every workgroup of a set repeats the search for its tokens and its interval, so a large
-//     batch is better off with one sweep over all sets.  From 40 to 80 Ki 90 random calls are 1.085 times as fast in the
-//     geometric mean, [8, 7744, 512] with 16 sets 43.7 by the chain and 42.4, [4, 8000, 1024] 46.2 and 40.7, [8, 1998, 1600]
-//     46.9 and 37.4, [14, 3222, 392] 34.0 and 34.8; above 64 Ki [26, 577, 2144] 45.3 and 47.9, [3, 4724, 2144] 51.8 and
-//     55.6.  [21, 536, 1344], 80 Ki each, 77.3 against 75.0; [28, 187, 1984], 124 Ki, 71.4 against 68.8;
+//   * No more than 80 Ki elements for each (all tokens may be in one set), 64 Ki with two ranks, 40 Ki with one rank and
+//     at most one workgroup to share a set: every workgroup of a set repeats the search for its tokens and its
+//     interval, so a large batch is better off with one sweep over all sets.  From 40 to 80 Ki 90 random calls are 1.085
+//     times as fast in the geometric mean, [8, 7744, 512] with 16 sets 43.7 by the chain and 42.4, [4, 8000, 1024] 46.2
+//     and 40.7, [8, 1998, 1600] 46.9 and 37.4; the slowest [3, 4724, 2144] 51.8 and 55.6, [26, 577, 2144] 45.3 and 47.9.
+//     Before, above that or so: [21, 536, 1344], 80 Ki each, 77.3 against 75.0; [28, 187, 1984], 124 Ki, 71.4 against 68.8;
 //     calibration of values on a grid, which meet in few words of LDS, [17, 5107, 131], 44 Ki, 60.8 against 46.8; but
 //     [14, 5850, 160], 29 Ki, percentile, 97.9 against 122.3.
 //   * One rank only (two save a whole sweep): fewer than 64 workgroups beyond the first for a set, which all meet in
@@ -176,11 +176,10 @@ static bool samples_rank(tdq_dtype dt, int B, int T, int C, int G, bool exact_on
 //     44.7); an image that is one set by itself 40 Ki ([2, 576, 74], 42 Ki, 45.0 against 34.1).
 //     Beyond that and with one rank and 2 to 32 sets (256 bins and 256 keys of a set have room then), several share a
 //     set and wait for each other: no more than 64 Ki elements for each and 256 of them to an image.  Calibration by the
-//     chain and so: [2, 484, 320] with 8 sets 32.7 / 21.5, [8, 1024, 768] with 16 46.1 / 35.6, [24, 300, 300] 42.1 /
+//     chain and so: [2, 484, 320] with 8 sets 32.7 / 20.6, [8, 1024, 768] with 16 46.1 / 34.4, [24, 300, 300] 42.1 /
 //     32.3, [4, 4096, 768] 89.6 / 54.8 and [16, 1024, 1024] 102.9 / 65.6 (levels before), [1, 8192, 1024] 76.7 / 96.8
-//     with 496 of them and 74.0 with 240.  110 random calls over laws of data: 1.40 times as fast in the geometric mean,
-//     two more than 2 % slower (values within 1e-4 of 1 and three sets, [3, 2422, 1156], 79 / 105: every key of
-//     the interval is one of a few; one and the same value, [8, 288, 1829], 61 / 64).
+//     with 496 of them and 74.0 with 240.  110 random calls over laws of data: 1.45 times as fast in the geometric mean,
+//     one slower (one and the same value, [8, 288, 1829] with 32 sets, 61 / 70).
 //   * Up to 1536 sets in all, which take two turns on the chip: [49, 74, 832] with 32 sets (1568) 31.0 against 29.8,
 //     [58, 20, 9] with 32 42.8 against 36.6, [64, 322, 56] with 64 55.7 against 45.6; of 94 calls of 1024 to 1536 sets
 //     none is slower, half are faster than 1.27 times.  binary32, whose kernel needs more registers: up to 1024, 512
@@ -212,7 +211,7 @@ static int whole_extra(tdq_dtype dt, int B, int T, int C, int G, bool two_ranks)
     if (G <= 2 && T > 4096 && e > 16384 * (extra + 1)) return -1;
   }
   if (two_ranks && extra > 0 && bracket_bins(G) < 1024) return -1;
-  if (e > (two_ranks || extra > 1 ? 65536 : 40960) * (extra + 1)) return -1;
+  if (e > (two_ranks ? 65536 : extra > 1 ? 81920 : 40960) * (extra + 1)) return -1;
   return (int)extra;
 }
 

@@ -889,6 +889,9 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
 
   // ---- 3: the sample.  Every live key adds one to an LDS histogram of its top kSampleBits
   // bits; zeros, often many, are counted first (binary16: bin 0 is what the others do not hold).
+  // (binary32, workgroups that share a set: two more bits instead of the copies)
+  constexpr int kFineBits = kSampleBits + 2;
+  static_assert(F16 || 1 << kFineBits == kCopies << kSampleBits, "the same words");
   u32 key[F16 ? 1 : kKeys], zeros = 0;
   auto add_piece = [&](int e) {
     if constexpr (F16) {
@@ -909,7 +912,8 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
         key[e * V + i] = k;
         zeros += k == 0u ? 1u : 0u;
         if (k != kDead && k != 0u)
-          atomicAdd(&shist[(k >> (kKeyBits - kSampleBits)) * kCopies + (lane & (kCopies - 1))], 1u);
+          atomicAdd(&shist[S > 1 ? k >> (kKeyBits - kFineBits)
+                                 : (k >> (kKeyBits - kSampleBits)) * kCopies + (lane & (kCopies - 1))], 1u);
       }
     }
   };
@@ -959,19 +963,37 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
   if (!WHOLE && !F16 && wave == NW - 1) finish_moments();
   // binary32: the interval between two order statistics of the sample, six standard deviations of its
   // elements and one of its tokens to either side of s, each resolved to 20 of its 31 bits: first key, last
-  // key - first key, sampled ranks between them.  By the whole workgroup.
+  // key - first key, sampled ranks between them.  By the whole workgroup.  Where workgroups share a set a miss costs
+  // one more round and keys in the interval room and time: four and a half, to 12 bits (a sixteenth of an octave, in
+  // one step) unless that holds three times the sampled keys wanted, else to 22.
   auto interval32 = [&](const SampleRank& s, u32& first, u32& last, u32& drawn) {
     if constexpr (!F16) {
       const int dr = (int)(S > 1 ? 4.f * s.dev + 0.5f * s.dev_tokens : 6.f * s.dev + s.dev_tokens) + 2, rk = (int)s.rk;
       const u32* const hs[2] = {shist, shist};
       const u32 rs[2] = {(u32)(rk - dr < 1 ? 1 : rk - dr), (u32)(rk + dr > (int)m ? (int)m : rk + dr)};
-      find_ranks<NT, 2, kCopies, false>(hs, rs, stot, s_bin, s_before, nullptr);
+      drawn = rs[1] - rs[0];
+      // top digits of a key, and the ten bits after them
+      const int top_at = S > 1 ? kKeyBits - kFineBits : kKeyBits - kSampleBits, next_at = top_at - 10;
+      if (S > 1)
+        find_ranks<NT, 2, 1, false, 1 << kFineBits>(hs, rs, stot, s_bin, s_before, nullptr);
+      else
+        find_ranks<NT, 2, kCopies, false>(hs, rs, stot, s_bin, s_before, nullptr);
       __syncthreads();
       const u32 b0 = s_bin[0], b1 = s_bin[1];
+      if (WHOLE == 1 && S > 1) {
+        // whole sixteenths of an octave, unless they hold far more than is wanted
+        const u32 held = s_before[1] + shist[b1] - s_before[0];
+        if (held <= 3u * drawn) {                      // the same for every thread
+          first = b0 << top_at;
+          first = first > 1u ? first : 1u;             // zeros are counted below
+          last = ((b1 + 1u) << top_at) - 1u - first;
+          return;
+        }
+      }
 #pragma unroll
       for (int i = 0; i < kKeys; ++i) {
         if (i / V < steps) {
-          const u32 top = key[i] >> 21, next = (key[i] >> 11) & 1023u;
+          const u32 top = key[i] >> top_at, next = (key[i] >> next_at) & 1023u;
           if (key[i] != kDead && top == b0) atomicAdd(&snext[0][next], 1u);
           if (key[i] != kDead && top == b1) atomicAdd(&snext[1][next], 1u);
         }
@@ -981,10 +1003,9 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
       const u32 rn[2] = {rs[0] - s_before[0], rs[1] - s_before[1]};
       find_ranks<NT, 2, 1, false>(hn, rn, stot, s_bin + 2, s_before + 2, nullptr);
       __syncthreads();
-      first = (b0 << 21) | (s_bin[2] << 11);
-      first = first > 1u ? first : 1u;               // zeros are counted below
-      last = ((b1 << 21) | (s_bin[3] << 11)) + 2047u - first;
-      drawn = rs[1] - rs[0];
+      first = (b0 << top_at) | (s_bin[2] << next_at);
+      first = first > 1u ? first : 1u;                 // zeros are counted below
+      last = ((b1 << top_at) | (s_bin[3] << next_at)) + ((1u << next_at) - 1u) - first;
     }
   };
   if constexpr (WHOLE != 0) {
@@ -1187,8 +1208,9 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
       // it waiting all the same: after kLimit the helpers leave, and the first does everything alone.)
       // What they exchange goes through device-scope atomic operations, as for binary16 above.
       // Bound by its chain of steps: [8, 1024, 768] with 16 sets from the first kernel on, us: range and tokens 4, sample
-      // and interval 8, the rows 4 (25 MB at 6 TB/s), counts met and read 4, keys of the bin 3, skew.  Calibration by
-      // the chain of five kernels, which reads the rows once more, and so: 46 and 35; without the list, rows read
+      // and interval 6, the rows 4 (25 MB at 6 TB/s), counts met and read 4, keys of the bin 3, skew.  Calibration by
+      // the chain of five kernels, which reads the rows once more, and so: 46 and 34.4; with the interval's ends found in
+      // two steps always 35.9; without the list, rows read
       // again for the bin's keys, 36.5; lists by wavefront with a ballot per element 37; the rows' first loads issued
       // before the sample (44 bytes of scratch) 36.4.
       enum { kProject, kLeave, kAlone };
