@@ -116,6 +116,23 @@ __device__ __forceinline__ void merge_low8(u32 (&k)[8]) {
   sort8_bitonic<PK>(k);
 }
 
+// a[], b[] sorted ascending: the K-th smallest of both (1 <= K <= 8).  However many of the K smallest a has, i, they
+// are its first i and the first K - i of b, and any other split has a larger maximum.
+template <bool PK, int K>
+__device__ __forceinline__ u32 kth_of_two(const u32 (&a)[8], const u32 (&b)[8]) {
+  u32 r = kmin<PK>(a[K - 1], b[K - 1]);
+#pragma unroll
+  for (int i = 1; i < K; ++i) r = kmin<PK>(r, kmax<PK>(a[i - 1], b[K - 1 - i]));
+  return r;
+}
+
+// ceil(0.2 * 32): the rank of the method's own zr.  The sweeps exist for it by itself, because only where the rank is
+// known need the second merge not be sorted, 26 of some 450 vector instructions of a pass: [32768, 1024] binary16 28.3 -> 26.9
+// us, in 6-bit fragments 31.3 -> 29.4, [8192, 768] 7.9 -> 7.6, binary32 9.1 -> 8.6.  (One kernel with a choice among eight
+// ranks inside: the same for large inputs, but [1664, 288] binary32 in fragments 10.04 -> 10.33, where the jump over the
+// choice is paid in each of eight passes; 9.22 so.)
+constexpr int kUsualRank = 7;
+
 // The rank-th smallest (1-based, 1 <= rank <= 32) of the block's 32 keys by bisection on
 // the key bits: the largest t with #{key < t} < rank.  PK: both blocks at once.
 template <bool PK>
@@ -158,7 +175,8 @@ __device__ __forceinline__ u32 kth_by_bisection(const u32 (&key)[8], u32 rank) {
 // and, in every lane of the quad, its clip radius and step.  Every lane of the wavefront
 // must take part (quad exchanges).
 // ---------------------------------------------------------------------------
-template <typename T>
+// KQ: the rank kq where it is known, else 0.
+template <typename T, int KQ>
 __device__ __forceinline__ void block_core(const u32 (&raw)[sizeof(T) == 2 ? 2 : 1][sizeof(T) == 2 ? 4 : 8],
                                            int ql, int kq, int kp, const Scalars& sc,
                                            u32 (&word)[sizeof(T) == 2 ? 2 : 1],
@@ -218,27 +236,38 @@ __device__ __forceinline__ void block_core(const u32 (&raw)[sizeof(T) == 2 ? 2 :
     for (int i = 0; i < 8; ++i) key[i] = raw[0][i] & 0x7FFFFFFFu;
   }
 
-  u32 top = key[0];
+  u32 top = key[0], thr;
+  if constexpr (KQ > 0) {
+    // every lane's keys sorted, the 8 smallest of two lanes sorted, and of two such pairs only the key of the rank;
+    // the largest key is the last of a lane's sorted ones
+    u32 k[8], o[8];
 #pragma unroll
-  for (int i = 1; i < 8; ++i) top = kmax<PK>(top, key[i]);
-  top = kmax<PK>(top, quad_u32<kQuadXor1>(top));
-  top = kmax<PK>(top, quad_u32<kQuadXor2>(top));
-  if (kp < kBlk) top = kth_by_bisection<PK>(key, (u32)kp);         // percentile base radius
-
-  u32 thr;
-  if (kq <= 8) {
+    for (int i = 0; i < 8; ++i) k[i] = key[i];
+    sort8<PK>(k);
+    top = k[7];
+    merge_low8<PK, kQuadXor1>(k);
+#pragma unroll
+    for (int i = 0; i < KQ; ++i) o[i] = quad_u32<kQuadXor2>(k[i]);
+    thr = kth_of_two<PK, KQ>(k, o);
+  } else if (kq <= 8) {
     u32 k[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) k[i] = key[i];
     sort8<PK>(k);
+    top = k[7];
     merge_low8<PK, kQuadXor1>(k);
     merge_low8<PK, kQuadXor2>(k);
     thr = k[0];
 #pragma unroll
     for (int i = 1; i < 8; ++i) thr = kq == i + 1 ? k[i] : thr;
   } else {
+#pragma unroll
+    for (int i = 1; i < 8; ++i) top = kmax<PK>(top, key[i]);
     thr = kth_by_bisection<PK>(key, (u32)kq);
   }
+  top = kmax<PK>(top, quad_u32<kQuadXor1>(top));
+  top = kmax<PK>(top, quad_u32<kQuadXor2>(top));
+  if (kp < kBlk) top = kth_by_bisection<PK>(key, (u32)kp);         // percentile base radius
 
   // Eq. (dcrp) in binary32 with the eps floors of the supplementary conventions.  Lane s
   // of the quad does block s; the results travel to the other lanes afterwards.
@@ -315,7 +344,7 @@ __device__ __forceinline__ void block_store(u32 word, float c, float d, bool own
 // ---------------------------------------------------------------------------
 // the sweep
 // ---------------------------------------------------------------------------
-template <typename T>
+template <typename T, int KQ>
 __global__ __launch_bounds__(256) void k_quantize_blocks(
     const T* __restrict__ X, long long ld, u32 total, int C, int KB, int vec_ok, int q_vec_ok,
     int kq, int kp, Scalars sc, uint8_t* __restrict__ Q, long long ld_q, float* __restrict__ bscale,
@@ -369,7 +398,7 @@ __global__ __launch_bounds__(256) void k_quantize_blocks(
 
   u32 word[NB];
   float cs[NB], ds[NB];
-  block_core<T>(raw, ql, kq, kp, sc, word, cs, ds);
+  block_core<T, KQ>(raw, ql, kq, kp, sc, word, cs, ds);
 #pragma unroll
   for (int s = 0; s < NB; ++s)
     if (live[s])
@@ -388,8 +417,12 @@ static hipError_t quantize_blocks_t(const T* X, long long M, int C, long long ld
   const int q_vec_ok = ((reinterpret_cast<uintptr_t>(Q) & 3) == 0 && ld_q % 4 == 0) ? 1 : 0;
   const long long total = M * KB;                          // checked by the caller: < 2^31
   const unsigned grid = (unsigned)((total + 4 * per_wave - 1) / (4 * per_wave));
-  hipLaunchKernelGGL((k_quantize_blocks<T>), dim3(grid), dim3(256), 0, st, X, ld, (u32)total, C, KB,
-                     vec_ok, q_vec_ok, kq, kp, sc, Q, ld_q, bscale, bclip, ld_s);
+  if (kq == kUsualRank)
+    hipLaunchKernelGGL((k_quantize_blocks<T, kUsualRank>), dim3(grid), dim3(256), 0, st, X, ld, (u32)total, C, KB,
+                       vec_ok, q_vec_ok, kq, kp, sc, Q, ld_q, bscale, bclip, ld_s);
+  else
+    hipLaunchKernelGGL((k_quantize_blocks<T, 0>), dim3(grid), dim3(256), 0, st, X, ld, (u32)total, C, KB,
+                       vec_ok, q_vec_ok, kq, kp, sc, Q, ld_q, bscale, bclip, ld_s);
   return hipGetLastError();
 }
 
@@ -417,7 +450,7 @@ hipError_t launch_quantize_blocks(const void* X, tdq_dtype dt, long long M, int 
 typedef float blk_v16f __attribute__((ext_vector_type(16)));
 typedef int blk_v6i __attribute__((ext_vector_type(6)));
 
-template <typename T>
+template <typename T, int KQ>
 __global__ __launch_bounds__(256) void k_quantize_blocks_f6(
     const T* __restrict__ X, long long ld, long long M, int C, int KB, int KB64, int k_tiles,
     int vec_ok, int kq, int kp, Scalars sc, uint8_t* __restrict__ F, float* __restrict__ bscale,
@@ -474,7 +507,7 @@ __global__ __launch_bounds__(256) void k_quantize_blocks_f6(
     }
     u32 word[NB];
     float cs[NB], ds[NB];
-    block_core<T>(raw, ql, kq, kp, sc, word, cs, ds);      // (a quad without a block works on zeros)
+    block_core<T, KQ>(raw, ql, kq, kp, sc, word, cs, ds);      // (a quad without a block works on zeros)
 #pragma unroll
     for (int s = 0; s < NB; ++s) {
       if (live[s] && ql == s) {
@@ -520,14 +553,24 @@ hipError_t launch_quantize_blocks_f6(const void* X, tdq_dtype dt, long long M, i
   const unsigned grid = (unsigned)(n_rb * k_tiles);        // checked by the caller: < 2^31
   if (dt == TDQ_F16) {
     const int vec_ok = ((reinterpret_cast<uintptr_t>(X) & 15) == 0 && ld % 8 == 0) ? 1 : 0;
-    hipLaunchKernelGGL((k_quantize_blocks_f6<u16>), dim3(grid), dim3(256), 0, st,
-                       static_cast<const u16*>(X), ld, M, C, KB, KB64, k_tiles, vec_ok, kq, kp, sc, F,
-                       bscale, bclip, ld_s);
+    if (kq == kUsualRank)
+      hipLaunchKernelGGL((k_quantize_blocks_f6<u16, kUsualRank>), dim3(grid), dim3(256), 0, st,
+                         static_cast<const u16*>(X), ld, M, C, KB, KB64, k_tiles, vec_ok, kq, kp, sc, F,
+                         bscale, bclip, ld_s);
+    else
+      hipLaunchKernelGGL((k_quantize_blocks_f6<u16, 0>), dim3(grid), dim3(256), 0, st,
+                         static_cast<const u16*>(X), ld, M, C, KB, KB64, k_tiles, vec_ok, kq, kp, sc, F,
+                         bscale, bclip, ld_s);
   } else {
     const int vec_ok = ((reinterpret_cast<uintptr_t>(X) & 15) == 0 && ld % 4 == 0) ? 1 : 0;
-    hipLaunchKernelGGL((k_quantize_blocks_f6<float>), dim3(grid), dim3(256), 0, st,
-                       static_cast<const float*>(X), ld, M, C, KB, KB64, k_tiles, vec_ok, kq, kp, sc, F,
-                       bscale, bclip, ld_s);
+    if (kq == kUsualRank)
+      hipLaunchKernelGGL((k_quantize_blocks_f6<float, kUsualRank>), dim3(grid), dim3(256), 0, st,
+                         static_cast<const float*>(X), ld, M, C, KB, KB64, k_tiles, vec_ok, kq, kp, sc, F,
+                         bscale, bclip, ld_s);
+    else
+      hipLaunchKernelGGL((k_quantize_blocks_f6<float, 0>), dim3(grid), dim3(256), 0, st,
+                         static_cast<const float*>(X), ld, M, C, KB, KB64, k_tiles, vec_ok, kq, kp, sc, F,
+                         bscale, bclip, ld_s);
   }
   return hipGetLastError();
 }
@@ -541,7 +584,7 @@ hipError_t launch_quantize_blocks_f6(const void* X, tdq_dtype dt, long long M, i
 // reads; rows 8 bytes longer than the data keep them to two-way bank conflicts) and
 // runs block_core.  Codes and steps are token-major, as from the token-major sweep.
 // ---------------------------------------------------------------------------
-template <typename T, int TC>
+template <typename T, int TC, int KQ>
 __global__ __launch_bounds__(256) void k_quantize_blocks_chw(
     const T* __restrict__ X, long long ld_c, long long ld_b, int C, int T_, int vin_ok, int q_vec_ok,
     int kq, int kp, Scalars sc, uint8_t* __restrict__ Q, long long ld_q, float* __restrict__ bscale,
@@ -604,7 +647,7 @@ __global__ __launch_bounds__(256) void k_quantize_blocks_chw(
       }
       u32 word[NB];
       float cs[NB], ds[NB];
-      block_core<T>(raw, ql, kq, kp, sc, word, cs, ds);
+      block_core<T, KQ>(raw, ql, kq, kp, sc, word, cs, ds);
       const bool tok_ok = t0 + tl < T_;
       const long long row = (long long)b * T_ + t0 + tl;
 #pragma unroll
@@ -631,8 +674,12 @@ static hipError_t quantize_blocks_chw_t(const T* X, int B, int C, int T_, long l
   const dim3 grid((unsigned)((T_ + 16 * E - 1) / (16 * E)), (unsigned)B);
   // 128-channel tiles: 256-channel ones (whole 128-byte lines of codes per token) measured
   // 20 % slower, with half as many workgroups per CU to hide the tile loads
-  hipLaunchKernelGGL((k_quantize_blocks_chw<T, 128>), grid, dim3(256), 0, st, X, ld_c, ld_b, C, T_,
-                     vin_ok, q_vec_ok, kq, kp, sc, Q, ld_q, bscale, bclip, ld_s);
+  if (kq == kUsualRank)
+    hipLaunchKernelGGL((k_quantize_blocks_chw<T, 128, kUsualRank>), grid, dim3(256), 0, st, X, ld_c, ld_b, C, T_,
+                       vin_ok, q_vec_ok, kq, kp, sc, Q, ld_q, bscale, bclip, ld_s);
+  else
+    hipLaunchKernelGGL((k_quantize_blocks_chw<T, 128, 0>), grid, dim3(256), 0, st, X, ld_c, ld_b, C, T_,
+                       vin_ok, q_vec_ok, kq, kp, sc, Q, ld_q, bscale, bclip, ld_s);
   return hipGetLastError();
 }
 
