@@ -99,3 +99,26 @@ def test_in_a_graph():
         torch.cuda.synchronize()
         for a, b in zip(out, tdq.tdq_calibrate_groups(x, p)[:3]):
             assert torch.equal(a, b)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["lap", "relu", "few"])
+@pytest.mark.parametrize("B,C,H,W,G", [(2, 130, 30, 31, 8), (1, 65, 40, 70, 16), (3, 258, 17, 19, 32)])
+def test_feature_maps_and_static_scratch(B, C, H, W, G, kind):
+    """The other entry points that take the route: what the workgroups meet in is cleared by their statistics kernels too."""
+    import torch
+    T = H * W
+    assert _extra(tdq.TDQ_F32, B, T, C, G) > 0
+    X = torch.from_numpy(_data(kind, B, T, C, np.float32, C)).to(U.dev())
+    p = tdq.default_params(G)
+    want = tdq.tdq_calibrate_groups(X, p)[:3]
+    Xc = X.transpose(1, 2).contiguous().view(B, C, H, W)
+    for _ in range(2):
+        Xt, *chw = tdq.tdq_calibrate_groups_chw(Xc, p)[:4]
+        static = tuple(torch.empty_like(t) for t in want)
+        tdq.tdq_calibrate_groups_static(X, p, static)
+        torch.cuda.synchronize()
+        assert torch.equal(Xt.view(B, T, C), X)
+        assert torch.equal(chw[0].view(B, T), want[0]) and torch.equal(static[0], want[0])
+        for a, b, c in zip(want[1:], chw[1:], static[1:]):
+            assert torch.equal(a, c) and torch.allclose(a, b, rtol=2e-7, atol=0)     # sigma: sums in another order
