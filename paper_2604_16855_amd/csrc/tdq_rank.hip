@@ -25,7 +25,8 @@
 //
 // Images of ordinary size take one kernel instead of these (k_sets with WHOLE): the workgroups that find a
 // set's tokens and place its interval then read the set's own rows, several sharing a set, and the last of
-// them to finish verifies, picks and projects.  Nothing but the statistics has to be complete before it.
+// them to finish verifies, picks and projects (binary32: they wait for each other's counts and pick the bin's key
+// together, shared_rank).  Nothing but the statistics has to be complete before it.
 //
 // The result is therefore always the exact order statistic; the sample only decides
 // which of the two routes computes it, i.e. how long it takes.
