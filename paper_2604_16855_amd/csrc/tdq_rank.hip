@@ -37,6 +37,7 @@
 #include <type_traits>
 
 #include "tdq_device.hpp"
+#include "tdq_workgroup.hpp"
 
 namespace tdq {
 
@@ -608,6 +609,7 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
   __shared__ u32 s_share[64];                        // sampled tokens of every set
   __shared__ Lost s_lost[2];
   __shared__ FinishLds<WHOLE ? NT : 64, true> s_search;
+  __shared__ unsigned s_known;                       // of known_to_all alone
   __shared__ unsigned short s_parts[WHOLE == 1 && !F16 ? NT + 1 : 1];     // shares of the set's rows claimed by this workgroup
   // (whole: the set, and which of the S workgroups that share it this is, follow from the sets' sizes)
   int S = 1, part = 0, j = (int)blockIdx.x;
@@ -1229,12 +1231,12 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
         if ((int)s_parts[0] >= S) return kLeave;
         int n_parts = 1;                               // shares of this workgroup, listed in s_parts
         u32 events = 0;                                // how often every share has been counted to have arrived
-        auto arrive = [&](int shares) {                // true in the last to arrive
+        auto arrive = [&](int shares) {                // for thread 0: how many have with these
+          return atomicAdd(&ctl[kCtlArrived], (u32)shares) + (u32)shares;
+        };
+        auto settle = [&]() {                          // what this workgroup has sent is where all see it
           asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
           __syncthreads();
-          if (tid == 0) s_last = atomicAdd(&ctl[kCtlArrived], (u32)shares) + (u32)shares == (u32)S * events ? 1u : 0u;
-          __syncthreads();
-          return s_last != 0;
         };
         auto until = [&](long long patience, auto&& so) {      // (looks until it is, or until it has waited long enough)
           bool is = so();
@@ -1247,11 +1249,7 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
           return is;
         };
         auto reached = [&](int word, u32 value, long long patience) {
-          if (tid == 0) s_last = until(patience, [&]() { return load(&ctl[word]) >= value; }) ? 1u : 0u;
-          __syncthreads();
-          const bool ok = s_last != 0;
-          __syncthreads();
-          return ok;
+          return known_to_all(&s_known, [&]() { return until(patience, [&]() { return load(&ctl[word]) >= value; }); });
         };
         const int share = (tokens + S - 1) / S;
         u32 k0 = first, span = last + 1u;              // the keys that are looked at: span of them from k0 on
@@ -1318,7 +1316,8 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
               if (v) atomicAdd(&words[i], v);
             }
             if (tid == 0 && !known && s_below[0]) atomicAdd(&ctl[kCtlBelow], s_below[0]);
-            arrive(known ? n_parts : 1);
+            settle();
+            if (tid == 0) (void)arrive(known ? n_parts : 1);
             more = false;
             if (!known && !reached(kCtlArrived, (u32)S, kPatience)) {
               if (tid == 0) s_parts[n_parts] = (unsigned short)min(atomicAdd(&ctl[kCtlClaimed], 1u), 0xFFFFu);
@@ -1365,10 +1364,10 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
           if (round > 0) {
             // the words are wanted again: the last to have read them clears them
             ++events;
-            if (arrive(n_parts)) {
+            settle();
+            if (known_to_all(&s_known, [&]() { return arrive(n_parts) == (u32)S * events; })) {
               for (int i = tid; i < W; i += NT) (void)atomicExch(&gh[i], 0u);
-              asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-              __syncthreads();
+              settle();
               if (tid == 0) (void)atomicExch(&ctl[kCtlReady], events);
             }
             ready = events;
