@@ -258,7 +258,8 @@ extern "C" int tdq_whole_extra(int32_t dt, int32_t B, int32_t T, int32_t C, int3
 static int calibrate_after_stats(const void* X, tdq_dtype dt, int32_t B, int32_t T, int32_t C,
                                  int64_t ld_x, const tdq_params* p, int32_t* group_id, float* clip,
                                  float* scale, tdq_group_stats* stats, void* workspace,
-                                 const LevelPlan& lp, const WorkspaceLayout& wl, hipStream_t st) {
+                                 const LevelPlan& lp, const WorkspaceLayout& wl, const Waits& waits,
+                                 hipStream_t st) {
   const int G = p->n_groups;
   char* ws = static_cast<char*>(workspace);
   unsigned* status = reinterpret_cast<unsigned*>(ws + wl.status);
@@ -292,7 +293,8 @@ static int calibrate_after_stats(const void* X, tdq_dtype dt, int32_t B, int32_t
   const int extra = calibration_extra(dt, B, T, C, p);
   if (extra >= 0) {
     if (launch_sets_whole(X, dt, B, T, C, ld_x, G, two_passes ? 2 : 1, extra, bracket_bins_zr(G), Wmax, r, mean, m2,
-                          group_id, sc, bhist, part, img_flag, status, clip, scale, stats, st) != hipSuccess)
+                          group_id, sc, bhist, part, img_flag, status, clip, scale, stats, waits,
+                          st) != hipSuccess)
       return TDQ_ERR_HIP;
     return TDQ_OK;
   }
@@ -340,6 +342,34 @@ static int calibrate_after_stats(const void* X, tdq_dtype dt, int32_t B, int32_t
     }
   }
   return TDQ_OK;
+}
+
+static int calibrate_groups(const void* X, tdq_dtype dt, int32_t B, int32_t T, int32_t C,
+                            int64_t ld_x, const tdq_params* p, int32_t* group_id, float* clip,
+                            float* scale, tdq_group_stats* stats, void* workspace,
+                            size_t workspace_bytes, const Waits& waits, void* stream) {
+  if (!X || !p || !group_id || !clip || !scale || !workspace) return TDQ_ERR_NULL;
+  if (dt != TDQ_F16 && dt != TDQ_F32) return TDQ_ERR_DTYPE;
+  int rc = check_params(p);
+  if (rc != TDQ_OK) return rc;
+  rc = check_shape(B, T, C, ld_x);
+  if (rc != TDQ_OK) return rc;
+  const int G = p->n_groups;
+  const LevelPlan lp = make_level_plan(dt, G);
+  const WorkspaceLayout wl = make_layout(B, T, G, lp);
+  if (workspace_bytes < wl.total) return TDQ_ERR_WORKSPACE;
+  if (reinterpret_cast<uintptr_t>(workspace) & 255) return TDQ_ERR_WORKSPACE;
+  const size_t esz = dt == TDQ_F16 ? 2 : 4;
+  if (reinterpret_cast<uintptr_t>(X) % esz) return TDQ_ERR_ALIGN;
+
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  char* ws = static_cast<char*>(workspace);
+  if (launch_token_stats(X, dt, B * T, C, ld_x, reinterpret_cast<float*>(ws + wl.r),
+                         reinterpret_cast<double*>(ws + wl.mean),
+                         reinterpret_cast<double*>(ws + wl.m2), select_clear(dt, B, T, C, p, ws, wl), st) != hipSuccess)
+    return TDQ_ERR_HIP;
+  return calibrate_after_stats(X, dt, B, T, C, ld_x, p, group_id, clip, scale, stats, workspace, lp,
+                               wl, waits, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -428,28 +458,20 @@ int tdq_calibrate_groups(const void* X, tdq_dtype dt, int32_t B, int32_t T, int3
                          int64_t ld_x, const tdq_params* p, int32_t* group_id, float* clip,
                          float* scale, tdq_group_stats* stats, void* workspace,
                          size_t workspace_bytes, void* stream) {
-  if (!X || !p || !group_id || !clip || !scale || !workspace) return TDQ_ERR_NULL;
-  if (dt != TDQ_F16 && dt != TDQ_F32) return TDQ_ERR_DTYPE;
-  int rc = check_params(p);
-  if (rc != TDQ_OK) return rc;
-  rc = check_shape(B, T, C, ld_x);
-  if (rc != TDQ_OK) return rc;
-  const int G = p->n_groups;
-  const LevelPlan lp = make_level_plan(dt, G);
-  const WorkspaceLayout wl = make_layout(B, T, G, lp);
-  if (workspace_bytes < wl.total) return TDQ_ERR_WORKSPACE;
-  if (reinterpret_cast<uintptr_t>(workspace) & 255) return TDQ_ERR_WORKSPACE;
-  const size_t esz = dt == TDQ_F16 ? 2 : 4;
-  if (reinterpret_cast<uintptr_t>(X) % esz) return TDQ_ERR_ALIGN;
+  return calibrate_groups(X, dt, B, T, C, ld_x, p, group_id, clip, scale, stats, workspace, workspace_bytes, kWaits,
+                          stream);
+}
 
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  char* ws = static_cast<char*>(workspace);
-  if (launch_token_stats(X, dt, B * T, C, ld_x, reinterpret_cast<float*>(ws + wl.r),
-                         reinterpret_cast<double*>(ws + wl.mean),
-                         reinterpret_cast<double*>(ws + wl.m2), select_clear(dt, B, T, C, p, ws, wl), st) != hipSuccess)
-    return TDQ_ERR_HIP;
-  return calibrate_after_stats(X, dt, B, T, C, ld_x, p, group_id, clip, scale, stats, workspace, lp,
-                               wl, st);
+// (not part of the ABI: the tests hurry the workgroups that wait for each other, and look at their words of the
+// workspace afterwards, kSetCtl for each set from byte *set_words on)
+int tdq_calibrate_groups_waits(const void* X, tdq_dtype dt, int32_t B, int32_t T, int32_t C, int64_t ld_x,
+                               const tdq_params* p, int32_t* group_id, float* clip, float* scale,
+                               tdq_group_stats* stats, void* workspace, size_t workspace_bytes, uint32_t patience,
+                               uint32_t limit, size_t* set_words, void* stream) {
+  const int rc = calibrate_groups(X, dt, B, T, C, ld_x, p, group_id, clip, scale, stats, workspace, workspace_bytes,
+                                  Waits{patience, limit}, stream);
+  if (rc == TDQ_OK) *set_words = make_layout(B, T, p->n_groups, make_level_plan(dt, p->n_groups)).part;
+  return rc;
 }
 
 int tdq_calibrate_groups_static(const void* X, tdq_dtype dt, int32_t B, int32_t T, int32_t C,
@@ -511,7 +533,7 @@ int tdq_calibrate_groups_chw(const void* X, tdq_dtype dt, int32_t B, int32_t C, 
                                 st) != hipSuccess)
     return TDQ_ERR_HIP;
   return calibrate_after_stats(Xt, dt, B, T, C, ld_xt, p, group_id, clip, scale, stats, workspace,
-                               lp, wl, st);
+                               lp, wl, kWaits, st);
 }
 
 int tdq_quantize_act(const void* X, tdq_dtype dt, int32_t B, int32_t T, int32_t C, int64_t ld_x,

@@ -159,11 +159,17 @@ hipError_t launch_sets(const void* X, tdq_dtype dt, int B, int T, int C, long lo
 constexpr int kWholeTokens = 8192;     // (the list of tokens and the rest fit 64 KiB of LDS)
 constexpr int kListTokens = 16384;     // most tokens of an image listed by rank in LDS
 constexpr int kSetCtl = 8;
+// binary32 sets that several workgroups share: how long, in ticks of 10 ns, one waits for the others before it claims
+// another share of the rows, and before it counts on them no more.
+struct Waits {
+  unsigned patience, limit;
+};
+constexpr Waits kWaits = {2000, 2000000};
 hipError_t launch_sets_whole(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G, int ranks,
                              int extra, int Wfew, int W, const float* r, const double* mean, const double* m2,
                              int* gid, const Scalars& sc, unsigned* bhist, void* ctl, unsigned* img_flag,
                              unsigned* status, float* clip, float* scale, tdq_group_stats* stats,
-                             hipStream_t st);
+                             const Waits& waits, hipStream_t st);
 hipError_t launch_bracket_hist(const void* X, tdq_dtype dt, int B, int T, int C, long long ld, int G,
                                int Wfew, int W, int cells, unsigned* lists, int cap, const int* gid,
                                Bracket* br, unsigned* bhist, hipStream_t st);

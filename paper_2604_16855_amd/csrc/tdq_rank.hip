@@ -51,8 +51,8 @@ constexpr int kIdRounds = 16;                                   // most range ke
 
 // Words of a set's control block: shares (binary16: workgroups) that have arrived, elements below the interval
 // (binary16, two ranks: the next word for the second); binary32: keys handed over, what the words have been
-// cleared for, shares claimed.
-enum { kCtlArrived = 0, kCtlBelow = 1, kCtlListed = 2, kCtlReady = 3, kCtlClaimed = 4 };
+// cleared for, claims of a share, whether one workgroup did it alone in the end.
+enum { kCtlArrived = 0, kCtlBelow = 1, kCtlListed = 2, kCtlReady = 3, kCtlClaimed = 4, kCtlAlone = 5 };
 
 // Arguments of a k_sets that sees a set through to its radius.
 struct WholeArgs {
@@ -62,6 +62,7 @@ struct WholeArgs {
   float* clip;
   float* scale;
   tdq_group_stats* stats;
+  Waits waits;
 };
 
 // binary32: what a set's `lists` area of cap words holds.  First a head: the largest ~key and the
@@ -1206,9 +1207,9 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
       // share gets the keys of that bin, a few dozen, and picks among them.  Where a bin has too many keys
       // (ties, gaps), or the interval misses the rank, the same again with the range that is known to hold it.
       // Workgroups wait for each other, and nothing makes all of a launch run at the same time: whoever has waited
-      // for kPatience claims another share, so that a wait only ever depends on workgroups that run, and one that
+      // for wa.waits.patience claims another share, so that a wait only ever depends on workgroups that run, and one that
       // starts when nothing is left leaves.  (Words that a second call on the same workspace overwrites could keep
-      // it waiting all the same: after kLimit the helpers leave, and the first does everything alone.)
+      // it waiting all the same: after wa.waits.limit the helpers leave, and the first does everything alone.)
       // What they exchange goes through device-scope atomic operations, as for binary16 above.
       // Bound by its chain of steps: [8, 1024, 768] with 16 sets from the first kernel on, us: range and tokens 4, sample
       // and interval 6, the rows 4 (25 MB at 6 TB/s), counts met and read 4, keys of the bin 3, skew.  Calibration by
@@ -1218,7 +1219,6 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
       // before the sample (44 bytes of scratch) 36.4.
       enum { kProject, kLeave, kAlone };
       auto shared_rank = [&](u32 kq, u32 first, u32 last) {
-        constexpr long long kPatience = 2000, kLimit = 2000000;         // ticks of 10 ns
         constexpr u32 kSeg = (kCopies << kSampleBits) / NT;      // keys a thread lists, where the sample was counted
         const int wbins = W / 2;                       // of the set's words these are bins, the others take the keys
         u32* gh = bhist + (size_t)idx * W;
@@ -1238,17 +1238,17 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
           asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
           __syncthreads();
         };
-        auto until = [&](long long patience, auto&& so) {      // (looks until it is, or until it has waited long enough)
+        auto until = [&](u32 patience, auto&& so) {      // (looks until it is, or until it has waited long enough)
           bool is = so();
           if (!is) {
             const long long since = wall_clock64();
 #pragma unroll 1
             do is = so();
-            while (!is && wall_clock64() - since < patience);
+            while (!is && wall_clock64() - since < (long long)patience);
           }
           return is;
         };
-        auto reached = [&](int word, u32 value, long long patience) {
+        auto reached = [&](int word, u32 value, u32 patience) {
           return known_to_all(&s_known, [&]() { return until(patience, [&]() { return load(&ctl[word]) >= value; }); });
         };
         const int share = (tokens + S - 1) / S;
@@ -1307,7 +1307,7 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
             below = group_sum_u32<64>(below);
             if (lane == 63 && below) atomicAdd(&s_below[0], below);
             // (the words were cleared by the statistics kernel, and from the third round on by the last to have read them)
-            if (ready != 0 && !reached(kCtlReady, ready, kLimit)) return picks ? kAlone : kLeave;
+            if (ready != 0 && !reached(kCtlReady, ready, wa.waits.limit)) return picks ? kAlone : kLeave;
             __syncthreads();
             for (int i = tid; i < (int)bins; i += NT) {
               u32 v = 0;
@@ -1319,14 +1319,14 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
             settle();
             if (tid == 0) (void)arrive(known ? n_parts : 1);
             more = false;
-            if (!known && !reached(kCtlArrived, (u32)S, kPatience)) {
+            if (!known && !reached(kCtlArrived, (u32)S, wa.waits.patience)) {
               if (tid == 0) s_parts[n_parts] = (unsigned short)min(atomicAdd(&ctl[kCtlClaimed], 1u), 0xFFFFu);
               __syncthreads();
               more = (int)s_parts[n_parts] < S;
               n_parts += more ? 1 : 0;
             }
           }
-          if (!reached(kCtlArrived, (u32)S * events, kLimit)) return picks ? kAlone : kLeave;
+          if (!reached(kCtlArrived, (u32)S * events, wa.waits.limit)) return picks ? kAlone : kLeave;
           for (int i = tid; i < wbins; i += NT) hist[0][i] = i < (int)bins ? load(&words[i]) : 0u;
           if (tid == 0) s_below[0] = known ? 0u : load(&ctl[kCtlBelow]);
           __syncthreads();
@@ -1375,7 +1375,7 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
           if (count <= keep) break;
         }
         // the bin's keys, `count` of them in all workgroups: one more than the key, so that a word that has none is 0
-        if (ready != 0 && !reached(kCtlReady, ready, kLimit)) return picks ? kAlone : kLeave;
+        if (ready != 0 && !reached(kCtlReady, ready, wa.waits.limit)) return picks ? kAlone : kLeave;
         u32* keys = s_search.h;
         if (tid == 0) s_below[0] = 0;
         __syncthreads();
@@ -1419,7 +1419,7 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
         const u32 at = s_below[0] + (u32)tid;          // (no more than NT in all)
         if (at < count) {
           u32 v = 0;
-          until(kLimit, [&]() { return (v = load(&gl[tid])) != 0u; });
+          until(wa.waits.limit, [&]() { return (v = load(&gl[tid])) != 0u; });
           keys[at] = v - 1u;
           if (v == 0) s_last = 0u;
         }
@@ -1442,6 +1442,7 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
         if (NR == 1 && S > 1) {
           const auto what = shared_rank(kq, first, last);
           if (what != kAlone) return what == kProject;
+          if (tid == 0) wa.ctl[(size_t)idx * kSetCtl + kCtlAlone] = 1u;
         }
         shift = last < (u32)kBins ? 0u : (u32)(__clz(kBins) - __clz(last) + 1);         // bins of 2^shift keys
         for (int i = tid; i < kBins; i += NT) hist[0][i] = 0;
@@ -1672,7 +1673,7 @@ template <typename TX, int WHOLE>
 static void sets_whole_t(const TX* X, int B, int T, int C, long long ld, int G, int extra, int Wfew, int W,
                          const float* r, const double* mean, const double* m2, int* gid, const Scalars& sc,
                          unsigned* bhist, void* ctl, unsigned* img_flag, unsigned* status, float* clip,
-                         float* scale, tdq_group_stats* stats, hipStream_t st) {
+                         float* scale, tdq_group_stats* stats, const Waits& waits, hipStream_t st) {
   constexpr int V = Elem<TX>::V;
   const int aligned = ((reinterpret_cast<uintptr_t>(X) & 15) == 0 && ld % V == 0 && C % V == 0) ? 1 : 0;
   WholeArgs wa;
@@ -1682,6 +1683,7 @@ static void sets_whole_t(const TX* X, int B, int T, int C, long long ld, int G, 
   wa.clip = clip;
   wa.scale = scale;
   wa.stats = stats;
+  wa.waits = waits;
   const size_t order_bytes = ((size_t)T * sizeof(unsigned short) + 15) & ~(size_t)15;
 #define TDQ_WHOLE_RD(RD, SM)                                                                            \
   hipLaunchKernelGGL((k_sets<TX, 512, RD, SM, WHOLE>), dim3(G + extra, B), dim3(512), order_bytes, st, X, ld, T, \
@@ -1707,10 +1709,10 @@ hipError_t launch_sets_whole(const void* X, tdq_dtype dt, int B, int T, int C, l
                              int extra, int Wfew, int W, const float* r, const double* mean, const double* m2,
                              int* gid, const Scalars& sc, unsigned* bhist, void* ctl, unsigned* img_flag,
                              unsigned* status, float* clip, float* scale, tdq_group_stats* stats,
-                             hipStream_t st) {
+                             const Waits& waits, hipStream_t st) {
 #define TDQ_SW(TX, NR)                                                                                       \
   sets_whole_t<TX, NR>(static_cast<const TX*>(X), B, T, C, ld, G, extra, Wfew, W, r, mean, m2, gid, sc, bhist, \
-                       ctl, img_flag, status, clip, scale, stats, st)
+                       ctl, img_flag, status, clip, scale, stats, waits, st)
   if (dt == TDQ_F16) {
     if (ranks == 1) TDQ_SW(u16, 1); else TDQ_SW(u16, 2);
   } else {

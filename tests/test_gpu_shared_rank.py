@@ -57,6 +57,62 @@ def test_against_oracle(B, T, C, G, pad, kind):
     assert np.allclose(g["scale"], h["scale"], rtol=2e-7, atol=0)        # sigma: sums in another order
 
 
+SET_WORDS, CLAIMED, ALONE = 8, 4, 5                  # of a set in the workspace
+
+
+def _calibrate_waiting(X, p, patience, limit):
+    """tdq_calibrate_groups whose workgroups wait `patience` before they take over more of a set and `limit` before
+    they give up, in ticks of 10 ns, as parity_util.gpu_calibrate gives it; and the sets' words, [B G, 8]."""
+    import torch
+    B, T, C = X.shape
+    G, Xd, c = p.n_groups, U.to_device(X), tdq.C
+    ws = tdq.alloc_workspace(B, T, C, tdq.TDQ_F32, p, Xd.device)
+    gid = torch.empty((B, T), dtype=torch.int32, device=Xd.device)
+    clip, scale = (torch.empty((B, G), device=Xd.device) for _ in range(2))
+    stats, at = torch.empty((B * G, 48), dtype=torch.uint8, device=Xd.device), c.c_size_t()
+    ptr = lambda t: c.c_void_p(t.data_ptr())
+    rc = tdq.lib().tdq_calibrate_groups_waits(
+        ptr(Xd), c.c_int(tdq.TDQ_F32), c.c_int32(B), c.c_int32(T), c.c_int32(C), c.c_int64(C), c.byref(p), ptr(gid),
+        ptr(clip), ptr(scale), ptr(stats), ptr(ws), c.c_size_t(ws.numel()), c.c_uint32(patience), c.c_uint32(limit),
+        c.byref(at), c.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0
+    torch.cuda.synchronize()
+    words = ws[at.value:at.value + 4 * SET_WORDS * B * G].view(torch.int32).view(B * G, SET_WORDS).cpu().numpy()
+    return dict(gid=gid.cpu().numpy(), clip=clip.cpu().numpy(), scale=scale.cpu().numpy(),
+                stats=tdq.stats_to_numpy(stats), status=tdq.device_status(ws)), words
+
+
+USUAL = (2000, 2000000)                              # what tdq_calibrate_groups waits
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("patience,limit", [(0, USUAL[1]), (USUAL[0], 0), (0, 0)])
+@pytest.mark.parametrize("B,T,C,G", [(2, 512, 113, 16), (1, 3000, 130, 8), (2, 700, 1026, 3), (1, 6666, 11, 24)])
+def test_workgroups_that_do_not_wait(B, T, C, G, patience, limit):
+    """Without patience workgroups take over shares of those that are not there yet; with no limit to speak of they leave
+    and the set's first does everything alone.  The words of the sets say that this is what happened."""
+    p, claims, alone, shares = tdq.default_params(G), 0, 0, 0
+    assert _extra(tdq.TDQ_F32, B, T, C, G) > 0
+    for kind in KINDS:
+        X = _data(kind, B, T, C, np.float32, T + C) if kind in KINDS[:6] else _gappy(kind, B, T, C, T + C)
+        g, words = _calibrate_waiting(X, p, patience, limit)
+        assert g["status"] == 0
+        U.assert_calibration_matches(g, X, p)
+        h, usual = _calibrate_waiting(X, p, *USUAL)
+        U.assert_calibration_matches(h, X, p)
+        assert np.array_equal(g["gid"], h["gid"]) and np.array_equal(g["scale"], h["scale"])
+        assert np.all(words[:, ALONE] <= 1) and (limit == 0 or not words[:, ALONE].any())
+        assert not usual[:, ALONE].any()
+        claims += int(words[:, CLAIMED].sum())
+        alone += int(words[:, ALONE].sum())
+        shares += int(usual[:, CLAIMED].sum())       # one claim of each workgroup that shares a set
+    print(f"claims {claims} of {shares} shares, alone {alone}", flush=True)
+    if patience == 0:
+        assert claims > shares
+    if limit == 0:
+        assert alone > 0
+
+
 @pytest.mark.gpu
 def test_calls_at_once():
     """More workgroups than the chip holds, of calls on several streams that wait for their own only."""
