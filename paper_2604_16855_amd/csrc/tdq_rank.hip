@@ -805,6 +805,9 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
     }
   }
   __syncthreads();
+  if constexpr (WHOLE == 1 && !F16) {
+    if (S > 1 && (int)s_parts[0] >= S) return;       // nothing of the set is left (the same for every thread)
+  }
 
   // The sample's loads first, in flight together with those of the moments.  Pieces of V
   // channels: piece p = NT e + tid is part p % PPR of run p / PPR, so a wavefront's load
@@ -1228,7 +1231,6 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
         static_assert(NT + 16 <= 1 << kFinishBits, "the keys of the last bin fit the search's histogram");
         auto load = [&](const u32* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
         const bool picks = s_parts[0] == 0;
-        if ((int)s_parts[0] >= S) return kLeave;
         int n_parts = 1;                               // shares of this workgroup, listed in s_parts
         u32 events = 0;                                // how often every share has been counted to have arrived
         auto arrive = [&](int shares) {                // for thread 0: how many have with these
