@@ -1002,11 +1002,11 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
         if (i / V < steps) {
           const u32 top = key[i] >> top_at, next = (key[i] >> next_at) & 1023u;
           if (key[i] != kDead && top == b0) atomicAdd(&snext[0][next], 1u);
-          if (key[i] != kDead && top == b1) atomicAdd(&snext[1][next], 1u);
+          if (key[i] != kDead && top == b1 && b1 != b0) atomicAdd(&snext[1][next], 1u);
         }
       }
       __syncthreads();
-      const u32* const hn[2] = {snext[0], snext[1]};
+      const u32* const hn[2] = {snext[0], snext[b1 != b0 ? 1 : 0]};
       const u32 rn[2] = {rs[0] - s_before[0], rs[1] - s_before[1]};
       find_ranks<NT, 2, 1, false>(hn, rn, stot, s_bin + 2, s_before + 2, nullptr);
       __syncthreads();
