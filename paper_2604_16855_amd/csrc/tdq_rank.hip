@@ -850,6 +850,9 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
   RowVisitor<TX, NT, 4, true> own(X + (long long)b * T * ld, ld, C, WHOLE && F16 ? wa.L : 1,
                          order + (share_rows > 0 ? share_from : 0), WHOLE && F16 ? share_rows : 0);
 
+  // (of workgroups that share a binary32 set the first to claim a share projects, or does everything alone)
+  bool sums = true;
+  if constexpr (WHOLE == 1 && !F16) sums = S == 1 || s_parts[0] == 0;
   // Moments of the set about the mean of its first token (zero if that is not finite: the
   // image's results are then undefined anyway and its flag is raised).
   const int first_token = listed ? order[0] : s_first;
@@ -858,7 +861,7 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
   double a1 = 0.0, a2 = 0.0;
   u32 cmax = 0;
   piv = (piv - piv == 0.0) ? piv : 0.0;
-  for (int t0 = 0; WHOLE ? t0 == 0 : t0 < T; t0 += RD * NT) {
+  for (int t0 = 0; WHOLE ? t0 == 0 && sums : t0 < T; t0 += RD * NT) {
     if (!one_batch) load_keys(t0);
     // half of the rounds at a time, their loads issued together (a token of another set
     // reads the first token's entry, which is not added)
