@@ -137,6 +137,45 @@ def test_few_values_cost_little_more(B, T, C, G, kind, most):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("B,T,C,G,pct,pad", [
+    (2, 3, 1027, 2, 0.0, 0), (2, 3, 1028, 2, 0.0, 1), (3, 9, 6001, 3, 0.99, 0), (1, 7, 9001, 3, 0.0, 2),
+    (2, 5, 20003, 5, 0.0, 0), (1, 2, 40001, 2, 0.0, 0), (2, 20, 3300, 4, 0.0, 0), (1, 1, 8195, 1, 0.0, 0)])
+def test_few_wide_rows(B, T, C, G, pct, pad, kind):
+    """Rows that 64 to 512 lanes read, one workgroup to a set and several, tails of rows."""
+    X = _data(kind, B, T, C, np.float32, T + C) if kind in KINDS[:6] else _gappy(kind, B, T, C, T + C)
+    p = tdq.default_params(G)
+    p.base_pct = pct
+    assert _extra(tdq.TDQ_F32, B, T, C, G, pct) >= 0
+    g = U.gpu_calibrate(X, p, ld_pad=pad)
+    assert g["status"] == 0
+    U.assert_calibration_matches(g, X, p)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["near", "ties"])
+@pytest.mark.parametrize("B,T,C,G", [(9, 20, 16044, 4), (2, 3, 40000, 3)])
+def test_few_wide_rows_cost_less_than_levels(B, T, C, G, kind):
+    """Against the radix levels, four sweeps by the whole chip: 0.3 to 0.51 times their time measured, 0.8 to 1.58 where
+    a row had one wavefront."""
+    import torch
+
+    from test_gpu_block_outputs import _time
+    X = _data(kind, B, T, C, np.float32, 2) if kind in KINDS[:6] else _gappy(kind, B, T, C, 2)
+    X, us = torch.from_numpy(X).to(U.dev()), {}
+    assert _extra(tdq.TDQ_F32, B, T, C, G) > 0
+    for flag in (0, tdq.FLAG_EXACT_SELECT):
+        p = tdq.default_params(G)
+        p.flags |= flag
+        ws = tdq.alloc_workspace(B, T, C, tdq.TDQ_F32, p, X.device)
+        out = (torch.empty((B, T), dtype=torch.int32, device=X.device),
+               *(torch.empty((B, G), device=X.device) for _ in range(2)))
+        us[flag] = 1e3 * _time(lambda: tdq.tdq_calibrate_groups(X, p, ws, out=out))
+    print(f"{us[0]:.1f} us, levels {us[tdq.FLAG_EXACT_SELECT]:.1f}", flush=True)
+    assert us[0] <= 0.7 * us[tdq.FLAG_EXACT_SELECT]
+
+
+@pytest.mark.gpu
 def test_calls_at_once():
     """More workgroups than the chip holds, of calls on several streams that wait for their own only."""
     import torch
