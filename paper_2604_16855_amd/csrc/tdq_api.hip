@@ -158,14 +158,20 @@ static bool samples_rank(tdq_dtype dt, int B, int T, int C, int G, bool exact_on
 // against three (or four).
 //   * A workgroup for every 8 Ki elements, and no more than 512 in all (two per CU): [8, 121, 512] with 16 sets
 //     22.1 / 22.0 / 21.1 with 64 / 16 / 8 Ki, [16, 484, 320] 35.8 / 34.2 / 33.2.
-//   * No more than 80 Ki elements for each (all tokens may be in one set), 64 Ki with two ranks, 40 Ki with one rank and
-//     at most one workgroup to share a set: every workgroup of a set repeats the search for its tokens and its
-//     interval, so a large batch is better off with one sweep over all sets.  From 40 to 80 Ki 90 random calls are 1.085
-//     times as fast in the geometric mean, [8, 7744, 512] with 16 sets 43.7 by the chain and 42.4, [4, 8000, 1024] 46.2
-//     and 40.7, [8, 1998, 1600] 46.9 and 37.4; the slowest [3, 4724, 2144] 51.8 and 55.6, [26, 577, 2144] 45.3 and 47.9.
-//     Before, above that or so: [21, 536, 1344], 80 Ki each, 77.3 against 75.0; [28, 187, 1984], 124 Ki, 71.4 against 68.8;
-//     calibration of values on a grid, which meet in few words of LDS, [17, 5107, 131], 44 Ki, 60.8 against 46.8; but
-//     [14, 5850, 160], 29 Ki, percentile, 97.9 against 122.3.
+//   * Every workgroup of a set repeats the search for its tokens and its interval, so a large batch is better off with
+//     one sweep over all sets.  Elements for each, no more than:
+//     - 64 Ki with two ranks ([14, 5850, 160], 29 Ki, 97.9 against 122.3);
+//     - 80 Ki with one rank and three workgroups to a set on average, about where the two are even.  Calls over 7 laws
+//       of an encoder's activations (as they are, clamped, after a rectifier or a GELU), in the geometric mean 0.98 times the
+//       chain's time from 40 to 64 Ki (606 calls, 38 of them more than 5 % slower), 1.00 to 80 (205, 26), 1.02 to 96,
+//       1.03 to 128; over 19 other laws (ties, grids, gaps, constants) 0.89 to 64 Ki (824, 85), 0.88 to 80 (317, 40).  [8,
+//       7744, 512] with 16 sets, 79 Ki, 42.9 by the chain and 40.8, [4, 8000, 1024] 46.2 and 40.7; after a rectifier 1.04
+//       times the chain's time throughout, [15, 4450, 216] 30.6 and 35.3, [2, 4808, 3283] with 24 73.4 and 87.4.  Sets that
+//       miss their interval have one workgroup search their rows alone, in the chain too: 170 such calls 0.73 times the
+//       chain's time, but one set of [4, 8079, 812] 631 and 850, 31 of [3, 2506, 2922] 398 and 623;
+//     - 40 Ki with fewer to a set: one set may hold nearly all rows then.  From 40 to 80 Ki such calls are even on an
+//       encoder's laws (589 calls, 1.01), but one in seven takes 1.1 times the chain's time or more: [27, 2800, 79] with 16
+//       sets, two beyond one each, 35.3 by the chain and 49.0, [27, 166, 1095] 26.8 and 36.1.
 //   * One rank only (two save a whole sweep): fewer than 64 workgroups beyond the first for a set, which all meet in
 //     the same words ([3, 2125, 1669] with one set, 169, 39.0 against 33.6, [2, 5545, 419] with two 36.8 against
 //     30.3; with 32 to 64 of them 41 calls of 8 Ki elements each 1.22 times as fast, 36 of more 1.04); at least a
@@ -225,7 +231,7 @@ static int whole_extra(tdq_dtype dt, int B, int T, int C, int G, bool two_ranks)
     if (G <= 2 && T > 4096 && e > 16384 * (extra + 1)) return -1;
   }
   if (two_ranks && extra > 0 && bracket_bins(G) < 1024) return -1;
-  if (e > (two_ranks ? 65536 : extra > 1 ? 81920 : 40960) * (extra + 1)) return -1;
+  if (e > (two_ranks ? 65536 : extra >= 2 * G ? 81920 : 40960) * (extra + 1)) return -1;
   return (int)extra;
 }
 

@@ -32,6 +32,10 @@ def _extra(dt, B, T, C, G, pct=0.0):
     (tdq.TDQ_F16, 16, 57, 5470, 4, 0.99, 28), (tdq.TDQ_F16, 1, 57, 5470, 4, 0.0, 38),
     (tdq.TDQ_F16, 58, 6152, 21, 1, 0.0, 7), (tdq.TDQ_F16, 58, 6152, 22, 1, 0.0, -1),       # many tokens in one set
     (tdq.TDQ_F16, 58, 4096, 44, 1, 0.0, 7), (tdq.TDQ_F16, 58, 6152, 44, 1, 0.99, 7),
+    (tdq.TDQ_F16, 11, 1000, 1500, 15, 0.0, 31), (tdq.TDQ_F16, 11, 1000, 1500, 16, 0.0, -1),  # three to a set, fewer
+    (tdq.TDQ_F16, 11, 1024, 1240, 16, 0.0, 30), (tdq.TDQ_F16, 11, 1024, 1241, 16, 0.0, -1),
+    (tdq.TDQ_F16, 8, 7840, 512, 16, 0.0, 48), (tdq.TDQ_F16, 8, 7841, 512, 16, 0.0, -1),
+    (tdq.TDQ_F16, 27, 2800, 79, 16, 0.0, -1), (tdq.TDQ_F16, 27, 166, 1095, 16, 0.0, -1),
 ])
 def test_rule(dt, B, T, C, G, pct, extra):
     assert _extra(dt, B, T, C, G, pct) == extra
