@@ -182,8 +182,10 @@ static bool samples_rank(tdq_dtype dt, int B, int T, int C, int G, bool exact_on
 //     44.7); an image that is one set by itself 40 Ki ([2, 576, 74], 42 Ki, 45.0 against 34.1).
 //     Beyond that and with one rank and 2 to 32 sets (256 bins and 256 keys of a set have room then), several share a
 //     set and wait for each other, each keeping its CU's slot meanwhile:
-//     - no more than 64 Ki elements for each of as many as the chip holds, and 256 of them to an image (they all meet in
-//       a set's words);
+//     - no more than 64 Ki elements for each of as many as the chip holds, and 256 of them to an image;
+//     - no more than 64 beyond the first for a set, which all meet in the same words and each read all of its tokens' ranges:
+//       with two sets and up to 256, 128 of them, and by the chain [2, 6434, 487] 122 / 72 / 88, [2, 2170, 1624] 79 / 52 / 61,
+//       [3, 2342, 1165] on a grid 96 / 83 / 85, [1, 3828, 2193] 92 / 97 / 90;
 //     - of the chip's slots (two per CU) a sixteenth stays free, for kernels of calls on other streams: [8, 1024, 768]
 //       with 16 sets on one and on eight streams, us a call, by the chain 46.8 / 21.5, by 512 workgroups 34.3 / 28.7, by
 //       480 34.8 / 25.3, by 384 37.9 / 22.6; [4, 4096, 768] 90.4 / 46.8, 55.4 / 50.8, 53.3 / 47.6;
@@ -192,11 +194,12 @@ static bool samples_rank(tdq_dtype dt, int B, int T, int C, int G, bool exact_on
 //       one set may hold nearly all rows.  [15, 5890, 87] with 24 sets 60.7 by the chain and 72.6, [23, 296, 1169] with
 //       16 60.7 / 73.0, with ties [15, 2780, 292] 68.3 / 88.5.
 //     Calibration by the chain (by levels from 1 Mi elements on) and so: [2, 484, 320] with 8 sets 33.4 / 20.8, [24, 300,
-//     300] with 16 41.7 / 29.3, [16, 1024, 1024] 103 / 65.  760 random calls over 19 laws of data (Laplace, rectified, masked,
-//     clamped, with ties, on a grid, constant, ...), T from 2, C up to 256 Ki: 1.63 times as fast in the geometric mean, seven
-//     more than 5 % slower: with two or three sets, where a second round reads many rows again, [4, 650, 1367] 49.0 / 69.7 (two
-//     groups of values), [2, 833, 6676] 83.5 / 119, [10, 376, 2366] 56.2 / 66.7; one value [17, 61, 4268] 66.5 / 80.4;
-//     three by 6 to 8 %.  And of 40 calls of one image and many tokens [1, 8192, 1024] with 8 sets 74 / 97, with 16 76.6 / 80.6.
+//     300] with 16 41.7 / 29.3, [16, 1024, 1024] 103 / 65, [1, 8192, 1024] with 8 72.8 / 60.  Over an encoder's laws 800
+//     calls take 0.62 times the chain's time, over 19 laws of data (Laplace, rectified, masked, clamped, with ties, on a
+//     grid, constant, ...; T from 2, C up to 256 Ki) 760 calls 0.61.  More than 5 % slower are, of 710 calls of two to four
+//     sets, where a second round reads many rows again, 19: values on a grid [7, 905, 864] with two 47.8 / 61.4, [3, 3676,
+//     356] with three 68 / 90; two groups of values [6, 179, 3932] with three 45.7 / 52.5; 19 % zeros [2, 440, 2208] with two
+//     40 / 46; of the calls of more sets those of one value, [17, 61, 4268] 66.5 / 80.4.
 //   * Up to 1536 sets in all, which take two turns on the chip: [49, 74, 832] with 32 sets (1568) 31.0 against 29.8,
 //     [58, 20, 9] with 32 42.8 against 36.6, [64, 322, 56] with 64 55.7 against 45.6; of 94 calls of 1024 to 1536 sets
 //     none is slower, half are faster than 1.27 times.  binary32, whose kernel needs more registers: up to 1024, 512
@@ -217,6 +220,7 @@ static int whole_extra(tdq_dtype dt, int B, int T, int C, int G, bool two_ranks)
     if (extra > 256) extra = 256;
     if (e > 65536 * (extra + 1)) return -1;
     if (extra > 480 / B - G) extra = 480 / B - G;
+    if (extra > 64 * G) extra = 64 * G;
     if (extra <= 0) return -1;
     if (extra < 2 * G && e > 24576 * (extra + 1) && T >= 128 && sampled_f32(T, C, G)) return -1;
     return (int)extra;

@@ -16,7 +16,8 @@ from test_gpu_whole import _data, _extra
     (24, 300, 300, 16, 0.0, 4), (25, 300, 300, 16, 0.0, 3), (26, 300, 300, 16, 0.0, -1),        # few to a set
     (28, 127, 900, 16, 0.0, 1), (28, 128, 900, 16, 0.0, -1), (30, 100, 900, 16, 0.0, -1),      # a slot in 16 left
     (16, 1024, 1024, 16, 0.0, 14), (16, 1023, 1024, 16, 0.0, -1), (8, 1024, 1024, 16, 0.0, 44), # by levels, by the chain
- (2, 512, 512, 1, 0.0, -1), (2, 512, 512, 2, 0.0, 32),
+    (2, 2170, 1624, 2, 0.0, 128), (2, 2170, 1624, 3, 0.0, 192), (2, 2170, 1624, 4, 0.0, 236),       # 64 more to a set
+    (1, 8192, 2056, 2, 0.0, 128), (1, 8192, 2057, 2, 0.0, -1), (2, 512, 512, 1, 0.0, -1), (2, 512, 512, 2, 0.0, 32),
     (2, 512, 512, 32, 0.0, 32), (2, 512, 512, 33, 0.0, -1), (2, 512, 512, 16, 0.99, -1)])
 def test_rule(B, T, C, G, pct, extra):
     assert _extra(tdq.TDQ_F32, B, T, C, G, pct) == extra
