@@ -196,8 +196,8 @@ static bool samples_rank(tdq_dtype dt, int B, int T, int C, int G, bool exact_on
 //     Calibration by the chain (by levels from 1 Mi elements on) and so: [2, 484, 320] with 8 sets 33.4 / 20.8, [24, 300,
 //     300] with 16 41.7 / 29.3, [16, 1024, 1024] 103 / 65, [1, 8192, 1024] with 8 72.8 / 60.  Over an encoder's laws 800
 //     calls take 0.62 times the chain's time, over 19 laws of data (Laplace, rectified, masked, clamped, with ties, on a
-//     grid, constant, ...; T from 2, C up to 256 Ki) 760 calls 0.61.  More than 5 % slower are, of 710 calls of two to four
-//     sets, where a second round reads many rows again, 19: values on a grid [7, 905, 864] with two 47.8 / 61.4, [3, 3676,
+//     grid, constant, ...; T from 2, C up to 256 Ki) 760 calls 0.61.  More than 5 % slower are, of 716 calls of two to four
+//     sets, where a second round reads many rows again, 18: values on a grid [7, 905, 864] with two 47.8 / 61.4, [3, 3676,
 //     356] with three 68 / 90; two groups of values [6, 179, 3932] with three 45.7 / 52.5; 19 % zeros [2, 440, 2208] with two
 //     40 / 46; of the calls of more sets those of one value, [17, 61, 4268] 66.5 / 80.4.
 //   * Up to 1536 sets in all, which take two turns on the chip: [49, 74, 832] with 32 sets (1568) 31.0 against 29.8,
@@ -239,7 +239,8 @@ static int whole_extra(tdq_dtype dt, int B, int T, int C, int G, bool two_ranks)
   return (int)extra;
 }
 
-// (not part of the ABI: the tests ask which route their images take)
+// (not part of the ABI: the tests ask whether the chain of kernels samples their images or takes the radix levels; images
+// for which tdq_whole_extra is not -1 take neither)
 extern "C" int tdq_samples_rank(int32_t dt, int32_t B, int32_t T, int32_t C, int32_t G) {
   return samples_rank(static_cast<tdq_dtype>(dt), B, T, C, G, false) ? 1 : 0;
 }

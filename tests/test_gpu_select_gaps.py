@@ -60,10 +60,14 @@ def test_interval_reaches_the_rank(kind, G):
 
 
 @pytest.mark.parametrize("kind", KINDS + EDGES + ("tie", "floor"))
-@pytest.mark.parametrize("T,C,G", [(1024, 768, 16), (1024, 768, 1), (700, 1496, 5), (600, 1040, 32), (400, 512, 64)])
-def test_bins_hold_little(kind, T, C, G):
-    """binary32: a bin never holds more keys than are collected, whatever the gaps and ties, and
-    the interval reaches the rank."""
+@pytest.mark.parametrize("T,C,G,whole", [
+    (1024, 768, 16, True), (1024, 768, 1, False), (700, 1496, 5, True), (600, 1040, 32, True), (400, 512, 64, False),
+    (8200, 96, 16, False), (9000, 116, 5, False), (8300, 75, 32, False)])
+def test_bins_hold_little(T, C, G, whole, kind):
+    """binary32: the interval reaches the rank, whatever the gaps and ties, and in the chain of kernels a bin never holds
+    more keys than are collected (the workgroups of the one kernel go another round, which is not counted)."""
+    assert (tdq.lib().tdq_whole_extra(tdq.TDQ_F32, 1, T, C, G, tdq.C.c_double(0.0)) >= 0) == whole
+    assert whole or tdq.lib().tdq_samples_rank(tdq.TDQ_F32, 1, T, C, G)
     assert _check(_data(kind, 1, T, C, np.float32, 7), G) == 0
 
 

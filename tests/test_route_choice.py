@@ -1,5 +1,5 @@
-"""Which images take the radix levels because their sets are many and small, or have more tokens to
-look at than elements; the rule itself needs no GPU."""
+"""Which images that the one kernel after the statistics does not take (tdq_whole_extra) go by the radix levels because
+their sets are many and small, or have more tokens to look at than elements; the rule itself needs no GPU."""
 import numpy as np
 import pytest
 
