@@ -576,8 +576,10 @@ __device__ __forceinline__ Lost lost_rank(u32 k, u32 n, u32 below, u32 inside, u
   return l;
 }
 
-template <typename TX, int NT, int RD, int SM, int WHOLE>
-__global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8 ? 6 : 1)) void k_sets(
+// MEET: binary32 sets that several workgroups share.  (A kernel of its own: the sets of one workgroup each, calls of 13 to 40 us,
+// lost 0.3 to 1.4 us to the code and the registers, 126 instead of 84, of a way that they never take.)
+template <typename TX, int NT, int RD, int SM, int WHOLE, bool MEET = false>
+__global__ __launch_bounds__(NT, (MEET ? 4 : WHOLE == 1 && sizeof(TX) == 2 && RD <= 8 ? 6 : 1)) void k_sets(
     const TX* __restrict__ X, long long ld, int T, int C, int G, int Wfew, int W, int cells, int aligned,
     const float* __restrict__ r, const double* __restrict__ mean, const double* __restrict__ m2,
     int* __restrict__ gid, Scalars sc, int pass, int keep_base, GroupWork* __restrict__ grp,
@@ -611,7 +613,7 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
   __shared__ Lost s_lost[2];
   __shared__ FinishLds<WHOLE ? NT : 64, true> s_search;
   __shared__ unsigned s_known;                       // of known_to_all alone
-  __shared__ unsigned short s_parts[WHOLE == 1 && !F16 ? NT + 1 : 1];     // shares of the set's rows claimed by this workgroup
+  __shared__ unsigned short s_parts[MEET ? NT + 1 : 1];     // shares of the set's rows claimed by this workgroup
   // (whole: the set, and which of the S workgroups that share it this is, follow from the sets' sizes)
   int S = 1, part = 0, j = (int)blockIdx.x;
   const int b = blockIdx.y;
@@ -709,10 +711,10 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
     const unsigned long long later = __ballot(incl > at);
     if (__builtin_expect(later == 0, 0)) return;     // the same for every thread
     j = __ffsll((long long)later) - 1;
-    S = __builtin_amdgcn_readlane((int)its, j);
-    part = (int)at - (__builtin_amdgcn_readlane((int)incl, j) - S);
+    S = F16 || MEET ? __builtin_amdgcn_readlane((int)its, j) : 1;
+    part = !F16 && !MEET ? 0 : (int)at - (__builtin_amdgcn_readlane((int)incl, j) - S);
     // (binary32; there is time until it is looked at)
-    if (WHOLE == 1 && !F16 && S > 1 && tid == 0)
+    if (MEET && S > 1 && tid == 0)
       s_parts[0] = (unsigned short)min(atomicAdd(&wa.ctl[(size_t)(b * G + j) * kSetCtl + kCtlClaimed], 1u), 0xFFFFu);
   }
   const u32 start = start_of(j), end = start_of(j + 1);
@@ -805,7 +807,7 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
     }
   }
   __syncthreads();
-  if constexpr (WHOLE == 1 && !F16) {
+  if constexpr (MEET) {
     if (S > 1 && (int)s_parts[0] >= S) return;       // nothing of the set is left (the same for every thread)
   }
 
@@ -852,7 +854,7 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
 
   // (of workgroups that share a binary32 set the first to claim a share projects, or does everything alone)
   bool sums = true;
-  if constexpr (WHOLE == 1 && !F16) sums = S == 1 || s_parts[0] == 0;
+  if constexpr (MEET) sums = S == 1 || s_parts[0] == 0;
   // Moments of the set about the mean of its first token (zero if that is not finite: the
   // image's results are then undefined anyway and its flag is raised).
   const int first_token = listed ? order[0] : s_first;
@@ -990,7 +992,7 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
         find_ranks<NT, 2, kCopies, false>(hs, rs, stot, s_bin, s_before, nullptr);
       __syncthreads();
       const u32 b0 = s_bin[0], b1 = s_bin[1];
-      if (WHOLE == 1 && S > 1) {
+      if (MEET && S > 1) {
         // whole sixteenths of an octave, unless they hold far more than is wanted
         const u32 held = s_before[1] + shist[b1] - s_before[0];
         if (held <= 3u * drawn) {                      // the same for every thread
@@ -1444,10 +1446,12 @@ __global__ __launch_bounds__(NT, (WHOLE != 1 ? 1 : sizeof(TX) == 4 ? 4 : RD <= 8
         }
         u32 first, last, drawn, shift = 0, below = 0;
         interval32(sample_rank(kq, nn, m, n_sel), first, last, drawn);
-        if (NR == 1 && S > 1) {
-          const auto what = shared_rank(kq, first, last);
-          if (what != kAlone) return what == kProject;
-          if (tid == 0) wa.ctl[(size_t)idx * kSetCtl + kCtlAlone] = 1u;
+        if constexpr (MEET) {
+          if (S > 1) {
+            const auto what = shared_rank(kq, first, last);
+            if (what != kAlone) return what == kProject;
+            if (tid == 0) wa.ctl[(size_t)idx * kSetCtl + kCtlAlone] = 1u;
+          }
         }
         shift = last < (u32)kBins ? 0u : (u32)(__clz(kBins) - __clz(last) + 1);         // bins of 2^shift keys
         for (int i = tid; i < kBins; i += NT) hist[0][i] = 0;
@@ -1674,7 +1678,7 @@ hipError_t launch_sets(const void* X, tdq_dtype dt, int B, int T, int C, long lo
   return hipGetLastError();
 }
 
-template <typename TX, int WHOLE>
+template <typename TX, int WHOLE, bool MEET = false>
 static void sets_whole_t(const TX* X, int B, int T, int C, long long ld, int G, int extra, int Wfew, int W,
                          const float* r, const double* mean, const double* m2, int* gid, const Scalars& sc,
                          unsigned* bhist, void* ctl, unsigned* img_flag, unsigned* status, float* clip,
@@ -1698,7 +1702,7 @@ static void sets_whole_t(const TX* X, int B, int T, int C, long long ld, int G, 
   wa.waits = waits;
   const size_t order_bytes = ((size_t)T * sizeof(unsigned short) + 15) & ~(size_t)15;
 #define TDQ_WHOLE_RD(RD, SM)                                                                            \
-  hipLaunchKernelGGL((k_sets<TX, 512, RD, SM, WHOLE>), dim3(G + extra, B), dim3(512), order_bytes, st, X, ld, T, \
+  hipLaunchKernelGGL((k_sets<TX, 512, RD, SM, WHOLE, MEET>), dim3(G + extra, B), dim3(512), order_bytes, st, X, ld, T, \
                      C, G, Wfew, W, 0, aligned, r, mean, m2, gid, sc, kPassZr, 0, nullptr, nullptr, bhist, nullptr, \
                      0, img_flag, status, wa)
 #define TDQ_WHOLE(SM)                                                            \
@@ -1722,13 +1726,15 @@ hipError_t launch_sets_whole(const void* X, tdq_dtype dt, int B, int T, int C, l
                              int* gid, const Scalars& sc, unsigned* bhist, void* ctl, unsigned* img_flag,
                              unsigned* status, float* clip, float* scale, tdq_group_stats* stats,
                              const Waits& waits, hipStream_t st) {
-#define TDQ_SW(TX, NR)                                                                                       \
-  sets_whole_t<TX, NR>(static_cast<const TX*>(X), B, T, C, ld, G, extra, Wfew, W, r, mean, m2, gid, sc, bhist, \
+#define TDQ_SW(TX, ...)                                                                                      \
+  sets_whole_t<TX, __VA_ARGS__>(static_cast<const TX*>(X), B, T, C, ld, G, extra, Wfew, W, r, mean, m2, gid, sc, bhist, \
                        ctl, img_flag, status, clip, scale, stats, waits, st)
   if (dt == TDQ_F16) {
     if (ranks == 1) TDQ_SW(u16, 1); else TDQ_SW(u16, 2);
   } else {
-    if (ranks == 1) TDQ_SW(float, 1); else TDQ_SW(float, 2);
+    if (ranks == 2) TDQ_SW(float, 2);
+    else if (extra > 0) TDQ_SW(float, 1, true);
+    else TDQ_SW(float, 1);
   }
 #undef TDQ_SW
   return hipGetLastError();
