@@ -153,90 +153,99 @@ static bool samples_rank(tdq_dtype dt, int B, int T, int C, int G, bool exact_on
   return !exact_only && !many_small_sets(B, T, C, G) && (dt == TDQ_F16 || sampled_f32(T, C, G));
 }
 
-// Whether the sampled route takes one kernel for assignment and rank select together, and if so with how many
-// workgroups per image beyond one per set (-1 = no).  Figures are us per layer or calibration, one kernel
-// against three (or four).
-//   * A workgroup for every 8 Ki elements, and no more than 512 in all (two per CU): [8, 121, 512] with 16 sets
-//     22.1 / 22.0 / 21.1 with 64 / 16 / 8 Ki, [16, 484, 320] 35.8 / 34.2 / 33.2.
-//   * Every workgroup of a set repeats the search for its tokens and its interval, so a large batch is better off with
-//     one sweep over all sets.  Elements for each, no more than:
-//     - 64 Ki with two ranks ([14, 5850, 160], 29 Ki, 97.9 against 122.3);
-//     - 80 Ki with one rank and three workgroups to a set on average, about where the two are even.  Calls over 7 laws
-//       of an encoder's activations (as they are, clamped, after a rectifier or a GELU), in the geometric mean 0.98 times the
-//       chain's time from 40 to 64 Ki (606 calls, 38 of them more than 5 % slower), 1.00 to 80 (205, 26), 1.02 to 96,
-//       1.03 to 128; over 19 other laws (ties, grids, gaps, constants) 0.89 to 64 Ki (824, 85), 0.88 to 80 (317, 40).  [8,
-//       7744, 512] with 16 sets, 79 Ki, 42.9 by the chain and 40.8, [4, 8000, 1024] 46.2 and 40.7; after a rectifier 1.04
-//       times the chain's time throughout, [15, 4450, 216] 30.6 and 35.3, [2, 4808, 3283] with 24 73.4 and 87.4.  Sets that
-//       miss their interval have one workgroup search their rows alone, in the chain too: 170 such calls 0.73 times the
-//       chain's time, but one set of [4, 8079, 812] 631 and 850, 31 of [3, 2506, 2922] 398 and 623;
-//     - 40 Ki with fewer to a set: one set may hold nearly all rows then.  From 40 to 80 Ki such calls are even on an
-//       encoder's laws (589 calls, 1.01), but one in seven takes 1.1 times the chain's time or more: [27, 2800, 79] with 16
-//       sets, two beyond one each, 35.3 by the chain and 49.0, [27, 166, 1095] 26.8 and 36.1.
-//   * One rank only (two save a whole sweep): fewer than 64 workgroups beyond the first for a set, which all meet in
-//     the same words ([3, 2125, 1669] with one set, 169, 39.0 against 33.6, [2, 5545, 419] with two 36.8 against
-//     30.3; with 32 to 64 of them 41 calls of 8 Ki elements each 1.22 times as fast, 36 of more 1.04); at least a
-//     quarter of the rows that a workgroup's lanes take at a time, where it has more than 8 Ki elements ([2, 457, 6172]
-//     with 16 sets, two rows for eight wavefronts, 43.8 against 39.5); and with one or two sets of more than 4096
-//     tokens, each read by every workgroup, no more than 16 Ki elements ([58, 6152, 44] 52.7 against 47.8).
-//   * binary32, up to 56 Ki elements: one workgroup sees all of a set ([2, 1400, 32], 45 Ki elements, 38.6 against
-//     44.7); an image that is one set by itself 40 Ki ([2, 576, 74], 42 Ki, 45.0 against 34.1).
-//     Beyond that and with one rank and 2 to 32 sets (256 bins and 256 keys of a set have room then), several share a
-//     set and wait for each other, each keeping its CU's slot meanwhile:
-//     - no more than 64 Ki elements for each of as many as the chip holds, and 256 of them to an image;
-//     - no more than 64 beyond the first for a set, which all meet in the same words and each read all of its tokens' ranges:
-//       with two sets and up to 256, 128 of them, and by the chain [2, 6434, 487] 122 / 72 / 88, [2, 2170, 1624] 79 / 52 / 61,
-//       [3, 2342, 1165] on a grid 96 / 83 / 85, [1, 3828, 2193] 92 / 97 / 90;
-//     - of the chip's slots (two per CU) a sixteenth stays free, for kernels of calls on other streams: [8, 1024, 768]
-//       with 16 sets on one and on eight streams, us a call, by the chain 46.8 / 21.5, by 512 workgroups 34.3 / 28.7, by
-//       480 34.8 / 25.3, by 384 37.9 / 22.6; [4, 4096, 768] 90.4 / 46.8, 55.4 / 50.8, 53.3 / 47.6;
-//     - an image that the chain samples and that has few workgroups to a set (fewer than three on average) gives each no
-//       more than 24 Ki elements, if it has 128 tokens or more: the chain's sweeps run at the chip's bandwidth then, while
-//       one set may hold nearly all rows.  [15, 5890, 87] with 24 sets 60.7 by the chain and 72.6, [23, 296, 1169] with
-//       16 60.7 / 73.0, with ties [15, 2780, 292] 68.3 / 88.5.
-//     Calibration by the chain (by levels from 1 Mi elements on) and so: [2, 484, 320] with 8 sets 33.4 / 20.8, [24, 300,
-//     300] with 16 41.7 / 29.3, [16, 1024, 1024] 103 / 65, [1, 8192, 1024] with 8 72.8 / 60.  Over an encoder's laws 800
-//     calls take 0.62 times the chain's time, over 19 laws of data (Laplace, rectified, masked, clamped, with ties, on a
-//     grid, constant, ...; T from 2, C up to 256 Ki) 760 calls 0.61.  More than 5 % slower are, of 716 calls of two to four
-//     sets, where a second round reads many rows again, 18: values on a grid [7, 905, 864] with two 47.8 / 61.4, [3, 3676,
-//     356] with three 68 / 90; two groups of values [6, 179, 3932] with three 45.7 / 52.5; 19 % zeros [2, 440, 2208] with two
-//     40 / 46; of the calls of more sets those of one value, [17, 61, 4268] 66.5 / 80.4.
-//   * Up to 1536 sets in all, which take two turns on the chip: [49, 74, 832] with 32 sets (1568) 31.0 against 29.8,
-//     [58, 20, 9] with 32 42.8 against 36.6, [64, 322, 56] with 64 55.7 against 45.6; of 94 calls of 1024 to 1536 sets
-//     none is slower, half are faster than 1.27 times.  binary32, whose kernel needs more registers: up to 1024, 512
-//     with two ranks ([42, 3, 2424] with 32, 1344 sets, 48.2 against 41.9; percentile [52, 25, 8] with 16, 832 sets,
-//     72.4 against 60.4, [120, 13, 3821] with 5, 600 sets, 137 against 117; but [292, 187, 8] with 2, 584, 43.0
-//     against 79.8).
-//   * Two ranks share the set's words of the workspace if several workgroups meet in them: 512 bins each are
-//     the least.
-static int whole_extra(tdq_dtype dt, int B, int T, int C, int G, bool two_ranks) {
+// Whether one kernel does assignment and rank select together (k_sets with WHOLE), and if so with how many workgroups per
+// image beyond one per set (-1 = no).  Every limit has its reason beside it.  Figures are us of one calibration (binary16
+// with few elements: of the layer), in the order that the text names; "the chain" is what takes the call otherwise, three or
+// four kernels after the statistics, five with binary32, ten with the radix levels.
+
+// binary16: a workgroup counts its share of a set's rows and leaves, the last to arrive picks.
+static int whole_extra_f16(int B, int T, int C, int G, bool two_ranks) {
   const long long e = (long long)T * C;
-  const long long sets = (long long)B * G;
-  if (T > kWholeTokens || sets > (dt == TDQ_F16 ? 1536 : two_ranks ? 512 : 1024)) return -1;
-  if (dt == TDQ_F32) {
-    if (e <= (G == 1 ? 40960 : 57344)) return 0;
-    if (two_ranks || G == 1 || G > 32) return -1;
-    long long extra = e / 8192;
-    if (extra > 512 / B - G) extra = 512 / B - G;
-    if (extra > 256) extra = 256;
-    if (e > 65536 * (extra + 1)) return -1;
-    if (extra > 480 / B - G) extra = 480 / B - G;
-    if (extra > 64 * G) extra = 64 * G;
-    if (extra <= 0) return -1;
-    if (extra < 2 * G && e > 24576 * (extra + 1) && T >= 128 && sampled_f32(T, C, G)) return -1;
-    return (int)extra;
-  }
+  // Three workgroups fit a CU, so these take two turns on the chip at most.  One kernel and chain: [49, 74, 832] with 32
+  // sets (1568) 31.0 / 29.8, [58, 20, 9] with 32 42.8 / 36.6, [64, 322, 56] with 64 55.7 / 45.6; of 94 calls of 1024 to
+  // 1536 sets none is slower.
+  if ((long long)B * G > 1536) return -1;
+  // One for every 8 Ki elements, 512 in all (two per CU): with one for 64 / 16 / 8 Ki [8, 121, 512] with 16 sets
+  // 22.1 / 22.0 / 21.1, [16, 484, 320] 35.8 / 34.2 / 33.2.
   long long extra = e / 8192;
   const long long most = 512 / B - G;
   if (extra > most) extra = most > 0 ? most : 0;
-  if (!two_ranks) {
-    const int slots = 512 / sweep_lanes_per_row(C, 8);       // rows that a workgroup's lanes take at a time
+  // Every workgroup of a set repeats the search for its tokens and its interval, so a large batch is better off with one
+  // sweep over all sets.  Elements for each, no more than this.
+  long long share;
+  if (two_ranks) {
+    // Two ranks share the set's words of the workspace if several meet in them: 512 bins each are the least.
+    if (extra > 0 && bracket_bins(G) < 1024) return -1;
+    share = 65536;                                     // (two sweeps by the chain; [14, 5850, 160], 29 Ki, 97.9 / 122.3)
+  } else {
+    // Fewer than 64 beyond the first for a set, which all meet in the same words: [3, 2125, 1669] with one set, 169 of
+    // them, 39.0 / 33.6, [2, 5545, 419] with two 36.8 / 30.3; with 32 to 64 of them 41 calls 1.22 times as fast.
     if (extra >= 64 * G) return -1;
+    // More than 8 Ki each: at least a quarter of the rows that its lanes take at a time ([2, 457, 6172] with 16 sets, two
+    // rows for eight wavefronts, 43.8 / 39.5).
+    const int slots = 512 / sweep_lanes_per_row(C, 8);
     if (e > 8192 * (extra + 1) && 4ll * T < slots * (extra + 1)) return -1;
+    // One or two sets of many tokens, each read by every workgroup: 16 Ki ([58, 6152, 44] 52.7 / 47.8).
     if (G <= 2 && T > 4096 && e > 16384 * (extra + 1)) return -1;
+    // With three to a set on average 80 Ki, about where the two are even.  Calls over 7 laws of an encoder's activations
+    // (as they are, clamped, after a rectifier or a GELU), in the geometric mean 0.98 times the chain's time from 40 to 64 Ki
+    // (606 calls, 38 of them more than 5 % slower), 1.00 to 80 (205, 26), 1.02 to 96, 1.03 to 128; over 19 other laws (ties,
+    // grids, gaps, constants) 0.89 to 64 Ki (824, 85), 0.88 to 80 (317, 40).  [8, 7744, 512] with 16 sets, 79 Ki, 40.8 / 42.9,
+    // [4, 8000, 1024] 40.7 / 46.2; after a rectifier 1.04 times the chain's time throughout, [15, 4450, 216] 35.3 / 30.6, [2,
+    // 4808, 3283] with 24 87.4 / 73.4.  Sets that miss their interval have one workgroup search their rows alone, in the
+    // chain too: 170 such calls 0.73, but one set of [4, 8079, 812] 850 / 631, 31 of [3, 2506, 2922] 623 / 398.
+    // With fewer one set may hold nearly all rows: 40 Ki.  From there to 80 Ki such calls are even on an encoder's laws (589
+    // calls, 1.01), but one in seven takes 1.1 times the chain's time or more: [27, 2800, 79] with 16 sets, two beyond one
+    // each, 49.0 / 35.3, [27, 166, 1095] 36.1 / 26.8.
+    share = extra >= 2 * G ? 81920 : 40960;
   }
-  if (two_ranks && extra > 0 && bracket_bins(G) < 1024) return -1;
-  if (e > (two_ranks ? 65536 : extra >= 2 * G ? 81920 : 40960) * (extra + 1)) return -1;
+  return e <= share * (extra + 1) ? (int)extra : -1;
+}
+
+// binary32: one workgroup to a set, or several that wait for each other.
+static int whole_extra_f32(int B, int T, int C, int G, bool two_ranks) {
+  const long long e = (long long)T * C;
+  // Two turns on the chip, as above, but two workgroups a CU, and with two ranks one: [42, 3, 2424] with 32 sets (1344)
+  // 48.2 / 41.9; percentile [52, 25, 8] with 16 (832) 72.4 / 60.4, [120, 13, 3821] with 5 (600) 137 / 117, but [292, 187,
+  // 8] with 2 (584) 43.0 / 79.8.
+  if ((long long)B * G > (two_ranks ? 512 : 1024)) return -1;
+  // One workgroup sees all of a set ([2, 1400, 32], 45 Ki elements, 38.6 / 44.7); an image that is one set by itself 40 Ki
+  // ([2, 576, 74], 42 Ki, 45.0 / 34.1).
+  if (e <= (G == 1 ? 40960 : 57344)) return 0;
+  // Beyond that several share a set: with one rank, and 2 to 32 sets (256 bins and 256 keys of a set have room then).  Each
+  // keeps its slot of a CU while it waits.  [2, 484, 320] with 8 sets 20.8 / 33.4, [24, 300, 300] with 16 29.3 / 41.7, [16,
+  // 1024, 1024] 65 / 103, [1, 8192, 1024] with 8 60 / 73.  Over an encoder's laws 800 calls take 0.62 times the chain's time,
+  // over 19 laws of data (Laplace, rectified, masked, clamped, with ties, on a grid, constant, ...; T from 2, C up to 256 Ki)
+  // 760 calls 0.61.  More than 5 % slower are, of 716 calls of two to four sets, where a second round reads many rows again,
+  // 18: values on a grid [7, 905, 864] with two 61.4 / 47.8, [3, 3676, 356] with three 90 / 68; two groups of values [6, 179,
+  // 3932] with three 52.5 / 45.7; 19 % zeros [2, 440, 2208] with two 46 / 40; of the calls of more sets those of one
+  // value, [17, 61, 4268] 80.4 / 66.5.
+  if (two_ranks || G == 1 || G > 32) return -1;
+  // One for every 8 Ki elements, of as many as the chip holds 64 Ki for each, 256 of them to an image ([1, 8192, 1024] with 8
+  // sets 97 with 496 of them, 74 with 240).
+  long long extra = e / 8192;
+  if (extra > 512 / B - G) extra = 512 / B - G;
+  if (extra > 256) extra = 256;
+  if (e > 65536 * (extra + 1)) return -1;
+  // A sixteenth of the slots stays free, for kernels of calls on other streams: [8, 1024, 768] with 16 sets on one and on
+  // eight streams, a call, by the chain 46.8 and 21.5, by 512 workgroups 34.3 and 28.7, by 480 34.8 and 25.3, by 384 37.9
+  // and 22.6; [4, 4096, 768] 90.4 and 46.8, 55.4 and 50.8, 53.3 and 47.6.
+  if (extra > 480 / B - G) extra = 480 / B - G;
+  // No more than 64 beyond the first for a set, which all meet in the same words and each read all of its tokens' ranges: with
+  // two sets and up to 256, 128 of them, and by the chain [2, 6434, 487] 122 / 72 / 88, [2, 2170, 1624] 79 / 52 / 61, [3,
+  // 2342, 1165] on a grid 96 / 83 / 85, [1, 3828, 2193] 92 / 97 / 90.
+  if (extra > 64 * G) extra = 64 * G;
+  if (extra <= 0) return -1;
+  // An image that the chain samples and that has fewer than three workgroups to a set on average: no more than 24 Ki for
+  // each, if it has 128 tokens or more.  The chain's sweeps run at the chip's bandwidth then, while one set may hold nearly
+  // all rows: [15, 5890, 87] with 24 sets 72.6 / 60.7, [23, 296, 1169] with 16 73.0 / 60.7, with ties [15, 2780, 292] 88.5 / 68.3.
+  if (extra < 2 * G && e > 24576 * (extra + 1) && T >= 128 && sampled_f32(T, C, G)) return -1;
   return (int)extra;
+}
+
+static int whole_extra(tdq_dtype dt, int B, int T, int C, int G, bool two_ranks) {
+  if (T > kWholeTokens) return -1;                     // (the list of its tokens is in LDS)
+  return dt == TDQ_F16 ? whole_extra_f16(B, T, C, G, two_ranks) : whole_extra_f32(B, T, C, G, two_ranks);
 }
 
 // (not part of the ABI: the tests ask whether the chain of kernels samples their images or takes the radix levels; images
