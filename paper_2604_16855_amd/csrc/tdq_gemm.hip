@@ -109,13 +109,22 @@ __device__ __forceinline__ void store_out_vec<_Float16>(_Float16* p, const float
   __builtin_nontemporal_store(v, reinterpret_cast<h8v*>(p));
 }
 
+// STREAM: past the caches, as nothing reads it here again.
+template <bool STREAM, typename V>
+__device__ __forceinline__ void store_as(V v, V* p) {
+  if constexpr (STREAM)
+    __builtin_nontemporal_store(v, p);
+  else
+    *p = v;
+}
+
 // The first `rows` of 32 rows and `cols` of 64 columns of results, staged in LDS by the wavefront, to rows that
 // need not start or end on 16-byte boundaries: neighbouring lanes take neighbouring outputs, with few columns of
 // several rows, so that an instruction writes runs of lines, and whole groups of rows without a branch per row.
 // (A run of outputs per lane instead, stored one by one, leaves every line in pieces to several instructions:
 // 124818 x 32 x 803 by k_w4a4_gemm_blocks, binary16, 877 us, 75 so; 32768 x 1024 x 4095 by k_w4a4_gemm_blocks_f6
 // 913 and 285.  A branch per row, as `rows` may end anywhere, 94 and 286, and 8.7 instead of 7.1 at 71 x 78 x 882.)
-template <typename OUT, typename GET>
+template <bool STREAM, typename OUT, typename GET>
 __device__ __forceinline__ void store_rows(OUT* __restrict__ y, long long ld_y, int rows, int cols, int lane,
                                            GET&& get) {
   if (cols <= 0) return;
@@ -131,11 +140,11 @@ __device__ __forceinline__ void store_rows(OUT* __restrict__ y, long long ld_y, 
 #pragma unroll
     for (int k = 0; k < 8; ++k) v[k] = get(r0 + k * step + sub, col);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) __builtin_nontemporal_store(v[k], to + k * step * ld_y);
+    for (int k = 0; k < 8; ++k) store_as<STREAM>(v[k], to + k * step * ld_y);
   }
 #pragma unroll 1
   for (int row = r0 + sub; row < limit; row += step, to += step * ld_y)
-    __builtin_nontemporal_store(get(row, col), to);
+    store_as<STREAM>(get(row, col), to);
 }
 
 // Wavefront tile = 64 x 64 of Y, workgroup = 2 x 2 wavefronts, stages through registers: for
@@ -1606,7 +1615,8 @@ __device__ __forceinline__ void dma4(const float* gptr, unsigned lds_base) {
                : "memory");
 }
 
-template <typename OUT, int MB>
+// STREAM: how outputs are stored (launch_w4a4_gemm_blocks says when).
+template <typename OUT, int MB, bool STREAM>
 __global__ __launch_bounds__(GEMM_THREADS, (MB == 1 ? 3 : 2)) void k_w4a4_gemm_blocks(
     const uint8_t* __restrict__ Qx, long long ld_q, const float* __restrict__ bscale, long long ld_s,
     int M, int K, int N, const uint8_t* __restrict__ Qw, long long ld_w,
@@ -1803,12 +1813,12 @@ __global__ __launch_bounds__(GEMM_THREADS, (MB == 1 ? 3 : 2)) void k_w4a4_gemm_b
         const int m = m0 + wm * 32 * MB + j * 32 + row;
         const uint8_t* from = mine + row * PITCH + part * 16;
         if (m < M && n_first + part * W < N)
-          __builtin_nontemporal_store(*reinterpret_cast<const v4u*>(from),
-                                      reinterpret_cast<v4u*>(Y + (long long)m * ld_y + n_first + part * W));
+          store_as<STREAM>(*reinterpret_cast<const v4u*>(from),
+                           reinterpret_cast<v4u*>(Y + (long long)m * ld_y + n_first + part * W));
       }
     } else {
       const int m = m0 + wm * 32 * MB + j * 32;
-      store_rows<OUT>(Y + (long long)m * ld_y + n_first, ld_y, M - m, N - n_first, lane, [&](int row, int c) {
+      store_rows<STREAM, OUT>(Y + (long long)m * ld_y + n_first, ld_y, M - m, N - n_first, lane, [&](int row, int c) {
         return *reinterpret_cast<const OUT*>(mine + row * PITCH + c * (int)sizeof(OUT));
       });
     }
@@ -1830,14 +1840,34 @@ hipError_t launch_w4a4_gemm_blocks(const uint8_t* Qx, long long ld_q, const floa
   const int bm = tall ? 128 : 64;
   const int m_tiles = (M + bm - 1) / bm;
   const unsigned grid = (unsigned)((long long)((m_tiles + XCDS - 1) / XCDS) * XCDS * n_tiles);
-#define TDQ_BLK(OUT, MB)                                                                                       \
-  hipLaunchKernelGGL((k_w4a4_gemm_blocks<OUT, MB>), dim3(grid), dim3(GEMM_THREADS), 0, st, Qx, ld_q, bscale, ld_s, \
+  // Streaming stores leave the caches at once.  Rows that start between 64-byte boundaries share those pieces of memory
+  // with the next tile's, which then go out in two parts, and with few stages the outputs of all tiles are under way together
+  // (binary32: four workgroups a CU with 32 KiB each are an XCD's whole L2).  Such calls of many tiles store as usual.
+  // Streamed / as usual, us: binary32 49334 x 224 x 1268 77 / 56, 32611 x 192 x 1519 64 / 47, 70006 x 160 x 3592 297 / 201, 64592
+  // x 96 x 937 90 / 51; binary16 67922 x 23 x 848 36.1 / 23.9.  Of 1359 random binary32 calls (most of them K up to 256, rows
+  // anywhere) 587 change, 0.74 times the time in the geometric mean, 42 of them more than 3 % slower, up to 1.14; of 900
+  // binary16 ones with more than 3000 tiles 94, 0.84, 10, up to 1.13.  Streamed stay rows on 64 bytes (35663 x 252 x 4016 binary32
+  // 149 / 169), one wavefront's columns (as usual 1.03 to 1.1 times), more channels (1.04 to 1.07, 222846 x 224 x 632
+  // by tall tiles 142 / 169; binary16 from 65 on even, from 129 on 1.04), and fewer tiles (even).
+  const bool apart = (reinterpret_cast<uintptr_t>(Y) & 63) == 0 && ld_y * esz % 64 == 0;
+  const long long tiles = (long long)((M + 63) / 64) * n_tiles;
+  const bool stream = apart || N <= 64 ||
+                      (y_dt == TDQ_F32 ? K > (tall ? 160 : 256) || tiles <= 1536 : K > 64 || tiles <= 4096);
+#define TDQ_BLK(OUT, MB, STREAM)                                                                               \
+  hipLaunchKernelGGL((k_w4a4_gemm_blocks<OUT, MB, STREAM>), dim3(grid), dim3(GEMM_THREADS), 0, st, Qx, ld_q, bscale, ld_s, \
                      M, K, N, Qw, ld_w, w_scale, bias, static_cast<OUT*>(Y), ld_y, m_tiles, n_tiles, y_vec_ok)
-  if (y_dt == TDQ_F32) {
-    if (tall) TDQ_BLK(float, 2); else TDQ_BLK(float, 1);
-  } else {
-    if (tall) TDQ_BLK(_Float16, 2); else TDQ_BLK(_Float16, 1);
+#define TDQ_BLK_OUT(OUT)                                                            \
+  if (stream) {                                                                     \
+    if (tall) TDQ_BLK(OUT, 2, true); else TDQ_BLK(OUT, 1, true);                    \
+  } else {                                                                          \
+    if (tall) TDQ_BLK(OUT, 2, false); else TDQ_BLK(OUT, 1, false);                  \
   }
+  if (y_dt == TDQ_F32) {
+    TDQ_BLK_OUT(float)
+  } else {
+    TDQ_BLK_OUT(_Float16)
+  }
+#undef TDQ_BLK_OUT
 #undef TDQ_BLK
   return hipGetLastError();
 }
@@ -2413,7 +2443,7 @@ __global__ __launch_bounds__(BF6_THREADS, 4) void k_w4a4_gemm_blocks_f6(
       }
     } else {
       const int m = m0 + wm * 32 * MT + i * 32, n = n0 + wn * 64;
-      store_rows<OUT>(Y + (long long)m * ld_y + n, ld_y, M - m, N - n, lane,
+      store_rows<true, OUT>(Y + (long long)m * ld_y + n, ld_y, M - m, N - n, lane,
                       [&](int row, int c) { return (OUT)T[row * TP + c]; });
     }
   }
