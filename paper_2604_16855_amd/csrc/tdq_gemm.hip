@@ -469,7 +469,7 @@ __device__ __forceinline__ void dma4s(const float* sbase, unsigned voff, unsigne
 // pointer plus one per-lane 32-bit offset.  wtile = &Y[first row][first column] of the
 // wavefront's part.  EDGE: only the first `rows` of its rows and
 // `cols` of its columns are stored (by masks).
-template <typename OUT, int MT, int NT, typename ACC, bool BIAS, bool EDGE = false>
+template <typename OUT, int MT, int NT, typename ACC, bool BIAS, bool EDGE = false, bool STREAM = true>
 __device__ __forceinline__ void tile_store_fast(ACC (&acc)[MT][NT], const float* sRow,
                                                 const float* sCol, const float* sBias, int lane,
                                                 int wm, int wn, OUT* __restrict__ wtile,
@@ -518,17 +518,17 @@ __device__ __forceinline__ void tile_store_fast(ACC (&acc)[MT][NT], const float*
           for (int j = 0; j < NT; ++j) p[j] = round_pair_to_half(y0[j], y1[j]);
 #pragma unroll
           for (int j = 0; j < NT; ++j)
-            if (in[j] && in0) __builtin_nontemporal_store(p[j][0], row0 + j * 32);
+            if (in[j] && in0) store_as<STREAM>((_Float16)p[j][0], row0 + j * 32);
 #pragma unroll
           for (int j = 0; j < NT; ++j)
-            if (in[j] && in1) __builtin_nontemporal_store(p[j][1], row1 + j * 32);
+            if (in[j] && in1) store_as<STREAM>((_Float16)p[j][1], row1 + j * 32);
         } else {
 #pragma unroll
           for (int j = 0; j < NT; ++j)
-            if (in[j] && in0) store_out<OUT>(row0 + j * 32, y0[j]);
+            if (in[j] && in0) store_as<STREAM>(y0[j], row0 + j * 32);
 #pragma unroll
           for (int j = 0; j < NT; ++j)
-            if (in[j] && in1) store_out<OUT>(row1 + j * 32, y1[j]);
+            if (in[j] && in1) store_as<STREAM>(y1[j], row1 + j * 32);
         }
       }
     }
@@ -637,7 +637,7 @@ __device__ __forceinline__ void tile_store_cols4(v16i (&acc)[4][4], const float*
 
 // Epilogue of the pipelined kernels.  Register r of a 32x32 accumulator fragment held
 // by lane l is element (row 8*(r/4) + 4*(l/32) + r%4, column l%32).
-template <typename OUT, int MT, int NT, typename ACC = v16i>
+template <typename OUT, int MT, int NT, typename ACC = v16i, bool KEEP = false>
 __device__ __forceinline__ void pipe_epilogue(ACC (&acc)[MT][NT], const float* sRow,
                                               const float* sCol, const float* sBias, int lane,
                                               int wm, int wn, int m0, int n0, int M, int N,
@@ -646,14 +646,14 @@ __device__ __forceinline__ void pipe_epilogue(ACC (&acc)[MT][NT], const float* s
   constexpr int BM = 64 * MT;
   const int ccol = lane & 31, rquad = (lane >> 5) * 4;
   // Of a tile at an edge of Y each wavefront decides for itself: nothing of it inside, all of it, a
-  // part of it.
+  // part of it.  KEEP: those of a tile cut in its columns all store by masks, and not past the caches.
   // (The whole tile by the path with two checks per output, and so, us: 12000 x 200 x 1000 binary32 16.9 and 14.3, 5000 x
   // 96 x 2000 binary16 10.6 and 8.8, 20000 x 77 x 333 8.8 and 7.3, 6845 x 333 x 777 binary32 9.9 and 9.2.)
   const int rows = M - (m0 + wm * 32 * MT), cols = N - (n0 + wn * 32 * NT);
   if (rows <= 0 || cols <= 0) return;
   if (!acc_dump && (long long)(BM + 8) * ld_y < (1ll << 31) / (long long)sizeof(OUT)) {
     OUT* wtile = Y + (long long)(m0 + wm * 32 * MT) * ld_y + (n0 + wn * 32 * NT);
-    if (rows >= 32 * MT && cols >= 32 * NT) {
+    if (rows >= 32 * MT && cols >= 32 * NT && (!KEEP || n0 + 64 * NT <= N)) {
       if (bias)
         tile_store_fast<OUT, MT, NT, ACC, true>(acc, sRow, sCol, sBias, lane, wm, wn, wtile, ld_y);
       else
@@ -662,9 +662,9 @@ __device__ __forceinline__ void pipe_epilogue(ACC (&acc)[MT][NT], const float* s
     }
     if constexpr (MT * NT <= 4) {
       if (bias)
-        tile_store_fast<OUT, MT, NT, ACC, true, true>(acc, sRow, sCol, sBias, lane, wm, wn, wtile, ld_y, rows, cols);
+        tile_store_fast<OUT, MT, NT, ACC, true, true, !KEEP>(acc, sRow, sCol, sBias, lane, wm, wn, wtile, ld_y, rows, cols);
       else
-        tile_store_fast<OUT, MT, NT, ACC, false, true>(acc, sRow, sCol, sBias, lane, wm, wn, wtile, ld_y, rows, cols);
+        tile_store_fast<OUT, MT, NT, ACC, false, true, !KEEP>(acc, sRow, sCol, sBias, lane, wm, wn, wtile, ld_y, rows, cols);
       return;
     }
   }
@@ -872,7 +872,8 @@ __global__ __launch_bounds__(GEMM_THREADS, (MT * NT >= 16 ? 1 : 2)) void k_w4a4_
 //     35.2).  That stage stands behind the loop, so that the loop is whole stages only (8192 x 768 x 768 9.9 -> 9.5,
 //     131072 x 1000 x 1024 176 -> 169).
 // ---------------------------------------------------------------------------
-template <typename OUT, int MT, int NT>
+// KEEP: how outputs are stored (launch_ring says when).
+template <typename OUT, int MT, int NT, bool KEEP>
 __global__ __launch_bounds__(GEMM_THREADS, (MT * NT >= 4 ? 2 : MT * NT >= 2 ? 3 : 6)) void k_w4a4_gemm_ring(
     const uint8_t* __restrict__ Qx, long long ld_q, const int* __restrict__ gid,
     const float* __restrict__ scale, int M, int T, int K, int N, int G,
@@ -1012,7 +1013,7 @@ __global__ __launch_bounds__(GEMM_THREADS, (MT * NT >= 4 ? 2 : MT * NT >= 2 ? 3 
     sBias[tid] = my_bs;
   }
   __syncthreads();
-  pipe_epilogue<OUT, MT, NT>(acc, sRow, sCol, sBias, lane, wm, wn, m0, n0, M, N, bias, Y, ld_y, acc_dump);
+  pipe_epilogue<OUT, MT, NT, v16i, KEEP>(acc, sRow, sCol, sBias, lane, wm, wn, m0, n0, M, N, bias, Y, ld_y, acc_dump);
 }
 
 // ---------------------------------------------------------------------------
@@ -1424,9 +1425,21 @@ static void launch_ring(const uint8_t* Qx, long long ld_q, const int* gid, const
   const int stages = ((K + 1) / 2 + BKB - 1) / BKB;
   constexpr int D = 4;
   const size_t lds = (size_t)(stages < D ? stages : D) * (BM + BN) * BKB;
-  hipLaunchKernelGGL((k_w4a4_gemm_ring<OUT, MT, NT>), dim3(grid), dim3(GEMM_THREADS), lds, st, Qx, ld_q,
-                     gid, scale, M, T, K, N, G, Qw, ld_w, w_scale, bias, static_cast<OUT*>(Y), ld_y,
-                     acc_dump, m_tiles, n_tiles);
+  // Streaming stores leave the caches at once.  At rows between 64-byte boundaries the wavefronts of a tile cut in its columns
+  // share pieces of memory with others, which then go out in parts: where the outputs are more than the L2s have room for
+  // beside the operands (24 of 32 MiB) such tiles store as usual.  With two checks per output, which is slow and so spreads
+  // the stores / streamed by masks / as usual by masks, us: 398437 x 136 x 59 binary32 39.3 / 55.2 / 24.0, 291908 x 108 x 63 31.8 /
+  // 41.5 / 18.3.  3400 random calls, as usual over streamed: from 24 to 32 MiB 0.81 times with 33 to 63 outputs, 0.97 with 65 to
+  // 127, beyond 64 MiB 0.51 and 0.6; more outputs 1.00 to 1.03 up to 48 MiB and 0.88 beyond; below 24 MiB 1.00 to 1.08.  (The
+  // choice in the kernel: its code made streamed calls 1.02 to 1.05 times as slow.)
+  const bool keep = N % BN != 0 && ((reinterpret_cast<uintptr_t>(Y) | (uintptr_t)ld_y * sizeof(OUT)) & 63) != 0 &&
+                    (long long)M * N * (int)sizeof(OUT) > (N < 64 ? 20ll : N < 128 ? 24ll : 48ll) << 20;
+#define TDQ_RING(KEEP)                                                                                          \
+  hipLaunchKernelGGL((k_w4a4_gemm_ring<OUT, MT, NT, KEEP>), dim3(grid), dim3(GEMM_THREADS), lds, st, Qx, ld_q,  \
+                     gid, scale, M, T, K, N, G, Qw, ld_w, w_scale, bias, static_cast<OUT*>(Y), ld_y, acc_dump,  \
+                     m_tiles, n_tiles)
+  if (keep) TDQ_RING(true); else TDQ_RING(false);
+#undef TDQ_RING
 }
 
 template <typename OUT, int MT, int NT>
