@@ -227,10 +227,10 @@ static int whole_extra_f32(int B, int T, int C, int G, bool two_ranks) {
   if (extra > 512 / B - G) extra = 512 / B - G;
   if (extra > 256) extra = 256;
   if (e > 65536 * (extra + 1)) return -1;
-  // A sixteenth of the slots stays free, for kernels of calls on other streams: [8, 1024, 768] with 16 sets on one and on
-  // eight streams, a call, by the chain 46.8 and 21.5, by 512 workgroups 34.3 and 28.7, by 480 34.8 and 25.3, by 384 37.9
-  // and 22.6; [4, 4096, 768] 90.4 and 46.8, 55.4 and 50.8, 53.3 and 47.6.
-  if (extra > 480 / B - G) extra = 480 / B - G;
+  // One slot in 32 stays free, for kernels of calls on other streams, which costs a call alone nothing: [8, 1024, 768] with 16
+  // sets on one and on eight streams, a call, by the chain 46.8 and 21.5, by 512 workgroups 33.0 and 29.0, by 496 32.8 and
+  // 27.4, by 480 33.8 and 26.4; [4, 4096, 768] 90.4 and 46.8, 54.5 and 53.2, 52.8 and 51.5, 53.2 and 49.9.
+  if (extra > 496 / B - G) extra = 496 / B - G;
   // No more than 64 beyond the first for a set, which all meet in the same words and each read all of its tokens' ranges: with
   // two sets and up to 256, 128 of them, and by the chain [2, 6434, 487] 122 / 72 / 88, [2, 2170, 1624] 79 / 52 / 61, [3,
   // 2342, 1165] on a grid 96 / 83 / 85, [1, 3828, 2193] 92 / 97 / 90.
